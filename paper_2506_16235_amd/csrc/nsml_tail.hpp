@@ -1066,13 +1066,15 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uin
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence();                             /* write the L2 back: visible to the other dies */
+        __builtin_amdgcn_s_waitcnt(0);               /* ... before the arrival is: the compiler, which sees no access in flight here, leaves the fence's own wait out */
         __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const unsigned long long t0 = wall_clock64();
         while (__hip_atomic_load(bar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
             __builtin_amdgcn_s_sleep(32);
             if (wall_clock64() - t0 > HARD_SPIN_TICKS) { err[0] = 1u; break; }
         }
-        __threadfence();                             /* and nothing stale is read afterwards */
+        __threadfence();                             /* and nothing stale is read afterwards, by the other wavefronts either */
+        __builtin_amdgcn_s_waitcnt(0);
     }
     __syncthreads();
 }
