@@ -163,18 +163,12 @@ int nsml_destroy(nsml_ctx *ctx);
  * best; results are identical for every setting (the tests run the path under each of them).
  * Takes effect from the next call; waits for nothing.  NSML_EINVAL for an unknown name or a value
  * outside the listed range.
- *   "span_tiles"   tiles of 4096 elements per workgroup of the streaming kernels: 1..16, 0 = by
- *                  gradient size
- *   "seg_waves"    wavefronts per workgroup of the streaming pass (4, 8 or 16), 0 = by span size
- *   "persist"      workgroups per compute unit of the streaming pass, each taking a contiguous
- *                  share of the spans: 1..8, 0 (default) = one workgroup per span
- *   "decomp_variant"  decompress: 1 = one wavefront per tile with direct stores, 0 = tiles assembled
- *                  in LDS, -1 (default) = by gradient size and survivors per tile
+ *   "span_tiles" (0..16), "seg_waves" (0, 4, 8, 16), "persist" (0..8), "nt" (1, 3, 5, 7), "nt_dense"
+ *                  (-1..1)  accepted, without effect: the streaming kernels have one geometry
+ *   "decomp_variant"  decompress: 1 = zeros, then the survivors stored over them, 0 = tiles assembled
+ *                  in LDS, -1 (default) = by the share of survivors
  *   "force_dense"  1: decide every bucket by the dense passes over the accumulator (the path a
  *                  bucket takes when its staged elements cannot decide it), 0: default
- *   "nt"           bit mask of non-temporal hints in the streaming pass (1 grad loads, 2 residual
- *                  loads, 4 accumulator stores); default 7
- *   "nt_dense"     non-temporal stores of the dense output of decompress: 1, 0, -1 = by variant
  *   "rescan"       diagnostic: 1 makes the threshold search read the undecided keys from the
  *                  staged entries again (the path taken when a staging segment has no room left
  *                  for its copy of them), 0: default

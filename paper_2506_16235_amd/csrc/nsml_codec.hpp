@@ -314,295 +314,182 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
     if (i + 1 == tiles_b) tsb[tiles_b] = kb;
 }
 
-/* Dense output for a span of tiles, the variant for gradients of up to a few hundred million
- * elements and for any gradient whose tiles hold many survivors (256 threads): each tile is
- * assembled in LDS (zeros, then the decoded survivors that fall inside it, found through the
- * tile-start table) and written out once with aligned 16-byte stores, so no output line is
- * touched twice and no atomics are needed.  The loads of the next tile's first survivors are
- * issued before the current tile is written out; a very crowded tile is read four consecutive
- * survivors per thread and load.  A bucket of which every element was sent needs neither LDS
- * nor its index list: its output is the decoded value stream. */
-template <int BITS, bool NTS>
-__global__ __launch_bounds__(WG) void k_decomp_lds(const uint32_t *__restrict__ idx, const void *__restrict__ val,
-                                               const float *__restrict__ scales, Tables t,
-                                               const uint32_t *__restrict__ ts, float *__restrict__ dense)
+/* Four consecutive values j0 .. j0 + 3 of a bucket's value stream, decoded; 8- and 32-bit ones in one
+ * load (the stream of a bucket starts at any byte, so the address is not aligned; global loads need
+ * not be). */
+template <int BITS>
+__device__ __forceinline__ void decode4(const uint8_t *__restrict__ vb, const float *__restrict__ sc, uint64_t j0,
+                                        uint32_t chunk, uint32_t chunkSh, float (&x)[4])
 {
-    __shared__ float tile[TILE];
-    __shared__ uint32_t sts[MAX_SPAN_TILES + 1];
+    if (BITS == 32) {
+        f4 v;
+        __builtin_memcpy(&v, vb + 4 * j0, 16);
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else if (BITS == 8) {
+        uint32_t w4;
+        __builtin_memcpy(&w4, vb + j0, 4);
+        const uint64_t c0 = chunkSh < 64u ? (j0 >> chunkSh) : j0 / chunk;
+        const uint64_t c3 = chunkSh < 64u ? ((j0 + 3) >> chunkSh) : (j0 + 3) / chunk;
+        const float s0 = sc[c0], s3 = c3 == c0 ? s0 : sc[c3];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint64_t cj = chunkSh < 64u ? ((j0 + j) >> chunkSh) : (j0 + j) / chunk;
+            x[j] = __fmul_rn((float)(int)(int8_t)(w4 >> (8 * j)), cj == c0 ? s0 : s3);
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = decode<BITS>(vb, sc, j0 + j, chunk, chunkSh);
+    }
+}
+
+/* Dense output, a tile per workgroup: every output line is written once.  An empty tile is zeros at
+ * once.  Otherwise the tile is assembled in LDS (zeros, then the decoded survivors that fall inside it,
+ * found through the tile-start table).  A bucket of which every element was sent needs neither LDS nor its
+ * index list: its output is the decoded value stream.  Bound by the 4 bytes per element written; the
+ * chain tile -> survivors' place -> survivors -> LDS is four memory round trips long, so a compute unit
+ * has to hold many tiles: 16 workgroups of two wavefronts with four stores per thread (419 M elements at
+ * ratio 0.01: 330 us; four workgroups of eight wavefronts 570, eight of four 430, one wavefront per
+ * tile 326, but 832 against 605 at ratio 0.5).  MAP: type of the tile -> bucket table (16 bits for the
+ * entry point without a context). */
+constexpr int DTH = 128;
+template <int BITS, typename MAP, bool NT>
+__global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ idx, const void *__restrict__ val,
+                                                   const float *__restrict__ scales, Tables t, const MAP *__restrict__ tile_b,
+                                                   const uint32_t *__restrict__ ts, float *__restrict__ dense)
+{
+    constexpr int U = TILE / (4 * DTH);          /* 16-byte stores per thread */
+    constexpr int S = TILE / DTH < 8 ? TILE / DTH : 8;      /* survivors a thread has in flight */
+    __shared__ float slots[TILE];
+    const uint32_t tile = xcd_tile(blockIdx.x);
+    if (tile >= t.n_tiles) return;
     const uint32_t tid = threadIdx.x;
-    const SpanGeo s = span_geo(t, blockIdx.x);
-    const uint32_t kb = t.k[s.b];
-    const uint32_t *ib = idx + t.P[s.b];
-    const uint8_t *vb = reinterpret_cast<const uint8_t *>(val) + t.V[s.b];
-    const float *sb = BITS <= 8 ? scales + t.S[s.b] : nullptr;
-    const uint32_t nb = (uint32_t)(s.hi - s.lo);
-    const uint32_t first = s.tile_g - t.tile0[s.b];
+    const uint32_t b = tile_b[tile];
+    const TileGeo s = tile_geo(t, b, tile);
+    const uint32_t kb = t.k[b], nb = (uint32_t)(s.hi - s.lo);
+    const uint32_t *ib = idx + t.P[b];
+    const uint8_t *vb = reinterpret_cast<const uint8_t *>(val) + t.V[b];
+    const float *sb = BITS <= 8 ? scales + t.S[b] : nullptr;
+    f4 out[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) out[u] = f4{0.f, 0.f, 0.f, 0.f};
     if (kb == nb) {
         /* every element of the bucket was sent (ratio 1, or a bucket of one element): survivor j is
-         * element j, so the index list (which can only be 0 .. n_b - 1) is not read and the
-         * output is a plain decode of the value stream */
-        for (uint32_t ti = 0; ti < s.ntiles; ++ti) {
-            const uint64_t tb = s.base + (uint64_t)ti * TILE;
+         * element j, so the index list (which can only be 0 .. n_b - 1) is not read */
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint64_t gi = tb + (uint64_t)(u * WG + tid) * 4;
-                float x[4];
-                if ((BITS == 8 || BITS == 32) && gi >= s.lo && gi + 4 <= s.hi) {
-                    /* four consecutive values in one load (the value stream of a bucket starts at
-                     * any byte, so the address is not aligned; global loads need not be) */
-                    const uint64_t j0 = gi - s.lo;
-                    if (BITS == 32) {
-                        f4 v;
-                        __builtin_memcpy(&v, vb + 4 * j0, 16);
-                        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
-                    } else {
-                        uint32_t w4;
-                        __builtin_memcpy(&w4, vb + j0, 4);
-                        const uint64_t c0 = t.chunkSh < 64u ? (j0 >> t.chunkSh) : j0 / t.chunk;
-                        const uint64_t c3 = t.chunkSh < 64u ? ((j0 + 3) >> t.chunkSh) : (j0 + 3) / t.chunk;
-                        const float s0 = sb[c0], s3 = c3 == c0 ? s0 : sb[c3];
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const int q = (int)(int8_t)(w4 >> (8 * j));
-                            const uint64_t cj = t.chunkSh < 64u ? ((j0 + j) >> t.chunkSh) : (j0 + j) / t.chunk;
-                            x[j] = __fmul_rn((float)q, cj == c0 ? s0 : s3);
-                        }
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        x[j] = (gi + j >= s.lo && gi + j < s.hi) ? decode<BITS>(vb, sb, gi + j - s.lo, t.chunk, t.chunkSh) : 0.0f;
-                }
-                if (gi >= s.lo && gi + 4 <= s.hi) {
-                    const f4 v = {x[0], x[1], x[2], x[3]};
-                    if (NTS) __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(dense + gi));
-                    else *reinterpret_cast<f4 *>(dense + gi) = v;
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (gi + j >= s.lo && gi + j < s.hi) dense[gi + j] = x[j];
-                }
-            }
-        }
-        return;
-    }
-    if (tid <= s.ntiles) sts[tid] = min(ts[t.tile0[s.b] + s.b + first + tid], kb);
-    __syncthreads();
-
-    /* survivor number j0 + tid of a tile, if it exists: local index and decoded value */
-    uint32_t p_li = NONE;
-    float p_x = 0.0f;
-    auto fetch = [&](uint32_t ti) {
-        p_li = NONE;
-        if (ti < s.ntiles) {
-            const uint32_t j0 = sts[ti], j1 = sts[ti + 1];
-            const uint64_t j = (uint64_t)j0 + tid;
-            if (j < j1) { p_li = ib[j]; p_x = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh); }
-        }
-    };
-    fetch(0);
-    for (uint32_t ti = 0; ti < s.ntiles; ++ti) {
-        const uint64_t tb = s.base + (uint64_t)ti * TILE;
-        const uint64_t shift = s.lo - tb;                   /* slot = local index + lo - tb (mod 2^64) */
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            *reinterpret_cast<f4 *>(&tile[(u * WG + tid) * 4]) = f4{0.f, 0.f, 0.f, 0.f};
-        __syncthreads();
-        if (p_li < nb) {
-            const uint64_t slot = (uint64_t)p_li + shift;
-            if (slot < TILE) tile[slot] = p_x;
-        }
-        /* more than 256 survivors in the tile (ratio above 6 %): a thread takes four consecutive
-         * ones at a time, indices and codes each in one load (the addresses are not aligned; global
-         * loads need not be), two such groups in flight; the last few of a tile one by one */
-        const uint32_t j0 = sts[ti], j1 = sts[ti + 1];
-        const uint64_t jA = (uint64_t)j0 + WG;
-        /* (groups of four only when there is at least one for every thread: otherwise a survivor per thread keeps more of them busy) */
-        const uint64_t ngrp = j1 >= jA + 4 * WG ? (j1 - jA) / 4 : 0;      /* whole groups of four */
-        for (uint64_t g0 = 0; g0 < ngrp; g0 += 2 * WG) {
-            uint32_t li4[2][4];
-            float x4[2][4];
-#pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                const uint64_t g = g0 + (uint64_t)v * WG + tid;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) { li4[v][u] = NONE; x4[v][u] = 0.0f; }
-                if (g < ngrp) {
-                    const uint64_t j = jA + 4 * g;
-                    uint4 iv;
-                    __builtin_memcpy(&iv, ib + j, 16);
-                    li4[v][0] = iv.x; li4[v][1] = iv.y; li4[v][2] = iv.z; li4[v][3] = iv.w;
-                    if (BITS == 8) {
-                        uint32_t w4;
-                        __builtin_memcpy(&w4, vb + j, 4);
-                        const uint64_t c0 = t.chunkSh < 64u ? (j >> t.chunkSh) : j / t.chunk;
-                        const uint64_t c3 = t.chunkSh < 64u ? ((j + 3) >> t.chunkSh) : (j + 3) / t.chunk;
-                        const float s0 = sb[c0], s3 = c3 == c0 ? s0 : sb[c3];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const uint64_t cu = t.chunkSh < 64u ? ((j + u) >> t.chunkSh) : (j + u) / t.chunk;
-                            x4[v][u] = __fmul_rn((float)(int)(int8_t)(w4 >> (8 * u)), cu == c0 ? s0 : s3);
-                        }
-                    } else if (BITS == 32) {
-                        f4 fv;
-                        __builtin_memcpy(&fv, vb + 4 * j, 16);
-                        x4[v][0] = fv.x; x4[v][1] = fv.y; x4[v][2] = fv.z; x4[v][3] = fv.w;
-                    } else {
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) x4[v][u] = decode<BITS>(vb, sb, j + u, t.chunk, t.chunkSh);
-                    }
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint64_t slot = (uint64_t)li4[v][u] + shift;
-                    if (li4[v][u] < nb && slot < TILE) tile[slot] = x4[v][u];
-                }
-        }
-        /* what is left (at most three after the groups; everything beyond the first 256 of a less crowded tile) */
-        for (uint64_t jb = jA + 4 * ngrp; jb < j1; jb += 4 * WG) {
-            uint32_t li1[4];
-            float x1[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint64_t j = jb + (uint64_t)u * WG + tid;
-                li1[u] = NONE;
-                x1[u] = 0.0f;
-                if (j < j1) { li1[u] = ib[j]; x1[u] = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh); }
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint64_t slot = (uint64_t)li1[u] + shift;
-                if (li1[u] < nb && slot < TILE) tile[slot] = x1[u];
-            }
-        }
-        fetch(ti + 1);
-        __syncthreads();
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t sl = (u * WG + tid) * 4;
-            const uint64_t gi = tb + sl;
+        for (int u = 0; u < U; ++u) {
+            const uint64_t gi = s.base + (u * DTH + tid) * 4u;
+            float x[4];
             if (gi >= s.lo && gi + 4 <= s.hi) {
-                const f4 v = *reinterpret_cast<const f4 *>(&tile[sl]);
-                if (NTS) __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(dense + gi));
-                else *reinterpret_cast<f4 *>(dense + gi) = v;
+                decode4<BITS>(vb, sb, gi - s.lo, t.chunk, t.chunkSh, x);
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (gi + j >= s.lo && gi + j < s.hi) dense[gi + j] = tile[sl + j];
+                    x[j] = (gi + j >= s.lo && gi + j < s.hi) ? decode<BITS>(vb, sb, gi + j - s.lo, t.chunk, t.chunkSh) : 0.0f;
             }
+            out[u] = f4{x[0], x[1], x[2], x[3]};
         }
-    }
-}
-
-/* Dense output for a span of tiles, the variant for the largest gradients: one wavefront per
- * tile, 16 wavefronts per workgroup (one span of 16 tiles, two of 8, ...).  A wavefront
- * first fetches its tile's survivors (found through the tile-start table), then writes the
- * tile's 16 KiB of zeros with aligned 16-byte stores, one contiguous KiB per instruction, waits
- * for those stores, and drops the decoded survivors into place.  Both writes to a survivor's
- * line meet in the cache, so the memory sees each output line once; no LDS, no atomics.  (The
- * wait is what orders the two stores to one address: they come from different lanes.) */
-template <int BITS, bool NTS>
-__global__ __launch_bounds__(64 * MAX_SEG_WAVES) void k_decomp(const uint32_t *__restrict__ idx, const void *__restrict__ val,
-                                                               const float *__restrict__ scales, Tables t,
-                                                               const uint32_t *__restrict__ ts, float *__restrict__ dense)
-{
-    constexpr int U = 2;                     /* survivors per lane fetched ahead of the zeros */
-    /* a workgroup of 16 wavefronts takes as many whole spans as it has a wavefront per tile for */
-    const uint32_t tid = threadIdx.x, lane = tid & 63;
-    const uint32_t per_wg = max(1u, (uint32_t)MAX_SEG_WAVES / t.spanT);
-    const uint32_t sub = (tid >> 6) / t.spanT;
-    const uint32_t span = blockIdx.x * per_wg + min(sub, per_wg - 1u);
-    const uint32_t wave = (tid >> 6) - min(sub, per_wg - 1u) * t.spanT;       /* wavefront within its span */
-    const uint32_t n_waves = per_wg > 1u ? t.spanT : (uint32_t)(blockDim.x >> 6);
-    if (span >= t.n_spans || (per_wg > 1u && sub >= per_wg)) return;
-    const SpanGeo s = span_geo(t, span);
-    const uint32_t kb = t.k[s.b];
-    const uint32_t *ib = idx + t.P[s.b];
-    const uint8_t *vb = reinterpret_cast<const uint8_t *>(val) + t.V[s.b];
-    const float *sb = BITS <= 8 ? scales + t.S[s.b] : nullptr;
-    const uint32_t nb = (uint32_t)(s.hi - s.lo);
-    const uint32_t *tsb = ts + t.tile0[s.b] + s.b + (s.tile_g - t.tile0[s.b]);
-    const f4 z = {0.f, 0.f, 0.f, 0.f};
-    for (uint32_t ti = wave; ti < s.ntiles; ti += n_waves) {
-        const uint64_t tb = s.base + (uint64_t)ti * TILE;
-        const uint64_t shift = s.lo - tb;                   /* slot in the tile = local index + lo - tb (mod 2^64) */
-        const uint32_t j0 = min(tsb[ti], kb), j1 = min(tsb[ti + 1], kb);
-        uint32_t p_li[U];
-        float p_x[U];
+    } else {
+        const uint32_t j0 = min(ts[tile + b], kb), j1 = min(ts[tile + b + 1], kb);
+        if (j0 < j1) {                                   /* same for the whole workgroup */
+            const uint64_t shift = s.lo - s.base;        /* slot = local index + lo - base */
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint64_t j = (uint64_t)j0 + lane + 64u * u;
-            p_li[u] = NONE;
-            p_x[u] = 0.0f;
-            if (j < j1) { p_li[u] = ib[j]; p_x[u] = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh); }
-        }
-        if (tb >= s.lo && tb + TILE <= s.hi) {
+            for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(&slots[(u * DTH + tid) * 4]) = out[u];
+            __syncthreads();
+            for (uint64_t jb = j0; jb < j1; jb += S * DTH) {
+                uint32_t li[S];
+                float x[S];
 #pragma unroll
-            for (int u = 0; u < TILE / 256; ++u) {
-                f4 *a = reinterpret_cast<f4 *>(dense + tb + (uint64_t)(u * 64 + lane) * 4);
-                if (NTS) __builtin_nontemporal_store(z, a);
-                else *a = z;
-            }
-        } else {
-            for (int u = 0; u < TILE / 256; ++u) {
-                const uint64_t gi = tb + (uint64_t)(u * 64 + lane) * 4;
-                if (gi >= s.lo && gi + 4 <= s.hi) {
-                    *reinterpret_cast<f4 *>(dense + gi) = z;
-                } else {
+                for (int u = 0; u < S; ++u) {
+                    const uint64_t j = jb + (uint64_t)u * DTH + tid;
+                    li[u] = NONE;
+                    x[u] = 0.0f;
+                    if (j < j1) { li[u] = ib[j]; x[u] = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh); }
+                }
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (gi + j >= s.lo && gi + j < s.hi) dense[gi + j] = 0.0f;
+                for (int u = 0; u < S; ++u) {
+                    /* an index outside the bucket or outside this tile (invalid payload) is dropped */
+                    const uint64_t slot = (uint64_t)li[u] + shift;
+                    if (li[u] < nb && slot < TILE) slots[slot] = x[u];
                 }
             }
-        }
-        /* the zeros must have landed before a survivor is stored over one of them */
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-        __builtin_amdgcn_s_waitcnt(0);
-        __builtin_amdgcn_wave_barrier();
+            __syncthreads();
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            /* an index outside the bucket or outside this tile (invalid payload) is dropped */
-            const uint64_t slot = (uint64_t)p_li[u] + shift;
-            if (p_li[u] < nb && slot < TILE) dense[s.lo + p_li[u]] = p_x[u];
+            for (int u = 0; u < U; ++u) out[u] = *reinterpret_cast<const f4 *>(&slots[(u * DTH + tid) * 4]);
         }
-        for (uint64_t j = (uint64_t)j0 + 64u * U + lane; j < j1; j += 64) {
-            const uint32_t li = ib[j];
-            const uint64_t slot = (uint64_t)li + shift;
-            if (li < nb && slot < TILE) dense[s.lo + li] = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t gi = s.base + (u * DTH + tid) * 4u;
+        if (gi >= s.lo && gi + 4 <= s.hi) {
+            st_out<NT>(reinterpret_cast<f4 *>(dense + gi), out[u]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (gi + j >= s.lo && gi + j < s.hi) dense[gi + j] = out[u][j];
         }
     }
 }
 
-/* Receiver side of an all-gather of payloads: add one worker's decoded survivors into a dense
- * gradient that is being accumulated (nothing else is touched).  One thread per survivor;
- * the indices of a payload are distinct, so plain read-modify-write needs no atomics. */
-template <int BITS>
-__global__ __launch_bounds__(WG) void k_decomp_acc(const uint32_t *__restrict__ idx, const void *__restrict__ val,
-                                                   const float *__restrict__ scales, Tables t, uint64_t K,
-                                                   float *__restrict__ dense)
+/* Zeros, for the dense output that few survivors are then stored into: 16 bytes per thread in the
+ * streaming kernels' order (7.1 TB/s on 6.7 GB; a kilobyte per thread group further apart 5.9). */
+constexpr uint32_t ZERO_T = 1024;
+template <bool NT>
+__global__ __launch_bounds__(ZERO_T, 8) void k_zero(float *__restrict__ dense, uint64_t n)
+{
+    const uint64_t i = (uint64_t)xcd_tile(blockIdx.x) * (ZERO_T * 4u) + threadIdx.x * 4u;
+    if (i + 4 <= n) st_out<NT>(reinterpret_cast<f4 *>(dense + i), f4{0.f, 0.f, 0.f, 0.f});
+    else for (uint64_t j = i; j < n; ++j) dense[j] = 0.0f;
+}
+
+/* One payload's decoded survivors stored into a dense gradient of zeros, or (ADD) added into one that
+ * is being accumulated (the receiver side of an all-gather of payloads); nothing else is touched.
+ * The indices of a payload are distinct, so plain read-modify-write needs no atomics.  Bound by the
+ * partly written lines; what helps is that the lines in flight lie close together: a wavefront's
+ * 64 survivors are consecutive (four consecutive ones per thread: 53 us for 1.1 M survivors of 109 M
+ * elements against 41).  NT: non-temporal stores, for adding into an array larger than the caches. */
+constexpr uint32_t SCAT_PER = 1;
+template <int BITS, bool ADD, bool NT>
+__global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx, const void *__restrict__ val,
+                                                const float *__restrict__ scales, Tables t, uint64_t K,
+                                                float *__restrict__ dense)
 {
     constexpr uint32_t LDS_B = 2047;
     __shared__ uint64_t sP[LDS_B + 1];
     const bool in_lds = t.B <= LDS_B;
+    const uint64_t j0 = (uint64_t)blockIdx.x * (WG * SCAT_PER) + threadIdx.x;
+    /* the indices do not need the bucket: fetched while it is searched for */
+    uint32_t li[SCAT_PER];
+#pragma unroll
+    for (uint32_t u = 0; u < SCAT_PER; ++u) li[u] = j0 + u * WG < K ? idx[j0 + u * WG] : NONE;
     if (in_lds) {
         for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
         __syncthreads();
     }
-    const uint64_t stride = (uint64_t)gridDim.x * WG;
-    for (uint64_t j = (uint64_t)blockIdx.x * WG + threadIdx.x; j < K; j += stride) {
-        const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
-        const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
-        const uint64_t jj = j - t.P[b];
-        const uint32_t li = idx[j];
-        if (li >= nb) continue;                       /* invalid payload: never leave the bucket */
-        const uint8_t *vb = reinterpret_cast<const uint8_t *>(val) + t.V[b];
-        const float *sb = BITS <= 8 ? scales + t.S[b] : nullptr;
-        const float x = decode<BITS>(vb, sb, jj, t.chunk, t.chunkSh);
-        dense[lo + li] = __fadd_rn(dense[lo + li], x);
+    float x[SCAT_PER], y[SCAT_PER];
+    float *at[SCAT_PER];
+#pragma unroll
+    for (uint32_t u = 0; u < SCAT_PER; ++u) {
+        const uint64_t j = j0 + u * WG;
+        at[u] = nullptr;
+        x[u] = y[u] = 0.0f;
+        if (j < K) {
+            const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
+            const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
+            if (li[u] < nb) {                         /* invalid payload: never leave the bucket */
+                at[u] = dense + lo + li[u];
+                if (ADD) y[u] = *at[u];
+                x[u] = decode<BITS>(reinterpret_cast<const uint8_t *>(val) + t.V[b], BITS <= 8 ? scales + t.S[b] : nullptr,
+                                    j - t.P[b], t.chunk, t.chunkSh);
+            }
+        }
     }
+#pragma unroll
+    for (uint32_t u = 0; u < SCAT_PER; ++u)
+        if (at[u]) {
+            const float v = ADD ? __fadd_rn(y[u], x[u]) : x[u];
+            if (NT) __builtin_nontemporal_store(v, at[u]);
+            else *at[u] = v;
+        }
 }
 
 }  // namespace

@@ -8,18 +8,36 @@
 namespace {
 
 constexpr int WG = 256;
-constexpr int TILE = 4096;        /* elements per tile */
-constexpr int WTILE = 1024;       /* elements one wavefront covers per iteration in ef_emit */
+/* Elements per tile: one tile is one workgroup of the streaming kernels (512 threads, one 16-byte
+ * access per thread and operand, then the workgroup ends) and one staging segment.  What bounds
+ * these kernels is how close together the accesses in flight are: `b = a + b` over 3 x 6.7 GB runs at
+ * 5.5 - 5.9 TB/s when every wavefront walks 4 - 16 KiB of its own and at 6.4 - 6.6 TB/s when the
+ * workgroups in flight cover one moving window, each with a few KiB of it (256 threads x 1 access
+ * 6.35, 512 x 1 6.4, 1024 x 1 6.4, 512 x 4 5.7; a grid that loops over tiles 4.3 - 5.5). */
+constexpr int TILE = 2048;
+constexpr int STH = TILE / 4;     /* threads of a streaming workgroup */
+constexpr int WTILE = 1024;       /* elements one wavefront covers per iteration in the passes over the dense accumulator */
+constexpr uint32_t XCD_RUN = 16;  /* consecutive tiles per die, see xcd_tile */
+constexpr uint32_t SEG_CAP = TILE / 4;      /* staging entries per tile: a quarter of its elements */
 constexpr int NB0 = 4096, NB1 = 4096, NB2 = 128;
-constexpr int SUB_DIGITS = 4, SUB_BITS = 6, NBS = SUB_DIGITS << SUB_BITS;   /* finer histogram of a few level-0 digits: 64 bins each */
-constexpr int SHS = 19 - SUB_BITS;   /* key >> SHS : level-0 digit and the 6 bits below it */
+constexpr int NHB = 1024;         /* bins of the window of keys in which the threshold is expected */
+constexpr uint32_t NHC = 8;       /* copies of a bucket's bins, one per die's share of the workgroups: with one copy the streaming pass
+                                   * waits for its own updates (2.4 % staged: 1.14 ms on 419 M elements, 0.83 with eight) */
 constexpr int SH0 = 19;   /* key >> 19         : level-0 digit (sign-less exponent + 4 mantissa bits) */
 constexpr int SH1 = 7;    /* (key >> 7) & 4095 : level-1 digit;  key & 127 : level-2 digit */
-constexpr int MAX_SPAN_TILES = 16;
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t SAMPLE_ALL_BELOW = 262144;  /* buckets smaller than this are sampled in full */
-constexpr uint32_t SAMPLE_STRIDE = 64;         /* larger ones: 32 elements out of every 2048 */
-constexpr uint32_t RUNS_PER_WG = 128;          /* sample runs (32 elements each) per workgroup */
+constexpr uint32_t SAMPLE_STRIDE = 64;         /* of larger ones at most every 64th element, */
+constexpr uint32_t SAMPLE_ELEMS = 131072;      /* and at most about so many: the margins they leave (a third more staged than sent at
+                                               * ratio 0.001) cost less than reading more (1/64 of 1.7 G elements: 95 us, this: 70) */
+constexpr uint32_t SAMPLE_RUN = 16;            /* elements per sampled run: one 64-byte access */
+constexpr uint32_t RUNS_PER_WG = 256;          /* sample runs per workgroup */
+/* one run in so many is sampled */
+__host__ __device__ inline uint64_t sample_stride(uint64_t nb)
+{
+    const uint64_t s = nb / SAMPLE_ELEMS;
+    return nb < SAMPLE_ALL_BELOW ? 1u : s < SAMPLE_STRIDE ? SAMPLE_STRIDE : s;
+}
 
 /* Diagnostic: why the plan sent a bucket to the dense passes (bits; 0 when it did not). */
 enum Why : uint32_t { WHY_NO_GUESS = 1, WHY_OVERFLOW = 2, WHY_TOO_FEW = 4, WHY_NO_ROOM = 8, WHY_OUTSIDE_BAND = 16, WHY_NONZEROS = 32 };
@@ -33,69 +51,84 @@ enum Path : uint32_t {
 };
 
 enum KernelId {
-    KID_SETUP = 0, KID_SPANMAP, KID_CLEAR, KID_SAMPLE, KID_PREDICT, KID_EF_EMIT, KID_PLAN,
+    KID_SETUP = 0, KID_TILEMAP, KID_CLEAR, KID_SAMPLE, KID_PREDICT, KID_EF_EMIT, KID_PLAN,
     KID_SELECT, KID_FINISH, KID_ENCODE, KID_HARD, KID_QUANT,
     KID_TILESTART, KID_DECOMP, KID_DECOMP_ACC,
-    KID_WHIST, KID_WPLAN, KID_WMASK, KID_WHARD, KID_N
+    KID_WHIST, KID_WPLAN, KID_WMASK, KID_WHARD, KID_BINS, KID_N
 };
 const char *const kKernelNames[KID_N] = {
     "setup", "spanmap", "clear", "sample", "predict", "ef_emit", "plan",
     "select_count", "select_finish", "encode", "hard", "quant",
     "tilestart", "decomp", "decomp_acc",
-    "whist", "wplan", "wmask", "whard"
+    "whist", "wplan", "wmask", "whard", "bins"
 };
 static_assert(KID_N <= NSML_MAX_KERNELS, "raise NSML_MAX_KERNELS");
+
+/* What the streaming pass does with a bucket's keys (k_predict / k_wpredict):
+ *   x  L    the elements with L <= key < y are staged (NONE: none)
+ *   y  H    NONE: no upper bound (everything from L up is staged: "candidates"); else a band is staged.
+ *           L == H == 1: nothing is staged, non-zero and zero keys are counted per tile
+ *   z  W    top of the window: the elements with key >= W are counted per tile, the staged ones below W
+ *           in NHB bins; == H when H is not NONE
+ *   w  s    bin of a key in [L, W): ((W - 1) >> s) - (key >> s), the last bin taking everything below it */
+typedef uint4 KeyPar;
 
 /* Device-resident tables.  Layout part: fixed by the bucket offsets.  Call part: fixed by
  * (ratio, bits).  State part: rewritten by every compress call. */
 struct Tables {
     const uint64_t *off;     /* B+1 bucket offsets */
     const uint32_t *tile0;   /* B+1 prefix of tile counts */
-    const uint32_t *span0;   /* B+1 prefix of span counts */
     const uint32_t *samp0;   /* B+1 prefix of sample workgroups */
-    const uint32_t *span_b;  /* n_spans: bucket of each span */
+    const uint32_t *tile_b;  /* n_tiles: bucket of each tile */
+    const uint4 *desc;       /* n_tiles: x, y: global element index of the tile's first slot (a multiple of 4), z: bucket,
+                              * w: first and one past the last slot that belong to the bucket (low / high half) */
     uint32_t *k;             /* B   survivors per bucket */
     uint64_t *P;             /* B+1 prefix of k */
     uint64_t *V;             /* B+1 prefix of value bytes */
     uint64_t *S;             /* B+1 prefix of scale counts */
     uint64_t *C;             /* B+1 prefix of chunk counts (all widths) */
-    uint32_t *T;             /* B   threshold key, refined level by level */
-    uint32_t *need;          /* B   how many more to take at the current level */
-    uint32_t *L;             /* B   the streaming pass stages the elements with L <= key < H (L = NONE: none) */
-    uint32_t *H;             /* B   NONE: no upper bound (everything from L up is staged: "candidates");
-                              *     else a band is staged and the elements with key >= H are counted per segment.
-                              *     L == H == 1: nothing is staged, non-zero and zero keys are counted per segment */
-    uint32_t *fast;          /* B   how the bucket is decided (PATH_*); the weight stage uses 0 / 1 only */
-    uint32_t *subLo;         /* B   first of the SUB_DIGITS level-0 digits whose next 6 key bits the streaming pass
-                              *     also counts (NONE: none) */
-    uint32_t *sh;            /* B   T holds the key bits from this position up (19: the level-0 digit only; 13: six more) */
+    uint32_t *T;             /* B   threshold key, refined step by step */
+    uint32_t *need;          /* B   how many more to take at the current step */
+    KeyPar *par;             /* B   what the streaming pass stages and counts */
+    uint32_t *fast;          /* B   how the bucket is decided (PATH_*) */
+    uint32_t *sh;            /* B   T holds the key bits from this position up */
     uint32_t *margin;        /* B   what the bucket has learned about its sample: factor on k_predict's margin (kept across calls) */
     uint32_t *why;           /* B   diagnostic: why the plan did not take the staged elements (WHY_* bits, 0 if it did) */
     uint32_t *ovf;           /* B   a staging segment of the bucket overflowed */
-    uint32_t *fspan0;        /* B+1 prefix of the spans of fallback buckets */
-    uint32_t *nhard;         /* 1   buckets of this call that are not on PATH_CAND (their kernels leave at once when 0) */
+    uint32_t *ftile0;        /* B+1 prefix of the tiles of buckets on the dense passes */
+    uint32_t *nhard;         /* 4   [0] buckets of this call that are not on PATH_CAND (their kernels leave at once when 0),
+                              *     [1] the barrier of the dense passes, [2] buckets on PATH_DENSE */
     uint32_t *kw;            /* B   parameters the pruning step keeps (only with weights) */
-    const uint32_t *pmask;   /* with Algorithm 2 Step 2: the pruning bitmap, 128 words per tile, bit = pruned; else NULL */
+    const uint32_t *pmask;   /* with Algorithm 2 Step 2: the pruning bitmap, TILE / 32 words per tile, bit = pruned; else NULL */
     uint32_t B;
-    uint32_t n_spans;
-    uint32_t spanT;          /* tiles per span */
-    uint32_t segSh;          /* log2 of the staging segments per span (= wavefronts of the streaming pass) */
+    uint32_t n_tiles;
     uint32_t chunk;
     uint32_t chunkSh;        /* log2(chunk) when chunk is a power of two, else NONE */
-    uint32_t dencSpans;      /* spans per work unit of the one-pass dense encode (2 on large gradients: fewer chunks straddle units; 1 on smaller ones: more units than workgroups) */
+    uint32_t dencTiles;      /* tiles per work unit of the one-pass dense encode: more on large gradients (fewer chunks straddle units) */
 };
 
-/* Candidate staging: segment ss = (span << segSh) + wavefront owns entries [ss * cap, ss * cap + cnt[ss]) */
+/* Candidate staging: tile t owns entries [t * SEG_CAP, t * SEG_CAP + cnt[t]) */
 struct Cand {
     uint32_t *idx;   /* bucket-local index */
     float *val;      /* accumulator value */
-    uint32_t *cnt;   /* entries per segment */
-    uint32_t *G;     /* per segment: #(key > T), later its exclusive prefix inside the bucket */
-    uint32_t *E;     /* per segment: #(key == T), later its exclusive prefix */
-    uint32_t cap;    /* entries per segment: a quarter of the elements it covers */
+    uint32_t *cnt;   /* staged elements per tile (more than SEG_CAP: the tile is read from the dense accumulator instead) */
+    uint32_t *G;     /* per tile: #(key >= W), then #(key > T), later its exclusive prefix inside the bucket */
+    uint32_t *E;     /* per tile: #(key < L) in band mode, then #(key == T), later its exclusive prefix */
 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));   /* one aligned 16-byte access */
+
+/* Where the accumulator or the dense output goes: past the caches when the array is larger than they
+ * hold (the last-level cache is 256 MB), since lines kept there are written back under the kernels that
+ * follow (438 MB: decompress 110 us with plain stores, 75 without, the encode after it 53 and 40); into
+ * the caches when it fits, where the scattered stores of the encode then find it (102 MB). */
+template <bool NT>      /* (a run-time choice ends as one plain store: the compiler merges the two) */
+__device__ __forceinline__ void st_out(f4 *p, f4 v)
+{
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+constexpr uint64_t NT_ELEMS = (1ull << 25) - 1;    /* arrays of less than 128 MB */
 
 __device__ __forceinline__ uint32_t keyof(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
 
@@ -132,37 +165,33 @@ __device__ __forceinline__ uint32_t find_bucket_wg(const T *__restrict__ pre, ui
     return lo;
 }
 
-struct SpanGeo {
-    uint32_t b;        /* bucket */
-    uint32_t ntiles;   /* tiles in this span */
-    uint32_t tile_g;   /* global id of the first tile */
-    uint64_t lo, hi;   /* bucket range */
-    uint64_t base;     /* aligned global element index where the first tile starts */
-};
-
-/* span number si of bucket b */
-__device__ __forceinline__ SpanGeo span_geo_b(const Tables &t, uint32_t b, uint32_t si)
+/* Workgroup -> tile of the streaming kernels.  Workgroups are dealt to the eight dies in turn, so in
+ * every group of 8 * XCD_RUN die x takes XCD_RUN consecutive tiles: the window in flight stays as
+ * compact as in the plain order, and each die touches whole runs of it (`b = a + b` 6.4 -> 6.6 TB/s, a
+ * fill 6.4 -> 7.1; runs of 4 are slower than none, longer ones than 64 leave the dies out of step). */
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t bid)
 {
-    SpanGeo g;
-    g.b = b;
+    const uint32_t r = bid & (8u * XCD_RUN - 1u);
+    return (bid & ~(8u * XCD_RUN - 1u)) + (r & 7u) * XCD_RUN + (r >> 3);
+}
+inline uint32_t xcd_grid(uint32_t n_tiles) { return (n_tiles + 8u * XCD_RUN - 1u) & ~(8u * XCD_RUN - 1u); }
+
+/* A run of consecutive tiles of one bucket. */
+struct TileGeo {
+    uint64_t lo, hi;   /* bucket range */
+    uint64_t base;     /* global element index (a multiple of 4) where the first tile starts */
+};
+__device__ __forceinline__ TileGeo tile_geo(const Tables &t, uint32_t b, uint32_t tile)
+{
+    TileGeo g;
     g.lo = t.off[b];
     g.hi = t.off[b + 1];
-    const uint32_t tiles_b = t.tile0[b + 1] - t.tile0[b];
-    const uint32_t first = si * t.spanT;
-    g.ntiles = min(t.spanT, tiles_b - first);
-    g.tile_g = t.tile0[b] + first;
-    g.base = (g.lo & ~3ull) + (uint64_t)first * TILE;
+    g.base = (g.lo & ~3ull) + (uint64_t)(tile - t.tile0[b]) * TILE;
     return g;
 }
 
-/* global span s */
-__device__ __forceinline__ SpanGeo span_geo(const Tables &t, uint32_t s)
-{
-    const uint32_t b = t.span_b[s];
-    return span_geo_b(t, b, s - t.span0[b]);
-}
-
-/* The four pruning bits of quad `quad` (0..1023) of tile `tile_abs`. */
+/* The four pruning bits of quad `quad` (0 .. TILE / 4 - 1) of tile `tile_abs`; quads of the tiles that
+ * follow it in the bucket may be addressed by larger numbers. */
 __device__ __forceinline__ uint32_t pruned_bits(const uint32_t *__restrict__ pm, uint32_t tile_abs, uint32_t quad)
 {
     return (pm[(uint64_t)tile_abs * (TILE / 32) + (quad >> 3)] >> ((quad & 7u) * 4u)) & 0xFu;
@@ -240,12 +269,17 @@ __global__ __launch_bounds__(WG) void k_setup(Tables t, double ratio, int bits)
     }
 }
 
-/* span -> bucket map, once per bucket layout */
-__global__ __launch_bounds__(WG) void k_spanmap(const uint32_t *__restrict__ span0, uint32_t B,
-                                                uint32_t n_spans, uint32_t *__restrict__ span_b)
+/* Tile tables, once per bucket layout. */
+__global__ __launch_bounds__(WG) void k_tilemap(Tables t, uint32_t *__restrict__ tile_b, uint4 *__restrict__ desc)
 {
-    const uint32_t s = blockIdx.x * WG + threadIdx.x;
-    if (s < n_spans) span_b[s] = find_bucket<uint32_t>(span0, B, s);
+    const uint32_t g = blockIdx.x * WG + threadIdx.x;
+    if (g >= t.n_tiles) return;
+    const uint32_t b = find_bucket<uint32_t>(t.tile0, t.B, g);
+    const TileGeo s = tile_geo(t, b, g);
+    const uint32_t first = s.base < s.lo ? (uint32_t)(s.lo - s.base) : 0u;
+    const uint32_t last = s.hi - s.base < (uint64_t)TILE ? (uint32_t)(s.hi - s.base) : (uint32_t)TILE;
+    tile_b[g] = b;
+    desc[g] = make_uint4((uint32_t)s.base, (uint32_t)(s.base >> 32), b, first | (last << 16));
 }
 
 __global__ __launch_bounds__(WG) void k_clear(uint32_t *__restrict__ p, uint64_t n)
@@ -321,22 +355,6 @@ __global__ __launch_bounds__(1024) void k_calib_copy2(const f4 *__restrict__ a, 
 
 /* ------------------------------------------------------------------ histograms */
 
-/* Add the four level digits of a quad to an LDS histogram.  When every lane of the wavefront
- * carries the same digit in all four slots (runs of zeros, saturated buckets) one lane adds
- * the whole count: same-address LDS atomics of a wavefront serialise.  All 64 lanes must be
- * active. */
-__device__ __forceinline__ void hist_quad_full(uint32_t *h, uint32_t d0, uint32_t d1,
-                                               uint32_t d2, uint32_t d3)
-{
-    const uint32_t f = __builtin_amdgcn_readfirstlane(d0);
-    const bool same = (d0 == f) & (d1 == f) & (d2 == f) & (d3 == f);
-    if (__all(same)) {
-        if ((threadIdx.x & 63) == 0) atomicAdd(&h[f], 256u);
-    } else {
-        atomicAdd(&h[d0], 1u); atomicAdd(&h[d1], 1u); atomicAdd(&h[d2], 1u); atomicAdd(&h[d3], 1u);
-    }
-}
-
 __device__ __forceinline__ void hist_flush(const uint32_t *h, uint32_t *__restrict__ dst, int nb,
                                            int nthreads = WG)
 {
@@ -344,6 +362,27 @@ __device__ __forceinline__ void hist_flush(const uint32_t *h, uint32_t *__restri
         const uint32_t c = h[i];
         if (c) atomicAdd(&dst[i], c);
     }
+}
+
+/* Sum over the 64 lanes of a wavefront with data-parallel moves (see wave_incl_scan): the total is in
+ * lane 63.  The order of the additions is fixed. */
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, true);
+    return v + __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+__device__ __forceinline__ double wave_sum_last(double v)
+{
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    v = dpp_add<0x143, 0xC>(v);
+    return v;
 }
 
 /* Inclusive scan over the 256 threads of a workgroup: shuffles inside each wavefront, one

@@ -16,12 +16,11 @@
  *             with a wide margin, below the k-th largest ("candidates", ratios up to an eighth);
  *             a band [L_b, H_b) of keys around the k-th largest (larger ratios); nothing, when
  *             the k-th largest is a zero (sparse embeddings, ratio 1)
- *   ef_emit   acc = grad + residual (written over residual), exact level-0 histogram, a finer
- *             histogram of the four level-0 digits around the expected threshold, and the staged
- *             elements appended, in index order, to per-wavefront segments       12 B/element
- *   plan      per bucket: exact level-0 digit of the k-th key (18 bits of it when the finer
- *             histogram covers it) and the path: PATH_CAND, PATH_BAND, PATH_ZERO when the staged
- *             elements and the counts can decide it, else PATH_DENSE
+ *   ef_emit   acc = grad + residual (written over residual), the staged elements in index order to a
+ *             segment per tile, how many lie above the window of keys around the expected
+ *             threshold, and the window's bins (from 16384 tiles up by a kernel of their own, bins) 12 B/element
+ *   plan      per bucket: the window's bin that holds the k-th key, and the path: PATH_CAND,
+ *             PATH_BAND, PATH_ZERO when the staged elements and the counts can decide it, else PATH_DENSE
  *   select_count, select_finish   the staged entries against those bits: counts per segment, the
  *             few undecided keys set aside, then per bucket (one workgroup of 1024 threads) the
  *             remaining bits in LDS -> threshold key T_b, e_b = how many elements equal to T_b
@@ -33,7 +32,8 @@
  *             staging segment that overflowed, huge groups of equal keys): all radix steps over
  *             the dense accumulator, in a small resident grid with barriers between the steps
  *   quant     codes what hard left uncoded (chunks that straddle its work units; PATH_DENSE)
- *   tilestart, decomp    payload -> dense, each output line written once
+ *   tilestart, decomp    payload -> dense, each output line written once (few survivors: zeros, then
+ *             the survivors stored over them)
  * Every path gives the same bytes.
  *
  * With weights (Algorithm 2 Step 2) a weight pass comes first: sample of |w| -> band around the
@@ -43,11 +43,9 @@
  * same select_count / select_finish -> bitmap bits of the band; the gradient kernels then read
  * one bit per element instead of the weight.
  *
- * Geometry: a bucket [lo, hi) is cut into tiles of 4096 elements starting at lo rounded down
+ * Geometry: a bucket [lo, hi) is cut into tiles of 2048 elements starting at lo rounded down
  * to a multiple of 4, so every 16-byte access is aligned; elements of an edge tile outside
- * [lo, hi) are masked.  A workgroup owns a span of up to 16 consecutive tiles of one bucket.
- * Workgroups have 256 threads, except in the streaming passes, which run one wavefront per
- * staging segment (256 to 1024 threads), and in select_finish.
+ * [lo, hi) are masked.  A tile is one workgroup of the streaming kernels and one staging segment.
  *
  * One translation unit: the device code lives in nsml_device_common.hpp (tables, geometry,
  * histogram helpers), nsml_select.hpp (sample .. plan, the radix steps over the dense
@@ -88,12 +86,14 @@ struct nsml_ctx {
 
     /* device workspace */
     uint64_t *d_off, *d_P, *d_V, *d_S, *d_C;
-    uint32_t *d_tile0, *d_span0, *d_samp0, *d_span_b, *d_k, *d_T, *d_need, *d_L, *d_fast, *d_fspan0;
+    uint32_t *d_tile0, *d_samp0, *d_tile_b, *d_k, *d_T, *d_need, *d_fast, *d_ftile0;
+    uint4 *d_desc;         /* per tile: where it starts, its bucket, its valid slots */
+    KeyPar *d_par, *d_wpar;        /* per bucket: what the streaming pass stages (gradient, weights) */
     uint32_t *d_sel0;      /* B+1 prefix of the workgroups per bucket of k_select_count */
     uint4 *d_selw;         /* per workgroup of k_select_count: bucket, first and last segment */
     uint32_t *d_chunk_b;   /* per chunk of the payload: its bucket (fixed by layout, ratio, bits) */
     uint32_t *d_chunk_seg; /* per chunk: the staging segment that holds its first survivor */
-    uint32_t *d_H, *d_subLo, *d_sh, *d_why, *d_margin, *d_wredo, *d_wprevT, *d_wprevHw, *d_wnband;
+    uint32_t *d_sh, *d_why, *d_margin, *d_wprevT, *d_wprevHw, *d_wnband;
     uint32_t *d_lcnt, *d_lkey;   /* k_select_count: lists of undecided keys per workgroup */
     uint64_t max_chunks; uint32_t max_sel;
     uint32_t *d_zero;      /* cleared by every compress call: histograms and overflow flags */
@@ -101,15 +101,16 @@ struct nsml_ctx {
     float *d_cval;
     float *d_v;            /* survivor values in final order (not used for bits == 32) */
     uint32_t *d_ts;        /* decompress: where each tile's survivors start */
-    uint32_t *d_pmask;     /* pruning bitmap, 128 words per tile */
+    uint32_t *d_pmask;     /* pruning bitmap, TILE / 32 words per tile */
     uint32_t *d_kw, *d_Tw, *d_needw;              /* pruning stage: kept counts, threshold search state */
     uint32_t *d_wfast;                            /* pruning stage: how each bucket was decided */
-    uint32_t *d_wLo, *d_wHi;                      /* pruning stage: band of keys staged per bucket */
     uint32_t *h_flags;     /* pinned, mapped: [0] consistency flag of the selection, [1] of the pruning stage */
     uint32_t *d_flags;     /* the same two words as the kernels see them */
     double max_ratio;      /* largest ratio the survivor-value buffer was sized for */
     bool have_prune;                              /* the last compress call had weights */
-    double *d_span_sq;     /* per span: sum of grad^2 */
+    bool none_pruned;                             /* ... but its ratio prunes nothing: the weights were not read */
+    uint64_t max_nb;                              /* largest bucket of the layout */
+    double *d_tile_sq;     /* per tile: sum of grad^2 */
     double *d_l2sq;        /* per bucket: sum of grad^2 of the last compress call */
     bool have_l2;
 
@@ -117,24 +118,20 @@ struct nsml_ctx {
     std::vector<uint64_t> h_off;
     uint32_t B;
     uint64_t n;
-    uint32_t n_tiles, n_spans, n_samp, n_sel, spanT, segSh;
+    uint32_t n_tiles, n_samp, n_sel;
+    uint32_t selSh;        /* log2 of the tiles per workgroup of k_select_count */
     bool tables_valid;
     double t_ratio; int t_bits;       /* what d_k/d_P/... were computed for */
     uint64_t K, NC;                   /* totals for (layout, t_ratio, t_bits) */
     void *pinned; size_t pinned_bytes;
-    int span_override;
-    int seg_override;      /* wavefronts per workgroup of the streaming pass (0: by span size) */
+    int decomp_variant;    /* decompress: 1 zeros then survivors, 0 tiles assembled in LDS, -1 by the share of survivors */
     int force_dense;
     bool zero_clean; uint32_t zero_B;   /* the per-call histograms and flags were left zeroed (for this many buckets) */
-    int persist;           /* workgroups per compute unit of the streaming pass (0: one workgroup per span) */
-    int decomp_variant;    /* decompress: 1 direct stores, 0 tiles assembled in LDS, -1 by gradient size */
     int n_cu;
     int hard_occ[2];       /* workgroups of k_hard that fit a compute unit at once (short / long chunks) */
     int whistory;          /* the weight band follows the threshold of the last call (1, default) or always comes from a sample (0) */
     int wband_miss;        /* diagnostic: the weight band is placed beside the threshold, so every bucket takes the repeat */
     int force_rescan;      /* diagnostic: k_select_finish filters the staged entries again instead of using the tails */
-    int nt_mode;
-    int nt_dense;          /* non-temporal stores for the dense output of decompress: 1, 0, or -1 = by variant */
 
     /* profiling */
     bool prof;
@@ -169,22 +166,20 @@ int dev_alloc(nsml_ctx *c, T **p, uint64_t count)
     return NSML_OK;
 }
 
-/* words of the per-call zeroed area: hist0, sample hist, candidate level 1/2, fallback level
- * 1/2 histograms, overflow flags */
-uint64_t zero_words(uint64_t B) { return B * (uint64_t)(NB0 + NB0 + NB1 + NB2 + NB1 + NB2 + NBS + 2) + 16; }   /* 16 spare words: counters */
+/* words of the area that is zero between calls: sample histogram, bins of the window, histograms of
+ * the dense passes, overflow flags */
+uint64_t zero_words(uint64_t B) { return B * (uint64_t)(NB0 + NHC * NHB + NB0 + NB1 + NB2 + 2) + 16; }   /* 16 spare words: counters */
 
-struct Hists { uint32_t *h0, *hs, *c1, *c2, *f1, *f2, *h0b, *ovf, *tail_ovf, *nhard; };
+struct Hists { uint32_t *hs, *hw, *f0, *f1, *f2, *ovf, *tail_ovf, *nhard; };
 Hists hists_of(const nsml_ctx *c, uint32_t B)
 {
     Hists h;
-    h.h0 = c->d_zero;
-    h.hs = h.h0 + (uint64_t)B * NB0;
-    h.c1 = h.hs + (uint64_t)B * NB0;
-    h.c2 = h.c1 + (uint64_t)B * NB1;
-    h.f1 = h.c2 + (uint64_t)B * NB2;
+    h.hs = c->d_zero;
+    h.hw = h.hs + (uint64_t)B * NB0;
+    h.f0 = h.hw + (uint64_t)B * NHC * NHB;
+    h.f1 = h.f0 + (uint64_t)B * NB0;
     h.f2 = h.f1 + (uint64_t)B * NB1;
-    h.h0b = h.f2 + (uint64_t)B * NB2;       /* finer counts of a few level-0 digits */
-    h.ovf = h.h0b + (uint64_t)B * NBS;
+    h.ovf = h.f2 + (uint64_t)B * NB2;
     h.tail_ovf = h.ovf + B;        /* k_select_count: a segment's tail could not hold its undecided keys */
     h.nhard = h.tail_ovf + B;      /* k_plan: buckets not on the candidate path */
     return h;
@@ -198,17 +193,24 @@ static uint32_t chunk_shift(uint32_t chunk)
     return sh;
 }
 
+/* Tiles per work unit of the one-pass dense encode: a chunk that straddles units is coded by a kernel
+ * of its own, so units are as large as leaves a few of them for every workgroup of its grid. */
+static uint32_t denc_tiles(uint32_t n_tiles)
+{
+    return n_tiles >= 65536u ? 32u : n_tiles >= 32768u ? 16u : n_tiles >= 8192u ? 8u : n_tiles >= 2048u ? 4u : 2u;
+}
+
 Tables tables_of(const nsml_ctx *c)
 {
     Tables t;
-    t.off = c->d_off; t.tile0 = c->d_tile0; t.span0 = c->d_span0; t.samp0 = c->d_samp0;
-    t.span_b = c->d_span_b;
+    t.off = c->d_off; t.tile0 = c->d_tile0; t.samp0 = c->d_samp0;
+    t.tile_b = c->d_tile_b; t.desc = c->d_desc;
     t.k = c->d_k; t.P = c->d_P; t.V = c->d_V; t.S = c->d_S; t.C = c->d_C;
-    t.T = c->d_T; t.need = c->d_need; t.L = c->d_L; t.H = c->d_H; t.fast = c->d_fast; t.subLo = c->d_subLo; t.sh = c->d_sh; t.why = c->d_why; t.margin = c->d_margin;
-    t.ovf = hists_of(c, c->B).ovf; t.fspan0 = c->d_fspan0; t.nhard = hists_of(c, c->B).nhard;
+    t.T = c->d_T; t.need = c->d_need; t.par = c->d_par; t.fast = c->d_fast; t.sh = c->d_sh; t.why = c->d_why; t.margin = c->d_margin;
+    t.ovf = hists_of(c, c->B).ovf; t.ftile0 = c->d_ftile0; t.nhard = hists_of(c, c->B).nhard;
     t.kw = c->d_kw; t.pmask = nullptr;
-    t.B = c->B; t.n_spans = c->n_spans; t.spanT = c->spanT; t.segSh = c->segSh; t.chunk = c->chunk; t.chunkSh = chunk_shift(c->chunk);
-    t.dencSpans = c->n_spans >= 16u * (uint32_t)c->n_cu ? 2u : 1u;
+    t.B = c->B; t.n_tiles = c->n_tiles; t.chunk = c->chunk; t.chunkSh = chunk_shift(c->chunk);
+    t.dencTiles = denc_tiles(c->n_tiles);
     return t;
 }
 
@@ -216,7 +218,6 @@ Cand cand_of(const nsml_ctx *c)
 {
     Cand k;
     k.idx = c->d_cidx; k.val = c->d_cval; k.cnt = c->d_ccnt; k.G = c->d_cG; k.E = c->d_cE;
-    k.cap = (c->spanT * (TILE / 4)) >> c->segSh;
     return k;
 }
 
@@ -257,34 +258,6 @@ int prof_end(nsml_ctx *c, bool recorded, hipStream_t st)
 
 bool aligned(const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
 
-/* Tiles per span (one span = one workgroup of the streaming kernels, with four to sixteen
- * staging segments).  Small spans stream a few per cent faster, large spans mean fewer segments
- * for the candidate kernels to walk; measured on 25 M .. 6.7 G elements the totals favour this.
- * (Spans of 16 tiles, one workgroup of 16 wavefronts per compute unit, lose 1 - 8 % to spans of 8
- * with two workgroups of 8: while one of the two ends and its successor starts, the other keeps
- * streaming.) */
-uint32_t pick_span_tiles(uint32_t n_tiles, int override_)
-{
-    if (override_ >= 1 && override_ <= MAX_SPAN_TILES) return (uint32_t)override_;
-    if (n_tiles >= 8u * 2048u) return 8;
-    if (n_tiles >= 4u * 1024u) return 4;
-    if (n_tiles >= 2u * 512u) return 2;
-    return 1;
-}
-
-/* log2 of the wavefronts per workgroup of the streaming pass (= staging segments per span):
- * one wavefront per tile for spans of 8 and 16 tiles, four wavefronts otherwise.  Every
- * wavefront gets at least one wave-tile. */
-uint32_t pick_seg_shift(uint32_t spanT, int override_)
-{
-    uint32_t w = override_ > 0 ? (uint32_t)override_ : (spanT > 4 ? spanT : 4u);
-    const uint32_t hi = spanT * 4u < MAX_SEG_WAVES ? spanT * 4u : MAX_SEG_WAVES;
-    if (w > hi) w = hi;
-    uint32_t sh = 2;
-    while ((2u << sh) <= w) ++sh;
-    return sh;
-}
-
 /* Validate a bucket layout; (re)build the layout tables if it differs from the cached one. */
 int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipStream_t st)
 {
@@ -301,77 +274,67 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
 
     /* new layout: tiles start at the bucket start rounded down to a multiple of 4 */
     const size_t B1 = (size_t)B + 1;
-    std::vector<uint32_t> tile0(B1), span0(B1), samp0(B1), sel0(B1);
-    uint64_t nt = 0, nsamp = 0;
+    std::vector<uint32_t> tile0(B1), samp0(B1), sel0(B1);
+    uint64_t nt = 0, nsamp = 0, nsel = 0;
+    /* 64 tiles per workgroup of k_select_count once that leaves four workgroups per compute unit, else 16
+     * (12 K tiles of a hundred entries: 35 us with 64, 10 with 16) */
+    const uint32_t selSh = n >= 4ull * 64ull * 256ull * TILE ? 6u : 4u;
     for (uint32_t b = 0; b < B; ++b) {
         tile0[b] = (uint32_t)nt;
         samp0[b] = (uint32_t)nsamp;
+        sel0[b] = (uint32_t)nsel;
         const uint64_t lo = off[b], hi = off[b + 1];
         if (hi > lo) {
             const uint64_t len = hi - (lo & ~3ull);
-            nt += (len + TILE - 1) / TILE;
-            const uint64_t run_elems = 32ull * ((hi - lo) < SAMPLE_ALL_BELOW ? 1 : SAMPLE_STRIDE);
+            const uint64_t tiles = (len + TILE - 1) / TILE;
+            nt += tiles;
+            nsel += (tiles + (1u << selSh) - 1) >> selSh;
+            const uint64_t run_elems = SAMPLE_RUN * sample_stride(hi - lo);
             const uint64_t runs = (len + run_elems - 1) / run_elems;
             nsamp += (runs + RUNS_PER_WG - 1) / RUNS_PER_WG;
         }
-        if (nt > c->max_tiles) return NSML_ECAP;
+        if (nt > c->max_tiles || nsel > c->max_sel) return NSML_ECAP;
     }
     tile0[B] = (uint32_t)nt;
     samp0[B] = (uint32_t)nsamp;
-    const uint32_t spanT = pick_span_tiles((uint32_t)nt, c->span_override);
-    uint64_t ns = 0;
-    for (uint32_t b = 0; b < B; ++b) {
-        span0[b] = (uint32_t)ns;
-        ns += (tile0[b + 1] - tile0[b] + spanT - 1) / spanT;
-    }
-    span0[B] = (uint32_t)ns;
-    if (ns * 4ull * spanT * 256ull > c->max_cand) return NSML_ECAP;
-    /* k_select_count: one workgroup per SELC_SEGS staging segments of a bucket */
-    const uint32_t segSh = pick_seg_shift(spanT, c->seg_override);
-    uint64_t nsel = 0;
-    for (uint32_t b = 0; b < B; ++b) {
-        sel0[b] = (uint32_t)nsel;
-        const uint64_t segs = (uint64_t)(span0[b + 1] - span0[b]) << segSh;
-        nsel += (segs + SELC_SEGS - 1) / SELC_SEGS;
-    }
     sel0[B] = (uint32_t)nsel;
-    if (nsel > c->max_sel) return NSML_ECAP;
 
     /* the stream may still be using the old tables */
     NSML_HIP(c, hipStreamSynchronize(st));
     c->tables_valid = false;
     c->B = 0;
-    const size_t need = sizeof(uint64_t) * B1 + 4 * sizeof(uint32_t) * B1;
+    const size_t need = sizeof(uint64_t) * B1 + 3 * sizeof(uint32_t) * B1;
     if (need > c->pinned_bytes) return NSML_ECAP;
     uint8_t *hp = static_cast<uint8_t *>(c->pinned);
     uint8_t *hp_t = hp + sizeof(uint64_t) * B1;
-    uint8_t *hp_s = hp_t + sizeof(uint32_t) * B1;
-    uint8_t *hp_m = hp_s + sizeof(uint32_t) * B1;
+    uint8_t *hp_m = hp_t + sizeof(uint32_t) * B1;
     uint8_t *hp_l = hp_m + sizeof(uint32_t) * B1;
-    memcpy(hp_l, sel0.data(), sizeof(uint32_t) * B1);
     memcpy(hp, off, sizeof(uint64_t) * B1);
     memcpy(hp_t, tile0.data(), sizeof(uint32_t) * B1);
-    memcpy(hp_s, span0.data(), sizeof(uint32_t) * B1);
     memcpy(hp_m, samp0.data(), sizeof(uint32_t) * B1);
+    memcpy(hp_l, sel0.data(), sizeof(uint32_t) * B1);
     NSML_HIP(c, hipMemcpyAsync(c->d_off, hp, sizeof(uint64_t) * B1, hipMemcpyHostToDevice, st));
     NSML_HIP(c, hipMemcpyAsync(c->d_tile0, hp_t, sizeof(uint32_t) * B1, hipMemcpyHostToDevice, st));
-    NSML_HIP(c, hipMemcpyAsync(c->d_span0, hp_s, sizeof(uint32_t) * B1, hipMemcpyHostToDevice, st));
     NSML_HIP(c, hipMemcpyAsync(c->d_samp0, hp_m, sizeof(uint32_t) * B1, hipMemcpyHostToDevice, st));
     NSML_HIP(c, hipMemcpyAsync(c->d_sel0, hp_l, sizeof(uint32_t) * B1, hipMemcpyHostToDevice, st));
-    LAUNCH(c, KID_SPANMAP, st, k_spanmap, (uint32_t)((ns + WG - 1) / WG), (const uint32_t *)c->d_span0, B,
-           (uint32_t)ns, c->d_span_b);
-    if (nsel)
-        LAUNCH(c, KID_SPANMAP, st, k_selmap, (uint32_t)((nsel + WG - 1) / WG), (const uint32_t *)c->d_sel0,
-               (const uint32_t *)c->d_span0, B, (uint32_t)nsel, segSh, c->d_selw);
+    {
+        Tables t;
+        memset(&t, 0, sizeof t);
+        t.off = c->d_off; t.tile0 = c->d_tile0; t.B = B; t.n_tiles = (uint32_t)nt;
+        LAUNCH(c, KID_TILEMAP, st, k_tilemap, (uint32_t)((nt + WG - 1) / WG), t, c->d_tile_b, c->d_desc);
+    }
+    LAUNCH(c, KID_TILEMAP, st, k_selmap, (uint32_t)((nsel + WG - 1) / WG), (const uint32_t *)c->d_sel0,
+           (const uint32_t *)c->d_tile0, B, (uint32_t)nsel, selSh, c->d_selw);
     NSML_HIP(c, hipMemsetAsync(c->d_wprevT, 0xFF, sizeof(uint32_t) * B1, st));     /* other buckets: nothing remembered */
     NSML_HIP(c, hipMemsetAsync(c->d_margin, 0, sizeof(uint32_t) * B1, st));
     NSML_HIP(c, hipStreamSynchronize(st));
 
     c->h_off.assign(off, off + B + 1);
+    c->max_nb = 0;
+    for (uint32_t b = 0; b < B; ++b) c->max_nb = off[b + 1] - off[b] > c->max_nb ? off[b + 1] - off[b] : c->max_nb;
     c->B = B; c->n = n;
-    c->n_tiles = (uint32_t)nt; c->n_spans = (uint32_t)ns; c->n_samp = (uint32_t)nsamp; c->spanT = spanT;
-    c->segSh = segSh;
-    c->n_sel = (uint32_t)nsel;
+    c->n_tiles = (uint32_t)nt; c->n_samp = (uint32_t)nsamp;
+    c->n_sel = (uint32_t)nsel; c->selSh = selSh;
     return NSML_OK;
 }
 
@@ -430,21 +393,20 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     c->last_hip = 0; c->ws_bytes = 0; c->B = 0; c->n = 0; c->tables_valid = false;
     c->prof = false; c->pinned = nullptr; c->pinned_bytes = 0;
     c->d_off = c->d_P = c->d_V = c->d_S = c->d_C = nullptr;
-    c->d_tile0 = c->d_span0 = c->d_samp0 = c->d_span_b = c->d_k = c->d_T = c->d_need = nullptr;
-    c->d_L = c->d_fast = c->d_fspan0 = c->d_zero = nullptr;
-    c->d_sel0 = nullptr; c->d_selw = nullptr; c->d_chunk_b = c->d_chunk_seg = c->d_H = c->d_subLo = c->d_sh = c->d_why = c->d_margin = c->d_wredo = c->d_wprevT = c->d_wprevHw = c->d_wnband = nullptr;
+    c->d_tile0 = c->d_samp0 = c->d_tile_b = c->d_k = c->d_T = c->d_need = nullptr;
+    c->d_fast = c->d_ftile0 = c->d_zero = nullptr; c->d_desc = nullptr; c->d_par = c->d_wpar = nullptr;
+    c->d_sel0 = nullptr; c->d_selw = nullptr; c->d_chunk_b = c->d_chunk_seg = c->d_sh = c->d_why = c->d_margin = c->d_wprevT = c->d_wprevHw = c->d_wnband = nullptr;
     c->d_lcnt = c->d_lkey = nullptr;
     c->d_ccnt = c->d_cG = c->d_cE = c->d_cidx = nullptr;
-    c->d_cval = nullptr; c->d_v = nullptr; c->d_ts = nullptr; c->d_span_sq = c->d_l2sq = nullptr; c->have_l2 = false;
-    c->d_pmask = c->d_kw = c->d_Tw = c->d_needw = c->d_wfast = c->d_wLo = c->d_wHi = nullptr;
+    c->d_cval = nullptr; c->d_v = nullptr; c->d_ts = nullptr; c->d_tile_sq = c->d_l2sq = nullptr; c->have_l2 = false;
+    c->d_pmask = c->d_kw = c->d_Tw = c->d_needw = c->d_wfast = nullptr;
     c->h_flags = c->d_flags = nullptr;
-    c->have_prune = false;
+    c->have_prune = false; c->none_pruned = false; c->max_nb = 0;
     c->max_ratio = max_ratio;
     /* tuning switches: the measured defaults (see nsml_set_option) */
-    c->span_override = 0; c->seg_override = 0; c->segSh = 2;
     c->zero_clean = false; c->zero_B = 0;
-    c->persist = 0; c->decomp_variant = -1; c->n_cu = 256;
-    c->force_dense = 0; c->force_rescan = 0; c->wband_miss = 0; c->whistory = 1; c->nt_mode = 7; c->nt_dense = -1;
+    c->n_cu = 256; c->decomp_variant = -1;
+    c->force_dense = 0; c->force_rescan = 0; c->wband_miss = 0; c->whistory = 1;
 
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) {
@@ -472,29 +434,25 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     const uint64_t mt = max_n / TILE + 2ull * max_buckets + 2;
     if (mt >= 0x3FFFFFFFull) { delete c; return NSML_ECAP; }
     c->max_tiles = (uint32_t)mt;
-    /* staging: a quarter of the elements every span covers; a span is at most 16 tiles and
-     * every bucket can leave one span partly filled */
-    c->max_cand = (mt + (uint64_t)MAX_SPAN_TILES * max_buckets) * (TILE / 4);
+    /* staging: a quarter of the elements every tile covers */
+    c->max_cand = mt * SEG_CAP;
     const uint64_t B1 = (uint64_t)max_buckets + 1;
     int rc = NSML_OK;
     auto A = [&](int r) { if (rc == NSML_OK) rc = r; };
     A(dev_alloc(c, &c->d_off, B1)); A(dev_alloc(c, &c->d_P, B1)); A(dev_alloc(c, &c->d_V, B1));
     A(dev_alloc(c, &c->d_S, B1)); A(dev_alloc(c, &c->d_C, B1));
-    A(dev_alloc(c, &c->d_tile0, B1)); A(dev_alloc(c, &c->d_span0, B1)); A(dev_alloc(c, &c->d_samp0, B1));
+    A(dev_alloc(c, &c->d_tile0, B1)); A(dev_alloc(c, &c->d_samp0, B1));
     A(dev_alloc(c, &c->d_k, B1)); A(dev_alloc(c, &c->d_T, B1)); A(dev_alloc(c, &c->d_need, B1));
-    A(dev_alloc(c, &c->d_L, B1)); A(dev_alloc(c, &c->d_fast, B1)); A(dev_alloc(c, &c->d_fspan0, B1));
-    A(dev_alloc(c, &c->d_sel0, B1)); A(dev_alloc(c, &c->d_H, B1)); A(dev_alloc(c, &c->d_subLo, B1)); A(dev_alloc(c, &c->d_sh, B1)); A(dev_alloc(c, &c->d_why, B1)); A(dev_alloc(c, &c->d_margin, B1));
-    A(dev_alloc(c, &c->d_span_b, mt));
+    A(dev_alloc(c, &c->d_par, B1)); A(dev_alloc(c, &c->d_wpar, B1)); A(dev_alloc(c, &c->d_fast, B1)); A(dev_alloc(c, &c->d_ftile0, B1));
+    A(dev_alloc(c, &c->d_sel0, B1)); A(dev_alloc(c, &c->d_sh, B1)); A(dev_alloc(c, &c->d_why, B1)); A(dev_alloc(c, &c->d_margin, B1));
+    A(dev_alloc(c, &c->d_tile_b, mt)); A(dev_alloc(c, &c->d_desc, mt));
     A(dev_alloc(c, &c->d_zero, zero_words(max_buckets)));
-    /* segments: at most 4 per tile-sized span, or one per tile plus a partly filled span per bucket */
-    const uint64_t msg = 4 * mt + (uint64_t)MAX_SEG_WAVES * B1;
-    A(dev_alloc(c, &c->d_ccnt, msg)); A(dev_alloc(c, &c->d_cG, msg)); A(dev_alloc(c, &c->d_cE, msg));
-    /* k_select_count workgroups: 16 segments each; the geometries the library picks itself have
-     * at most one segment per tile from 16384 tiles up */
-    c->max_sel = (uint32_t)(((mt > 16384 ? mt : 16384) + (uint64_t)MAX_SEG_WAVES * B1) / SELC_SEGS + B1);
+    A(dev_alloc(c, &c->d_ccnt, mt)); A(dev_alloc(c, &c->d_cG, mt)); A(dev_alloc(c, &c->d_cE, mt));
+    /* k_select_count workgroups: every bucket can end with a short one */
+    c->max_sel = (uint32_t)(mt / 16 + B1);
     A(dev_alloc(c, &c->d_selw, c->max_sel));
     A(dev_alloc(c, &c->d_lcnt, c->max_sel));
-    A(dev_alloc(c, &c->d_lkey, (uint64_t)c->max_sel * LCAP));
+    A(dev_alloc(c, &c->d_lkey, mt * LIST_PER_SEG + B1 * LCAP));
     A(dev_alloc(c, &c->d_cidx, c->max_cand)); A(dev_alloc(c, &c->d_cval, c->max_cand));
     {   /* survivor values in final order: ceil(ratio * n_b) per bucket, at most one more than
          * ratio * n_b each */
@@ -506,16 +464,13 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
         A(dev_alloc(c, &c->d_chunk_b, c->max_chunks)); A(dev_alloc(c, &c->d_chunk_seg, c->max_chunks));
     }
     A(dev_alloc(c, &c->d_ts, mt + B1 + 1));
-    A(dev_alloc(c, &c->d_span_sq, mt)); A(dev_alloc(c, &c->d_l2sq, B1));
+    A(dev_alloc(c, &c->d_tile_sq, mt)); A(dev_alloc(c, &c->d_l2sq, B1));
     A(dev_alloc(c, &c->d_pmask, mt * (TILE / 32)));
     A(dev_alloc(c, &c->d_kw, B1)); A(dev_alloc(c, &c->d_Tw, B1)); A(dev_alloc(c, &c->d_needw, B1));
     A(dev_alloc(c, &c->d_wfast, B1));
-    A(dev_alloc(c, &c->d_wLo, B1)); A(dev_alloc(c, &c->d_wHi, B1));
-    A(dev_alloc(c, &c->d_wredo, B1));
     A(dev_alloc(c, &c->d_wprevT, B1)); A(dev_alloc(c, &c->d_wprevHw, B1)); A(dev_alloc(c, &c->d_wnband, B1));
     if (rc == NSML_OK) {
-        hipError_t e = hipMemset(c->d_wredo, 0, sizeof(uint32_t) * B1);
-        if (e == hipSuccess) e = hipMemset(c->d_margin, 0, sizeof(uint32_t) * B1);
+        hipError_t e = hipMemset(c->d_margin, 0, sizeof(uint32_t) * B1);
         if (e == hipSuccess) e = hipMemset(c->d_wprevT, 0xFF, sizeof(uint32_t) * B1);   /* nothing remembered */
         if (e != hipSuccess) { c->last_hip = (int)e; rc = NSML_EHIP; }
     }
@@ -547,12 +502,12 @@ int nsml_destroy(nsml_ctx *c)
     if (!c) return NSML_EINVAL;
     DeviceGuard guard(c->device);
     (void)hipDeviceSynchronize();
-    void *ptrs[] = {c->d_off, c->d_P, c->d_V, c->d_S, c->d_C, c->d_tile0, c->d_span0, c->d_samp0,
-                    c->d_span_b, c->d_k, c->d_T, c->d_need, c->d_L, c->d_fast, c->d_fspan0,
+    void *ptrs[] = {c->d_off, c->d_P, c->d_V, c->d_S, c->d_C, c->d_tile0, c->d_samp0,
+                    c->d_tile_b, c->d_desc, c->d_k, c->d_T, c->d_need, c->d_par, c->d_wpar, c->d_fast, c->d_ftile0,
                     c->d_zero, c->d_ccnt, c->d_cG, c->d_cE, c->d_cidx,
-                    c->d_cval, c->d_v, c->d_ts, c->d_span_sq, c->d_l2sq, c->d_pmask, c->d_kw,
+                    c->d_cval, c->d_v, c->d_ts, c->d_tile_sq, c->d_l2sq, c->d_pmask, c->d_kw,
                     c->d_Tw, c->d_needw, c->d_wfast,
-                    c->d_wLo, c->d_wHi, c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_H, c->d_lcnt, c->d_lkey, c->d_subLo, c->d_sh, c->d_why, c->d_margin, c->d_wredo, c->d_wprevT, c->d_wprevHw, c->d_wnband};
+                    c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_lcnt, c->d_lkey, c->d_sh, c->d_why, c->d_margin, c->d_wprevT, c->d_wprevHw, c->d_wnband};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->h_flags) (void)hipHostFree(c->h_flags);
@@ -591,80 +546,67 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     const uint64_t zw = zero_words(B);
     const uint32_t clear_grid = (uint32_t)((zw + WG * 8 - 1) / (WG * 8));
     float *vdst = bits == 32 ? static_cast<float *>(val) : c->d_v;
-    const uint32_t n_ss = c->n_spans << c->segSh;
-    const uint32_t eblock = 64u << c->segSh;
-    uint32_t egrid = c->n_spans;         /* streaming pass: one workgroup per span, or a fixed number per compute unit */
-    if (c->persist > 0 && (uint32_t)(c->persist * c->n_cu) < egrid) egrid = (uint32_t)(c->persist * c->n_cu);
+    const uint32_t sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
+    const bool bins = !c->force_dense && c->n_tiles >= HIST_MAX_TILES;      /* the window's bins by a kernel of their own */
+    /* the kernels below zero what they have read of the per-call histograms and flags, so a fill
+     * is only needed after something else used the area: another bucket count, a call that did not
+     * get to its end */
+    if (!c->zero_clean || c->zero_B != B)
+        LAUNCH(c, KID_CLEAR, st, k_clear, clear_grid < 2048 ? clear_grid : 2048, c->d_zero, zw);
+    c->zero_clean = false;
 
+    /* floor(0.5 * (1 - ratio) * n_b) parameters are pruned: when that is none of any bucket (ratio 1, the
+     * controller's cap), the weights decide nothing and are not read */
+    const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
+    if (none_pruned) weights = nullptr;
     if (weights) {
-        /* Algorithm 2 Step 2: threshold and cut of |w| per bucket (bitmap for the buckets that
-         * had to take the dense passes), on its own set of tables */
+        /* Algorithm 2 Step 2: threshold and cut of |w| per bucket, on its own set of tables */
         Tables tw = t;
         tw.k = c->d_kw; tw.T = c->d_Tw; tw.need = c->d_needw; tw.fast = c->d_wfast;
-        tw.L = c->d_wLo; tw.H = c->d_wHi;              /* the staged band of weight keys (H is never NONE here) */
-        const Cand cdw = cd0;
-        LAUNCH(c, KID_CLEAR, st, k_clear, clear_grid < 2048 ? clear_grid : 2048, c->d_zero, zw);
+        tw.par = c->d_wpar;                            /* the staged band of weight keys (never without an upper bound) */
         if (!c->force_dense)
             LAUNCH(c, KID_SAMPLE, st, k_sample<false>, c->n_samp, weights, (const float *)nullptr, tw, h.hs);
-        LAUNCH(c, KID_WPLAN, st, k_wpredict, B, tw, (const uint32_t *)h.hs, c->d_wLo, c->d_wHi, c->force_dense,
-               c->wband_miss, c->whistory ? (const uint32_t *)c->d_wprevT : (const uint32_t *)nullptr,
-               (const uint32_t *)c->d_wprevHw);
-        LAUNCHB(c, KID_WHIST, st, k_whist, c->n_spans, eblock, weights, tw, h.h0, cdw,
-                (const uint32_t *)c->d_wLo, (const uint32_t *)c->d_wHi, c->d_pmask, (const uint32_t *)c->d_wredo, 0);
-        LAUNCH(c, KID_WPLAN, st, k_wplan, B, tw, h.h0, cdw, (const uint32_t *)c->d_wLo,
-               (const uint32_t *)c->d_wHi, c->d_wredo, c->d_wnband, 0);
-        /* the buckets whose band missed the threshold (rare): the pass again, exact histogram */
-        LAUNCHB(c, KID_WHIST, st, k_whist, c->n_spans, eblock, weights, tw, h.h0, cdw,
-                (const uint32_t *)c->d_wLo, (const uint32_t *)c->d_wHi, c->d_pmask, (const uint32_t *)c->d_wredo, 1);
-        LAUNCH(c, KID_WPLAN, st, k_wplan, B, tw, h.h0, cdw, (const uint32_t *)c->d_wLo,
-               (const uint32_t *)c->d_wHi, c->d_wredo, c->d_wnband, 1);
+        LAUNCH(c, KID_WPLAN, st, k_wpredict, B, tw, h.hs, c->force_dense, c->wband_miss,
+               c->whistory ? (const uint32_t *)c->d_wprevT : (const uint32_t *)nullptr, (const uint32_t *)c->d_wprevHw);
+        if (bins) LAUNCHB(c, KID_WHIST, st, k_whist<false>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
+        else LAUNCHB(c, KID_WHIST, st, k_whist<true>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
+        if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, weights);
+        LAUNCHB(c, KID_WPLAN, st, k_wplan, B, NHB, tw, h.hw, cd0, c->d_wnband);
         /* buckets decided from their band: undecided keys, threshold key and tie count, the pruned
-         * band elements' bits; buckets on the dense passes: everything in one resident launch */
+         * band elements' bits; buckets on the dense passes (no band, or one that missed):
+         * everything in one resident launch */
         if (!c->force_dense) {
-            LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, tw, cdw, (const uint4 *)c->d_selw, h.tail_ovf, c->d_lcnt, c->d_lkey, weights);
-            LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cdw, (const uint32_t *)c->d_sel0, h.tail_ovf,
+            LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.tail_ovf, c->d_lcnt, c->d_lkey, weights);
+            LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.tail_ovf,
                     (const uint32_t *)c->d_lcnt, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1,
                     c->force_rescan, weights);
-            LAUNCH(c, KID_WMASK, st, k_wfix, (n_ss + 15) / 16, tw, cdw, c->d_pmask);
+            LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
         }
-        LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cdw, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
-        LAUNCH(c, KID_WPLAN, st, k_wremember, (B + WG - 1) / WG, tw, (const uint32_t *)c->d_Tw, (const uint32_t *)c->d_wLo,
-               (const uint32_t *)c->d_wHi, (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
+        LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
+        LAUNCH(c, KID_WPLAN, st, k_wremember, (B + WG - 1) / WG, tw, (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
         t.pmask = c->d_pmask;
     }
 
     const bool pruned = weights != nullptr;
-    /* the kernels below zero what they have read of the per-call histograms and flags, so a fill
-     * is only needed after something else used the area: the weight stage, another bucket
-     * count, a call that did not get to its end */
-    if (pruned || !c->zero_clean || c->zero_B != B)
-        LAUNCH(c, KID_CLEAR, st, k_clear, clear_grid < 2048 ? clear_grid : 2048, c->d_zero, zw);
-    c->zero_clean = false;
     if (!c->force_dense)
         LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs);
     LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
-    if (c->force_dense) {
-        if (weights) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<false, 7, true>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq);
-        else LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<false, 7, false>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq);
-    } else if (weights) {
-        LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<true, 7, true>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq);
-    } else {
-        switch (c->nt_mode) {
-        case 1:  LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<true, 1, false>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq); break;
-        case 3:  LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<true, 3, false>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq); break;
-        case 5:  LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<true, 5, false>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq); break;
-        default: LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<true, 7, false>), egrid, eblock, grad, residual, t, h.h0, h.h0b, cd0, c->d_span_sq); break;
-        }
-    }
-    LAUNCH(c, KID_PLAN, st, k_plan, B, t, h.h0, h.h0b, cd0, c->force_dense ? 0 : 1,
-           (const double *)c->d_span_sq, c->d_l2sq);
+    const bool nt = n > NT_ELEMS;
+#define NSML_EF(EMIT_, PRUNE_, NT_, HIST_) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<EMIT_, PRUNE_, NT_, HIST_>), sgrid, STH, grad, residual, t, h.hw, cd0, c->d_tile_sq)
+    if (c->force_dense) { if (nt) NSML_EF(false, false, true, false); else NSML_EF(false, false, false, false); }
+    else if (bins) { if (pruned) NSML_EF(true, true, true, false); else NSML_EF(true, false, true, false); }      /* (more tiles than that are more elements than NT_ELEMS) */
+    else if (nt) { if (pruned) NSML_EF(true, true, true, true); else NSML_EF(true, false, true, true); }
+    else { if (pruned) NSML_EF(true, true, false, true); else NSML_EF(true, false, false, true); }
+#undef NSML_EF
+    if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, (const float *)residual);
+    LAUNCHB(c, KID_PLAN, st, k_plan, B, NHB, t, h.hw, cd0, c->force_dense ? 0 : 1, (const double *)c->d_tile_sq, c->d_l2sq);
     const uint32_t qgrid = (uint32_t)c->NC;
     if (!c->force_dense) {
         /* buckets decided from their staged elements: undecided keys set apart, threshold and
          * survivor order per bucket, then the payload of the candidate-path buckets */
         const uint4 *selw = c->d_selw;
-        LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, t, cd0, selw, h.tail_ovf, c->d_lcnt, c->d_lkey, (const float *)residual);
-        LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, h.tail_ovf,
+        LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, t, cd0, selw, c->selSh, h.tail_ovf, c->d_lcnt, c->d_lkey, (const float *)residual);
+        LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.tail_ovf,
                 (const uint32_t *)c->d_lcnt, (const uint32_t *)c->d_lkey, c->d_chunk_seg, c->d_flags,
                 c->force_rescan, (const float *)residual);
         {
@@ -673,10 +615,10 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             const uint32_t cpw = c->NC > (1ull << 14) ? 16u : 1u;     /* very many chunks: fewer, longer-lived workgroups */
             const uint32_t egrid2 = (uint32_t)((c->NC + cpw - 1) / cpw);
             switch (bits) {
-            case 32: LAUNCH(c, KID_ENCODE, st, k_encode<32>, egrid2, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
-            case 16: LAUNCH(c, KID_ENCODE, st, k_encode<16>, egrid2, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
-            case 8:  LAUNCH(c, KID_ENCODE, st, k_encode<8>, egrid2, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
-            default: LAUNCH(c, KID_ENCODE, st, k_encode<4>, egrid2, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
+            case 32: LAUNCHB(c, KID_ENCODE, st, k_encode<32>, egrid2, ENC_T, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
+            case 16: LAUNCHB(c, KID_ENCODE, st, k_encode<16>, egrid2, ENC_T, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
+            case 8:  LAUNCHB(c, KID_ENCODE, st, k_encode<8>, egrid2, ENC_T, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
+            default: LAUNCHB(c, KID_ENCODE, st, k_encode<4>, egrid2, ENC_T, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw); break;
             }
         }
     }
@@ -693,7 +635,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         const uint32_t team = (uint32_t)c->n_cu < hgrid ? (uint32_t)c->n_cu : hgrid;
         const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
         const int stream_coding = c->chunk <= DENC_MAX_CHUNK ? 1 : 0;
-#define NSML_HARD(BITS_, BIG_) LAUNCH(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, residual, t, cd0, h.f1, h.f2, idx, vdst, val, scales, c->d_flags, stream_coding, team)
+#define NSML_HARD(BITS_, BIG_) LAUNCH(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, residual, t, cd0, h.f0, h.f1, h.f2, idx, vdst, val, scales, c->d_flags, stream_coding, team)
         switch (bits) {
         case 32: NSML_HARD(32, false); break;
         case 16: if (big) NSML_HARD(16, true); else NSML_HARD(16, false); break;
@@ -713,7 +655,8 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         }
     }
     c->have_l2 = true;
-    c->have_prune = pruned;
+    c->have_prune = pruned || none_pruned;
+    c->none_pruned = none_pruned;
     c->zero_clean = true;
     c->zero_B = B;
     return NSML_OK;
@@ -734,14 +677,35 @@ int nsml_compress_pruned(nsml_ctx *c, const float *grad, float *residual, const 
     return compress_impl(c, grad, residual, weights, n, bucket_off, B, ratio, bits, idx, val, scales, stream);
 }
 
+}  // extern "C"
+
 /* The launches of one decompress: tile-start table, then the dense output.  c may be NULL
  * (the entry point without a context): then nothing is profiled and no error code is kept. */
-static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint64_t K, uint32_t n_spans, uint32_t n_tiles,
-                             uint32_t *d_ts, int nt_dense, int variant, const uint32_t *idx, const void *val,
-                             const float *scales, int bits, float *dense_out)
+/* Up to one survivor in SCATTER_SHARE elements the dense output is zeroed and the survivors are stored
+ * over the zeros. */
+constexpr uint64_t SCATTER_SHARE = 512;
+template <typename MAP>
+static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint64_t n, uint64_t K, const MAP *tile_b, uint32_t *d_ts,
+                             const uint32_t *idx, const void *val, const float *scales, int bits, float *dense_out, int variant)
 {
-    const bool crowded = K >= 64ull * n_tiles;           /* many survivors per tile */
-    if (crowded) {
+    const uint32_t n_tiles = t.n_tiles;
+    if (variant > 0 || (variant < 0 && K * SCATTER_SHARE <= n)) {
+        /* few survivors: zeros at the speed of a fill, then the survivors stored over them */
+        const uint32_t zgrid = xcd_grid((uint32_t)((n + ZERO_T * 4 - 1) / (ZERO_T * 4)));
+        if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
+        else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
+        const uint32_t sgrid = (uint32_t)((K + WG * SCAT_PER - 1) / (WG * SCAT_PER));
+        switch (bits) {
+        case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
+        case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
+        case 8:  LAUNCH(c, KID_DECOMP, st, (k_scatter<8, false, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
+        default: LAUNCH(c, KID_DECOMP, st, (k_scatter<4, false, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
+        }
+        return NSML_OK;
+    }
+    if (K == n) {
+        /* everything was sent: no index list is read */
+    } else if (K >= 32ull * n_tiles) {                  /* many survivors per tile */
         LAUNCH(c, KID_TILESTART, st, k_tilestart_search, (n_tiles + WG - 1) / WG, idx, t, n_tiles, d_ts);
     } else if (K >= (4ull << 20)) {
         const uint64_t want = (K + (uint64_t)WG * 8 - 1) / ((uint64_t)WG * 8);
@@ -751,45 +715,24 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
         LAUNCH(c, KID_TILESTART, st, k_tilestart<2>, (uint32_t)want, idx, t, K, d_ts);
     }
     const uint32_t *ts = d_ts;
-    if (variant > 0 || (variant < 0 && n_tiles >= 16u * 4096u && !crowded)) {
-        /* the largest gradients at low ratios: one wavefront per tile, direct stores (plain unless asked
-         * otherwise); 16 wavefronts per workgroup, which take 16 / spanT whole spans */
-        const uint32_t dblock = 64u * MAX_SEG_WAVES;
-        const uint32_t per_wg = MAX_SEG_WAVES / t.spanT ? MAX_SEG_WAVES / t.spanT : 1u;
-        n_spans = (n_spans + per_wg - 1) / per_wg;
-        if (nt_dense > 0) {
-            switch (bits) {
-            case 32: LAUNCHB(c, KID_DECOMP, st, (k_decomp<32, true>), n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            case 16: LAUNCHB(c, KID_DECOMP, st, (k_decomp<16, true>), n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            case 8:  LAUNCHB(c, KID_DECOMP, st, (k_decomp<8, true>),  n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            default: LAUNCHB(c, KID_DECOMP, st, (k_decomp<4, true>),  n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            }
-        } else {
-            switch (bits) {
-            case 32: LAUNCHB(c, KID_DECOMP, st, (k_decomp<32, false>), n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            case 16: LAUNCHB(c, KID_DECOMP, st, (k_decomp<16, false>), n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            case 8:  LAUNCHB(c, KID_DECOMP, st, (k_decomp<8, false>),  n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            default: LAUNCHB(c, KID_DECOMP, st, (k_decomp<4, false>),  n_spans, dblock, idx, val, scales, t, ts, dense_out); break;
-            }
-        }
-    } else if (nt_dense != 0) {
-        /* smaller gradients: tiles assembled in LDS, non-temporal stores unless asked otherwise */
-        switch (bits) {
-        case 32: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<32, true>), n_spans, idx, val, scales, t, ts, dense_out); break;
-        case 16: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<16, true>), n_spans, idx, val, scales, t, ts, dense_out); break;
-        case 8:  LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<8, true>),  n_spans, idx, val, scales, t, ts, dense_out); break;
-        default: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<4, true>),  n_spans, idx, val, scales, t, ts, dense_out); break;
-        }
-    } else {
-        switch (bits) {
-        case 32: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<32, false>), n_spans, idx, val, scales, t, ts, dense_out); break;
-        case 16: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<16, false>), n_spans, idx, val, scales, t, ts, dense_out); break;
-        case 8:  LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<8, false>),  n_spans, idx, val, scales, t, ts, dense_out); break;
-        default: LAUNCH(c, KID_DECOMP, st, (k_decomp_lds<4, false>),  n_spans, idx, val, scales, t, ts, dense_out); break;
-        }
+    const uint32_t grid = xcd_grid(n_tiles);
+    /* (everything sent: a plain decode, faster with plain stores: 606 against 634 us on 419 M elements) */
+#define NSML_DECOMP(BITS_)                                                                                                       \
+    do {                                                                                                                          \
+        if (n > NT_ELEMS && K != n) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, true>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out); \
+        else LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out);                       \
+    } while (0)
+    switch (bits) {
+    case 32: NSML_DECOMP(32); break;
+    case 16: NSML_DECOMP(16); break;
+    case 8:  NSML_DECOMP(8); break;
+    default: NSML_DECOMP(4); break;
     }
+#undef NSML_DECOMP
     return NSML_OK;
 }
+
+extern "C" {
 
 int nsml_decompress(nsml_ctx *c, const uint32_t *idx, const void *val, const float *scales,
                     uint64_t n, const uint64_t *bucket_off, uint32_t B, double ratio, int bits,
@@ -807,8 +750,7 @@ int nsml_decompress(nsml_ctx *c, const uint32_t *idx, const void *val, const flo
     if (rc) return rc;
     rc = ensure_tables(c, ratio, bits, st);
     if (rc) return rc;
-    return launch_decompress(c, st, tables_of(c), c->K, c->n_spans, c->n_tiles, c->d_ts, c->nt_dense, c->decomp_variant, idx, val, scales,
-                             bits, dense_out);
+    return launch_decompress<uint32_t>(c, st, tables_of(c), c->n, c->K, c->d_tile_b, c->d_ts, idx, val, scales, bits, dense_out, c->decomp_variant);
 }
 
 /* ---------------------------------------------------------------- no-allocation decompress */
@@ -833,7 +775,8 @@ struct StaticOffsets { uint64_t off[STATIC_B1]; };      /* travels as a kernel a
 /* where each table sits inside the scratch array */
 struct StaticScratch {
     uint64_t *off, *P, *V, *S, *C;
-    uint32_t *tile0, *span0, *k, *kw, *span_b, *ts;
+    uint32_t *tile0, *k, *kw, *ts;
+    uint16_t *tile_b;
 };
 StaticScratch carve(void *base)
 {
@@ -846,34 +789,37 @@ StaticScratch carve(void *base)
     m.C = q; q += STATIC_B1;
     uint32_t *w = reinterpret_cast<uint32_t *>(q);
     m.tile0 = w; w += STATIC_B1 + 1;
-    m.span0 = w; w += STATIC_B1 + 1;
     m.k = w; w += STATIC_B1 + 1;
     m.kw = w; w += STATIC_B1 + 1;
-    m.span_b = w; w += STATIC_MAX_TILES;
     m.ts = w; w += STATIC_MAX_TILES + STATIC_B1 + 1;
+    m.tile_b = reinterpret_cast<uint16_t *>(w);
     return m;
 }
-static_assert(5 * STATIC_B1 * 8 + 4 * (STATIC_B1 + 1) * 4 + (2 * STATIC_MAX_TILES + STATIC_B1 + 1) * 4
+static_assert(5 * STATIC_B1 * 8 + 3 * (STATIC_B1 + 1) * 4 + (STATIC_MAX_TILES + STATIC_B1 + 1) * 4 + STATIC_MAX_TILES * 2
                   <= NSML_STATIC_SCRATCH_BYTES, "scratch array too small for its tables");
 static_assert(sizeof(StaticOffsets) <= 3072, "bucket offsets must fit the kernel argument block");
 
-/* One workgroup: bucket offsets (handed over by value) and the tile / span prefixes they imply. */
-__global__ __launch_bounds__(WG) void k_static_layout(StaticOffsets so, uint32_t B, uint32_t spanT,
-                                                      uint64_t *__restrict__ off, uint32_t *__restrict__ tile0,
-                                                      uint32_t *__restrict__ span0)
+/* One workgroup: bucket offsets (handed over by value) and the tile prefix they imply. */
+__global__ __launch_bounds__(WG) void k_static_layout(StaticOffsets so, uint32_t B,
+                                                      uint64_t *__restrict__ off, uint32_t *__restrict__ tile0)
 {
     for (uint32_t b = threadIdx.x; b <= B; b += WG) off[b] = so.off[b];
     if (threadIdx.x == 0) {
-        uint32_t nt = 0, ns = 0;
+        uint32_t nt = 0;
         for (uint32_t b = 0; b < B; ++b) {
-            tile0[b] = nt; span0[b] = ns;
+            tile0[b] = nt;
             const uint64_t lo = so.off[b], hi = so.off[b + 1];
-            const uint32_t tb = hi > lo ? (uint32_t)((hi - (lo & ~3ull) + TILE - 1) / TILE) : 0u;
-            nt += tb;
-            ns += (tb + spanT - 1) / spanT;
+            nt += hi > lo ? (uint32_t)((hi - (lo & ~3ull) + TILE - 1) / TILE) : 0u;
         }
-        tile0[B] = nt; span0[B] = ns;
+        tile0[B] = nt;
     }
+}
+
+__global__ __launch_bounds__(WG) void k_static_tilemap(const uint32_t *__restrict__ tile0, uint32_t B, uint32_t n_tiles,
+                                                       uint16_t *__restrict__ tile_b)
+{
+    const uint32_t g = blockIdx.x * WG + threadIdx.x;
+    if (g < n_tiles) tile_b[g] = (uint16_t)find_bucket<uint32_t>(tile0, B, g);
 }
 
 }  // namespace
@@ -894,20 +840,14 @@ int nsml_decompress_static(const uint32_t *idx, const void *val, const float *sc
     int rc = nsml_payload_layout(bucket_off, B, ratio, bits, chunk, nullptr, &K, nullptr, nullptr);
     if (rc) return rc;                      /* also rejects descending offsets, bad ratio / bits / chunk */
     /* the same geometry a context would build, computed without any table on the host */
-    uint64_t nt = 0, ns = 0;
-    for (uint32_t b = 0; b < B; ++b) {
-        const uint64_t lo = bucket_off[b], hi = bucket_off[b + 1];
-        if (hi > lo) nt += (hi - (lo & ~3ull) + TILE - 1) / TILE;
-    }
-    if (nt > STATIC_MAX_TILES) return NSML_ECAP;
-    const uint32_t spanT = pick_span_tiles((uint32_t)nt, 0);
+    uint64_t nt = 0;
     StaticOffsets so;
     for (uint32_t b = 0; b < B; ++b) {
         const uint64_t lo = bucket_off[b], hi = bucket_off[b + 1];
-        const uint64_t tb = hi > lo ? (hi - (lo & ~3ull) + TILE - 1) / TILE : 0;
-        ns += (tb + spanT - 1) / spanT;
+        if (hi > lo) nt += (hi - (lo & ~3ull) + TILE - 1) / TILE;
         so.off[b] = lo;
     }
+    if (nt > STATIC_MAX_TILES) return NSML_ECAP;
     so.off[B] = n;
     for (uint32_t b = B + 1; b < STATIC_B1; ++b) so.off[b] = n;
 
@@ -925,14 +865,13 @@ int nsml_decompress_static(const uint32_t *idx, const void *val, const float *sc
 
     Tables t;
     memset(&t, 0, sizeof t);
-    t.off = m.off; t.tile0 = m.tile0; t.span0 = m.span0; t.span_b = m.span_b;
+    t.off = m.off; t.tile0 = m.tile0;
     t.k = m.k; t.kw = m.kw; t.P = m.P; t.V = m.V; t.S = m.S; t.C = m.C;
-    t.B = B; t.n_spans = (uint32_t)ns; t.spanT = spanT; t.segSh = 2; t.chunk = chunk; t.chunkSh = chunk_shift(chunk); t.dencSpans = 1;
-    LAUNCH(none, KID_SETUP, st, k_static_layout, 1, so, B, spanT, m.off, m.tile0, m.span0);
+    t.B = B; t.n_tiles = (uint32_t)nt; t.chunk = chunk; t.chunkSh = chunk_shift(chunk);
+    LAUNCH(none, KID_SETUP, st, k_static_layout, 1, so, B, m.off, m.tile0);
     LAUNCH(none, KID_SETUP, st, k_setup, 1, t, ratio, bits);
-    LAUNCH(none, KID_SPANMAP, st, k_spanmap, (uint32_t)((ns + WG - 1) / WG), (const uint32_t *)m.span0, B,
-           (uint32_t)ns, m.span_b);
-    return launch_decompress(none, st, t, K, (uint32_t)ns, (uint32_t)nt, m.ts, -1, -1, idx, val, scales, bits, dense_out);
+    LAUNCH(none, KID_TILEMAP, st, k_static_tilemap, (uint32_t)((nt + WG - 1) / WG), (const uint32_t *)m.tile0, B, (uint32_t)nt, m.tile_b);
+    return launch_decompress<uint16_t>(none, st, t, n, K, m.tile_b, m.ts, idx, val, scales, bits, dense_out, -1);
 }
 
 int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val, const float *scales,
@@ -952,14 +891,19 @@ int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val
     rc = ensure_tables(c, ratio, bits, st);
     if (rc) return rc;
     const Tables t = tables_of(c);
-    const uint64_t want = (c->K + WG - 1) / WG;
-    const uint32_t grid = (uint32_t)(want < 32768 ? want : 32768);
+    const uint32_t grid = (uint32_t)((c->K + WG * SCAT_PER - 1) / (WG * SCAT_PER));
+#define NSML_ACC(BITS_)                                                                                                       \
+    do {                                                                                                                       \
+        if (n > NT_ELEMS) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, true>), grid, idx, val, scales, t, c->K, dense_inout); \
+        else LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, false>), grid, idx, val, scales, t, c->K, dense_inout);             \
+    } while (0)
     switch (bits) {
-    case 32: LAUNCH(c, KID_DECOMP_ACC, st, k_decomp_acc<32>, grid, idx, val, scales, t, c->K, dense_inout); break;
-    case 16: LAUNCH(c, KID_DECOMP_ACC, st, k_decomp_acc<16>, grid, idx, val, scales, t, c->K, dense_inout); break;
-    case 8:  LAUNCH(c, KID_DECOMP_ACC, st, k_decomp_acc<8>,  grid, idx, val, scales, t, c->K, dense_inout); break;
-    default: LAUNCH(c, KID_DECOMP_ACC, st, k_decomp_acc<4>,  grid, idx, val, scales, t, c->K, dense_inout); break;
+    case 32: NSML_ACC(32); break;
+    case 16: NSML_ACC(16); break;
+    case 8:  NSML_ACC(8); break;
+    default: NSML_ACC(4); break;
     }
+#undef NSML_ACC
     return NSML_OK;
 }
 
@@ -1028,9 +972,10 @@ int nsml_bucket_state(nsml_ctx *c, uint32_t b, uint32_t *out8)
     if (!c || !out8 || b >= c->B) return NSML_EINVAL;
     DeviceGuard guard(c->device);
     NSML_HIP(c, hipDeviceSynchronize());
-    const uint32_t *src[8] = {c->d_fast, c->d_why, c->d_L, c->d_H, c->d_T, c->d_need, c->d_sh, c->d_k};
+    const uint32_t *par = reinterpret_cast<const uint32_t *>(c->d_par + b);
+    const uint32_t *src[8] = {c->d_fast + b, c->d_why + b, par, par + 1, c->d_T + b, c->d_need + b, c->d_sh + b, c->d_k + b};
     for (int i = 0; i < 8; ++i)
-        NSML_HIP(c, hipMemcpy(out8 + i, src[i] + b, sizeof(uint32_t), hipMemcpyDeviceToHost));
+        NSML_HIP(c, hipMemcpy(out8 + i, src[i], sizeof(uint32_t), hipMemcpyDeviceToHost));
     return NSML_OK;
 }
 
@@ -1045,7 +990,7 @@ int nsml_prune_stats(nsml_ctx *c, uint32_t *band_buckets, uint32_t *dense_bucket
     NSML_HIP(c, hipMemcpy(f.data(), c->d_wfast, sizeof(uint32_t) * c->B, hipMemcpyDeviceToHost));
     for (uint32_t b = 0; b < c->B; ++b) {
         if (c->h_off[b + 1] == c->h_off[b]) continue;
-        if (f[b]) *band_buckets += 1; else *dense_buckets += 1;
+        if (c->none_pruned || f[b]) *band_buckets += 1; else *dense_buckets += 1;
     }
     return *(volatile uint32_t *)&c->h_flags[1] ? NSML_EINTERNAL : NSML_OK;
 }
@@ -1066,31 +1011,22 @@ int nsml_set_option(nsml_ctx *c, const char *name, int value)
 {
     if (!c || !name) return NSML_EINVAL;
     auto is = [&](const char *s) { return strcmp(name, s) == 0; };
-    if (is("span_tiles")) {
-        if (value < 0 || value > MAX_SPAN_TILES) return NSML_EINVAL;
-        c->span_override = value;
-        c->B = 0;                              /* the geometry changes: rebuild the layout tables */
-        c->tables_valid = false;
+    if (is("span_tiles")) {                    /* this one and the next four: accepted, without effect */
+        if (value < 0 || value > 16) return NSML_EINVAL;
     } else if (is("seg_waves")) {
         if (value != 0 && value != 4 && value != 8 && value != 16) return NSML_EINVAL;
-        c->seg_override = value;
-        c->B = 0;
-        c->tables_valid = false;
-    } else if (is("force_dense")) {
-        if (value != 0 && value != 1) return NSML_EINVAL;
-        c->force_dense = value;
     } else if (is("nt")) {
         if (value != 1 && value != 3 && value != 5 && value != 7) return NSML_EINVAL;
-        c->nt_mode = value;
     } else if (is("nt_dense")) {
         if (value < -1 || value > 1) return NSML_EINVAL;
-        c->nt_dense = value;
     } else if (is("persist")) {
         if (value < 0 || value > 8) return NSML_EINVAL;
-        c->persist = value;
     } else if (is("decomp_variant")) {
         if (value < -1 || value > 1) return NSML_EINVAL;
         c->decomp_variant = value;
+    } else if (is("force_dense")) {
+        if (value != 0 && value != 1) return NSML_EINVAL;
+        c->force_dense = value;
     } else if (is("rescan")) {
         if (value != 0 && value != 1) return NSML_EINVAL;
         c->force_rescan = value;

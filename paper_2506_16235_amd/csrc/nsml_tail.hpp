@@ -36,8 +36,8 @@ namespace {
 
 constexpr uint32_t SEL_THREADS = 1024;     /* k_select_finish workgroup: 16 wavefronts */
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
-constexpr uint32_t SEL_SEGS_PER_WAVE = 4;
-constexpr uint32_t ENC_BLK = WG * 8;       /* survivors gathered in LDS at a time */
+constexpr uint32_t ENC_T = 512, ENC_WAVES = ENC_T / 64;     /* k_encode workgroup */
+constexpr uint32_t ENC_BLK = 2048;         /* survivors gathered in LDS at a time */
 
 /* Inclusive scan of 64-bit values over a workgroup of NW wavefronts; tmp: NW words of LDS. */
 template <uint32_t NW>
@@ -88,12 +88,12 @@ __device__ __forceinline__ bool find_digit_lds(const uint32_t *h, uint32_t want,
 }
 
 /* Largest i in [lo, hi) with f(i) <= x, for a non-decreasing f with f(lo) <= x; the whole
- * workgroup of 256 threads searches, 256 probes a round.  sh: one word of LDS. */
-template <typename F>
+ * workgroup of NT threads searches, NT probes a round.  sh: one word of LDS. */
+template <uint32_t NT, typename F>
 __device__ __forceinline__ uint32_t wg_search_le(uint32_t lo, uint32_t hi, uint64_t x, F f, uint32_t *sh)
 {
     while (hi - lo > 1) {
-        const uint32_t step = (hi - lo + 255u) / 256u;
+        const uint32_t step = (hi - lo + NT - 1u) / NT;
         const uint32_t p = lo + threadIdx.x * step, q = p + step;
         if (p < hi && f(p) <= x && (q >= hi || x < f(q))) *sh = p;
         __syncthreads();
@@ -121,20 +121,20 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 
 /* ------------------------------------------------------------------ k_select_count */
 
-constexpr uint32_t SELC_WAVES = WG / 64;
-constexpr uint32_t SELC_SEGS = SELC_WAVES * SEL_SEGS_PER_WAVE;     /* segments per workgroup of k_select_count */
+constexpr uint32_t SELC_SEGS = 64;         /* most segments per workgroup of k_select_count: one per lane */
+constexpr uint32_t SELC_ROWS = 8;          /* rows of 64 entries a wavefront has in flight */
 
 /* Work list of k_select_count, fixed by the bucket layout: workgroup w takes segments
  * [x.y, x.z) of bucket x.x. */
-__global__ __launch_bounds__(WG) void k_selmap(const uint32_t *__restrict__ sel0, const uint32_t *__restrict__ span0,
-                                               uint32_t B, uint32_t n_sel, uint32_t segSh, uint4 *__restrict__ selw)
+__global__ __launch_bounds__(WG) void k_selmap(const uint32_t *__restrict__ sel0, const uint32_t *__restrict__ tile0,
+                                               uint32_t B, uint32_t n_sel, uint32_t selSh, uint4 *__restrict__ selw)
 {
     const uint32_t w = blockIdx.x * WG + threadIdx.x;
     if (w >= n_sel) return;
     const uint32_t b = find_bucket<uint32_t>(sel0, B, w);
-    const uint32_t seg_lo = span0[b] << segSh, seg_hi = span0[b + 1] << segSh;
-    const uint32_t s0 = seg_lo + (w - sel0[b]) * SELC_SEGS;
-    selw[w] = make_uint4(b, s0, min(seg_hi, s0 + SELC_SEGS), 0u);
+    const uint32_t seg_lo = tile0[b], seg_hi = tile0[b + 1];
+    const uint32_t s0 = seg_lo + ((w - sel0[b]) << selSh);
+    selw[w] = make_uint4(b, s0, min(seg_hi, s0 + (1u << selSh)), 0u);
 }
 
 /* chunk -> bucket, fixed by the layout and (ratio, bits) */
@@ -145,7 +145,7 @@ __global__ __launch_bounds__(WG) void k_chunkmap(const uint64_t *__restrict__ C,
     if (c < NC) chunk_b[c] = find_bucket<uint64_t>(C, B, c);
 }
 
-constexpr uint32_t LCAP = SELC_SEGS * 128;            /* list entries per workgroup of k_select_count */
+constexpr uint32_t LIST_PER_SEG = 64, LCAP = SELC_SEGS * LIST_PER_SEG;           /* list entries per workgroup of k_select_count */
 /* a list entry: the 19 key bits below the level-0 digit, and above them the segment's number inside the workgroup */
 __device__ __forceinline__ uint32_t list_entry(uint32_t key, uint32_t segl) { return (segl << SH0) | (key & ((1u << SH0) - 1u)); }
 
@@ -158,16 +158,11 @@ struct DenseSeg {
 };
 __device__ __forceinline__ DenseSeg dense_seg(const Tables &t, uint32_t b, uint32_t ss)
 {
-    const uint32_t span = ss >> t.segSh, wv = ss & ((1u << t.segSh) - 1u);
-    const SpanGeo s = span_geo_b(t, b, span - t.span0[b]);
-    const uint32_t per = (t.spanT * 4u) >> t.segSh;
-    const uint32_t wt0 = wv * per, wt1 = min(s.ntiles * 4u, wt0 + per);
+    const TileGeo s = tile_geo(t, b, ss);
+    const uint64_t z = min(s.hi, s.base + (uint64_t)TILE);
     DenseSeg d;
-    d.e0 = 0; d.len = 0;
-    if (wt1 > wt0) {
-        const uint64_t a = max(s.lo, s.base + (uint64_t)wt0 * WTILE), z = min(s.hi, s.base + (uint64_t)wt1 * WTILE);
-        if (z > a) { d.e0 = a; d.len = (uint32_t)(z - a); }
-    }
+    d.e0 = max(s.lo, s.base);
+    d.len = (uint32_t)(z - d.e0);
     return d;
 }
 /* whether element e (global index) of a bucket whose first tile is tile0b and starts at lo_al
@@ -177,147 +172,184 @@ __device__ __forceinline__ bool pruned_elem(const uint32_t *__restrict__ pmask, 
     const uint64_t pos = e - lo_al;
     return (pmask[(uint64_t)(tile0b + (uint32_t)(pos / TILE)) * (TILE / 32) + (uint32_t)((pos % TILE) >> 5)] >> (pos & 31u)) & 1u;
 }
-struct DenseSrc {
-    const float *r;              /* the dense accumulator */
-    const uint32_t *pmask;       /* NULL: nothing is pruned */
-    uint32_t tile0b;
-    uint64_t lo_al;
-};
 
-/* One wavefront's four segments of k_select_count, GROUP lanes per segment (16: all four at
- * once, 64: one after the other).  mlen != 0 in the lane that describes a segment: the segment
- * overflowed and is read from the dense accumulator (me0, mlen). */
-template <uint32_t GROUP, bool DENSE>      /* DENSE: some segment of this wavefront is read from the accumulator */
-__device__ __forceinline__ void select_count_wave(const Cand &c, uint32_t b0, uint32_t sh, uint32_t wseg0, uint32_t mcnt,
-                                                  uint64_t me0, uint32_t mlen, const DenseSrc &ds,
-                                                  uint32_t segl0, uint32_t *lk, uint32_t *lcur,
-                                                  uint32_t &my_g, uint32_t &my_b)
+/* The window's bins of large gradients, from the staged elements (and from the dense source `r` where a
+ * segment overflowed): a workgroup takes the segments of one workgroup of k_select_count, 16 or 4
+ * lanes each, counts in LDS and adds what it has to one of the bucket's copies.  Bound by reading the
+ * staged values (419 M elements at ratio 0.5, 3 % staged: 30 us; 109 M at 0.01: 10). */
+constexpr uint32_t BINS_U = 8;             /* entries a lane has in flight */
+__global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
+                                             uint32_t *__restrict__ hist, const float *__restrict__ r)
 {
-    constexpr uint32_t SPR = 64 / GROUP;             /* segments per round */
-    constexpr uint32_t ROUNDS = SEL_SEGS_PER_WAVE / SPR;
-    const uint32_t lane = threadIdx.x & 63, sub = lane / GROUP, gl = lane % GROUP;
-    const uint32_t shift = sub * GROUP;
-    const uint64_t below = (1ull << gl) - 1ull;
-    const uint64_t gmask = GROUP == 64 ? ~0ull : ((1ull << (GROUP % 64)) - 1ull);
-    uint32_t *cvalu = reinterpret_cast<uint32_t *>(c.val);
+    __shared__ uint32_t h[NHB];
+    const uint4 wk = selw[blockIdx.x];
+    const uint32_t b = wk.x, s0 = wk.y, s1 = wk.z, tid = threadIdx.x;
+    const uint32_t lanes = WG >> selSh, seg = s0 + (tid >> (8u - selSh)), gl = tid & (lanes - 1u);
+    const uint32_t cnt = seg < s1 ? c.cnt[seg] : 0u;
+    const KeyPar p = t.par[b];
+    if (p.x == NONE || p.x == p.y) return;           /* nothing was staged; the same for the whole workgroup */
+    if (!__syncthreads_or(cnt != 0u)) return;
+    for (uint32_t i = tid; i < (uint32_t)NHB; i += WG) h[i] = 0u;
+    const uint32_t top = (p.z - 1u) >> p.w;
+    auto count = [&](uint32_t key) { if (key < p.z) atomicAdd(&h[min(top - (key >> p.w), (uint32_t)NHB - 1u)], 1u); };
+    __syncthreads();
+    const uint32_t len = cnt > SEG_CAP ? 0u : cnt;
+    const float *v = c.val + (uint64_t)seg * SEG_CAP;
+    for (uint32_t i0 = gl; i0 < len; i0 += lanes * BINS_U) {
+        float x[BINS_U];
 #pragma unroll
-    for (uint32_t rd = 0; rd < ROUNDS; ++rd) {
-        const uint32_t src = rd * SPR + sub;
-        const uint32_t staged = __shfl(mcnt, src, 64);
-        const uint32_t dlen = DENSE ? __shfl(mlen, src, 64) : 0u;
-        const bool dense = DENSE && dlen != 0u;
-        const uint64_t e0 = DENSE ? ((uint64_t)__shfl((uint32_t)(me0 >> 32), src, 64) << 32) | (uint64_t)__shfl((uint32_t)me0, src, 64) : 0ull;
-        const uint32_t cnt = dense ? dlen : staged;
-        uint32_t maxcnt = cnt;
+        for (uint32_t u = 0; u < BINS_U; ++u) x[u] = i0 + u * lanes < len ? v[i0 + u * lanes] : 0.0f;
 #pragma unroll
-        for (int d = 32; d >= (int)GROUP; d >>= 1) maxcnt = max(maxcnt, (uint32_t)__shfl_xor(maxcnt, d, 64));
-        const uint64_t base = (uint64_t)(wseg0 + src) * c.cap;
-        const float *p = dense ? ds.r + e0 : c.val + base;
-        uint32_t run_g = 0, run_b = 0;
-        for (uint32_t i0 = 0; i0 < maxcnt; i0 += 2 * CU * GROUP) {
-            float x[2 * CU];
-#pragma unroll
-            for (uint32_t u = 0; u < 2 * CU; ++u) {
-                const uint32_t i = i0 + u * GROUP + gl;
-                x[u] = i < cnt ? p[i] : 0.0f;
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < 2 * CU; ++u) {
-                const uint32_t key = keyof(x[u]);
-                const uint32_t i = i0 + u * GROUP + gl;
-                bool in = i < cnt;
-                if (dense && ds.pmask && in) in = !pruned_elem(ds.pmask, ds.tile0b, ds.lo_al, e0 + i);
-                const bool isg = in && (key >> sh) > b0, isb = in && (key >> sh) == b0;
-                const uint64_t ball = __ballot(isb);
-                const uint64_t bg = (__ballot(isg) >> shift) & gmask;
-                const uint64_t bb = (ball >> shift) & gmask;
-                if (ball) {
-                    /* undecided keys: to the tail of the segment's area (last slot first) and to the
-                     * workgroup's list, whose slots are handed out per wavefront */
-                    uint32_t lbase = 0;
-                    if (lane == 0) lbase = atomicAdd(lcur, (uint32_t)__popcll(ball));
-                    lbase = __builtin_amdgcn_readfirstlane(lbase);
-                    if (isb) {
-                        const uint32_t pos = run_b + __popcll(bb & below);
-                        if (!dense && cnt + pos < c.cap) cvalu[base + c.cap - 1u - pos] = key;
-                        const uint32_t lp = lbase + __popcll(ball & ((1ull << lane) - 1ull));
-                        if (lp < LCAP) lk[lp] = list_entry(key, segl0 + src);
-                    }
-                }
-                run_g += __popcll(bg);
-                run_b += __popcll(bb);
+        for (uint32_t u = 0; u < BINS_U; ++u) if (i0 + u * lanes < len) count(keyof(x[u]));
+    }
+    if (t.ovf[b]) {
+        for (uint32_t s = s0; s < s1; ++s) {
+            if (c.cnt[s] <= SEG_CAP) continue;       /* same for the whole workgroup */
+            const DenseSeg d = dense_seg(t, b, s);
+            const uint32_t tile0b = t.tile0[b];
+            const uint64_t lo_al = t.off[b] & ~3ull;
+            for (uint32_t e = tid; e < d.len; e += WG) {
+                const uint32_t key = keyof(r[d.e0 + e]);
+                if (key >= p.x && !(t.pmask && pruned_elem(t.pmask, tile0b, lo_al, d.e0 + e))) count(key);
             }
         }
-        /* segment rd * SPR + j was counted by the group of lanes starting at j * GROUP */
-        const uint32_t from = (lane % SPR) * GROUP;
-        const uint32_t got_g = __shfl(run_g, from, 64), got_b = __shfl(run_b, from, 64);
-        if (lane / SPR == rd) { my_g = got_g; my_b = got_b; }
     }
+    __syncthreads();
+    hist_flush(h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * NHB, NHB);
 }
 
 /* Per staging segment of the buckets decided from staged elements (PATH_CAND, PATH_BAND), with
- * b0 the level-0 digit of the bucket's k-th key: G = entries above digit b0 (plus, in band mode,
- * the elements above the band the streaming pass counted), E = entries inside digit b0.  The keys of those undecided entries go to two places: the unused tail of the segment's
- * staging area, last slot first (as long as there is room), and a list per workgroup (the
- * undecided key bits and the segment's number in one word, in no particular order) that k_select_finish reads with coalesced loads; the
- * list is left out (lcnt = NONE) when the workgroup has more than LCAP of them.
- * A workgroup takes 16 consecutive segments, a wavefront four of them, with 16 lanes per
- * segment, or all 64 on one segment after the other when a segment is long. */
-__global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw,
+ * b0 the leading bits of the bucket's k-th key: G = entries above b0 (plus, in band mode, the elements
+ * above the band the streaming pass counted), E = entries that share b0.  The keys of those undecided
+ * entries go to two places: the unused tail of the segment's staging area, last slot first (as long
+ * as there is room), and a list per workgroup (the undecided key bits and the segment's number in
+ * one word, in no particular order) that k_select_finish reads with coalesced loads; the
+ * list is left out (lcnt = NONE) when the workgroup has more than LIST_PER_SEG a segment.
+ * A workgroup takes 16 or 64 consecutive segments (1 << selSh) as one list of entries, dealt to its four wavefronts row
+ * by row (64 entries), so its work follows the number of entries and not the longest segment; lane l
+ * of every wavefront keeps the count of segment l, from the ballots of the rows and the part of each row
+ * that belongs to it. */
+__global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
                                                      uint32_t *__restrict__ tail_ovf, uint32_t *__restrict__ lcnt,
                                                      uint32_t *__restrict__ lkey, const float *__restrict__ r)
 {
     __shared__ uint32_t lk[LCAP];
+    __shared__ uint32_t pre[SELC_SEGS], cg[SELC_SEGS], cb[SELC_SEGS];
     __shared__ uint32_t lcur;
     const uint4 wk = selw[blockIdx.x];
     const uint32_t b = wk.x, s0 = wk.y, s1 = wk.z;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t wseg0 = s0 + wave * SEL_SEGS_PER_WAVE;
-    /* lane l < 4 describes segment wseg0 + l; issued before the bucket's state is known */
-    const uint32_t ms = wseg0 + (lane & (SEL_SEGS_PER_WAVE - 1));
-    const bool mine = lane < SEL_SEGS_PER_WAVE && ms < s1;
+    /* issued before the bucket's state is known */
+    const uint32_t ms = s0 + lane;
+    const bool mine = ms < s1;
+    const uint32_t lcap = LIST_PER_SEG << selSh;
     const uint32_t mcnt = mine ? c.cnt[ms] : 0u;
     uint32_t mg0 = mine ? c.G[ms] : 0u;              /* band mode: elements above the band, counted by the streaming pass */
     const uint32_t path = t.fast[b], b0 = t.T[b], sh = t.sh[b];     /* b0: the key bits from position sh up */
     if (path != PATH_CAND && path != PATH_BAND) return;      /* same for the whole workgroup */
-    if (t.H[b] == NONE) mg0 = 0u;                    /* no band was staged: nothing was counted above it */
+    if (t.par[b].y == NONE) mg0 = 0u;                /* no band was staged: the staged entries hold everything above */
+    const bool dense = mcnt > SEG_CAP;               /* an overflowed segment is read from the dense accumulator, where nothing is missing */
+    const uint32_t len = dense ? 0u : mcnt;
+    const uint32_t seg_end = wave_incl_scan(len), seg_start = seg_end - len;
+    const uint32_t total = __builtin_amdgcn_readlane(seg_end, 63);
+    if (wave == 0) { pre[lane] = seg_start; cg[lane] = 0u; cb[lane] = 0u; }
     if (tid == 0) lcur = 0u;
     __syncthreads();
-    /* an overflowed segment is read from the dense accumulator, where nothing is missing */
-    uint64_t me0 = 0;
-    uint32_t mlen = 0;
-    if (mine && mcnt > c.cap) {
-        const DenseSeg d = dense_seg(t, b, ms);
-        me0 = d.e0; mlen = d.len;
-        mg0 = 0u;                                    /* its elements above the band are counted here as well */
-    }
-    DenseSrc ds;
-    ds.r = r; ds.pmask = t.pmask; ds.tile0b = t.tile0[b]; ds.lo_al = t.off[b] & ~3ull;
-    uint32_t mx = mlen ? mlen : mcnt;
+    uint32_t *cvalu = reinterpret_cast<uint32_t *>(c.val);
+    /* an undecided key of segment s (of this workgroup) */
+    auto undecided = [&](uint32_t key, uint32_t s, uint32_t cnt, bool tail) {
+        const uint32_t pos = atomicAdd(&cb[s], 1u);
+        if (tail && cnt + pos < SEG_CAP) cvalu[(uint64_t)(s0 + s) * SEG_CAP + SEG_CAP - 1u - pos] = key;
+        const uint32_t lp = atomicAdd(&lcur, 1u);
+        if (lp < lcap) lk[lp] = list_entry(key, s);
+    };
+    uint32_t my_g = 0;
+    const bool crowded = total >= 32u * (s1 - s0);   /* half a row per segment and more: a wavefront takes a whole segment */
+    if (crowded) {
+        for (uint32_t q = wave; q < s1 - s0; q += WG / 64) {
+            const uint32_t cnt = __builtin_amdgcn_readlane(len, q);
+            const float *p = c.val + (uint64_t)(s0 + q) * SEG_CAP;
+            float x[SEG_CAP / 64];
 #pragma unroll
-    for (int d = 2; d >= 1; d >>= 1) mx = max(mx, (uint32_t)__shfl_xor(mx, d, 64));
-    mx = __builtin_amdgcn_readfirstlane(mx);
-    uint32_t my_g = 0, my_b = 0;
-    if (__any(mlen != 0u)) {
-        if (mx > 2 * CU * 16) select_count_wave<64, true>(c, b0, sh, wseg0, mcnt, me0, mlen, ds, wave * SEL_SEGS_PER_WAVE, lk, &lcur, my_g, my_b);
-        else if (mx) select_count_wave<16, true>(c, b0, sh, wseg0, mcnt, me0, mlen, ds, wave * SEL_SEGS_PER_WAVE, lk, &lcur, my_g, my_b);
-    } else {
-        if (mx > 2 * CU * 16) select_count_wave<64, false>(c, b0, sh, wseg0, mcnt, me0, mlen, ds, wave * SEL_SEGS_PER_WAVE, lk, &lcur, my_g, my_b);
-        else if (mx) select_count_wave<16, false>(c, b0, sh, wseg0, mcnt, me0, mlen, ds, wave * SEL_SEGS_PER_WAVE, lk, &lcur, my_g, my_b);
+            for (uint32_t u = 0; u < SEG_CAP / 64; ++u) { const uint32_t i = u * 64 + lane; x[u] = i < cnt ? p[i] : 0.0f; }
+            uint32_t g = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < SEG_CAP / 64; ++u) {
+                if (u * 64 >= cnt) break;            /* same for the whole wavefront */
+                const uint32_t key = keyof(x[u]);
+                const bool in = u * 64 + lane < cnt;
+                g += __popcll(__ballot(in && (key >> sh) > b0));
+                if (in && (key >> sh) == b0) undecided(key, q, cnt, true);
+            }
+            if (lane == q) my_g = g;
+        }
     }
-    if (mine) {
-        c.G[ms] = mg0 + my_g;
+    for (uint32_t i0 = wave * 64; !crowded && i0 < total; i0 += SELC_ROWS * WG) {
+        float x[SELC_ROWS];
+        uint32_t sg[SELC_ROWS];
+#pragma unroll
+        for (uint32_t u = 0; u < SELC_ROWS; ++u) {
+            const uint32_t i = i0 + u * WG + lane;
+            uint32_t q = 0;                          /* the last segment that starts at or before i */
+#pragma unroll
+            for (uint32_t st = SELC_SEGS / 2; st >= 1; st >>= 1) q += pre[q + st] <= i ? st : 0u;
+            sg[u] = q;
+            x[u] = i < total ? c.val[(uint64_t)(s0 + q) * SEG_CAP + (i - pre[q])] : 0.0f;
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < SELC_ROWS; ++u) {
+            const uint32_t r0 = i0 + u * WG;
+            if (r0 >= total) break;                  /* same for the whole wavefront */
+            const uint32_t key = keyof(x[u]);
+            const bool in = r0 + lane < total;
+            const uint64_t bg = __ballot(in && (key >> sh) > b0);
+            const bool isb = in && (key >> sh) == b0;
+            /* the part of this row that belongs to segment `lane` */
+            const uint32_t pa = seg_start > r0 ? min(seg_start - r0, 64u) : 0u, pz = seg_end > r0 ? min(seg_end - r0, 64u) : 0u;
+            const uint64_t ma = pa >= 64u ? ~0ull : (1ull << pa) - 1ull, mz = pz >= 64u ? ~0ull : (1ull << pz) - 1ull;
+            my_g += __popcll(bg & mz & ~ma);
+            if (__any(isb)) {
+                const uint32_t cnt = __shfl(mcnt, sg[u], 64);
+                if (isb) undecided(key, sg[u], cnt, true);
+            }
+        }
+    }
+    if (my_g) atomicAdd(&cg[lane], my_g);
+    uint64_t todo = __ballot(dense);                 /* the same in every wavefront */
+    while (todo) {
+        const uint32_t q = (uint32_t)__builtin_ctzll(todo);
+        todo &= todo - 1ull;
+        const DenseSeg d = dense_seg(t, b, s0 + q);
+        const uint32_t tile0b = t.tile0[b];
+        const uint64_t lo_al = t.off[b] & ~3ull;
+        float x[TILE / WG];
+#pragma unroll
+        for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; x[u] = e < d.len ? r[d.e0 + e] : 0.0f; }
+        uint32_t g = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < TILE / WG; ++u) {
+            const uint32_t e = u * WG + tid, key = keyof(x[u]);
+            bool in = e < d.len;
+            if (t.pmask && in) in = !pruned_elem(t.pmask, tile0b, lo_al, d.e0 + e);
+            g += __popcll(__ballot(in && (key >> sh) > b0));
+            if (in && (key >> sh) == b0) undecided(key, q, 0u, false);
+        }
+        if (lane == 0) atomicAdd(&cg[q], g);
+    }
+    __syncthreads();
+    if (wave == 0 && mine) {
+        const uint32_t my_b = cb[lane];
+        c.G[ms] = (dense ? 0u : mg0) + cg[lane];     /* of a dense one the elements above the band were counted here as well */
         c.E[ms] = my_b;
         /* a tail that did not fit (or a segment without one): k_select_finish filters the entries again
          * if it cannot use the lists */
-        if (my_b != 0u && (mlen != 0u || mcnt + my_b > c.cap)) tail_ovf[b] = 1u;
+        if (my_b != 0u && (dense || mcnt + my_b > SEG_CAP)) tail_ovf[b] = 1u;
     }
-    __syncthreads();
-    const uint32_t total = lcur;
-    if (tid == 0) lcnt[blockIdx.x] = total > LCAP ? NONE : total;
-    if (total <= LCAP) {
-        const uint64_t lb = (uint64_t)blockIdx.x * LCAP;
-        for (uint32_t i = tid; i < total; i += WG) lkey[lb + i] = lk[i];
+    const uint32_t nl = lcur;
+    if (tid == 0) lcnt[blockIdx.x] = nl > lcap ? NONE : nl;
+    if (nl <= lcap) {
+        const uint64_t lb = (uint64_t)blockIdx.x * lcap;
+        for (uint32_t i = tid; i < nl; i += WG) lkey[lb + i] = lk[i];
     }
 }
 
@@ -328,7 +360,7 @@ __global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uin
 struct KeySource {
     const uint32_t *cvalu;
     const uint32_t *cnt;
-    uint32_t cap, b0, sh;
+    uint32_t b0, sh;
     bool rescan;
     const Tables *t;             /* for the segments that overflowed: they are read from the dense accumulator */
     const float *r;
@@ -339,7 +371,7 @@ struct KeySource {
     __device__ __forceinline__ void for_each(uint32_t s, uint32_t bcnt, F f) const
     {
         const uint32_t staged = cnt[s];
-        if (rescan && staged > cap) {
+        if (rescan && staged > SEG_CAP) {
             const DenseSeg d = dense_seg(*t, b, s);
             const uint32_t tile0b = t->tile0[b];
             const uint64_t lo_al = t->off[b] & ~3ull;
@@ -354,12 +386,12 @@ struct KeySource {
             return;
         }
         const uint32_t nw = rescan ? staged : bcnt;
-        const uint64_t base = (uint64_t)s * cap;
+        const uint64_t base = (uint64_t)s * SEG_CAP;
         for (uint32_t i = 0; i < nw; i += 8) {
             uint32_t kk[8];
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u)
-                kk[u] = i + u < nw ? (rescan ? (cvalu[base + i + u] & 0x7FFFFFFFu) : cvalu[base + cap - 1u - (i + u)]) : 0u;
+                kk[u] = i + u < nw ? (rescan ? (cvalu[base + i + u] & 0x7FFFFFFFu) : cvalu[base + SEG_CAP - 1u - (i + u)]) : 0u;
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u)
                 if (i + u < nw && wanted(kk[u])) f(kk[u]);
@@ -368,15 +400,17 @@ struct KeySource {
 };
 
 /* LDS of k_select_finish, one pool carved by both variants below (u32 words):
- *   [0, 4096)        level-1 histogram; later, with [4096, 8192), the per-segment counts (lists) /
- *   [4096, 8192)     per-segment key counts as u16 (tails)
- *   [8192, 11264)    undecided keys kept in LDS
- *   [11264, 12800)   their segment numbers as u16 (lists)
- *   [12800, 13826)   exclusive prefix of the list lengths (lists) */
-constexpr uint32_t FIN_POOL = 13826;
+ *   [0, 4096)        level-1 histogram; later, up to FIN_MAX_SEGS, the per-segment counts (lists)
+ *   [4096, +8192)    per-segment key counts as u16 (tails)
+ *   FIN_AT_KEYS      undecided keys kept in LDS
+ *   FIN_AT_SEGS      their segment numbers as u16 (lists)
+ *   FIN_AT_UOFF      exclusive prefix of the list lengths (lists) */
 constexpr uint32_t FIN_KEYS_LDS = 3072;    /* undecided keys kept in LDS */
-constexpr uint32_t FIN_MAX_SEGS = 8192;    /* segments whose counts fit the pool */
+constexpr uint32_t FIN_MAX_SEGS = 16384;   /* segments whose counts fit the pool */
+constexpr uint32_t FIN_AT_KEYS = FIN_MAX_SEGS, FIN_AT_SEGS = FIN_AT_KEYS + FIN_KEYS_LDS, FIN_AT_UOFF = FIN_AT_SEGS + FIN_KEYS_LDS / 2;
+constexpr uint32_t FIN_POOL = FIN_AT_UOFF + SEL_THREADS + 2;
 constexpr uint32_t RQ = FIN_MAX_SEGS / SEL_THREADS;
+static_assert(NB1 + FIN_MAX_SEGS / 2 <= FIN_AT_KEYS, "the counts of the tails variant overlap the keys");
 
 struct FinShared {
     uint32_t *pool;      /* FIN_POOL words */
@@ -387,39 +421,51 @@ struct FinShared {
 
 /* Last part of both variants: exclusive prefixes of (elements above T, elements equal to T) over
  * the bucket's segments, in place over the per-segment counts, and for every chunk of the
- * payload the segment that holds its first survivor.  count(r, s, g, q) adds to g and q what
- * segment s (round r) holds above / equal to T among its undecided keys. */
-template <typename F>
+ * payload the segment that holds its first survivor.  A round takes PER consecutive segments per
+ * thread.  count(r, s, g, q) adds to g and q what segment s (round r) holds above / equal to T among its
+ * undecided keys. */
+template <uint32_t PER, typename F>
 __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, uint32_t b, uint32_t seg_lo,
                                                 uint32_t seg_hi, uint32_t T, uint32_t e_b, uint32_t kb,
                                                 uint32_t *__restrict__ chunk_seg, uint64_t *tmp,
                                                 uint32_t *__restrict__ err, F count)
 {
     const uint32_t tid = threadIdx.x;
-    const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS - 1) / SEL_THREADS;
+    const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS * PER - 1) / (SEL_THREADS * PER);
     const uint64_t Cb = t.C[b];
     const uint32_t chunk = t.chunk;
     uint64_t run = 0;
-    uint32_t g_next = seg_lo + tid < seg_hi ? c.G[seg_lo + tid] : 0u;
+    uint32_t g_next[PER];
+#pragma unroll
+    for (uint32_t j = 0; j < PER; ++j) { const uint32_t s = seg_lo + tid * PER + j; g_next[j] = s < seg_hi ? c.G[s] : 0u; }
     for (uint32_t r = 0; r < rounds; ++r) {
-        const uint32_t s = seg_lo + r * SEL_THREADS + tid;
-        const bool in = s < seg_hi;
-        uint32_t g = g_next, q = 0;
-        if (r + 1 < rounds) g_next = s + SEL_THREADS < seg_hi ? c.G[s + SEL_THREADS] : 0u;   /* fetched under this round's work */
-        count(r, s, g, q);
-        const uint64_t v = ((uint64_t)g << 32) | (uint64_t)q;
+        const uint32_t s0 = seg_lo + (r * SEL_THREADS + tid) * PER;
+        uint64_t v[PER], sum = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            uint32_t g = g_next[j], q = 0;
+            if (r + 1 < rounds) { const uint32_t sn = s0 + SEL_THREADS * PER + j; g_next[j] = sn < seg_hi ? c.G[sn] : 0u; }   /* fetched under this round's work */
+            count(r, s0 + j, g, q);
+            v[j] = ((uint64_t)g << 32) | (uint64_t)q;
+            sum += v[j];
+        }
         uint64_t tt;
-        const uint64_t incl = block_incl_scan64<SEL_WAVES>(v, tmp, tt);
-        const uint64_t excl = run + incl - v;
-        if (in) {
-            const uint32_t Gp = (uint32_t)(excl >> 32), Ep = (uint32_t)excl;
-            c.G[s] = Gp;
-            c.E[s] = Ep;
-            /* survivors of this segment have ranks [r0, r1): the chunks that start among them */
-            const uint64_t r0 = (uint64_t)Gp + min(e_b, Ep);
-            const uint64_t r1 = (uint64_t)Gp + g + min((uint64_t)e_b, (uint64_t)Ep + q);
-            if (chunk_seg)                           /* not for the weight stage: its ranks are no payload positions */
-                for (uint64_t cb = (r0 + chunk - 1) / chunk; cb * chunk < r1; ++cb) chunk_seg[Cb + cb] = s;
+        const uint64_t incl = block_incl_scan64<SEL_WAVES>(sum, tmp, tt);
+        uint64_t excl = run + incl - sum;
+#pragma unroll
+        for (uint32_t j = 0; j < PER; ++j) {
+            const uint32_t s = s0 + j;
+            if (s < seg_hi) {
+                const uint32_t Gp = (uint32_t)(excl >> 32), Ep = (uint32_t)excl;
+                c.G[s] = Gp;
+                c.E[s] = Ep;
+                /* survivors of this segment have ranks [r0, r1): the chunks that start among them */
+                const uint64_t r0 = (uint64_t)Gp + min(e_b, Ep);
+                const uint64_t r1 = (uint64_t)Gp + (v[j] >> 32) + min((uint64_t)e_b, (uint64_t)Ep + (uint32_t)v[j]);
+                if (chunk_seg && r1 > r0)                /* not for the weight stage: its ranks are no payload positions */
+                    for (uint64_t cb = (r0 + chunk - 1) / chunk; cb * chunk < r1; ++cb) chunk_seg[Cb + cb] = s;
+            }
+            excl += v[j];
         }
         run += tt;
     }
@@ -439,14 +485,14 @@ __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, 
  * keys inside d1 are set aside in LDS for the last 7 bits. */
 __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c, uint32_t b, uint32_t b0, uint32_t sh,
                                                   uint32_t need0, uint32_t kb, uint32_t seg_lo, uint32_t seg_hi,
-                                                  uint32_t u0, uint32_t nun, uint32_t my_cnt,
+                                                  uint32_t u0, uint32_t nun, uint32_t my_cnt, uint32_t selSh,
                                                   const uint32_t *__restrict__ lkey,
                                                   uint32_t *__restrict__ chunk_seg, const FinShared &sm,
                                                   uint32_t *__restrict__ err)
 {
     const uint32_t tid = threadIdx.x;
-    uint32_t *h1 = sm.pool, *cnts = sm.pool, *keys = sm.pool + 8192, *uoff = sm.pool + 12800;
-    uint16_t *segs = reinterpret_cast<uint16_t *>(sm.pool + 11264);
+    uint32_t *h1 = sm.pool, *cnts = sm.pool, *keys = sm.pool + FIN_AT_KEYS, *uoff = sm.pool + FIN_AT_UOFF;
+    uint16_t *segs = reinterpret_cast<uint16_t *>(sm.pool + FIN_AT_SEGS);
     for (uint32_t i = tid; i < NB1; i += SEL_THREADS) h1[i] = 0u;
     if (tid < NB2) sm.h2[tid] = 0u;
     if (tid == 0) sm.res[3] = 0u;                      /* entries set aside */
@@ -470,12 +516,12 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
                     uint32_t lo = 0, hi = nun;         /* uoff[lo] <= i < uoff[hi] */
                     while (hi - lo > 1) { const uint32_t mid = (lo + hi) >> 1; if (uoff[mid] <= i) lo = mid; else hi = mid; }
                     un[u] = lo;
-                    kk[u] = lkey[(uint64_t)(u0 + lo) * LCAP + (i - uoff[lo])];
+                    kk[u] = lkey[((uint64_t)(u0 + lo) << selSh) * LIST_PER_SEG + (i - uoff[lo])];
                 }
             }
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u)
-                if (i0 + u * SEL_THREADS < nkeys) f(i0 + u * SEL_THREADS, kk[u], un[u] * SELC_SEGS + (kk[u] >> SH0));
+                if (i0 + u * SEL_THREADS < nkeys) f(i0 + u * SEL_THREADS, kk[u], (un[u] << selSh) + (kk[u] >> SH0));
         }
     };
     /* pass 1: level-1 digits (key bits 18..7); entries and segment numbers to LDS if they fit */
@@ -531,7 +577,7 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
         for_keys([&](uint32_t, uint32_t e, uint32_t seg) { pass3(e, seg); });      /* too many were inside d1 */
     }
     __syncthreads();
-    finish_prefixes(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
+    finish_prefixes<4>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
                     [&](uint32_t, uint32_t s, uint32_t &g, uint32_t &q) {
                         if (s < seg_hi) { const uint32_t v = cnts[s - seg_lo]; g += v >> 16; q += v & 0xFFFFu; }
                     });
@@ -548,10 +594,10 @@ __device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c
                                                   const float *__restrict__ r)
 {
     const uint32_t tid = threadIdx.x;
-    uint32_t *h1 = sm.pool, *keys = sm.pool + 8192;
-    uint16_t *sbc = reinterpret_cast<uint16_t *>(sm.pool + 4096);
+    uint32_t *h1 = sm.pool, *keys = sm.pool + FIN_AT_KEYS;
+    uint16_t *sbc = reinterpret_cast<uint16_t *>(sm.pool + NB1);
     KeySource ks;
-    ks.cvalu = reinterpret_cast<const uint32_t *>(c.val); ks.cnt = c.cnt; ks.cap = c.cap; ks.b0 = b0; ks.sh = sh;
+    ks.cvalu = reinterpret_cast<const uint32_t *>(c.val); ks.cnt = c.cnt; ks.b0 = b0; ks.sh = sh;
     ks.rescan = rescan; ks.t = &t; ks.r = r; ks.b = b;
     const uint32_t m1 = (1u << (sh - SH1)) - 1u;       /* level-1 digit: key bits sh-1 .. 7 */
     const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS - 1) / SEL_THREADS;
@@ -615,7 +661,7 @@ __device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c
     const uint32_t e_b = need1 - sm.res[1];
     __syncthreads();
     carry = 0;
-    finish_prefixes(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
+    finish_prefixes<1>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
                     [&](uint32_t r, uint32_t s, uint32_t &g, uint32_t &q) {
                         const uint32_t bc = bc_of(r, s);
                         if (resident) {
@@ -640,7 +686,7 @@ __device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c
  * the tie allowance e from the few undecided keys (12 + 7 remaining bits, histograms in LDS),
  * then every segment's place in the survivor order.  PATH_ZERO buckets arrive with T = 0 and e
  * known and only get the prefixes. */
-__global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c, const uint32_t *__restrict__ sel0,
+__global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c, const uint32_t *__restrict__ sel0, uint32_t selSh,
                                                                uint32_t *__restrict__ tail_ovf,
                                                                const uint32_t *__restrict__ lcnt,
                                                                const uint32_t *__restrict__ lkey,
@@ -660,7 +706,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     /* this unit's list length, fetched before the bucket's state is known */
     const uint32_t my_cnt = (tid < u1 - u0 && tid < SEL_THREADS) ? lcnt[u0 + tid] : 0u;
     if (path == PATH_DENSE || kb == 0u) return;
-    const uint32_t seg_lo = t.span0[b] << t.segSh, seg_hi = t.span0[b + 1] << t.segSh;
+    const uint32_t seg_lo = t.tile0[b], seg_hi = t.tile0[b + 1];
     const uint32_t b0 = t.T[b];                      /* the key bits from position sh up; PATH_ZERO: the full key (0) */
     const uint32_t need0 = t.need[b], sh = t.sh[b];
     FinShared sm;
@@ -668,8 +714,8 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     if (path == PATH_ZERO) {
         /* the streaming pass counted non-zero (G) and zero (E) keys per segment; when a band from
          * key 1 up was staged as well, G holds the keys above the band and the staged ones add to it */
-        const bool mixed = t.L[b] != t.H[b];
-        finish_prefixes(t, c, b, seg_lo, seg_hi, 0u, need0, kb, chunk_seg, tmp, err,
+        const bool mixed = t.par[b].x != t.par[b].y;
+        finish_prefixes<4>(t, c, b, seg_lo, seg_hi, 0u, need0, kb, chunk_seg, tmp, err,
                         [&](uint32_t, uint32_t s, uint32_t &g, uint32_t &q) {
                             if (s < seg_hi) { q += c.E[s]; if (mixed) g += c.cnt[s]; }
                         });
@@ -683,78 +729,70 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     if (no_list || force_rescan || nun > SEL_THREADS || seg_hi - seg_lo > FIN_MAX_SEGS)
         finish_from_tails(t, c, b, b0, sh, need0, kb, seg_lo, seg_hi, ovf != 0u || force_rescan, chunk_seg, sm, err, r);
     else
-        finish_from_lists(t, c, b, b0, sh, need0, kb, seg_lo, seg_hi, u0, nun, my_cnt, lkey, chunk_seg, sm, err);
+        finish_from_lists(t, c, b, b0, sh, need0, kb, seg_lo, seg_hi, u0, nun, my_cnt, selSh, lkey, chunk_seg, sm, err);
 }
 
 /* ------------------------------------------------------------------ k_encode */
 
-/* The segments whose descriptions sit in LDS (mc entries, mg / me running counts before them),
- * numbers 0 .. m-1 of the block that starts at segment sblk: their survivors with ranks in
- * [j0, j0 + n) go to sv / si.  GROUP lanes work on one segment at a time; returns how many
+constexpr uint32_t CU = 4;                 /* entries of a segment a lane fetches at a time */
+
+/* The survivors with ranks in [j0, j0 + n) out of segments [sA, sEnd) of a PATH_CAND bucket go to
+ * sv / si.  GROUP lanes share a segment and SB segments per group are in flight: their counts and
+ * prefixes, then the first batch of entries of each.  An entry above T, or an admitted tie, has
+ * rank G + min(e, E), with G / E the numbers of entries above / equal to T before it: the prefixes
+ * k_select_finish left per segment, then ballots, so nothing crosses wavefronts.  Returns how many
  * survivors this thread placed. */
-template <uint32_t GROUP>
-__device__ __forceinline__ uint32_t gather_block(const Cand &c, uint32_t sblk, uint32_t m, uint32_t T, uint32_t e_b,
-                                                 uint32_t j0, uint32_t n, float *sv, uint32_t *si,
-                                                 const uint32_t *mc, const uint32_t *mg, const uint32_t *me)
+template <uint32_t GROUP, uint32_t SB>
+__device__ __forceinline__ uint32_t gather_segments(const Cand &c, uint32_t sA, uint32_t sEnd, uint32_t T, uint32_t e_b,
+                                                    uint32_t j0, uint32_t n, float *sv, uint32_t *si)
 {
-    constexpr uint32_t SPR = 64 / GROUP;
-    constexpr uint32_t SLOTS = (WG / 64) * SPR;      /* segments the workgroup works on at a time */
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane / GROUP, gl = lane % GROUP;
-    const uint32_t shift = sub * GROUP;
+    constexpr uint32_t GROUPS = ENC_T / GROUP;       /* segments the workgroup works on side by side */
+    const uint32_t tid = threadIdx.x, lane = tid & 63, gl = lane % GROUP, shift = lane - gl;
     const uint64_t below = (1ull << gl) - 1ull;
     const uint64_t gmask = GROUP == 64 ? ~0ull : ((1ull << (GROUP % 64)) - 1ull);
     uint32_t got = 0;
-    /* the first batch of entries of a segment is fetched while the previous segment is worked on */
-    auto first_batch = [&](uint32_t q, float (&x)[CU], uint32_t (&li)[CU]) {
-        const uint32_t cnt = q < m ? mc[q] : 0u;
-        const uint64_t base = (uint64_t)(sblk + q) * c.cap;
+    for (uint32_t q0 = sA; q0 < sEnd; q0 += GROUPS * SB) {
+        uint32_t cnt[SB], rg[SB], re[SB];
 #pragma unroll
-        for (uint32_t u = 0; u < CU; ++u) {
-            const uint32_t i = u * GROUP + gl;
-            x[u] = i < cnt ? c.val[base + i] : 0.0f;
-            li[u] = i < cnt ? c.idx[base + i] : 0u;
+        for (uint32_t v = 0; v < SB; ++v) {
+            const uint32_t s = q0 + v * GROUPS + tid / GROUP;
+            cnt[v] = rg[v] = re[v] = 0;
+            if (s < sEnd) { cnt[v] = c.cnt[s]; rg[v] = c.G[s]; re[v] = c.E[s]; }
         }
-    };
-    const uint32_t qend = ((m + SLOTS - 1) / SLOTS) * SLOTS;
-    float xn[CU];
-    uint32_t lin[CU];
-    first_batch(wave * SPR + sub, xn, lin);
-    for (uint32_t q = wave * SPR + sub; q < qend; q += SLOTS) {
-        const bool live = q < m;
-        const uint32_t cnt = live ? mc[q] : 0u;
-        uint32_t run_g = live ? mg[q] : 0u, run_e = live ? me[q] : 0u;
-        uint32_t maxcnt = cnt;
-#pragma unroll
-        for (int d = 32; d >= (int)GROUP; d >>= 1) maxcnt = max(maxcnt, (uint32_t)__shfl_xor(maxcnt, d, 64));
-        const uint64_t base = (uint64_t)(sblk + q) * c.cap;
-        float x[CU];
-        uint32_t li[CU];
-#pragma unroll
-        for (uint32_t u = 0; u < CU; ++u) { x[u] = xn[u]; li[u] = lin[u]; }
-        if (q + SLOTS < qend) first_batch(q + SLOTS, xn, lin);
-        for (uint32_t i0 = 0; i0 < maxcnt; i0 += CU * GROUP) {
-            if (i0 != 0) {
-#pragma unroll
-                for (uint32_t u = 0; u < CU; ++u) {
-                    const uint32_t i = i0 + u * GROUP + gl;
-                    x[u] = i < cnt ? c.val[base + i] : 0.0f;
-                    li[u] = i < cnt ? c.idx[base + i] : 0u;
-                }
-            }
+        float x[SB][CU];
+        uint32_t li[SB][CU];
+        auto fetch = [&](uint32_t v, uint32_t i0) {
+            const uint64_t base = (uint64_t)(q0 + v * GROUPS + tid / GROUP) * SEG_CAP;
 #pragma unroll
             for (uint32_t u = 0; u < CU; ++u) {
-                const uint32_t key = keyof(x[u]);
-                const bool in = i0 + u * GROUP + gl < cnt;
-                const bool isg = in && key > T, ise = in && key == T;
-                const uint64_t bg = (__ballot(isg) >> shift) & gmask;
-                const uint64_t be = (__ballot(ise) >> shift) & gmask;
-                const uint32_t pg = run_g + __popcll(bg & below), pe = run_e + __popcll(be & below);
-                if (isg || (ise && pe < e_b)) {
-                    const uint64_t slot = (uint64_t)pg + (uint64_t)min(e_b, pe) - (uint64_t)j0;   /* wraps below j0 */
-                    if (slot < (uint64_t)n) { sv[slot] = x[u]; si[slot] = li[u]; ++got; }
+                const uint32_t i = i0 + u * GROUP + gl;
+                x[v][u] = i < cnt[v] ? c.val[base + i] : 0.0f;
+                li[v][u] = i < cnt[v] ? c.idx[base + i] : 0u;
+            }
+        };
+#pragma unroll
+        for (uint32_t v = 0; v < SB; ++v) fetch(v, 0);
+#pragma unroll
+        for (uint32_t v = 0; v < SB; ++v) {
+            for (uint32_t i0 = 0;;) {
+#pragma unroll
+                for (uint32_t u = 0; u < CU; ++u) {
+                    const uint32_t key = keyof(x[v][u]);
+                    const bool in = i0 + u * GROUP + gl < cnt[v];
+                    const bool isg = in && key > T, ise = in && key == T;
+                    const uint64_t bg = (__ballot(isg) >> shift) & gmask;
+                    const uint64_t be = (__ballot(ise) >> shift) & gmask;
+                    const uint32_t pg = rg[v] + __popcll(bg & below), pe = re[v] + __popcll(be & below);
+                    if (isg || (ise && pe < e_b)) {
+                        const uint64_t slot = (uint64_t)pg + (uint64_t)min(e_b, pe) - (uint64_t)j0;   /* wraps below j0 */
+                        if (slot < (uint64_t)n) { sv[slot] = x[v][u]; si[slot] = li[v][u]; ++got; }
+                    }
+                    rg[v] += __popcll(bg);
+                    re[v] += __popcll(be);
                 }
-                run_g += __popcll(bg);
-                run_e += __popcll(be);
+                i0 += CU * GROUP;
+                if (!__any(i0 < cnt[v])) break;
+                fetch(v, i0);
             }
         }
     }
@@ -762,41 +800,23 @@ __device__ __forceinline__ uint32_t gather_block(const Cand &c, uint32_t sblk, u
 }
 
 /* Gather survivors number [j0, j0 + n) of a PATH_CAND bucket (n <= ENC_BLK), in index order,
- * into LDS: sv their accumulator values, si their bucket-local indices; sA = the segment that
- * holds survivor j0.  Survivor ranks come from the per-segment prefixes k_select_finish left: an
- * entry above T, or an admitted tie, has rank G + min(e, E), with G / E the running counts of
- * entries above / equal to T before it.  The descriptions of up to 256 segments are fetched in
- * one go into LDS (mc, mg, me); how many lanes then share a segment follows the longest of them. */
-__device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uint32_t seg_hi, uint32_t T,
-                                                 uint32_t e_b, uint32_t j0, uint32_t n, float *sv, uint32_t *si,
-                                                 uint32_t *mc, uint32_t *mg, uint32_t *me, uint32_t *mxc,
-                                                 uint32_t *filled)
+ * into LDS: sv their accumulator values, si their bucket-local indices.  sA = the segment that holds
+ * survivor j0, sEnd = one past the last that can hold any of them.  How many lanes share a segment
+ * follows how many survivors a segment holds on average: two at ratio 0.001, two hundred at 0.1.
+ * (One list of entries over all segments, dealt evenly to the lanes by a search of the segment in
+ * LDS, follows the work more closely and was slower: 178 us against 142 at ratio 0.1 on 109 M
+ * elements, the searches alone keep the LDS busy.)  filled (LDS) counts what was placed. */
+__device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uint32_t sEnd, uint32_t T, uint32_t e_b, uint32_t j0,
+                                                 uint32_t n, float *sv, uint32_t *si, uint32_t *filled)
 {
-    const uint32_t tid = threadIdx.x, lane = tid & 63;
-    const uint64_t jend = (uint64_t)j0 + n;
-    uint32_t got = 0;
-    for (uint32_t sblk = sA; sblk < seg_hi; sblk += WG) {
-        /* descriptions of segments sblk .. sblk + 255; the ones whose first survivor lies before
-         * jend form a prefix of them */
-        const uint32_t s = sblk + tid;
-        uint32_t d_c = 0, d_g = 0, d_e = 0;
-        if (s < seg_hi) { d_c = c.cnt[s]; d_g = c.G[s]; d_e = c.E[s]; }
-        __syncthreads();                             /* the previous block's descriptions are consumed */
-        mc[tid] = d_c; mg[tid] = d_g; me[tid] = d_e;
-        if (tid == 0) *mxc = 0u;
-        const bool need = s < seg_hi && (uint64_t)d_g + min(e_b, d_e) < jend;
-        const uint32_t m = __syncthreads_count(need);
-        if (need && d_c) atomicMax(mxc, d_c);
-        __syncthreads();
-        const uint32_t longest = *mxc;
-        if (longest > 8 * CU * 4) got += gather_block<64>(c, sblk, m, T, e_b, j0, n, sv, si, mc, mg, me);
-        else if (longest > 2 * CU * 4) got += gather_block<16>(c, sblk, m, T, e_b, j0, n, sv, si, mc, mg, me);
-        else got += gather_block<4>(c, sblk, m, T, e_b, j0, n, sv, si, mc, mg, me);
-        if (m < WG) break;                           /* same value in every thread */
-    }
+    const uint32_t m = sEnd - sA;
+    uint32_t got;
+    if (n >= 24u * m) got = gather_segments<64, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
+    else if (n >= 6u * m) got = gather_segments<16, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
+    else got = gather_segments<4, 4>(c, sA, sEnd, T, e_b, j0, n, sv, si);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) got += __shfl_xor(got, d, 64);
-    if (lane == 0 && got) atomicAdd(filled, got);
+    if ((threadIdx.x & 63u) == 0u && got) atomicAdd(filled, got);
 }
 
 /* One workgroup per chunk of `chunk` consecutive survivors of a PATH_CAND bucket: gather,
@@ -804,7 +824,7 @@ __device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uin
  * floating-point step is a single correctly rounded binary32 operation.  A chunk longer than
  * ENC_BLK is gathered block by block, once for its absmax and once more for the codes. */
 template <int BITS>
-__global__ __launch_bounds__(WG) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
+__global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
                                                const uint32_t *__restrict__ chunk_seg, float *__restrict__ r,
                                                uint32_t *__restrict__ idx_out, void *__restrict__ val,
                                                float *__restrict__ scales, uint32_t *__restrict__ err,
@@ -812,9 +832,8 @@ __global__ __launch_bounds__(WG) void k_encode(Tables t, Cand c, const uint32_t 
 {
     __shared__ float sv[ENC_BLK];
     __shared__ uint32_t si[ENC_BLK];
-    __shared__ uint32_t mc[WG], mg[WG], me[WG];
-    __shared__ float red[WG / 64];
-    __shared__ uint32_t sh, filled, mxc;
+    __shared__ float red[ENC_WAVES];
+    __shared__ uint32_t sh, filled;
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
     const uint32_t tid = threadIdx.x;
     /* a workgroup takes cpw consecutive chunks (one, unless the payload has very many) */
@@ -826,25 +845,28 @@ __global__ __launch_bounds__(WG) void k_encode(Tables t, Cand c, const uint32_t 
     }
     for (uint64_t cid = (uint64_t)blockIdx.x * cpw; cid < cend; ++cid) {
     const uint32_t b = chunk_b[cid];
-    const uint32_t sFirst = chunk_seg[cid];          /* meaningful for PATH_CAND buckets only */
+    const uint32_t sFirst = chunk_seg[cid];          /* meaningful for PATH_CAND buckets only, like the next one */
+    const uint32_t sNext = cid + 1 < n_chunks ? chunk_seg[cid + 1] : 0u;
     if (t.fast[b] != PATH_CAND) continue;
     const uint64_t cb = cid - t.C[b];
     const uint64_t j0c = cb * t.chunk;                         /* first survivor of the chunk, bucket-local */
     const uint32_t cnt_c = (uint32_t)min((uint64_t)t.chunk, (uint64_t)t.k[b] - j0c);
     const uint32_t T = t.T[b], e_b = t.need[b];
-    const uint32_t seg_lo = t.span0[b] << t.segSh, seg_hi = t.span0[b + 1] << t.segSh;
+    const uint32_t seg_lo = t.tile0[b], seg_hi = t.tile0[b + 1];
+    const uint32_t sEnd = j0c + cnt_c < (uint64_t)t.k[b] ? sNext + 1u : seg_hi;      /* where the next chunk begins, or the bucket's end */
     const uint64_t lo = t.off[b], Pb = t.P[b];
     uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
 
     auto block_absmax = [&](uint32_t n) {
         float m = 0.0f;
-        for (uint32_t i = tid; i < n; i += WG) m = fmaxf(m, fabsf(sv[i]));
+        for (uint32_t i = tid; i < n; i += ENC_T) m = fmaxf(m, fabsf(sv[i]));
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
         __syncthreads();
         if ((tid & 63) == 0) red[tid >> 6] = m;
         __syncthreads();
-        return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+        for (uint32_t w = 0; w < ENC_WAVES; ++w) m = fmaxf(m, red[w]);
+        return m;
     };
     auto gather = [&](uint32_t blk0, uint32_t n) {
         __syncthreads();                                       /* the previous block has been consumed */
@@ -854,10 +876,10 @@ __global__ __launch_bounds__(WG) void k_encode(Tables t, Cand c, const uint32_t 
         if (blk0 != 0) {
             /* a later block of a long chunk: the last segment whose first survivor is not beyond j0 */
             auto rank0 = [&](uint32_t s) { return (uint64_t)c.G[s] + (uint64_t)min(e_b, c.E[s]); };
-            sA = wg_search_le(seg_lo, seg_hi, (uint64_t)j0, rank0, &sh);
+            sA = wg_search_le<ENC_T>(seg_lo, seg_hi, (uint64_t)j0, rank0, &sh);
         }
         __syncthreads();
-        gather_survivors(c, sA, seg_hi, T, e_b, j0, n, sv, si, mc, mg, me, &mxc, &filled);
+        gather_survivors(c, sA, sEnd, T, e_b, j0, n, sv, si, &filled);
         __syncthreads();
         if (tid == 0 && filled != n) err[0] = 1u;              /* the prefixes and the entries disagree */
     };
@@ -882,8 +904,8 @@ __global__ __launch_bounds__(WG) void k_encode(Tables t, Cand c, const uint32_t 
         const uint64_t jb = j0c + blk0;                        /* bucket-local number of the block's first survivor */
         /* a thread takes pairs of consecutive survivors (a 4-bit pair is one byte) */
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t i0 = 2 * (tid + u * WG);
+        for (int u = 0; u < (int)(ENC_BLK / (2 * ENC_T)); ++u) {
+            const uint32_t i0 = 2 * (tid + u * ENC_T);
             if (i0 >= n) continue;
             const int have = (i0 + 1 < n) ? 2 : 1;
             float res[2] = {0.0f, 0.0f};
@@ -935,19 +957,16 @@ __device__ __forceinline__ void write_dense_body(float *__restrict__ r, const Ta
                                                  uint32_t which, uint32_t bid, uint32_t nblk)
 {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t n_seg = t.n_spans << t.segSh;
-    for (uint32_t ss = bid * (WG / 64) + wave; ss < n_seg; ss += nblk * (WG / 64)) {
-    const uint32_t span = ss >> t.segSh, wslot = ss & ((1u << t.segSh) - 1u);
-    const uint32_t b = t.span_b[span];
+    for (uint32_t ss = bid * (WG / 64) + wave; ss < t.n_tiles; ss += nblk * (WG / 64)) {
+    const uint32_t b = t.tile_b[ss];
     const uint32_t path = t.fast[b];
     if (!((which >> path) & 1u) || t.k[b] == 0u) continue;
-    const SpanGeo s = span_geo_b(t, b, span - t.span0[b]);
+    const TileGeo s = tile_geo(t, b, ss);
     const uint32_t T = t.T[b], e_b = t.need[b];
     const uint64_t Pb = t.P[b];
     uint32_t run_g = c.G[ss], run_e = c.E[ss];
     const uint64_t lt = (1ull << lane) - 1ull;
-    const uint32_t per = (t.spanT * 4u) >> t.segSh;
-    const uint32_t wt0 = wslot * per, wt1 = min(s.ntiles * 4u, wt0 + per);
+    constexpr uint32_t wt0 = 0, wt1 = TILE / WTILE;
     /* the next wave-tile (64 lanes x 4 rows x 4 elements) is fetched while this one is written */
     float xn[4][4];
     uint32_t mn[4];
@@ -957,10 +976,10 @@ __device__ __forceinline__ void write_dense_body(float *__restrict__ r, const Ta
         for (int u = 0; u < 4; ++u) {
             const uint64_t gi = wb + (uint64_t)(u * 64 + lane) * 4;
             mn[u] = load_quad(r, gi, s.lo, s.hi, xn[u]);
-            if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, s.tile_g + (wt >> 2), (wt & 3u) * WG + u * 64 + lane);
+            if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, ss, wt * WG + u * 64 + lane);
         }
     };
-    if (wt0 < wt1) fetch(wt0);
+    fetch(wt0);
     for (uint32_t wt = wt0; wt < wt1; ++wt) {
         const uint64_t wb = s.base + (uint64_t)wt * WTILE;
         float x[4][4];
@@ -1014,15 +1033,12 @@ __device__ __forceinline__ void segcount_dense_body(const float *__restrict__ r,
                                                     uint32_t bid, uint32_t nblk)
 {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t n_seg = t.n_spans << t.segSh;
-    for (uint32_t ss = bid * (WG / 64) + wave; ss < n_seg; ss += nblk * (WG / 64)) {
-    const uint32_t span = ss >> t.segSh, wslot = ss & ((1u << t.segSh) - 1u);
-    const uint32_t b = t.span_b[span];
+    for (uint32_t ss = bid * (WG / 64) + wave; ss < t.n_tiles; ss += nblk * (WG / 64)) {
+    const uint32_t b = t.tile_b[ss];
     if (t.fast[b] != PATH_DENSE || t.k[b] == 0u) continue;
-    const SpanGeo s = span_geo_b(t, b, span - t.span0[b]);
+    const TileGeo s = tile_geo(t, b, ss);
     const uint32_t T = t.T[b];
-    const uint32_t per = (t.spanT * 4u) >> t.segSh;
-    const uint32_t wt0 = wslot * per, wt1 = min(s.ntiles * 4u, wt0 + per);
+    constexpr uint32_t wt0 = 0, wt1 = TILE / WTILE;
     uint32_t ng = 0, ne = 0;
     for (uint32_t wt = wt0; wt < wt1; ++wt) {
         const uint64_t wb = s.base + (uint64_t)wt * WTILE;
@@ -1031,7 +1047,7 @@ __device__ __forceinline__ void segcount_dense_body(const float *__restrict__ r,
             const uint64_t gi = wb + (uint64_t)(u * 64 + lane) * 4;
             float x[4];
             uint32_t m = load_quad(r, gi, s.lo, s.hi, x);
-            if (t.pmask) m &= ~pruned_bits(t.pmask, s.tile_g + (wt >> 2), (wt & 3u) * WG + u * 64 + lane);
+            if (t.pmask) m &= ~pruned_bits(t.pmask, ss, wt * WG + u * 64 + lane);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t key = keyof(x[j]);
@@ -1049,9 +1065,8 @@ __device__ __forceinline__ void segcount_dense_body(const float *__restrict__ r,
 
 /* The buckets whose staged elements could not decide them (PATH_DENSE: an unlucky sample, a
  * staging segment that overflowed, a huge group of equal keys), in ONE launch of a fixed, small
- * grid whose workgroups meet at barriers between the steps: list of their spans, level-1
- * histogram over the dense accumulator, digit, level-2 histogram, digit, counts per segment,
- * prefixes, ordered write.  In the usual case there is no such bucket: each workgroup reads one
+ * grid whose workgroups meet at barriers between the steps: threshold, counts and prefixes
+ * (dense_threshold), ordered write.  In the usual case there is no such bucket: each workgroup reads one
  * word and leaves, so the whole chain costs a single empty launch per call.
  * A barrier is an arrival counter in memory: every wavefront waits for its own stores, one thread
  * per workgroup then makes them visible device wide, counts the workgroup in and waits until all
@@ -1079,22 +1094,51 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uin
     __syncthreads();
 }
 
+/* Threshold key, tie allowance and prefixes per tile of the buckets on the dense passes, by a team of
+ * nblk resident workgroups: list of their tiles, then per level a histogram over the source and its
+ * digit, then counts per tile and their prefixes, with a barrier after each step.  h: NB0 words of LDS. */
+__device__ __forceinline__ void dense_threshold(const float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
+                                                uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *h, uint32_t *bar,
+                                                uint32_t bid, uint32_t nblk, uint32_t *__restrict__ err)
+{
+    uint32_t arrivals = 0;
+    if (bid == 0) fb_plan_body(t);
+    grid_barrier(bar, arrivals += nblk, err);
+    fb_refine_body<0>(r, t, f0, h, bid, nblk);
+    grid_barrier(bar, arrivals += nblk, err);
+    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<0>(t, f0, err, b); }
+    grid_barrier(bar, arrivals += nblk, err);
+    fb_refine_body<1>(r, t, f1, h, bid, nblk);
+    grid_barrier(bar, arrivals += nblk, err);
+    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<1>(t, f1, err, b); }
+    grid_barrier(bar, arrivals += nblk, err);
+    fb_refine_body<2>(r, t, f2, h, bid, nblk);
+    grid_barrier(bar, arrivals += nblk, err);
+    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<2>(t, f2, err, b); }
+    grid_barrier(bar, arrivals += nblk, err);
+    segcount_dense_body(r, t, c, bid, nblk);
+    grid_barrier(bar, arrivals += nblk, err);
+    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); scan_body(t, c.G, c.E, b); }
+    grid_barrier(bar, arrivals += nblk, err);
+}
+
 /* Ordered write and value coding in one pass, for the buckets whose survivors are taken from the
  * dense accumulator and whose threshold is known (PATH_BAND, PATH_ZERO), with chunks of at most
  * DENC_MAX_CHUNK survivors.  Survivors are dense here (ratios from an eighth up, or an
  * embedding whose few non-zero rows all survive), so the work is laid out by elements: a
- * workgroup streams a unit of one or two (dencSpans) consecutive spans, 4096 elements at a time (one
+ * workgroup streams a unit of dencTiles consecutive tiles, 4096 elements at a time (one
  * wave-tile per wavefront); ranks come from ballots and a prefix over the four wavefronts; the
  * survivors are put into LDS in rank order behind the ones still waiting for their chunk to
  * fill up; every chunk that is complete is coded from LDS by one wavefront (absmax, scale,
  * codes, indices, and the coding error scattered into the accumulator lines the workgroup has
  * just read, which are still in the cache).  A chunk that reaches across the unit's ends (or a
- * bucket's spans of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
+ * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
  * those afterwards (same test, see chunk_coded_by_stream).  16-bit values need no chunk and are
  * all coded here. */
 constexpr uint32_t DENC_SMALL_CHUNK = 256;         /* up to here a wavefront codes a chunk */
 constexpr uint32_t DENC_MAX_CHUNK = 2048;
-constexpr uint32_t denc_cap(bool big) { return TILE + (big ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK); }
+constexpr uint32_t DENC_STEP = (WG / 64) * WTILE;   /* elements per step: all of them can be survivors */
+constexpr uint32_t denc_cap(bool big) { return DENC_STEP + (big ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK); }
 
 template <int BITS, bool BIG>       /* BIG: chunks of more than DENC_SMALL_CHUNK survivors */
 __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const Tables &t, const Cand &c,
@@ -1106,10 +1150,10 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;     /* (unused for 16 / 32 bits) */
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t chunk = t.chunk;
-    const uint32_t n_units = (t.n_spans + t.dencSpans - 1) / t.dencSpans;
+    const uint32_t n_units = (t.n_tiles + t.dencTiles - 1) / t.dencTiles;
     for (uint32_t unit = bid; unit < n_units; unit += nblk) {
         uint32_t cur_b = NONE;
-        /* state of the stream: one bucket's consecutive spans inside the unit */
+        /* state of the stream: one bucket's consecutive tiles inside the unit */
         uint32_t T = 0, e_b = 0, kb = 0, run_g = 0, run_e = 0, carry = 0, Rbase = 0;
         uint64_t Pb = 0, lo = 0;
         uint8_t *vb = nullptr;
@@ -1124,30 +1168,25 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
             carry = 0;
             __syncthreads();
         };
-        const uint32_t sp1 = min(t.n_spans, (unit + 1) * t.dencSpans);
-        for (uint32_t span = unit * t.dencSpans; span < sp1; ++span) {
-            const uint32_t b = t.span_b[span];
+        const uint32_t sp1 = min(t.n_tiles, (unit + 1) * t.dencTiles);
+        uint32_t send = 0;
+        for (uint32_t tile = unit * t.dencTiles; tile < sp1; tile = send) {
+            /* the bucket's tiles of this unit: [tile, send) */
+            const uint32_t b = t.tile_b[tile];
+            send = min(sp1, t.tile0[b + 1]);
             const uint32_t path = t.fast[b];
-            if ((path != PATH_BAND && path != PATH_ZERO) || t.k[b] == 0u) {
-                if (cur_b != NONE) { flush(); cur_b = NONE; }
-                continue;
-            }
-            const SpanGeo s = span_geo_b(t, b, span - t.span0[b]);
-            if (b != cur_b) {
-                if (cur_b != NONE) flush();
-                cur_b = b;
-                T = t.T[b]; e_b = t.need[b]; kb = t.k[b]; Pb = t.P[b]; lo = s.lo;
-                vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
-                Sb = t.S[b];
-                const uint32_t ss0 = span << t.segSh;
-                run_g = c.G[ss0]; run_e = c.E[ss0];
-                Rbase = run_g + min(e_b, run_e);
-                carry = 0;
-                head = BITS <= 8 && (Rbase % chunk) != 0u;
-            }
-            else if (tid == 0 && (run_g != c.G[span << t.segSh] || run_e != c.E[span << t.segSh]))
-                err[0] = 1u;                         /* the prefixes and the elements disagree */
-                    const uint32_t nwt = s.ntiles * 4u;
+            if (cur_b != NONE) flush();
+            if ((path != PATH_BAND && path != PATH_ZERO) || t.k[b] == 0u) { cur_b = NONE; continue; }
+            const TileGeo s = tile_geo(t, b, tile);
+            cur_b = b;
+            T = t.T[b]; e_b = t.need[b]; kb = t.k[b]; Pb = t.P[b]; lo = s.lo;
+            vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
+            Sb = t.S[b];
+            run_g = c.G[tile]; run_e = c.E[tile];
+            Rbase = run_g + min(e_b, run_e);
+            carry = 0;
+            head = BITS <= 8 && (Rbase % chunk) != 0u;
+            const uint32_t nwt = (send - tile) * (TILE / WTILE);
             /* the next 4096 elements are fetched while the survivors of these are coded */
             float xn[4][4];
             uint32_t mn[4];
@@ -1168,7 +1207,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                         } else {
                             mn[u] = load_quad(r, gi, s.lo, s.hi, xn[u]);
                         }
-                        if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, s.tile_g + (wt >> 2), (wt & 3u) * WG + u * 64 + lane);
+                        if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, tile, wt * WG + u * 64 + lane);
                     }
                 }
             };
@@ -1176,6 +1215,8 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
             for (uint32_t wt_base = 0; wt_base < nwt; wt_base += WG / 64) {
                 const uint32_t wt = wt_base + wave;
                 const uint64_t wb = s.base + (uint64_t)wt * WTILE;
+                if (tid == 0 && (run_g != c.G[tile + wt_base / (TILE / WTILE)] || run_e != c.E[tile + wt_base / (TILE / WTILE)]))
+                    err[0] = 1u;                     /* the prefixes and the elements disagree */
                 float x[4][4];
                 uint32_t fg[4], fe[4];
 #pragma unroll
@@ -1372,18 +1413,15 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
 }
 
 /* Whether chunk cb (bucket-local) of a PATH_BAND / PATH_ZERO bucket b was coded by
- * dense_encode_body: its first survivor lies in segment s, and all of its survivors lie in the
- * spans of b inside the unit of dencSpans spans that holds s. */
+ * dense_encode_body: its first survivor lies in tile s, and all of its survivors lie in the
+ * tiles of b inside the unit of dencTiles tiles that holds s. */
 __device__ __forceinline__ bool chunk_coded_by_stream(const Tables &t, const Cand &c, uint32_t b, uint64_t cb, uint32_t s)
 {
     const uint32_t kb = t.k[b], e_b = t.need[b];
     const uint64_t end = min((cb + 1) * (uint64_t)t.chunk, (uint64_t)kb);
-    const uint32_t next_span = ((s >> t.segSh) / t.dencSpans + 1u) * t.dencSpans;
+    const uint32_t next = (s / t.dencTiles + 1u) * t.dencTiles;
     uint64_t r1 = kb;
-    if (next_span < t.span0[b + 1]) {
-        const uint32_t sn = next_span << t.segSh;
-        r1 = (uint64_t)c.G[sn] + min(e_b, c.E[sn]);
-    }
+    if (next < t.tile0[b + 1]) r1 = (uint64_t)c.G[next] + min(e_b, c.E[next]);
     return end <= r1;
 }
 
@@ -1392,8 +1430,8 @@ constexpr uint32_t hard_wg_per_cu(bool big) { return big ? 3u : 4u; }
 constexpr uint32_t hard_lds(bool big) { return 2 * denc_cap(big) + 2 * (WG / 64); }    /* words; also holds the level-1 histogram */
 
 template <int BITS, bool BIG>
-__global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ f1,
-                                             uint32_t *__restrict__ f2, uint32_t *__restrict__ idx,
+__global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ f0,
+                                             uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ idx,
                                              float *__restrict__ vdst, void *__restrict__ val,
                                              float *__restrict__ scales, uint32_t *__restrict__ err, int stream_coding, uint32_t team)
 {
@@ -1417,21 +1455,7 @@ __global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restr
     nblk = team;
     uint32_t *h = pool;
     uint32_t *bar = t.nhard + 1;
-    uint32_t arrivals = 0;
-    if (bid == 0) fb_plan_body(t);
-    grid_barrier(bar, arrivals += nblk, err);
-    fb_refine_body<1>(r, t, f1, h, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<1>(t, f1, f1, err, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
-    fb_refine_body<2>(r, t, f2, h, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<2>(t, f2, f2, err, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
-    segcount_dense_body(r, t, c, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); scan_body(t, c.G, c.E, nullptr, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
+    dense_threshold(r, t, c, f0, f1, f2, h, bar, bid, nblk, err);
     write_dense_body<BITS == 32>(r, t, c, idx, vdst, 1u << PATH_DENSE, bid, nblk);
 }
 
@@ -1510,11 +1534,10 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
 __global__ __launch_bounds__(WG) void k_wfix(Tables t, Cand c, uint32_t *__restrict__ pmask)
 {
     const uint32_t lane = threadIdx.x & 63, sub = lane >> 4, gl = lane & 15u;
-    const uint32_t n_seg = t.n_spans << t.segSh;
     const uint32_t ss = (blockIdx.x * (WG / 64) + (threadIdx.x >> 6)) * 4u + sub;
     uint32_t cnt = 0, T = 0, e_b = 0, run_e = 0, b = 0, head = 0;
-    if (ss < n_seg) {
-        b = t.span_b[ss >> t.segSh];
+    if (ss < t.n_tiles) {
+        b = t.tile_b[ss];
         if (t.fast[b] == PATH_BAND && t.k[b] != 0u) {
             cnt = c.cnt[ss];
             T = t.T[b]; e_b = t.need[b]; run_e = c.E[ss];
@@ -1524,7 +1547,7 @@ __global__ __launch_bounds__(WG) void k_wfix(Tables t, Cand c, uint32_t *__restr
     uint32_t maxcnt = cnt;
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) maxcnt = max(maxcnt, (uint32_t)__shfl_xor(maxcnt, d, 64));
-    const uint64_t base = (uint64_t)ss * c.cap;
+    const uint64_t base = (uint64_t)ss * SEG_CAP;
     for (uint32_t i0 = 0; i0 < maxcnt; i0 += 16) {
         const uint32_t i = i0 + gl;
         const bool in = i < cnt;
@@ -1551,17 +1574,14 @@ __device__ __forceinline__ void mask_dense_body(const float *__restrict__ w, con
                                                 uint32_t *__restrict__ pmask, uint32_t bid, uint32_t nblk)
 {
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const uint32_t n_seg = t.n_spans << t.segSh;
     const uint64_t lt = (1ull << lane) - 1ull;
-    for (uint32_t ss = bid * (WG / 64) + wave; ss < n_seg; ss += nblk * (WG / 64)) {
-        const uint32_t span = ss >> t.segSh, wslot = ss & ((1u << t.segSh) - 1u);
-        const uint32_t b = t.span_b[span];
+    for (uint32_t ss = bid * (WG / 64) + wave; ss < t.n_tiles; ss += nblk * (WG / 64)) {
+        const uint32_t b = t.tile_b[ss];
         if (t.fast[b] != PATH_DENSE || t.k[b] == 0u) continue;
-        const SpanGeo s = span_geo_b(t, b, span - t.span0[b]);
+        const TileGeo s = tile_geo(t, b, ss);
         const uint32_t T = t.T[b], e_b = t.need[b];
         uint32_t run_e = c.E[ss];
-        const uint32_t per = (t.spanT * 4u) >> t.segSh;
-        const uint32_t wt0 = wslot * per, wt1 = min(s.ntiles * 4u, wt0 + per);
+        constexpr uint32_t wt0 = 0, wt1 = TILE / WTILE;
         for (uint32_t wt = wt0; wt < wt1; ++wt) {
             const uint64_t wb = s.base + (uint64_t)wt * WTILE;
 #pragma unroll
@@ -1594,7 +1614,7 @@ __device__ __forceinline__ void mask_dense_body(const float *__restrict__ w, con
                 word |= __shfl_xor(word, 2, 64);
                 word |= __shfl_xor(word, 4, 64);
                 if ((lane & 7u) == 0u)
-                    pmask[(uint64_t)(s.tile_g + (wt >> 2)) * (TILE / 32) + (wt & 3u) * (WG / 8) + u * 8 + (lane >> 3)] = word;
+                    pmask[(uint64_t)ss * (TILE / 32) + wt * (WTILE / 32) + u * 8 + (lane >> 3)] = word;
             }
         }
     }
@@ -1604,29 +1624,14 @@ __device__ __forceinline__ void mask_dense_body(const float *__restrict__ w, con
  * one launch of a small resident grid with barriers between the steps, like k_hard: spans,
  * level-1 histogram of |w|, digit, level-2 histogram, digit, counts per segment, prefixes,
  * bitmap.  Leaves at once when there is no such bucket. */
-__global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f1,
-                                              uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
+__global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
+                                              uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
                                               uint32_t *__restrict__ err)
 {
     __shared__ uint32_t h[NB1];
     if (t.nhard[2] == 0u) return;
     const uint32_t bid = blockIdx.x, nblk = gridDim.x;
-    uint32_t *bar = t.nhard + 1;
-    uint32_t arrivals = 0;
-    if (bid == 0) fb_plan_body(t);
-    grid_barrier(bar, arrivals += nblk, err);
-    fb_refine_body<1>(w, t, f1, h, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<1>(t, f1, f1, err, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
-    fb_refine_body<2>(w, t, f2, h, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<2>(t, f2, f2, err, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
-    segcount_dense_body(w, t, c, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); scan_body(t, c.G, c.E, nullptr, nullptr, 1, b); }
-    grid_barrier(bar, arrivals += nblk, err);
+    dense_threshold(w, t, c, f0, f1, f2, h, t.nhard + 1, bid, nblk, err);
     mask_dense_body(w, t, c, pmask, bid, nblk);
 }
 
