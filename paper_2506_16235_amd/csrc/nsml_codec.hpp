@@ -133,7 +133,7 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
         if ((tid & 63) == 0) red[tid >> 6] = m;
-        __syncthreads();
+        wg_sync();
         m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
         constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
         scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
@@ -158,7 +158,7 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
 #pragma unroll
             for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
             if ((tid & 63) == 0) red[tid >> 6] = m;
-            __syncthreads();
+            wg_sync();
             m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
             constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
             scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
@@ -259,7 +259,7 @@ __global__ __launch_bounds__(WG) void k_tilestart(const uint32_t *__restrict__ i
     const bool in_lds = t.B <= LDS_B;
     if (in_lds) {
         for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
-        __syncthreads();
+        wg_sync();
     }
     const uint64_t stride = (uint64_t)gridDim.x * WG * TS_PER;
     for (uint64_t j0 = ((uint64_t)blockIdx.x * WG + threadIdx.x) * TS_PER; j0 < K; j0 += stride) {
@@ -394,7 +394,7 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
             const uint64_t shift = s.lo - s.base;        /* slot = local index + lo - base */
 #pragma unroll
             for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(&slots[(u * DTH + tid) * 4]) = out[u];
-            __syncthreads();
+            wg_sync();
             for (uint64_t jb = j0; jb < j1; jb += S * DTH) {
                 uint32_t li[S];
                 float x[S];
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
                     if (li[u] < nb && slot < TILE) slots[slot] = x[u];
                 }
             }
-            __syncthreads();
+            wg_sync();
 #pragma unroll
             for (int u = 0; u < U; ++u) out[u] = *reinterpret_cast<const f4 *>(&slots[(u * DTH + tid) * 4]);
         }
@@ -463,7 +463,7 @@ __global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx
     for (uint32_t u = 0; u < SCAT_PER; ++u) li[u] = j0 + u * WG < K ? idx[j0 + u * WG] : NONE;
     if (in_lds) {
         for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
-        __syncthreads();
+        wg_sync();
     }
     float x[SCAT_PER], y[SCAT_PER];
     float *at[SCAT_PER];

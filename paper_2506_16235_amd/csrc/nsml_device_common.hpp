@@ -8,6 +8,17 @@
 namespace {
 
 constexpr int WG = 256;
+/* The workgroup barrier of every kernel here.  The wait for this wavefront's own LDS accesses is
+ * written out: the compiler is to put one before the barrier, but where the accesses in flight come
+ * only over a loop's back edge it has been seen to drop it (the histogram of the dense passes was read
+ * while other wavefronts' additions were still on their way: counts lost about once in a few hundred
+ * calls).  Where the compiler's own wait is there, this one merges with it. */
+__device__ __forceinline__ void wg_sync()
+{
+    __builtin_amdgcn_s_waitcnt(0xC07F);              /* lgkmcnt(0), the other counters at their maximum */
+    __syncthreads();
+}
+
 /* Elements per tile: one tile is one workgroup of the streaming kernels (512 threads, one 16-byte
  * access per thread and operand, then the workgroup ends) and one staging segment.  What bounds
  * these kernels is how close together the accesses in flight are: `b = a + b` over 3 x 6.7 GB runs at
@@ -156,9 +167,9 @@ __device__ __forceinline__ uint32_t find_bucket_wg(const T *__restrict__ pre, ui
         const uint32_t p = lo + threadIdx.x * step, q = p + step;
         /* thread t owns [p, q) clipped to hi; exactly one thread's range holds the answer */
         if (p < hi && pre[p] <= x && (q >= hi || x < pre[q])) *sh = p;
-        __syncthreads();
+        wg_sync();
         const uint32_t np = *sh;
-        __syncthreads();
+        wg_sync();
         lo = np;
         hi = np + step < hi ? np + step : hi;
     }
@@ -244,12 +255,12 @@ __global__ __launch_bounds__(WG) void k_setup(Tables t, double ratio, int bits)
         sc += ch;
     }
     part[0][tid] = sk; part[1][tid] = sv; part[2][tid] = ss; part[3][tid] = sc;
-    __syncthreads();
+    wg_sync();
     if (tid < 4) {
         uint64_t run = 0;
         for (int i = 0; i < WG; ++i) { const uint64_t x = part[tid][i]; part[tid][i] = run; run += x; }
     }
-    __syncthreads();
+    wg_sync();
     uint64_t pk = part[0][tid], pv = part[1][tid], ps = part[2][tid], pc = part[3][tid];
     for (uint32_t b = b0; b < b1; ++b) {
         const uint64_t k = survivors_dev(ratio, t.off[b + 1] - t.off[b]);
@@ -397,15 +408,15 @@ __device__ __forceinline__ uint32_t block_incl_scan(uint32_t x, uint32_t *tmp)
         if (lane >= (uint32_t)d) x += y;
     }
     if (lane == 63) tmp[wave] = x;
-    __syncthreads();
+    wg_sync();
     uint32_t add = 0;
 #pragma unroll
     for (int w = 0; w < WG / 64; ++w) add += (uint32_t)w < wave ? tmp[w] : 0u;
     const uint32_t total = tmp[0] + tmp[1] + tmp[2] + tmp[3];
-    __syncthreads();
+    wg_sync();
     x += add;
     if (tid == WG - 1) tmp[WG - 1] = total;
-    __syncthreads();
+    wg_sync();
     return x;
 }
 
@@ -430,7 +441,7 @@ struct DigitWalk {
         }
         incl = block_incl_scan(sum, tmp);
         total = tmp[WG - 1];
-        __syncthreads();
+        wg_sync();
     }
     /* Zero the row again once it has been read (every thread its own digits): the histograms
      * of a call are left clean for the next one, which saves a fill kernel per call. */

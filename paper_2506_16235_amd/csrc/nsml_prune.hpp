@@ -73,7 +73,7 @@ __global__ __launch_bounds__(WG) void k_wpredict(Tables t, uint32_t *__restrict_
     uint32_t digit, above, at;
     if (w.find((uint32_t)r_up, digit, above, at)) { res[0] = digit; res[1] = above; res[2] = at; }
     if (w.find((uint32_t)r_dn, digit, above, at)) { res[3] = digit; res[4] = above; res[5] = at; }
-    __syncthreads();
+    wg_sync();
     if (tid == 0) {
         /* sample entries inside the band -> expected staged elements */
         const double in_band = (double)(res[4] + res[5]) - (double)res[1];
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ 
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) ca += __shfl_xor(ca, d, 64);
         if ((tid & 63) == 0) red[tid >> 6] = ca;
-        __syncthreads();
+        wg_sync();
         for (uint32_t w = 0; w < NHB / 64; ++w) n_above += red[w];
     }
     uint32_t total;

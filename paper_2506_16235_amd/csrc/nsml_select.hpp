@@ -25,7 +25,7 @@ __global__ __launch_bounds__(WG) void k_sample(const float *__restrict__ g, cons
     const uint64_t a0 = lo & ~3ull;
     const uint64_t run_elems = SAMPLE_RUN * sample_stride(hi - lo);
     const uint64_t n_runs = (hi - a0 + run_elems - 1) / run_elems;
-    __syncthreads();
+    wg_sync();
 #pragma unroll 4
     for (uint32_t i = 0; i < RUNS_PER_WG * SAMPLE_RUN / (4 * WG); ++i) {
         const uint64_t run = (uint64_t)wi * RUNS_PER_WG + i * (4 * WG / SAMPLE_RUN) + tid / (SAMPLE_RUN / 4);
@@ -43,7 +43,7 @@ __global__ __launch_bounds__(WG) void k_sample(const float *__restrict__ g, cons
                 if ((m >> j) & 1u) atomicAdd(&h[keyof(SUM ? __fadd_rn(x[j], y[j]) : x[j]) >> SH0], 1u);
         }
     }
-    __syncthreads();
+    wg_sync();
     hist_flush(h, hist_s + (uint64_t)b * NB0, NB0);
 }
 
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
     if (w.find((uint32_t)r_up, digit, above, at)) { res[3] = digit; res[4] = above; res[5] = at; }
     if (w.find((uint32_t)r_dn, digit, above, at)) { res[6] = digit; res[7] = above; res[8] = at; }
     if (w.find((uint32_t)r_top, digit, above, at)) res[9] = digit;
-    __syncthreads();
+    wg_sync();
     if (tid != 0) return;
     KeyPar p = nothing;
     bool done = false;
@@ -216,7 +216,7 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
     }
     if constexpr (HIST)
         for (uint32_t i = tid; i < (uint32_t)NHB; i += NTH) sm.bins.h[i] = 0u;
-    __syncthreads();
+    wg_sync();
     uint32_t all = 0, before[Q];
 #pragma unroll
     for (uint32_t w = 0; w < Q * W; ++w) {
@@ -258,7 +258,7 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
                 }
             }
     }
-    __syncthreads();
+    wg_sync();
     const uint64_t cbase = (uint64_t)tile * SEG_CAP;
     for (uint32_t i = tid; i < min(all, SEG_CAP); i += NTH) { c.idx[cbase + i] = sm.si[i]; c.val[cbase + i] = sm.sv[i]; }
     if constexpr (HIST) hist_flush(sm.bins.h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * NHB, NHB, NTH);
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
         const uint32_t b = d.z;
         stage_tile<STH, HIST>(av, mv, t.par[b], b, tile, (uint32_t)(gi - e - t.off[b]), c, hist, t.ovf + b, sm);
     } else {
-        __syncthreads();
+        wg_sync();
     }
     if (tid == 0) {
         double tot = 0.0;
@@ -347,13 +347,13 @@ __device__ __forceinline__ bool window_find(uint32_t *__restrict__ hist_b, uint3
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) { const uint32_t y = __shfl_up(incl, d, 64); if (lane >= (uint32_t)d) incl += y; }
     if (lane == 63) wsum[wave] = incl;
-    __syncthreads();
+    wg_sync();
     total = 0;
 #pragma unroll
     for (uint32_t w = 0; w < NHB / 64; ++w) { incl += w < wave ? wsum[w] : 0u; total += wsum[w]; }
     const uint64_t upto = (uint64_t)n_hi + incl;
     if (upto >= want && upto - cnt < want) { res[0] = tid; res[1] = (uint32_t)(upto - cnt); res[2] = cnt; }
-    __syncthreads();
+    wg_sync();
     return n_hi < want && (uint64_t)n_hi + total >= want;
 }
 
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ h
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) { acc += __shfl_xor(acc, d, 64); ch += __shfl_xor(ch, d, 64); }
         if ((tid & 63) == 0) { red[tid >> 6] = acc; redh[tid >> 6] = ch; }
-        __syncthreads();
+        wg_sync();
         if (tid == 0) {
             double tot = 0.0;
             for (uint32_t w = 0; w < NHB / 64; w += 4) tot += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
@@ -453,7 +453,7 @@ __device__ __forceinline__ void fb_plan_body(const Tables &t)
         const uint32_t x = fb ? t.tile0[bb + 1] - t.tile0[bb] : 0u;
         const uint32_t incl = block_incl_scan(x, tmp);
         const uint32_t tot = tmp[WG - 1];
-        __syncthreads();
+        wg_sync();
         if (bb < t.B) t.ftile0[bb] = carry + incl - x;
         carry += tot;
     }
@@ -511,11 +511,11 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
             if (lane >= (uint32_t)d) x += ((uint64_t)hi << 32) | (uint64_t)lo;
         }
         if (lane == 63) tmp[wave] = x;
-        __syncthreads();
+        wg_sync();
         uint64_t before = carry, total = 0;
 #pragma unroll
         for (uint32_t w = 0; w < WG / 64; ++w) { before += w < wave ? tmp[w] : 0ull; total += tmp[w]; }
-        __syncthreads();
+        wg_sync();
         uint64_t run = before + x - own;         /* exclusive prefix of this thread's first tile */
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -549,12 +549,12 @@ __device__ __forceinline__ void fb_refine_body(const float *__restrict__ r, cons
         uint32_t prefix = 0;
         for (uint32_t f = f0; f < f1; ++f) {
             if (f >= fend) {                           /* the next bucket (same in every thread) */
-                if (b != NONE) { __syncthreads(); hist_flush(h, hist + (uint64_t)b * NB, NB); __syncthreads(); }
+                if (b != NONE) { wg_sync(); hist_flush(h, hist + (uint64_t)b * NB, NB); wg_sync(); }
                 b = find_bucket<uint32_t>(t.ftile0, t.B, f);
                 fend = t.ftile0[b + 1];
                 prefix = LEVEL == 0 ? 0u : t.T[b];
                 for (int i = tid; i < NB; i += WG) h[i] = 0;
-                __syncthreads();
+                wg_sync();
             }
             const uint32_t tile = t.tile0[b] + (f - t.ftile0[b]);
             const TileGeo s = tile_geo(t, b, tile);
@@ -587,9 +587,9 @@ __device__ __forceinline__ void fb_refine_body(const float *__restrict__ r, cons
                     if ((hit >> j) & 1u) atomicAdd(&h[d[j]], 1u);
             }
         }
-        __syncthreads();
+        wg_sync();
         if (b != NONE) hist_flush(h, hist + (uint64_t)b * NB, NB);
-        __syncthreads();
+        wg_sync();
     }
 }
 

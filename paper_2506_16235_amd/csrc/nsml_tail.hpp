@@ -50,12 +50,12 @@ __device__ __forceinline__ uint64_t block_incl_scan64(uint64_t x, uint64_t *tmp,
         if (lane >= (uint32_t)d) x += ((uint64_t)hi << 32) | (uint64_t)lo;
     }
     if (lane == 63) tmp[wave] = x;
-    __syncthreads();
+    wg_sync();
     uint64_t before = 0;
     total = 0;
 #pragma unroll
     for (uint32_t w = 0; w < NW; ++w) { const uint64_t v = tmp[w]; before += w < wave ? v : 0ull; total += v; }
-    __syncthreads();
+    wg_sync();
     return x + before;
 }
 
@@ -83,7 +83,7 @@ __device__ __forceinline__ bool find_digit_lds(const uint32_t *h, uint32_t want,
             acc += cnt[i];
         }
     }
-    __syncthreads();
+    wg_sync();
     return (uint32_t)total >= want;
 }
 
@@ -96,9 +96,9 @@ __device__ __forceinline__ uint32_t wg_search_le(uint32_t lo, uint32_t hi, uint6
         const uint32_t step = (hi - lo + NT - 1u) / NT;
         const uint32_t p = lo + threadIdx.x * step, q = p + step;
         if (p < hi && f(p) <= x && (q >= hi || x < f(q))) *sh = p;
-        __syncthreads();
+        wg_sync();
         const uint32_t np = *sh;
-        __syncthreads();
+        wg_sync();
         lo = np;
         hi = np + step < hi ? np + step : hi;
     }
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
     for (uint32_t i = tid; i < (uint32_t)NHB; i += WG) h[i] = 0u;
     const uint32_t top = (p.z - 1u) >> p.w;
     auto count = [&](uint32_t key) { if (key < p.z) atomicAdd(&h[min(top - (key >> p.w), (uint32_t)NHB - 1u)], 1u); };
-    __syncthreads();
+    wg_sync();
     const uint32_t len = cnt > SEG_CAP ? 0u : cnt;
     const float *v = c.val + (uint64_t)seg * SEG_CAP;
     for (uint32_t i0 = gl; i0 < len; i0 += lanes * BINS_U) {
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
             }
         }
     }
-    __syncthreads();
+    wg_sync();
     hist_flush(h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * NHB, NHB);
 }
 
@@ -254,7 +254,7 @@ __global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uin
     const uint32_t total = __builtin_amdgcn_readlane(seg_end, 63);
     if (wave == 0) { pre[lane] = seg_start; cg[lane] = 0u; cb[lane] = 0u; }
     if (tid == 0) lcur = 0u;
-    __syncthreads();
+    wg_sync();
     uint32_t *cvalu = reinterpret_cast<uint32_t *>(c.val);
     /* an undecided key of segment s (of this workgroup) */
     auto undecided = [&](uint32_t key, uint32_t s, uint32_t cnt, bool tail) {
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uin
         }
         if (lane == 0) atomicAdd(&cg[q], g);
     }
-    __syncthreads();
+    wg_sync();
     if (wave == 0 && mine) {
         const uint32_t my_b = cb[lane];
         c.G[ms] = (dense ? 0u : mg0) + cg[lane];     /* of a dense one the elements above the band were counted here as well */
@@ -500,7 +500,7 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
     const uint32_t incl = (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)my_cnt, sm.tmp, tot64);
     if (tid < nun) uoff[tid] = incl - my_cnt;
     if (tid == 0) uoff[nun] = (uint32_t)tot64;
-    __syncthreads();
+    wg_sync();
     const uint32_t nkeys = (uint32_t)tot64;
     const bool resident = nkeys <= FIN_KEYS_LDS;
     const uint32_t m1 = (1u << (sh - SH1)) - 1u;       /* level-1 digit: key bits sh-1 .. 7 (12 or 6 bits) */
@@ -529,16 +529,16 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
         atomicAdd(&h1[(e >> SH1) & m1], 1u);
         if (resident) { keys[i] = e; segs[i] = (uint16_t)seg; }
     });
-    __syncthreads();
+    wg_sync();
     if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t d1 = sm.res[0];
     const uint32_t need1 = need0 - sm.res[1];
-    __syncthreads();
+    wg_sync();
     /* pass 2: per segment, entries above digit d1 (high half of the count); level-2 digits (key
      * bits 6..0) of the entries inside d1, which are set aside when they came from memory */
     const uint32_t nseg = seg_hi - seg_lo;
     for (uint32_t i = tid; i < nseg; i += SEL_THREADS) cnts[i] = 0u;       /* takes the place of the level-1 histogram */
-    __syncthreads();
+    wg_sync();
     auto pass2 = [&](uint32_t e, uint32_t seg, bool collect) {
         const uint32_t d = (e >> SH1) & m1;
         if (d > d1) atomicAdd(&cnts[seg], 1u << 16);
@@ -555,13 +555,13 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
     } else {
         for_keys([&](uint32_t, uint32_t e, uint32_t seg) { pass2(e, seg, true); });
     }
-    __syncthreads();
+    wg_sync();
     if (!find_digit_lds<NB2, SEL_WAVES>(sm.h2, need1, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t d2 = sm.res[0];
     const uint32_t T = (b0 << sh) | (d1 << SH1) | d2;
     const uint32_t e_b = need1 - sm.res[1];            /* ties admitted: 1 <= e_b <= keys equal to T */
     const uint32_t aside = sm.res[3];
-    __syncthreads();
+    wg_sync();
     /* pass 3: the entries inside d1 against the last digit: above T, or equal to T (low half) */
     auto pass3 = [&](uint32_t e, uint32_t seg) {
         if (((e >> SH1) & m1) != d1) return;
@@ -576,7 +576,7 @@ __device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c
     } else {
         for_keys([&](uint32_t, uint32_t e, uint32_t seg) { pass3(e, seg); });      /* too many were inside d1 */
     }
-    __syncthreads();
+    wg_sync();
     finish_prefixes<4>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
                     [&](uint32_t, uint32_t s, uint32_t &g, uint32_t &q) {
                         if (s < seg_hi) { const uint32_t v = cnts[s - seg_lo]; g += v >> 16; q += v & 0xFFFFu; }
@@ -636,11 +636,11 @@ __device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c
                 ++kept;
             });
     }
-    __syncthreads();
+    wg_sync();
     if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t prefix24 = (b0 << (sh - SH1)) | sm.res[0];     /* the key bits from position 7 up */
     const uint32_t need1 = need0 - sm.res[1];
-    __syncthreads();
+    wg_sync();
     if (resident) {
         for (uint32_t i = tid; i < nkeys; i += SEL_THREADS) {
             const uint32_t key = keys[i];
@@ -655,11 +655,11 @@ __device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c
                 });
         }
     }
-    __syncthreads();
+    wg_sync();
     if (!find_digit_lds<NB2, SEL_WAVES>(sm.h2, need1, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t T = (prefix24 << 7) | sm.res[0];
     const uint32_t e_b = need1 - sm.res[1];
-    __syncthreads();
+    wg_sync();
     carry = 0;
     finish_prefixes<1>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
                     [&](uint32_t r, uint32_t s, uint32_t &g, uint32_t &q) {
@@ -862,14 +862,14 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
         for (uint32_t i = tid; i < n; i += ENC_T) m = fmaxf(m, fabsf(sv[i]));
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
-        __syncthreads();
+        wg_sync();
         if ((tid & 63) == 0) red[tid >> 6] = m;
-        __syncthreads();
+        wg_sync();
         for (uint32_t w = 0; w < ENC_WAVES; ++w) m = fmaxf(m, red[w]);
         return m;
     };
     auto gather = [&](uint32_t blk0, uint32_t n) {
-        __syncthreads();                                       /* the previous block has been consumed */
+        wg_sync();                                       /* the previous block has been consumed */
         if (tid == 0) filled = 0u;
         const uint32_t j0 = (uint32_t)j0c + blk0;
         uint32_t sA = sFirst;
@@ -878,9 +878,9 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
             auto rank0 = [&](uint32_t s) { return (uint64_t)c.G[s] + (uint64_t)min(e_b, c.E[s]); };
             sA = wg_search_le<ENC_T>(seg_lo, seg_hi, (uint64_t)j0, rank0, &sh);
         }
-        __syncthreads();
+        wg_sync();
         gather_survivors(c, sA, sEnd, T, e_b, j0, n, sv, si, &filled);
-        __syncthreads();
+        wg_sync();
         if (tid == 0 && filled != n) err[0] = 1u;              /* the prefixes and the entries disagree */
     };
 
@@ -1078,7 +1078,7 @@ constexpr unsigned long long HARD_SPIN_TICKS = 500000000ull;      /* 5 s of the 
 __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uint32_t *__restrict__ err)
 {
     __builtin_amdgcn_s_waitcnt(0);                   /* this wavefront's stores have reached the L2 */
-    __syncthreads();
+    wg_sync();
     if (threadIdx.x == 0) {
         __threadfence();                             /* write the L2 back: visible to the other dies */
         __builtin_amdgcn_s_waitcnt(0);               /* ... before the arrival is: the compiler, which sees no access in flight here, leaves the fence's own wait out */
@@ -1091,7 +1091,7 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uin
         __threadfence();                             /* and nothing stale is read afterwards, by the other wavefronts either */
         __builtin_amdgcn_s_waitcnt(0);
     }
-    __syncthreads();
+    wg_sync();
 }
 
 /* Threshold key, tie allowance and prefixes per tile of the buckets on the dense passes, by a team of
@@ -1106,19 +1106,19 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
     grid_barrier(bar, arrivals += nblk, err);
     fb_refine_body<0>(r, t, f0, h, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<0>(t, f0, err, b); }
+    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<0>(t, f0, err, b); }
     grid_barrier(bar, arrivals += nblk, err);
     fb_refine_body<1>(r, t, f1, h, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<1>(t, f1, err, b); }
+    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<1>(t, f1, err, b); }
     grid_barrier(bar, arrivals += nblk, err);
     fb_refine_body<2>(r, t, f2, h, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); pick_body<2>(t, f2, err, b); }
+    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<2>(t, f2, err, b); }
     grid_barrier(bar, arrivals += nblk, err);
     segcount_dense_body(r, t, c, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { __syncthreads(); scan_body(t, c.G, c.E, b); }
+    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); scan_body(t, c.G, c.E, b); }
     grid_barrier(bar, arrivals += nblk, err);
 }
 
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                 v_out[Pb + Rbase + i] = sv[i];
             }
             carry = 0;
-            __syncthreads();
+            wg_sync();
         };
         const uint32_t sp1 = min(t.n_tiles, (unit + 1) * t.dencTiles);
         uint32_t send = 0;
@@ -1242,7 +1242,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                     wsum += __builtin_amdgcn_readlane(incl, 63);
                 }
                 if (lane == 0) wtot[wave] = wsum;
-                __syncthreads();
+                wg_sync();
                 uint32_t woff = 0, all = 0;
 #pragma unroll
                 for (uint32_t w = 0; w < WG / 64; ++w) {
@@ -1271,7 +1271,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                 }
                 run_g += all_g;
                 run_e += all_e;
-                __syncthreads();
+                wg_sync();
                 if (wt_base + WG / 64 < nwt) fetch(wt_base + WG / 64);
                 /* consume what is complete */
                 const uint32_t total = carry + nsurv;
@@ -1370,7 +1370,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                                 for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
                                 float *red = reinterpret_cast<float *>(wtot);
                                 if (lane == 0) red[wave] = mx;
-                                __syncthreads();
+                                wg_sync();
                                 mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
                                 const float scale = mx == 0.0f ? 0.0f : __fdiv_rn(mx, QMAX);
                                 if (tid == 0) scales[Sb + rank0 / chunk] = scale;
@@ -1379,13 +1379,13 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                                     const uint32_t li[2] = {si[base + i0], i0 + 1 < cnt ? si[base + i0 + 1] : 0u};
                                     code_pair(rank0, i0, cnt, scale, xv, li);
                                 }
-                                __syncthreads();
+                                wg_sync();
                             }
                         }
                         p += min(avail, ncode * chunk);
                     }
                 }
-                __syncthreads();
+                wg_sync();
                 /* the rest waits at the front for the next elements */
                 const uint32_t left = total - p;
                 constexpr uint32_t KEEP = (BIG ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK) / WG;
@@ -1397,7 +1397,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                     keep_v[u] = 0.0f; keep_i[u] = 0u;
                     if (i < left) { keep_v[u] = sv[p + i]; keep_i[u] = si[p + i]; }
                 }
-                __syncthreads();
+                wg_sync();
 #pragma unroll
                 for (uint32_t u = 0; u < KEEP; ++u) {
                     const uint32_t i = tid + u * WG;
@@ -1408,7 +1408,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
             }
         }
         if (cur_b != NONE) flush();
-        __syncthreads();
+        wg_sync();
     }
 }
 
@@ -1451,7 +1451,7 @@ __global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restr
      * resident at once even next to the teams of other contexts; a barrier that still cannot
      * complete runs into its time limit and raises the consistency flag. */
     if (t.nhard[2] == 0u || bid >= team) return;
-    __syncthreads();
+    wg_sync();
     nblk = team;
     uint32_t *h = pool;
     uint32_t *bar = t.nhard + 1;
@@ -1491,7 +1491,7 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
             const uint64_t bal = __ballot(todo);
             if (threadIdx.x == 0) todo_sh = (uint32_t)bal;
         }
-        __syncthreads();
+        wg_sync();
         const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t mine = (todo_sh >> (wave * QUANT_PER_WAVE)) & ((1u << QUANT_PER_WAVE) - 1u);
         if (mine) quant_wave<BITS>(v, idx, t, r, val, scales, chunk_b, cw + wave * QUANT_PER_WAVE, mine);
@@ -1513,12 +1513,12 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
             const uint64_t bal = __ballot(todo);
             if (threadIdx.x == 0) todo_big = (uint32_t)bal;
         }
-        __syncthreads();
+        wg_sync();
         uint32_t mask = todo_big;
         while (mask) {
             const uint32_t q = (uint32_t)__builtin_ctz(mask);
             mask &= mask - 1u;
-            __syncthreads();                         /* the previous chunk's use of LDS is over */
+            wg_sync();                         /* the previous chunk's use of LDS is over */
             quant_body<BITS>(v, idx, t, r, val, scales, chunk_b, cw + q);
         }
     }
