@@ -352,13 +352,13 @@ __device__ __forceinline__ void decode4(const uint8_t *__restrict__ vb, const fl
  * tile 326, but 832 against 605 at ratio 0.5).  MAP: type of the tile -> bucket table (16 bits for the
  * entry point without a context). */
 constexpr int DTH = 128;
-template <int BITS, typename MAP, bool NT>
-__global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ idx, const void *__restrict__ val,
+template <int BITS, typename MAP, bool NT, int NTH>
+__global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ idx, const void *__restrict__ val,
                                                    const float *__restrict__ scales, Tables t, const MAP *__restrict__ tile_b,
                                                    const uint32_t *__restrict__ ts, float *__restrict__ dense)
 {
-    constexpr int U = TILE / (4 * DTH);          /* 16-byte stores per thread */
-    constexpr int S = TILE / DTH < 8 ? TILE / DTH : 8;      /* survivors a thread has in flight */
+    constexpr int U = TILE / (4 * NTH);          /* 16-byte stores per thread */
+    constexpr int S = TILE / NTH < 8 ? TILE / NTH : 8;      /* survivors a thread has in flight */
     __shared__ float slots[TILE];
     const uint32_t tile = xcd_tile(blockIdx.x);
     if (tile >= t.n_tiles) return;
@@ -377,7 +377,7 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
          * element j, so the index list (which can only be 0 .. n_b - 1) is not read */
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint64_t gi = s.base + (u * DTH + tid) * 4u;
+            const uint64_t gi = s.base + (u * NTH + tid) * 4u;
             float x[4];
             if (gi >= s.lo && gi + 4 <= s.hi) {
                 decode4<BITS>(vb, sb, gi - s.lo, t.chunk, t.chunkSh, x);
@@ -393,14 +393,14 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
         if (j0 < j1) {                                   /* same for the whole workgroup */
             const uint64_t shift = s.lo - s.base;        /* slot = local index + lo - base */
 #pragma unroll
-            for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(&slots[(u * DTH + tid) * 4]) = out[u];
+            for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(&slots[(u * NTH + tid) * 4]) = out[u];
             wg_sync();
-            for (uint64_t jb = j0; jb < j1; jb += S * DTH) {
+            for (uint64_t jb = j0; jb < j1; jb += S * NTH) {
                 uint32_t li[S];
                 float x[S];
 #pragma unroll
                 for (int u = 0; u < S; ++u) {
-                    const uint64_t j = jb + (uint64_t)u * DTH + tid;
+                    const uint64_t j = jb + (uint64_t)u * NTH + tid;
                     li[u] = NONE;
                     x[u] = 0.0f;
                     if (j < j1) { li[u] = ib[j]; x[u] = decode<BITS>(vb, sb, j, t.chunk, t.chunkSh); }
@@ -414,12 +414,12 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
             }
             wg_sync();
 #pragma unroll
-            for (int u = 0; u < U; ++u) out[u] = *reinterpret_cast<const f4 *>(&slots[(u * DTH + tid) * 4]);
+            for (int u = 0; u < U; ++u) out[u] = *reinterpret_cast<const f4 *>(&slots[(u * NTH + tid) * 4]);
         }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const uint64_t gi = s.base + (u * DTH + tid) * 4u;
+        const uint64_t gi = s.base + (u * NTH + tid) * 4u;
         if (gi >= s.lo && gi + 4 <= s.hi) {
             st_out<NT>(reinterpret_cast<f4 *>(dense + gi), out[u]);
         } else {
@@ -428,6 +428,177 @@ __global__ __launch_bounds__(DTH, 8) void k_decomp(const uint32_t *__restrict__ 
                 if (gi + j >= s.lo && gi + j < s.hi) dense[gi + j] = out[u][j];
         }
     }
+}
+
+/* ------------------------------------------------------------------ everything is sent */
+
+/* The whole of a compress call in which every element of every bucket is sent (ratio 1, the
+ * controller's cap): nothing is selected, survivor j of a bucket is its element j.  One pass: a = g + r,
+ * indices, values or codes, and the coding error over the residual.  A workgroup takes tile i of a
+ * bucket counted from the bucket's own start, so that chunks of 2048 / 2^x survivors (the host checks)
+ * nest in tiles and a scale needs one exchange inside the workgroup.  Bound by HBM: 8 bytes read and
+ * 8 + payload per element written (419 M elements, 32-bit values: 1.30 ms, 6.5 TB/s; selection, dense
+ * encode and the launches between took 2.25).
+ * By-products as from the streaming pass: |grad|^2 and the number of zeros per tile. */
+template <int BITS, bool NT>
+__global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, float *__restrict__ r, Tables t, Cand c,
+                                                 double *__restrict__ tile_sq, uint32_t *__restrict__ idx_out,
+                                                 void *__restrict__ val, float *__restrict__ scales)
+{
+    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
+    __shared__ double sq_w[STH / 64];
+    __shared__ uint32_t z_w[STH / 64];
+    __shared__ float red[STH / 64];
+    const uint32_t tile = xcd_tile(blockIdx.x);
+    if (tile >= t.n_tiles) return;
+    const uint32_t b = t.tile_b[tile];
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lo = t.off[b];
+    const uint32_t nb = (uint32_t)(t.off[b + 1] - lo);
+    const uint64_t e64 = (uint64_t)(tile - t.tile0[b]) * TILE + tid * 4u;      /* local index of this thread's first element */
+    const uint32_t have = e64 >= nb ? 0u : (uint32_t)min((uint64_t)4, nb - e64);
+    const uint32_t e0 = (uint32_t)e64;
+    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    double sq = 0.0;
+    f4 x, y;
+    if (have == 4u) {
+        /* (a bucket may start at any element: 16-byte accesses that are aligned to 4) */
+        if (NT) {
+            x = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(g + lo + e0));
+            y = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(r + lo + e0));
+        } else {
+            __builtin_memcpy(&x, g + lo + e0, 16);
+            __builtin_memcpy(&y, r + lo + e0, 16);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = __fadd_rn(x[j], y[j]);
+        sq = (double)(__fmaf_rn(x.x, x.x, __fmul_rn(x.y, x.y)) + __fmaf_rn(x.z, x.z, __fmul_rn(x.w, x.w)));
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (j < have) {
+                const float xv = g[lo + e0 + j];
+                a[j] = __fadd_rn(xv, r[lo + e0 + j]);
+                sq += (double)__fmul_rn(xv, xv);
+            }
+    }
+    uint32_t zeros = 0;
+#pragma unroll
+    for (uint32_t j = 0; j < 4; ++j) zeros += __popcll(__ballot(j < have && keyof(a[j]) == 0u));
+    sq = wave_sum_last(sq);
+    if (lane == 63) { sq_w[wave] = sq; z_w[wave] = zeros; }
+    uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
+    const uint64_t Pb = t.P[b];
+    float scale = 0.0f;
+    if (BITS <= 8) {
+        float m = 0.0f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m = fmaxf(m, fabsf(a[j]));
+        const uint32_t cq = t.chunk / 4u;                   /* threads per chunk: a power of two from 2 to 512 */
+        for (uint32_t d = 1; d < 64u && d < cq; d <<= 1) m = fmaxf(m, __shfl_xor(m, (int)d, 64));
+        if (lane == 0) red[wave] = m;
+        wg_sync();
+        if (cq > 64u) {
+            const uint32_t wpc = cq / 64u, w0 = wave & ~(wpc - 1u);
+            for (uint32_t w = w0; w < w0 + wpc; ++w) m = fmaxf(m, red[w]);
+        }
+        scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
+        if (have && tid % cq == 0u) scales[t.S[b] + e0 / t.chunk] = scale;
+    } else {
+        wg_sync();
+    }
+    if (tid == 0) {
+        double tot = 0.0;
+        uint32_t z = 0;
+#pragma unroll
+        for (uint32_t w = 0; w < STH / 64; w += 4) {
+            tot += (sq_w[w] + sq_w[w + 1]) + (sq_w[w + 2] + sq_w[w + 3]);
+            z += (z_w[w] + z_w[w + 1]) + (z_w[w + 2] + z_w[w + 3]);
+        }
+        tile_sq[tile] = tot;
+        c.E[tile] = z;
+    }
+    float left[4];
+    int q[4];
+    uint16_t hbits[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        float deq = a[j];
+        q[j] = 0; hbits[j] = 0;
+        if (BITS == 16) {
+            const __half hv = __float2half_rn(a[j]);
+            hbits[j] = __half_as_ushort(hv);
+            deq = __half2float(hv);
+        } else if (BITS <= 8) {
+            if (scale != 0.0f) {
+                float tq = rintf(__fdiv_rn(a[j], scale));
+                tq = fminf(fmaxf(tq, -QMAX), QMAX);
+                q[j] = (int)tq;
+            }
+            deq = __fmul_rn((float)q[j], scale);
+        }
+        left[j] = BITS == 32 ? 0.0f : __fsub_rn(a[j], deq);        /* 32 bits: value - value, nothing is left behind */
+    }
+    if (have == 4u) {
+        const f4 rv = {left[0], left[1], left[2], left[3]}, av = {a[0], a[1], a[2], a[3]};
+        const uint4 iv = make_uint4(e0, e0 + 1u, e0 + 2u, e0 + 3u);
+        if (NT) {
+            f4 fi;
+            __builtin_memcpy(&fi, &iv, 16);
+            __builtin_nontemporal_store(rv, reinterpret_cast<f4 *>(r + lo + e0));
+            __builtin_nontemporal_store(fi, reinterpret_cast<f4 *>(idx_out + Pb + e0));
+            if (BITS == 32) __builtin_nontemporal_store(av, reinterpret_cast<f4 *>(vb + 4ull * e0));
+        } else {
+            __builtin_memcpy(r + lo + e0, &rv, 16);
+            __builtin_memcpy(idx_out + Pb + e0, &iv, 16);
+            if (BITS == 32) __builtin_memcpy(vb + 4ull * e0, &av, 16);
+        }
+        if (BITS == 16) __builtin_memcpy(vb + 2ull * e0, hbits, 8);
+        if (BITS == 8) {
+            const uint32_t w = (uint32_t)(q[0] & 0xFF) | ((uint32_t)(q[1] & 0xFF) << 8) | ((uint32_t)(q[2] & 0xFF) << 16) | ((uint32_t)(q[3] & 0xFF) << 24);
+            __builtin_memcpy(vb + e0, &w, 4);
+        }
+        if (BITS == 4) {
+            const uint16_t w = (uint16_t)((q[0] & 0xF) | ((q[1] & 0xF) << 4) | ((q[2] & 0xF) << 8) | ((q[3] & 0xF) << 12));
+            __builtin_memcpy(vb + (e0 >> 1), &w, 2);
+        }
+    } else {
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j)
+            if (j < have) {
+                r[lo + e0 + j] = left[j];
+                idx_out[Pb + e0 + j] = e0 + j;
+                if (BITS == 32) reinterpret_cast<float *>(vb)[e0 + j] = a[j];
+                if (BITS == 16) reinterpret_cast<uint16_t *>(vb)[e0 + j] = hbits[j];
+                if (BITS == 8) vb[e0 + j] = (uint8_t)q[j];
+                if (BITS == 4 && (j & 1u) == 0u) vb[(e0 + j) >> 1] = (uint8_t)((q[j] & 0xF) | (j + 1 < have ? (q[j + 1] & 0xF) << 4 : 0));
+            }
+    }
+}
+
+/* The per-bucket records of such a call: |grad|^2 and the selection state (threshold key 0, the zeros
+ * admitted as its ties). */
+__global__ __launch_bounds__(WG) void k_full_state(Tables t, Cand c, const double *__restrict__ tile_sq, double *__restrict__ l2sq)
+{
+    __shared__ double red[WG / 64];
+    __shared__ uint32_t redz[WG / 64];
+    const uint32_t b = blockIdx.x, tid = threadIdx.x;
+    double acc = 0.0;
+    uint32_t z = 0;
+    for (uint32_t s = t.tile0[b] + tid; s < t.tile0[b + 1]; s += WG) { acc += tile_sq[s]; z += c.E[s]; }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) { acc += __shfl_xor(acc, d, 64); z += __shfl_xor(z, d, 64); }
+    if ((tid & 63) == 0) { red[tid >> 6] = acc; redz[tid >> 6] = z; }
+    wg_sync();
+    if (tid != 0) return;
+    const bool empty = t.k[b] == 0u;
+    l2sq[b] = (red[0] + red[1]) + (red[2] + red[3]);
+    t.T[b] = empty ? NONE : 0u;
+    t.need[b] = redz[0] + redz[1] + redz[2] + redz[3];
+    t.fast[b] = empty ? PATH_CAND : PATH_ZERO;
+    t.sh[b] = SH0;
+    t.why[b] = 0u;
+    t.par[b] = empty ? make_uint4(NONE, NONE, NONE, SH1) : make_uint4(1u, 1u, 1u, SH1);
 }
 
 /* Zeros, for the dense output that few survivors are then stored into: 16 bytes per thread in the
@@ -447,7 +618,6 @@ __global__ __launch_bounds__(ZERO_T, 8) void k_zero(float *__restrict__ dense, u
  * partly written lines; what helps is that the lines in flight lie close together: a wavefront's
  * 64 survivors are consecutive (four consecutive ones per thread: 53 us for 1.1 M survivors of 109 M
  * elements against 41).  NT: non-temporal stores, for adding into an array larger than the caches. */
-constexpr uint32_t SCAT_PER = 1;
 template <int BITS, bool ADD, bool NT>
 __global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx, const void *__restrict__ val,
                                                 const float *__restrict__ scales, Tables t, uint64_t K,
@@ -456,40 +626,23 @@ __global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx
     constexpr uint32_t LDS_B = 2047;
     __shared__ uint64_t sP[LDS_B + 1];
     const bool in_lds = t.B <= LDS_B;
-    const uint64_t j0 = (uint64_t)blockIdx.x * (WG * SCAT_PER) + threadIdx.x;
-    /* the indices do not need the bucket: fetched while it is searched for */
-    uint32_t li[SCAT_PER];
-#pragma unroll
-    for (uint32_t u = 0; u < SCAT_PER; ++u) li[u] = j0 + u * WG < K ? idx[j0 + u * WG] : NONE;
     if (in_lds) {
         for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
         wg_sync();
     }
-    float x[SCAT_PER], y[SCAT_PER];
-    float *at[SCAT_PER];
-#pragma unroll
-    for (uint32_t u = 0; u < SCAT_PER; ++u) {
-        const uint64_t j = j0 + u * WG;
-        at[u] = nullptr;
-        x[u] = y[u] = 0.0f;
-        if (j < K) {
-            const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
-            const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
-            if (li[u] < nb) {                         /* invalid payload: never leave the bucket */
-                at[u] = dense + lo + li[u];
-                if (ADD) y[u] = *at[u];
-                x[u] = decode<BITS>(reinterpret_cast<const uint8_t *>(val) + t.V[b], BITS <= 8 ? scales + t.S[b] : nullptr,
-                                    j - t.P[b], t.chunk, t.chunkSh);
-            }
-        }
-    }
-#pragma unroll
-    for (uint32_t u = 0; u < SCAT_PER; ++u)
-        if (at[u]) {
-            const float v = ADD ? __fadd_rn(y[u], x[u]) : x[u];
-            if (NT) __builtin_nontemporal_store(v, at[u]);
-            else *at[u] = v;
-        }
+    const uint64_t j = (uint64_t)blockIdx.x * WG + threadIdx.x;
+    if (j >= K) return;
+    const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
+    const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
+    const uint32_t li = idx[j];
+    if (li >= nb) return;                             /* invalid payload: never leave the bucket */
+    float *at = dense + lo + li;
+    const float y = ADD ? *at : 0.0f;
+    const float x = decode<BITS>(reinterpret_cast<const uint8_t *>(val) + t.V[b], BITS <= 8 ? scales + t.S[b] : nullptr,
+                                 j - t.P[b], t.chunk, t.chunkSh);
+    const float v = ADD ? __fadd_rn(y, x) : x;
+    if (NT) __builtin_nontemporal_store(v, at);
+    else *at = v;
 }
 
 }  // namespace

@@ -110,6 +110,7 @@ struct nsml_ctx {
     bool have_prune;                              /* the last compress call had weights */
     bool none_pruned;                             /* ... but its ratio prunes nothing: the weights were not read */
     uint64_t max_nb;                              /* largest bucket of the layout */
+    bool off_mult4;                               /* every bucket of it starts at a multiple of 4 elements */
     double *d_tile_sq;     /* per tile: sum of grad^2 */
     double *d_l2sq;        /* per bucket: sum of grad^2 of the last compress call */
     bool have_l2;
@@ -330,7 +331,8 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
     NSML_HIP(c, hipStreamSynchronize(st));
 
     c->h_off.assign(off, off + B + 1);
-    c->max_nb = 0;
+    c->max_nb = 0; c->off_mult4 = true;
+    for (uint32_t b = 0; b < B; ++b) c->off_mult4 = c->off_mult4 && off[b] % 4 == 0;
     for (uint32_t b = 0; b < B; ++b) c->max_nb = off[b + 1] - off[b] > c->max_nb ? off[b + 1] - off[b] : c->max_nb;
     c->B = B; c->n = n;
     c->n_tiles = (uint32_t)nt; c->n_samp = (uint32_t)nsamp;
@@ -548,6 +550,32 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     float *vdst = bits == 32 ? static_cast<float *>(val) : c->d_v;
     const uint32_t sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
     const bool bins = !c->force_dense && c->n_tiles >= HIST_MAX_TILES;      /* the window's bins by a kernel of their own */
+    /* floor(0.5 * (1 - ratio) * n_b) parameters are pruned: when that is none of any bucket (ratio 1, the
+     * controller's cap), the weights decide nothing and are not read */
+    const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
+    if (none_pruned) weights = nullptr;
+    const bool nt = n > NT_ELEMS;
+    if (c->K == n && !c->force_dense && (bits >= 16 || TILE % c->chunk == 0)) {
+        /* everything is sent: nothing to select (TILE % chunk: chunks nest in tiles) */
+        const bool fnt = nt && c->off_mult4 && aligned(idx, 16) && aligned(val, 16);      /* (misaligned non-temporal stores leave partly written lines) */
+#define NSML_FULL(BITS_)                                                                                                                      \
+    do {                                                                                                                                       \
+        if (fnt) LAUNCHB(c, KID_EF_EMIT, st, (k_full<BITS_, true>), sgrid, STH, grad, residual, t, cd0, c->d_tile_sq, idx, val, scales);        \
+        else LAUNCHB(c, KID_EF_EMIT, st, (k_full<BITS_, false>), sgrid, STH, grad, residual, t, cd0, c->d_tile_sq, idx, val, scales);           \
+    } while (0)
+        switch (bits) {
+        case 32: NSML_FULL(32); break;
+        case 16: NSML_FULL(16); break;
+        case 8:  NSML_FULL(8); break;
+        default: NSML_FULL(4); break;
+        }
+#undef NSML_FULL
+        LAUNCH(c, KID_PLAN, st, k_full_state, B, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
+        c->have_l2 = true;
+        c->have_prune = none_pruned; c->none_pruned = none_pruned;
+        return NSML_OK;
+    }
+
     /* the kernels below zero what they have read of the per-call histograms and flags, so a fill
      * is only needed after something else used the area: another bucket count, a call that did not
      * get to its end */
@@ -555,10 +583,6 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         LAUNCH(c, KID_CLEAR, st, k_clear, clear_grid < 2048 ? clear_grid : 2048, c->d_zero, zw);
     c->zero_clean = false;
 
-    /* floor(0.5 * (1 - ratio) * n_b) parameters are pruned: when that is none of any bucket (ratio 1, the
-     * controller's cap), the weights decide nothing and are not read */
-    const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
-    if (none_pruned) weights = nullptr;
     if (weights) {
         /* Algorithm 2 Step 2: threshold and cut of |w| per bucket, on its own set of tables */
         Tables tw = t;
@@ -591,7 +615,6 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     if (!c->force_dense)
         LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs);
     LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
-    const bool nt = n > NT_ELEMS;
 #define NSML_EF(EMIT_, PRUNE_, NT_, HIST_) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<EMIT_, PRUNE_, NT_, HIST_>), sgrid, STH, grad, residual, t, h.hw, cd0, c->d_tile_sq)
     if (c->force_dense) { if (nt) NSML_EF(false, false, true, false); else NSML_EF(false, false, false, false); }
     else if (bins) { if (pruned) NSML_EF(true, true, true, false); else NSML_EF(true, false, true, false); }      /* (more tiles than that are more elements than NT_ELEMS) */
@@ -694,7 +717,7 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
         const uint32_t zgrid = xcd_grid((uint32_t)((n + ZERO_T * 4 - 1) / (ZERO_T * 4)));
         if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
         else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
-        const uint32_t sgrid = (uint32_t)((K + WG * SCAT_PER - 1) / (WG * SCAT_PER));
+        const uint32_t sgrid = (uint32_t)((K + WG - 1) / WG);
         switch (bits) {
         case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
         case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
@@ -716,11 +739,13 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
     }
     const uint32_t *ts = d_ts;
     const uint32_t grid = xcd_grid(n_tiles);
-    /* (everything sent: a plain decode, faster with plain stores: 606 against 634 us on 419 M elements) */
+    /* everything sent: a plain decode without a chain of dependent loads, so in the streaming kernels' shape (419 M
+     * elements, 32-bit values: 577 us, 606 with DTH threads per tile, 634 with non-temporal stores on top) */
 #define NSML_DECOMP(BITS_)                                                                                                       \
     do {                                                                                                                          \
-        if (n > NT_ELEMS && K != n) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, true>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out); \
-        else LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out);                       \
+        if (K == n) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false, STH>), grid, STH, idx, val, scales, t, tile_b, ts, dense_out);       \
+        else if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, true, DTH>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out); \
+        else LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false, DTH>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out);                  \
     } while (0)
     switch (bits) {
     case 32: NSML_DECOMP(32); break;
@@ -891,7 +916,7 @@ int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val
     rc = ensure_tables(c, ratio, bits, st);
     if (rc) return rc;
     const Tables t = tables_of(c);
-    const uint32_t grid = (uint32_t)((c->K + WG * SCAT_PER - 1) / (WG * SCAT_PER));
+    const uint32_t grid = (uint32_t)((c->K + WG - 1) / WG);
 #define NSML_ACC(BITS_)                                                                                                       \
     do {                                                                                                                       \
         if (n > NT_ELEMS) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, true>), grid, idx, val, scales, t, c->K, dense_inout); \

@@ -8,7 +8,7 @@ import torch
 import oracle
 from paper_2506_16235_amd import binding as nsml
 from paper_2506_16235_amd import workloads as W
-from gpu_util import DEV, Case, say
+from gpu_util import DEV, Case, compare_payload, say
 
 pytestmark = pytest.mark.gpu
 
@@ -522,3 +522,46 @@ def test_context_sized_for_a_maximum_ratio():
     with pytest.raises(nsml.NsmlError) as e:
         small.compress(c.g, c.r, off, 0.11, 8)
     assert e.value.code == nsml.ECAP
+
+
+@pytest.mark.parametrize("bits,chunk", [(32, 2048), (16, 24), (8, 8), (8, 256), (8, 2048), (4, 64), (4, 2048), (8, 4096), (4, 24)])
+def test_everything_sent(path, bits, chunk):
+    """Ratio 1: every element of every bucket is sent, coded in one pass where chunks nest in tiles of
+    2048 (4096 and 24 do not: the general path).  Bucket starts at every alignment mod 4, buckets of
+    one tile, one element less and more, an empty one; zeros of both signs; a payload that starts 4
+    bytes into its buffers; three steps with the residual carried; norm and bucket state checked."""
+    sizes = [2048, 1, 2047, 0, 2049, 6, 70_003, 4096, 3]
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    ctx = nsml.Context(n, len(sizes), chunk)
+    r = torch.zeros(n, device=DEV)
+    r_h = np.zeros(n, dtype=np.float32)
+    _, K, vb, ns = nsml.payload_layout(off, 1.0, bits, chunk)
+    assert K == n
+    for step in range(3):
+        g = _rand(n, 300 + step)
+        g[5:900:3] = 0.0
+        g[6:900:3] = -0.0
+        if step == 0:
+            g[2049:4096] = 0.0                      # a whole bucket of zeros (and its scale)
+        idx = torch.empty(K + 1, dtype=torch.int32, device=DEV)[1:]
+        val = torch.empty((vb + 7) // 4 * 4 + 4, dtype=torch.uint8, device=DEV)[4:]
+        sc = torch.empty(max(ns, 1), dtype=torch.float32, device=DEV)
+        ctx.compress(g, r, off, 1.0, bits, idx, val, sc)
+        dense = ctx.decompress(idx, val, sc, n, off, 1.0, bits)
+        torch.cuda.synchronize()
+        assert ctx.path_stats() == ((0, 8) if path == "dense" else (8, 0))
+        g_h = g.cpu().numpy()
+        acc = (g_h + r_h)[:2048]
+        w_idx, w_val, w_sc = oracle.compress(g_h, r_h, off, 1.0, bits, chunk)
+        got = (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns])
+        compare_payload(off, 1.0, bits, chunk, got, (w_idx, w_val, w_sc))
+        assert np.array_equal(r.cpu().numpy().view(np.uint32), r_h.view(np.uint32))
+        w_dense = oracle.decompress(w_idx, w_val, w_sc, n, off, 1.0, bits, chunk)
+        assert np.array_equal(dense.cpu().numpy().view(np.uint32), w_dense.view(np.uint32))
+        st = ctx.bucket_state(0)
+        if path == "auto":
+            assert (st["path"], st["T"], st["need"], st["k"]) == (3, 0, int((acc == 0.0).sum()), 2048), st
+        tot, per = ctx.last_l2norm(len(sizes))
+        w_tot, w_per = oracle.l2norm(g_h, off)
+        assert abs(tot - w_tot) <= 1e-6 * w_tot and np.all(np.abs(per - w_per) <= 1e-6 * np.maximum(w_per, 1e-30))
