@@ -250,21 +250,15 @@ __device__ __forceinline__ void tilestart_one(const uint32_t *__restrict__ idx, 
         for (uint32_t tt = tcur + 1; tt <= tiles_b; ++tt) tsb[tt] = kb;
 }
 
+/* P: the buckets' first survivors, in memory or in LDS */
 template <uint32_t TS_PER>
-__global__ __launch_bounds__(WG) void k_tilestart(const uint32_t *__restrict__ idx, Tables t,
-                                                  uint64_t K, uint32_t *__restrict__ ts)
+__device__ __forceinline__ void tilestart_walk(const uint32_t *__restrict__ idx, const Tables &t, const uint64_t *P, uint64_t K,
+                                               uint32_t *__restrict__ ts)
 {
-    constexpr uint32_t LDS_B = 2047;
-    __shared__ uint64_t sP[LDS_B + 1];
-    const bool in_lds = t.B <= LDS_B;
-    if (in_lds) {
-        for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
-        wg_sync();
-    }
     const uint64_t stride = (uint64_t)gridDim.x * WG * TS_PER;
     for (uint64_t j0 = ((uint64_t)blockIdx.x * WG + threadIdx.x) * TS_PER; j0 < K; j0 += stride) {
-        const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j0) : find_bucket<uint64_t>(t.P, t.B, j0);
-        const uint64_t Pb = t.P[b], Pn = t.P[b + 1];
+        const uint32_t b = find_bucket<uint64_t>(P, t.B, j0);
+        const uint64_t Pb = P[b], Pn = P[b + 1];
         if (j0 > Pb && j0 + TS_PER < Pn) {
             /* all of them inside one bucket, none its first or last survivor: only tile changes matter */
             const uint32_t tiles_b = t.tile0[b + 1] - t.tile0[b];
@@ -282,22 +276,32 @@ __global__ __launch_bounds__(WG) void k_tilestart(const uint32_t *__restrict__ i
                     for (uint32_t tt = v[i - 1] + 1; tt <= v[i]; ++tt) tsb[tt] = jj0 + i - 1;
             }
         } else {
-            for (uint64_t j = j0; j < min(K, j0 + TS_PER); ++j) {
-                const uint32_t bj = j < Pn ? b : (in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j));
-                tilestart_one(idx, t, bj, j, ts);
-            }
+            for (uint64_t j = j0; j < min(K, j0 + TS_PER); ++j)
+                tilestart_one(idx, t, j < Pn ? b : find_bucket<uint64_t>(P, t.B, j), j, ts);
         }
+    }
+}
+
+template <uint32_t TS_PER>
+__global__ __launch_bounds__(WG) void k_tilestart(const uint32_t *__restrict__ idx, Tables t,
+                                                  uint64_t K, uint32_t *__restrict__ ts)
+{
+    constexpr uint32_t LDS_B = 2047;
+    __shared__ uint64_t sP[LDS_B + 1];
+    if (t.B <= LDS_B) {
+        for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
+        wg_sync();
+        tilestart_walk<TS_PER>(idx, t, sP, K, ts);
+    } else {
+        tilestart_walk<TS_PER>(idx, t, t.P, K, ts);
     }
 }
 
 /* The same table by binary search, one thread per tile: cheaper than walking the whole index
  * list once a tile holds many survivors (high ratios).  An index list that is not ascending (an
  * invalid payload) gives entries that are wrong but still within [0, k_b]. */
-__global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restrict__ idx, Tables t, uint32_t n_tiles,
-                                                         uint32_t *__restrict__ ts)
+__device__ __forceinline__ void tilestart_find(const uint32_t *__restrict__ idx, const Tables &t, uint32_t g, uint32_t *__restrict__ ts)
 {
-    const uint32_t g = blockIdx.x * WG + threadIdx.x;
-    if (g >= n_tiles) return;
     const uint32_t b = find_bucket<uint32_t>(t.tile0, t.B, g);
     const uint32_t i = g - t.tile0[b], tiles_b = t.tile0[b + 1] - t.tile0[b];
     const uint32_t kb = t.k[b];
@@ -312,6 +316,12 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
     uint32_t *tsb = ts + t.tile0[b] + b;
     tsb[i] = lo;
     if (i + 1 == tiles_b) tsb[tiles_b] = kb;
+}
+__global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restrict__ idx, Tables t, uint32_t n_tiles,
+                                                         uint32_t *__restrict__ ts)
+{
+    const uint32_t g = blockIdx.x * WG + threadIdx.x;
+    if (g < n_tiles) tilestart_find(idx, t, g, ts);
 }
 
 /* Four consecutive values j0 .. j0 + 3 of a bucket's value stream, decoded; 8- and 32-bit ones in one

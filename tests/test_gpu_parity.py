@@ -565,3 +565,52 @@ def test_everything_sent(path, bits, chunk):
         tot, per = ctx.last_l2norm(len(sizes))
         w_tot, w_per = oracle.l2norm(g_h, off)
         assert abs(tot - w_tot) <= 1e-6 * w_tot and np.all(np.abs(per - w_per) <= 1e-6 * np.maximum(w_per, 1e-30))
+
+
+@pytest.mark.parametrize("B", [1, 63, 64, 255, 256, 257, 2047, 2048, 2500])
+def test_setup_tables(B):
+    """The prefix tables made by one workgroup: bucket counts around its 256 threads and its largest table,
+    odd sizes, empty buckets; both code widths whose streams do not start at multiples of the count."""
+    rng = np.random.default_rng(B)
+    sizes = [int(x) for x in rng.integers(0, 90, size=B)]
+    sizes[B // 2] = 9000
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    ctx = nsml.Context(n, B, 24)
+    g = _rand(n, B)
+    g_h = g.cpu().numpy()
+    for ratio, bits in ((0.3, 4), (0.07, 8)):
+        r = torch.zeros(n, device=DEV)
+        r_h = np.zeros(n, dtype=np.float32)
+        idx, val, sc = ctx.compress(g, r, off, ratio, bits)
+        dense = ctx.decompress(idx, val, sc, n, off, ratio, bits)
+        torch.cuda.synchronize()
+        _, K, vb, ns = nsml.payload_layout(off, ratio, bits, 24)
+        want = oracle.compress(g_h, r_h, off, ratio, bits, 24)
+        got = (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns])
+        compare_payload(off, ratio, bits, 24, got, want)
+        assert np.array_equal(r.cpu().numpy().view(np.uint32), r_h.view(np.uint32))
+        w_dense = oracle.decompress(*want, n, off, ratio, bits, 24)
+        assert np.array_equal(dense.cpu().numpy().view(np.uint32), w_dense.view(np.uint32))
+
+
+@pytest.mark.parametrize("B", [1, 256, 257, 320])
+@pytest.mark.parametrize("ratio", [0.001, 0.01, 0.3, 1.0])
+def test_static_setup(B, ratio):
+    """Tables, tile map and tile starts of a call without a context in one launch: by scatter, by walking
+    the survivors, by search, everything sent; odd and empty buckets, a payload that is not ascending."""
+    rng = np.random.default_rng(B)
+    sizes = [int(x) for x in rng.integers(0, 900, size=B)]
+    sizes[-1] = 300_001
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    ctx = nsml.Context(n, B, 256)
+    g, r = _rand(n, 3), torch.zeros(n, device=DEV)
+    idx, val, sc = ctx.compress(g, r, off, ratio, 4)
+    want = ctx.decompress(idx, val, sc, n, off, ratio, 4)
+    out = torch.full((n,), 7.0, device=DEV)
+    nsml.decompress_static(idx, val, sc, n, off, ratio, 4, 256, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+    nsml.decompress_static(idx.flip(0).contiguous(), val, sc, n, off, ratio, 4, 256, out)      # refused nowhere, wrong nowhere else
+    torch.cuda.synchronize()
