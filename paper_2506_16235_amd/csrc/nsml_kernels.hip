@@ -429,9 +429,9 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
          * runtime how many of them a compute unit holds (the variants per width use the same LDS) */
         int occ = 0;
         c->hard_occ[0] = c->hard_occ[1] = 1;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_hard<8, false>, (int)WG, 0) == hipSuccess && occ > 0)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_hard<8, false>, (int)HTH, 0) == hipSuccess && occ > 0)
             c->hard_occ[0] = occ < (int)hard_wg_per_cu(false) ? occ : (int)hard_wg_per_cu(false);
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_hard<8, true>, (int)WG, 0) == hipSuccess && occ > 0)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_hard<8, true>, (int)HTH, 0) == hipSuccess && occ > 0)
             c->hard_occ[1] = occ < (int)hard_wg_per_cu(true) ? occ : (int)hard_wg_per_cu(true);
         (void)hipGetLastError();
     }
@@ -662,7 +662,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         const uint32_t team = (uint32_t)c->n_cu < hgrid ? (uint32_t)c->n_cu : hgrid;
         const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
         const int stream_coding = c->chunk <= DENC_MAX_CHUNK ? 1 : 0;
-#define NSML_HARD(BITS_, BIG_) LAUNCH(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, residual, t, cd0, h.f0, h.f1, h.f2, idx, vdst, val, scales, c->d_flags, stream_coding, team)
+#define NSML_HARD(BITS_, BIG_) LAUNCHB(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, HTH, residual, t, cd0, h.f0, h.f1, h.f2, idx, vdst, val, scales, c->d_flags, stream_coding, team)
         switch (bits) {
         case 32: NSML_HARD(32, false); break;
         case 16: if (big) NSML_HARD(16, true); else NSML_HARD(16, false); break;

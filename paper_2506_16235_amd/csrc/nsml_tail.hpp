@@ -1126,8 +1126,8 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
  * dense accumulator and whose threshold is known (PATH_BAND, PATH_ZERO), with chunks of at most
  * DENC_MAX_CHUNK survivors.  Survivors are dense here (ratios from an eighth up, or an
  * embedding whose few non-zero rows all survive), so the work is laid out by elements: a
- * workgroup streams a unit of dencTiles consecutive tiles, 4096 elements at a time (one
- * wave-tile per wavefront); ranks come from ballots and a prefix over the four wavefronts; the
+ * workgroup streams a unit of dencTiles consecutive tiles, 4096 elements at a time (512
+ * consecutive ones per wavefront); ranks come from ballots and a prefix over the eight wavefronts; the
  * survivors are put into LDS in rank order behind the ones still waiting for their chunk to
  * fill up; every chunk that is complete is coded from LDS by one wavefront (absmax, scale,
  * codes, indices, and the coding error scattered into the accumulator lines the workgroup has
@@ -1135,10 +1135,62 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
  * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
  * those afterwards (same test, see chunk_coded_by_stream).  16-bit values need no chunk and are
  * all coded here. */
+/* What bounds it: half of 419 M elements sent as 8-bit codes take 956 us; without the scattered residual
+ * 680, without any store 690, so the steps' chain of barriers and the instructions between them (59 per element
+ * before the counts came from comparison masks and the codes from a product, 37 now) come first.  Was 1010 with four
+ * wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
+ * alignment, residual stores 8 elements apart) 975, full residual lines 1057, non-temporal index stores 1169.
+ * 32-bit values, 25.6 M elements: 65 -> 62. */
 constexpr uint32_t DENC_SMALL_CHUNK = 256;         /* up to here a wavefront codes a chunk */
 constexpr uint32_t DENC_MAX_CHUNK = 2048;
-constexpr uint32_t DENC_STEP = (WG / 64) * WTILE;   /* elements per step: all of them can be survivors */
+constexpr uint32_t DENC_STEP = 4096;               /* elements per step: all of them can be survivors */
+constexpr uint32_t HTH = 512;                      /* threads of a workgroup of k_hard */
+constexpr uint32_t DENC_ROWS = DENC_STEP / HTH / 4; /* 16-byte accesses per thread and step */
+constexpr uint32_t DENC_WT = DENC_STEP / (HTH / 64); /* consecutive elements of one wavefront per step */
 constexpr uint32_t denc_cap(bool big) { return DENC_STEP + (big ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK); }
+
+/* Codes of four values: rint(x / scale) of the correctly rounded quotient, clamped; 0 where the scale is.
+ * The product with the reciprocal differs from that quotient by less than 4e-5 (v_rcp_f32 is
+ * good to 2^-23, the two roundings add 2^-23, and the quotient is below 128.5), so away from the middle between two codes it gives the same code; the few
+ * values near one, and what is not a finite number, are divided. */
+template <int BITS>
+__device__ __forceinline__ void quantize_four(const float (&x)[4], float scale, int (&q)[4])
+{
+    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
+    const float inv = __builtin_amdgcn_rcpf(scale);
+    bool sure = true;
+    float w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float y = __fmul_rn(x[j], inv);
+        w[j] = rintf(y);
+        sure = sure && fabsf(__fsub_rn(y, w[j])) < 0.4999f;      /* (false for NaN) */
+    }
+    if (!sure) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = scale != 0.0f ? rintf(__fdiv_rn(x[j], scale)) : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = (int)fminf(fmaxf(w[j], -QMAX), QMAX);
+}
+
+/* Largest over the wavefront, the same in all lanes. */
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max(float v)
+{
+    const int i = __float_as_int(v);
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = dpp_max<0x111, 0xF>(v);
+    v = dpp_max<0x112, 0xF>(v);
+    v = dpp_max<0x114, 0xF>(v);
+    v = dpp_max<0x118, 0xF>(v);
+    v = dpp_max<0x142, 0xA>(v);
+    v = dpp_max<0x143, 0xC>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
 
 template <int BITS, bool BIG>       /* BIG: chunks of more than DENC_SMALL_CHUNK survivors */
 __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const Tables &t, const Cand &c,
@@ -1148,21 +1200,22 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                                                   uint32_t bid, uint32_t nblk)
 {
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;     /* (unused for 16 / 32 bits) */
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t chunk = t.chunk;
     const uint32_t n_units = (t.n_tiles + t.dencTiles - 1) / t.dencTiles;
     for (uint32_t unit = bid; unit < n_units; unit += nblk) {
         uint32_t cur_b = NONE;
         /* state of the stream: one bucket's consecutive tiles inside the unit */
         uint32_t T = 0, e_b = 0, kb = 0, run_g = 0, run_e = 0, carry = 0, Rbase = 0;
-        uint64_t Pb = 0, lo = 0;
+        uint64_t Pb = 0;
         uint8_t *vb = nullptr;
         uint64_t Sb = 0;
         bool head = false;
+        uint32_t li_stream = 0;
         /* what is left in LDS when a stream ends belongs to a chunk that goes on elsewhere */
         auto flush = [&]() {
-            for (uint32_t i = tid; i < carry; i += WG) {
-                idx_out[Pb + Rbase + i] = si[i];
+            for (uint32_t i = tid; i < carry; i += HTH) {
+                idx_out[Pb + Rbase + i] = si[i] + li_stream;
                 v_out[Pb + Rbase + i] = sv[i];
             }
             carry = 0;
@@ -1179,117 +1232,147 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
             if ((path != PATH_BAND && path != PATH_ZERO) || t.k[b] == 0u) { cur_b = NONE; continue; }
             const TileGeo s = tile_geo(t, b, tile);
             cur_b = b;
-            T = t.T[b]; e_b = t.need[b]; kb = t.k[b]; Pb = t.P[b]; lo = s.lo;
+            T = t.T[b]; e_b = t.need[b]; kb = t.k[b]; Pb = t.P[b];
             vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
             Sb = t.S[b];
             run_g = c.G[tile]; run_e = c.E[tile];
             Rbase = run_g + min(e_b, run_e);
             carry = 0;
             head = BITS <= 8 && (Rbase % chunk) != 0u;
-            const uint32_t nwt = (send - tile) * (TILE / WTILE);
+            const uint32_t nwt = (send - tile) * (TILE / DENC_WT);
             /* the next 4096 elements are fetched while the survivors of these are coded */
-            float xn[4][4];
-            uint32_t mn[4];
+            float xn[DENC_ROWS][4];
+            uint32_t mn[DENC_ROWS];
             auto fetch = [&](uint32_t wt_base) {
                 const uint32_t wt = wt_base + wave;
-                const uint64_t wb = s.base + (uint64_t)wt * WTILE;
+                const uint64_t wb = s.base + (uint64_t)wt * DENC_WT;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < (int)DENC_ROWS; ++u) {
                     const uint64_t gi = wb + (uint64_t)(u * 64 + lane) * 4;
                     mn[u] = 0;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) xn[u][j] = 0.0f;
                     if (wt < nwt) {
-                        if (wb >= s.lo && wb + WTILE <= s.hi) {          /* the whole wave-tile lies inside the bucket */
+                        if (wb >= s.lo && wb + DENC_WT <= s.hi) {          /* the whole wave-tile lies inside the bucket */
                             const f4 v = *reinterpret_cast<const f4 *>(r + gi);
                             xn[u][0] = v.x; xn[u][1] = v.y; xn[u][2] = v.z; xn[u][3] = v.w;
                             mn[u] = 0xFu;
                         } else {
                             mn[u] = load_quad(r, gi, s.lo, s.hi, xn[u]);
                         }
-                        if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, tile, wt * WG + u * 64 + lane);
+                        if (t.pmask) mn[u] &= ~pruned_bits(t.pmask, tile, wt * (DENC_WT / 4) + u * 64 + lane);
                     }
                 }
             };
             fetch(0);
-            for (uint32_t wt_base = 0; wt_base < nwt; wt_base += WG / 64) {
+            const uint32_t li_base = li_stream = (uint32_t)(s.base - s.lo);       /* bucket-local index = position from s.base + this (mod 2^32) */
+            float *rb = r + s.base;
+            for (uint32_t wt_base = 0; wt_base < nwt; wt_base += HTH / 64) {
                 const uint32_t wt = wt_base + wave;
-                const uint64_t wb = s.base + (uint64_t)wt * WTILE;
-                if (tid == 0 && (run_g != c.G[tile + wt_base / (TILE / WTILE)] || run_e != c.E[tile + wt_base / (TILE / WTILE)]))
+                const uint64_t wb = s.base + (uint64_t)wt * DENC_WT;
+                if (tid == 0 && (run_g != c.G[tile + wt_base / (TILE / DENC_WT)] || run_e != c.E[tile + wt_base / (TILE / DENC_WT)]))
                     err[0] = 1u;                     /* the prefixes and the elements disagree */
-                float x[4][4];
-                uint32_t fg[4], fe[4];
+                float x[DENC_ROWS][4];
+                bool fg[DENC_ROWS][4];
+                const bool full = wt < nwt && wb >= s.lo && wb + DENC_WT <= s.hi && !t.pmask;      /* every element counts */
+                uint64_t ties = 0;
+                /* Ranks: a lane's elements of a row are consecutive, so the elements before one are those of
+                 * the lower lanes of its row, of the earlier rows and of the earlier wavefronts.  A
+                 * comparison's result is the mask over the wavefront that counting needs. */
+                uint32_t row_g[DENC_ROWS], row_e[DENC_ROWS];       /* elements above / equal to T in a row (same in all lanes) */
+                uint32_t bef_g[DENC_ROWS];                         /* those above T in the lower lanes of the row */
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    fg[u] = fe[u] = 0;
+                for (int u = 0; u < (int)DENC_ROWS; ++u) {
+                    row_g[u] = row_e[u] = bef_g[u] = 0;
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         x[u][j] = xn[u][j];
                         const uint32_t key = keyof(x[u][j]);
-                        if ((mn[u] >> j) & 1u) { fg[u] |= (key > T ? 1u : 0u) << j; fe[u] |= (key == T ? 1u : 0u) << j; }
+                        const bool in = full || ((mn[u] >> j) & 1u);
+                        fg[u][j] = in && key > T;
+                        const uint64_t bg = __ballot(fg[u][j]), be = __ballot(in && key == T);
+                        row_g[u] += (uint32_t)__popcll(bg);
+                        row_e[u] += (uint32_t)__popcll(be);
+                        bef_g[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, bef_g[u]));
+                        ties |= be;
                     }
                 }
-                /* ranks: a lane's elements of a row are consecutive, so the elements before one are
-                 * those of the lower lanes of its row, of the earlier rows and of the earlier
-                 * wavefronts.  Counts of elements above T (low half) and equal to T (high half)
-                 * travel in one word; 4096 elements cannot carry from one half into the other. */
-                uint32_t ex[4], wsum = 0;
+                uint32_t wsum = 0;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint32_t cnt = (uint32_t)__popc(fg[u]) | ((uint32_t)__popc(fe[u]) << 16);
-                    const uint32_t incl = wave_incl_scan(cnt);
-                    ex[u] = wsum + incl - cnt;
-                    wsum += __builtin_amdgcn_readlane(incl, 63);
-                }
+                for (int u = 0; u < (int)DENC_ROWS; ++u) wsum += row_g[u] | (row_e[u] << 16);      /* 4096 elements cannot carry */
                 if (lane == 0) wtot[wave] = wsum;
                 wg_sync();
                 uint32_t woff = 0, all = 0;
+                {
+                    const uint32_t mine = wtot[lane & (HTH / 64 - 1)];
 #pragma unroll
-                for (uint32_t w = 0; w < WG / 64; ++w) {
-                    if (w < wave) woff += wtot[w];
-                    all += wtot[w];
+                    for (uint32_t w = 0; w < HTH / 64; ++w) {
+                        const uint32_t v = (uint32_t)__builtin_amdgcn_readlane((int)mine, w);
+                        if (w < wave) woff += v;
+                        all += v;
+                    }
                 }
                 const uint32_t all_g = all & 0xFFFFu, all_e = all >> 16;
                 const uint32_t Rnext = run_g + min(e_b, run_e);               /* rank of the next survivor = Rbase + carry */
                 const uint32_t nsurv = (run_g + all_g + min(e_b, run_e + all_e)) - Rnext;
+                /* survivors into LDS in rank order, behind those that wait */
+                auto put = [&](int u, int j, uint32_t slot) {
+                    sv[slot] = x[u][j];
+                    si[slot] = wt * DENC_WT + (uint32_t)(u * 64 + lane) * 4 + (uint32_t)j;
+                };
+                uint32_t g0 = run_g + (woff & 0xFFFFu), e0 = run_e + (woff >> 16);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const uint64_t gi = wb + (uint64_t)(u * 64 + lane) * 4;
-                    const uint32_t before = woff + ex[u];
-                    uint32_t pe = run_e + (before >> 16);
-                    /* a lane's survivors are consecutive in rank: one slot computed, then counted on */
-                    uint32_t slot = carry + (run_g + (before & 0xFFFFu) + min(e_b, pe) - Rnext);
-                    const uint32_t li0 = (uint32_t)(gi - s.lo);
+                for (int u = 0; u < (int)DENC_ROWS; ++u) {
+                    if (ties == 0) {                 /* none in this wavefront, the ordinary case */
+                        uint32_t slot = carry + g0 + bef_g[u] + min(e_b, e0) - Rnext;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool ise = (fe[u] >> j) & 1u;
-                        const bool take = ((fg[u] >> j) & 1u) || (ise && pe < e_b);
-                        if (take) { sv[slot] = x[u][j]; si[slot] = li0 + j; }
-                        slot += take ? 1u : 0u;
-                        pe += ise ? 1u : 0u;
+                        for (int j = 0; j < 4; ++j) {
+                            if (fg[u][j]) put(u, j, slot);
+                            slot += fg[u][j] ? 1u : 0u;
+                        }
+                    } else {
+                        uint32_t pe = e0;
+                        bool fe[4];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            fe[j] = (full || ((mn[u] >> j) & 1u)) && keyof(x[u][j]) == T;
+                            const uint64_t be = __ballot(fe[j]);
+                            pe = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, pe));
+                        }
+                        uint32_t slot = carry + g0 + bef_g[u] + min(e_b, pe) - Rnext;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const bool take = fg[u][j] || (fe[j] && pe < e_b);
+                            if (take) put(u, j, slot);
+                            slot += take ? 1u : 0u;
+                            pe += fe[j] ? 1u : 0u;
+                        }
                     }
+                    g0 += row_g[u];
+                    e0 += row_e[u];
                 }
                 run_g += all_g;
                 run_e += all_e;
                 wg_sync();
-                if (wt_base + WG / 64 < nwt) fetch(wt_base + WG / 64);
+                if (wt_base + HTH / 64 < nwt) fetch(wt_base + HTH / 64);
                 /* consume what is complete */
                 const uint32_t total = carry + nsurv;
                 uint32_t p = 0;
                 if (BITS >= 16) {
                     /* no scale to wait for: every survivor is final at once */
-                    for (uint32_t i = tid; i < total; i += WG) {
+                    for (uint32_t i = tid; i < total; i += HTH) {
                         const float xv = sv[i];
-                        const uint32_t li = si[i];
-                        idx_out[Pb + Rbase + i] = li;
+                        const uint32_t at = si[i];
+                        idx_out[Pb + Rbase + i] = at + li_base;
+                        float left = 0.0f;               /* value - value: nothing is left behind */
                         if (BITS == 16) {
                             const __half hv = __float2half_rn(xv);
                             reinterpret_cast<__half *>(vb)[Rbase + i] = hv;
-                            r[lo + li] = __fsub_rn(xv, __half2float(hv));
+                            left = __fsub_rn(xv, __half2float(hv));
                         } else {
                             reinterpret_cast<float *>(vb)[Rbase + i] = xv;
-                            r[lo + li] = 0.0f;       /* value - value: nothing is left behind */
                         }
+                        *reinterpret_cast<float *>(reinterpret_cast<char *>(rb) + at * 4u) = left;
                     }
                     p = total;
                 } else {
@@ -1297,8 +1380,8 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                         /* up to the next chunk boundary: part of a chunk that began before this stream */
                         const uint32_t to_edge = chunk - (Rbase % chunk);
                         const uint32_t nh = min(total, to_edge);
-                        for (uint32_t i = tid; i < nh; i += WG) {
-                            idx_out[Pb + Rbase + i] = si[i];
+                        for (uint32_t i = tid; i < nh; i += HTH) {
+                            idx_out[Pb + Rbase + i] = si[i] + li_base;
                             v_out[Pb + Rbase + i] = sv[i];
                         }
                         p = nh;
@@ -1308,55 +1391,45 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                         const uint32_t avail = total - p;
                         const uint32_t nfull = avail / chunk, rem = avail - nfull * chunk;
                         const uint32_t ncode = nfull + ((rem != 0u && Rbase + total == kb) ? 1u : 0u);   /* the bucket's last chunk may be short */
-                        /* one pair of consecutive survivors of a chunk: codes, index, coding error */
-                        auto code_pair = [&](uint32_t rank0, uint32_t i0, uint32_t cnt, float scale, const float (&xv)[2],
-                                             const uint32_t (&li)[2]) {
-                            const int have = (i0 + 1 < cnt) ? 2 : 1;
-                            int qq[2] = {0, 0};
-                            float res[2] = {0.0f, 0.0f};
+                        /* four survivors of a chunk, `step` apart, so that the lanes of a wavefront hold consecutive
+                         * ones: values and positions; then codes, indices and coding errors */
+                        float xv[4];
+                        uint32_t at[4];
+                        auto take_four = [&](uint32_t base, uint32_t i0, uint32_t step, uint32_t cnt) {
 #pragma unroll
-                            for (int hh = 0; hh < 2; ++hh) {
-                                if (hh >= have) continue;
-                                if (scale != 0.0f) {
-                                    float tq = rintf(__fdiv_rn(xv[hh], scale));
-                                    tq = fminf(fmaxf(tq, -QMAX), QMAX);
-                                    qq[hh] = (int)tq;
-                                }
-                                res[hh] = __fsub_rn(xv[hh], __fmul_rn((float)qq[hh], scale));
-                                if (BITS == 8) reinterpret_cast<int8_t *>(vb)[rank0 + i0 + hh] = (int8_t)qq[hh];
-                                idx_out[Pb + rank0 + i0 + hh] = li[hh];
+                            for (int h = 0; h < 4; ++h) {
+                                const uint32_t i = i0 + h * step;
+                                xv[h] = i < cnt ? sv[base + i] : 0.0f;
+                                at[h] = i < cnt ? si[base + i] : 0u;
                             }
-                            if (BITS == 4) vb[(rank0 + i0) >> 1] = (uint8_t)((qq[0] & 0xF) | ((qq[1] & 0xF) << 4));
+                            return fmaxf(fmaxf(fabsf(xv[0]), fabsf(xv[1])), fmaxf(fabsf(xv[2]), fabsf(xv[3])));
+                        };
+                        auto code_four = [&](uint32_t rank0, uint32_t i0, uint32_t step, uint32_t cnt, float scale) {
+                            int qq[4];
+                            quantize_four<BITS>(xv, scale, qq);
 #pragma unroll
-                            for (int hh = 0; hh < 2; ++hh)
-                                if (hh < have) r[lo + li[hh]] = res[hh];
+                            for (int h = 0; h < 4; ++h) {
+                                const uint32_t i = i0 + h * step;
+                                /* a pair's codes in one byte at 4 bits: the odd lane's comes over */
+                                const int odd = BITS == 4 ? __builtin_amdgcn_mov_dpp(qq[h], 0xF5, 0xF, 0xF, false) : 0;      /* lanes 1 1 3 3 */
+                                if (i < cnt) {
+                                    idx_out[Pb + rank0 + i] = at[h] + li_base;
+                                    if (BITS == 8) vb[rank0 + i] = (uint8_t)qq[h];
+                                    else if (!(lane & 1u)) vb[(rank0 + i) >> 1] = (uint8_t)((qq[h] & 0xF) | ((odd & 0xF) << 4));
+                                    *reinterpret_cast<float *>(reinterpret_cast<char *>(rb) + at[h] * 4u) = __fsub_rn(xv[h], __fmul_rn((float)qq[h], scale));
+                                }
+                            }
                         };
                         if (!BIG) {
-                            /* chunks of up to 256: a wavefront each, two pairs per lane */
-                            for (uint32_t q = wave; q < ncode; q += WG / 64) {
+                            /* chunks of up to 256: a wavefront each */
+                            for (uint32_t q = wave; q < ncode; q += HTH / 64) {
                                 const uint32_t base = p + q * chunk;
                                 const uint32_t cnt = min(chunk, total - base);
                                 const uint32_t rank0 = Rbase + base;
-                                float xv[2][2];
-                                uint32_t li[2][2];
-#pragma unroll
-                                for (int u = 0; u < 2; ++u)
-#pragma unroll
-                                    for (int hh = 0; hh < 2; ++hh) {
-                                        const uint32_t i = 2 * (lane + u * 64) + hh;
-                                        xv[u][hh] = i < cnt ? sv[base + i] : 0.0f;
-                                        li[u][hh] = i < cnt ? si[base + i] : 0u;
-                                    }
-                                float mx = fmaxf(fmaxf(fabsf(xv[0][0]), fabsf(xv[0][1])), fmaxf(fabsf(xv[1][0]), fabsf(xv[1][1])));
-#pragma unroll
-                                for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+                                const float mx = wave_max(take_four(base, lane, 64, cnt));
                                 const float scale = mx == 0.0f ? 0.0f : __fdiv_rn(mx, QMAX);
                                 if (lane == 0) scales[Sb + rank0 / chunk] = scale;
-#pragma unroll
-                                for (int u = 0; u < 2; ++u) {
-                                    const uint32_t i0 = 2 * (lane + u * 64);
-                                    if (i0 < cnt) code_pair(rank0, i0, cnt, scale, xv[u], li[u]);
-                                }
+                                code_four(rank0, lane, 64, cnt, scale);
                             }
                         } else {
                             /* longer chunks: the whole workgroup on one chunk after the other */
@@ -1364,21 +1437,16 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                                 const uint32_t base = p + q * chunk;
                                 const uint32_t cnt = min(chunk, total - base);
                                 const uint32_t rank0 = Rbase + base;
-                                float mx = 0.0f;
-                                for (uint32_t i = tid; i < cnt; i += WG) mx = fmaxf(mx, fabsf(sv[base + i]));
-#pragma unroll
-                                for (int d = 32; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, 64));
+                                const float wm = wave_max(take_four(base, tid, HTH, cnt));
                                 float *red = reinterpret_cast<float *>(wtot);
-                                if (lane == 0) red[wave] = mx;
+                                if (lane == 0) red[wave] = wm;
                                 wg_sync();
-                                mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+                                float mx = 0.0f;
+#pragma unroll
+                                for (uint32_t w = 0; w < HTH / 64; ++w) mx = fmaxf(mx, red[w]);
                                 const float scale = mx == 0.0f ? 0.0f : __fdiv_rn(mx, QMAX);
                                 if (tid == 0) scales[Sb + rank0 / chunk] = scale;
-                                for (uint32_t i0 = 2 * tid; i0 < cnt; i0 += 2 * WG) {
-                                    const float xv[2] = {sv[base + i0], i0 + 1 < cnt ? sv[base + i0 + 1] : 0.0f};
-                                    const uint32_t li[2] = {si[base + i0], i0 + 1 < cnt ? si[base + i0 + 1] : 0u};
-                                    code_pair(rank0, i0, cnt, scale, xv, li);
-                                }
+                                code_four(rank0, tid, HTH, cnt, scale);
                                 wg_sync();
                             }
                         }
@@ -1388,19 +1456,19 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                 wg_sync();
                 /* the rest waits at the front for the next elements */
                 const uint32_t left = total - p;
-                constexpr uint32_t KEEP = (BIG ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK) / WG;
+                constexpr uint32_t KEEP = BIG ? DENC_MAX_CHUNK / HTH : 1u;
                 float keep_v[KEEP];
                 uint32_t keep_i[KEEP];
 #pragma unroll
                 for (uint32_t u = 0; u < KEEP; ++u) {
-                    const uint32_t i = tid + u * WG;
+                    const uint32_t i = tid + u * HTH;
                     keep_v[u] = 0.0f; keep_i[u] = 0u;
                     if (i < left) { keep_v[u] = sv[p + i]; keep_i[u] = si[p + i]; }
                 }
                 wg_sync();
 #pragma unroll
                 for (uint32_t u = 0; u < KEEP; ++u) {
-                    const uint32_t i = tid + u * WG;
+                    const uint32_t i = tid + u * HTH;
                     if (i < left) { sv[i] = keep_v[u]; si[i] = keep_i[u]; }
                 }
                 Rbase += p;
@@ -1426,17 +1494,17 @@ __device__ __forceinline__ bool chunk_coded_by_stream(const Tables &t, const Can
 }
 
 /* workgroups of k_hard per compute unit: what its LDS allows (all of them must be resident) */
-constexpr uint32_t hard_wg_per_cu(bool big) { return big ? 3u : 4u; }
-constexpr uint32_t hard_lds(bool big) { return 2 * denc_cap(big) + 2 * (WG / 64); }    /* words; also holds the level-1 histogram */
+constexpr uint32_t hard_wg_per_cu(bool) { return 3u; }
+constexpr uint32_t hard_lds(bool big) { return 2 * denc_cap(big) + HTH / 64; }    /* words; also holds the level-1 histogram */
 
 template <int BITS, bool BIG>
-__global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ f0,
+__global__ __launch_bounds__(HTH, hard_wg_per_cu(BIG) * (HTH / 256)) void k_hard(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ f0,
                                              uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ idx,
                                              float *__restrict__ vdst, void *__restrict__ val,
                                              float *__restrict__ scales, uint32_t *__restrict__ err, int stream_coding, uint32_t team)
 {
     static_assert(hard_lds(BIG) >= NB1, "the pool must hold the level-1 histogram");
-    __shared__ uint32_t pool[hard_lds(BIG)];
+    __shared__ __align__(16) uint32_t pool[hard_lds(BIG)];
     if (t.nhard[0] == 0u) return;                    /* every bucket was decided and coded from its staged elements */
     const uint32_t bid = blockIdx.x;
     uint32_t nblk = gridDim.x;
@@ -1444,7 +1512,8 @@ __global__ __launch_bounds__(WG, hard_wg_per_cu(BIG)) void k_hard(float *__restr
     if (stream_coding)
         dense_encode_body<BITS, BIG>(r, t, c, idx, vdst, val, scales, reinterpret_cast<float *>(pool),
                                      pool + denc_cap(BIG), pool + 2 * denc_cap(BIG), err, bid, nblk);
-    else
+    if (threadIdx.x >= WG) return;                   /* what follows is work for four wavefronts */
+    if (!stream_coding)
         write_dense_body<BITS == 32>(r, t, c, idx, vdst, (1u << PATH_BAND) | (1u << PATH_ZERO), bid, nblk);
     /* the dense passes: the first `team` workgroups only.  They are dispatched before the others
      * of this launch, and the team is small enough (one workgroup per compute unit) to be
