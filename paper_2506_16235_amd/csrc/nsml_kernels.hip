@@ -72,6 +72,7 @@
 #include "nsml_prune.hpp"
 #include "nsml_codec.hpp"
 #include "nsml_tail.hpp"
+#include "nsml_small.hpp"
 
 /* ====================================================================== host side */
 
@@ -575,6 +576,20 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         }
 #undef NSML_FULL
         LAUNCH(c, KID_PLAN, st, k_full_state, B, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
+        c->have_l2 = true;
+        c->have_prune = none_pruned; c->none_pruned = none_pruned;
+        return NSML_OK;
+    }
+
+    /* Small buckets: the whole call in one launch.  A workgroup fills a compute unit, so at most two rounds of
+     * them; with more the chain, whose launches all buckets share, is faster. */
+    if (!weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B <= 2u * (uint32_t)c->n_cu) {
+        switch (bits) {
+        case 32: LAUNCHB(c, KID_EF_EMIT, st, k_small<32>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
+        case 16: LAUNCHB(c, KID_EF_EMIT, st, k_small<16>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
+        case 8:  LAUNCHB(c, KID_EF_EMIT, st, k_small<8>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
+        default: LAUNCHB(c, KID_EF_EMIT, st, k_small<4>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
+        }
         c->have_l2 = true;
         c->have_prune = none_pruned; c->none_pruned = none_pruned;
         return NSML_OK;

@@ -614,3 +614,60 @@ def test_static_setup(B, ratio):
     assert torch.equal(out.view(torch.int32), want.view(torch.int32))
     nsml.decompress_static(idx.flip(0).contiguous(), val, sc, n, off, ratio, 4, 256, out)      # refused nowhere, wrong nowhere else
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("bits,chunk", [(32, 256), (16, 24), (8, 8), (8, 24), (8, 4096), (4, 256), (4, 40)])
+@pytest.mark.parametrize("ratio", [0.01, 0.3, 0.98])
+def test_small_buckets(path, bits, chunk, ratio):
+    """A workgroup per bucket: the largest that fits (32764), one row and its edges, every start mod 4, an empty
+    bucket, all zeros, huge groups of equal keys, infinities and NaN (payload as the chain of kernels makes it);
+    two steps with the residual, norm and bucket state."""
+    sizes = [32764, 1, 0, 4095, 4096, 4097, 2, 3, 20_001, 700, 5]
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    _, K, vb, ns = nsml.payload_layout(off, ratio, bits, chunk)
+    ctxs = [nsml.Context(n, len(sizes), chunk) for _ in range(2)]
+    ctxs[1].set_option("rescan", 1)                  # never in one launch
+    rs = [torch.zeros(n, device=DEV) for _ in range(2)]
+    r_h = np.zeros(n, dtype=np.float32)
+    for step in range(3):
+        g = _rand(n, 900 + step)
+        g[:32764:2] = 0.25 * torch.sign(g[:32764:2])       # half of the largest bucket: two keys
+        g[int(off[3]):int(off[4])] = 0.0
+        g[int(off[5]) + 5] = -0.0
+        if step == 2:                                      # from here on the two routes are compared
+            p = int(off[8])
+            g[p + 7], g[p + 8], g[p + 4000] = float("inf"), float("-inf"), float("nan")
+        out = []
+        for ctx, r in zip(ctxs, rs):
+            idx, val, sc = ctx.compress(g, r, off, ratio, bits)
+            torch.cuda.synchronize()
+            out.append((idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns].view(np.uint32)))
+        for a, w in zip(*out):
+            assert np.array_equal(a, w)
+        ra, rb = (r.cpu().numpy() for r in rs)
+        if step == 2:                                      # (32 bits: the chain leaves 0 or NaN there, by the path)
+            ra[[p + 7, p + 8, p + 4000]] = rb[[p + 7, p + 8, p + 4000]] = 0.0
+        nan = np.isnan(ra)
+        assert np.array_equal(nan, np.isnan(rb)) and np.array_equal(ra[~nan].view(np.uint32), rb[~nan].view(np.uint32))
+        assert ctxs[0].path_stats() == ((0, 10) if path == "dense" else (10, 0))
+        if step == 2:
+            continue
+        want = oracle.compress(g.cpu().numpy(), r_h, off, ratio, bits, chunk)
+        compare_payload(off, ratio, bits, chunk, (out[0][0], out[0][1], out[0][2].view(np.float32)), want)
+        assert np.array_equal(ra.view(np.uint32), r_h.view(np.uint32))
+        for b in (0, 3, 8):
+            st, sw = ctxs[0].bucket_state(b), ctxs[1].bucket_state(b)
+            assert (st["T"], st["need"], st["k"]) == (sw["T"], sw["need"], sw["k"])
+        tot, per = ctxs[0].last_l2norm(len(sizes))
+        w_tot, w_per = oracle.l2norm(g.cpu().numpy(), off)
+        assert abs(tot - w_tot) <= 1e-6 * w_tot and np.all(np.abs(per - w_per) <= 1e-6 * np.maximum(w_per, 1e-30))
+
+
+def test_small_bucket_limits(path):
+    """One element more than fits a workgroup, and more buckets than two for every compute unit, take the chain."""
+    for sizes in ([32765, 100], [40] * (2 * torch.cuda.get_device_properties(0).multi_processor_count + 1)):
+        off = W.offsets_of(sizes)
+        c = Case(_rand(int(off[-1]), 5), off, chunk=64)
+        c.step(0.05, 8)
+        c.step(0.2, 16)
