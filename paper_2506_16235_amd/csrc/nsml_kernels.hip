@@ -740,10 +740,10 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
         else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
         const uint32_t sgrid = (uint32_t)((K + WG - 1) / WG);
         switch (bits) {
-        case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
-        case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false, false>), sgrid, idx, val, scales, t, K, dense_out); break;
-        case 8:  LAUNCH(c, KID_DECOMP, st, (k_scatter<8, false, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
-        default: LAUNCH(c, KID_DECOMP, st, (k_scatter<4, false, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
+        case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false>), sgrid, idx, val, scales, t, K, dense_out); break;
+        case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false>), sgrid, idx, val, scales, t, K, dense_out); break;
+        case 8:  LAUNCH(c, KID_DECOMP, st, (k_scatter<8, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
+        default: LAUNCH(c, KID_DECOMP, st, (k_scatter<4, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
         }
         return NSML_OK;
     }
@@ -947,11 +947,7 @@ int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val
     if (rc) return rc;
     const Tables t = tables_of(c);
     const uint32_t grid = (uint32_t)((c->K + WG - 1) / WG);
-#define NSML_ACC(BITS_)                                                                                                       \
-    do {                                                                                                                       \
-        if (n > NT_ELEMS) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, true>), grid, idx, val, scales, t, c->K, dense_inout); \
-        else LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, false>), grid, idx, val, scales, t, c->K, dense_inout);             \
-    } while (0)
+#define NSML_ACC(BITS_) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true>), grid, idx, val, scales, t, c->K, dense_inout)
     switch (bits) {
     case 32: NSML_ACC(32); break;
     case 16: NSML_ACC(16); break;
