@@ -34,6 +34,8 @@
  *   quant     codes what hard left uncoded (chunks that straddle its work units; PATH_DENSE)
  *   tilestart, decomp    payload -> dense, each output line written once (few survivors: zeros, then
  *             the survivors stored over them)
+ * Two kinds of call need none of the selection: small buckets (small: a workgroup per bucket does the
+ * whole call) and ratio 1 (full: one streaming pass).
  * Every path gives the same bytes.
  *
  * With weights (Algorithm 2 Step 2) a weight pass comes first: sample of |w| -> band around the
@@ -50,7 +52,7 @@
  * One translation unit: the device code lives in nsml_device_common.hpp (tables, geometry,
  * histogram helpers), nsml_select.hpp (sample .. plan, the radix steps over the dense
  * accumulator), nsml_prune.hpp (weight pass), nsml_codec.hpp (value coding of leftover chunks,
- * decompress) and nsml_tail.hpp (select_count .. quant, the bitmap kernels); this file holds
+ * decompress, ratio 1), nsml_tail.hpp (select_count .. quant, the bitmap kernels) and nsml_small.hpp; this file holds
  * the context, the launch sequences and the C-ABI entry points.
  */
 #include <hip/hip_runtime.h>
