@@ -583,8 +583,10 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         return NSML_OK;
     }
 
-    /* Small buckets: the whole call in one launch.  A workgroup fills a compute unit, so at most two rounds of
-     * them; with more the chain, whose launches all buckets share, is faster. */
+    /* Small buckets: the whole call in one launch.  A workgroup fills a compute unit, so its time goes in rounds,
+     * while the buckets share the chain's launches: the line is drawn at two rounds, where it takes about half of
+     * the chain's time (us, 1 % sent as 8-bit codes, this / the chain: 1 bucket of 32764 elements 39 / 69, 256 of
+     * them 51 / 124, 512 98 / 205; 512 of 500 26 / 86, of 40 26 / 70). */
     if (!weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B <= 2u * (uint32_t)c->n_cu) {
         switch (bits) {
         case 32: LAUNCHB(c, KID_EF_EMIT, st, k_small<32>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
