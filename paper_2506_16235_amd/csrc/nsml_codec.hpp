@@ -627,10 +627,9 @@ __global__ __launch_bounds__(ZERO_T, 8) void k_zero(float *__restrict__ dense, u
  * The indices of a payload are distinct, so plain read-modify-write needs no atomics.  Bound by the
  * partly written lines; what helps is that the lines in flight lie close together: a wavefront's
  * 64 survivors are consecutive (four consecutive ones per thread: 53 us for 1.1 M survivors of 109 M
- * elements against 41).  Additions run from the last survivor to the first: what a fill or the addition
- * before wrote last is still in the 256 MB cache (38.6 us per payload of 1.1 M, from the front 41.9, with
- * non-temporal stores 41.4). */
-template <int BITS, bool ADD>
+ * elements against 41).  A workgroup takes blocks of 256 survivors gridDim.x apart; the host picks the
+ * grid and the direction (scatter_grid). */
+template <int BITS, bool ADD, bool BACK>
 __global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx, const void *__restrict__ val,
                                                 const float *__restrict__ scales, Tables t, uint64_t K,
                                                 float *__restrict__ dense)
@@ -638,21 +637,26 @@ __global__ __launch_bounds__(WG) void k_scatter(const uint32_t *__restrict__ idx
     constexpr uint32_t LDS_B = 2047;
     __shared__ uint64_t sP[LDS_B + 1];
     const bool in_lds = t.B <= LDS_B;
-    const uint64_t j = (uint64_t)(ADD ? gridDim.x - 1u - blockIdx.x : blockIdx.x) * WG + threadIdx.x;
-    const uint32_t li = j < K ? idx[j] : NONE;        /* fetched while its bucket is searched for */
+    const uint64_t n_blk = (K + WG - 1) / WG;
     if (in_lds) {
         for (uint32_t i = threadIdx.x; i <= t.B; i += WG) sP[i] = t.P[i];
         wg_sync();
     }
-    if (j >= K) return;
-    const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
-    const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
-    if (li >= nb) return;                             /* invalid payload: never leave the bucket */
-    float *at = dense + lo + li;
-    const float y = ADD ? *at : 0.0f;
-    const float x = decode<BITS>(reinterpret_cast<const uint8_t *>(val) + t.V[b], BITS <= 8 ? scales + t.S[b] : nullptr,
-                                 j - t.P[b], t.chunk, t.chunkSh);
-    *at = ADD ? __fadd_rn(y, x) : x;
+    for (uint64_t q = blockIdx.x; q < n_blk; q += gridDim.x) {
+        const uint64_t j = (BACK ? n_blk - 1u - q : q) * WG + threadIdx.x;
+        if (j >= K) continue;
+        const uint32_t li = idx[j];                       /* fetched while its bucket is searched for */
+        const uint32_t b = in_lds ? find_bucket<uint64_t>(sP, t.B, j) : find_bucket<uint64_t>(t.P, t.B, j);
+        const uint64_t lo = t.off[b], nb = t.off[b + 1] - lo;
+        if (li >= nb) continue;                           /* invalid payload: never leave the bucket */
+        float *at = dense + lo + li;
+        float y = 0.0f;
+        if (ADD && BACK) y = *at;                         /* few survivors: the long way first */
+        const float x = decode<BITS>(reinterpret_cast<const uint8_t *>(val) + t.V[b], BITS <= 8 ? scales + t.S[b] : nullptr,
+                                     j - t.P[b], t.chunk, t.chunkSh);
+        if (ADD && !BACK) y = *at;
+        *at = ADD ? __fadd_rn(y, x) : x;
+    }
 }
 
 }  // namespace

@@ -731,6 +731,20 @@ int nsml_compress_pruned(nsml_ctx *c, const float *grad, float *residual, const 
  * over the zeros. */
 constexpr uint64_t SCATTER_SHARE = 512;
 static bool decomp_by_scatter(int variant, uint64_t K, uint64_t n) { return variant > 0 || (variant < 0 && K * SCATTER_SHARE <= n); }
+/* Workgroups of k_scatter for K survivors of n elements, and from which end.  Up to one survivor in eight
+ * elements additions run from the last to the first, a block of 256 per workgroup: what a fill or the
+ * addition before wrote last is still in the 256 MB cache (a fill and four payloads of 1.1 M into 110 M
+ * elements, 8-bit codes: 57.2 us per payload, from the front 58.6; of 3.3 M: 96.9 and 98.5).  From there to one
+ * in four from the front (84 M into 419 M: 778 us, from the back 805, in a loop 824).  Beyond that nearly every
+ * line is touched and what counts is the order of the payload's reads: 8192 workgroups that walk it together
+ * (all of 110 M: 448 us, a block per workgroup 594 from the front and 653 from the back, 32768 workgroups 468;
+ * half of 34 M, 32-bit values: 89, 106, 129, 97). */
+struct ScatterGrid { uint32_t grid; bool backward; };
+static ScatterGrid scatter_grid(uint64_t K, uint64_t n, bool add)
+{
+    const uint64_t blocks = (K + WG - 1) / WG, most = add && K * 4u > n ? 8192u : 1u << 23;      /* (2^32 threads cannot be launched) */
+    return {(uint32_t)std::min(blocks, most), add && K * 8u <= n};
+}
 static bool tilestart_by_search(uint64_t K, uint32_t n_tiles) { return K >= 32ull * n_tiles; }      /* many survivors per tile */
 template <typename MAP>
 static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint64_t n, uint64_t K, const MAP *tile_b, uint32_t *d_ts,
@@ -742,12 +756,12 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
         const uint32_t zgrid = xcd_grid((uint32_t)((n + ZERO_T * 4 - 1) / (ZERO_T * 4)));
         if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
         else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
-        const uint32_t sgrid = (uint32_t)((K + WG - 1) / WG);
+        const ScatterGrid sg = scatter_grid(K, n, false);
         switch (bits) {
-        case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false>), sgrid, idx, val, scales, t, K, dense_out); break;
-        case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false>), sgrid, idx, val, scales, t, K, dense_out); break;
-        case 8:  LAUNCH(c, KID_DECOMP, st, (k_scatter<8, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
-        default: LAUNCH(c, KID_DECOMP, st, (k_scatter<4, false>),  sgrid, idx, val, scales, t, K, dense_out); break;
+        case 32: LAUNCH(c, KID_DECOMP, st, (k_scatter<32, false, false>), sg.grid, idx, val, scales, t, K, dense_out); break;
+        case 16: LAUNCH(c, KID_DECOMP, st, (k_scatter<16, false, false>), sg.grid, idx, val, scales, t, K, dense_out); break;
+        case 8:  LAUNCH(c, KID_DECOMP, st, (k_scatter<8, false, false>),  sg.grid, idx, val, scales, t, K, dense_out); break;
+        default: LAUNCH(c, KID_DECOMP, st, (k_scatter<4, false, false>),  sg.grid, idx, val, scales, t, K, dense_out); break;
         }
         return NSML_OK;
     }
@@ -950,8 +964,12 @@ int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val
     rc = ensure_tables(c, ratio, bits, st);
     if (rc) return rc;
     const Tables t = tables_of(c);
-    const uint32_t grid = (uint32_t)((c->K + WG - 1) / WG);
-#define NSML_ACC(BITS_) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true>), grid, idx, val, scales, t, c->K, dense_inout)
+    const ScatterGrid sg = scatter_grid(c->K, c->n, true);
+#define NSML_ACC(BITS_)                                                                                                                     \
+    do {                                                                                                                                     \
+        if (sg.backward) LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, true>), sg.grid, idx, val, scales, t, c->K, dense_inout);      \
+        else LAUNCH(c, KID_DECOMP_ACC, st, (k_scatter<BITS_, true, false>), sg.grid, idx, val, scales, t, c->K, dense_inout);                 \
+    } while (0)
     switch (bits) {
     case 32: NSML_ACC(32); break;
     case 16: NSML_ACC(16); break;

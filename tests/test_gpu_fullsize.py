@@ -337,3 +337,31 @@ def test_maximum_bucket_size_properties():
     dense = ctx.decompress(ctx_idx := got.to(torch.int32), val, sc, n, off, ratio, bits)
     assert torch.equal(dense[pos], q * want_scale)
     assert int(torch.count_nonzero(dense)) == k
+
+
+def test_accumulate_more_than_2_32_survivors():
+    """A payload of more survivors than a launch can have threads: every element of 2^32 + 20011 sent as 4-bit
+    codes of scale 1, added to ones; every second code is 3, the others -2."""
+    sizes = [1 << 31, 20_011, 1 << 31]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    n = int(off[-1])
+    _, K, vb, ns = nsml.payload_layout(off, 1.0, 4, 2048)
+    assert K == n > 1 << 32
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    idx = torch.empty(K, dtype=torch.int32, device=DEV)
+    at = 0
+    for nb in sizes:
+        for lo in range(0, nb, 1 << 28):
+            hi = min(nb, lo + (1 << 28))
+            idx[at + lo:at + hi] = torch.arange(lo, hi, device=DEV).to(torch.int32)
+        at += nb
+    val = torch.full(((vb + 3) // 4 * 4,), 0xE3, dtype=torch.uint8, device=DEV)
+    sc = torch.ones(ns, dtype=torch.float32, device=DEV)
+    ctx = nsml.Context(n, len(sizes), 2048)
+    dense = torch.ones(n, dtype=torch.float32, device=DEV)
+    ctx.decompress_accumulate(idx, val, sc, off, 1.0, 4, dense)
+    torch.cuda.synchronize()
+    for b in range(len(sizes)):           # the code's place in its byte counts from the bucket's start
+        x = dense[int(off[b]):int(off[b + 1])]
+        assert bool((x[0::2] == 4.0).all()) and bool((x[1::2] == -1.0).all())

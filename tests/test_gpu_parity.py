@@ -437,6 +437,26 @@ def test_decompress_accumulate(bits):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits", [4, 8, 16, 32])
+@pytest.mark.parametrize("ratio", [0.124, 0.13, 0.249, 0.26, 1.0])
+def test_accumulate_dense_payloads(bits, ratio):
+    """Both sides of each line of the accumulation's rule, with more survivors than its largest grid takes at
+    once (8192 x 256) at ratio 1; the last block of 256 not full."""
+    sizes = [5, 70_000, 0, 33_333, 2_100_001]
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    ctx = nsml.Context(n, len(sizes), 64)
+    dense = torch.full((n,), 0.125, device=DEV)
+    want = np.full(n, 0.125, dtype=np.float32)
+    for w in range(2):
+        g = _rand(n, 400 + w, sigma=1e-2)
+        idx, val, sc = ctx.compress(g, torch.zeros(n, device=DEV), off, ratio, bits)
+        ctx.decompress_accumulate(idx, val, sc, off, ratio, bits, dense)
+        w_idx, w_val, w_sc = oracle.compress(g.cpu().numpy(), np.zeros(n, np.float32), off, ratio, bits, 64)
+        oracle.decompress_accumulate(w_idx, w_val, w_sc, want, off, ratio, bits, 64)
+    assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 def test_hip_graph_capture_and_replay(path):
     """A compress + decompress step captured in a HIP graph (no memset nodes, no host
     synchronisation once the tables exist) replays correctly: three replays with fresh gradients
