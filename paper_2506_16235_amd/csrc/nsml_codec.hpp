@@ -352,17 +352,17 @@ __device__ __forceinline__ void decode4(const uint8_t *__restrict__ vb, const fl
     }
 }
 
-/* Dense output, a tile per workgroup: every output line is written once.  An empty tile is zeros at
- * once.  Otherwise the tile is assembled in LDS (zeros, then the decoded survivors that fall inside it,
- * found through the tile-start table).  A bucket of which every element was sent needs neither LDS nor its
- * index list: its output is the decoded value stream.  Bound by the 4 bytes per element written; the
- * chain tile -> survivors' place -> survivors -> LDS is four memory round trips long, so a compute unit
- * has to hold many tiles: 16 workgroups of two wavefronts with four stores per thread (419 M elements at
- * ratio 0.01: 330 us; four workgroups of eight wavefronts 570, eight of four 430, one wavefront per
- * tile 326, but 832 against 605 at ratio 0.5).  MAP: type of the tile -> bucket table (16 bits for the
- * entry point without a context). */
-constexpr int DTH = 128;
-template <int BITS, typename MAP, bool NT, int NTH>
+/* Dense output, a tile per workgroup: every output line is written once, past the caches (with plain stores
+ * half of 4 M elements into one of nine buffers 19.0 us, so 15.8; 25 M at ratio 0.05 36.2 and 27.4).  An empty
+ * tile is zeros at once.  Otherwise the tile is assembled in LDS (zeros, then the decoded survivors that fall
+ * inside it, found through the tile-start table).  Where a tile has four survivors and more for every thread, a
+ * thread takes four consecutive ones at a time, indices and codes each in one load (419 M elements at ratio 0.9:
+ * 8-bit codes 642 us, one by one 776; for 32-bit values, whose loads are as wide either way, 852 and 839, so not
+ * there).  A bucket of which every element was sent needs neither LDS nor its index list: its output is the
+ * decoded value stream.  Bound by the 4 bytes per element written; the chain tile -> survivors' place ->
+ * survivors -> LDS is four memory round trips long, so a compute unit has to hold many tiles.  NTH: see
+ * launch_decompress.  MAP: type of the tile -> bucket table (16 bits for the entry point without a context). */
+template <int BITS, typename MAP, int NTH>
 __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ idx, const void *__restrict__ val,
                                                    const float *__restrict__ scales, Tables t, const MAP *__restrict__ tile_b,
                                                    const uint32_t *__restrict__ ts, float *__restrict__ dense)
@@ -405,7 +405,37 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
 #pragma unroll
             for (int u = 0; u < U; ++u) *reinterpret_cast<f4 *>(&slots[(u * NTH + tid) * 4]) = out[u];
             wg_sync();
-            for (uint64_t jb = j0; jb < j1; jb += S * NTH) {
+            uint32_t one = j0;                           /* from here on one by one */
+            if (BITS <= 16 && j1 - j0 >= 4u * NTH) {
+                constexpr int V = TILE / (4 * NTH) < 2 ? 1 : 2;      /* groups a thread has in flight */
+                const uint32_t ngrp = (j1 - j0) / 4u;
+                one = j0 + 4u * ngrp;
+                for (uint32_t q0 = 0; q0 < ngrp; q0 += V * NTH) {
+                    uint4 li[V];
+                    float x[V][4];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const uint32_t q = q0 + v * NTH + tid;
+                        li[v] = make_uint4(NONE, NONE, NONE, NONE);
+                        x[v][0] = x[v][1] = x[v][2] = x[v][3] = 0.0f;
+                        if (q < ngrp) {
+                            const uint64_t j = (uint64_t)j0 + 4ull * q;
+                            __builtin_memcpy(&li[v], ib + j, 16);        /* (aligned to 4) */
+                            decode4<BITS>(vb, sb, j, t.chunk, t.chunkSh, x[v]);
+                        }
+                    }
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const uint32_t l4[4] = {li[v].x, li[v].y, li[v].z, li[v].w};
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const uint64_t slot = (uint64_t)l4[u] + shift;
+                            if (l4[u] < nb && slot < TILE) slots[slot] = x[v][u];
+                        }
+                    }
+                }
+            }
+            for (uint64_t jb = one; jb < j1; jb += S * NTH) {
                 uint32_t li[S];
                 float x[S];
 #pragma unroll
@@ -431,7 +461,7 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
     for (int u = 0; u < U; ++u) {
         const uint64_t gi = s.base + (u * NTH + tid) * 4u;
         if (gi >= s.lo && gi + 4 <= s.hi) {
-            st_out<NT>(reinterpret_cast<f4 *>(dense + gi), out[u]);
+            st_out<true>(reinterpret_cast<f4 *>(dense + gi), out[u]);
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)

@@ -778,21 +778,27 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
     }
     const uint32_t *ts = d_ts;
     const uint32_t grid = xcd_grid(n_tiles);
-    /* everything sent: a plain decode without a chain of dependent loads, so in the streaming kernels' shape (419 M
-     * elements, 32-bit values: 577 us, 606 with DTH threads per tile, 634 with non-temporal stores on top) */
-#define NSML_DECOMP(BITS_)                                                                                                       \
-    do {                                                                                                                          \
-        if (K == n) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false, STH>), grid, STH, idx, val, scales, t, tile_b, ts, dense_out);       \
-        else if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, true, DTH>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out); \
-        else LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, false, DTH>), grid, DTH, idx, val, scales, t, tile_b, ts, dense_out);                  \
+    /* Threads per tile.  Everything sent is a plain decode without a chain of dependent loads: whole values in the
+     * streaming kernels' shape (419 M elements: 537 us with 512 threads, 575 with 128), narrower ones with more of
+     * them per thread (8 bits: 393 us with 128 threads, 474 with 512; 16: 415 and 450; 4: 540 and 591).  Up to one
+     * survivor in eight elements (in 32 for whole values) 256 threads, beyond that 128 (419 M elements, 8 bits:
+     * ratio 0.01 239 us with 256, 280 with 128; 0.05 266 and 296; 0.2 533 and 465; 0.9 633 and 642; 32 bits:
+     * 0.01 235 and 281, 0.05 365 and 336, 0.2 434 and 422). */
+    const bool sparse = K * (bits == 32 ? 32u : 8u) <= n;
+#define NSML_DECOMP1(BITS_, NTH_) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, NTH_>), grid, NTH_, idx, val, scales, t, tile_b, ts, dense_out)
+#define NSML_DECOMP(BITS_)                                      \
+    do {                                                         \
+        if (K != n && sparse) NSML_DECOMP1(BITS_, 256);          \
+        else NSML_DECOMP1(BITS_, 128);                           \
     } while (0)
     switch (bits) {
-    case 32: NSML_DECOMP(32); break;
+    case 32: if (K == n) NSML_DECOMP1(32, STH); else NSML_DECOMP(32); break;
     case 16: NSML_DECOMP(16); break;
     case 8:  NSML_DECOMP(8); break;
     default: NSML_DECOMP(4); break;
     }
 #undef NSML_DECOMP
+#undef NSML_DECOMP1
     return NSML_OK;
 }
 

@@ -437,6 +437,36 @@ def test_decompress_accumulate(bits):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits,chunk", [(4, 8), (4, 2048), (8, 24), (8, 2048), (16, 8), (32, 8)])
+@pytest.mark.parametrize("start", [0, 1, 2, 3])
+def test_decode_of_crowded_tiles(bits, chunk, start):
+    """Tiles with one survivor less and more than the decoder takes four at a time (512), twice that, all but one,
+    none; every bucket start mod 4, so that groups straddle chunks and bytes of two codes; with and without a context."""
+    per_tile = [511, 512, 513, 515, 0, 1023, 1024, 1027, 2047, 1]
+    n1 = 2048 * len(per_tile) - start                # the bucket's first tile is short by what lies before it
+    off = W.offsets_of([start, n1] if start else [n1])
+    n, K1 = start + n1, sum(per_tile)
+    g = torch.zeros(n, device=DEV)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(bits + start)
+    for i, k in enumerate(per_tile):
+        a, z = max(start, 2048 * i), 2048 * (i + 1)
+        at = a + torch.randperm(z - a, generator=gen, device=DEV)[:k]
+        g[at] = torch.rand(at.numel(), generator=gen, device=DEV) + 0.5
+    ratio = (K1 - 0.5) / n1
+    k_b, K, vb, ns = oracle.layout(off, ratio, bits, chunk)
+    assert int(k_b[-1]) == K1
+    ctx = nsml.Context(n, len(off) - 1, chunk)
+    idx, val, sc = ctx.compress(g, torch.zeros(n, device=DEV), off, ratio, bits)
+    want = oracle.decompress(idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns], n, off, ratio, bits, chunk)
+    for variant in (-1, 0, 1):
+        ctx.set_option("decomp_variant", variant)
+        dense = ctx.decompress(idx, val, sc, n, off, ratio, bits, torch.full((n,), 7.0, device=DEV))
+        assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32)), variant
+    dense = nsml.decompress_static(idx, val, sc, n, off, ratio, bits, chunk, torch.full((n,), 7.0, device=DEV))
+    assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 @pytest.mark.parametrize("bits", [4, 8, 16, 32])
 @pytest.mark.parametrize("ratio", [0.124, 0.13, 0.249, 0.26, 1.0])
 def test_accumulate_dense_payloads(bits, ratio):
