@@ -780,11 +780,16 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
     const uint32_t grid = xcd_grid(n_tiles);
     /* Threads per tile.  Everything sent is a plain decode without a chain of dependent loads: whole values in the
      * streaming kernels' shape (419 M elements: 537 us with 512 threads, 575 with 128), narrower ones with more of
-     * them per thread (8 bits: 393 us with 128 threads, 474 with 512; 16: 415 and 450; 4: 540 and 591).  Up to one
-     * survivor in eight elements (in 32 for whole values) 256 threads, beyond that 128 (419 M elements, 8 bits:
-     * ratio 0.01 239 us with 256, 280 with 128; 0.05 266 and 296; 0.2 533 and 465; 0.9 633 and 642; 32 bits:
-     * 0.01 235 and 281, 0.05 365 and 336, 0.2 434 and 422). */
-    const bool sparse = K * (bits == 32 ? 32u : 8u) <= n;
+     * them per thread (8 bits: 393 us with 128 threads, 474 with 512; 16: 415 and 450; 4: 540 and 591).  Few
+     * survivors decode faster with 256 threads than with 128 (419 M elements, 8 bits: ratio 0.01 239 us and 280,
+     * 0.05 266 and 296, 0.2 533 and 465), but the compress call that follows in a worker's round then takes longer:
+     * 200 tensors of 110 M, a whole round at 0.003 426 us with 256 and 439 with 128, at 0.01 450 and 451, at 0.05
+     * 592 and 575; a BERT-shaped one at 0.01 429 and 411.  So 256 up to one in 128, in 64 where no cache holds the
+     * output (419 M at 0.01, 200 tensors: decode 300 and 376, round 1514 and 1503), and for a receiver without a
+     * context, who compresses nothing, up to one in eight (25.6 M at 0.01: 25.4 and 26.5), in 32 for whole values
+     * (419 M at 0.05: 365 and 336). */
+    const bool receiver = c == nullptr;
+    const bool sparse = receiver ? K * (bits == 32 ? 32u : 8u) <= n : K * (n > (1ull << 27) ? 64u : 128u) <= n;
 #define NSML_DECOMP1(BITS_, NTH_) LAUNCHB(c, KID_DECOMP, st, (k_decomp<BITS_, MAP, NTH_>), grid, NTH_, idx, val, scales, t, tile_b, ts, dense_out)
 #define NSML_DECOMP(BITS_)                                      \
     do {                                                         \
