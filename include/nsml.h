@@ -169,9 +169,9 @@ int nsml_destroy(nsml_ctx *ctx);
  *                  in LDS, -1 (default) = by the share of survivors
  *   "force_dense"  1: decide every bucket by the dense passes over the accumulator (the path a
  *                  bucket takes when its staged elements cannot decide it), 0: default
- *   "rescan"       diagnostic: 1 makes the threshold search read the undecided keys from the
- *                  staged entries again (the path taken when a staging segment has no room left
- *                  for its copy of them), 0: default
+ *   "rescan"       diagnostic: 1 makes the threshold search go through the undecided keys in memory, two
+ *                  workgroups' parts at a time (the path of very large buckets), and small buckets take the
+ *                  chain of kernels, 0: default
  *   "whistory"     pruning step: 1 (default) stages a narrow band of weight magnitudes around the
  *                  threshold the previous call on this context found for the bucket (weights move
  *                  little between steps; a band that misses costs a repeat of the weight pass, the

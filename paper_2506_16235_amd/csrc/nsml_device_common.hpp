@@ -30,6 +30,13 @@ constexpr int STH = TILE / 4;     /* threads of a streaming workgroup */
 constexpr int WTILE = 1024;       /* elements one wavefront covers per iteration in the passes over the dense accumulator */
 constexpr uint32_t XCD_RUN = 16;  /* consecutive tiles per die, see xcd_tile */
 constexpr uint32_t SEG_CAP = TILE / 4;      /* staging entries per tile: a quarter of its elements */
+constexpr uint32_t SELC_SEGS = 64;          /* most segments per workgroup of k_select_count: one per lane */
+/* The undecided keys of a bucket, from list_base on: OWN_PER_SEG words per segment that belong to the workgroup of
+ * k_select_count that counts it, then list_room words for the workgroups that have more than that. */
+constexpr uint32_t LIST_PER_SEG = 64, OWN_PER_SEG = 16;
+constexpr uint32_t LCAP = SELC_SEGS * LIST_PER_SEG;        /* what a workgroup of k_select_count collects in LDS */
+__host__ __device__ inline uint64_t list_base(uint32_t tile0, uint32_t b) { return (uint64_t)tile0 * LIST_PER_SEG + (uint64_t)b * LCAP; }
+__host__ __device__ inline uint64_t list_room(uint32_t segs) { return (uint64_t)segs * (LIST_PER_SEG - OWN_PER_SEG) + LCAP; }
 constexpr int NB0 = 4096, NB1 = 4096, NB2 = 128;
 constexpr int NHB = 1024;         /* bins of the window of keys in which the threshold is expected */
 constexpr uint32_t NHC = 8;       /* copies of a bucket's bins, one per die's share of the workgroups: with one copy the streaming pass

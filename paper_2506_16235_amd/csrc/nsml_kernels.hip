@@ -98,7 +98,8 @@ struct nsml_ctx {
     uint32_t *d_chunk_b;   /* per chunk of the payload: its bucket (fixed by layout, ratio, bits) */
     uint32_t *d_chunk_seg; /* per chunk: the staging segment that holds its first survivor */
     uint32_t *d_sh, *d_why, *d_margin, *d_wprevT, *d_wprevHw, *d_wnband;
-    uint32_t *d_lcnt, *d_lkey;   /* k_select_count: lists of undecided keys per workgroup */
+    uint2 *d_part;         /* per workgroup of k_select_count: its part of the bucket's list of undecided keys */
+    uint32_t *d_lkey;      /* the lists */
     uint64_t max_chunks; uint32_t max_sel;
     uint32_t *d_zero;      /* cleared by every compress call: histograms and overflow flags */
     uint32_t *d_ccnt, *d_cG, *d_cE, *d_cidx;   /* candidate staging */
@@ -136,7 +137,7 @@ struct nsml_ctx {
     int hard_occ[2];       /* workgroups of k_hard that fit a compute unit at once (short / long chunks) */
     int whistory;          /* the weight band follows the threshold of the last call (1, default) or always comes from a sample (0) */
     int wband_miss;        /* diagnostic: the weight band is placed beside the threshold, so every bucket takes the repeat */
-    int force_rescan;      /* diagnostic: k_select_finish filters the staged entries again instead of using the tails */
+    int force_rescan;      /* diagnostic: k_select_finish in small windows; small buckets by the chain of kernels */
 
     /* profiling */
     bool prof;
@@ -175,7 +176,7 @@ int dev_alloc(nsml_ctx *c, T **p, uint64_t count)
  * the dense passes, overflow flags */
 uint64_t zero_words(uint64_t B) { return B * (uint64_t)(NB0 + NHC * NHB + NB0 + NB1 + NB2 + 2) + 16; }   /* 16 spare words: counters */
 
-struct Hists { uint32_t *hs, *hw, *f0, *f1, *f2, *ovf, *tail_ovf, *nhard; };
+struct Hists { uint32_t *hs, *hw, *f0, *f1, *f2, *ovf, *cursor, *nhard; };
 Hists hists_of(const nsml_ctx *c, uint32_t B)
 {
     Hists h;
@@ -185,8 +186,8 @@ Hists hists_of(const nsml_ctx *c, uint32_t B)
     h.f1 = h.f0 + (uint64_t)B * NB0;
     h.f2 = h.f1 + (uint64_t)B * NB1;
     h.ovf = h.f2 + (uint64_t)B * NB2;
-    h.tail_ovf = h.ovf + B;        /* k_select_count: a segment's tail could not hold its undecided keys */
-    h.nhard = h.tail_ovf + B;      /* k_plan: buckets not on the candidate path */
+    h.cursor = h.ovf + B;          /* k_select_count: length of the bucket's list of undecided keys */
+    h.nhard = h.cursor + B;      /* k_plan: buckets not on the candidate path */
     return h;
 }
 
@@ -405,7 +406,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     c->d_tile0 = c->d_samp0 = c->d_tile_b = c->d_k = c->d_T = c->d_need = nullptr;
     c->d_fast = c->d_ftile0 = c->d_zero = nullptr; c->d_desc = nullptr; c->d_par = c->d_wpar = nullptr;
     c->d_sel0 = nullptr; c->d_selw = nullptr; c->d_chunk_b = c->d_chunk_seg = c->d_sh = c->d_why = c->d_margin = c->d_wprevT = c->d_wprevHw = c->d_wnband = nullptr;
-    c->d_lcnt = c->d_lkey = nullptr;
+    c->d_part = nullptr; c->d_lkey = nullptr;
     c->d_ccnt = c->d_cG = c->d_cE = c->d_cidx = nullptr;
     c->d_cval = nullptr; c->d_v = nullptr; c->d_ts = nullptr; c->d_tile_sq = c->d_l2sq = nullptr; c->have_l2 = false;
     c->d_pmask = c->d_kw = c->d_Tw = c->d_needw = c->d_wfast = nullptr;
@@ -460,7 +461,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     /* k_select_count workgroups: every bucket can end with a short one */
     c->max_sel = (uint32_t)(mt / 16 + B1);
     A(dev_alloc(c, &c->d_selw, c->max_sel));
-    A(dev_alloc(c, &c->d_lcnt, c->max_sel));
+    A(dev_alloc(c, &c->d_part, c->max_sel));
     A(dev_alloc(c, &c->d_lkey, mt * LIST_PER_SEG + B1 * LCAP));
     A(dev_alloc(c, &c->d_cidx, c->max_cand)); A(dev_alloc(c, &c->d_cval, c->max_cand));
     {   /* survivor values in final order: ceil(ratio * n_b) per bucket, at most one more than
@@ -516,7 +517,7 @@ int nsml_destroy(nsml_ctx *c)
                     c->d_zero, c->d_ccnt, c->d_cG, c->d_cE, c->d_cidx,
                     c->d_cval, c->d_v, c->d_ts, c->d_tile_sq, c->d_l2sq, c->d_pmask, c->d_kw,
                     c->d_Tw, c->d_needw, c->d_wfast,
-                    c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_lcnt, c->d_lkey, c->d_sh, c->d_why, c->d_margin, c->d_wprevT, c->d_wprevHw, c->d_wnband};
+                    c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_part, c->d_lkey, c->d_sh, c->d_why, c->d_margin, c->d_wprevT, c->d_wprevHw, c->d_wnband};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->h_flags) (void)hipHostFree(c->h_flags);
@@ -623,10 +624,9 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
          * band elements' bits; buckets on the dense passes (no band, or one that missed):
          * everything in one resident launch */
         if (!c->force_dense) {
-            LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.tail_ovf, c->d_lcnt, c->d_lkey, weights);
-            LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.tail_ovf,
-                    (const uint32_t *)c->d_lcnt, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1,
-                    c->force_rescan, weights);
+            LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights);
+            LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
+                    (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1, c->force_rescan);
             LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
         }
         LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
@@ -651,10 +651,9 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         /* buckets decided from their staged elements: undecided keys set apart, threshold and
          * survivor order per bucket, then the payload of the candidate-path buckets */
         const uint4 *selw = c->d_selw;
-        LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, t, cd0, selw, c->selSh, h.tail_ovf, c->d_lcnt, c->d_lkey, (const float *)residual);
-        LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.tail_ovf,
-                (const uint32_t *)c->d_lcnt, (const uint32_t *)c->d_lkey, c->d_chunk_seg, c->d_flags,
-                c->force_rescan, (const float *)residual);
+        LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, t, cd0, selw, h.cursor, c->d_part, c->d_lkey, c->d_flags, (const float *)residual);
+        LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
+                (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, c->d_chunk_seg, c->d_flags, c->force_rescan);
         {
             const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
             const uint64_t nc64e = c->NC;

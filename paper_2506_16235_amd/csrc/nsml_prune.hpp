@@ -155,8 +155,8 @@ __global__ __launch_bounds__(WTH, 8) void k_whist(const float *__restrict__ w, T
 }
 
 /* Per bucket: the bin of the kw-th largest |weight|, from the counts above the band and the bins of
- * the band; the staged band decides the rest iff the kw-th largest lies inside it and no staging
- * segment overflowed, otherwise the bucket takes the dense passes. */
+ * the band; the staged band decides the rest iff the kw-th largest lies inside it, no staging
+ * segment overflowed and the list of undecided keys holds them, otherwise the bucket takes the dense passes. */
 __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ hist, Cand c, uint32_t *__restrict__ nband_out)
 {
     __shared__ uint32_t wsum[NHB / 64], red[NHB / 64], res[3];
@@ -185,7 +185,8 @@ __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ 
     if (ovf) t.ovf[b] = 0u;
     nband_out[b] = total;
     const uint32_t top = (p.z - 1u) >> p.w;
-    if (p.x != NONE && !ovf && found && !(res[0] == (uint32_t)NHB - 1u && (p.x >> p.w) != top - res[0])) {
+    if (p.x != NONE && !ovf && found && !(res[0] == (uint32_t)NHB - 1u && (p.x >> p.w) != top - res[0])
+        && res[2] <= list_room(t.tile0[b + 1] - t.tile0[b])) {
         t.T[b] = top - res[0];
         t.need[b] = want - res[1];
         t.sh[b] = p.w;

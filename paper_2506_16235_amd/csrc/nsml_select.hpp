@@ -361,8 +361,7 @@ __device__ __forceinline__ bool window_find(uint32_t *__restrict__ hist_b, uint3
  * (PATH_*).  The staged elements can decide it when they are known to hold every element of that
  * bin: in candidate mode they are exactly the elements with key >= L_b, so they do iff there are at
  * least k of them and the key lies below the window's top; in band mode iff it lies inside the band;
- * in both only if the undecided keys of the bin are few enough to fit the free part of the staging
- * area (k_select_count parks them there).  In zero mode the counts settle everything: fewer non-zero
+ * in both only if the undecided keys of the bin fit the bucket's list of them (k_select_count).  In zero mode the counts settle everything: fewer non-zero
  * elements than k means threshold key 0. */
 __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ hist, Cand c, int have_cand,
                                               const double *__restrict__ tile_sq, double *__restrict__ l2sq)
@@ -415,10 +414,8 @@ __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ h
          * that find the threshold; the survivors of such a bucket are then taken from the dense
          * accumulator as well (PATH_BAND), since the staged entries cannot supply them all */
         const uint32_t top = (p.z - 1u) >> p.w, bin = res[0], at = res[2];
-        const uint64_t cap_b = (uint64_t)(t.tile0[b + 1] - t.tile0[b]) * SEG_CAP;
-        const uint64_t staged = (uint64_t)total + (p.y == NONE ? n_hi : 0u);
         if (bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin) why = WHY_OUTSIDE_BAND;    /* the open last bin */
-        else if (staged > cap_b || (uint64_t)at * 2u > cap_b - staged) why = WHY_NO_ROOM;
+        else if (at > list_room(t.tile0[b + 1] - t.tile0[b])) why = WHY_NO_ROOM;
         else { path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND; T = top - bin; need = want - res[1]; sh = p.w; }
     } else why = n_hi < want ? WHY_TOO_FEW : WHY_OUTSIDE_BAND;
     t.why[b] = why;

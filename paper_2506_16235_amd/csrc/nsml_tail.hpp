@@ -3,15 +3,13 @@
  * Included by nsml_kernels.hip (one translation unit); not a public header.
  *
  * What the tail knows when it starts (left by the streaming pass and the plan): for every
- * bucket the leading bits b0 of its k-th largest key (the level-0 digit, or 18 bits when the
- * finer histogram covered it) and how many of the keys that share them are still wanted; for
+ * bucket the leading bits b0 of its k-th largest key (down to the shift of the bins that the streaming pass
+ * counted) and how many of the keys that share them are still wanted; for
  * every staging segment its entries (index, value) in index order.  Entries above b0 are
  * survivors, entries below it are not, the ones that share it are the only undecided ones, and
  * they are few.
  *
- *   k_select_count   per segment: entries above b0; the keys of the undecided entries go to a list
- *                    per workgroup (read back with coalesced loads) and, as a fallback, into the
- *                    unused tail of the segment's own staging area
+ *   k_select_count   per segment: entries above b0; the keys of the undecided entries go to the bucket's list
  *   k_select_finish  per bucket, one workgroup of 1024 threads: threshold key T and tie allowance
  *                    e from those few keys (the remaining bits, histograms in LDS); per segment
  *                    the number of survivors and of threshold ties that precede it in the bucket;
@@ -121,7 +119,6 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
 
 /* ------------------------------------------------------------------ k_select_count */
 
-constexpr uint32_t SELC_SEGS = 64;         /* most segments per workgroup of k_select_count: one per lane */
 constexpr uint32_t SELC_ROWS = 8;          /* rows of 64 entries a wavefront has in flight */
 
 /* Work list of k_select_count, fixed by the bucket layout: workgroup w takes segments
@@ -145,7 +142,6 @@ __global__ __launch_bounds__(WG) void k_chunkmap(const uint64_t *__restrict__ C,
     if (c < NC) chunk_b[c] = find_bucket<uint64_t>(C, B, c);
 }
 
-constexpr uint32_t LIST_PER_SEG = 64, LCAP = SELC_SEGS * LIST_PER_SEG;           /* list entries per workgroup of k_select_count */
 /* a list entry: the 19 key bits below the level-0 digit, and above them the segment's number inside the workgroup */
 __device__ __forceinline__ uint32_t list_entry(uint32_t key, uint32_t segl) { return (segl << SH0) | (key & ((1u << SH0) - 1u)); }
 
@@ -220,58 +216,57 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
 
 /* Per staging segment of the buckets decided from staged elements (PATH_CAND, PATH_BAND), with
  * b0 the leading bits of the bucket's k-th key: G = entries above b0 (plus, in band mode, the elements
- * above the band the streaming pass counted), E = entries that share b0.  The keys of those undecided
- * entries go to two places: the unused tail of the segment's staging area, last slot first (as long
- * as there is room), and a list per workgroup (the undecided key bits and the segment's number in
- * one word, in no particular order) that k_select_finish reads with coalesced loads; the
- * list is left out (lcnt = NONE) when the workgroup has more than LIST_PER_SEG a segment.
+ * above the band the streaming pass counted).  The keys of the entries that share b0, the only undecided
+ * ones, go to the bucket's list (the undecided key bits and the segment's number inside the workgroup in one
+ * word, in no particular order); a workgroup's part of it is one range, whose place and length are left in `part`:
+ * its own share, or when that is too small a range of the room that the bucket's workgroups have in common (the
+ * plan has counted the keys: they fit).  (With shares alone, a cluster of survivors sent the bucket to a search by
+ * one thread per segment: 12 - 50 ms on 110 M elements, now 0.1; with the common room alone every workgroup waits
+ * for its place in it: 3200 of them 62 us, so 36.)
  * A workgroup takes 16 or 64 consecutive segments (1 << selSh) as one list of entries, dealt to its four wavefronts row
  * by row (64 entries), so its work follows the number of entries and not the longest segment; lane l
  * of every wavefront keeps the count of segment l, from the ballots of the rows and the part of each row
  * that belongs to it. */
-__global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
-                                                     uint32_t *__restrict__ tail_ovf, uint32_t *__restrict__ lcnt,
-                                                     uint32_t *__restrict__ lkey, const float *__restrict__ r)
+__global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw,
+                                                     uint32_t *__restrict__ cursor, uint2 *__restrict__ part,
+                                                     uint32_t *__restrict__ lkey, uint32_t *__restrict__ err, const float *__restrict__ r)
 {
     __shared__ uint32_t lk[LCAP];
-    __shared__ uint32_t pre[SELC_SEGS], cg[SELC_SEGS], cb[SELC_SEGS];
-    __shared__ uint32_t lcur;
+    __shared__ uint32_t pre[SELC_SEGS], cg[SELC_SEGS];
+    __shared__ uint32_t lcur, lbase;
     const uint4 wk = selw[blockIdx.x];
     const uint32_t b = wk.x, s0 = wk.y, s1 = wk.z;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     /* issued before the bucket's state is known */
     const uint32_t ms = s0 + lane;
     const bool mine = ms < s1;
-    const uint32_t lcap = LIST_PER_SEG << selSh;
     const uint32_t mcnt = mine ? c.cnt[ms] : 0u;
     uint32_t mg0 = mine ? c.G[ms] : 0u;              /* band mode: elements above the band, counted by the streaming pass */
     const uint32_t path = t.fast[b], b0 = t.T[b], sh = t.sh[b];     /* b0: the key bits from position sh up */
+    const KeyPar p = t.par[b];
     if (path != PATH_CAND && path != PATH_BAND) return;      /* same for the whole workgroup */
-    if (t.par[b].y == NONE) mg0 = 0u;                /* no band was staged: the staged entries hold everything above */
+    if (p.y == NONE) mg0 = 0u;                       /* no band was staged: the staged entries hold everything above */
     const bool dense = mcnt > SEG_CAP;               /* an overflowed segment is read from the dense accumulator, where nothing is missing */
     const uint32_t len = dense ? 0u : mcnt;
     const uint32_t seg_end = wave_incl_scan(len), seg_start = seg_end - len;
     const uint32_t total = __builtin_amdgcn_readlane(seg_end, 63);
-    if (wave == 0) { pre[lane] = seg_start; cg[lane] = 0u; cb[lane] = 0u; }
+    if (wave == 0) { pre[lane] = seg_start; cg[lane] = 0u; }
     if (tid == 0) lcur = 0u;
     wg_sync();
-    uint32_t *cvalu = reinterpret_cast<uint32_t *>(c.val);
-    /* an undecided key of segment s (of this workgroup) */
-    auto undecided = [&](uint32_t key, uint32_t s, uint32_t cnt, bool tail) {
-        const uint32_t pos = atomicAdd(&cb[s], 1u);
-        if (tail && cnt + pos < SEG_CAP) cvalu[(uint64_t)(s0 + s) * SEG_CAP + SEG_CAP - 1u - pos] = key;
-        const uint32_t lp = atomicAdd(&lcur, 1u);
-        if (lp < lcap) lk[lp] = list_entry(key, s);
-    };
     uint32_t my_g = 0;
+    /* an undecided key of segment s (of this workgroup) */
+    auto undecided = [&](uint32_t key, uint32_t s) {
+        const uint32_t at = atomicAdd(&lcur, 1u);
+        if (at < LCAP) lk[at] = list_entry(key, s);
+    };
     const bool crowded = total >= 32u * (s1 - s0);   /* half a row per segment and more: a wavefront takes a whole segment */
     if (crowded) {
         for (uint32_t q = wave; q < s1 - s0; q += WG / 64) {
             const uint32_t cnt = __builtin_amdgcn_readlane(len, q);
-            const float *p = c.val + (uint64_t)(s0 + q) * SEG_CAP;
+            const float *v = c.val + (uint64_t)(s0 + q) * SEG_CAP;
             float x[SEG_CAP / 64];
 #pragma unroll
-            for (uint32_t u = 0; u < SEG_CAP / 64; ++u) { const uint32_t i = u * 64 + lane; x[u] = i < cnt ? p[i] : 0.0f; }
+            for (uint32_t u = 0; u < SEG_CAP / 64; ++u) { const uint32_t i = u * 64 + lane; x[u] = i < cnt ? v[i] : 0.0f; }
             uint32_t g = 0;
 #pragma unroll
             for (uint32_t u = 0; u < SEG_CAP / 64; ++u) {
@@ -279,7 +274,7 @@ __global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uin
                 const uint32_t key = keyof(x[u]);
                 const bool in = u * 64 + lane < cnt;
                 g += __popcll(__ballot(in && (key >> sh) > b0));
-                if (in && (key >> sh) == b0) undecided(key, q, cnt, true);
+                if (in && (key >> sh) == b0) undecided(key, q);
             }
             if (lane == q) my_g = g;
         }
@@ -303,114 +298,105 @@ __global__ __launch_bounds__(WG) void k_select_count(Tables t, Cand c, const uin
             const uint32_t key = keyof(x[u]);
             const bool in = r0 + lane < total;
             const uint64_t bg = __ballot(in && (key >> sh) > b0);
-            const bool isb = in && (key >> sh) == b0;
             /* the part of this row that belongs to segment `lane` */
             const uint32_t pa = seg_start > r0 ? min(seg_start - r0, 64u) : 0u, pz = seg_end > r0 ? min(seg_end - r0, 64u) : 0u;
             const uint64_t ma = pa >= 64u ? ~0ull : (1ull << pa) - 1ull, mz = pz >= 64u ? ~0ull : (1ull << pz) - 1ull;
             my_g += __popcll(bg & mz & ~ma);
-            if (__any(isb)) {
-                const uint32_t cnt = __shfl(mcnt, sg[u], 64);
-                if (isb) undecided(key, sg[u], cnt, true);
-            }
+            if (in && (key >> sh) == b0) undecided(key, sg[u]);
         }
     }
     if (my_g) atomicAdd(&cg[lane], my_g);
-    uint64_t todo = __ballot(dense);                 /* the same in every wavefront */
-    while (todo) {
+    /* element e of a segment that is read from the dense source, if it counts */
+    auto dense_in = [&](const DenseSeg &d, uint32_t e, uint32_t key) {
+        return e < d.len && key >= p.x               /* (zeros lie below a band that starts at key 1) */
+               && !(t.pmask && pruned_elem(t.pmask, t.tile0[b], t.off[b] & ~3ull, d.e0 + e));
+    };
+    const uint64_t over = __ballot(dense);           /* the same in every wavefront */
+    for (uint64_t todo = over; todo; todo &= todo - 1ull) {
         const uint32_t q = (uint32_t)__builtin_ctzll(todo);
-        todo &= todo - 1ull;
         const DenseSeg d = dense_seg(t, b, s0 + q);
-        const uint32_t tile0b = t.tile0[b];
-        const uint64_t lo_al = t.off[b] & ~3ull;
         float x[TILE / WG];
 #pragma unroll
         for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; x[u] = e < d.len ? r[d.e0 + e] : 0.0f; }
         uint32_t g = 0;
 #pragma unroll
         for (uint32_t u = 0; u < TILE / WG; ++u) {
-            const uint32_t e = u * WG + tid, key = keyof(x[u]);
-            bool in = e < d.len;
-            if (t.pmask && in) in = !pruned_elem(t.pmask, tile0b, lo_al, d.e0 + e);
+            const uint32_t key = keyof(x[u]);
+            const bool in = dense_in(d, u * WG + tid, key);
             g += __popcll(__ballot(in && (key >> sh) > b0));
-            if (in && (key >> sh) == b0) undecided(key, q, 0u, false);
+            if (in && (key >> sh) == b0) undecided(key, q);
         }
         if (lane == 0) atomicAdd(&cg[q], g);
     }
     wg_sync();
-    if (wave == 0 && mine) {
-        const uint32_t my_b = cb[lane];
-        c.G[ms] = (dense ? 0u : mg0) + cg[lane];     /* of a dense one the elements above the band were counted here as well */
-        c.E[ms] = my_b;
-        /* a tail that did not fit (or a segment without one): k_select_finish filters the entries again
-         * if it cannot use the lists */
-        if (my_b != 0u && (dense || mcnt + my_b > SEG_CAP)) tail_ovf[b] = 1u;
+    if (wave == 0 && mine) c.G[ms] = (dense ? 0u : mg0) + cg[lane];     /* of a dense one the elements above the band were counted here as well */
+    const uint32_t nl = lcur, tile0b = t.tile0[b], segs = t.tile0[b + 1] - tile0b;
+    uint32_t *list = lkey + list_base(tile0b, b);
+    const bool alone = s1 - s0 == segs;              /* the bucket's only workgroup: all of the list is its own */
+    if (nl <= (s1 - s0) * OWN_PER_SEG || (alone && nl <= LCAP)) {
+        const uint32_t at = (s0 - tile0b) * OWN_PER_SEG;
+        if (tid == 0) part[blockIdx.x] = make_uint2(at, nl);
+        for (uint32_t i = tid; i < nl; i += WG) list[at + i] = lk[i];
+        return;
     }
-    const uint32_t nl = lcur;
-    if (tid == 0) lcnt[blockIdx.x] = nl > lcap ? NONE : nl;
-    if (nl <= lcap) {
-        const uint64_t lb = (uint64_t)blockIdx.x * lcap;
-        for (uint32_t i = tid; i < nl; i += WG) lkey[lb + i] = lk[i];
+    wg_sync();
+    if (tid == 0) {
+        const uint32_t at = atomicAdd(&cursor[b], nl);
+        const bool fits = (uint64_t)at + nl <= list_room(segs);
+        if (!fits) err[0] = 1u;                      /* cannot happen: the plan has counted them */
+        part[blockIdx.x] = make_uint2(segs * OWN_PER_SEG + at, fits ? nl : 0u);
+        lbase = fits ? at : NONE;
+        lcur = 0u;
+    }
+    wg_sync();
+    if (lbase == NONE) return;
+    list += segs * OWN_PER_SEG + lbase;
+    if (nl <= LCAP) {
+        for (uint32_t i = tid; i < nl; i += WG) list[i] = lk[i];
+        return;
+    }
+    /* rare: more of them than LDS holds; gone through once more, to their places in memory at once */
+    auto store = [&](bool is, uint32_t key, uint32_t s) {
+        const uint64_t bal = __ballot(is);
+        if (!bal) return;                            /* same for the whole wavefront */
+        uint32_t at = 0;
+        if (lane == 0) at = atomicAdd(&lcur, (uint32_t)__popcll(bal));
+        at = __builtin_amdgcn_readfirstlane(at);
+        at = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, at));
+        if (is) list[at] = list_entry(key, s);
+    };
+#pragma unroll 1
+    for (uint32_t q = wave; q < s1 - s0; q += WG / 64) {
+        if ((over >> q) & 1ull) {
+            const DenseSeg d = dense_seg(t, b, s0 + q);
+#pragma unroll 1
+            for (uint32_t e0 = 0; e0 < d.len; e0 += 64) {
+                const uint32_t e = e0 + lane, key = e < d.len ? keyof(r[d.e0 + e]) : 0u;
+                store(dense_in(d, e, key) && (key >> sh) == b0, key, q);
+            }
+        } else {
+            const uint32_t cnt = __builtin_amdgcn_readlane(len, q);
+#pragma unroll 1
+            for (uint32_t e0 = 0; e0 < cnt; e0 += 64) {
+                const uint32_t e = e0 + lane, key = e < cnt ? keyof(c.val[(uint64_t)(s0 + q) * SEG_CAP + e]) : 0u;
+                store(e < cnt && (key >> sh) == b0, key, q);
+            }
+        }
     }
 }
 
 /* ------------------------------------------------------------------ k_select_finish */
 
-/* The undecided keys of one segment: the tail list k_select_count wrote, or, when some tail did
- * not fit (`rescan`), the segment's staged entries filtered again. */
-struct KeySource {
-    const uint32_t *cvalu;
-    const uint32_t *cnt;
-    uint32_t b0, sh;
-    bool rescan;
-    const Tables *t;             /* for the segments that overflowed: they are read from the dense accumulator */
-    const float *r;
-    uint32_t b;
-    __device__ __forceinline__ bool wanted(uint32_t key) const { return !rescan || (key >> sh) == b0; }
-    /* f(key) for every undecided key of segment s, eight loads in flight at a time */
-    template <typename F>
-    __device__ __forceinline__ void for_each(uint32_t s, uint32_t bcnt, F f) const
-    {
-        const uint32_t staged = cnt[s];
-        if (rescan && staged > SEG_CAP) {
-            const DenseSeg d = dense_seg(*t, b, s);
-            const uint32_t tile0b = t->tile0[b];
-            const uint64_t lo_al = t->off[b] & ~3ull;
-            for (uint32_t i = 0; i < d.len; i += 8) {
-                uint32_t kk[8];
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u) kk[u] = i + u < d.len ? keyof(r[d.e0 + i + u]) : 0u;
-#pragma unroll
-                for (uint32_t u = 0; u < 8; ++u)
-                    if (i + u < d.len && wanted(kk[u]) && !(t->pmask && pruned_elem(t->pmask, tile0b, lo_al, d.e0 + i + u))) f(kk[u]);
-            }
-            return;
-        }
-        const uint32_t nw = rescan ? staged : bcnt;
-        const uint64_t base = (uint64_t)s * SEG_CAP;
-        for (uint32_t i = 0; i < nw; i += 8) {
-            uint32_t kk[8];
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u)
-                kk[u] = i + u < nw ? (rescan ? (cvalu[base + i + u] & 0x7FFFFFFFu) : cvalu[base + SEG_CAP - 1u - (i + u)]) : 0u;
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u)
-                if (i + u < nw && wanted(kk[u])) f(kk[u]);
-        }
-    }
-};
-
-/* LDS of k_select_finish, one pool carved by both variants below (u32 words):
- *   [0, 4096)        level-1 histogram; later, up to FIN_MAX_SEGS, the per-segment counts (lists)
- *   [4096, +8192)    per-segment key counts as u16 (tails)
- *   FIN_AT_KEYS      undecided keys kept in LDS
- *   FIN_AT_SEGS      their segment numbers as u16 (lists)
- *   FIN_AT_UOFF      exclusive prefix of the list lengths (lists) */
+/* LDS of k_select_finish, one pool (u32 words):
+ *   [0, 4096)        level-1 histogram; later the counts of up to FIN_MAX_SEGS segments
+ *   FIN_AT_KEYS      undecided keys, when all of the bucket's fit, in the order of the parts
+ *   FIN_AT_UPRE      exclusive prefix of the lengths of the list's parts
+ *   FIN_AT_UPOS      where each part begins in the list */
 constexpr uint32_t FIN_KEYS_LDS = 3072;    /* undecided keys kept in LDS */
-constexpr uint32_t FIN_MAX_SEGS = 16384;   /* segments whose counts fit the pool */
-constexpr uint32_t FIN_AT_KEYS = FIN_MAX_SEGS, FIN_AT_SEGS = FIN_AT_KEYS + FIN_KEYS_LDS, FIN_AT_UOFF = FIN_AT_SEGS + FIN_KEYS_LDS / 2;
-constexpr uint32_t FIN_POOL = FIN_AT_UOFF + SEL_THREADS + 2;
-constexpr uint32_t RQ = FIN_MAX_SEGS / SEL_THREADS;
-static_assert(NB1 + FIN_MAX_SEGS / 2 <= FIN_AT_KEYS, "the counts of the tails variant overlap the keys");
+constexpr uint32_t FIN_MAX_SEGS = 16384;   /* segments whose counts fit the pool: larger buckets go in windows of so many */
+constexpr uint32_t FIN_AT_KEYS = FIN_MAX_SEGS, FIN_AT_UPRE = FIN_AT_KEYS + FIN_KEYS_LDS, FIN_AT_UPOS = FIN_AT_UPRE + SEL_THREADS + 1;
+constexpr uint32_t FIN_POOL = FIN_AT_UPOS + SEL_THREADS;
+static_assert(NB1 <= FIN_MAX_SEGS, "the level-1 histogram overlaps the keys");
 
 struct FinShared {
     uint32_t *pool;      /* FIN_POOL words */
@@ -419,22 +405,20 @@ struct FinShared {
     uint32_t *res;       /* 4 */
 };
 
-/* Last part of both variants: exclusive prefixes of (elements above T, elements equal to T) over
- * the bucket's segments, in place over the per-segment counts, and for every chunk of the
- * payload the segment that holds its first survivor.  A round takes PER consecutive segments per
- * thread.  count(r, s, g, q) adds to g and q what segment s (round r) holds above / equal to T among its
- * undecided keys. */
+/* Exclusive prefixes of (elements above T, elements equal to T) over the segments [seg_lo, seg_hi) of a
+ * bucket, in place over the per-segment counts, and for every chunk of the payload the segment that holds
+ * its first survivor.  A round takes PER consecutive segments per thread.  run: the two totals of the
+ * segments before, brought up to date.  count(s, g, q) adds to g and q what segment s holds above / equal
+ * to T among its undecided keys. */
 template <uint32_t PER, typename F>
 __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, uint32_t b, uint32_t seg_lo,
-                                                uint32_t seg_hi, uint32_t T, uint32_t e_b, uint32_t kb,
-                                                uint32_t *__restrict__ chunk_seg, uint64_t *tmp,
-                                                uint32_t *__restrict__ err, F count)
+                                                uint32_t seg_hi, uint32_t e_b, uint64_t &run,
+                                                uint32_t *__restrict__ chunk_seg, uint64_t *tmp, F count)
 {
     const uint32_t tid = threadIdx.x;
     const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS * PER - 1) / (SEL_THREADS * PER);
     const uint64_t Cb = t.C[b];
     const uint32_t chunk = t.chunk;
-    uint64_t run = 0;
     uint32_t g_next[PER];
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j) { const uint32_t s = seg_lo + tid * PER + j; g_next[j] = s < seg_hi ? c.G[s] : 0u; }
@@ -445,7 +429,7 @@ __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, 
         for (uint32_t j = 0; j < PER; ++j) {
             uint32_t g = g_next[j], q = 0;
             if (r + 1 < rounds) { const uint32_t sn = s0 + SEL_THREADS * PER + j; g_next[j] = sn < seg_hi ? c.G[sn] : 0u; }   /* fetched under this round's work */
-            count(r, s0 + j, g, q);
+            count(s0 + j, g, q);
             v[j] = ((uint64_t)g << 32) | (uint64_t)q;
             sum += v[j];
         }
@@ -469,230 +453,43 @@ __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, 
         }
         run += tt;
     }
-    if (tid == 0) {
-        t.T[b] = T;
-        t.need[b] = e_b;
-        /* above + admitted ties must be exactly k */
-        const uint32_t above = (uint32_t)(run >> 32), ties = (uint32_t)run;
-        if (above + e_b != kb || e_b > ties) err[0] = 1u;
-    }
+}
+/* The bucket's threshold and tie allowance, once its prefixes are done. */
+__device__ __forceinline__ void finish_state(const Tables &t, uint32_t b, uint32_t T, uint32_t e_b, uint32_t kb, uint64_t run,
+                                             uint32_t *__restrict__ err)
+{
+    if (threadIdx.x != 0) return;
+    t.T[b] = T;
+    t.need[b] = e_b;
+    /* above + admitted ties must be exactly k */
+    const uint32_t above = (uint32_t)(run >> 32), ties = (uint32_t)run;
+    if (above + e_b != kb || e_b > ties) err[0] = 1u;
 }
 
-/* Variant 1 (the usual one): the undecided keys come from the lists of the bucket's
- * k_select_count workgroups ("units"), read with coalesced loads, eight per thread in flight.
- * Two passes over them when they do not fit in LDS: level-1 digits; then, knowing the level-1
- * digit d1 of the threshold, everything above d1 is tallied per segment at once and the few
- * keys inside d1 are set aside in LDS for the last 7 bits. */
-__device__ __forceinline__ void finish_from_lists(const Tables &t, const Cand &c, uint32_t b, uint32_t b0, uint32_t sh,
-                                                  uint32_t need0, uint32_t kb, uint32_t seg_lo, uint32_t seg_hi,
-                                                  uint32_t u0, uint32_t nun, uint32_t my_cnt, uint32_t selSh,
-                                                  const uint32_t *__restrict__ lkey,
-                                                  uint32_t *__restrict__ chunk_seg, const FinShared &sm,
-                                                  uint32_t *__restrict__ err)
+/* add to a word of LDS that many active lanes of the wavefront may share (equal keys): one addition then */
+__device__ __forceinline__ void add_shared(uint32_t *h, uint32_t at, uint32_t add)
 {
-    const uint32_t tid = threadIdx.x;
-    uint32_t *h1 = sm.pool, *cnts = sm.pool, *keys = sm.pool + FIN_AT_KEYS, *uoff = sm.pool + FIN_AT_UOFF;
-    uint16_t *segs = reinterpret_cast<uint16_t *>(sm.pool + FIN_AT_SEGS);
-    for (uint32_t i = tid; i < NB1; i += SEL_THREADS) h1[i] = 0u;
-    if (tid < NB2) sm.h2[tid] = 0u;
-    if (tid == 0) sm.res[3] = 0u;                      /* entries set aside */
-    uint64_t tot64;
-    const uint32_t incl = (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)my_cnt, sm.tmp, tot64);
-    if (tid < nun) uoff[tid] = incl - my_cnt;
-    if (tid == 0) uoff[nun] = (uint32_t)tot64;
-    wg_sync();
-    const uint32_t nkeys = (uint32_t)tot64;
-    const bool resident = nkeys <= FIN_KEYS_LDS;
-    const uint32_t m1 = (1u << (sh - SH1)) - 1u;       /* level-1 digit: key bits sh-1 .. 7 (12 or 6 bits) */
-    /* f(i, entry, segment number inside the bucket) for every list entry of the bucket */
-    auto for_keys = [&](auto f) {
-        for (uint32_t i0 = tid; i0 < nkeys; i0 += 8 * SEL_THREADS) {
-            uint32_t kk[8], un[8];
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u) {
-                const uint32_t i = i0 + u * SEL_THREADS;
-                kk[u] = 0; un[u] = 0;
-                if (i < nkeys) {
-                    uint32_t lo = 0, hi = nun;         /* uoff[lo] <= i < uoff[hi] */
-                    while (hi - lo > 1) { const uint32_t mid = (lo + hi) >> 1; if (uoff[mid] <= i) lo = mid; else hi = mid; }
-                    un[u] = lo;
-                    kk[u] = lkey[((uint64_t)(u0 + lo) << selSh) * LIST_PER_SEG + (i - uoff[lo])];
-                }
-            }
-#pragma unroll
-            for (uint32_t u = 0; u < 8; ++u)
-                if (i0 + u * SEL_THREADS < nkeys) f(i0 + u * SEL_THREADS, kk[u], (un[u] << selSh) + (kk[u] >> SH0));
-        }
-    };
-    /* pass 1: level-1 digits (key bits 18..7); entries and segment numbers to LDS if they fit */
-    for_keys([&](uint32_t i, uint32_t e, uint32_t seg) {
-        atomicAdd(&h1[(e >> SH1) & m1], 1u);
-        if (resident) { keys[i] = e; segs[i] = (uint16_t)seg; }
-    });
-    wg_sync();
-    if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
-    const uint32_t d1 = sm.res[0];
-    const uint32_t need1 = need0 - sm.res[1];
-    wg_sync();
-    /* pass 2: per segment, entries above digit d1 (high half of the count); level-2 digits (key
-     * bits 6..0) of the entries inside d1, which are set aside when they came from memory */
-    const uint32_t nseg = seg_hi - seg_lo;
-    for (uint32_t i = tid; i < nseg; i += SEL_THREADS) cnts[i] = 0u;       /* takes the place of the level-1 histogram */
-    wg_sync();
-    auto pass2 = [&](uint32_t e, uint32_t seg, bool collect) {
-        const uint32_t d = (e >> SH1) & m1;
-        if (d > d1) atomicAdd(&cnts[seg], 1u << 16);
-        else if (d == d1) {
-            atomicAdd(&sm.h2[e & (NB2 - 1)], 1u);
-            if (collect) {
-                const uint32_t at = atomicAdd(&sm.res[3], 1u);
-                if (at < FIN_KEYS_LDS) { keys[at] = e; segs[at] = (uint16_t)seg; }
-            }
-        }
-    };
-    if (resident) {
-        for (uint32_t i = tid; i < nkeys; i += SEL_THREADS) pass2(keys[i], segs[i], false);
+    const uint32_t fa = __builtin_amdgcn_readfirstlane(at), fv = __builtin_amdgcn_readfirstlane(add);
+    const uint64_t here = __ballot(true);
+    if (__ballot(at == fa && add == fv) == here) {
+        if ((threadIdx.x & 63u) == (uint32_t)__builtin_ctzll(here)) atomicAdd(&h[fa], fv * (uint32_t)__popcll(here));
     } else {
-        for_keys([&](uint32_t, uint32_t e, uint32_t seg) { pass2(e, seg, true); });
+        atomicAdd(&h[at], add);
     }
-    wg_sync();
-    if (!find_digit_lds<NB2, SEL_WAVES>(sm.h2, need1, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
-    const uint32_t d2 = sm.res[0];
-    const uint32_t T = (b0 << sh) | (d1 << SH1) | d2;
-    const uint32_t e_b = need1 - sm.res[1];            /* ties admitted: 1 <= e_b <= keys equal to T */
-    const uint32_t aside = sm.res[3];
-    wg_sync();
-    /* pass 3: the entries inside d1 against the last digit: above T, or equal to T (low half) */
-    auto pass3 = [&](uint32_t e, uint32_t seg) {
-        if (((e >> SH1) & m1) != d1) return;
-        const uint32_t d = e & (NB2 - 1);
-        if (d > d2) atomicAdd(&cnts[seg], 1u << 16);
-        else if (d == d2) atomicAdd(&cnts[seg], 1u);
-    };
-    if (resident) {
-        for (uint32_t i = tid; i < nkeys; i += SEL_THREADS) pass3(keys[i], segs[i]);
-    } else if (aside <= FIN_KEYS_LDS) {
-        for (uint32_t i = tid; i < aside; i += SEL_THREADS) pass3(keys[i], segs[i]);
-    } else {
-        for_keys([&](uint32_t, uint32_t e, uint32_t seg) { pass3(e, seg); });      /* too many were inside d1 */
-    }
-    wg_sync();
-    finish_prefixes<4>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
-                    [&](uint32_t, uint32_t s, uint32_t &g, uint32_t &q) {
-                        if (s < seg_hi) { const uint32_t v = cnts[s - seg_lo]; g += v >> 16; q += v & 0xFFFFu; }
-                    });
-}
-
-/* Variant 2: the undecided keys of a segment come from the tail of its staging area, or, when
- * some tail did not fit (`rescan`), from the staged entries filtered again; one thread per
- * segment.  Taken when a list was left out (a workgroup with more than LCAP undecided keys) or
- * the bucket has more segments than the LDS tables of variant 1 hold; slower, same result. */
-__device__ __forceinline__ void finish_from_tails(const Tables &t, const Cand &c, uint32_t b, uint32_t b0, uint32_t sh,
-                                                  uint32_t need0, uint32_t kb, uint32_t seg_lo, uint32_t seg_hi,
-                                                  bool rescan, uint32_t *__restrict__ chunk_seg,
-                                                  const FinShared &sm, uint32_t *__restrict__ err,
-                                                  const float *__restrict__ r)
-{
-    const uint32_t tid = threadIdx.x;
-    uint32_t *h1 = sm.pool, *keys = sm.pool + FIN_AT_KEYS;
-    uint16_t *sbc = reinterpret_cast<uint16_t *>(sm.pool + NB1);
-    KeySource ks;
-    ks.cvalu = reinterpret_cast<const uint32_t *>(c.val); ks.cnt = c.cnt; ks.b0 = b0; ks.sh = sh;
-    ks.rescan = rescan; ks.t = &t; ks.r = r; ks.b = b;
-    const uint32_t m1 = (1u << (sh - SH1)) - 1u;       /* level-1 digit: key bits sh-1 .. 7 */
-    const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS - 1) / SEL_THREADS;
-    for (uint32_t i = tid; i < NB1; i += SEL_THREADS) h1[i] = 0u;
-    if (tid < NB2) sm.h2[tid] = 0u;
-    for (uint32_t r = 0; r < RQ; ++r) {
-        const uint32_t s = seg_lo + r * SEL_THREADS + tid;
-        sbc[r * SEL_THREADS + tid] = (uint16_t)((r < rounds && s < seg_hi) ? c.E[s] : 0u);
-    }
-    auto bc_of = [&](uint32_t r, uint32_t s) -> uint32_t {
-        return r < RQ ? (uint32_t)sbc[r * SEL_THREADS + tid] : (s < seg_hi ? c.E[s] : 0u);
-    };
-    uint64_t tot64;
-    {
-        uint32_t mine = 0;
-        for (uint32_t r = 0; r < rounds; ++r) mine += bc_of(r, seg_lo + r * SEL_THREADS + tid);
-        block_incl_scan64<SEL_WAVES>((uint64_t)mine, sm.tmp, tot64);
-    }
-    const bool resident = !ks.rescan && tot64 <= (uint64_t)FIN_KEYS_LDS;
-    const uint32_t nkeys = (uint32_t)tot64;
-    uint32_t carry = 0;
-    for (uint32_t r = 0; r < rounds; ++r) {
-        const uint32_t s = seg_lo + r * SEL_THREADS + tid;
-        const uint32_t bc = bc_of(r, s);
-        uint32_t off = 0;
-        if (resident) {
-            uint64_t tt;
-            off = carry + (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)bc, sm.tmp, tt) - bc;
-            carry += (uint32_t)tt;
-        }
-        uint32_t kept = 0;
-        if (s < seg_hi)
-            ks.for_each(s, bc, [&](uint32_t key) {
-                atomicAdd(&h1[(key >> SH1) & m1], 1u);
-                if (resident) keys[off + kept] = key;
-                ++kept;
-            });
-    }
-    wg_sync();
-    if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
-    const uint32_t prefix24 = (b0 << (sh - SH1)) | sm.res[0];     /* the key bits from position 7 up */
-    const uint32_t need1 = need0 - sm.res[1];
-    wg_sync();
-    if (resident) {
-        for (uint32_t i = tid; i < nkeys; i += SEL_THREADS) {
-            const uint32_t key = keys[i];
-            if ((key >> SH1) == prefix24) atomicAdd(&sm.h2[key & (NB2 - 1)], 1u);
-        }
-    } else {
-        for (uint32_t r = 0; r < rounds; ++r) {
-            const uint32_t s = seg_lo + r * SEL_THREADS + tid;
-            if (s < seg_hi)
-                ks.for_each(s, bc_of(r, s), [&](uint32_t key) {
-                    if ((key >> SH1) == prefix24) atomicAdd(&sm.h2[key & (NB2 - 1)], 1u);
-                });
-        }
-    }
-    wg_sync();
-    if (!find_digit_lds<NB2, SEL_WAVES>(sm.h2, need1, sm.tmp, sm.res)) { if (tid == 0) err[0] = 1u; return; }
-    const uint32_t T = (prefix24 << 7) | sm.res[0];
-    const uint32_t e_b = need1 - sm.res[1];
-    wg_sync();
-    carry = 0;
-    finish_prefixes<1>(t, c, b, seg_lo, seg_hi, T, e_b, kb, chunk_seg, sm.tmp, err,
-                    [&](uint32_t r, uint32_t s, uint32_t &g, uint32_t &q) {
-                        const uint32_t bc = bc_of(r, s);
-                        if (resident) {
-                            uint64_t tt;
-                            const uint32_t off = carry + (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)bc, sm.tmp, tt) - bc;
-                            carry += (uint32_t)tt;
-                            for (uint32_t i = 0; i < bc; ++i) {
-                                const uint32_t key = keys[off + i];
-                                g += key > T ? 1u : 0u;
-                                q += key == T ? 1u : 0u;
-                            }
-                        } else if (s < seg_hi) {
-                            ks.for_each(s, bc, [&](uint32_t key) {
-                                g += key > T ? 1u : 0u;
-                                q += key == T ? 1u : 0u;
-                            });
-                        }
-                    });
 }
 
 /* One workgroup of 1024 threads per bucket decided from staged elements: the threshold key T and
- * the tie allowance e from the few undecided keys (12 + 7 remaining bits, histograms in LDS),
- * then every segment's place in the survivor order.  PATH_ZERO buckets arrive with T = 0 and e
- * known and only get the prefixes. */
+ * the tie allowance e from the bucket's undecided keys (12 + 7 remaining bits, histograms in LDS),
+ * then every segment's place in the survivor order.  The keys are read once per step, four per thread in
+ * flight, and kept in LDS when they fit.  A bucket of more than FIN_MAX_SEGS segments goes through every step
+ * in windows of so many, a range of the list's parts each (110 M elements in one bucket, 0.1 %: 77 us; by one
+ * thread per segment 264).  PATH_ZERO buckets arrive with T = 0 and e known and only get the
+ * prefixes.  in_windows: diagnostic, windows of two parts and nothing kept in LDS. */
 __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c, const uint32_t *__restrict__ sel0, uint32_t selSh,
-                                                               uint32_t *__restrict__ tail_ovf,
-                                                               const uint32_t *__restrict__ lcnt,
+                                                               uint32_t *__restrict__ cursor, const uint2 *__restrict__ part,
                                                                const uint32_t *__restrict__ lkey,
                                                                uint32_t *__restrict__ chunk_seg,
-                                                               uint32_t *__restrict__ err, int force_rescan,
-                                                               const float *__restrict__ r)
+                                                               uint32_t *__restrict__ err, int in_windows)
 {
     __shared__ uint32_t pool[FIN_POOL];
     __shared__ uint32_t h2[NB2];
@@ -700,36 +497,112 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     __shared__ uint32_t res[4];
     const uint32_t b = blockIdx.x, tid = threadIdx.x;
     const uint32_t path = t.fast[b], kb = t.k[b];
-    const uint32_t u0 = sel0[b], u1 = sel0[b + 1];
-    const uint32_t ovf = tail_ovf[b];
-    if (tid == 0 && ovf) tail_ovf[b] = 0u;           /* left clean for the next call */
-    /* this unit's list length, fetched before the bucket's state is known */
-    const uint32_t my_cnt = (tid < u1 - u0 && tid < SEL_THREADS) ? lcnt[u0 + tid] : 0u;
+    const uint32_t u0 = sel0[b], nun = sel0[b + 1] - u0;
+    const uint32_t in_room = cursor[b];
+    const uint32_t wun = in_windows ? 2u : min(SEL_THREADS, FIN_MAX_SEGS >> selSh);      /* parts per window */
+    /* the first window's part of this thread, fetched before the bucket's state is known */
+    uint2 mine = tid < min(nun, wun) ? part[u0 + tid] : make_uint2(0u, 0u);
     if (path == PATH_DENSE || kb == 0u) return;
     const uint32_t seg_lo = t.tile0[b], seg_hi = t.tile0[b + 1];
     const uint32_t b0 = t.T[b];                      /* the key bits from position sh up; PATH_ZERO: the full key (0) */
     const uint32_t need0 = t.need[b], sh = t.sh[b];
-    FinShared sm;
-    sm.pool = pool; sm.h2 = h2; sm.tmp = tmp; sm.res = res;
+    uint64_t run = 0;
     if (path == PATH_ZERO) {
         /* the streaming pass counted non-zero (G) and zero (E) keys per segment; when a band from
          * key 1 up was staged as well, G holds the keys above the band and the staged ones add to it */
         const bool mixed = t.par[b].x != t.par[b].y;
-        finish_prefixes<4>(t, c, b, seg_lo, seg_hi, 0u, need0, kb, chunk_seg, tmp, err,
-                        [&](uint32_t, uint32_t s, uint32_t &g, uint32_t &q) {
+        finish_prefixes<4>(t, c, b, seg_lo, seg_hi, need0, run, chunk_seg, tmp,
+                        [&](uint32_t s, uint32_t &g, uint32_t &q) {
                             if (s < seg_hi) { q += c.E[s]; if (mixed) g += c.cnt[s]; }
                         });
+        finish_state(t, b, 0u, need0, kb, run, err);
         return;
     }
-    const uint32_t nun = u1 - u0;
-    const int no_list = __syncthreads_or(my_cnt == NONE);
-    /* the lists hold every undecided key whenever none of them was left out; the tails are the
-     * fallback, and when a tail did not fit either (or a segment has none: it overflowed), the
-     * segments are filtered again */
-    if (no_list || force_rescan || nun > SEL_THREADS || seg_hi - seg_lo > FIN_MAX_SEGS)
-        finish_from_tails(t, c, b, b0, sh, need0, kb, seg_lo, seg_hi, ovf != 0u || force_rescan, chunk_seg, sm, err, r);
-    else
-        finish_from_lists(t, c, b, b0, sh, need0, kb, seg_lo, seg_hi, u0, nun, my_cnt, selSh, lkey, chunk_seg, sm, err);
+    uint32_t *h1 = pool, *cnts = pool, *keys = pool + FIN_AT_KEYS, *upre = pool + FIN_AT_UPRE, *upos = pool + FIN_AT_UPOS;
+    const uint32_t *list = lkey + list_base(seg_lo, b);
+    for (uint32_t i = tid; i < NB1; i += SEL_THREADS) h1[i] = 0u;
+    if (tid < NB2) h2[tid] = 0u;
+    wg_sync();
+    if (tid == 0 && in_room) cursor[b] = 0u;         /* every thread has read it: left clean for the next call */
+    const bool one = nun <= wun;
+    const uint32_t m1 = (1u << (sh - SH1)) - 1u;     /* level-1 digit: key bits sh-1 .. 7 (at most 12) */
+    /* the parts [w0, w0 + wn) of the list: their prefixes and places to LDS; returns how many keys they hold */
+    auto window = [&](uint32_t w0) {
+        const uint32_t wn = min(wun, nun - w0);
+        if (!one) mine = tid < wn ? part[u0 + w0 + tid] : make_uint2(0u, 0u);
+        uint64_t tot64;
+        const uint32_t incl = (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)mine.y, tmp, tot64);      /* (the window before has been consumed, too) */
+        if (tid < wn) { upre[tid] = incl - mine.y; upos[tid] = mine.x; }
+        wg_sync();
+        return (uint32_t)tot64;
+    };
+    /* f(i, part, entry) for the n keys of the window; LDS: they are in `keys` */
+    auto for_keys = [&](uint32_t w0, uint32_t n, bool lds, auto f) {
+        const uint32_t wn = min(wun, nun - w0);
+#pragma unroll 1
+        for (uint32_t i0 = tid; i0 < n; i0 += 4 * SEL_THREADS) {
+            uint32_t e[4], un[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + u * SEL_THREADS;
+                e[u] = un[u] = 0u;
+                if (i < n) {
+                    uint32_t lo = 0, hi = wn;            /* upre[lo] <= i < upre[hi] */
+                    while (hi - lo > 1) { const uint32_t mid = (lo + hi) >> 1; if (upre[mid] <= i) lo = mid; else hi = mid; }
+                    un[u] = lo;
+                    e[u] = lds ? keys[i] : list[upos[lo] + (i - upre[lo])];
+                }
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u)
+                if (i0 + u * SEL_THREADS < n) f(i0 + u * SEL_THREADS, un[u], e[u]);
+        }
+    };
+    bool resident = false;
+    uint32_t n0 = 0;
+    for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
+        const uint32_t n = n0 = window(w0);
+        resident = one && n <= FIN_KEYS_LDS && !in_windows;
+        for_keys(w0, n, false, [&](uint32_t i, uint32_t, uint32_t e) {
+            add_shared(h1, (e >> SH1) & m1, 1u);
+            if (resident) keys[i] = e;
+        });
+    }
+    wg_sync();
+    if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
+    const uint32_t d1 = res[0];
+    const uint32_t need1 = need0 - res[1];
+    uint32_t n = 0;
+    for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
+        n = one ? n0 : window(w0);
+        for_keys(w0, n, resident, [&](uint32_t, uint32_t, uint32_t e) {
+            if (((e >> SH1) & m1) == d1) add_shared(h2, e & (NB2 - 1), 1u);
+        });
+    }
+    wg_sync();
+    if (!find_digit_lds<NB2, SEL_WAVES>(h2, need1, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
+    const uint32_t d2 = res[0];
+    const uint32_t T = (b0 << sh) | (d1 << SH1) | d2;
+    const uint32_t e_b = need1 - res[1];             /* ties admitted: 1 <= e_b <= keys equal to T */
+    const uint32_t low = (1u << sh) - 1u, Tlow = T & low;      /* the undecided bits */
+    for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
+        const uint32_t wn = min(wun, nun - w0);
+        const uint32_t s_lo = seg_lo + (w0 << selSh), s_hi = min(seg_hi, s_lo + (wn << selSh));
+        if (!one) n = window(w0);
+        for (uint32_t i = tid; i < s_hi - s_lo; i += SEL_THREADS) cnts[i] = 0u;       /* takes the place of the level-1 histogram */
+        wg_sync();
+        /* per segment: keys above T (high half of its count) and equal to it */
+        for_keys(w0, n, resident, [&](uint32_t, uint32_t un, uint32_t e) {
+            const uint32_t v = e & low;
+            if (v >= Tlow) add_shared(cnts, (un << selSh) + (e >> SH0), v > Tlow ? 1u << 16 : 1u);
+        });
+        wg_sync();
+        finish_prefixes<4>(t, c, b, s_lo, s_hi, e_b, run, chunk_seg, tmp,
+                        [&](uint32_t s, uint32_t &g, uint32_t &q) {
+                            if (s < s_hi) { const uint32_t v = cnts[s - s_lo]; g += v >> 16; q += v & 0xFFFFu; }
+                        });
+    }
+    finish_state(t, b, T, e_b, kb, run, err);
 }
 
 /* ------------------------------------------------------------------ k_encode */

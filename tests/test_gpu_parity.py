@@ -437,6 +437,48 @@ def test_decompress_accumulate(bits):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("rescan", [0, 1])
+@pytest.mark.parametrize("bits,where", [(8, "ties"), (4, "close"), (32, "close"), (16, "ties")])
+def test_undecided_keys_in_one_place(path, rescan, bits, where):
+    """The keys around the threshold all lie in a few neighbouring tiles: more of them than one workgroup of the
+    search collects in LDS (4096), staging segments that overflow, a bucket list that holds them all the same (by the
+    candidate and by the band path), one key too many for it; in one window and in windows of two parts (rescan)."""
+    sizes = [1_048_576, 300_003, 7]
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    c = Case(_rand(n, 61), off, chunk=256)
+    c.ctx.set_option("rescan", rescan)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7)
+    room = 48 * 512 + 4096                           # what the first bucket's 512 tiles have in common
+    for step, (run, ratio) in enumerate(((20_000, 0.012), (room, 0.02), (room + 1, 0.02), (60_000, 0.3), (5000, 0.004))):
+        g = _rand(n, 70 + step)
+        c.set_residual(np.zeros(n, dtype=np.float32))
+        for lo in (3_001, int(off[1]) + 2_050):
+            m = min(run, 100_000 if lo > n // 2 else run)
+            x = torch.full((m,), 0.125, device=DEV)
+            if where == "close":                     # distinct keys that share their leading bits
+                x = x * (1.0 + torch.rand(m, generator=gen, device=DEV) * 2.0 ** -9)
+            g[lo:lo + m] = x * torch.where(torch.arange(m, device=DEV) % 3 == 0, -1.0, 1.0)
+        c.set_grad(g)
+        c.step(ratio, bits)
+
+
+def test_one_bucket_of_more_tiles_than_a_window(path):
+    """36 M elements in one bucket: 17579 tiles, more than the search's counts in LDS hold; candidates, a band, ties."""
+    if path == "dense":
+        pytest.skip("the dense passes know no windows")
+    n = 36_000_001
+    g = _rand(n, 9)
+    g[20_000_000:20_300_000] = torch.round(g[20_000_000:20_300_000] * 2e3) / 2e3
+    c = Case(g, W.offsets_of([n]))
+    c.step(0.01, 8)
+    assert c.ctx.bucket_state(0)["path"] in (1, 2)
+    c.set_grad(torch.round(_rand(n, 10) * 3e5) / 3e5)
+    c.step(0.4, 8)
+    assert c.ctx.bucket_state(0)["path"] == 2
+
+
 @pytest.mark.parametrize("bits,chunk", [(4, 8), (4, 2048), (8, 24), (8, 2048), (16, 8), (32, 8)])
 @pytest.mark.parametrize("start", [0, 1, 2, 3])
 def test_decode_of_crowded_tiles(bits, chunk, start):
