@@ -44,6 +44,7 @@ constexpr uint32_t NHC = 8;       /* copies of a bucket's bins, one per die's sh
 constexpr int SH0 = 19;   /* key >> 19         : level-0 digit (sign-less exponent + 4 mantissa bits) */
 constexpr int SH1 = 7;    /* (key >> 7) & 4095 : level-1 digit;  key & 127 : level-2 digit */
 constexpr uint32_t NONE = 0xFFFFFFFFu;
+constexpr uint32_t SH_NONE = 31;  /* Tables::sh of a bucket of whose threshold nothing is known yet */
 constexpr uint32_t SAMPLE_ALL_BELOW = 262144;  /* buckets smaller than this are sampled in full */
 constexpr uint32_t SAMPLE_STRIDE = 64;         /* of larger ones at most every 64th element, */
 constexpr uint32_t SAMPLE_ELEMS = 131072;      /* and at most about so many: the margins they leave (a third more staged than sent at
@@ -115,7 +116,8 @@ struct Tables {
     uint32_t *ovf;           /* B   a staging segment of the bucket overflowed */
     uint32_t *ftile0;        /* B+1 prefix of the tiles of buckets on the dense passes */
     uint32_t *nhard;         /* 4   [0] buckets of this call that are not on PATH_CAND (their kernels leave at once when 0),
-                              *     [1] the barrier of the dense passes, [2] buckets on PATH_DENSE */
+                              *     [1] the barrier of the dense passes, [2] buckets on PATH_DENSE,
+                              *     [3] those of them whose sh is SH_NONE */
     uint32_t *kw;            /* B   parameters the pruning step keeps (only with weights) */
     const uint32_t *pmask;   /* with Algorithm 2 Step 2: the pruning bitmap, TILE / 32 words per tile, bit = pruned; else NULL */
     uint32_t B;

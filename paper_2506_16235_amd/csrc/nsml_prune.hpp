@@ -185,15 +185,16 @@ __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ 
     if (ovf) t.ovf[b] = 0u;
     nband_out[b] = total;
     const uint32_t top = (p.z - 1u) >> p.w;
-    if (p.x != NONE && !ovf && found && !(res[0] == (uint32_t)NHB - 1u && (p.x >> p.w) != top - res[0])
-        && res[2] <= list_room(t.tile0[b + 1] - t.tile0[b])) {
-        t.T[b] = top - res[0];
-        t.need[b] = want - res[1];
-        t.sh[b] = p.w;
+    const bool known = p.x != NONE && found && !(res[0] == (uint32_t)NHB - 1u && (p.x >> p.w) != top - res[0]);
+    t.T[b] = known ? top - res[0] : 0u;
+    t.need[b] = known ? want - res[1] : want;
+    t.sh[b] = known ? p.w : SH_NONE;
+    if (known && !ovf && res[2] <= list_room(t.tile0[b + 1] - t.tile0[b])) {
         t.fast[b] = PATH_BAND;
     } else {
         t.fast[b] = PATH_DENSE;
         atomicAdd(t.nhard + 2, 1u);                      /* k_whard has work */
+        if (!known) atomicAdd(t.nhard + 3, 1u);
     }
 }
 

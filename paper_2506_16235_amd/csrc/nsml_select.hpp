@@ -149,6 +149,12 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
                 p.x = dig_dn != 0u ? dig_dn << SH0 : 1u;
                 p.y = p.z = (dig_up + 1u) << SH0;
                 p.w = window_shift(p.x, p.z);
+            } else if (exact) {
+                /* too many keys in one digit to stage them, but all of the bucket was sampled: the dense passes
+                 * need not look for that digit again */
+                p.w = SH0;
+                t.T[b] = res[0];
+                t.need[b] = k - res[1];
             }
         }
     }
@@ -399,24 +405,30 @@ __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ h
     if (tid != 0) return;
     const uint32_t ovf = t.ovf[b];
     if (ovf) t.ovf[b] = 0u;                    /* left clean for the next call, like the bins */
-    uint32_t path = PATH_DENSE, T = 0u, need = want, sh = SH0, why = 0u;
-    if (!have_cand || p.x == NONE) why = WHY_NO_GUESS;
+    uint32_t path = PATH_DENSE, T = 0u, need = want, sh = SH_NONE, why = 0u;
+    if (!have_cand || p.x == NONE) {
+        why = WHY_NO_GUESS;
+        if (have_cand && p.w == (uint32_t)SH0) { T = t.T[b]; need = t.need[b]; sh = SH0; }       /* (left there by k_predict) */
+    }
     else if (p.x == p.y) {
         /* n_hi = non-zero keys among the selectable elements: if they are no more than k,
          * all of them survive and zeros (lowest indices first) fill the rest */
-        if (n_hi <= want) { path = PATH_ZERO; need = want - n_hi; }
+        if (n_hi <= want) { path = PATH_ZERO; need = want - n_hi; sh = SH0; }
         else why = WHY_NONZEROS;
     } else if (p.x == 1u && p.y != NONE && (uint64_t)n_hi + total <= want) {
         /* the band starts at key 1 and everything non-zero is still not enough: zero threshold */
-        path = PATH_ZERO; need = want - (n_hi + total);
+        path = PATH_ZERO; need = want - (n_hi + total); sh = SH0;
     } else if (found) {
         /* a tile whose segment overflowed is read from the dense accumulator by the kernels
          * that find the threshold; the survivors of such a bucket are then taken from the dense
          * accumulator as well (PATH_BAND), since the staged entries cannot supply them all */
         const uint32_t top = (p.z - 1u) >> p.w, bin = res[0], at = res[2];
         if (bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin) why = WHY_OUTSIDE_BAND;    /* the open last bin */
-        else if (at > list_room(t.tile0[b + 1] - t.tile0[b])) why = WHY_NO_ROOM;
-        else { path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND; T = top - bin; need = want - res[1]; sh = p.w; }
+        else {
+            T = top - bin; need = want - res[1]; sh = p.w;
+            if (at > list_room(t.tile0[b + 1] - t.tile0[b])) why = WHY_NO_ROOM;       /* (the dense passes go on from that bin) */
+            else path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND;
+        }
     } else why = n_hi < want ? WHY_TOO_FEW : WHY_OUTSIDE_BAND;
     t.why[b] = why;
     {
@@ -434,6 +446,7 @@ __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ h
     t.fast[b] = path;
     if (path != PATH_CAND) atomicAdd(t.nhard, 1u);
     if (path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);
+    if (path == PATH_DENSE && sh == SH_NONE) atomicAdd(t.nhard + 3, 1u);
 }
 
 /* One workgroup: the list of tiles that belong to buckets on the dense passes.  (Kept as its own small
@@ -457,18 +470,19 @@ __device__ __forceinline__ void fb_plan_body(const Tables &t)
     if (tid == 0) t.ftile0[t.B] = carry;
 }
 
-/* The next digit of a dense bucket's k-th key from its histogram over the accumulator (levels of
- * 12, 12 and 7 bits); the histogram is left clean for the next call. */
+/* The next digit of a dense bucket's k-th key from its histogram over the accumulator: level 0 the 12 bits
+ * from position 19 up, of the buckets of which nothing is known yet; level 1 the bits below what is known down to
+ * position 7; level 2 the last 7.  The histogram is left clean for the next call. */
 template <int LEVEL>
 __device__ __forceinline__ void pick_body(const Tables &t, uint32_t *__restrict__ hist, uint32_t *__restrict__ err, uint32_t b)
 {
     constexpr int NB = LEVEL == 0 ? NB0 : LEVEL == 1 ? NB1 : NB2;
-    constexpr int BITS = LEVEL == 2 ? 7 : 12;
     __shared__ uint32_t tmp[WG];
     const uint32_t tid = threadIdx.x;
     if (t.fast[b]) return;                     /* decided from its staged elements */
-    const uint32_t want = LEVEL == 0 ? t.k[b] : t.need[b];
+    const uint32_t want = t.need[b], sh = t.sh[b];
     if (want == 0) return;                     /* empty bucket */
+    if (LEVEL == 0 && sh != SH_NONE) return;
     DigitWalk<NB> w;
     w.load(hist + (uint64_t)b * NB, tmp);
     w.clear(hist + (uint64_t)b * NB);
@@ -478,8 +492,9 @@ __device__ __forceinline__ void pick_body(const Tables &t, uint32_t *__restrict_
     }
     uint32_t digit, above, at;
     if (w.find(want, digit, above, at)) {
-        t.T[b] = LEVEL == 0 ? digit : (t.T[b] << BITS) | digit;
+        t.T[b] = LEVEL == 0 ? digit : (t.T[b] << (LEVEL == 1 ? sh - (uint32_t)SH1 : 7u)) | digit;
         t.need[b] = want - above;
+        if (LEVEL == 0) t.sh[b] = SH0;
     }
 }
 
@@ -527,66 +542,75 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
 
 /* Histogram of a level's digit over the dense source of the buckets on the dense passes.  A work
  * unit is FB_TILES consecutive tiles of that list, of one bucket or several; the LDS histogram is
- * flushed when the bucket changes. */
-constexpr uint32_t FB_TILES = 16;
+ * flushed when the bucket changes.  The team is a workgroup per compute unit, so what bounds it is how much each
+ * has in flight: FB_AHEAD tiles at a time (two 16-byte accesses per thread and tile; one tile at a time took 1.5
+ * times as long as the four accesses that a tile had when it was twice as large). */
+constexpr uint32_t FB_TILES = 16, FB_AHEAD = 4;
 template <int LEVEL>
 __device__ __forceinline__ void fb_refine_body(const float *__restrict__ r, const Tables &t,
                                                uint32_t *__restrict__ hist, uint32_t *h,
                                                uint32_t bid, uint32_t nblk)
 {
     constexpr int NB = LEVEL == 0 ? NB0 : LEVEL == 1 ? NB1 : NB2;
-    constexpr int PSH = LEVEL == 0 ? 31 : LEVEL == 1 ? SH0 : SH1;          /* key >> PSH is the prefix (0 at level 0) */
-    constexpr int DSH = LEVEL == 0 ? SH0 : LEVEL == 1 ? SH1 : 0;
-    constexpr uint32_t DMASK = NB - 1;
+    constexpr int Q = TILE / (4 * WG);
+    constexpr uint32_t DSH = LEVEL == 0 ? SH0 : LEVEL == 1 ? SH1 : 0;
     const uint32_t tid = threadIdx.x;
     const uint32_t total = t.ftile0[t.B];
     for (uint32_t f0 = bid * FB_TILES; f0 < total; f0 += nblk * FB_TILES) {
         const uint32_t f1 = min(total, f0 + FB_TILES);
-        uint32_t b = NONE, fend = f0;
-        uint32_t prefix = 0;
-        for (uint32_t f = f0; f < f1; ++f) {
-            if (f >= fend) {                           /* the next bucket (same in every thread) */
-                if (b != NONE) { wg_sync(); hist_flush(h, hist + (uint64_t)b * NB, NB); wg_sync(); }
-                b = find_bucket<uint32_t>(t.ftile0, t.B, f);
-                fend = t.ftile0[b + 1];
-                prefix = LEVEL == 0 ? 0u : t.T[b];
-                for (int i = tid; i < NB; i += WG) h[i] = 0;
-                wg_sync();
-            }
-            const uint32_t tile = t.tile0[b] + (f - t.ftile0[b]);
-            const TileGeo s = tile_geo(t, b, tile);
-            const bool interior = s.base >= s.lo && s.base + TILE <= s.hi;
+        uint32_t f = f0;
+        while (f < f1) {                               /* bucket by bucket (the same in every thread) */
+            const uint32_t b = find_bucket<uint32_t>(t.ftile0, t.B, f), fend = min(f1, t.ftile0[b + 1]);
+            const uint32_t sh = t.sh[b];
+            if (LEVEL == 0 && sh != SH_NONE) { f = fend; continue; }
+            const uint32_t psh = LEVEL == 0 ? 31u : LEVEL == 1 ? sh : (uint32_t)SH1;       /* key >> psh is what is known */
+            const uint32_t dmask = LEVEL == 1 ? (1u << (sh - SH1)) - 1u : NB - 1u;
+            const uint32_t prefix = LEVEL == 0 ? 0u : t.T[b];
+            for (int i = tid; i < NB; i += WG) h[i] = 0;
+            wg_sync();
+            for (; f < fend; f += FB_AHEAD) {
+                float x[FB_AHEAD][Q][4];
+                uint32_t m[FB_AHEAD][Q];
+                const uint32_t tile = t.tile0[b] + (f - t.ftile0[b]);
+                const TileGeo s = tile_geo(t, b, tile);
 #pragma unroll
-            for (int u = 0; u < TILE / (4 * WG); ++u) {
-                const uint64_t gi = s.base + (uint64_t)(u * WG + tid) * 4;
-                float x[4];
-                uint32_t m = load_quad(r, gi, s.lo, s.hi, x);
-                if (t.pmask) m &= ~pruned_bits(t.pmask, tile, u * WG + tid);
-                uint32_t d[4];
-                uint32_t hit = 0;
+                for (uint32_t v = 0; v < FB_AHEAD; ++v)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const uint32_t key = keyof(x[j]);
-                    d[j] = (key >> DSH) & DMASK;
-                    if (((m >> j) & 1u) && (key >> PSH) == prefix) hit |= 1u << j;
-                }
-                if (interior) {
-                    /* all lanes active here: whole-wavefront shortcut for runs of equal keys */
-                    const uint32_t fd = __builtin_amdgcn_readfirstlane(d[0]);
-                    const bool same = hit == 0xFu && d[0] == fd && d[1] == fd && d[2] == fd && d[3] == fd;
-                    if (__all(same)) {
-                        if ((tid & 63) == 0) atomicAdd(&h[fd], 256u);
-                        continue;
+                    for (int u = 0; u < Q; ++u) {
+                        m[v][u] = 0u;
+                        if (f + v < fend) {
+                            m[v][u] = load_quad(r, s.base + (uint64_t)v * TILE + (uint64_t)(u * WG + tid) * 4, s.lo, s.hi, x[v][u]);
+                            if (t.pmask) m[v][u] &= ~pruned_bits(t.pmask, tile + v, u * WG + tid);
+                        }
                     }
-                }
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if ((hit >> j) & 1u) atomicAdd(&h[d[j]], 1u);
+                for (uint32_t v = 0; v < FB_AHEAD; ++v)
+#pragma unroll
+                    for (int u = 0; u < Q; ++u) {
+                        if (f + v >= fend) continue;
+                        uint32_t d[4], hit = 0;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t key = keyof(x[v][u][j]);
+                            d[j] = (key >> DSH) & dmask;
+                            if (((m[v][u] >> j) & 1u) && (key >> psh) == prefix) hit |= 1u << j;
+                        }
+                        /* runs of equal keys: one addition for the wavefront */
+                        const uint32_t fd = __builtin_amdgcn_readfirstlane(d[0]);
+                        if (__all(hit == 0xFu && d[0] == fd && d[1] == fd && d[2] == fd && d[3] == fd)) {
+                            if ((tid & 63) == 0) atomicAdd(&h[fd], 256u);
+                            continue;
+                        }
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if ((hit >> j) & 1u) atomicAdd(&h[d[j]], 1u);
+                    }
             }
+            f = fend;
+            wg_sync();
+            hist_flush(h, hist + (uint64_t)b * NB, NB);
+            wg_sync();
         }
-        wg_sync();
-        if (b != NONE) hist_flush(h, hist + (uint64_t)b * NB, NB);
-        wg_sync();
     }
 }
 

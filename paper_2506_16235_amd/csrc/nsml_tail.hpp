@@ -911,25 +911,23 @@ __device__ __forceinline__ void segcount_dense_body(const float *__restrict__ r,
     if (t.fast[b] != PATH_DENSE || t.k[b] == 0u) continue;
     const TileGeo s = tile_geo(t, b, ss);
     const uint32_t T = t.T[b];
-    constexpr uint32_t wt0 = 0, wt1 = TILE / WTILE;
     uint32_t ng = 0, ne = 0;
-    for (uint32_t wt = wt0; wt < wt1; ++wt) {
-        const uint64_t wb = s.base + (uint64_t)wt * WTILE;
+    float x[TILE / 256][4];
+    uint32_t m[TILE / 256];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint64_t gi = wb + (uint64_t)(u * 64 + lane) * 4;
-            float x[4];
-            uint32_t m = load_quad(r, gi, s.lo, s.hi, x);
-            if (t.pmask) m &= ~pruned_bits(t.pmask, ss, wt * WG + u * 64 + lane);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t key = keyof(x[j]);
-                const bool ok = (m >> j) & 1u;
-                ng += (ok && key > T) ? 1u : 0u;
-                ne += (ok && key == T) ? 1u : 0u;
-            }
-        }
+    for (int u = 0; u < TILE / 256; ++u) {             /* all of the tile in flight */
+        m[u] = load_quad(r, s.base + (uint64_t)(u * 64 + lane) * 4, s.lo, s.hi, x[u]);
+        if (t.pmask) m[u] &= ~pruned_bits(t.pmask, ss, u * 64 + lane);
     }
+#pragma unroll
+    for (int u = 0; u < TILE / 256; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t key = keyof(x[u][j]);
+            const bool ok = (m[u] >> j) & 1u;
+            ng += (ok && key > T) ? 1u : 0u;
+            ne += (ok && key == T) ? 1u : 0u;
+        }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) { ng += __shfl_xor(ng, d, 64); ne += __shfl_xor(ne, d, 64); }
     if (lane == 0) { c.G[ss] = ng; c.E[ss] = ne; }
@@ -969,7 +967,8 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uin
 
 /* Threshold key, tie allowance and prefixes per tile of the buckets on the dense passes, by a team of
  * nblk resident workgroups: list of their tiles, then per level a histogram over the source and its
- * digit, then counts per tile and their prefixes, with a barrier after each step.  h: NB0 words of LDS. */
+ * digit (the first one only where a bucket's leading bits are not known from the counts), then counts per tile and
+ * their prefixes, with a barrier after each step.  h: NB0 words of LDS. */
 __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
                                                 uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *h, uint32_t *bar,
                                                 uint32_t bid, uint32_t nblk, uint32_t *__restrict__ err)
@@ -977,10 +976,12 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
     uint32_t arrivals = 0;
     if (bid == 0) fb_plan_body(t);
     grid_barrier(bar, arrivals += nblk, err);
-    fb_refine_body<0>(r, t, f0, h, bid, nblk);
-    grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<0>(t, f0, err, b); }
-    grid_barrier(bar, arrivals += nblk, err);
+    if (t.nhard[3] != 0u) {                          /* (not written any more in this launch: the same in the whole team) */
+        fb_refine_body<0>(r, t, f0, h, bid, nblk);
+        grid_barrier(bar, arrivals += nblk, err);
+        for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<0>(t, f0, err, b); }
+        grid_barrier(bar, arrivals += nblk, err);
+    }
     fb_refine_body<1>(r, t, f1, h, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
     for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); pick_body<1>(t, f1, err, b); }
