@@ -172,7 +172,8 @@ __device__ __forceinline__ bool pruned_elem(const uint32_t *__restrict__ pmask, 
 /* The window's bins of large gradients, from the staged elements (and from the dense source `r` where a
  * segment overflowed): a workgroup takes the segments of one workgroup of k_select_count, 16 or 4
  * lanes each, counts in LDS and adds what it has to one of the bucket's copies.  Bound by reading the
- * staged values (419 M elements at ratio 0.5, 3 % staged: 30 us; 109 M at 0.01: 10). */
+ * staged values (419 M elements at ratio 0.5, 3 % staged: 30 us; 109 M at 0.01: 17); an overflowed segment is
+ * fetched whole before any of it is counted (BERT-shaped gradient at 0.1: 65 us, one load after the other 71). */
 constexpr uint32_t BINS_U = 8;             /* entries a lane has in flight */
 __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
                                              uint32_t *__restrict__ hist, const float *__restrict__ r)
@@ -198,15 +199,21 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
 #pragma unroll
         for (uint32_t u = 0; u < BINS_U; ++u) if (i0 + u * lanes < len) count(keyof(x[u]));
     }
-    if (t.ovf[b]) {
-        for (uint32_t s = s0; s < s1; ++s) {
-            if (c.cnt[s] <= SEG_CAP) continue;       /* same for the whole workgroup */
-            const DenseSeg d = dense_seg(t, b, s);
-            const uint32_t tile0b = t.tile0[b];
-            const uint64_t lo_al = t.off[b] & ~3ull;
-            for (uint32_t e = tid; e < d.len; e += WG) {
-                const uint32_t key = keyof(r[d.e0 + e]);
-                if (key >= p.x && !(t.pmask && pruned_elem(t.pmask, tile0b, lo_al, d.e0 + e))) count(key);
+    if (t.ovf[b]) {                                  /* same for the whole workgroup */
+        const uint32_t lane = tid & 63u;
+        const uint32_t tile0b = t.tile0[b];
+        const uint64_t lo_al = t.off[b] & ~3ull;
+        /* which of them: a lane per segment, the same in every wavefront */
+        uint64_t todo = __ballot(lane < s1 - s0 && c.cnt[s0 + min(lane, s1 - s0 - 1u)] > SEG_CAP);
+        for (; todo; todo &= todo - 1ull) {
+            const DenseSeg d = dense_seg(t, b, s0 + (uint32_t)__builtin_ctzll(todo));
+            float x[TILE / WG];
+#pragma unroll
+            for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; x[u] = e < d.len ? r[d.e0 + e] : 0.0f; }
+#pragma unroll
+            for (uint32_t u = 0; u < TILE / WG; ++u) {
+                const uint32_t e = u * WG + tid, key = keyof(x[u]);
+                if (e < d.len && key >= p.x && key < p.z && !(t.pmask && pruned_elem(t.pmask, tile0b, lo_al, d.e0 + e))) count(key);
             }
         }
     }
