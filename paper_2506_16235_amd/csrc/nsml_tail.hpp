@@ -34,7 +34,6 @@ namespace {
 
 constexpr uint32_t SEL_THREADS = 1024;     /* k_select_finish workgroup: 16 wavefronts */
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
-constexpr uint32_t ENC_T = 512, ENC_WAVES = ENC_T / 64;     /* k_encode workgroup */
 constexpr uint32_t ENC_BLK = 2048;         /* survivors gathered in LDS at a time */
 
 /* Inclusive scan of 64-bit values over a workgroup of NW wavefronts; tmp: NW words of LDS. */
@@ -622,7 +621,7 @@ constexpr uint32_t CU = 4;                 /* entries of a segment a lane fetche
  * rank G + min(e, E), with G / E the numbers of entries above / equal to T before it: the prefixes
  * k_select_finish left per segment, then ballots, so nothing crosses wavefronts.  Returns how many
  * survivors this thread placed. */
-template <uint32_t GROUP, uint32_t SB>
+template <uint32_t ENC_T, uint32_t GROUP, uint32_t SB>
 __device__ __forceinline__ uint32_t gather_segments(const Cand &c, uint32_t sA, uint32_t sEnd, uint32_t T, uint32_t e_b,
                                                     uint32_t j0, uint32_t n, float *sv, uint32_t *si)
 {
@@ -686,14 +685,15 @@ __device__ __forceinline__ uint32_t gather_segments(const Cand &c, uint32_t sA, 
  * (One list of entries over all segments, dealt evenly to the lanes by a search of the segment in
  * LDS, follows the work more closely and was slower: 178 us against 142 at ratio 0.1 on 109 M
  * elements, the searches alone keep the LDS busy.)  filled (LDS) counts what was placed. */
+template <uint32_t ENC_T>
 __device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uint32_t sEnd, uint32_t T, uint32_t e_b, uint32_t j0,
                                                  uint32_t n, float *sv, uint32_t *si, uint32_t *filled)
 {
     const uint32_t m = sEnd - sA;
     uint32_t got;
-    if (n >= 24u * m) got = gather_segments<64, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
-    else if (n >= 6u * m) got = gather_segments<16, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
-    else got = gather_segments<4, 4>(c, sA, sEnd, T, e_b, j0, n, sv, si);
+    if (n >= 24u * m) got = gather_segments<ENC_T, 64, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
+    else if (n >= 6u * m) got = gather_segments<ENC_T, 16, 2>(c, sA, sEnd, T, e_b, j0, n, sv, si);
+    else got = gather_segments<ENC_T, 4, 4>(c, sA, sEnd, T, e_b, j0, n, sv, si);
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) got += __shfl_xor(got, d, 64);
     if ((threadIdx.x & 63u) == 0u && got) atomicAdd(filled, got);
@@ -703,7 +703,7 @@ __device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uin
  * absmax, scale, codes, packing, indices, and the coding error left in the residual.  Every
  * floating-point step is a single correctly rounded binary32 operation.  A chunk longer than
  * ENC_BLK is gathered block by block, once for its absmax and once more for the codes. */
-template <int BITS>
+template <int BITS, uint32_t ENC_T>
 __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
                                                const uint32_t *__restrict__ chunk_seg, float *__restrict__ r,
                                                uint32_t *__restrict__ idx_out, void *__restrict__ val,
@@ -712,9 +712,10 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
 {
     __shared__ float sv[ENC_BLK];
     __shared__ uint32_t si[ENC_BLK];
-    __shared__ float red[ENC_WAVES];
+    __shared__ float red[ENC_T / 64];
     __shared__ uint32_t sh, filled;
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
+    constexpr uint32_t ENC_WAVES = ENC_T / 64;
     const uint32_t tid = threadIdx.x;
     /* a workgroup takes cpw consecutive chunks (one, unless the payload has very many) */
     const uint64_t cend = min(n_chunks, ((uint64_t)blockIdx.x + 1) * cpw);
@@ -759,7 +760,7 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
             sA = wg_search_le<ENC_T>(seg_lo, seg_hi, (uint64_t)j0, rank0, &sh);
         }
         wg_sync();
-        gather_survivors(c, sA, sEnd, T, e_b, j0, n, sv, si, &filled);
+        gather_survivors<ENC_T>(c, sA, sEnd, T, e_b, j0, n, sv, si, &filled);
         wg_sync();
         if (tid == 0 && filled != n) err[0] = 1u;              /* the prefixes and the entries disagree */
     };
