@@ -395,12 +395,14 @@ __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const 
 
 /* LDS of k_select_finish, one pool (u32 words):
  *   [0, 4096)        level-1 histogram; later the counts of up to FIN_MAX_SEGS segments
- *   FIN_AT_KEYS      undecided keys, when all of the bucket's fit, in the order of the parts
+ *   FIN_AT_KEYS      undecided keys, when all of the bucket's fit
+ *   FIN_AT_SEGS      their segment numbers as u16
  *   FIN_AT_UPRE      exclusive prefix of the lengths of the list's parts
  *   FIN_AT_UPOS      where each part begins in the list */
 constexpr uint32_t FIN_KEYS_LDS = 3072;    /* undecided keys kept in LDS */
 constexpr uint32_t FIN_MAX_SEGS = 16384;   /* segments whose counts fit the pool: larger buckets go in windows of so many */
-constexpr uint32_t FIN_AT_KEYS = FIN_MAX_SEGS, FIN_AT_UPRE = FIN_AT_KEYS + FIN_KEYS_LDS, FIN_AT_UPOS = FIN_AT_UPRE + SEL_THREADS + 1;
+constexpr uint32_t FIN_AT_KEYS = FIN_MAX_SEGS, FIN_AT_SEGS = FIN_AT_KEYS + FIN_KEYS_LDS, FIN_AT_UPRE = FIN_AT_SEGS + FIN_KEYS_LDS / 2;
+constexpr uint32_t FIN_AT_UPOS = FIN_AT_UPRE + SEL_THREADS + 1;
 constexpr uint32_t FIN_POOL = FIN_AT_UPOS + SEL_THREADS;
 static_assert(NB1 <= FIN_MAX_SEGS, "the level-1 histogram overlaps the keys");
 
@@ -525,6 +527,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
         return;
     }
     uint32_t *h1 = pool, *cnts = pool, *keys = pool + FIN_AT_KEYS, *upre = pool + FIN_AT_UPRE, *upos = pool + FIN_AT_UPOS;
+    uint16_t *segs = reinterpret_cast<uint16_t *>(pool + FIN_AT_SEGS);
     const uint32_t *list = lkey + list_base(seg_lo, b);
     for (uint32_t i = tid; i < NB1; i += SEL_THREADS) h1[i] = 0u;
     if (tid < NB2) h2[tid] = 0u;
@@ -542,8 +545,8 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
         wg_sync();
         return (uint32_t)tot64;
     };
-    /* f(i, part, entry) for the n keys of the window; LDS: they are in `keys` */
-    auto for_keys = [&](uint32_t w0, uint32_t n, bool lds, auto f) {
+    /* f(i, entry, segment number inside the window) for the n keys of the window */
+    auto for_keys = [&](uint32_t w0, uint32_t n, auto f) {
         const uint32_t wn = min(wun, nun - w0);
 #pragma unroll 1
         for (uint32_t i0 = tid; i0 < n; i0 += 4 * SEL_THREADS) {
@@ -556,12 +559,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
                     uint32_t lo = 0, hi = wn;            /* upre[lo] <= i < upre[hi] */
                     while (hi - lo > 1) { const uint32_t mid = (lo + hi) >> 1; if (upre[mid] <= i) lo = mid; else hi = mid; }
                     un[u] = lo;
-                    e[u] = lds ? keys[i] : list[upos[lo] + (i - upre[lo])];
+                    e[u] = list[upos[lo] + (i - upre[lo])];
                 }
             }
 #pragma unroll
             for (uint32_t u = 0; u < 4; ++u)
-                if (i0 + u * SEL_THREADS < n) f(i0 + u * SEL_THREADS, un[u], e[u]);
+                if (i0 + u * SEL_THREADS < n) f(i0 + u * SEL_THREADS, e[u], (un[u] << selSh) + (e[u] >> SH0));
         }
     };
     bool resident = false;
@@ -569,21 +572,20 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
         const uint32_t n = n0 = window(w0);
         resident = one && n <= FIN_KEYS_LDS && !in_windows;
-        for_keys(w0, n, false, [&](uint32_t i, uint32_t, uint32_t e) {
+        for_keys(w0, n, [&](uint32_t i, uint32_t e, uint32_t seg) {
             add_shared(h1, (e >> SH1) & m1, 1u);
-            if (resident) keys[i] = e;
+            if (resident) { keys[i] = e; segs[i] = (uint16_t)seg; }
         });
     }
     wg_sync();
     if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t d1 = res[0];
     const uint32_t need1 = need0 - res[1];
-    uint32_t n = 0;
-    for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
-        n = one ? n0 : window(w0);
-        for_keys(w0, n, resident, [&](uint32_t, uint32_t, uint32_t e) {
-            if (((e >> SH1) & m1) == d1) add_shared(h2, e & (NB2 - 1), 1u);
-        });
+    auto last_digit = [&](uint32_t e) { if (((e >> SH1) & m1) == d1) add_shared(h2, e & (NB2 - 1), 1u); };
+    if (resident) {
+        for (uint32_t i = tid; i < n0; i += SEL_THREADS) last_digit(keys[i]);
+    } else {
+        for (uint32_t w0 = 0; w0 < nun; w0 += wun) for_keys(w0, one ? n0 : window(w0), [&](uint32_t, uint32_t e, uint32_t) { last_digit(e); });
     }
     wg_sync();
     if (!find_digit_lds<NB2, SEL_WAVES>(h2, need1, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
@@ -594,14 +596,19 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     for (uint32_t w0 = 0; w0 < nun; w0 += wun) {
         const uint32_t wn = min(wun, nun - w0);
         const uint32_t s_lo = seg_lo + (w0 << selSh), s_hi = min(seg_hi, s_lo + (wn << selSh));
-        if (!one) n = window(w0);
+        const uint32_t n = one ? n0 : window(w0);
         for (uint32_t i = tid; i < s_hi - s_lo; i += SEL_THREADS) cnts[i] = 0u;       /* takes the place of the level-1 histogram */
         wg_sync();
         /* per segment: keys above T (high half of its count) and equal to it */
-        for_keys(w0, n, resident, [&](uint32_t, uint32_t un, uint32_t e) {
+        auto tally = [&](uint32_t e, uint32_t seg) {
             const uint32_t v = e & low;
-            if (v >= Tlow) add_shared(cnts, (un << selSh) + (e >> SH0), v > Tlow ? 1u << 16 : 1u);
-        });
+            if (v >= Tlow) add_shared(cnts, seg, v > Tlow ? 1u << 16 : 1u);
+        };
+        if (resident) {
+            for (uint32_t i = tid; i < n; i += SEL_THREADS) tally(keys[i], segs[i]);
+        } else {
+            for_keys(w0, n, [&](uint32_t, uint32_t e, uint32_t seg) { tally(e, seg); });
+        }
         wg_sync();
         finish_prefixes<4>(t, c, b, s_lo, s_hi, e_b, run, chunk_seg, tmp,
                         [&](uint32_t s, uint32_t &g, uint32_t &q) {
