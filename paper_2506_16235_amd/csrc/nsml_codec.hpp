@@ -370,7 +370,7 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
     constexpr int U = TILE / (4 * NTH);          /* 16-byte stores per thread */
     constexpr int S = TILE / NTH < 8 ? TILE / NTH : 8;      /* survivors a thread has in flight */
     __shared__ float slots[TILE];
-    const uint32_t tile = xcd_tile(blockIdx.x);
+    const uint32_t tile = grid_tile();
     if (tile >= t.n_tiles) return;
     const uint32_t tid = threadIdx.x;
     const uint32_t b = tile_b[tile];
@@ -489,7 +489,7 @@ __global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, fl
     __shared__ double sq_w[STH / 64];
     __shared__ uint32_t z_w[STH / 64];
     __shared__ float red[STH / 64];
-    const uint32_t tile = xcd_tile(blockIdx.x);
+    const uint32_t tile = grid_tile();
     if (tile >= t.n_tiles) return;
     const uint32_t b = t.tile_b[tile];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -647,7 +647,7 @@ constexpr uint32_t ZERO_T = 1024;
 template <bool NT>
 __global__ __launch_bounds__(ZERO_T, 8) void k_zero(float *__restrict__ dense, uint64_t n)
 {
-    const uint64_t i = (uint64_t)xcd_tile(blockIdx.x) * (ZERO_T * 4u) + threadIdx.x * 4u;
+    const uint64_t i = (uint64_t)grid_tile() * (ZERO_T * 4u) + threadIdx.x * 4u;
     if (i + 4 <= n) st_out<NT>(reinterpret_cast<f4 *>(dense + i), f4{0.f, 0.f, 0.f, 0.f});
     else for (uint64_t j = i; j < n; ++j) dense[j] = 0.0f;
 }

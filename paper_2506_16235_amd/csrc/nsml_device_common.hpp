@@ -194,7 +194,15 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t bid)
     const uint32_t r = bid & (8u * XCD_RUN - 1u);
     return (bid & ~(8u * XCD_RUN - 1u)) + (r & 7u) * XCD_RUN + (r >> 3);
 }
-inline uint32_t xcd_grid(uint32_t n_tiles) { return (n_tiles + 8u * XCD_RUN - 1u) & ~(8u * XCD_RUN - 1u); }
+/* The grid of a streaming kernel: a launch may not have 2^32 threads in one dimension (512 for each of 2^23 tiles:
+ * 17 G elements), so beyond GRID_X workgroups they go on in the second one. */
+constexpr uint32_t GRID_X = 1u << 21;      /* (x 1024 threads = 2^31; a multiple of 8 * XCD_RUN) */
+inline dim3 xcd_grid(uint64_t n_tiles)
+{
+    const uint64_t g = (n_tiles + 8u * XCD_RUN - 1u) & ~(uint64_t)(8u * XCD_RUN - 1u);
+    return g <= GRID_X ? dim3((uint32_t)g) : dim3(GRID_X, (uint32_t)((g + GRID_X - 1u) / GRID_X));
+}
+__device__ __forceinline__ uint32_t grid_tile() { return xcd_tile(blockIdx.y * GRID_X + blockIdx.x); }
 
 /* A run of consecutive tiles of one bucket. */
 struct TileGeo {

@@ -556,7 +556,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     const uint64_t zw = zero_words(B);
     const uint32_t clear_grid = (uint32_t)((zw + WG * 8 - 1) / (WG * 8));
     float *vdst = bits == 32 ? static_cast<float *>(val) : c->d_v;
-    const uint32_t sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
+    const dim3 sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
     const bool bins = !c->force_dense && c->n_tiles >= HIST_MAX_TILES;      /* the window's bins by a kernel of their own */
     /* floor(0.5 * (1 - ratio) * n_b) parameters are pruned: when that is none of any bucket (ratio 1, the
      * controller's cap), the weights decide nothing and are not read */
@@ -764,7 +764,7 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
     const uint32_t n_tiles = t.n_tiles;
     if (decomp_by_scatter(variant, K, n)) {
         /* few survivors: zeros at the speed of a fill, then the survivors stored over them */
-        const uint32_t zgrid = xcd_grid((uint32_t)((n + ZERO_T * 4 - 1) / (ZERO_T * 4)));
+        const dim3 zgrid = xcd_grid((n + ZERO_T * 4 - 1) / (ZERO_T * 4));
         if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
         else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
         const ScatterGrid sg = scatter_grid(K, n, false);
@@ -788,7 +788,7 @@ static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint6
         LAUNCH(c, KID_TILESTART, st, k_tilestart<2>, (uint32_t)want, idx, t, K, d_ts);
     }
     const uint32_t *ts = d_ts;
-    const uint32_t grid = xcd_grid(n_tiles);
+    const dim3 grid = xcd_grid(n_tiles);
     /* Threads per tile.  Everything sent is a plain decode without a chain of dependent loads: whole values in the
      * streaming kernels' shape (419 M elements: 537 us with 512 threads, 575 with 128), narrower ones with more of
      * them per thread (8 bits: 393 us with 128 threads, 474 with 512; 16: 415 and 450; 4: 540 and 591).  Few

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(WTH, 8) void k_whist(const float *__restrict__ w, T
 {
     constexpr int Q = TILE / (4 * WTH);
     __shared__ StageShared<HIST> sm;
-    const uint32_t tile = xcd_tile(blockIdx.x);
+    const uint32_t tile = grid_tile();
     if (tile >= t.n_tiles) return;
     const uint4 d = t.desc[tile];
     const uint32_t tid = threadIdx.x, lane = tid & 63, first = d.w & 0xFFFFu, last = d.w >> 16;

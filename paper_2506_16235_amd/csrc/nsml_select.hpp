@@ -282,7 +282,7 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
 {
     __shared__ StageShared<HIST> sm;
     __shared__ double sq_w[STH / 64];
-    const uint32_t tile = xcd_tile(blockIdx.x);
+    const uint32_t tile = grid_tile();
     if (tile >= t.n_tiles) return;
     const uint4 d = t.desc[tile];
     const uint32_t tid = threadIdx.x, e = tid * 4u, first = d.w & 0xFFFFu, last = d.w >> 16;

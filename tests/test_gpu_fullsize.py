@@ -347,6 +347,7 @@ def test_accumulate_more_than_2_32_survivors():
     n = int(off[-1])
     _, K, vb, ns = nsml.payload_layout(off, 1.0, 4, 2048)
     assert K == n > 1 << 32
+    torch.cuda.empty_cache()
     if torch.cuda.mem_get_info()[0] < 100 << 30:
         pytest.skip("needs 100 GB of device memory")
     idx = torch.empty(K, dtype=torch.int32, device=DEV)
@@ -365,3 +366,49 @@ def test_accumulate_more_than_2_32_survivors():
     for b in range(len(sizes)):           # the code's place in its byte counts from the bucket's start
         x = dense[int(off[b]):int(off[b + 1])]
         assert bool((x[0::2] == 4.0).all()) and bool((x[1::2] == -1.0).all())
+
+
+def test_more_than_2_34_elements():
+    """17.2 G elements in five buckets: a thread per four elements would be 2^32 of them, more than one dimension
+    of a launch holds.  As for the largest bucket: the survivors of every bucket were planted, everything else is
+    smaller; then the payload back, over the gradient's own memory."""
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 200 << 30:
+        pytest.skip("needs 200 GB of device memory")
+    sizes = [(1 << 32) - 4096, (1 << 32) - 4096, 3, (1 << 32) - 4096, (1 << 32) - 4096, 30_000_001]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.uint64)
+    n = int(off[-1])
+    assert n > 1 << 34
+    ratio, bits = 2.0 ** -22, 8
+    k_b, K, vb, ns = nsml.payload_layout(off, ratio, bits)
+    ctx = nsml.Context(n, len(sizes), 2048, max_ratio=1e-6)
+    g = torch.empty(n, dtype=torch.float32, device=DEV)
+    for lo in range(0, n, 1 << 30):
+        g[lo:min(n, lo + (1 << 30))].uniform_(-1e-3, 1e-3)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(6)
+    want = []
+    for b, nb in enumerate(sizes):
+        k = int(k_b[b])
+        pos = torch.unique(torch.randint(0, nb, (k,), generator=gen, device=DEV))
+        while pos.numel() < k:
+            pos = torch.unique(torch.cat([pos, torch.randint(0, nb, (k - pos.numel(),), generator=gen, device=DEV)]))
+        g[pos + int(off[b])] = torch.where(torch.arange(k, device=DEV) % 2 == 0, 2.0, -2.0)
+        want.append(pos)
+    r = torch.zeros(n, dtype=torch.float32, device=DEV)
+    idx, val, sc = ctx.compress(g, r, off, ratio, bits)
+    torch.cuda.synchronize()
+    ctx.path_stats()
+    assert torch.equal(idx[:K].to(torch.int64) & 0xFFFFFFFF, torch.cat(want))
+    scale = np.float32(2.0) / np.float32(127.0)
+    assert bool((sc[:ns] == float(scale)).all())
+    at = torch.cat([p + int(off[b]) for b, p in enumerate(want)])
+    last = int(at.max()) + 1
+    assert bool(torch.equal(r[last:], g[last:]))            # nothing sent there: all of it stays
+    dense = g.fill_(7.0)
+    for variant in (-1, 0):
+        ctx.set_option("decomp_variant", variant)
+        ctx.decompress(idx, val, sc, n, off, ratio, bits, dense)
+        assert sum(int(torch.count_nonzero(dense[lo:min(n, lo + (1 << 30))])) for lo in range(0, n, 1 << 30)) == K
+        assert torch.equal(dense[at].abs(), torch.full((K,), float(np.float32(127.0) * scale), device=DEV))
+        dense.fill_(7.0)
