@@ -578,7 +578,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         default: NSML_FULL(4); break;
         }
 #undef NSML_FULL
-        LAUNCH(c, KID_PLAN, st, k_full_state, B, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
+        LAUNCHB(c, KID_PLAN, st, k_full_state, B, NHB, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
         c->have_l2 = true;
         c->have_prune = none_pruned; c->none_pruned = none_pruned;
         return NSML_OK;
