@@ -477,8 +477,8 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
  * indices, values or codes, and the coding error over the residual.  A workgroup takes tile i of a
  * bucket counted from the bucket's own start, so that chunks of 2048 / 2^x survivors (the host checks)
  * nest in tiles and a scale needs one exchange inside the workgroup.  Bound by HBM: 8 bytes read and
- * 8 + payload per element written (419 M elements, 32-bit values: 1.30 ms, 6.5 TB/s; selection, dense
- * encode and the launches between took 2.25).
+ * 8 + payload per element written (419 M elements, 32-bit values: 1.35 ms in one bucket, 1.43 in 16, 5.9 - 6.2
+ * TB/s; selection, dense encode and the launches between took 2.25).
  * By-products as from the streaming pass: |grad|^2 and the number of zeros per tile. */
 template <int BITS, bool NT>
 __global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, float *__restrict__ r, Tables t, Cand c,
@@ -577,7 +577,8 @@ __global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, fl
             }
             deq = __fmul_rn((float)q[j], scale);
         }
-        left[j] = BITS == 32 ? 0.0f : __fsub_rn(a[j], deq);        /* 32 bits: value - value, nothing is left behind */
+        left[j] = __fsub_rn(a[j], deq);        /* 32 bits: nothing is left behind (NaN where no value was) */
+
     }
     if (have == 4u) {
         const f4 rv = {left[0], left[1], left[2], left[3]}, av = {a[0], a[1], a[2], a[3]};
@@ -618,7 +619,7 @@ __global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, fl
 
 /* The per-bucket records of such a call: |grad|^2 and the selection state (threshold key 0, the zeros
  * admitted as its ties).  Bound by the latency of its loads: a thread's four at a time, 1024 threads (one bucket of
- * 419 M elements: FULL_NOW us, with 256 threads and one load at a time 228). */
+ * 419 M elements: 36 us, with 256 threads and one load at a time 228). */
 __global__ __launch_bounds__(NHB) void k_full_state(Tables t, Cand c, const double *__restrict__ tile_sq, double *__restrict__ l2sq)
 {
     __shared__ double red[NHB / 64];

@@ -903,7 +903,7 @@ __device__ __forceinline__ void write_dense_body(float *__restrict__ r, const Ta
                     const uint64_t pos = Pb + pg + min(e_b, pe);
                     idx_out[pos] = (uint32_t)(gi + j - s.lo);
                     v_out[pos] = x[u][j];
-                    if (DIRECT) r[gi + j] = 0.0f;    /* value - value: nothing is left behind */
+                    if (DIRECT) r[gi + j] = __fsub_rn(x[u][j], x[u][j]);      /* nothing is left behind (NaN where no value was) */
                 }
                 pg += isg ? 1u : 0u;
                 pe += ise ? 1u : 0u;
@@ -1253,7 +1253,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                         const float xv = sv[i];
                         const uint32_t at = si[i];
                         idx_out[Pb + Rbase + i] = at + li_base;
-                        float left = 0.0f;               /* value - value: nothing is left behind */
+                        float left = __fsub_rn(xv, xv);  /* nothing is left behind (NaN where no value was) */
                         if (BITS == 16) {
                             const __half hv = __float2half_rn(xv);
                             reinterpret_cast<__half *>(vb)[Rbase + i] = hv;

@@ -437,6 +437,33 @@ def test_decompress_accumulate(bits):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits", [32, 16])
+@pytest.mark.parametrize("ratio", [0.01, 0.4, 1.0])
+@pytest.mark.parametrize("sizes", [[1003, 20_001], [700_001, 3], [4000] * 600], ids=["small", "large", "many"])
+def test_infinities_and_nan(path, bits, ratio, sizes):
+    """Whatever the path: they are sent first, and what is left of them is value - value, no number (as the oracle
+    has it), with 32- and with 16-bit values."""
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    ctx = nsml.Context(n, len(sizes), 64)
+    g = _rand(n, 31)
+    g[5], g[6], g[900], g[n - 2] = float("inf"), float("nan"), float("-inf"), float("nan")
+    r, r_h = torch.zeros(n, device=DEV), np.zeros(n, dtype=np.float32)
+    idx, val, sc = ctx.compress(g, r, off, ratio, bits)
+    torch.cuda.synchronize()
+    ctx.path_stats()
+    _, K, vb, ns = nsml.payload_layout(off, ratio, bits, 64)
+    with np.errstate(invalid="ignore"):
+        w_idx, w_val, _ = oracle.compress(g.cpu().numpy(), r_h, off, ratio, bits, 64)
+    assert np.array_equal(idx.cpu().numpy().view(np.uint32)[:K], w_idx)
+    dt = np.float32 if bits == 32 else np.float16
+    got, want = val.cpu().numpy()[:vb].view(dt), np.asarray(w_val)[:vb].view(dt)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~np.isnan(got)], want[~np.isnan(want)])
+    left = r.cpu().numpy()
+    assert np.isnan(r_h).sum() >= 4 and np.array_equal(np.isnan(left), np.isnan(r_h))
+    assert np.array_equal(left[~np.isnan(left)].view(np.uint32), r_h[~np.isnan(r_h)].view(np.uint32))
+
+
 @pytest.mark.parametrize("rescan", [0, 1])
 @pytest.mark.parametrize("bits,where", [(8, "ties"), (4, "close"), (32, "close"), (16, "ties")])
 def test_undecided_keys_in_one_place(path, rescan, bits, where):
@@ -738,8 +765,6 @@ def test_small_buckets(path, bits, chunk, ratio):
         for a, w in zip(*out):
             assert np.array_equal(a, w)
         ra, rb = (r.cpu().numpy() for r in rs)
-        if step == 2:                                      # (32 bits: the chain leaves 0 or NaN there, by the path)
-            ra[[p + 7, p + 8, p + 4000]] = rb[[p + 7, p + 8, p + 4000]] = 0.0
         nan = np.isnan(ra)
         assert np.array_equal(nan, np.isnan(rb)) and np.array_equal(ra[~nan].view(np.uint32), rb[~nan].view(np.uint32))
         assert ctxs[0].path_stats() == ((0, 10) if path == "dense" else (10, 0))
