@@ -163,8 +163,14 @@ int nsml_destroy(nsml_ctx *ctx);
  * best; results are identical for every setting (the tests run the path under each of them).
  * Takes effect from the next call; waits for nothing.  NSML_EINVAL for an unknown name or a value
  * outside the listed range.
- *   "span_tiles" (0..16), "seg_waves" (0, 4, 8, 16), "persist" (0..8), "nt" (1, 3, 5, 7), "nt_dense"
- *                  (-1..1)  accepted, without effect: the streaming kernels have one geometry
+ *   "span_tiles"   tiles of 2048 elements per work unit of the coding of survivors taken from the dense
+ *                  accumulator: 1..16, 0 (default) = by gradient size
+ *   "seg_waves"    tiles per workgroup of the threshold search's count: 64 (16), 16 (4, 8), by gradient size
+ *                  (0, default); the next call rebuilds the layout's tables, as for another layout
+ *   "nt"           accumulator past the caches and the threshold's bins by a kernel of their own, as for large
+ *                  gradients (5, 7), into the caches (1, 3); by gradient size unless set
+ *   "nt_dense"     zeros of a sparse decompress past the caches: 1, 0, -1 (default) = by gradient size
+ *   "persist" (0..8)  accepted, without effect: a workgroup of the streaming kernels takes one tile
  *   "decomp_variant"  decompress: 1 = zeros, then the survivors stored over them, 0 = tiles assembled
  *                  in LDS, -1 (default) = by the share of survivors
  *   "force_dense"  1: decide every bucket by the dense passes over the accumulator (the path a
@@ -174,11 +180,11 @@ int nsml_destroy(nsml_ctx *ctx);
  *                  chain of kernels, 0: default
  *   "whistory"     pruning step: 1 (default) stages a narrow band of weight magnitudes around the
  *                  threshold the previous call on this context found for the bucket (weights move
- *                  little between steps; a band that misses costs a repeat of the weight pass, the
+ *                  little between steps; a bucket whose band misses takes the dense passes, the
  *                  result is the same), 0: the band always comes from a sample of the weights
  *   "wband_miss"   diagnostic: 1 places the band of weight magnitudes that the pruning step stages
- *                  beside the threshold, so that every bucket takes the repeat of the weight pass
- *                  (the path of a band that missed), 0: default
+ *                  beside the threshold, so that every bucket takes the dense passes (the path of a
+ *                  band that missed), 0: default
  *   "trip_check"   diagnostic: 1 raises the flag a failed device-side consistency check raises,
  *                  so the error reporting of the next call can be exercised without a failure */
 int nsml_set_option(nsml_ctx *ctx, const char *name, int value);

@@ -132,11 +132,15 @@ struct nsml_ctx {
     void *pinned; size_t pinned_bytes;
     int decomp_variant;    /* decompress: 1 zeros then survivors, 0 tiles assembled in LDS, -1 by the share of survivors */
     int force_dense;
+    int unit_tiles;        /* tiles per work unit of the one-pass dense encode, 0 by gradient size */
+    int sel_waves;         /* 16: 64 tiles per workgroup of k_select_count, 4, 8: 16 of them, 0 by gradient size */
+    int built_sel_waves;   /* ... when the layout tables were made */
+    int nt_acc, nt_dense;  /* accumulator / zeros of the dense output past the caches: 1, 0, -1 by size */
     bool zero_clean; uint32_t zero_B;   /* the per-call histograms and flags were left zeroed (for this many buckets) */
     int n_cu;
     int hard_occ[2];       /* workgroups of k_hard that fit a compute unit at once (short / long chunks) */
     int whistory;          /* the weight band follows the threshold of the last call (1, default) or always comes from a sample (0) */
-    int wband_miss;        /* diagnostic: the weight band is placed beside the threshold, so every bucket takes the repeat */
+    int wband_miss;        /* diagnostic: the weight band is placed beside the threshold, so every bucket takes the dense passes */
     int force_rescan;      /* diagnostic: k_select_finish in small windows; small buckets by the chain of kernels */
 
     /* profiling */
@@ -216,7 +220,7 @@ Tables tables_of(const nsml_ctx *c)
     t.ovf = hists_of(c, c->B).ovf; t.ftile0 = c->d_ftile0; t.nhard = hists_of(c, c->B).nhard;
     t.kw = c->d_kw; t.pmask = nullptr;
     t.B = c->B; t.n_tiles = c->n_tiles; t.chunk = c->chunk; t.chunkSh = chunk_shift(c->chunk);
-    t.dencTiles = denc_tiles(c->n_tiles);
+    t.dencTiles = c->unit_tiles > 0 ? (uint32_t)c->unit_tiles : denc_tiles(c->n_tiles);
     return t;
 }
 
@@ -274,7 +278,7 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
         if (off[b + 1] < off[b]) return NSML_EINVAL;
         if (off[b + 1] - off[b] > 0xFFFFFFFFull) return NSML_EINVAL;
     }
-    if (c->B == B && c->n == n && c->h_off.size() == (size_t)B + 1 &&
+    if (c->B == B && c->n == n && c->built_sel_waves == c->sel_waves && c->h_off.size() == (size_t)B + 1 &&
         memcmp(c->h_off.data(), off, sizeof(uint64_t) * ((size_t)B + 1)) == 0)
         return NSML_OK;
 
@@ -284,7 +288,7 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
     uint64_t nt = 0, nsamp = 0, nsel = 0;
     /* 64 tiles per workgroup of k_select_count once that leaves four workgroups per compute unit, else 16
      * (12 K tiles of a hundred entries: 35 us with 64, 10 with 16) */
-    const uint32_t selSh = n >= 4ull * 64ull * 256ull * TILE ? 6u : 4u;
+    const uint32_t selSh = c->sel_waves ? (c->sel_waves == 16 ? 6u : 4u) : n >= 4ull * 64ull * 256ull * TILE ? 6u : 4u;
     for (uint32_t b = 0; b < B; ++b) {
         tile0[b] = (uint32_t)nt;
         samp0[b] = (uint32_t)nsamp;
@@ -341,7 +345,7 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
     for (uint32_t b = 0; b < B; ++b) c->max_nb = off[b + 1] - off[b] > c->max_nb ? off[b + 1] - off[b] : c->max_nb;
     c->B = B; c->n = n;
     c->n_tiles = (uint32_t)nt; c->n_samp = (uint32_t)nsamp;
-    c->n_sel = (uint32_t)nsel; c->selSh = selSh;
+    c->n_sel = (uint32_t)nsel; c->selSh = selSh; c->built_sel_waves = c->sel_waves;
     return NSML_OK;
 }
 
@@ -416,6 +420,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     /* tuning switches: the measured defaults (see nsml_set_option) */
     c->zero_clean = false; c->zero_B = 0;
     c->n_cu = 256; c->decomp_variant = -1;
+    c->unit_tiles = c->sel_waves = c->built_sel_waves = 0; c->nt_acc = c->nt_dense = -1;
     c->force_dense = 0; c->force_rescan = 0; c->wband_miss = 0; c->whistory = 1;
 
     int ndev = 0;
@@ -557,12 +562,14 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     const uint32_t clear_grid = (uint32_t)((zw + WG * 8 - 1) / (WG * 8));
     float *vdst = bits == 32 ? static_cast<float *>(val) : c->d_v;
     const dim3 sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
-    const bool bins = !c->force_dense && c->n_tiles >= HIST_MAX_TILES;      /* the window's bins by a kernel of their own */
+    const bool nt = c->nt_acc < 0 ? n > NT_ELEMS : c->nt_acc != 0;
+    /* the window's bins by a kernel of their own: with many tiles, which may be those of many small buckets (and
+     * whenever the accumulator goes past the caches, which it does with more elements than so many tiles have) */
+    const bool bins = !c->force_dense && (nt || c->n_tiles >= HIST_MAX_TILES);
     /* floor(0.5 * (1 - ratio) * n_b) parameters are pruned: when that is none of any bucket (ratio 1, the
      * controller's cap), the weights decide nothing and are not read */
     const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
     if (none_pruned) weights = nullptr;
-    const bool nt = n > NT_ELEMS;
     if (c->K == n && !c->force_dense && (bits >= 16 || TILE % c->chunk == 0)) {
         /* everything is sent: nothing to select (TILE % chunk: chunks nest in tiles) */
         const bool fnt = nt && c->off_mult4 && aligned(idx, 16) && aligned(val, 16);      /* (misaligned non-temporal stores leave partly written lines) */
@@ -640,8 +647,8 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
 #define NSML_EF(EMIT_, PRUNE_, NT_, HIST_) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<EMIT_, PRUNE_, NT_, HIST_>), sgrid, STH, grad, residual, t, h.hw, cd0, c->d_tile_sq)
     if (c->force_dense) { if (nt) NSML_EF(false, false, true, false); else NSML_EF(false, false, false, false); }
-    else if (bins) { if (pruned) NSML_EF(true, true, true, false); else NSML_EF(true, false, true, false); }      /* (more tiles than that are more elements than NT_ELEMS) */
-    else if (nt) { if (pruned) NSML_EF(true, true, true, true); else NSML_EF(true, false, true, true); }
+    else if (nt) { if (pruned) NSML_EF(true, true, true, false); else NSML_EF(true, false, true, false); }
+    else if (bins) { if (pruned) NSML_EF(true, true, false, false); else NSML_EF(true, false, false, false); }
     else { if (pruned) NSML_EF(true, true, false, true); else NSML_EF(true, false, false, true); }
 #undef NSML_EF
     if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, (const float *)residual);
@@ -759,13 +766,13 @@ static ScatterGrid scatter_grid(uint64_t K, uint64_t n, bool add)
 static bool tilestart_by_search(uint64_t K, uint32_t n_tiles) { return K >= 32ull * n_tiles; }      /* many survivors per tile */
 template <typename MAP>
 static int launch_decompress(nsml_ctx *c, hipStream_t st, const Tables &t, uint64_t n, uint64_t K, const MAP *tile_b, uint32_t *d_ts,
-                             const uint32_t *idx, const void *val, const float *scales, int bits, float *dense_out, int variant, bool starts_done = false)
+                             const uint32_t *idx, const void *val, const float *scales, int bits, float *dense_out, int variant, int nt_zero, bool starts_done = false)
 {
     const uint32_t n_tiles = t.n_tiles;
     if (decomp_by_scatter(variant, K, n)) {
         /* few survivors: zeros at the speed of a fill, then the survivors stored over them */
         const dim3 zgrid = xcd_grid((n + ZERO_T * 4 - 1) / (ZERO_T * 4));
-        if (n > NT_ELEMS) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
+        if (nt_zero < 0 ? n > NT_ELEMS : nt_zero != 0) LAUNCHB(c, KID_DECOMP, st, k_zero<true>, zgrid, ZERO_T, dense_out, n);
         else LAUNCHB(c, KID_DECOMP, st, k_zero<false>, zgrid, ZERO_T, dense_out, n);
         const ScatterGrid sg = scatter_grid(K, n, false);
         switch (bits) {
@@ -836,7 +843,7 @@ int nsml_decompress(nsml_ctx *c, const uint32_t *idx, const void *val, const flo
     if (rc) return rc;
     rc = ensure_tables(c, ratio, bits, st);
     if (rc) return rc;
-    return launch_decompress<uint32_t>(c, st, tables_of(c), c->n, c->K, c->d_tile_b, c->d_ts, idx, val, scales, bits, dense_out, c->decomp_variant);
+    return launch_decompress<uint32_t>(c, st, tables_of(c), c->n, c->K, c->d_tile_b, c->d_ts, idx, val, scales, bits, dense_out, c->decomp_variant, c->nt_dense);
 }
 
 /* ---------------------------------------------------------------- no-allocation decompress */
@@ -966,7 +973,7 @@ int nsml_decompress_static(const uint32_t *idx, const void *val, const float *sc
     const uint64_t tgrid = (nt + WG - 1) / WG, wgrid = walk ? (K + WG * 2 - 1) / (WG * 2) : 1u;
     LAUNCH(none, KID_SETUP, st, k_static_setup, (uint32_t)std::min<uint64_t>(1024, std::max(tgrid, wgrid)), so, t, m.off, m.tile0, ratio, bits, m.tile_b,
            idx, K, m.ts, walk, find);
-    return launch_decompress<uint16_t>(none, st, t, n, K, m.tile_b, m.ts, idx, val, scales, bits, dense_out, -1, true);
+    return launch_decompress<uint16_t>(none, st, t, n, K, m.tile_b, m.ts, idx, val, scales, bits, dense_out, -1, -1, true);
 }
 
 int nsml_decompress_accumulate(nsml_ctx *c, const uint32_t *idx, const void *val, const float *scales,
@@ -1106,15 +1113,19 @@ int nsml_set_option(nsml_ctx *c, const char *name, int value)
 {
     if (!c || !name) return NSML_EINVAL;
     auto is = [&](const char *s) { return strcmp(name, s) == 0; };
-    if (is("span_tiles")) {                    /* this one and the next four: accepted, without effect */
+    if (is("span_tiles")) {
         if (value < 0 || value > 16) return NSML_EINVAL;
+        c->unit_tiles = value;
     } else if (is("seg_waves")) {
         if (value != 0 && value != 4 && value != 8 && value != 16) return NSML_EINVAL;
+        c->sel_waves = value;
     } else if (is("nt")) {
         if (value != 1 && value != 3 && value != 5 && value != 7) return NSML_EINVAL;
+        c->nt_acc = (value & 4) != 0;
     } else if (is("nt_dense")) {
         if (value < -1 || value > 1) return NSML_EINVAL;
-    } else if (is("persist")) {
+        c->nt_dense = value;
+    } else if (is("persist")) {                /* accepted, without effect: a workgroup takes one tile */
         if (value < 0 || value > 8) return NSML_EINVAL;
     } else if (is("decomp_variant")) {
         if (value < -1 || value > 1) return NSML_EINVAL;

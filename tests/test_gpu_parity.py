@@ -437,6 +437,57 @@ def test_decompress_accumulate(bits):
     assert np.array_equal(dense.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+@pytest.mark.parametrize("bits,chunk", [(4, 2048), (8, 64), (8, 2048), (16, 24), (32, 256)])
+@pytest.mark.parametrize("sizes", [[40_000, 4, 0, 300_000, 65_536, 1 << 20], [40_001, 3, 0, 300_002, 65_537, (1 << 20) + 1]],
+                         ids=["starts_mod4_0", "odd_starts"])
+def test_route_of_large_gradients_on_a_small_one(path, monkeypatch, sizes, bits, chunk):
+    """What is chosen by size alone from 33 M elements up, forced: the accumulator and the zeros past the caches, the
+    bins by a kernel of their own, 64 tiles per workgroup of the count, units of 16 tiles; candidates, a band, zeros
+    to be sent, overflowed segments, everything sent (into aligned buffers, and 4 bytes off), few survivors scattered."""
+    for k, v in (("nt", 7), ("nt_dense", 1), ("seg_waves", 16), ("span_tiles", 16)):
+        monkeypatch.setitem(nsml.Context.default_options, k, v)
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    g = _rand(n, 51)
+    g[5_000:9_000] = torch.round(g[5_000:9_000] * 2e3) / 2e3          # plateaus of equal magnitudes
+    c = Case(g, off, chunk=chunk)
+    c.step(0.02, bits)
+    c.set_grad(_rand(n, 52))
+    c.step(0.001, bits)
+    g = _rand(n, 53)
+    g[100_000:109_000] *= 50.0                                        # whole tiles of survivors
+    c.set_grad(g)
+    c.step(0.03, bits)
+    c.set_grad(_rand(n, 54))
+    c.step(0.3, bits)
+    g = _rand(n, 55)
+    g[torch.rand(n, device=DEV, generator=torch.Generator(device=DEV).manual_seed(5)) < 0.7] = 0.0
+    c.set_residual(np.zeros(n, dtype=np.float32))
+    c.set_grad(g)
+    c.step(0.45, bits)
+    c.set_grad(_rand(n, 56))
+    c.step(1.0, bits)
+    _, K, vb, ns = nsml.payload_layout(off, 1.0, bits, chunk)
+    idx = torch.empty(K + 1, dtype=torch.int32, device=DEV)[1:]
+    val = torch.empty((vb + 7) // 4 * 4 + 4, dtype=torch.uint8, device=DEV)[4:]
+    sc = torch.empty(max(ns, 1), dtype=torch.float32, device=DEV)
+    c.ctx.compress(c.g, c.r, off, 1.0, bits, idx, val, sc)
+    torch.cuda.synchronize()
+    want = oracle.compress(c.g_host, c.r_host, off, 1.0, bits, chunk)
+    compare_payload(off, 1.0, bits, chunk, (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns]), want)
+
+
+@pytest.mark.parametrize("ratio", [0.02, 0.3])
+def test_many_small_buckets(path, ratio):
+    """17000 buckets: more tiles than the streaming pass counts bins for, in an array that fits the caches."""
+    rng = np.random.default_rng(3)
+    off = W.offsets_of([int(x) for x in rng.integers(1, 90, size=17_000)])
+    c = Case(_rand(int(off[-1]), 8), off, chunk=64)
+    c.step(ratio, 8)
+    c.set_grad(_rand(int(off[-1]), 9))
+    c.step(ratio, 32)
+
+
 @pytest.mark.parametrize("bits", [32, 16])
 @pytest.mark.parametrize("ratio", [0.01, 0.4, 1.0])
 @pytest.mark.parametrize("sizes", [[1003, 20_001], [700_001, 3], [4000] * 600], ids=["small", "large", "many"])
@@ -731,8 +782,10 @@ def test_static_setup(B, ratio):
     nsml.decompress_static(idx, val, sc, n, off, ratio, 4, 256, out)
     torch.cuda.synchronize()
     assert torch.equal(out.view(torch.int32), want.view(torch.int32))
-    nsml.decompress_static(idx.flip(0).contiguous(), val, sc, n, off, ratio, 4, 256, out)      # refused nowhere, wrong nowhere else
+    pad = torch.full((n + 16384,), 7.0, device=DEV)          # indices in the wrong order: values unspecified, nothing outside
+    nsml.decompress_static(idx.flip(0).contiguous(), val, sc, n, off, ratio, 4, 256, pad[8192:8192 + n])
     torch.cuda.synchronize()
+    assert bool((pad[:8192] == 7.0).all()) and bool((pad[8192 + n:] == 7.0).all())
 
 
 @pytest.mark.parametrize("bits,chunk", [(32, 256), (16, 24), (8, 8), (8, 24), (8, 4096), (4, 256), (4, 40)])

@@ -126,3 +126,14 @@ def test_clustered_survivors_with_pruning():
 
 def test_large_single_bucket():
     _run([5_000_000], 0.01, 8, 2048, steps=2)
+
+
+@pytest.mark.parametrize("seg_waves", [4, 16])
+def test_pruning_by_the_route_of_large_gradients(monkeypatch, seg_waves):
+    """The window's bins of weights and gradient by a kernel of their own, overflowed segments among them (read from
+    the dense accumulator, minus the pruned parameters), forced on small gradients."""
+    monkeypatch.setitem(nsml.Context.default_options, "nt", 7)
+    monkeypatch.setitem(nsml.Context.default_options, "seg_waves", seg_waves)
+    test_clustered_survivors_with_pruning()
+    _run([1, 70, 4095, 0, 300_003, 65_537, 900_001], 0.01, 8, 64, steps=3, seed=5)
+    _run([300_003, 65_537], 0.3, 32, 64, steps=2, ties=True, seed=6)

@@ -21,7 +21,7 @@ def _case(seed, pruned, monkeypatch):
     rs.choice([0, 4, 16, 64])                 # (keeps the stream of the later draws as it was)
     for k, v in (("span_tiles", st), ("seg_waves", sw)):
         monkeypatch.setitem(nsml.Context.default_options, k, v)
-    rs.randint(0, 2)                          # (keeps the stream of the later draws as it was)
+    monkeypatch.setitem(nsml.Context.default_options, "nt", int(rs.randint(0, 2)) * 4 + 3)
     monkeypatch.setitem(nsml.Context.default_options, "force_dense", 1 if rs.rand() < 0.15 else 0)
     monkeypatch.setitem(nsml.Context.default_options, "rescan", 1 if rs.rand() < 0.25 else 0)
     B = int(rs.randint(1, 9))
