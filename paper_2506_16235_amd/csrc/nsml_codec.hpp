@@ -618,17 +618,20 @@ __global__ __launch_bounds__(STH, 8) void k_full(const float *__restrict__ g, fl
 }
 
 /* The per-bucket records of such a call: |grad|^2 and the selection state (threshold key 0, the zeros
- * admitted as its ties).  Bound by the latency of its loads: a thread's four at a time, 1024 threads (one bucket of
- * 419 M elements: 36 us, with 256 threads and one load at a time 228). */
-__global__ __launch_bounds__(NHB) void k_full_state(Tables t, Cand c, const double *__restrict__ tile_sq, double *__restrict__ l2sq)
+ * admitted as its ties).  Bound by the latency of its loads: a thread's four at a time, 1024 threads for buckets of
+ * more than STATE_BIG elements (one of 419 M: 36 us, with 256 threads and one load at a time 228), 256 otherwise (20000 of
+ * 100: 1024 threads add 50 us). */
+constexpr uint64_t STATE_BIG = 1ull << 22;
+template <uint32_t NT>
+__global__ __launch_bounds__(NT) void k_full_state(Tables t, Cand c, const double *__restrict__ tile_sq, double *__restrict__ l2sq)
 {
-    __shared__ double red[NHB / 64];
-    __shared__ uint32_t redz[NHB / 64];
+    __shared__ double red[NT / 64];
+    __shared__ uint32_t redz[NT / 64];
     const uint32_t b = blockIdx.x, tid = threadIdx.x, t1 = t.tile0[b + 1];
     double acc = 0.0;
     uint32_t z = 0;
 #pragma unroll 4
-    for (uint32_t s = t.tile0[b] + tid; s < t1; s += NHB) { acc += tile_sq[s]; z += c.E[s]; }
+    for (uint32_t s = t.tile0[b] + tid; s < t1; s += NT) { acc += tile_sq[s]; z += c.E[s]; }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) { acc += __shfl_xor(acc, d, 64); z += __shfl_xor(z, d, 64); }
     if ((tid & 63) == 0) { red[tid >> 6] = acc; redz[tid >> 6] = z; }
@@ -637,7 +640,7 @@ __global__ __launch_bounds__(NHB) void k_full_state(Tables t, Cand c, const doub
     const bool empty = t.k[b] == 0u;
     double tot = 0.0;
     uint32_t zeros = 0;
-    for (uint32_t w = 0; w < NHB / 64; w += 4) {
+    for (uint32_t w = 0; w < NT / 64; w += 4) {
         tot += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
         zeros += (redz[w] + redz[w + 1]) + (redz[w + 2] + redz[w + 3]);
     }

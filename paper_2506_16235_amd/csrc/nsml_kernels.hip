@@ -585,7 +585,8 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         default: NSML_FULL(4); break;
         }
 #undef NSML_FULL
-        LAUNCHB(c, KID_PLAN, st, k_full_state, B, NHB, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
+        if (c->max_nb > STATE_BIG) LAUNCHB(c, KID_PLAN, st, k_full_state<1024>, B, 1024, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
+        else LAUNCHB(c, KID_PLAN, st, k_full_state<256>, B, 256, t, cd0, (const double *)c->d_tile_sq, c->d_l2sq);
         c->have_l2 = true;
         c->have_prune = none_pruned; c->none_pruned = none_pruned;
         return NSML_OK;
