@@ -32,11 +32,19 @@ constexpr uint32_t XCD_RUN = 16;  /* consecutive tiles per die, see xcd_tile */
 constexpr uint32_t SEG_CAP = TILE / 4;      /* staging entries per tile: a quarter of its elements */
 constexpr uint32_t SELC_SEGS = 64;          /* most segments per workgroup of k_select_count: one per lane */
 /* The undecided keys of a bucket, from list_base on: OWN_PER_SEG words per segment that belong to the workgroup of
- * k_select_count that counts it, then list_room words for the workgroups that have more than that. */
-constexpr uint32_t LIST_PER_SEG = 64, OWN_PER_SEG = 16;
-constexpr uint32_t LCAP = SELC_SEGS * LIST_PER_SEG;        /* what a workgroup of k_select_count collects in LDS */
+ * k_select_count that counts it, then list_room words for the workgroups that have more than that (a third of
+ * what a segment stages, so that ties of several per cent of a bucket still fit). */
+constexpr uint32_t LIST_PER_SEG = 192, OWN_PER_SEG = 16;
+constexpr uint32_t LCAP = 4096;            /* what a workgroup of k_select_count collects in LDS; a bucket's room has so many more */
 __host__ __device__ inline uint64_t list_base(uint32_t tile0, uint32_t b) { return (uint64_t)tile0 * LIST_PER_SEG + (uint64_t)b * LCAP; }
 __host__ __device__ inline uint64_t list_room(uint32_t segs) { return (uint64_t)segs * (LIST_PER_SEG - OWN_PER_SEG) + LCAP; }
+/* Whether `at` undecided keys of a bucket of `segs` segments are searched in its list, or by the dense passes: they
+ * have to fit, and one workgroup takes about 1 ns for each (a whole chip's worth of buckets at the same time) where
+ * the dense passes take 27 ns for a segment's share of all steps and 60 us for their barriers. */
+__device__ __forceinline__ bool list_pays(uint32_t at, uint32_t segs, uint32_t n_tiles)
+{
+    return at <= list_room(segs) && at <= 65536u + 24ull * n_tiles;
+}
 constexpr int NB0 = 4096, NB1 = 4096, NB2 = 128;
 constexpr int NHB = 1024;         /* bins of the window of keys in which the threshold is expected */
 constexpr uint32_t NHC = 8;       /* copies of a bucket's bins, one per die's share of the workgroups: with one copy the streaming pass

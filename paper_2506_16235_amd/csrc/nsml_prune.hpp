@@ -189,7 +189,7 @@ __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ 
     t.T[b] = known ? top - res[0] : 0u;
     t.need[b] = known ? want - res[1] : want;
     t.sh[b] = known ? p.w : SH_NONE;
-    if (known && !ovf && res[2] <= list_room(t.tile0[b + 1] - t.tile0[b])) {
+    if (known && !ovf && list_pays(res[2], t.tile0[b + 1] - t.tile0[b], t.n_tiles)) {
         t.fast[b] = PATH_BAND;
     } else {
         t.fast[b] = PATH_DENSE;

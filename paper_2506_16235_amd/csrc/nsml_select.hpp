@@ -107,58 +107,66 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
      * ones the pruning step kept */
     const double pop = t.pmask ? (double)t.kw[b] : (double)nb;
     const double ks = (double)k * (double)m / pop;
-    /* the margin: four standard deviations of a binomial sample, times what the bucket has
-     * learned (a sample of runs of a gradient whose large values come in runs has far
-     * fewer independent draws than entries; a bucket whose guess missed widens its margin) */
-    const double widen = (double)(t.margin[b] & 0xFFu ? t.margin[b] & 0xFFu : 1u);
-    const double dev = exact ? 0.0 : (4.0 * sqrt(ks) + 4.0) * widen;
-    const double want_d = exact ? (double)k : ceil(ks + dev);
     const double cap_b = (double)(t.tile0[b + 1] - t.tile0[b]) * (double)SEG_CAP;
     auto clip = [&](double x) { return x < 1.0 ? 1.0 : (x > (double)m ? (double)m : x); };
-    const double r_up = clip(floor(ks - dev)), r_dn = clip(ceil(ks + dev)), r_top = clip(floor(ks - 2.0 * dev));
-    const double r_c = clip(want_d);
-    uint32_t digit, above, at;
-    if (w.find((uint32_t)r_c, digit, above, at)) { res[0] = digit; res[1] = above; res[2] = at; }
-    if (w.find((uint32_t)r_up, digit, above, at)) { res[3] = digit; res[4] = above; res[5] = at; }
-    if (w.find((uint32_t)r_dn, digit, above, at)) { res[6] = digit; res[7] = above; res[8] = at; }
-    if (w.find((uint32_t)r_top, digit, above, at)) res[9] = digit;
-    wg_sync();
-    if (tid != 0) return;
-    KeyPar p = nothing;
-    bool done = false;
-    if (want_d <= (double)m && (double)k <= 0.5 * cap_b) {
-        const double est = (double)(res[1] + res[2]) * pop / (double)m;
-        if (est <= 0.8 * cap_b) {
-            p.x = res[0] << SH0;
-            p.z = (max(res[9], res[0]) + 1u) << SH0;
-            p.w = window_shift(p.x, p.z);
-            done = true;
-        }
-    }
-    if (!done) {
-        const uint32_t dig_up = res[3], dig_dn = res[6];
-        if (dig_up == 0u) {
-            p = make_uint4(1u, 1u, 1u, SH1);
-        } else {
-            /* a pessimistic rank among the zeros (digit 0) while the optimistic one is not: the band
-             * starts at key 1, zeros are only counted, and the plan decides between a zero
-             * threshold and one inside the band */
-            const double in_band = (double)res[7] + (dig_dn != 0u ? (double)res[8] : 0.0) - (double)res[4];
-            const double est = in_band * pop / (double)m;
+    /* the margin: four standard deviations of a binomial sample, times what the bucket has
+     * learned (a sample of runs of a gradient whose large values come in runs has far
+     * fewer independent draws than entries; a bucket whose guess missed widens its margin).  Where so wide a margin
+     * leaves nothing that can be staged, half of it is tried, down to the plain one (a bucket that had once missed
+     * was on the dense passes for 64 calls: 25 M elements at 0.8 500 us a call, so 285). */
+    uint32_t widen = t.margin[b] & 0xFFu ? t.margin[b] & 0xFFu : 1u;
+    while (true) {
+        const double dev = exact ? 0.0 : (4.0 * sqrt(ks) + 4.0) * (double)widen;
+        const double want_d = exact ? (double)k : ceil(ks + dev);
+        const double r_up = clip(floor(ks - dev)), r_dn = clip(ceil(ks + dev)), r_top = clip(floor(ks - 2.0 * dev));
+        const double r_c = clip(want_d);
+        uint32_t digit, above, at;
+        if (w.find((uint32_t)r_c, digit, above, at)) { res[0] = digit; res[1] = above; res[2] = at; }
+        if (w.find((uint32_t)r_up, digit, above, at)) { res[3] = digit; res[4] = above; res[5] = at; }
+        if (w.find((uint32_t)r_dn, digit, above, at)) { res[6] = digit; res[7] = above; res[8] = at; }
+        if (w.find((uint32_t)r_top, digit, above, at)) res[9] = digit;
+        wg_sync();
+        /* every thread comes to the same p */
+        KeyPar p = nothing;
+        bool done = false;
+        if (want_d <= (double)m && (double)k <= 0.5 * cap_b) {
+            const double est = (double)(res[1] + res[2]) * pop / (double)m;
             if (est <= 0.8 * cap_b) {
-                p.x = dig_dn != 0u ? dig_dn << SH0 : 1u;
-                p.y = p.z = (dig_up + 1u) << SH0;
+                p.x = res[0] << SH0;
+                p.z = (max(res[9], res[0]) + 1u) << SH0;
                 p.w = window_shift(p.x, p.z);
-            } else if (exact) {
-                /* too many keys in one digit to stage them, but all of the bucket was sampled: the dense passes
-                 * need not look for that digit again */
-                p.w = SH0;
-                t.T[b] = res[0];
-                t.need[b] = k - res[1];
+                done = true;
             }
         }
+        if (!done) {
+            const uint32_t dig_up = res[3], dig_dn = res[6];
+            if (dig_up == 0u) {
+                p = make_uint4(1u, 1u, 1u, SH1);
+            } else {
+                /* a pessimistic rank among the zeros (digit 0) while the optimistic one is not: the band
+                 * starts at key 1, zeros are only counted, and the plan decides between a zero
+                 * threshold and one inside the band */
+                const double in_band = (double)res[7] + (dig_dn != 0u ? (double)res[8] : 0.0) - (double)res[4];
+                const double est = in_band * pop / (double)m;
+                if (est <= 0.8 * cap_b) {
+                    p.x = dig_dn != 0u ? dig_dn << SH0 : 1u;
+                    p.y = p.z = (dig_up + 1u) << SH0;
+                    p.w = window_shift(p.x, p.z);
+                } else if (exact) {
+                    /* too many keys in one digit to stage them, but all of the bucket was sampled: the dense passes
+                     * need not look for that digit again */
+                    p.w = SH0;
+                    if (tid == 0) { t.T[b] = res[0]; t.need[b] = k - res[1]; }
+                }
+            }
+        }
+        if (p.x != NONE || exact || widen == 1u) {
+            if (tid == 0) t.par[b] = p;
+            return;
+        }
+        widen >>= 1;
+        wg_sync();                                       /* res is written again */
     }
-    t.par[b] = p;
 }
 
 /* ------------------------------------------------------------------ the streaming pass */
@@ -426,7 +434,7 @@ __global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ h
         if (bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin) why = WHY_OUTSIDE_BAND;    /* the open last bin */
         else {
             T = top - bin; need = want - res[1]; sh = p.w;
-            if (at > list_room(t.tile0[b + 1] - t.tile0[b])) why = WHY_NO_ROOM;       /* (the dense passes go on from that bin) */
+            if (!list_pays(at, t.tile0[b + 1] - t.tile0[b], t.n_tiles)) why = WHY_NO_ROOM;       /* (the dense passes go on from that bin) */
             else path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND;
         }
     } else why = n_hi < want ? WHY_TOO_FEW : WHY_OUTSIDE_BAND;

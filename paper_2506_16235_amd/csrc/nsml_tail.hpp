@@ -542,12 +542,29 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
         uint64_t tot64;
         const uint32_t incl = (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)mine.y, tmp, tot64);      /* (the window before has been consumed, too) */
         if (tid < wn) { upre[tid] = incl - mine.y; upos[tid] = mine.x; }
+        if (tid == 0) upre[wn] = (uint32_t)tot64;
         wg_sync();
         return (uint32_t)tot64;
     };
     /* f(i, entry, segment number inside the window) for the n keys of the window */
     auto for_keys = [&](uint32_t w0, uint32_t n, auto f) {
         const uint32_t wn = min(wun, nun - w0);
+        if (n >= 128u * wn) {
+            /* long parts (many ties): a wavefront each, no search for a key's part */
+#pragma unroll 1
+            for (uint32_t q = tid >> 6; q < wn; q += SEL_WAVES) {
+                const uint32_t i1 = upre[q + 1], shift = upos[q] - upre[q];
+#pragma unroll 1
+                for (uint32_t i0 = upre[q] + (tid & 63u); i0 < i1; i0 += 4 * 64) {
+                    uint32_t e[4];
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) { const uint32_t i = i0 + u * 64; e[u] = i < i1 ? list[shift + i] : 0u; }
+#pragma unroll
+                    for (uint32_t u = 0; u < 4; ++u) { const uint32_t i = i0 + u * 64; if (i < i1) f(i, e[u], (q << selSh) + (e[u] >> SH0)); }
+                }
+            }
+            return;
+        }
 #pragma unroll 1
         for (uint32_t i0 = tid; i0 < n; i0 += 4 * SEL_THREADS) {
             uint32_t e[4], un[4];
