@@ -138,9 +138,9 @@ typedef struct nsml_ctx nsml_ctx;
 
 /* Allocate a context and its device workspace on GPU `device` for gradients of up to max_n
  * elements in up to max_buckets buckets, quantized in chunks of `chunk` survivors (2048 in
- * the benchmark configurations; a positive multiple of 8).  Workspace: about 6.3 bytes per
- * element of max_n (4 for survivor values at ratio 1, 2 for the staging segments, 0.3 for the
- * lists of undecided keys, the pruning bitmap and the per-tile tables) plus 200 KiB per bucket.  NSML_EHIP if the device or its memory is not
+ * the benchmark configurations; a positive multiple of 8).  Workspace: about 6.5 bytes per
+ * element of max_n (4 for survivor values at ratio 1, 2 for the staging segments, 0.4 for the
+ * lists of undecided keys, 0.15 for the pruning bitmap and the per-tile tables) plus 110 KiB per bucket.  NSML_EHIP if the device or its memory is not
  * available (there is no CPU fallback).
  * A context serialises nothing itself: its calls share the workspace and the cached tables, so
  * they must not overlap, neither from several host threads nor on different streams (use one
@@ -153,7 +153,7 @@ typedef struct nsml_ctx nsml_ctx;
 int nsml_create(nsml_ctx **ctx, int device, uint64_t max_n, uint32_t max_buckets, uint32_t chunk);
 /* As nsml_create for callers that never exceed a ratio: the buffer of survivor values is sized
  * for max_ratio in (0, 1] instead of 1 (nsml_create is nsml_create_ex with max_ratio = 1), which
- * brings the workspace to about 2.3 + 4 * max_ratio bytes per element.  A compress call with a
+ * brings the workspace to about 2.5 + 4 * max_ratio bytes per element.  A compress call with a
  * larger ratio returns NSML_ECAP. */
 int nsml_create_ex(nsml_ctx **ctx, int device, uint64_t max_n, uint32_t max_buckets, uint32_t chunk,
                    double max_ratio);
@@ -221,8 +221,9 @@ int nsml_compress(nsml_ctx *ctx, const float *grad, float *residual, uint64_t n,
  * survivors are chosen among the kept parameters only.  Pruning is not permanent: a pruned
  * parameter's accumulated gradient is written to the residual like any other unsent element
  * and competes again in later steps.  Outputs, payload layout and errors as nsml_compress.
- * Costs about two extra reads of `weights` per call (five for a bucket in which a huge group
- * of equal weights surrounds the pruning threshold). */
+ * Costs one extra read of `weights` per call and a sample of them (four or five for a bucket that
+ * takes the dense passes: a band that missed, a huge group of equal weights around the pruning
+ * threshold); nothing where the ratio prunes no parameter of any bucket. */
 int nsml_compress_pruned(nsml_ctx *ctx, const float *grad, float *residual, const float *weights,
                          uint64_t n, const uint64_t *bucket_off, uint32_t B, double ratio,
                          int bits, uint32_t *idx, void *val, float *scales, void *stream);
@@ -291,7 +292,7 @@ int nsml_path_stats(nsml_ctx *ctx, uint32_t *fast_buckets, uint32_t *fallback_bu
  * words to out8 (host): how it was decided (0 dense passes, 1 candidates, 2 band, 3 zero
  * threshold), why the dense passes were taken (bits: 1 the sample gave no usable guess, 2 not
  * used (a staging segment that overflows is read from the dense accumulator instead), 4 fewer
- * staged elements than k, 8 no room for the undecided keys,
+ * staged elements than k, 8 too many undecided keys for the bucket's list,
  * 16 the threshold lies outside the staged band, 32 more non-zero elements than k in zero mode),
  * the staged key range [L, H) (0xFFFFFFFF: none / no upper bound), the threshold key, the number
  * of admitted elements equal to it, the bit position the threshold was known to before the

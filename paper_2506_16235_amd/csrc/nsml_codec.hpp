@@ -74,9 +74,7 @@ __device__ __forceinline__ void quant_wave(const float *__restrict__ v, const ui
                 if (hh >= have) continue;
                 const float xv = x[q][u][hh];
                 float deq;
-                if (BITS == 32) {
-                    deq = xv;
-                } else if (BITS == 16) {
+                if (BITS == 16) {
                     const __half hv = __float2half_rn(xv);
                     reinterpret_cast<__half *>(vb)[j0[q] + i0 + hh] = hv;
                     deq = __half2float(hv);
@@ -176,9 +174,7 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
                 if (hh >= have) continue;
                 const float xv = x[u][hh];
                 float deq;
-                if (BITS == 32) {
-                    deq = xv;
-                } else if (BITS == 16) {
+                if (BITS == 16) {
                     const __half hv = __float2half_rn(xv);
                     reinterpret_cast<__half *>(vb)[j0 + i0 + hh] = hv;
                     deq = __half2float(hv);

@@ -282,7 +282,7 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
  * is accumulated locally; the add is that), the counts and bins of the keys, and the staged
  * elements.  Bound by HBM: 12 bytes per element plus 8 per staged one.  One tile per workgroup, four
  * workgroups per compute unit: 1.68 G elements in 3.1 ms (6.5 TB/s; workgroups that walked 8 tiles with
- * a contiguous 16 KiB per wavefront and a 4096-bin histogram took 3.46 ms), 25.6 M in 52 us (68). */
+ * a contiguous 16 KiB per wavefront and a 4096-bin histogram took 3.46 ms), 25.6 M in 64 us (75). */
 template <bool EMIT, bool PRUNE, bool NT, bool HIST>
 __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g, float *__restrict__ r,
                                                     Tables t, uint32_t *__restrict__ hist, Cand c,

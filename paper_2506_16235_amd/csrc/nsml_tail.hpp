@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
  * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
  * those afterwards (same test, see chunk_coded_by_stream).  16-bit values need no chunk and are
  * all coded here. */
-/* What bounds it: half of 419 M elements sent as 8-bit codes take 956 us; without the scattered residual
+/* What bounds it: half of 419 M elements sent as 8-bit codes take 860 - 960 us, by box; without the scattered residual
  * 680, without any store 690, so the steps' chain of barriers and the instructions between them (59 per element
  * before the counts came from comparison masks and the codes from a product, 37 now) come first.  Was 1010 with four
  * wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
@@ -1595,9 +1595,9 @@ __device__ __forceinline__ void mask_dense_body(const float *__restrict__ w, con
     }
 }
 
-/* The weight buckets on the dense passes (no usable band, or a band that missed twice over), in
- * one launch of a small resident grid with barriers between the steps, like k_hard: spans,
- * level-1 histogram of |w|, digit, level-2 histogram, digit, counts per segment, prefixes,
+/* The weight buckets on the dense passes (no usable band, a band that missed or overflowed), in
+ * one launch of a small resident grid with barriers between the steps, like k_hard: list of tiles,
+ * up to three histograms of |w| and their digits, counts per segment, prefixes,
  * bitmap.  Leaves at once when there is no such bucket. */
 __global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
                                               uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
