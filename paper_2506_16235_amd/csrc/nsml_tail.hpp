@@ -490,7 +490,7 @@ __device__ __forceinline__ void add_shared(uint32_t *h, uint32_t at, uint32_t ad
  * the tie allowance e from the bucket's undecided keys (12 + 7 remaining bits, histograms in LDS),
  * then every segment's place in the survivor order.  The keys are read once per step, four per thread in
  * flight, and kept in LDS when they fit.  A bucket of more than FIN_MAX_SEGS segments goes through every step
- * in windows of so many, a range of the list's parts each (110 M elements in one bucket, 0.1 %: 77 us; by one
+ * in windows of so many, a range of the list's parts each (110 M elements in one bucket, 0.1 %: 93 us; by one
  * thread per segment 264).  PATH_ZERO buckets arrive with T = 0 and e known and only get the
  * prefixes.  in_windows: diagnostic, windows of two parts and nothing kept in LDS. */
 __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c, const uint32_t *__restrict__ sel0, uint32_t selSh,
