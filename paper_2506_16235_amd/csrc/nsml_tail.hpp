@@ -1041,7 +1041,7 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
  * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
  * those afterwards (same test, see chunk_coded_by_stream).  16-bit values need no chunk and are
  * all coded here. */
-/* What bounds it: half of 419 M elements sent as 8-bit codes take 860 - 960 us, by box; without the scattered residual
+/* What bounds it: half of 419 M elements sent as 8-bit codes take 860 - 960 us, from one machine to another; without the scattered residual
  * 680, without any store 690, so the steps' chain of barriers and the instructions between them (59 per element
  * before the counts came from comparison masks and the codes from a product, 37 now) come first.  Was 1010 with four
  * wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
