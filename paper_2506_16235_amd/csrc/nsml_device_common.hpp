@@ -263,12 +263,12 @@ __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t x)
 
 /* k_b and the prefix tables of (ratio, bits, chunk) by one workgroup: each(b, n_b, k_b, P, V, C, tile0)
  * for every bucket, and once more with b == B and the totals.  off_at(b) is where bucket b starts. */
-template <typename OFF, typename EACH>
+template <uint32_t NT, typename OFF, typename EACH>
 __device__ __forceinline__ void setup_body(uint32_t B, uint32_t chunk, double ratio, int bits, OFF off_at, EACH each)
 {
-    __shared__ uint64_t part[4][WG / 64];
+    __shared__ uint64_t part[4][NT / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint32_t per = (B + WG - 1) / WG;
+    const uint32_t per = (B + NT - 1) / NT;
     const uint32_t b0 = min(B, tid * per), b1 = min(B, b0 + per);
     auto sizes = [&](uint32_t b, uint64_t &nb, uint64_t (&x)[4]) {
         const uint64_t lo = off_at(b), hi = off_at(b + 1);
@@ -302,15 +302,19 @@ __device__ __forceinline__ void setup_body(uint32_t B, uint32_t chunk, double ra
         if (b == B - 1) each(B, 0ull, 0ull, run[0], run[1], run[2], run[3]);
     }
 }
+/* Algorithm 2 Step 2: floor(0.5 * (1 - ratio) * n_b) parameters are pruned, the others kept */
+__device__ __forceinline__ uint32_t kept_dev(double ratio, uint64_t nb)
+{
+    const double np = floor(0.5 * (1.0 - ratio) * (double)nb);
+    return (uint32_t)(nb - (uint64_t)(np < 0.0 ? 0.0 : np));
+}
 __device__ __forceinline__ void setup_store(const Tables &t, double ratio, int bits, uint32_t b, uint64_t nb, uint64_t k,
                                             uint64_t P, uint64_t V, uint64_t C)
 {
     t.P[b] = P; t.V[b] = V; t.S[b] = bits <= 8 ? C : 0u; t.C[b] = C;
     if (b == t.B) return;
     t.k[b] = (uint32_t)k;
-    /* Algorithm 2 Step 2: floor(0.5 * (1 - ratio) * n_b) parameters are pruned */
-    const double np = floor(0.5 * (1.0 - ratio) * (double)nb);
-    t.kw[b] = (uint32_t)(nb - (uint64_t)(np < 0.0 ? 0.0 : np));
+    t.kw[b] = kept_dev(ratio, nb);
 }
 
 /* The tables of a (ratio, bits), and the bucket of every chunk.  What it costs is the chain of a
@@ -318,19 +322,24 @@ __device__ __forceinline__ void setup_store(const Tables &t, double ratio, int b
  * chunk map needs no launch of its own (5.1 us for 161 buckets and 12 Ki chunks; as two kernels 5.7 + 4.7).  Up to
  * SETUP_MAX_B buckets; with more (n_chunks 0 here) the prefixes would be made too often, and k_chunkmap follows. */
 constexpr uint32_t SETUP_MAX_B = 2047;
+template <uint32_t NT>      /* sC: SETUP_MAX_B + 1 words of LDS; workgroup `wg` of n_wg */
+__device__ __forceinline__ void setup_all(const Tables &t, double ratio, int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b,
+                                          uint64_t *sC, uint32_t wg, uint32_t n_wg)
+{
+    setup_body<NT>(t.B, t.chunk, ratio, bits, [&](uint32_t b) { return t.off[b]; },
+                   [&](uint32_t b, uint64_t nb, uint64_t k, uint64_t P, uint64_t V, uint64_t C, uint64_t) {
+                       if (wg == 0u) setup_store(t, ratio, bits, b, nb, k, P, V, C);
+                       if (n_chunks) sC[b] = C;
+                   });
+    if (!n_chunks) return;
+    wg_sync();
+    for (uint64_t c = (uint64_t)wg * NT + threadIdx.x; c < n_chunks; c += (uint64_t)n_wg * NT)
+        chunk_b[c] = find_bucket<uint64_t>(sC, t.B, c);
+}
 __global__ __launch_bounds__(WG) void k_setup(Tables t, double ratio, int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
 {
     __shared__ uint64_t sC[SETUP_MAX_B + 1];
-    const bool first = blockIdx.x == 0;
-    setup_body(t.B, t.chunk, ratio, bits, [&](uint32_t b) { return t.off[b]; },
-               [&](uint32_t b, uint64_t nb, uint64_t k, uint64_t P, uint64_t V, uint64_t C, uint64_t) {
-                   if (first) setup_store(t, ratio, bits, b, nb, k, P, V, C);
-                   if (n_chunks) sC[b] = C;
-               });
-    if (!n_chunks) return;
-    wg_sync();
-    for (uint64_t c = (uint64_t)blockIdx.x * WG + threadIdx.x; c < n_chunks; c += (uint64_t)gridDim.x * WG)
-        chunk_b[c] = find_bucket<uint64_t>(sC, t.B, c);
+    setup_all<WG>(t, ratio, bits, n_chunks, chunk_b, sC, blockIdx.x, gridDim.x);
 }
 
 /* Tile tables, once per bucket layout. */

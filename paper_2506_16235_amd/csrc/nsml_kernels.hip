@@ -349,12 +349,14 @@ int ensure_layout(nsml_ctx *c, uint64_t n, const uint64_t *off, uint32_t B, hipS
     return NSML_OK;
 }
 
-/* Make d_k / d_P / d_V / d_S / d_C match (ratio, bits) for the cached layout. */
-int ensure_tables(nsml_ctx *c, double ratio, int bits, hipStream_t st)
+/* K and NC of (ratio, bits) for the cached layout; stale: d_k / d_P / d_V / d_S / d_C are those of another. */
+int plan_tables(nsml_ctx *c, double ratio, int bits, bool &stale)
 {
     if (!(ratio > 0.0 && ratio <= 1.0)) return NSML_EINVAL;
     if (bits != 4 && bits != 8 && bits != 16 && bits != 32) return NSML_EINVAL;
-    if (c->tables_valid && c->t_ratio == ratio && c->t_bits == bits) return NSML_OK;
+    stale = !(c->tables_valid && c->t_ratio == ratio && c->t_bits == bits);
+    if (!stale) return NSML_OK;
+    c->tables_valid = false;
     uint64_t K = 0, nc = 0;
     {
         std::vector<uint64_t> kb(c->B);
@@ -363,15 +365,38 @@ int ensure_tables(nsml_ctx *c, double ratio, int bits, hipStream_t st)
         for (uint32_t b = 0; b < c->B; ++b) nc += (kb[b] + c->chunk - 1) / c->chunk;
     }
     if (nc >= 0x7FFFFFFFull || nc > c->max_chunks) return NSML_ECAP;
-    const bool map = c->B <= SETUP_MAX_B;
-    const uint64_t mgrid = (nc + WG - 1) / WG;
-    LAUNCH(c, KID_SETUP, st, k_setup, map && mgrid > 1 ? (uint32_t)(mgrid < 1024 ? mgrid : 1024) : 1u, tables_of(c), ratio, bits,
-           map ? nc : 0u, c->d_chunk_b);
-    if (nc && !map) LAUNCH(c, KID_SETUP, st, k_chunkmap, (uint32_t)mgrid, (const uint64_t *)c->d_C, c->B, nc, c->d_chunk_b);
     c->K = K; c->NC = nc;
     c->t_ratio = ratio; c->t_bits = bits;
+    return NSML_OK;
+}
+
+/* Workgroups (of `threads`) that make the tables, and the chunks they map */
+uint32_t setup_grid(const nsml_ctx *c, uint32_t threads, uint64_t &chunks)
+{
+    chunks = c->B <= SETUP_MAX_B ? c->NC : 0u;
+    return (uint32_t)std::min<uint64_t>(1024u, std::max<uint64_t>(1u, (chunks + threads - 1) / threads));
+}
+int chunk_map(nsml_ctx *c, hipStream_t st)
+{
+    if (c->NC && c->B > SETUP_MAX_B)
+        LAUNCH(c, KID_SETUP, st, k_chunkmap, (uint32_t)((c->NC + WG - 1) / WG), (const uint64_t *)c->d_C, c->B, c->NC, c->d_chunk_b);
     c->tables_valid = true;
     return NSML_OK;
+}
+
+/* Make the tables match (ratio, bits) in a launch of their own. */
+int make_tables(nsml_ctx *c, hipStream_t st)
+{
+    uint64_t chunks;
+    const uint32_t grid = setup_grid(c, WG, chunks);
+    LAUNCH(c, KID_SETUP, st, k_setup, grid, tables_of(c), c->t_ratio, c->t_bits, chunks, c->d_chunk_b);
+    return chunk_map(c, st);
+}
+int ensure_tables(nsml_ctx *c, double ratio, int bits, hipStream_t st)
+{
+    bool stale;
+    const int rc = plan_tables(c, ratio, bits, stale);
+    return rc || !stale ? rc : make_tables(c, st);
 }
 
 /* A device-side consistency check that tripped during an earlier call is reported once, by the
@@ -552,8 +577,13 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     if (!guard.ok) { c->last_hip = (int)hipErrorInvalidDevice; return NSML_EHIP; }
     int rc = ensure_layout(c, n, bucket_off, B, st);
     if (rc) return rc;
-    rc = ensure_tables(c, ratio, bits, st);
+    bool stale;
+    rc = plan_tables(c, ratio, bits, stale);
     if (rc) return rc;
+    /* Sample and prediction by a workgroup per bucket, which also makes stale tables: up to two turns of two workgroups
+     * on every compute unit, and no bucket that needs a larger sample (compress, us, this / k_sample and k_predict: 1024 buckets of
+     * 45 elements 100 / 103, 1000 of 40000 204 / 243, one of 1 Mi 50.6 / 54.1; 16 of 4 M 195 / 202). */
+    const bool presample = B <= 4u * (uint32_t)c->n_cu && c->max_nb < PRE_BIG && !c->force_dense;
 
     Tables t = tables_of(c);
     const Cand cd0 = cand_of(c);
@@ -570,7 +600,14 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
      * controller's cap), the weights decide nothing and are not read */
     const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
     if (none_pruned) weights = nullptr;
-    if (c->K == n && !c->force_dense && (bits >= 16 || TILE % c->chunk == 0)) {
+    const bool full = c->K == n && !c->force_dense && (bits >= 16 || TILE % c->chunk == 0);
+    const bool small = !weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B <= 2u * (uint32_t)c->n_cu;
+    if (stale && (full || small || weights || !presample)) {
+        rc = make_tables(c, st);
+        if (rc) return rc;
+        stale = false;
+    }
+    if (full) {
         /* everything is sent: nothing to select (TILE % chunk: chunks nest in tiles) */
         const bool fnt = nt && c->off_mult4 && aligned(idx, 16) && aligned(val, 16);      /* (misaligned non-temporal stores leave partly written lines) */
 #define NSML_FULL(BITS_)                                                                                                                      \
@@ -596,7 +633,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
      * while the buckets share the chain's launches: the line is drawn at two rounds, where it takes about half of
      * the chain's time (us, 1 % sent as 8-bit codes, this / the chain: 1 bucket of 32764 elements 39 / 69, 256 of
      * them 51 / 124, 512 98 / 205; 512 of 500 26 / 86, of 40 26 / 70). */
-    if (!weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B <= 2u * (uint32_t)c->n_cu) {
+    if (small) {
         switch (bits) {
         case 32: LAUNCHB(c, KID_EF_EMIT, st, k_small<32>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
         case 16: LAUNCHB(c, KID_EF_EMIT, st, k_small<16>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;
@@ -643,9 +680,16 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     }
 
     const bool pruned = weights != nullptr;
-    if (!c->force_dense)
-        LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs);
-    LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
+    if (presample) {
+        uint64_t chunks = 0;
+        const uint32_t extra = stale ? setup_grid(c, PRE_T, chunks) : 0u;
+        LAUNCHB(c, KID_SAMPLE, st, k_presample, B + extra, PRE_T, grad, (const float *)residual, t, ratio, bits, chunks, c->d_chunk_b);
+        if (stale) { rc = chunk_map(c, st); if (rc) return rc; }
+    } else {
+        if (!c->force_dense)
+            LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs);
+        LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
+    }
 #define NSML_EF(EMIT_, PRUNE_, NT_, HIST_) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<EMIT_, PRUNE_, NT_, HIST_>), sgrid, STH, grad, residual, t, h.hw, cd0, c->d_tile_sq)
     if (c->force_dense) { if (nt) NSML_EF(false, false, true, false); else NSML_EF(false, false, false, false); }
     else if (nt) { if (pruned) NSML_EF(true, true, true, false); else NSML_EF(true, false, true, false); }
@@ -904,7 +948,7 @@ __global__ __launch_bounds__(WG) void k_static_setup(StaticOffsets so, Tables t,
     __shared__ uint64_t sOff[STATIC_B1], sP[STATIC_B1];
     __shared__ uint32_t sT[STATIC_B1], sK[STATIC_B1];
     const bool first = blockIdx.x == 0;
-    setup_body(t.B, t.chunk, ratio, bits, [&](uint32_t b) { return so.off[b]; },
+    setup_body<WG>(t.B, t.chunk, ratio, bits, [&](uint32_t b) { return so.off[b]; },
                [&](uint32_t b, uint64_t nb, uint64_t k, uint64_t P, uint64_t V, uint64_t C, uint64_t tile) {
                    sOff[b] = so.off[b]; sP[b] = P; sT[b] = (uint32_t)tile; sK[b] = (uint32_t)k;
                    if (first) {

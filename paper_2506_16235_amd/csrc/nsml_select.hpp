@@ -75,37 +75,16 @@ __device__ __forceinline__ uint32_t window_shift(uint32_t L, uint32_t W)
  * in the same bins was no gain in safety and cost an atomic each.)
  * A bucket for which none of this fits (or whose guess turns out wrong once the exact counts are
  * known) takes the dense passes and still gets the exact result. */
-__global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__ hist_s,
-                                                int force_dense)
+template <typename WALK>      /* the sample's histogram: find(rank, digit, above, at), total */
+__device__ __forceinline__ void predict_bucket(const Tables &t, uint32_t b, uint64_t nb, uint32_t k, double pop, bool exact, uint32_t wide, const WALK &w, uint32_t *res)
 {
-    __shared__ uint32_t tmp[WG];
-    __shared__ uint32_t res[10];         /* digit, above, at for three ranks; digit of the window's top */
-    const uint32_t b = blockIdx.x, tid = threadIdx.x;
-    const uint64_t nb = t.off[b + 1] - t.off[b];
-    const uint32_t k = t.k[b];
+    const uint32_t tid = threadIdx.x;
     const KeyPar nothing = make_uint4(NONE, NONE, NONE, SH1);
-    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by this call's plan ([1]: the barrier of k_hard) */
-    if (nb == 0 || force_dense) {
-        if (tid == 0) t.par[b] = nothing;
-        return;
-    }
-    if ((uint64_t)k == nb) {             /* everything is sent: all keys >= 1, and the zeros as ties of key 0 */
-        if (tid == 0) t.par[b] = make_uint4(1u, 1u, 1u, SH1);
-        for (int i = tid; i < NB0; i += WG) hist_s[(uint64_t)b * NB0 + i] = 0u;     /* left clean for the next call */
-        return;
-    }
-    DigitWalk<NB0> w;
-    w.load(hist_s + (uint64_t)b * NB0, tmp);
-    w.clear(hist_s + (uint64_t)b * NB0);
     const uint32_t m = w.total;
     if (m == 0) {
         if (tid == 0) t.par[b] = nothing;
         return;
     }
-    const bool exact = nb < SAMPLE_ALL_BELOW;
-    /* the sample was drawn from the parameters that can be selected: all of them, or the
-     * ones the pruning step kept */
-    const double pop = t.pmask ? (double)t.kw[b] : (double)nb;
     const double ks = (double)k * (double)m / pop;
     const double cap_b = (double)(t.tile0[b + 1] - t.tile0[b]) * (double)SEG_CAP;
     auto clip = [&](double x) { return x < 1.0 ? 1.0 : (x > (double)m ? (double)m : x); };
@@ -114,7 +93,7 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
      * fewer independent draws than entries; a bucket whose guess missed widens its margin).  Where so wide a margin
      * leaves nothing that can be staged, half of it is tried, down to the plain one (a bucket that had once missed
      * was on the dense passes for 64 calls: 25 M elements at 0.8 500 us a call, so 285). */
-    uint32_t widen = t.margin[b] & 0xFFu ? t.margin[b] & 0xFFu : 1u;
+    uint32_t widen = (t.margin[b] & 0xFFu ? t.margin[b] & 0xFFu : 1u) * wide;
     while (true) {
         const double dev = exact ? 0.0 : (4.0 * sqrt(ks) + 4.0) * (double)widen;
         const double want_d = exact ? (double)k : ceil(ks + dev);
@@ -167,6 +146,145 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
         widen >>= 1;
         wg_sync();                                       /* res is written again */
     }
+}
+
+/* The sample was taken by k_sample (many small buckets). */
+__global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__ hist_s, int force_dense)
+{
+    __shared__ uint32_t tmp[WG];
+    __shared__ uint32_t res[10];         /* digit, above, at for three ranks; digit of the window's top */
+    const uint32_t b = blockIdx.x, tid = threadIdx.x;
+    const uint64_t nb = t.off[b + 1] - t.off[b];
+    const uint32_t k = t.k[b];
+    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by this call's plan ([1]: the barrier of k_hard) */
+    if (nb == 0 || force_dense) {
+        if (tid == 0) t.par[b] = make_uint4(NONE, NONE, NONE, SH1);
+        return;
+    }
+    if ((uint64_t)k == nb) {             /* everything is sent: all keys >= 1, and the zeros as ties of key 0 */
+        if (tid == 0) t.par[b] = make_uint4(1u, 1u, 1u, SH1);
+        for (int i = tid; i < NB0; i += WG) hist_s[(uint64_t)b * NB0 + i] = 0u;     /* left clean for the next call */
+        return;
+    }
+    DigitWalk<NB0> w;
+    w.load(hist_s + (uint64_t)b * NB0, tmp);
+    w.clear(hist_s + (uint64_t)b * NB0);
+    /* the sample was drawn from the parameters that can be selected: all of them, or the
+     * ones the pruning step kept */
+    predict_bucket(t, b, nb, k, t.pmask ? (double)t.kw[b] : (double)nb, nb < SAMPLE_ALL_BELOW, 1u, w, res);
+}
+
+/* Sample and prediction of a bucket by one workgroup, and the tables of a new (ratio, bits) beside them: three launches
+ * that wait for each other in one.  What a compute unit can fetch alone (25 - 50 GB/s) bounds it, so the sample is
+ * PRE_ELEMS elements (in the same runs of 16), and in buckets of which k_sample takes every element the margin of the
+ * candidates is twice as wide (a wider band would overflow the segments of clustered values).  ResNet-50's 161 buckets: 9.6 us, by k_sample and k_predict 12 + 8 (and 5 for the tables); 1 Mi
+ * elements 7.5, 6.2 + 5.5.  With 32768 elements 22 us. */
+constexpr uint32_t PRE_T = 1024, PRE_U = 2;        /* 16-byte accesses a thread has in flight, per operand */
+constexpr uint32_t PRE_ELEMS = 8192;
+constexpr uint64_t PRE_BIG = 1ull << 22;           /* larger buckets need a larger sample (16 of 4 M, rows of zeros: already 4 % slower) */
+__device__ __forceinline__ uint64_t pre_stride(uint64_t nb) { return nb < 2u * PRE_ELEMS ? 1u : nb / PRE_ELEMS; }
+/* the histogram's digits from the top, four per thread */
+struct DigitWalk1024 {
+    uint32_t c[NB0 / PRE_T], sum, incl, total;
+    int top;
+    __device__ __forceinline__ void load(const uint32_t *h, uint32_t *tmp)
+    {
+        const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        top = NB0 - 1 - (int)threadIdx.x * (NB0 / (int)PRE_T);
+        sum = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < NB0 / PRE_T; ++i) { c[i] = h[top - (int)i]; sum += c[i]; }
+        incl = sum;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) { const uint32_t y = __shfl_up(incl, d, 64); if (lane >= (uint32_t)d) incl += y; }
+        if (lane == 63) tmp[wave] = incl;
+        wg_sync();
+        total = 0;
+#pragma unroll
+        for (uint32_t v = 0; v < PRE_T / 64; ++v) { incl += v < wave ? tmp[v] : 0u; total += tmp[v]; }
+    }
+    __device__ __forceinline__ bool find(uint32_t want, uint32_t &digit, uint32_t &above, uint32_t &at) const
+    {
+        uint32_t acc = incl - sum;
+        if (!(acc < want && want <= incl)) return false;
+#pragma unroll
+        for (uint32_t i = 0; i < NB0 / PRE_T; ++i) {
+            if (acc + c[i] >= want) { digit = (uint32_t)(top - (int)i); above = acc; at = c[i]; return true; }
+            acc += c[i];
+        }
+        return false;
+    }
+};
+__global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g, const float *__restrict__ r, Tables t, double ratio,
+                                                     int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
+{
+    __shared__ uint32_t h[NB0];
+    __shared__ uint32_t tmp[PRE_T / 64], res[10];
+    const uint32_t b = blockIdx.x, tid = threadIdx.x;
+    if (b >= t.B) {                                  /* workgroups beyond the buckets: set-up */
+        setup_all<PRE_T>(t, ratio, bits, n_chunks, chunk_b, reinterpret_cast<uint64_t *>(h), b - t.B, gridDim.x - t.B);
+        return;
+    }
+    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by this call's plan ([1]: the barrier of k_hard) */
+    const uint64_t lo = t.off[b], hi = t.off[b + 1], nb = hi - lo, a0 = lo & ~3ull;
+    const uint32_t k = (uint32_t)survivors_dev(ratio, nb);
+    if (nb == 0 || (uint64_t)k == nb) {              /* everything is sent: all keys >= 1, and the zeros as ties of key 0 */
+        if (tid == 0) t.par[b] = nb == 0 ? make_uint4(NONE, NONE, NONE, SH1) : make_uint4(1u, 1u, 1u, SH1);
+        return;
+    }
+    for (uint32_t i = tid; i < (uint32_t)NB0; i += PRE_T) h[i] = 0u;
+    const uint64_t stride = pre_stride(nb), run_elems = SAMPLE_RUN * stride, n_runs = (hi - a0 + run_elems - 1) / run_elems;
+    const uint32_t tile0b = t.pmask ? t.tile0[b] : 0u;
+    wg_sync();
+    constexpr uint32_t RUNS = PRE_T / (SAMPLE_RUN / 4);         /* per access of all threads */
+#pragma unroll 1
+    for (uint64_t run0 = tid / (SAMPLE_RUN / 4); run0 < n_runs; run0 += RUNS * PRE_U) {
+        f4 x[PRE_U], y[PRE_U];
+        uint32_t m[PRE_U];
+#pragma unroll
+        for (uint32_t u = 0; u < PRE_U; ++u) {
+            const uint64_t gi = a0 + (run0 + u * RUNS) * run_elems + (tid % (SAMPLE_RUN / 4)) * 4;
+            x[u] = y[u] = f4{0.f, 0.f, 0.f, 0.f};
+            m[u] = 0u;
+            if (run0 + u * RUNS < n_runs && gi >= lo && gi + 4 <= hi) {
+                x[u] = *reinterpret_cast<const f4 *>(g + gi);
+                y[u] = *reinterpret_cast<const f4 *>(r + gi);
+                m[u] = 0xFu;
+                if (t.pmask) m[u] = ~pruned_bits(t.pmask, tile0b + (uint32_t)((gi - a0) / TILE), (uint32_t)((gi - a0) % TILE) / 4) & 0xFu;
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < PRE_U; ++u) {
+            const uint64_t gi = a0 + (run0 + u * RUNS) * run_elems + (tid % (SAMPLE_RUN / 4)) * 4;
+            if (run0 + u * RUNS < n_runs && gi < hi && (gi < lo || gi + 4 > hi)) {
+                /* the bucket's first and last quad may be partly another's */
+                float xa[4], ya[4];
+                m[u] = load_quad(g, gi, lo, hi, xa);
+                load_quad(r, gi, lo, hi, ya);
+                if (t.pmask) m[u] &= ~pruned_bits(t.pmask, tile0b + (uint32_t)((gi - a0) / TILE), (uint32_t)((gi - a0) % TILE) / 4);
+                x[u] = f4{xa[0], xa[1], xa[2], xa[3]};
+                y[u] = f4{ya[0], ya[1], ya[2], ya[3]};
+            }
+            uint32_t d[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) d[j] = keyof(__fadd_rn(x[u][j], y[u][j])) >> SH0;
+            /* runs of equal keys (zeros): one addition for the wavefront */
+            const uint32_t fd = __builtin_amdgcn_readfirstlane(d[0]);
+            if (__all(m[u] == 0xFu && d[0] == fd && d[1] == fd && d[2] == fd && d[3] == fd)) {
+                if ((tid & 63u) == 0u) atomicAdd(&h[fd], 256u);
+                continue;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((m[u] >> j) & 1u) atomicAdd(&h[d[j]], 1u);
+        }
+    }
+    wg_sync();
+    DigitWalk1024 w;
+    w.load(h, tmp);
+    double pop = (double)nb;
+    if (t.pmask) pop = (double)kept_dev(ratio, nb);
+    predict_bucket(t, b, nb, k, pop, stride == 1u, nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, w, res);
 }
 
 /* ------------------------------------------------------------------ the streaming pass */
