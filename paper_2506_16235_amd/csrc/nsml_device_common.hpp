@@ -49,6 +49,8 @@ constexpr int NB0 = 4096, NB1 = 4096, NB2 = 128;
 constexpr int NHB = 1024;         /* bins of the window of keys in which the threshold is expected */
 constexpr uint32_t NHC = 8;       /* copies of a bucket's bins, one per die's share of the workgroups: with one copy the streaming pass
                                    * waits for its own updates (2.4 % staged: 1.14 ms on 419 M elements, 0.83 with eight) */
+constexpr uint32_t HROW = NHB + 32;            /* words of a copy: the bins, then how many elements lie at or above the window (in a line of its own: the
+                                                * counts of several buckets side by side made the pass twice as long) */
 constexpr int SH0 = 19;   /* key >> 19         : level-0 digit (sign-less exponent + 4 mantissa bits) */
 constexpr int SH1 = 7;    /* (key >> 7) & 4095 : level-1 digit;  key & 127 : level-2 digit */
 constexpr uint32_t NONE = 0xFFFFFFFFu;

@@ -19,9 +19,9 @@
  *   ef_emit   acc = grad + residual (written over residual), the staged elements in index order to a
  *             segment per tile, how many lie above the window of keys around the expected
  *             threshold, and the window's bins (from 16384 tiles up by a kernel of their own, bins) 12 B/element
- *   plan      per bucket: the window's bin that holds the k-th key, and the path: PATH_CAND,
- *             PATH_BAND, PATH_ZERO when the staged elements and the counts can decide it, else PATH_DENSE
- *   select_count, select_finish   the staged entries against those bits: counts per segment, the
+ *   select_count, select_finish   per bucket the plan: the window's bin that holds the k-th key, and the path: PATH_CAND,
+ *             PATH_BAND, PATH_ZERO when the staged elements and the counts can decide it, else PATH_DENSE; then
+ *             the staged entries against those bits: counts per segment, the
  *             few undecided keys set aside, then per bucket (one workgroup of 1024 threads) the
  *             remaining bits in LDS -> threshold key T_b, e_b = how many elements equal to T_b
  *             are admitted (lowest indices first), and every segment's place in the survivor order
@@ -178,7 +178,7 @@ int dev_alloc(nsml_ctx *c, T **p, uint64_t count)
 
 /* words of the area that is zero between calls: sample histogram, bins of the window, histograms of
  * the dense passes, overflow flags */
-uint64_t zero_words(uint64_t B) { return B * (uint64_t)(NB0 + NHC * NHB + NB0 + NB1 + NB2 + 2) + 16; }   /* 16 spare words: counters */
+uint64_t zero_words(uint64_t B) { return B * (uint64_t)(NB0 + NHC * HROW + NB0 + NB1 + NB2 + 2) + 16; }   /* 16 spare words: counters */
 
 struct Hists { uint32_t *hs, *hw, *f0, *f1, *f2, *ovf, *cursor, *nhard; };
 Hists hists_of(const nsml_ctx *c, uint32_t B)
@@ -186,12 +186,12 @@ Hists hists_of(const nsml_ctx *c, uint32_t B)
     Hists h;
     h.hs = c->d_zero;
     h.hw = h.hs + (uint64_t)B * NB0;
-    h.f0 = h.hw + (uint64_t)B * NHC * NHB;
+    h.f0 = h.hw + (uint64_t)B * NHC * HROW;
     h.f1 = h.f0 + (uint64_t)B * NB0;
     h.f2 = h.f1 + (uint64_t)B * NB1;
     h.ovf = h.f2 + (uint64_t)B * NB2;
     h.cursor = h.ovf + B;          /* k_select_count: length of the bucket's list of undecided keys */
-    h.nhard = h.cursor + B;      /* k_plan: buckets not on the candidate path */
+    h.nhard = h.cursor + B;      /* k_select_count: buckets not on the candidate path */
     return h;
 }
 
@@ -663,13 +663,13 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
                c->whistory ? (const uint32_t *)c->d_wprevT : (const uint32_t *)nullptr, (const uint32_t *)c->d_wprevHw);
         if (bins) LAUNCHB(c, KID_WHIST, st, k_whist<false>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
         else LAUNCHB(c, KID_WHIST, st, k_whist<true>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
-        if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, weights);
+        if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, 0, weights);
         LAUNCHB(c, KID_WPLAN, st, k_wplan, B, NHB, tw, h.hw, cd0, c->d_wnband);
         /* buckets decided from their band: undecided keys, threshold key and tie count, the pruned
          * band elements' bits; buckets on the dense passes (no band, or one that missed):
          * everything in one resident launch */
         if (!c->force_dense) {
-            LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights);
+            LAUNCH(c, KID_SELECT, st, k_select_count<false>, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, (const uint32_t *)nullptr, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights);
             LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                     (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1, c->force_rescan);
             LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
@@ -696,14 +696,14 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     else if (bins) { if (pruned) NSML_EF(true, true, false, false); else NSML_EF(true, false, false, false); }
     else { if (pruned) NSML_EF(true, true, false, true); else NSML_EF(true, false, false, true); }
 #undef NSML_EF
-    if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, (const float *)residual);
-    LAUNCHB(c, KID_PLAN, st, k_plan, B, NHB, t, h.hw, cd0, c->force_dense ? 0 : 1, (const double *)c->d_tile_sq, c->d_l2sq);
+    if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, 1, (const float *)residual);
+    if (c->force_dense) LAUNCHB(c, KID_PLAN, st, k_plan_dense, B, 1024, t, (const double *)c->d_tile_sq, c->d_l2sq);
     const uint32_t qgrid = (uint32_t)c->NC;
     if (!c->force_dense) {
         /* buckets decided from their staged elements: undecided keys set apart, threshold and
          * survivor order per bucket, then the payload of the candidate-path buckets */
         const uint4 *selw = c->d_selw;
-        LAUNCH(c, KID_SELECT, st, k_select_count, c->n_sel, t, cd0, selw, h.cursor, c->d_part, c->d_lkey, c->d_flags, (const float *)residual);
+        LAUNCH(c, KID_SELECT, st, k_select_count<true>, c->n_sel, t, cd0, selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags, (const float *)residual);
         LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                 (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, c->d_chunk_seg, c->d_flags, c->force_rescan);
         {
@@ -719,8 +719,8 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             const bool narrow = c->NC >= 2u * (uint64_t)c->n_cu && c->K <= 1900u * c->NC;
 #define NSML_ENCODE(BITS_)                                                                                                              \
     do {                                                                                                                                 \
-        if (narrow) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 256>), egrid2, 256, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw);  \
-        else LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 512>), egrid2, 512, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw);         \
+        if (narrow) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 256>), B + egrid2, 256, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);  \
+        else LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 512>), B + egrid2, 512, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);         \
     } while (0)
             switch (bits) {
             case 32: NSML_ENCODE(32); break;

@@ -151,7 +151,7 @@ __global__ __launch_bounds__(WTH, 8) void k_whist(const float *__restrict__ w, T
         word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0x104, 0xF, 0xF, true);     /* from lane + 4 */
         if ((lane & 7u) == 0u) pmask[(uint64_t)tile * (TILE / 32) + ((u * WTH + tid) >> 3)] = word;
     }
-    stage_tile<WTH, HIST>(a, m, p, b, tile, (uint32_t)(g0 - t.off[b]), c, hist, t.ovf + b, sm);
+    stage_tile<WTH, HIST>(a, m, p, b, tile, (uint32_t)(g0 - t.off[b]), c, hist, false, t.ovf + b, sm);
 }
 
 /* Per bucket: the bin of the kw-th largest |weight|, from the counts above the band and the bins of
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ 
         for (uint32_t w = 0; w < NHB / 64; ++w) n_above += red[w];
     }
     uint32_t total;
-    const bool found = window_find(hist + (uint64_t)b * NHC * NHB, n_above, want, wsum, res, total);
+    const bool found = window_find(hist + (uint64_t)b * NHC * HROW, n_above, want, wsum, res, total);
     if (tid != 0) return;
     const uint32_t ovf = t.ovf[b];
     if (ovf) t.ovf[b] = 0u;

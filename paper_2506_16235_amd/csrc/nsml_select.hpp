@@ -313,7 +313,7 @@ struct StageShared {
 template <int NTH, bool HIST>
 __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4], const uint32_t (&cm)[TILE / (4 * NTH)], const KeyPar &p,
                                            uint32_t b, uint32_t tile, uint32_t li0, const Cand &c, uint32_t *__restrict__ hist,
-                                           uint32_t *__restrict__ ovf, StageShared<HIST> &sm)
+                                           bool count_hi, uint32_t *__restrict__ ovf, StageShared<HIST> &sm)
 {
     constexpr int Q = TILE / (4 * NTH);
     constexpr uint32_t W = NTH / 64;
@@ -372,6 +372,8 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
         c.G[tile] = thi;
         c.E[tile] = tlo;
         if (all > SEG_CAP) *ovf = 1u;
+        if constexpr (HIST)
+            if (count_hi && thi) atomicAdd(hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW + NHB, thi);
     }
     if (all == 0u) return;                             /* same for the whole workgroup */
     const uint32_t top = (p.z - 1u) >> p.w;
@@ -393,7 +395,7 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
     wg_sync();
     const uint64_t cbase = (uint64_t)tile * SEG_CAP;
     for (uint32_t i = tid; i < min(all, SEG_CAP); i += NTH) { c.idx[cbase + i] = sm.si[i]; c.val[cbase + i] = sm.sv[i]; }
-    if constexpr (HIST) hist_flush(sm.bins.h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * NHB, NHB, NTH);
+    if constexpr (HIST) hist_flush(sm.bins.h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW, NHB, NTH);
 }
 
 /* acc = grad + residual over a tile, written over residual (Sec. 4.2 Step 3: what top-k filters out
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
     if (EMIT) {
         if (PRUNE) m &= ~pruned_bits(t.pmask, tile, tid);
         const uint32_t b = d.z;
-        stage_tile<STH, HIST>(av, mv, t.par[b], b, tile, (uint32_t)(gi - e - t.off[b]), c, hist, t.ovf + b, sm);
+        stage_tile<STH, HIST>(av, mv, t.par[b], b, tile, (uint32_t)(gi - e - t.off[b]), c, hist, true, t.ovf + b, sm);
     } else {
         wg_sync();
     }
@@ -471,8 +473,8 @@ __device__ __forceinline__ bool window_find(uint32_t *__restrict__ hist_b, uint3
     uint32_t cnt = 0;
 #pragma unroll
     for (uint32_t q = 0; q < NHC; ++q) {
-        const uint32_t v = hist_b[q * NHB + tid];
-        if (v) hist_b[q * NHB + tid] = 0u;
+        const uint32_t v = hist_b[q * HROW + tid];
+        if (v) hist_b[q * HROW + tid] = 0u;
         cnt += v;
     }
     uint32_t incl = cnt;
@@ -489,90 +491,96 @@ __device__ __forceinline__ bool window_find(uint32_t *__restrict__ hist_b, uint3
     return n_hi < want && (uint64_t)n_hi + total >= want;
 }
 
-/* Per bucket: the bin of the k-th largest key, the gradient's |.|^2, and how the bucket is decided
- * (PATH_*).  The staged elements can decide it when they are known to hold every element of that
- * bin: in candidate mode they are exactly the elements with key >= L_b, so they do iff there are at
- * least k of them and the key lies below the window's top; in band mode iff it lies inside the band;
- * in both only if the undecided keys of the bin fit the bucket's list of them (k_select_count).  In zero mode the counts settle everything: fewer non-zero
- * elements than k means threshold key 0. */
-__global__ __launch_bounds__(NHB) void k_plan(Tables t, uint32_t *__restrict__ hist, Cand c, int have_cand,
-                                              const double *__restrict__ tile_sq, double *__restrict__ l2sq)
+/* How a bucket is decided (PATH_*), from its exact counts: n_hi elements at or above the window's top; found: the k-th key lies
+ * in the window, in its bin `bin`, with `above` elements above that bin and `at` in it; total: all of the window's.  The staged elements can decide
+ * it when they are known to hold every element of that bin: in candidate mode they are exactly the elements with
+ * key >= L_b, so they do iff there are at least k of them and the key lies below the window's top; in band mode iff it
+ * lies inside the band; in both only if the undecided keys of the bin fit the bucket's list of them (k_select_count).  In
+ * zero mode the counts settle everything: fewer non-zero elements than k means threshold key 0. */
+struct Plan { uint32_t path, T, need, sh, why; };
+__device__ __forceinline__ Plan plan_bucket(const Tables &t, uint32_t b, const KeyPar &p, uint32_t want, uint32_t n_hi, uint32_t total, bool found,
+                                            uint32_t bin, uint32_t above, uint32_t at, uint32_t ovf, uint32_t segs)
 {
-    __shared__ uint32_t wsum[NHB / 64], redh[NHB / 64], res[3];
-    __shared__ double red[NHB / 64];
-    const uint32_t b = blockIdx.x, tid = threadIdx.x;
-    const KeyPar p = t.par[b];
-    const uint32_t want = t.k[b];
-    uint32_t n_hi = 0;
-    {   /* |grad|^2 of the bucket: strided partial sums, then a fixed tree; the counts above the window likewise */
-        double acc = 0.0;
-        uint32_t ch = 0;
-        const uint32_t t1 = t.tile0[b + 1];
-        const bool cand = have_cand && p.x != NONE;
-#pragma unroll 4
-        for (uint32_t s = t.tile0[b] + tid; s < t1; s += NHB) { acc += tile_sq[s]; ch += cand ? c.G[s] : 0u; }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) { acc += __shfl_xor(acc, d, 64); ch += __shfl_xor(ch, d, 64); }
-        if ((tid & 63) == 0) { red[tid >> 6] = acc; redh[tid >> 6] = ch; }
-        wg_sync();
-        if (tid == 0) {
-            double tot = 0.0;
-            for (uint32_t w = 0; w < NHB / 64; w += 4) tot += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
-            l2sq[b] = tot;
-        }
-        for (uint32_t w = 0; w < NHB / 64; ++w) n_hi += redh[w];
-    }
-    if (want == 0) {                       /* empty bucket: nothing can match */
-        if (tid == 0) { t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_CAND; t.sh[b] = SH0; t.why[b] = 0u; }
-        return;
-    }
-    uint32_t total;
-    const bool found = window_find(hist + (uint64_t)b * NHC * NHB, n_hi, want, wsum, res, total);
-    if (tid != 0) return;
-    const uint32_t ovf = t.ovf[b];
-    if (ovf) t.ovf[b] = 0u;                    /* left clean for the next call, like the bins */
-    uint32_t path = PATH_DENSE, T = 0u, need = want, sh = SH_NONE, why = 0u;
-    if (!have_cand || p.x == NONE) {
-        why = WHY_NO_GUESS;
-        if (have_cand && p.w == (uint32_t)SH0) { T = t.T[b]; need = t.need[b]; sh = SH0; }       /* (left there by k_predict) */
+    Plan q = {PATH_DENSE, 0u, want, SH_NONE, 0u};
+    if (p.x == NONE) {
+        q.why = WHY_NO_GUESS;
+        if (p.w == (uint32_t)SH0) { q.T = t.T[b]; q.need = t.need[b]; q.sh = SH0; }       /* (left there by the prediction) */
     }
     else if (p.x == p.y) {
         /* n_hi = non-zero keys among the selectable elements: if they are no more than k,
          * all of them survive and zeros (lowest indices first) fill the rest */
-        if (n_hi <= want) { path = PATH_ZERO; need = want - n_hi; sh = SH0; }
-        else why = WHY_NONZEROS;
+        if (n_hi <= want) { q.path = PATH_ZERO; q.need = want - n_hi; q.sh = SH0; }
+        else q.why = WHY_NONZEROS;
     } else if (p.x == 1u && p.y != NONE && (uint64_t)n_hi + total <= want) {
         /* the band starts at key 1 and everything non-zero is still not enough: zero threshold */
-        path = PATH_ZERO; need = want - (n_hi + total); sh = SH0;
+        q.path = PATH_ZERO; q.need = want - (n_hi + total); q.sh = SH0;
     } else if (found) {
         /* a tile whose segment overflowed is read from the dense accumulator by the kernels
          * that find the threshold; the survivors of such a bucket are then taken from the dense
          * accumulator as well (PATH_BAND), since the staged entries cannot supply them all */
-        const uint32_t top = (p.z - 1u) >> p.w, bin = res[0], at = res[2];
-        if (bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin) why = WHY_OUTSIDE_BAND;    /* the open last bin */
+        const uint32_t top = (p.z - 1u) >> p.w;
+        if (bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin) q.why = WHY_OUTSIDE_BAND;    /* the open last bin */
         else {
-            T = top - bin; need = want - res[1]; sh = p.w;
-            if (!list_pays(at, t.tile0[b + 1] - t.tile0[b], t.n_tiles)) why = WHY_NO_ROOM;       /* (the dense passes go on from that bin) */
-            else path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND;
+            q.T = top - bin; q.need = want - above; q.sh = p.w;
+            if (!list_pays(at, segs, t.n_tiles)) q.why = WHY_NO_ROOM;       /* (the dense passes go on from that bin) */
+            else q.path = p.y == NONE && !ovf ? PATH_CAND : PATH_BAND;
         }
-    } else why = n_hi < want ? WHY_TOO_FEW : WHY_OUTSIDE_BAND;
-    t.why[b] = why;
+    } else q.why = n_hi < want ? WHY_TOO_FEW : WHY_OUTSIDE_BAND;
+    return q;
+}
+/* The plan's record (one thread per bucket). */
+__device__ __forceinline__ void plan_store(const Tables &t, uint32_t b, const Plan &q)
+{
+    t.why[b] = q.why;
     {
-        /* low byte: factor on the margin of k_predict (1, 2, 4, 8, 16); above it: calls since it last grew.
+        /* low byte: factor on the margin of the prediction (1, 2, 4, 8, 16); above it: calls since it last grew.
          * A guess that missed doubles it, 64 calls without a miss halve it. */
         const uint32_t mg = t.margin[b];
         uint32_t f = mg & 0xFFu ? mg & 0xFFu : 1u, age = mg >> 8;
-        if (why == WHY_TOO_FEW || why == WHY_OUTSIDE_BAND) { f = f < 16u ? f * 2u : 16u; age = 0u; }
+        if (q.why == WHY_TOO_FEW || q.why == WHY_OUTSIDE_BAND) { f = f < 16u ? f * 2u : 16u; age = 0u; }
         else if (++age >= 64u) { f = f > 1u ? f / 2u : 1u; age = 0u; }
         t.margin[b] = (age << 8) | f;
     }
-    t.T[b] = T;
-    t.need[b] = need;
-    t.sh[b] = sh;
-    t.fast[b] = path;
-    if (path != PATH_CAND) atomicAdd(t.nhard, 1u);
-    if (path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);
-    if (path == PATH_DENSE && sh == SH_NONE) atomicAdd(t.nhard + 3, 1u);
+    t.T[b] = q.T;
+    t.need[b] = q.need;
+    t.sh[b] = q.sh;
+    t.fast[b] = q.path;
+    if (q.path != PATH_CAND) atomicAdd(t.nhard, 1u);
+    if (q.path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);
+    if (q.path == PATH_DENSE && q.sh == SH_NONE) atomicAdd(t.nhard + 3, 1u);
+}
+/* An empty bucket: nothing can match. */
+__device__ __forceinline__ void plan_empty(const Tables &t, uint32_t b)
+{
+    t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_CAND; t.sh[b] = SH0; t.why[b] = 0u;
+}
+
+/* |grad|^2 of a bucket by a workgroup of NT threads: strided partial sums, then a fixed tree.  red: NT / 64 words. */
+template <uint32_t NT>
+__device__ __forceinline__ void bucket_sq(const Tables &t, uint32_t b, const double *__restrict__ tile_sq, double *red, double *__restrict__ out)
+{
+    double acc = 0.0;
+    const uint32_t t1 = t.tile0[b + 1];
+#pragma unroll 4
+    for (uint32_t s = t.tile0[b] + threadIdx.x; s < t1; s += NT) acc += tile_sq[s];
+    acc = wave_sum_last(acc);
+    if ((threadIdx.x & 63u) == 63u) red[threadIdx.x >> 6] = acc;
+    wg_sync();
+    if (threadIdx.x != 0) return;
+    double tot = 0.0;
+    for (uint32_t w = 0; w < NT / 64; w += 4) tot += (red[w] + red[w + 1]) + (red[w + 2] + red[w + 3]);
+    *out = tot;
+}
+
+/* The plan when every bucket is sent to the dense passes (force_dense). */
+__global__ __launch_bounds__(1024) void k_plan_dense(Tables t, const double *__restrict__ tile_sq, double *__restrict__ l2sq)
+{
+    __shared__ double red[16];
+    const uint32_t b = blockIdx.x;
+    bucket_sq<1024>(t, b, tile_sq, red, l2sq + b);
+    if (threadIdx.x != 0) return;
+    if (t.k[b] == 0u) { plan_empty(t, b); return; }
+    plan_store(t, b, Plan{PATH_DENSE, 0u, t.k[b], SH_NONE, WHY_NO_GUESS});
 }
 
 /* One workgroup: the list of tiles that belong to buckets on the dense passes.  (Kept as its own small

@@ -2,8 +2,8 @@
  * libnsml device code, part 5: the tail of the selection.
  * Included by nsml_kernels.hip (one translation unit); not a public header.
  *
- * What the tail knows when it starts (left by the streaming pass and the plan): for every
- * bucket the leading bits b0 of its k-th largest key (down to the shift of the bins that the streaming pass
+ * What the tail knows when it starts (left by the streaming pass): the bins of the window of keys, from which
+ * k_select_count makes the plan: for every bucket the leading bits b0 of its k-th largest key (down to the shift of the bins that the streaming pass
  * counted) and how many of the keys that share them are still wanted; for
  * every staging segment its entries (index, value) in index order.  Entries above b0 are
  * survivors, entries below it are not, the ones that share it are the only undecided ones, and
@@ -175,15 +175,26 @@ __device__ __forceinline__ bool pruned_elem(const uint32_t *__restrict__ pmask, 
  * fetched whole before any of it is counted (BERT-shaped gradient at 0.1: 65 us, one load after the other 71). */
 constexpr uint32_t BINS_U = 8;             /* entries a lane has in flight */
 __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
-                                             uint32_t *__restrict__ hist, const float *__restrict__ r)
+                                             uint32_t *__restrict__ hist, int count_hi, const float *__restrict__ r)
 {
-    __shared__ uint32_t h[NHB];
+    __shared__ uint32_t h[NHB], hi_all;
     const uint4 wk = selw[blockIdx.x];
     const uint32_t b = wk.x, s0 = wk.y, s1 = wk.z, tid = threadIdx.x;
     const uint32_t lanes = WG >> selSh, seg = s0 + (tid >> (8u - selSh)), gl = tid & (lanes - 1u);
     const uint32_t cnt = seg < s1 ? c.cnt[seg] : 0u;
+    uint32_t hi = count_hi && gl == 0u && seg < s1 ? c.G[seg] : 0u;     /* elements at or above the window's top */
     const KeyPar p = t.par[b];
-    if (p.x == NONE || p.x == p.y) return;           /* nothing was staged; the same for the whole workgroup */
+    uint32_t *row = hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW;
+    if (p.x == NONE) return;                         /* no guess; the same for the whole workgroup */
+    if (count_hi) {
+        if (tid == 0) hi_all = 0u;
+        wg_sync();
+        hi = wave_incl_scan(hi);
+        if ((tid & 63u) == 63u && hi) atomicAdd(&hi_all, hi);
+        wg_sync();
+        if (tid == 0 && hi_all) atomicAdd(row + NHB, hi_all);
+    }
+    if (p.x == p.y) return;                          /* nothing was staged */
     if (!__syncthreads_or(cnt != 0u)) return;
     for (uint32_t i = tid; i < (uint32_t)NHB; i += WG) h[i] = 0u;
     const uint32_t top = (p.z - 1u) >> p.w;
@@ -217,10 +228,13 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
         }
     }
     wg_sync();
-    hist_flush(h, hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * NHB, NHB);
+    hist_flush(h, row, NHB);
 }
 
-/* Per staging segment of the buckets decided from staged elements (PATH_CAND, PATH_BAND), with
+/* PLAN (the gradient): every workgroup first makes its bucket's plan for itself from the window's bins, 33 KB that the L2
+ * holds; a kernel of its own for it was one more that the next had to wait for (ResNet-50's 161 buckets: 9.0 + 9.9 us, so
+ * 12.8; BERT's 199: 9.2 + 10.2, so 15.3; one bucket of 1 Mi elements: 6.0 + 5.4, so 7.0).
+ * Then, per staging segment of the buckets decided from staged elements (PATH_CAND, PATH_BAND), with
  * b0 the leading bits of the bucket's k-th key: G = entries above b0 (plus, in band mode, the elements
  * above the band the streaming pass counted).  The keys of the entries that share b0, the only undecided
  * ones, go to the bucket's list (the undecided key bits and the segment's number inside the workgroup in one
@@ -233,7 +247,9 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
  * by row (64 entries), so its work follows the number of entries and not the longest segment; lane l
  * of every wavefront keeps the count of segment l, from the ballots of the rows and the part of each row
  * that belongs to it. */
+template <bool PLAN>
 __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw,
+                                                     const uint32_t *__restrict__ hist,
                                                      uint32_t *__restrict__ cursor, uint2 *__restrict__ part,
                                                      uint32_t *__restrict__ lkey, uint32_t *__restrict__ err, const float *__restrict__ r)
 {
@@ -248,9 +264,42 @@ __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const 
     const bool mine = ms < s1;
     const uint32_t mcnt = mine ? c.cnt[ms] : 0u;
     uint32_t mg0 = mine ? c.G[ms] : 0u;              /* band mode: elements above the band, counted by the streaming pass */
-    const uint32_t path = t.fast[b], b0 = t.T[b], sh = t.sh[b];     /* b0: the key bits from position sh up */
     const KeyPar p = t.par[b];
-    if (path != PATH_CAND && path != PATH_BAND) return;      /* same for the whole workgroup */
+    uint32_t path, b0, sh;                           /* b0: the key bits from position sh up */
+    if constexpr (PLAN) {
+        /* the bucket's plan, made by each of its workgroups for itself, four bins of the window per thread from the top */
+        const uint32_t seg0 = t.tile0[b], segs_b = t.tile0[b + 1] - seg0, want = t.k[b], ovf = t.ovf[b];
+        const uint32_t *row = hist + (uint64_t)b * NHC * HROW;
+        uint32_t h[4] = {0u, 0u, 0u, 0u}, n_hi = 0;
+#pragma unroll
+        for (uint32_t q = 0; q < NHC; ++q) {
+            const uint4 v = reinterpret_cast<const uint4 *>(row + q * HROW)[tid];
+            h[0] += v.x; h[1] += v.y; h[2] += v.z; h[3] += v.w;
+            n_hi += row[q * HROW + NHB];
+        }
+        const uint32_t sum = (h[0] + h[1]) + (h[2] + h[3]);
+        uint32_t incl = wave_incl_scan(sum), tot = 0;
+        if (lane == 63) pre[wave] = incl;
+        wg_sync();
+#pragma unroll
+        for (uint32_t v = 0; v < WG / 64; ++v) { incl += v < wave ? pre[v] : 0u; tot += pre[v]; }
+        uint64_t acc = (uint64_t)n_hi + incl - sum;
+        if (acc < want && want <= acc + sum) {       /* at most one thread */
+            uint32_t i = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < 3; ++u) if (i == u && acc + h[u] < want) { acc += h[u]; ++i; }
+            cg[0] = 4u * tid + i; cg[1] = (uint32_t)acc; cg[2] = i == 0 ? h[0] : i == 1 ? h[1] : i == 2 ? h[2] : h[3];
+        }
+        wg_sync();
+        const Plan q = plan_bucket(t, b, p, want, n_hi, tot, n_hi < want && (uint64_t)n_hi + tot >= want, cg[0], cg[1], cg[2], ovf, segs_b);
+        if (s0 == seg0 && tid == 0) plan_store(t, b, q);
+        path = q.path; b0 = q.T; sh = q.sh;
+        if (path != PATH_CAND && path != PATH_BAND) return;      /* same for the whole workgroup */
+        wg_sync();                                   /* pre and cg are written again */
+    } else {
+        path = t.fast[b]; b0 = t.T[b]; sh = t.sh[b];
+        if (path != PATH_CAND && path != PATH_BAND) return;
+    }
     if (p.y == NONE) mg0 = 0u;                       /* no band was staged: the staged entries hold everything above */
     const bool dense = mcnt > SEG_CAP;               /* an overflowed segment is read from the dense accumulator, where nothing is missing */
     const uint32_t len = dense ? 0u : mcnt;
@@ -732,23 +781,37 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
                                                const uint32_t *__restrict__ chunk_seg, float *__restrict__ r,
                                                uint32_t *__restrict__ idx_out, void *__restrict__ val,
                                                float *__restrict__ scales, uint32_t *__restrict__ err,
-                                               uint64_t n_chunks, uint32_t cpw)
+                                               uint64_t n_chunks, uint32_t cpw, uint32_t *__restrict__ hist,
+                                               const double *__restrict__ tile_sq, double *__restrict__ l2sq)
 {
-    __shared__ float sv[ENC_BLK];
+    __shared__ __align__(16) float sv[ENC_BLK];
     __shared__ uint32_t si[ENC_BLK];
     __shared__ float red[ENC_T / 64];
     __shared__ uint32_t sh, filled;
+    if (blockIdx.x < t.B) {
+        /* The first workgroups keep the buckets' records: the norm, and what the plan was made from left clean for the next
+         * call.  (In k_select_finish, whose time all of it would add to, 4 us.) */
+        const uint32_t b = blockIdx.x;
+        bucket_sq<ENC_T>(t, b, tile_sq, reinterpret_cast<double *>(sv), l2sq + b);
+        for (uint32_t i = threadIdx.x * 4u; i < NHC * HROW; i += ENC_T * 4u) *reinterpret_cast<uint4 *>(hist + (uint64_t)b * NHC * HROW + i) = make_uint4(0u, 0u, 0u, 0u);
+        if (threadIdx.x == 0) {
+            if (t.k[b] == 0u) plan_empty(t, b);
+            t.ovf[b] = 0u;
+        }
+        return;
+    }
+    const uint32_t bid = blockIdx.x - t.B;
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
     constexpr uint32_t ENC_WAVES = ENC_T / 64;
     const uint32_t tid = threadIdx.x;
     /* a workgroup takes cpw consecutive chunks (one, unless the payload has very many) */
-    const uint64_t cend = min(n_chunks, ((uint64_t)blockIdx.x + 1) * cpw);
+    const uint64_t cend = min(n_chunks, ((uint64_t)bid + 1) * cpw);
     if (cpw > 1) {
         /* all of them in one bucket that is not coded here: nothing to do */
-        const uint32_t bf = chunk_b[(uint64_t)blockIdx.x * cpw], bl = chunk_b[cend - 1];
+        const uint32_t bf = chunk_b[(uint64_t)bid * cpw], bl = chunk_b[cend - 1];
         if (bf == bl && t.fast[bf] != PATH_CAND) return;
     }
-    for (uint64_t cid = (uint64_t)blockIdx.x * cpw; cid < cend; ++cid) {
+    for (uint64_t cid = (uint64_t)bid * cpw; cid < cend; ++cid) {
     const uint32_t b = chunk_b[cid];
     const uint32_t sFirst = chunk_seg[cid];          /* meaningful for PATH_CAND buckets only, like the next one */
     const uint32_t sNext = cid + 1 < n_chunks ? chunk_seg[cid + 1] : 0u;
