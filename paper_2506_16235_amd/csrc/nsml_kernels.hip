@@ -709,18 +709,18 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         {
             const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
             const uint64_t nc64e = c->NC;
-            /* very many chunks: fewer, longer-lived workgroups (and at most 2^22 of them: 2^32 threads cannot be launched) */
-            const uint64_t cpw64 = c->NC > (1ull << 14) ? std::max<uint64_t>(16u, (c->NC + (1u << 22) - 1) >> 22) : 1u;
-            const uint32_t cpw = (uint32_t)cpw64, egrid2 = (uint32_t)((c->NC + cpw64 - 1) / cpw64);
             /* Threads per chunk: 256 once there are two workgroups for every compute unit, unless the chunks are long
              * (8-bit codes in chunks of 2048, 256 / 512 threads, us: 2000 buckets of 5000 elements at 0.001, five
              * survivors a chunk, 22 / 45; 600 of 30000 at 0.1, 1500 a chunk, 32 / 45; fewer workgroups: ResNet-50's
              * 165 chunks of 156 survivors 25 / 18, 279 of 940 22 / 20; full chunks: 3072 of 2048 190 / 182). */
             const bool narrow = c->NC >= 2u * (uint64_t)c->n_cu && c->K <= 1900u * c->NC;
+            /* A workgroup per chunk; not of very many (2^32 threads cannot be launched), nor beyond a ratio of an eighth, where
+             * all but the smallest buckets are coded by k_hard. */
+            const uint32_t egrid2 = (uint32_t)std::min<uint64_t>(c->NC, c->K * 8u > n ? (narrow ? 4u : 2u) * (uint64_t)c->n_cu : 16384u);
 #define NSML_ENCODE(BITS_)                                                                                                              \
     do {                                                                                                                                 \
-        if (narrow) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 256>), B + egrid2, 256, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);  \
-        else LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 512>), B + egrid2, 512, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, cpw, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);         \
+        if (narrow) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 256>), B + egrid2, 256, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);  \
+        else LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 512>), B + egrid2, 512, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);         \
     } while (0)
             switch (bits) {
             case 32: NSML_ENCODE(32); break;

@@ -714,12 +714,14 @@ __device__ __forceinline__ uint32_t gather_segments(const Cand &c, uint32_t sA, 
         float x[SB][CU];
         uint32_t li[SB][CU];
         auto fetch = [&](uint32_t v, uint32_t i0) {
-            const uint64_t base = (uint64_t)(q0 + v * GROUPS + tid / GROUP) * SEG_CAP;
+            const uint64_t base = (uint64_t)(q0 + v * GROUPS + tid / GROUP) * SEG_CAP + (i0 + gl);
+            const float *pv = c.val + base;
+            const uint32_t *pi = c.idx + base;
 #pragma unroll
             for (uint32_t u = 0; u < CU; ++u) {
-                const uint32_t i = i0 + u * GROUP + gl;
-                x[v][u] = i < cnt[v] ? c.val[base + i] : 0.0f;
-                li[v][u] = i < cnt[v] ? c.idx[base + i] : 0u;
+                const bool in = i0 + gl + u * GROUP < cnt[v];
+                x[v][u] = in ? pv[u * GROUP] : 0.0f;
+                li[v][u] = in ? pi[u * GROUP] : 0u;
             }
         };
 #pragma unroll
@@ -772,16 +774,59 @@ __device__ __forceinline__ void gather_survivors(const Cand &c, uint32_t sA, uin
     if ((threadIdx.x & 63u) == 0u && got) atomicAdd(filled, got);
 }
 
+/* Codes of four values: rint(x / scale) of the correctly rounded quotient, clamped; 0 where the scale is.
+ * The product with the reciprocal differs from that quotient by less than 4e-5 (v_rcp_f32 is
+ * good to 2^-23, the two roundings add 2^-23, and the quotient is below 128.5), so away from the middle between two codes it gives the same code; the few
+ * values near one, and what is not a finite number, are divided. */
+template <int BITS>
+__device__ __forceinline__ void quantize_four(const float (&x)[4], float scale, int (&q)[4])
+{
+    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
+    const float inv = __builtin_amdgcn_rcpf(scale);
+    bool sure = true;
+    float w[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float y = __fmul_rn(x[j], inv);
+        w[j] = rintf(y);
+        sure = sure && fabsf(__fsub_rn(y, w[j])) < 0.4999f;      /* (false for NaN) */
+    }
+    if (!sure) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = scale != 0.0f ? rintf(__fdiv_rn(x[j], scale)) : 0.0f;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = (int)fminf(fmaxf(w[j], -QMAX), QMAX);
+}
+
+/* Largest over the wavefront, the same in all lanes. */
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_max(float v)
+{
+    const int i = __float_as_int(v);
+    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xF, false)));
+}
+__device__ __forceinline__ float wave_max(float v)
+{
+    v = dpp_max<0x111, 0xF>(v);
+    v = dpp_max<0x112, 0xF>(v);
+    v = dpp_max<0x114, 0xF>(v);
+    v = dpp_max<0x118, 0xF>(v);
+    v = dpp_max<0x142, 0xA>(v);
+    v = dpp_max<0x143, 0xC>(v);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
 /* One workgroup per chunk of `chunk` consecutive survivors of a PATH_CAND bucket: gather,
  * absmax, scale, codes, packing, indices, and the coding error left in the residual.  Every
  * floating-point step is a single correctly rounded binary32 operation.  A chunk longer than
  * ENC_BLK is gathered block by block, once for its absmax and once more for the codes. */
 template <int BITS, uint32_t ENC_T>
-__global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
+__global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
                                                const uint32_t *__restrict__ chunk_seg, float *__restrict__ r,
                                                uint32_t *__restrict__ idx_out, void *__restrict__ val,
                                                float *__restrict__ scales, uint32_t *__restrict__ err,
-                                               uint64_t n_chunks, uint32_t cpw, uint32_t *__restrict__ hist,
+                                               uint64_t n_chunks, uint32_t *__restrict__ hist,
                                                const double *__restrict__ tile_sq, double *__restrict__ l2sq)
 {
     __shared__ __align__(16) float sv[ENC_BLK];
@@ -804,18 +849,22 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
     constexpr uint32_t ENC_WAVES = ENC_T / 64;
     const uint32_t tid = threadIdx.x;
-    /* a workgroup takes cpw consecutive chunks (one, unless the payload has very many) */
-    const uint64_t cend = min(n_chunks, ((uint64_t)bid + 1) * cpw);
-    if (cpw > 1) {
-        /* all of them in one bucket that is not coded here: nothing to do */
-        const uint32_t bf = chunk_b[(uint64_t)bid * cpw], bl = chunk_b[cend - 1];
-        if (bf == bl && t.fast[bf] != PATH_CAND) return;
+    /* A workgroup takes the chunks bid, bid + grid, ..: its only one, or up to 64 at a time, of which the lanes
+     * first find those that are coded here (of a workgroup each, 2742 chunks of other paths took 15 us to skip, so 5) */
+    const uint32_t grid = gridDim.x - t.B, lane = tid & 63;
+    const bool single = grid == n_chunks;
+    for (uint64_t c0 = bid; c0 < n_chunks; c0 += 64ull * grid) {
+    uint64_t todo = 1ull;
+    if (!single) {
+        const uint64_t cl = c0 + (uint64_t)lane * grid;
+        todo = __ballot(cl < n_chunks && t.fast[chunk_b[min(cl, n_chunks - 1u)]] == PATH_CAND);
     }
-    for (uint64_t cid = (uint64_t)bid * cpw; cid < cend; ++cid) {
+    for (; todo; todo &= todo - 1ull) {
+    const uint64_t cid = c0 + (uint64_t)__builtin_ctzll(todo) * grid;
     const uint32_t b = chunk_b[cid];
     const uint32_t sFirst = chunk_seg[cid];          /* meaningful for PATH_CAND buckets only, like the next one */
     const uint32_t sNext = cid + 1 < n_chunks ? chunk_seg[cid + 1] : 0u;
-    if (t.fast[b] != PATH_CAND) continue;
+    if (single && t.fast[b] != PATH_CAND) return;
     const uint64_t cb = cid - t.C[b];
     const uint64_t j0c = cb * t.chunk;                         /* first survivor of the chunk, bucket-local */
     const uint32_t cnt_c = (uint32_t)min((uint64_t)t.chunk, (uint64_t)t.k[b] - j0c);
@@ -825,14 +874,23 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
     const uint64_t lo = t.off[b], Pb = t.P[b];
     uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
 
-    auto block_absmax = [&](uint32_t n) {
-        float m = 0.0f;
-        for (uint32_t i = tid; i < n; i += ENC_T) m = fmaxf(m, fabsf(sv[i]));
+    /* a thread holds PER survivors of the block, ENC_T apart: the lanes of a wavefront hold consecutive ones */
+    constexpr uint32_t PER = ENC_BLK / ENC_T;
+    static_assert(PER % 4u == 0u, "coded four at a time");
+    float xv[PER];
+    auto fetch_values = [&](uint32_t n) {
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+        for (uint32_t h = 0; h < PER; ++h) { const uint32_t i = h * ENC_T + tid; xv[h] = i < n ? sv[i] : 0.0f; }
+    };
+    auto block_absmax = [&]() {
+        float m = 0.0f;
+#pragma unroll
+        for (uint32_t h = 0; h < PER; ++h) m = fmaxf(m, fabsf(xv[h]));
+        m = wave_max(m);
         wg_sync();
-        if ((tid & 63) == 0) red[tid >> 6] = m;
+        if (lane == 0) red[tid >> 6] = m;
         wg_sync();
+#pragma unroll
         for (uint32_t w = 0; w < ENC_WAVES; ++w) m = fmaxf(m, red[w]);
         return m;
     };
@@ -858,56 +916,52 @@ __global__ __launch_bounds__(ENC_T) void k_encode(Tables t, Cand c, const uint32
         for (uint32_t blk0 = 0; blk0 < cnt_c; blk0 += ENC_BLK) {
             const uint32_t n = min(ENC_BLK, cnt_c - blk0);
             gather(blk0, n);
-            m = fmaxf(m, block_absmax(n));
+            fetch_values(n);
+            m = fmaxf(m, block_absmax());
         }
     for (uint32_t blk0 = 0; blk0 < cnt_c; blk0 += ENC_BLK) {
         const uint32_t n = min(ENC_BLK, cnt_c - blk0);
         gather(blk0, n);
+        fetch_values(n);
         float scale = 0.0f;
         if (BITS <= 8) {
-            if (!long_chunk) m = block_absmax(n);
+            if (!long_chunk) m = block_absmax();
             scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
             if (tid == 0 && blk0 == 0) scales[t.S[b] + cb] = scale;
         }
         const uint64_t jb = j0c + blk0;                        /* bucket-local number of the block's first survivor */
-        /* a thread takes pairs of consecutive survivors (a 4-bit pair is one byte) */
 #pragma unroll
-        for (int u = 0; u < (int)(ENC_BLK / (2 * ENC_T)); ++u) {
-            const uint32_t i0 = 2 * (tid + u * ENC_T);
-            if (i0 >= n) continue;
-            const int have = (i0 + 1 < n) ? 2 : 1;
-            float res[2] = {0.0f, 0.0f};
-            int q[2] = {0, 0};
-            uint32_t li[2] = {si[i0], have == 2 ? si[i0 + 1] : 0u};
+        for (uint32_t h0 = 0; h0 < PER; h0 += 4) {
+            float x4[4];
+            int q[4] = {0, 0, 0, 0};
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                if (hh >= have) continue;
-                const float xv = sv[i0 + hh];
+            for (int h = 0; h < 4; ++h) x4[h] = xv[h0 + h];
+            if (BITS <= 8) quantize_four<BITS>(x4, scale, q);
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const uint32_t i = (h0 + h) * ENC_T + tid;
+                /* a pair's codes in one byte at 4 bits: the odd lane's comes over (0 beyond the last) */
+                const int odd = BITS == 4 ? __builtin_amdgcn_mov_dpp(q[h], 0xF5, 0xF, 0xF, false) : 0;      /* lanes 1 1 3 3 */
+                if (i >= n) continue;
                 float deq;
                 if (BITS == 32) {
-                    reinterpret_cast<float *>(vb)[jb + i0 + hh] = xv;
-                    deq = xv;
+                    reinterpret_cast<float *>(vb)[jb + i] = x4[h];
+                    deq = x4[h];
                 } else if (BITS == 16) {
-                    const __half hv = __float2half_rn(xv);
-                    reinterpret_cast<__half *>(vb)[jb + i0 + hh] = hv;
+                    const __half hv = __float2half_rn(x4[h]);
+                    reinterpret_cast<__half *>(vb)[jb + i] = hv;
                     deq = __half2float(hv);
                 } else {
-                    if (scale != 0.0f) {
-                        float tq = rintf(__fdiv_rn(xv, scale));
-                        tq = fminf(fmaxf(tq, -QMAX), QMAX);
-                        q[hh] = (int)tq;
-                    }
-                    deq = __fmul_rn((float)q[hh], scale);
-                    if (BITS == 8) reinterpret_cast<int8_t *>(vb)[jb + i0 + hh] = (int8_t)q[hh];
+                    deq = __fmul_rn((float)q[h], scale);
+                    if (BITS == 8) reinterpret_cast<int8_t *>(vb)[jb + i] = (int8_t)q[h];
+                    else if (!(lane & 1u)) vb[(jb + i) >> 1] = (uint8_t)((q[h] & 0xF) | ((odd & 0xF) << 4));
                 }
-                res[hh] = __fsub_rn(xv, deq);
-                idx_out[Pb + jb + i0 + hh] = li[hh];
+                const uint32_t li = si[i];
+                idx_out[Pb + jb + i] = li;
+                r[lo + li] = __fsub_rn(x4[h], deq);
             }
-            if (BITS == 4) vb[(jb + i0) >> 1] = (uint8_t)((q[0] & 0xF) | ((q[1] & 0xF) << 4));
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh)
-                if (hh < have) r[lo + li[hh]] = res[hh];
         }
+    }
     }
     }
 }
@@ -1117,49 +1171,6 @@ constexpr uint32_t HTH = 512;                      /* threads of a workgroup of 
 constexpr uint32_t DENC_ROWS = DENC_STEP / HTH / 4; /* 16-byte accesses per thread and step */
 constexpr uint32_t DENC_WT = DENC_STEP / (HTH / 64); /* consecutive elements of one wavefront per step */
 constexpr uint32_t denc_cap(bool big) { return DENC_STEP + (big ? DENC_MAX_CHUNK : DENC_SMALL_CHUNK); }
-
-/* Codes of four values: rint(x / scale) of the correctly rounded quotient, clamped; 0 where the scale is.
- * The product with the reciprocal differs from that quotient by less than 4e-5 (v_rcp_f32 is
- * good to 2^-23, the two roundings add 2^-23, and the quotient is below 128.5), so away from the middle between two codes it gives the same code; the few
- * values near one, and what is not a finite number, are divided. */
-template <int BITS>
-__device__ __forceinline__ void quantize_four(const float (&x)[4], float scale, int (&q)[4])
-{
-    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
-    const float inv = __builtin_amdgcn_rcpf(scale);
-    bool sure = true;
-    float w[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float y = __fmul_rn(x[j], inv);
-        w[j] = rintf(y);
-        sure = sure && fabsf(__fsub_rn(y, w[j])) < 0.4999f;      /* (false for NaN) */
-    }
-    if (!sure) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) w[j] = scale != 0.0f ? rintf(__fdiv_rn(x[j], scale)) : 0.0f;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = (int)fminf(fmaxf(w[j], -QMAX), QMAX);
-}
-
-/* Largest over the wavefront, the same in all lanes. */
-template <int CTRL, int ROWS>
-__device__ __forceinline__ float dpp_max(float v)
-{
-    const int i = __float_as_int(v);
-    return fmaxf(v, __int_as_float(__builtin_amdgcn_update_dpp(i, i, CTRL, ROWS, 0xF, false)));
-}
-__device__ __forceinline__ float wave_max(float v)
-{
-    v = dpp_max<0x111, 0xF>(v);
-    v = dpp_max<0x112, 0xF>(v);
-    v = dpp_max<0x114, 0xF>(v);
-    v = dpp_max<0x118, 0xF>(v);
-    v = dpp_max<0x142, 0xA>(v);
-    v = dpp_max<0x143, 0xC>(v);
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
-}
 
 template <int BITS, bool BIG>       /* BIG: chunks of more than DENC_SMALL_CHUNK survivors */
 __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const Tables &t, const Cand &c,
