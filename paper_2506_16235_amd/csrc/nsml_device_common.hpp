@@ -460,6 +460,20 @@ __device__ __forceinline__ double wave_sum_last(double v)
     return v;
 }
 
+/* Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel moves: shifts by 1, 2,
+ * 4, 8 lanes inside each row of 16 (lanes shifted in from outside a row read 0), then lane 15 of
+ * rows 0 and 2 added to rows 1 and 3, then lane 31 added to rows 2 and 3. */
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+    return v;
+}
+
 /* Inclusive scan over the 256 threads of a workgroup: shuffles inside each wavefront, one
  * exchange of the four wavefront totals through LDS.  tmp needs WG words; on return
  * tmp[WG - 1] holds the grand total (callers read it, then synchronise before reusing tmp). */

@@ -36,52 +36,59 @@ constexpr uint32_t SEL_THREADS = 1024;     /* k_select_finish workgroup: 16 wave
 constexpr uint32_t SEL_WAVES = SEL_THREADS / 64;
 constexpr uint32_t ENC_BLK = 2048;         /* survivors gathered in LDS at a time */
 
-/* Inclusive scan of 64-bit values over a workgroup of NW wavefronts; tmp: NW words of LDS. */
-template <uint32_t NW>
-__device__ __forceinline__ uint64_t block_incl_scan64(uint64_t x, uint64_t *tmp, uint64_t &total)
+/* Inclusive scan over a workgroup of 16 wavefronts, total the sum of all; tmp: 16 words of LDS.  A wavefront's total comes
+ * from its scan, the wavefronts before it from a scan of the 16 totals that every row of 16 lanes does for itself.
+ * (With shuffles and 64-bit words a search of the digit below took 1.7 us, so 0.6.) */
+__device__ __forceinline__ uint32_t scan_totals(const uint32_t *tmp, uint32_t &total)
 {
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t hi = __shfl_up((uint32_t)(x >> 32), d, 64), lo = __shfl_up((uint32_t)x, d, 64);
-        if (lane >= (uint32_t)d) x += ((uint64_t)hi << 32) | (uint64_t)lo;
-    }
-    if (lane == 63) tmp[wave] = x;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t v = tmp[threadIdx.x & 15u];
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)v, 15);
+    return wave ? (uint32_t)__builtin_amdgcn_readlane((int)v, (int)wave - 1) : 0u;
+}
+__device__ __forceinline__ uint32_t block16_incl_scan(uint32_t x, uint32_t *tmp, uint32_t &total)
+{
+    x = wave_incl_scan(x);
+    if ((threadIdx.x & 63u) == 63u) tmp[threadIdx.x >> 6] = x;
     wg_sync();
-    uint64_t before = 0;
-    total = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < NW; ++w) { const uint64_t v = tmp[w]; before += w < wave ? v : 0ull; total += v; }
+    x += scan_totals(tmp, total);
     wg_sync();
-    return x + before;
+    return x;
 }
 
 /* The digit of an LDS histogram of NB bins that holds the want-th entry counted from the top
- * digit down (1 <= want <= number of entries).  Every thread of the NW-wavefront workgroup must
+ * digit down (1 <= want <= number of entries).  Every thread of the workgroup of 16 wavefronts must
  * call it; res (3 words of LDS) receives digit, entries in higher digits, entries in the digit.
  * Returns false (in every thread) when the histogram holds fewer than `want` entries. */
-template <int NB, uint32_t NW>
-__device__ __forceinline__ bool find_digit_lds(const uint32_t *h, uint32_t want, uint64_t *tmp, uint32_t *res)
+template <int NB>
+__device__ __forceinline__ bool find_digit_lds(const uint32_t *h, uint32_t want, uint32_t *tmp, uint32_t *res)
 {
-    constexpr int NT = NW * 64;
-    constexpr int PER = NB >= NT ? NB / NT : 1;
-    const int top = NB - 1 - (int)threadIdx.x * PER;
-    uint32_t cnt[PER], sum = 0;
+    /* four digits per thread from the top */
+    const int top = NB - 1 - (int)threadIdx.x * 4;
+    uint32_t cnt[4] = {0u, 0u, 0u, 0u}, sum = 0;
+    if (top >= 3) {
+        const uint4 v = *reinterpret_cast<const uint4 *>(h + top - 3);
+        cnt[0] = v.w; cnt[1] = v.z; cnt[2] = v.y; cnt[3] = v.x;
+        sum = (cnt[0] + cnt[1]) + (cnt[2] + cnt[3]);
+    }
+    uint32_t total;
+    uint32_t incl = wave_incl_scan(sum);
+    if ((threadIdx.x & 63u) == 63u) tmp[threadIdx.x >> 6] = incl;
+    wg_sync();
+    incl += scan_totals(tmp, total);
+    uint32_t acc = incl - sum;
+    if (acc < want && want <= incl) {
+        uint32_t q = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) { const int d = top - i; cnt[i] = d >= 0 ? h[d] : 0u; sum += cnt[i]; }
-    uint64_t total;
-    const uint32_t incl = (uint32_t)block_incl_scan64<NW>((uint64_t)sum, tmp, total);
-    const uint32_t before = incl - sum;
-    if (before < want && want <= incl) {
-        uint32_t acc = before;
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if (acc + cnt[i] >= want) { res[0] = (uint32_t)(top - i); res[1] = acc; res[2] = cnt[i]; break; }
-            acc += cnt[i];
-        }
+        for (uint32_t i = 0; i < 3; ++i) if (q == i && acc + cnt[i] < want) { acc += cnt[i]; ++q; }
+        res[0] = (uint32_t)top - q; res[1] = acc; res[2] = q == 0 ? cnt[0] : q == 1 ? cnt[1] : q == 2 ? cnt[2] : cnt[3];
     }
     wg_sync();
-    return (uint32_t)total >= want;
+    return total >= want;
 }
 
 /* Largest i in [lo, hi) with f(i) <= x, for a non-decreasing f with f(lo) <= x; the whole
@@ -100,20 +107,6 @@ __device__ __forceinline__ uint32_t wg_search_le(uint32_t lo, uint32_t hi, uint6
         hi = np + step < hi ? np + step : hi;
     }
     return lo;
-}
-
-/* Inclusive prefix sum over the 64 lanes of a wavefront with data-parallel moves: shifts by 1, 2,
- * 4, 8 lanes inside each row of 16 (lanes shifted in from outside a row read 0), then lane 15 of
- * rows 0 and 2 added to rows 1 and 3, then lane 31 added to rows 2 and 3. */
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
-{
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
-    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
-    return v;
 }
 
 /* ------------------------------------------------------------------ k_select_count */
@@ -455,13 +448,6 @@ constexpr uint32_t FIN_AT_UPOS = FIN_AT_UPRE + SEL_THREADS + 1;
 constexpr uint32_t FIN_POOL = FIN_AT_UPOS + SEL_THREADS;
 static_assert(NB1 <= FIN_MAX_SEGS, "the level-1 histogram overlaps the keys");
 
-struct FinShared {
-    uint32_t *pool;      /* FIN_POOL words */
-    uint32_t *h2;        /* NB2 */
-    uint64_t *tmp;       /* SEL_WAVES */
-    uint32_t *res;       /* 4 */
-};
-
 /* Exclusive prefixes of (elements above T, elements equal to T) over the segments [seg_lo, seg_hi) of a
  * bucket, in place over the per-segment counts, and for every chunk of the payload the segment that holds
  * its first survivor.  A round takes PER consecutive segments per thread.  run: the two totals of the
@@ -469,57 +455,59 @@ struct FinShared {
  * to T among its undecided keys. */
 template <uint32_t PER, typename F>
 __device__ __forceinline__ void finish_prefixes(const Tables &t, const Cand &c, uint32_t b, uint32_t seg_lo,
-                                                uint32_t seg_hi, uint32_t e_b, uint64_t &run,
-                                                uint32_t *__restrict__ chunk_seg, uint64_t *tmp, F count)
+                                                uint32_t seg_hi, uint32_t e_b, uint32_t &run_g, uint32_t &run_e,
+                                                uint32_t *__restrict__ chunk_seg, uint32_t *tmp, F count)
 {
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, wave = tid >> 6;
     const uint32_t rounds = (seg_hi - seg_lo + SEL_THREADS * PER - 1) / (SEL_THREADS * PER);
-    const uint64_t Cb = t.C[b];
-    const uint32_t chunk = t.chunk;
+    uint32_t *first = chunk_seg ? chunk_seg + t.C[b] : nullptr;
+    const uint32_t chunk = t.chunk, chunkSh = t.chunkSh;
     uint32_t g_next[PER];
 #pragma unroll
     for (uint32_t j = 0; j < PER; ++j) { const uint32_t s = seg_lo + tid * PER + j; g_next[j] = s < seg_hi ? c.G[s] : 0u; }
     for (uint32_t r = 0; r < rounds; ++r) {
         const uint32_t s0 = seg_lo + (r * SEL_THREADS + tid) * PER;
-        uint64_t v[PER], sum = 0;
+        uint32_t vg[PER], ve[PER], sum_g = 0, sum_e = 0;
 #pragma unroll
         for (uint32_t j = 0; j < PER; ++j) {
             uint32_t g = g_next[j], q = 0;
             if (r + 1 < rounds) { const uint32_t sn = s0 + SEL_THREADS * PER + j; g_next[j] = sn < seg_hi ? c.G[sn] : 0u; }   /* fetched under this round's work */
             count(s0 + j, g, q);
-            v[j] = ((uint64_t)g << 32) | (uint64_t)q;
-            sum += v[j];
+            vg[j] = g; ve[j] = q;
+            sum_g += g; sum_e += q;
         }
-        uint64_t tt;
-        const uint64_t incl = block_incl_scan64<SEL_WAVES>(sum, tmp, tt);
-        uint64_t excl = run + incl - sum;
+        uint32_t Gp = wave_incl_scan(sum_g), Ep = wave_incl_scan(sum_e), tot_g, tot_e;
+        if ((tid & 63u) == 63u) { tmp[wave] = Gp; tmp[SEL_WAVES + wave] = Ep; }
+        wg_sync();
+        Gp += run_g + scan_totals(tmp, tot_g) - sum_g;
+        Ep += run_e + scan_totals(tmp + SEL_WAVES, tot_e) - sum_e;
 #pragma unroll
         for (uint32_t j = 0; j < PER; ++j) {
             const uint32_t s = s0 + j;
             if (s < seg_hi) {
-                const uint32_t Gp = (uint32_t)(excl >> 32), Ep = (uint32_t)excl;
                 c.G[s] = Gp;
                 c.E[s] = Ep;
                 /* survivors of this segment have ranks [r0, r1): the chunks that start among them */
-                const uint64_t r0 = (uint64_t)Gp + min(e_b, Ep);
-                const uint64_t r1 = (uint64_t)Gp + (v[j] >> 32) + min((uint64_t)e_b, (uint64_t)Ep + (uint32_t)v[j]);
-                if (chunk_seg && r1 > r0)                /* not for the weight stage: its ranks are no payload positions */
-                    for (uint64_t cb = (r0 + chunk - 1) / chunk; cb * chunk < r1; ++cb) chunk_seg[Cb + cb] = s;
+                const uint32_t r0 = Gp + min(e_b, Ep), r1 = Gp + vg[j] + min(e_b, Ep + ve[j]);
+                if (first && r1 > r0)                    /* not for the weight stage: its ranks are no payload positions */
+                    for (uint64_t cb = chunkSh < 32u ? ((uint64_t)r0 + chunk - 1u) >> chunkSh : ((uint64_t)r0 + chunk - 1u) / chunk; cb * chunk < r1; ++cb) first[cb] = s;
             }
-            excl += v[j];
+            Gp += vg[j];
+            Ep += ve[j];
         }
-        run += tt;
+        run_g += tot_g;
+        run_e += tot_e;
+        wg_sync();                                       /* tmp is written again */
     }
 }
 /* The bucket's threshold and tie allowance, once its prefixes are done. */
-__device__ __forceinline__ void finish_state(const Tables &t, uint32_t b, uint32_t T, uint32_t e_b, uint32_t kb, uint64_t run,
+__device__ __forceinline__ void finish_state(const Tables &t, uint32_t b, uint32_t T, uint32_t e_b, uint32_t kb, uint32_t above, uint32_t ties,
                                              uint32_t *__restrict__ err)
 {
     if (threadIdx.x != 0) return;
     t.T[b] = T;
     t.need[b] = e_b;
     /* above + admitted ties must be exactly k */
-    const uint32_t above = (uint32_t)(run >> 32), ties = (uint32_t)run;
     if (above + e_b != kb || e_b > ties) err[0] = 1u;
 }
 
@@ -540,7 +528,9 @@ __device__ __forceinline__ void add_shared(uint32_t *h, uint32_t at, uint32_t ad
  * then every segment's place in the survivor order.  The keys are read once per step, four per thread in
  * flight, and kept in LDS when they fit.  A bucket of more than FIN_MAX_SEGS segments goes through every step
  * in windows of so many, a range of the list's parts each (110 M elements in one bucket, 0.1 %: 93 us; by one
- * thread per segment 264).  PATH_ZERO buckets arrive with T = 0 and e known and only get the
+ * thread per segment 264).  Bound by the latency of its steps: with scans by data-parallel moves, 32-bit prefixes and shifts for
+ * the chunk numbers 8.1 us for ResNet-50's 161 buckets, 16 for BERT's 199, 7.4 for one of 1 Mi elements; with
+ * shuffles, 64-bit words and 64-bit divisions 12.7, 22, 11.3.  PATH_ZERO buckets arrive with T = 0 and e known and only get the
  * prefixes.  in_windows: diagnostic, windows of two parts and nothing kept in LDS. */
 __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c, const uint32_t *__restrict__ sel0, uint32_t selSh,
                                                                uint32_t *__restrict__ cursor, const uint2 *__restrict__ part,
@@ -548,9 +538,9 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
                                                                uint32_t *__restrict__ chunk_seg,
                                                                uint32_t *__restrict__ err, int in_windows)
 {
-    __shared__ uint32_t pool[FIN_POOL];
-    __shared__ uint32_t h2[NB2];
-    __shared__ uint64_t tmp[SEL_WAVES];
+    __shared__ __align__(16) uint32_t pool[FIN_POOL];
+    __shared__ __align__(16) uint32_t h2[NB2];
+    __shared__ uint32_t tmp[2 * SEL_WAVES];
     __shared__ uint32_t res[4];
     const uint32_t b = blockIdx.x, tid = threadIdx.x;
     const uint32_t path = t.fast[b], kb = t.k[b];
@@ -563,16 +553,16 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     const uint32_t seg_lo = t.tile0[b], seg_hi = t.tile0[b + 1];
     const uint32_t b0 = t.T[b];                      /* the key bits from position sh up; PATH_ZERO: the full key (0) */
     const uint32_t need0 = t.need[b], sh = t.sh[b];
-    uint64_t run = 0;
+    uint32_t run_g = 0, run_e = 0;
     if (path == PATH_ZERO) {
         /* the streaming pass counted non-zero (G) and zero (E) keys per segment; when a band from
          * key 1 up was staged as well, G holds the keys above the band and the staged ones add to it */
         const bool mixed = t.par[b].x != t.par[b].y;
-        finish_prefixes<4>(t, c, b, seg_lo, seg_hi, need0, run, chunk_seg, tmp,
+        finish_prefixes<4>(t, c, b, seg_lo, seg_hi, need0, run_g, run_e, chunk_seg, tmp,
                         [&](uint32_t s, uint32_t &g, uint32_t &q) {
                             if (s < seg_hi) { q += c.E[s]; if (mixed) g += c.cnt[s]; }
                         });
-        finish_state(t, b, 0u, need0, kb, run, err);
+        finish_state(t, b, 0u, need0, kb, run_g, run_e, err);
         return;
     }
     uint32_t *h1 = pool, *cnts = pool, *keys = pool + FIN_AT_KEYS, *upre = pool + FIN_AT_UPRE, *upos = pool + FIN_AT_UPOS;
@@ -588,12 +578,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
     auto window = [&](uint32_t w0) {
         const uint32_t wn = min(wun, nun - w0);
         if (!one) mine = tid < wn ? part[u0 + w0 + tid] : make_uint2(0u, 0u);
-        uint64_t tot64;
-        const uint32_t incl = (uint32_t)block_incl_scan64<SEL_WAVES>((uint64_t)mine.y, tmp, tot64);      /* (the window before has been consumed, too) */
+        uint32_t tot;
+        const uint32_t incl = block16_incl_scan(mine.y, tmp, tot);      /* (the window before has been consumed, too) */
         if (tid < wn) { upre[tid] = incl - mine.y; upos[tid] = mine.x; }
-        if (tid == 0) upre[wn] = (uint32_t)tot64;
+        if (tid == 0) upre[wn] = tot;
         wg_sync();
-        return (uint32_t)tot64;
+        return tot;
     };
     /* f(i, entry, segment number inside the window) for the n keys of the window */
     auto for_keys = [&](uint32_t w0, uint32_t n, auto f) {
@@ -644,7 +634,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
         });
     }
     wg_sync();
-    if (!find_digit_lds<NB1, SEL_WAVES>(h1, need0, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
+    if (!find_digit_lds<NB1>(h1, need0, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t d1 = res[0];
     const uint32_t need1 = need0 - res[1];
     auto last_digit = [&](uint32_t e) { if (((e >> SH1) & m1) == d1) add_shared(h2, e & (NB2 - 1), 1u); };
@@ -654,7 +644,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
         for (uint32_t w0 = 0; w0 < nun; w0 += wun) for_keys(w0, one ? n0 : window(w0), [&](uint32_t, uint32_t e, uint32_t) { last_digit(e); });
     }
     wg_sync();
-    if (!find_digit_lds<NB2, SEL_WAVES>(h2, need1, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
+    if (!find_digit_lds<NB2>(h2, need1, tmp, res)) { if (tid == 0) err[0] = 1u; return; }
     const uint32_t d2 = res[0];
     const uint32_t T = (b0 << sh) | (d1 << SH1) | d2;
     const uint32_t e_b = need1 - res[1];             /* ties admitted: 1 <= e_b <= keys equal to T */
@@ -676,12 +666,12 @@ __global__ __launch_bounds__(SEL_THREADS) void k_select_finish(Tables t, Cand c,
             for_keys(w0, n, [&](uint32_t, uint32_t e, uint32_t seg) { tally(e, seg); });
         }
         wg_sync();
-        finish_prefixes<4>(t, c, b, s_lo, s_hi, e_b, run, chunk_seg, tmp,
+        finish_prefixes<4>(t, c, b, s_lo, s_hi, e_b, run_g, run_e, chunk_seg, tmp,
                         [&](uint32_t s, uint32_t &g, uint32_t &q) {
                             if (s < s_hi) { const uint32_t v = cnts[s - s_lo]; g += v >> 16; q += v & 0xFFFFu; }
                         });
     }
-    finish_state(t, b, T, e_b, kb, run, err);
+    finish_state(t, b, T, e_b, kb, run_g, run_e, err);
 }
 
 /* ------------------------------------------------------------------ k_encode */
