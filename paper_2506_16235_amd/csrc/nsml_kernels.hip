@@ -601,7 +601,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     const bool none_pruned = weights && floor(0.5 * (1.0 - ratio) * (double)c->max_nb) < 1.0;
     if (none_pruned) weights = nullptr;
     const bool full = c->K == n && !c->force_dense && (bits >= 16 || TILE % c->chunk == 0);
-    const bool small = !weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B <= 2u * (uint32_t)c->n_cu;
+    const bool small = !weights && !c->force_dense && !c->force_rescan && c->max_nb <= SMALL_MAX && B < (1u << 22);      /* (2^32 threads cannot be launched) */
     if (stale && (full || small || weights || !presample)) {
         rc = make_tables(c, st);
         if (rc) return rc;
@@ -629,10 +629,10 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         return NSML_OK;
     }
 
-    /* Small buckets: the whole call in one launch.  A workgroup fills a compute unit, so its time goes in rounds,
-     * while the buckets share the chain's launches: the line is drawn at two rounds, where it takes about half of
-     * the chain's time (us, 1 % sent as 8-bit codes, this / the chain: 1 bucket of 32764 elements 39 / 69, 256 of
-     * them 51 / 124, 512 98 / 205; 512 of 500 26 / 86, of 40 26 / 70). */
+    /* Small buckets: the whole call in one launch.  A workgroup fills a compute unit, so its time goes in rounds of one
+     * bucket for each of them, and it is ahead of the chain of kernels however many there are (us, 1 % sent as 8-bit codes, this /
+     * the chain: 1 bucket of 32764 elements 31 / 34, 512 of them 89 / 115, 4000 of them 611 / 781; 1000 of 5000 50 / 94,
+     * 20000 of them 878 / 1617; 17000 of 45 521 / 1105). */
     if (small) {
         switch (bits) {
         case 32: LAUNCHB(c, KID_EF_EMIT, st, k_small<32>, B, SMALL_T, grad, residual, t, c->d_l2sq, idx, val, scales); break;

@@ -12,24 +12,16 @@ namespace {
  * all that a call costs.  Gradient and residual are read once into registers (a wavefront holds consecutive
  * elements, four of a row per lane), the k-th key is found digit by digit with histograms in LDS, ranks
  * come from ballots, chunk maxima from LDS, and payload and residual are written once.
- * 60007 elements in 24 buckets, 10 %, fp16: 27 us, by the chain 52. */
+ * Bound by the instructions of the passes over the registers (3 us for every 4096 elements) on top of about 8 us, so only the
+ * first digit is counted over all elements; the few keys that share it are listed, and the rest of the search is theirs.  Four
+ * rows of loads are in flight, and a phase keeps none of the last one's masks.  60007 elements in 24 buckets, 10 %, fp16: 19.8 us
+ * (25.2 with three passes and a row of loads at a time; by the chain 52); one of 32764, 1 % as 8-bit codes 31.4 (39.3), of 500 9.5 (13.2). */
 constexpr uint32_t SMALL_T = 1024;
 constexpr uint32_t SMALL_ROWS = 8;                                   /* rows of four elements per lane, at most */
 constexpr uint32_t SMALL_MAX = SMALL_T * SMALL_ROWS * 4 - 4;         /* elements, less the ones a bucket may start before a multiple of 4 */
 constexpr uint32_t SMALL_WAVES = SMALL_T / 64;
+constexpr uint32_t SMALL_LIST = 4096;                                /* undecided keys that are searched in a list */
 constexpr uint32_t SMALL_CHUNKS = SMALL_T * SMALL_ROWS * 4 / 8;      /* chunks have at least 8 survivors */
-
-/* Inclusive prefix over the workgroup's threads; tmp: SMALL_WAVES words. */
-__device__ __forceinline__ uint32_t small_incl_scan(uint32_t x, uint32_t *tmp)
-{
-    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t incl = wave_incl_scan(x);
-    if (lane == 63) tmp[wave] = incl;
-    wg_sync();
-    for (uint32_t w = 0; w < wave; ++w) incl += tmp[w];
-    wg_sync();
-    return incl;
-}
 
 template <int BITS>
 __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, float *__restrict__ r, Tables t, double *__restrict__ l2sq,
@@ -37,14 +29,15 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
 {
     constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;     /* (unused for 16 / 32 bits) */
     constexpr bool CODED = BITS <= 8;
-    __shared__ uint32_t hist[NB0];
+    __shared__ __align__(16) uint32_t hist[NB0];
     __shared__ uint32_t cmax[CODED ? SMALL_CHUNKS : 1];   /* a chunk's largest magnitude, then its scale */
-    __shared__ uint32_t code[CODED ? SMALL_T * SMALL_ROWS : 1];
-    __shared__ uint32_t tmp[SMALL_WAVES], wg_[SMALL_WAVES], we_[SMALL_WAVES], res[2];
+    __shared__ uint32_t code[CODED ? SMALL_T * SMALL_ROWS : SMALL_LIST];      /* first the undecided keys, then the codes */
+    __shared__ uint32_t tmp[SMALL_WAVES], wg_[SMALL_WAVES], we_[SMALL_WAVES], res[3], listed;
     __shared__ double red[SMALL_WAVES];
     const uint32_t b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint64_t lo = t.off[b], hi = t.off[b + 1], base = lo & ~3ull;
     const uint32_t kb = t.k[b], chunk = t.chunk;
+    uint32_t *list = code;
     if (hi == lo) {
         if (tid == 0) {
             l2sq[b] = 0.0;
@@ -60,33 +53,57 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
     float x[SMALL_ROWS][4];
     uint32_t valid = 0;                                                  /* four bits per row */
     double sq = 0.0;
+    constexpr uint32_t FLY = 4;                                          /* rows in flight */
 #pragma unroll
-    for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
+    for (uint32_t u0 = 0; u0 < SMALL_ROWS; u0 += FLY) {
+        f4 y[FLY], z[FLY];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) x[u][j] = 0.0f;
-        if (u < rows) {
-            const uint64_t gi = base + (uint64_t)(q0 + u * 64) * 4;
-            float y[4];
-            const uint32_t m = load_quad(g, gi, lo, hi, y);
-            load_quad(r, gi, lo, hi, x[u]);
-            valid |= m << (4 * u);
-            sq += (double)(__fmaf_rn(y[0], y[0], __fmul_rn(y[1], y[1])) + __fmaf_rn(y[2], y[2], __fmul_rn(y[3], y[3])));
+        for (uint32_t u = 0; u < FLY; ++u) {
+            const uint64_t gi = base + (uint64_t)(q0 + (u0 + u) * 64) * 4;
+            y[u] = z[u] = f4{0.f, 0.f, 0.f, 0.f};
+            if (u0 + u < rows && gi >= lo && gi + 4 <= hi) {
+                y[u] = *reinterpret_cast<const f4 *>(g + gi);
+                z[u] = *reinterpret_cast<const f4 *>(r + gi);
+                valid |= 0xFu << (4 * (u0 + u));
+            }
+        }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) x[u][j] = __fadd_rn(y[j], x[u][j]);
+        for (uint32_t u = 0; u < FLY; ++u) {
+            const uint64_t gi = base + (uint64_t)(q0 + (u0 + u) * 64) * 4;
+            if (u0 + u < rows && gi < hi && !((valid >> (4 * (u0 + u))) & 1u)) {
+                /* the bucket's first and last quad may be partly another's */
+                float ya[4], za[4];
+                valid |= load_quad(g, gi, lo, hi, ya) << (4 * (u0 + u));
+                load_quad(r, gi, lo, hi, za);
+                y[u] = f4{ya[0], ya[1], ya[2], ya[3]};
+                z[u] = f4{za[0], za[1], za[2], za[3]};
+            }
+            sq += (double)(__fmaf_rn(y[u].x, y[u].x, __fmul_rn(y[u].y, y[u].y)) + __fmaf_rn(y[u].z, y[u].z, __fmul_rn(y[u].w, y[u].w)));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[u0 + u][j] = __fadd_rn(y[u][j], z[u][j]);
         }
     }
     sq = wave_sum_last(sq);
     if (lane == 63) red[wave] = sq;
+    /* Keys, comparisons and masks of one phase are not kept for the next (the compiler would, and spill them). */
+    auto anew = [&]() {
+        asm volatile("" : "+v"(valid));
+#pragma unroll
+        for (uint32_t u = 0; u < SMALL_ROWS; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm volatile("" : "+v"(x[u][j]));
+    };
 
-    /* the k-th largest key, a digit of 12, 12 and 7 bits at a time */
-    uint32_t T = 0, want = kb;
+    /* The k-th largest key, a digit of 12, 12 and 7 bits at a time: the first over all elements, and the next as well as long as
+     * more keys are undecided than the list holds; then those keys are listed and the remaining digits come from the list. */
+    uint32_t T = 0, want = kb, psh = 31u, at = 0;        /* T: the bits from psh up */
 #pragma unroll 1
-    for (int level = 0; level < 3; ++level) {
-        const uint32_t psh = level == 0 ? 31u : level == 1 ? (uint32_t)SH0 : (uint32_t)SH1;
-        const uint32_t dsh = level == 0 ? (uint32_t)SH0 : level == 1 ? (uint32_t)SH1 : 0u;
-        const uint32_t nbin = level == 2 ? (uint32_t)NB2 : (uint32_t)NB0;
+    while (true) {
+        const uint32_t dsh = psh == 31u ? (uint32_t)SH0 : psh == (uint32_t)SH0 ? (uint32_t)SH1 : 0u;
+        const uint32_t nbin = dsh == 0u ? (uint32_t)NB2 : (uint32_t)NB0;
         for (uint32_t i = tid; i < nbin; i += SMALL_T) hist[i] = 0u;
         wg_sync();
+        anew();
 #pragma unroll
         for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
             if (u >= rows) continue;
@@ -107,48 +124,77 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
                     if ((hit >> j) & 1u) atomicAdd(&hist[d[j]], 1u);
             }
         }
+        if (tid == 0) listed = 0u;
         wg_sync();
-        constexpr uint32_t PER = NB0 / SMALL_T;
-        uint32_t c[PER], sum = 0;
-        const int top = (int)nbin - 1 - (int)(tid * PER);
+        (void)(dsh == 0u ? find_digit_lds<NB2>(hist, want, tmp, res) : find_digit_lds<NB0>(hist, want, tmp, res));
+        T = (T << (psh == 31u ? 12u : psh - dsh)) | res[0];
+        want -= res[1];
+        at = res[2];
+        psh = dsh;
+        wg_sync();
+        if (psh == 0u || at <= SMALL_LIST) break;
+    }
+
+    /* keys above T's bits per wavefront, those that share them into the list (its order does not matter; when T is complete they are counted) */
+    {
+        uint32_t ng = 0, ne = 0;
+        anew();
 #pragma unroll
-        for (uint32_t i = 0; i < PER; ++i) { c[i] = top - (int)i >= 0 ? hist[top - (int)i] : 0u; sum += c[i]; }
-        const uint32_t incl = small_incl_scan(sum, tmp), before = incl - sum;
-        if (before < want && want <= incl) {             /* exactly one thread: the digits seen here number at least `want` */
-            uint32_t acc = before, digit = 0;
-            bool found = false;
+        for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
+            if (u >= rows) continue;
 #pragma unroll
-            for (uint32_t i = 0; i < PER; ++i) {
-                if (!found && acc + c[i] >= want) { digit = (uint32_t)(top - (int)i); found = true; }
-                if (!found) acc += c[i];
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t key = keyof(x[u][j]);
+                const bool is = ((valid >> (4 * u + j)) & 1u) && (key >> psh) == T;
+                ng += (uint32_t)__popcll(__ballot((key >> psh) > T));      /* (what is not valid has key 0) */
+                const uint64_t be = __ballot(is);
+                if (!be) continue;
+                if (psh == 0u) { ne += (uint32_t)__popcll(be); continue; }
+                uint32_t p = 0;
+                if (lane == 0) p = atomicAdd(&listed, (uint32_t)__popcll(be));
+                p = __builtin_amdgcn_readfirstlane(p);
+                p = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, p));
+                if (is) list[p] = (key & ((1u << psh) - 1u)) | (wave << SH0);        /* at most 19 undecided bits, then the wavefront */
             }
-            res[0] = digit; res[1] = acc;
+        }
+        if (lane == 0) { wg_[wave] = ng; we_[wave] = ne; }
+    }
+    if (psh) {
+        const uint32_t low = (1u << psh) - 1u, T0 = T;
+        if (psh > (uint32_t)SH1) {
+            for (uint32_t i = tid; i < (uint32_t)NB1; i += SMALL_T) hist[i] = 0u;
+            wg_sync();
+            for (uint32_t i = tid; i < at; i += SMALL_T) atomicAdd(&hist[(list[i] & low) >> SH1], 1u);
+            wg_sync();
+            (void)find_digit_lds<NB1>(hist, want, tmp, res);
+            T = (T << (psh - SH1)) | res[0];
+            want -= res[1];
+            wg_sync();
+        }
+        if (tid < (uint32_t)NB2) hist[tid] = 0u;
+        wg_sync();
+        for (uint32_t i = tid; i < at; i += SMALL_T) {
+            const uint32_t k = list[i] & low;
+            if (((T0 << psh) | k) >> SH1 == T) atomicAdd(&hist[k & (NB2 - 1u)], 1u);
         }
         wg_sync();
-        T = (T << (level == 2 ? 7 : 12)) | res[0];
+        (void)find_digit_lds<NB2>(hist, want, tmp, res);
+        T = (T << SH1) | res[0];
         want -= res[1];
-        wg_sync();
+        for (uint32_t i = tid; i < at; i += SMALL_T) {
+            const uint32_t e = list[i], k = (T0 << psh) | (e & low);
+            if (k >= T) atomicAdd(k > T ? &wg_[e >> SH0] : &we_[e >> SH0], 1u);
+        }
     }
     const uint32_t e_b = want;                           /* of the keys equal to T the first so many survive */
-
-    /* ranks: survivors before this wavefront, then row by row */
-    uint32_t ng = 0, ne = 0;
-#pragma unroll
-    for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
-        if (u >= rows) continue;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool in = (valid >> (4 * u + j)) & 1u;
-            ng += (uint32_t)__popcll(__ballot(in && keyof(x[u][j]) > T));
-            ne += (uint32_t)__popcll(__ballot(in && keyof(x[u][j]) == T));
-        }
-    }
-    if (lane == 0) { wg_[wave] = ng; we_[wave] = ne; }
-    if (CODED)
-        for (uint32_t i = tid; i < (kb + chunk - 1) / chunk; i += SMALL_T) cmax[i] = 0u;
     wg_sync();
-    uint32_t g0 = 0, e0 = 0;
-    for (uint32_t w = 0; w < wave; ++w) { g0 += wg_[w]; e0 += we_[w]; }
+    /* ranks: survivors before this wavefront, then row by row */
+    uint32_t all;
+    uint32_t g0 = scan_totals(wg_, all), e0 = scan_totals(we_, all);
+    if (CODED) {
+        for (uint32_t i = tid; i < (kb + chunk - 1) / chunk; i += SMALL_T) cmax[i] = 0u;
+        wg_sync();
+    }
     const uint64_t Pb = t.P[b];
     uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
     uint8_t *code8 = reinterpret_cast<uint8_t *>(code);
@@ -178,6 +224,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
     };
     if (CODED) {
         uint32_t g1 = g0, e1 = e0;
+        anew();
 #pragma unroll
         for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
             if (u >= rows) continue;
@@ -212,6 +259,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
         if (tid == 0 && (kb & 1u)) code8[kb] = 0u;       /* what fills the last byte of an odd number of 4-bit codes */
         wg_sync();
     }
+    anew();
 #pragma unroll
     for (uint32_t u = 0; u < SMALL_ROWS; ++u) {
         if (u >= rows) continue;
@@ -232,8 +280,11 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
                 x[u][j] = __fsub_rn(xv, __half2float(hv));
             } else {
                 const float scale = __uint_as_float(cmax[chunk_of(rank)]);
-                int q = 0;
-                if (scale != 0.0f) q = (int)fminf(fmaxf(rintf(__fdiv_rn(xv, scale)), -QMAX), QMAX);
+                /* (the product with the reciprocal gives the quotient's code away from the middle of two: see quantize_four) */
+                const float y = __fmul_rn(xv, __builtin_amdgcn_rcpf(scale));
+                float wq = rintf(y);
+                if (!(fabsf(__fsub_rn(y, wq)) < 0.4999f)) wq = scale != 0.0f ? rintf(__fdiv_rn(xv, scale)) : 0.0f;
+                const int q = (int)fminf(fmaxf(wq, -QMAX), QMAX);
                 code8[rank] = (uint8_t)q;
                 x[u][j] = __fsub_rn(xv, __fmul_rn((float)q, scale));
             }
