@@ -320,6 +320,22 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
     if (g < n_tiles) tilestart_find(idx, t, g, ts);
 }
 
+/* One of its entries by a wavefront: the first j in [0, kb] with ib[j] + head >= edge, 64 probes a round. */
+__device__ __forceinline__ uint32_t tilestart_wave(const uint32_t *__restrict__ ib, uint32_t kb, uint32_t head, uint64_t edge)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    uint32_t lo = 0, hi = kb;
+    while (lo < hi) {                                    /* (the range shrinks every round, whatever the list holds) */
+        const uint32_t step = (hi - lo + 63u) / 64u;
+        const uint64_t p = (uint64_t)lo + (uint64_t)lane * step;
+        const uint64_t beyond = __ballot(p >= hi || (uint64_t)ib[p < hi ? p : lo] + head >= edge);
+        const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */
+        hi = (uint32_t)min((uint64_t)hi, (uint64_t)lo + (uint64_t)f * step);
+        if (f) lo += (f - 1u) * step + 1u;
+    }
+    return lo;
+}
+
 /* Four consecutive values j0 .. j0 + 3 of a bucket's value stream, decoded; 8- and 32-bit ones in one
  * load (the stream of a bucket starts at any byte, so the address is not aligned; global loads need
  * not be). */
@@ -351,7 +367,7 @@ __device__ __forceinline__ void decode4(const uint8_t *__restrict__ vb, const fl
 /* Dense output, a tile per workgroup: every output line is written once, past the caches (with plain stores
  * half of 4 M elements into one of nine buffers 19.0 us, so 15.8; 25 M at ratio 0.05 36.2 and 27.4).  An empty
  * tile is zeros at once.  Otherwise the tile is assembled in LDS (zeros, then the decoded survivors that fall
- * inside it, found through the tile-start table).  Where a tile has four survivors and more for every thread, a
+ * inside it, found through the tile-start table, or with few tiles by a search of its own: see launch_decompress).  Where a tile has four survivors and more for every thread, a
  * thread takes four consecutive ones at a time, indices and codes each in one load (419 M elements at ratio 0.9:
  * 8-bit codes 642 us, one by one 776; for 32-bit values, whose loads are as wide either way, 852 and 839, so not
  * there).  A bucket of which every element was sent needs neither LDS nor its index list: its output is the
@@ -395,7 +411,20 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
             out[u] = f4{x[0], x[1], x[2], x[3]};
         }
     } else {
-        const uint32_t j0 = min(ts[tile + b], kb), j1 = min(ts[tile + b + 1], kb);
+        uint32_t j0, j1;
+        if (ts) {
+            j0 = min(ts[tile + b], kb); j1 = min(ts[tile + b + 1], kb);
+        } else {
+            /* no table: a wavefront each for the tile's first survivor and the one after its last */
+            __shared__ uint32_t place[2];
+            const uint32_t w = tid >> 6, i = tile - t.tile0[b] + w, tiles_b = t.tile0[b + 1] - t.tile0[b];
+            if (w < 2u) {
+                const uint32_t at = i >= tiles_b ? kb : tilestart_wave(ib, kb, (uint32_t)(s.lo & 3ull), (uint64_t)i * TILE);
+                if ((tid & 63u) == 0u) place[w] = at;
+            }
+            wg_sync();
+            j0 = place[0]; j1 = place[1];
+        }
         if (j0 < j1) {                                   /* same for the whole workgroup */
             const uint64_t shift = s.lo - s.base;        /* slot = local index + lo - base */
 #pragma unroll
