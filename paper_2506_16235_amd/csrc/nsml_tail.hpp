@@ -165,7 +165,8 @@ __device__ __forceinline__ bool pruned_elem(const uint32_t *__restrict__ pmask, 
  * segment overflowed): a workgroup takes the segments of one workgroup of k_select_count, 16 or 4
  * lanes each, counts in LDS and adds what it has to one of the bucket's copies.  Bound by reading the
  * staged values (419 M elements at ratio 0.5, 3 % staged: 30 us; 109 M at 0.01: 17); an overflowed segment is
- * fetched whole before any of it is counted (BERT-shaped gradient at 0.1: 65 us, one load after the other 71). */
+ * fetched whole, and the next one while it is counted (BERT-shaped gradient at 0.1: 35 us; without the next one on its
+ * way 65, one load after the other 71). */
 constexpr uint32_t BINS_U = 8;             /* entries a lane has in flight */
 __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
                                              uint32_t *__restrict__ hist, int count_hi, const float *__restrict__ r)
@@ -208,11 +209,21 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
         const uint64_t lo_al = t.off[b] & ~3ull;
         /* which of them: a lane per segment, the same in every wavefront */
         uint64_t todo = __ballot(lane < s1 - s0 && c.cnt[s0 + min(lane, s1 - s0 - 1u)] > SEG_CAP);
-        for (; todo; todo &= todo - 1ull) {
-            const DenseSeg d = dense_seg(t, b, s0 + (uint32_t)__builtin_ctzll(todo));
+        DenseSeg dn = {};
+        float xn[TILE / WG];
+        auto fetch = [&]() {
+            dn = dense_seg(t, b, s0 + (uint32_t)__builtin_ctzll(todo));
+#pragma unroll
+            for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; xn[u] = e < dn.len ? r[dn.e0 + e] : 0.0f; }
+        };
+        if (todo) fetch();
+        while (todo) {
+            const DenseSeg d = dn;
             float x[TILE / WG];
 #pragma unroll
-            for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; x[u] = e < d.len ? r[d.e0 + e] : 0.0f; }
+            for (uint32_t u = 0; u < TILE / WG; ++u) x[u] = xn[u];
+            todo &= todo - 1ull;
+            if (todo) fetch();                       /* the next one is on its way while this is counted */
 #pragma unroll
             for (uint32_t u = 0; u < TILE / WG; ++u) {
                 const uint32_t e = u * WG + tid, key = keyof(x[u]);
@@ -239,7 +250,8 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
  * A workgroup takes 16 or 64 consecutive segments (1 << selSh) as one list of entries, dealt to its four wavefronts row
  * by row (64 entries), so its work follows the number of entries and not the longest segment; lane l
  * of every wavefront keeps the count of segment l, from the ballots of the rows and the part of each row
- * that belongs to it. */
+ * that belongs to it.  Overflowed segments are read from the accumulator, the next one on its way while one is counted:
+ * up to 16 of them are a workgroup's longest work (BERT-shaped gradient at 0.1: 42 us one after the other, so 28). */
 template <bool PLAN>
 __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw,
                                                      const uint32_t *__restrict__ hist,
@@ -360,12 +372,23 @@ __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const 
                && !(t.pmask && pruned_elem(t.pmask, t.tile0[b], t.off[b] & ~3ull, d.e0 + e));
     };
     const uint64_t over = __ballot(dense);           /* the same in every wavefront */
-    for (uint64_t todo = over; todo; todo &= todo - 1ull) {
+    uint64_t todo = over;
+    DenseSeg dn = {};
+    float xn[TILE / WG];
+    auto fetch = [&]() {
+        dn = dense_seg(t, b, s0 + (uint32_t)__builtin_ctzll(todo));
+#pragma unroll
+        for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; xn[u] = e < dn.len ? r[dn.e0 + e] : 0.0f; }
+    };
+    if (todo) fetch();
+    while (todo) {
         const uint32_t q = (uint32_t)__builtin_ctzll(todo);
-        const DenseSeg d = dense_seg(t, b, s0 + q);
+        const DenseSeg d = dn;
         float x[TILE / WG];
 #pragma unroll
-        for (uint32_t u = 0; u < TILE / WG; ++u) { const uint32_t e = u * WG + tid; x[u] = e < d.len ? r[d.e0 + e] : 0.0f; }
+        for (uint32_t u = 0; u < TILE / WG; ++u) x[u] = xn[u];
+        todo &= todo - 1ull;
+        if (todo) fetch();                           /* the next one is on its way while this is counted */
         uint32_t g = 0;
 #pragma unroll
         for (uint32_t u = 0; u < TILE / WG; ++u) {
