@@ -1558,14 +1558,15 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
         const uint32_t mine = (todo_sh >> (wave * QUANT_PER_WAVE)) & ((1u << QUANT_PER_WAVE) - 1u);
         if (mine) quant_wave<BITS>(v, idx, t, r, val, scales, chunk_b, cw + wave * QUANT_PER_WAVE, mine);
     } else {
-        /* longer chunks: QUANT_BIG_PER_WG chunks per workgroup, one after the other; which of them
+        /* longer chunks: up to QUANT_BIG_PER_WG per workgroup, one after the other; which of them
          * are still to be coded is found by one lane per chunk first */
         __shared__ uint32_t todo_big;
-        const uint64_t cw = (uint64_t)blockIdx.x * QUANT_BIG_PER_WG;
+        const uint32_t per = (uint32_t)((n_chunks + gridDim.x - 1) / gridDim.x);
+        const uint64_t cw = (uint64_t)blockIdx.x * per;
         if (threadIdx.x < 64) {
             const uint64_t cid = cw + threadIdx.x;
             bool todo = false;
-            if (threadIdx.x < QUANT_BIG_PER_WG && cid < n_chunks) {
+            if (threadIdx.x < per && cid < n_chunks) {
                 const uint32_t b = chunk_b[cid];
                 const uint32_t path = t.fast[b];
                 todo = path != PATH_CAND;

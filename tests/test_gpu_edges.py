@@ -64,6 +64,20 @@ def test_more_chunks_than_workgroups_that_code_them(ratio, bits):
     c.step(ratio, bits)
 
 
+@pytest.mark.parametrize("dense", [0, 1])
+@pytest.mark.parametrize("n", [4_200_003, 4_400_003, 9_000_001])
+def test_long_chunks_left_to_a_second_pass(monkeypatch, n, dense):
+    """Chunks longer than a wavefront codes that the ordered pass leaves uncoded (those across its units, or all of them):
+    about as many as make the second pass give a workgroup one (below 32 for every compute unit), two, and four."""
+    monkeypatch.setitem(nsml.Context.default_options, "force_dense", dense)
+    off = W.offsets_of([n - 70_001, 70_001])
+    g = _rand(n, 13)
+    g[: n // 3].mul_((torch.arange(n // 3, device=DEV) % 2048 < 700).float())
+    c = Case(g, off, chunk=264)
+    c.step(0.5, 8)
+    c.step(0.499, 4)
+
+
 @pytest.mark.parametrize("digits", [1, 2])
 @pytest.mark.parametrize("close", [4095, 4096, 4097, 9000])
 def test_undecided_keys_of_a_small_bucket(close, digits):
