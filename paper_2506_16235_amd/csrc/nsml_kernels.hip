@@ -16,6 +16,7 @@
  *             with a wide margin, below the k-th largest ("candidates", ratios up to an eighth);
  *             a band [L_b, H_b) of keys around the k-th largest (larger ratios); nothing, when
  *             the k-th largest is a zero (sparse embeddings, ratio 1)
+ *             (presample: both in one launch, a workgroup per bucket, unless buckets are many or large)
  *   ef_emit   acc = grad + residual (written over residual), the staged elements in index order to a
  *             segment per tile, how many lie above the window of keys around the expected
  *             threshold, and the window's bins (from 16384 tiles up by a kernel of their own, bins) 12 B/element
@@ -32,8 +33,8 @@
  *             staging segment that overflowed, huge groups of equal keys): all radix steps over
  *             the dense accumulator, in a small resident grid with barriers between the steps
  *   quant     codes what hard left uncoded (chunks that straddle its work units; PATH_DENSE)
- *   tilestart, decomp    payload -> dense, each output line written once (few survivors: zeros, then
- *             the survivors stored over them)
+ *   tilestart, decomp    payload -> dense, each output line written once (with few tiles decomp looks for
+ *             its survivors itself; few survivors: zeros, then the survivors stored over them)
  * Two kinds of call need none of the selection: small buckets (small: a workgroup per bucket does the
  * whole call) and ratio 1 (full: one streaming pass).
  * Every path gives the same bytes.

@@ -583,9 +583,9 @@ __global__ __launch_bounds__(1024) void k_plan_dense(Tables t, const double *__r
     plan_store(t, b, Plan{PATH_DENSE, 0u, t.k[b], SH_NONE, WHY_NO_GUESS});
 }
 
-/* One workgroup: the list of tiles that belong to buckets on the dense passes.  (Kept as its own small
- * launch: doing it in the last workgroup of k_plan needs a device-scope fence in every
- * workgroup, which on this multi-die GPU writes back each L2 and costs more than a launch.) */
+/* One workgroup: the list of tiles that belong to buckets on the dense passes.  (The team's first step: done by the last
+ * workgroup of the launch that makes the plans, it needs a device-scope fence in every workgroup there, which on this multi-die
+ * GPU writes back each L2 and costs more than a launch.) */
 __device__ __forceinline__ void fb_plan_body(const Tables &t)
 {
     __shared__ uint32_t tmp[WG];

@@ -8,7 +8,7 @@
 namespace {
 
 /* A bucket that fits the registers of one workgroup needs none of the passes over memory that the long
- * chain of kernels is made of, and with small buckets the chain's eleven launches of 4 - 10 us each are
+ * chain of kernels is made of, and with small buckets the chain's eight launches of 4 - 10 us each are
  * all that a call costs.  Gradient and residual are read once into registers (a wavefront holds consecutive
  * elements, four of a row per lane), the k-th key is found digit by digit with histograms in LDS, ranks
  * come from ballots, chunk maxima from LDS, and payload and residual are written once.
