@@ -237,8 +237,10 @@ __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g
     const uint32_t tile0b = t.pmask ? t.tile0[b] : 0u;
     wg_sync();
     constexpr uint32_t RUNS = PRE_T / (SAMPLE_RUN / 4);         /* per access of all threads */
+    /* a wavefront goes on as long as its first lane has a run: the addition for all of it below counts 64 lanes */
 #pragma unroll 1
-    for (uint64_t run0 = tid / (SAMPLE_RUN / 4); run0 < n_runs; run0 += RUNS * PRE_U) {
+    for (uint64_t first = tid / 64 * (64 / (SAMPLE_RUN / 4)); first < n_runs; first += RUNS * PRE_U) {
+        const uint64_t run0 = first + (tid & 63u) / (SAMPLE_RUN / 4);
         f4 x[PRE_U], y[PRE_U];
         uint32_t m[PRE_U];
 #pragma unroll

@@ -49,6 +49,39 @@ def test_sample_and_prediction_in_one_launch(sizes):
     c.step(0.02, 16)
 
 
+@pytest.mark.parametrize("pruned", [False, True])
+@pytest.mark.parametrize("ratio", [0.1, 0.2, 0.3, 0.5])
+def test_one_magnitude_in_small_buckets_of_the_chain(ratio, pruned):
+    """Buckets of under 16384 elements beside one that is too large for a single launch, whose last wavefront has
+    1, 2, 5, 10 or 15 runs of 16 to sample: one magnitude (or zeros) and 16 to 240 larger values at the end, so that more
+    elements share a digit than can be staged and the dense passes go on from the sample's counts."""
+    sizes = [40_000, 8208, 7840, 4112, 8192 + 80, 16 * 175, 16_368, 32, 12_304]
+    larger = [16, 16, 32, 16, 80, 240, 160, 16, 16]
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    rng = np.random.default_rng(int(ratio * 10) + pruned)
+    g_h = np.where(rng.random(n) < 0.5, -1e-3, 1e-3).astype(np.float32)
+    for b, m in enumerate(larger):
+        g_h[int(off[b + 1]) - m:int(off[b + 1])] *= 2
+    g_h[int(off[8]):int(off[9]) - 16] = 0.0
+    c = Case(torch.from_numpy(g_h).to(DEV), off, chunk=256)
+    if not pruned:
+        for bits in (4, 8, 16, 32):
+            c.set_residual(np.zeros(n))
+            c.step(ratio, bits)
+        return
+    w = _rand(n, 5)
+    for bits in (4, 8, 16, 32):
+        c.set_residual(np.zeros(n))
+        idx, val, sc = c.ctx.compress_pruned(c.g, c.r, w, off, ratio, bits)
+        torch.cuda.synchronize()
+        c.ctx.path_stats()
+        want = oracle.compress_pruned(c.g_host, c.r_host, w.cpu().numpy(), off, ratio, bits, 256, nthreads=8)
+        _, K, vb, ns = oracle.layout(off, ratio, bits, 256)
+        compare_payload(off, ratio, bits, 256, (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns]), want)
+        assert np.array_equal(c.r.cpu().numpy().view(np.uint32), c.r_host.view(np.uint32))
+
+
 @pytest.mark.parametrize("bits", [4, 8, 32])
 @pytest.mark.parametrize("ratio", [0.09, 0.12, 0.13, 0.3])
 def test_more_chunks_than_workgroups_that_code_them(ratio, bits):
