@@ -636,8 +636,11 @@ __device__ __forceinline__ void pick_body(const Tables &t, uint32_t *__restrict_
 
 /* Exclusive scan, in place, of a dense bucket's counts per tile.  Both counts of a tile travel as
  * one 64-bit word (neither total can reach 2^32: a bucket has fewer elements), and every thread
- * takes four consecutive tiles, so a round covers 1024 tiles with one scan. */
-__device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict__ G, uint32_t *__restrict__ E, uint32_t b)
+ * takes four consecutive tiles, so a round covers 1024 tiles with one scan.
+ * Totals that do not give k survivors (cannot happen: the steps before counted them) raise the flag.  coded: the
+ * survivors are written and coded next, through the places written, so such a bucket is left alone from here on, like
+ * one that is coded already.  (A pruning bitmap is written whole, whatever the totals say.) */
+__device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict__ G, uint32_t *__restrict__ E, uint32_t *__restrict__ err, bool coded, uint32_t b)
 {
     __shared__ uint64_t tmp[WG / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -671,6 +674,13 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
             run += v[j];
         }
         carry += total;
+    }
+    if (tid == 0) {
+        const uint32_t above = (uint32_t)(carry >> 32), ties = (uint32_t)carry, e_b = t.need[b];
+        if (above + e_b != t.k[b] || e_b > ties) {
+            err[0] = 1u;
+            if (coded) t.fast[b] = PATH_CAND;
+        }
     }
 }
 

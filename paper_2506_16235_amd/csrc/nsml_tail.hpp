@@ -1130,10 +1130,10 @@ __device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t target, uin
 /* Threshold key, tie allowance and prefixes per tile of the buckets on the dense passes, by a team of
  * nblk resident workgroups: list of their tiles, then per level a histogram over the source and its
  * digit (the first one only where a bucket's leading bits are not known from the counts), then counts per tile and
- * their prefixes, with a barrier after each step.  h: NB0 words of LDS. */
+ * their prefixes, with a barrier after each step.  h: NB0 words of LDS.  coded: see scan_body. */
 __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
                                                 uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *h, uint32_t *bar,
-                                                uint32_t bid, uint32_t nblk, uint32_t *__restrict__ err)
+                                                uint32_t bid, uint32_t nblk, bool coded, uint32_t *__restrict__ err)
 {
     uint32_t arrivals = 0;
     if (bid == 0) fb_plan_body(t);
@@ -1154,7 +1154,7 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
     grid_barrier(bar, arrivals += nblk, err);
     segcount_dense_body(r, t, c, bid, nblk);
     grid_barrier(bar, arrivals += nblk, err);
-    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); scan_body(t, c.G, c.E, b); }
+    for (uint32_t b = bid; b < t.B; b += nblk) { wg_sync(); scan_body(t, c.G, c.E, err, coded, b); }
     grid_barrier(bar, arrivals += nblk, err);
 }
 
@@ -1517,7 +1517,7 @@ __global__ __launch_bounds__(HTH, hard_wg_per_cu(BIG) * (HTH / 256)) void k_hard
     nblk = team;
     uint32_t *h = pool;
     uint32_t *bar = t.nhard + 1;
-    dense_threshold(r, t, c, f0, f1, f2, h, bar, bid, nblk, err);
+    dense_threshold(r, t, c, f0, f1, f2, h, bar, bid, nblk, true, err);
     write_dense_body<BITS == 32>(r, t, c, idx, vdst, 1u << PATH_DENSE, bid, nblk);
 }
 
@@ -1694,7 +1694,7 @@ __global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Table
     __shared__ uint32_t h[NB1];
     if (t.nhard[2] == 0u) return;
     const uint32_t bid = blockIdx.x, nblk = gridDim.x;
-    dense_threshold(w, t, c, f0, f1, f2, h, t.nhard + 1, bid, nblk, err);
+    dense_threshold(w, t, c, f0, f1, f2, h, t.nhard + 1, bid, nblk, false, err);
     mask_dense_body(w, t, c, pmask, bid, nblk);
 }
 

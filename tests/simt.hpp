@@ -42,13 +42,13 @@ struct Fiber {
     jmp_buf at;
 };
 inline std::vector<Fiber> fibers;
-inline std::vector<char> stacks;
+inline char *stacks;
 inline Fiber *cur;
 inline jmp_buf scheduler;
 inline ucontext_t home;
 inline std::function<void()> body;
 inline dim3 block, grid;
-constexpr size_t STACK = 64 * 1024;
+constexpr size_t STACK = 256 * 1024;
 
 inline void entry()
 {
@@ -72,7 +72,7 @@ __attribute__((noinline)) inline void resume(Fiber *f)
 /* One workgroup of `threads`. */
 inline void run(uint32_t threads, dim3 block_, dim3 grid_, std::function<void()> f)
 {
-    if (fibers.size() < threads) { fibers.resize(threads); stacks.resize(threads * STACK); }
+    if (fibers.size() < threads) { fibers.resize(threads); stacks = static_cast<char *>(realloc(stacks, threads * STACK)); }
     body = f; block = block_; grid = grid_;
     for (uint32_t i = 0; i < threads; ++i) {
         Fiber &b = fibers[i];
@@ -148,6 +148,26 @@ template <typename T> T read(T x, int from, int line)
     return x;
 }
 template <typename T> T shfl_up(T x, int d, int line) { const int l = (int)lane(); return read(x, l >= d ? l - d : l, line); }
+/* data-parallel moves: shifts inside a row of 16 lanes, the last lane of a row or of the first half to the rows behind it,
+ * permutations of four; lanes of rows outside `rows`, and without `zero` those that get nothing, keep old */
+inline int dpp(int old, int x, uint32_t ctrl, uint32_t rows, bool zero, int line)
+{
+    const int l = (int)lane(), row = l / 16;
+    int src = -1;
+    if (ctrl < 0x100) src = (l & ~3) | (int)((ctrl >> (2 * (l & 3))) & 3u);
+    else if (ctrl > 0x100 && ctrl < 0x110) src = l + (int)(ctrl - 0x100);
+    else if (ctrl > 0x110 && ctrl < 0x120) src = l - (int)(ctrl - 0x110);
+    else if (ctrl == 0x142) src = row ? row * 16 - 1 : -1;
+    else if (ctrl == 0x143) src = row >= 2 ? 31 : -1;
+    else { fprintf(stderr, "dpp %x\n", ctrl); abort(); }
+    if (ctrl > 0x100 && ctrl < 0x120 && (src < row * 16 || src >= row * 16 + 16)) src = -1;
+    const uint64_t g = meet((uint32_t)x, line);
+    int v = src >= 0 && ((g >> src) & 1ull) ? (int)(uint32_t)wave0()[src].in : zero ? 0 : old;
+    if (!((rows >> row) & 1u)) v = old;
+    leave(line);
+    return v;
+}
+inline uint32_t mbcnt(uint32_t mask, uint32_t below, uint32_t add) { return add + (uint32_t)__builtin_popcount(mask & below); }
 inline void barrier() { cur->state = BARRIER; yield(); }
 [[noreturn]] inline void missing(const char *what) { fprintf(stderr, "%s is not emulated\n", what); abort(); }
 
@@ -170,18 +190,42 @@ inline void barrier() { cur->state = BARRIER; yield(); }
 #define __shfl_xor(x, d, w) simt::read(x, (int)(simt::lane() ^ (uint32_t)(d)), __LINE__)
 #define __builtin_amdgcn_readfirstlane(x) simt::read(x, -1, __LINE__)
 #define __builtin_amdgcn_s_waitcnt(x) ((void)0)
-#define __builtin_amdgcn_update_dpp(...) (simt::missing("update_dpp"), 0)
-#define __builtin_amdgcn_mbcnt_lo(...) (simt::missing("mbcnt_lo"), 0u)
-#define __builtin_amdgcn_mbcnt_hi(...) (simt::missing("mbcnt_hi"), 0u)
+#define __shfl(x, l, w) simt::read(x, (int)(l), __LINE__)
+#define __any(p) (simt::ballot(p, __LINE__) != 0)
+#define __builtin_amdgcn_readlane(x, l) simt::read((int)(x), (int)(l), __LINE__)
+#define __builtin_amdgcn_update_dpp(old, x, ctrl, rows, banks, zero) simt::dpp(old, x, ctrl, rows, zero, __LINE__)
+#define __builtin_amdgcn_mov_dpp(x, ctrl, rows, banks, zero) simt::dpp(0, x, ctrl, rows, zero, __LINE__)
+#define __builtin_amdgcn_mbcnt_lo(m, add) simt::mbcnt(m, simt::lane() < 32 ? (1u << simt::lane()) - 1u : ~0u, add)
+#define __builtin_amdgcn_mbcnt_hi(m, add) simt::mbcnt(m, simt::lane() < 32 ? 0u : (1u << (simt::lane() - 32)) - 1u, add)
+#define __builtin_amdgcn_s_sleep(x) ((void)0)
+#define __builtin_amdgcn_rcpf(x) (1.0f / (x))
+#define __syncthreads_or(p) (simt::missing("__syncthreads_or"), 0)
+#define __HIP_MEMORY_SCOPE_AGENT 0
+#define __hip_atomic_fetch_add(p, x, order, scope) atomicAdd(p, x)
+#define __hip_atomic_load(p, order, scope) (*(p))
+#define __threadfence() ((void)0)
+#define wall_clock64() 0ull
 #define __builtin_nontemporal_load(p) (*(p))
 #define __builtin_nontemporal_store(v, p) ((void)(*(p) = (v)))
 
 inline uint32_t atomicAdd(uint32_t *p, uint32_t x) { const uint32_t old = *p; *p += x; return old; }
+inline uint32_t atomicMax(uint32_t *p, uint32_t x) { const uint32_t old = *p; *p = old > x ? old : x; return old; }
+inline uint32_t atomicOr(uint32_t *p, uint32_t x) { const uint32_t old = *p; *p |= x; return old; }
+inline int __popc(uint32_t x) { return __builtin_popcount(x); }
 inline int __popcll(uint64_t x) { return __builtin_popcountll(x); }
 inline uint32_t __float_as_uint(float x) { uint32_t u; memcpy(&u, &x, 4); return u; }
+inline float __uint_as_float(uint32_t u) { float x; memcpy(&x, &u, 4); return x; }
+inline int __float_as_int(float x) { return (int)__float_as_uint(x); }
+inline float __int_as_float(int u) { return __uint_as_float((uint32_t)u); }
+typedef _Float16 __half;
+inline __half __float2half_rn(float x) { return (__half)x; }
+inline float __half2float(__half x) { return (float)x; }
+inline unsigned short __half_as_ushort(__half x) { unsigned short u; memcpy(&u, &x, 2); return u; }
 inline long long __double_as_longlong(double x) { long long u; memcpy(&u, &x, 8); return u; }
 inline double __longlong_as_double(long long u) { double x; memcpy(&x, &u, 8); return x; }
 inline float __fadd_rn(float a, float b) { return a + b; }
+inline float __fsub_rn(float a, float b) { return a - b; }
+inline float __fdiv_rn(float a, float b) { return a / b; }
 inline float __fmul_rn(float a, float b) { return a * b; }
 inline float __fmaf_rn(float a, float b, float c) { return fmaf(a, b, c); }
 template <typename A, typename B> std::common_type_t<A, B> min(A a, B b) { std::common_type_t<A, B> x = a, y = b; return x < y ? x : y; }

@@ -23,3 +23,7 @@ def _run(tmp_path, source):
 
 def test_sampled_counts_are_those_of_a_plain_histogram(tmp_path):
     _run(tmp_path, "sample_driver.cpp")
+
+
+def test_dense_passes_notice_a_wrong_count_before_they_write(tmp_path):
+    _run(tmp_path, "dense_driver.cpp")
