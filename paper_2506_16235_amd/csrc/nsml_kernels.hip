@@ -581,7 +581,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     bool stale;
     rc = plan_tables(c, ratio, bits, stale);
     if (rc) return rc;
-    /* Sample and prediction by a workgroup per bucket, which also makes stale tables: up to two turns of two workgroups
+    /* Sample and prediction by a workgroup per bucket, which also makes stale tables: up to four turns of a workgroup
      * on every compute unit, and no bucket that needs a larger sample (compress, us, this / k_sample and k_predict: 1024 buckets of
      * 45 elements 100 / 103, 1000 of 40000 204 / 243, one of 1 Mi 50.6 / 54.1; 16 of 4 M 195 / 202). */
     const bool presample = B <= 4u * (uint32_t)c->n_cu && c->max_nb < PRE_BIG && !c->force_dense;

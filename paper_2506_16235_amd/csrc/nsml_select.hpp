@@ -75,15 +75,15 @@ __device__ __forceinline__ uint32_t window_shift(uint32_t L, uint32_t W)
  * in the same bins was no gain in safety and cost an atomic each.)
  * A bucket for which none of this fits (or whose guess turns out wrong once the exact counts are
  * known) takes the dense passes and still gets the exact result. */
-template <typename WALK>      /* the sample's histogram: find(rank, digit, above, at), total */
-__device__ __forceinline__ void predict_bucket(const Tables &t, uint32_t b, uint64_t nb, uint32_t k, double pop, bool exact, uint32_t wide, const WALK &w, uint32_t *res)
+template <typename WALK>      /* the sample's histogram: find(rank, digit, above, at), total; -> whether there is anything to stage or count */
+__device__ __forceinline__ bool predict_bucket(const Tables &t, uint32_t b, uint64_t nb, uint32_t k, double pop, bool exact, uint32_t wide, const WALK &w, uint32_t *res)
 {
     const uint32_t tid = threadIdx.x;
     const KeyPar nothing = make_uint4(NONE, NONE, NONE, SH1);
     const uint32_t m = w.total;
     if (m == 0) {
         if (tid == 0) t.par[b] = nothing;
-        return;
+        return false;
     }
     const double ks = (double)k * (double)m / pop;
     const double cap_b = (double)(t.tile0[b + 1] - t.tile0[b]) * (double)SEG_CAP;
@@ -141,7 +141,7 @@ __device__ __forceinline__ void predict_bucket(const Tables &t, uint32_t b, uint
         }
         if (p.x != NONE || exact || widen == 1u) {
             if (tid == 0) t.par[b] = p;
-            return;
+            return p.x != NONE;
         }
         widen >>= 1;
         wg_sync();                                       /* res is written again */
@@ -178,9 +178,14 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
  * that wait for each other in one.  What a compute unit can fetch alone (25 - 50 GB/s) bounds it, so the sample is
  * PRE_ELEMS elements (in the same runs of 16), and in buckets of which k_sample takes every element the margin of the
  * candidates is twice as wide (a wider band would overflow the segments of clustered values).  ResNet-50's 161 buckets: 9.6 us, by k_sample and k_predict 12 + 8 (and 5 for the tables); 1 Mi
- * elements 7.5, 6.2 + 5.5.  With 32768 elements 22 us. */
-constexpr uint32_t PRE_T = 1024, PRE_U = 2;        /* 16-byte accesses a thread has in flight, per operand */
+ * elements 7.5, 6.2 + 5.5.  With 32768 elements 22 us.
+ * A bucket in which so few leave nothing to stage (a large group of equal values near the threshold) is sampled once more as
+ * k_sample does: a narrower band may fit, or the dense passes need not look for the first digit, which costs them a read and
+ * two barriers (compress at 0.4 as 32-bit values, us, without / with: 400 buckets of 40003 clipped values 245 / 178, 12 of 3 M 277 /
+ * 241, 100000 elements of two magnitudes 194 / 169, by k_sample 160). */
+constexpr uint32_t PRE_T = 1024, PRE_U = 2, PRE_AGAIN_U = 4;       /* 16-byte accesses a thread has in flight, per operand */
 constexpr uint32_t PRE_ELEMS = 8192;
+constexpr uint32_t PRE_COPIES = 8, PRE_ROW = NB0 + 4;       /* copies of the histogram, and words of one: the copies of a digit in different banks */
 constexpr uint64_t PRE_BIG = 1ull << 22;           /* larger buckets need a larger sample (16 of 4 M, rows of zeros: already 4 % slower) */
 __device__ __forceinline__ uint64_t pre_stride(uint64_t nb) { return nb < 2u * PRE_ELEMS ? 1u : nb / PRE_ELEMS; }
 /* the histogram's digits from the top, four per thread */
@@ -215,36 +220,28 @@ struct DigitWalk1024 {
         return false;
     }
 };
-__global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g, const float *__restrict__ r, Tables t, double ratio,
-                                                     int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
+/* The histogram h of a bucket's runs, one in `stride`, by a workgroup of PRE_T threads with U accesses each in flight per operand.
+ * COPIES: of the histogram, which the lanes take in turn and which are added up at the end (a few values that nearly all
+ * elements have are one word's additions after the other otherwise: those 100000 elements 188 us with one copy). */
+template <uint32_t U, uint32_t COPIES>
+__device__ __forceinline__ void sample_bucket(const float *__restrict__ g, const float *__restrict__ r, const Tables &t, uint32_t b,
+                                              uint64_t lo, uint64_t hi, uint64_t stride, uint32_t *h)
 {
-    __shared__ uint32_t h[NB0];
-    __shared__ uint32_t tmp[PRE_T / 64], res[10];
-    const uint32_t b = blockIdx.x, tid = threadIdx.x;
-    if (b >= t.B) {                                  /* workgroups beyond the buckets: set-up */
-        setup_all<PRE_T>(t, ratio, bits, n_chunks, chunk_b, reinterpret_cast<uint64_t *>(h), b - t.B, gridDim.x - t.B);
-        return;
-    }
-    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by this call's plan ([1]: the barrier of k_hard) */
-    const uint64_t lo = t.off[b], hi = t.off[b + 1], nb = hi - lo, a0 = lo & ~3ull;
-    const uint32_t k = (uint32_t)survivors_dev(ratio, nb);
-    if (nb == 0 || (uint64_t)k == nb) {              /* everything is sent: all keys >= 1, and the zeros as ties of key 0 */
-        if (tid == 0) t.par[b] = nb == 0 ? make_uint4(NONE, NONE, NONE, SH1) : make_uint4(1u, 1u, 1u, SH1);
-        return;
-    }
-    for (uint32_t i = tid; i < (uint32_t)NB0; i += PRE_T) h[i] = 0u;
-    const uint64_t stride = pre_stride(nb), run_elems = SAMPLE_RUN * stride, n_runs = (hi - a0 + run_elems - 1) / run_elems;
+    const uint32_t tid = threadIdx.x;
+    const uint64_t a0 = lo & ~3ull, run_elems = SAMPLE_RUN * stride, n_runs = (hi - a0 + run_elems - 1) / run_elems;
     const uint32_t tile0b = t.pmask ? t.tile0[b] : 0u;
+    for (uint32_t i = tid * 4u; i < COPIES * PRE_ROW; i += PRE_T * 4u) *reinterpret_cast<uint4 *>(h + i) = make_uint4(0u, 0u, 0u, 0u);
     wg_sync();
+    uint32_t *hc = h + (COPIES > 1 ? (tid % COPIES) * PRE_ROW : 0u);
     constexpr uint32_t RUNS = PRE_T / (SAMPLE_RUN / 4);         /* per access of all threads */
     /* a wavefront goes on as long as its first lane has a run: the addition for all of it below counts 64 lanes */
 #pragma unroll 1
-    for (uint64_t first = tid / 64 * (64 / (SAMPLE_RUN / 4)); first < n_runs; first += RUNS * PRE_U) {
+    for (uint64_t first = tid / 64 * (64 / (SAMPLE_RUN / 4)); first < n_runs; first += RUNS * U) {
         const uint64_t run0 = first + (tid & 63u) / (SAMPLE_RUN / 4);
-        f4 x[PRE_U], y[PRE_U];
-        uint32_t m[PRE_U];
+        f4 x[U], y[U];
+        uint32_t m[U];
 #pragma unroll
-        for (uint32_t u = 0; u < PRE_U; ++u) {
+        for (uint32_t u = 0; u < U; ++u) {
             const uint64_t gi = a0 + (run0 + u * RUNS) * run_elems + (tid % (SAMPLE_RUN / 4)) * 4;
             x[u] = y[u] = f4{0.f, 0.f, 0.f, 0.f};
             m[u] = 0u;
@@ -256,7 +253,7 @@ __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g
             }
         }
 #pragma unroll
-        for (uint32_t u = 0; u < PRE_U; ++u) {
+        for (uint32_t u = 0; u < U; ++u) {
             const uint64_t gi = a0 + (run0 + u * RUNS) * run_elems + (tid % (SAMPLE_RUN / 4)) * 4;
             if (run0 + u * RUNS < n_runs && gi < hi && (gi < lo || gi + 4 > hi)) {
                 /* the bucket's first and last quad may be partly another's */
@@ -278,15 +275,47 @@ __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if ((m[u] >> j) & 1u) atomicAdd(&h[d[j]], 1u);
+                if ((m[u] >> j) & 1u) atomicAdd(&hc[d[j]], 1u);
         }
     }
     wg_sync();
+    if constexpr (COPIES > 1) {
+        static_assert(NB0 == 4u * PRE_T, "four digits per thread");
+        uint4 sum = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+        for (uint32_t q = 0; q < COPIES; ++q) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(h + q * PRE_ROW + tid * 4u);
+            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+        }
+        *reinterpret_cast<uint4 *>(h + tid * 4u) = sum;      /* (read by this thread alone) */
+        wg_sync();
+    }
+}
+__global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g, const float *__restrict__ r, Tables t, double ratio,
+                                                     int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
+{
+    __shared__ __align__(16) uint32_t h[PRE_COPIES * PRE_ROW];
+    __shared__ uint32_t tmp[PRE_T / 64], res[10];
+    const uint32_t b = blockIdx.x, tid = threadIdx.x;
+    if (b >= t.B) {                                  /* workgroups beyond the buckets: set-up */
+        setup_all<PRE_T>(t, ratio, bits, n_chunks, chunk_b, reinterpret_cast<uint64_t *>(h), b - t.B, gridDim.x - t.B);
+        return;
+    }
+    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by this call's plan ([1]: the barrier of k_hard) */
+    const uint64_t lo = t.off[b], hi = t.off[b + 1], nb = hi - lo, stride = pre_stride(nb);
+    const uint32_t k = (uint32_t)survivors_dev(ratio, nb);
+    if (nb == 0 || (uint64_t)k == nb) {              /* everything is sent: all keys >= 1, and the zeros as ties of key 0 */
+        if (tid == 0) t.par[b] = nb == 0 ? make_uint4(NONE, NONE, NONE, SH1) : make_uint4(1u, 1u, 1u, SH1);
+        return;
+    }
+    auto pop = [&]() { return t.pmask ? (double)kept_dev(ratio, nb) : (double)nb; };
+    sample_bucket<PRE_U, 1>(g, r, t, b, lo, hi, stride, h);
     DigitWalk1024 w;
     w.load(h, tmp);
-    double pop = (double)nb;
-    if (t.pmask) pop = (double)kept_dev(ratio, nb);
-    predict_bucket(t, b, nb, k, pop, stride == 1u, nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, w, res);
+    if (predict_bucket(t, b, nb, k, pop(), stride == 1u, nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, w, res) || stride <= sample_stride(nb)) return;
+    sample_bucket<PRE_AGAIN_U, PRE_COPIES>(g, r, t, b, lo, hi, sample_stride(nb), h);
+    w.load(h, tmp);
+    (void)predict_bucket(t, b, nb, k, pop(), nb < SAMPLE_ALL_BELOW, 1u, w, res);
 }
 
 /* ------------------------------------------------------------------ the streaming pass */

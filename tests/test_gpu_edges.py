@@ -82,6 +82,31 @@ def test_one_magnitude_in_small_buckets_of_the_chain(ratio, pruned):
         assert np.array_equal(c.r.cpu().numpy().view(np.uint32), c.r_host.view(np.uint32))
 
 
+@pytest.mark.parametrize("sizes", [[16_384, 40_003, 100_001], [262_143, 1], [262_144, 16_385], [1_000_003, 60_001], [(1 << 22) - 1]],
+                         ids=lambda s: str(max(s)))
+@pytest.mark.parametrize("values", ["clipped", "two"])
+def test_buckets_sampled_a_second_time(sizes, values):
+    """Large groups of equal values near the threshold, of which the small sample leaves nothing to stage: the whole
+    bucket is sampled then (up to 262143 elements), or as much of a larger one as when buckets are many.  Plain rounds with
+    error feedback, then a pruned call."""
+    off = W.offsets_of(sizes)
+    n = int(off[-1])
+    say("again", n, len(sizes), values)
+    g = _rand(n, n & 1023)
+    g = g.clamp(-1e-3, 1e-3) if values == "clipped" else torch.where(g.abs() < 6e-4, 1e-3, 2e-3) * torch.sign(g)
+    c = Case(g, off, chunk=2048)
+    for ratio, bits in ((0.4, 32), (0.38, 8), (0.5, 4), (0.1, 8)):
+        c.step(ratio, bits)
+    w = _rand(n, 9)
+    idx, val, sc = c.ctx.compress_pruned(c.g, c.r, w, off, 0.4, 16)
+    torch.cuda.synchronize()
+    c.ctx.path_stats()
+    want = oracle.compress_pruned(c.g_host, c.r_host, w.cpu().numpy(), off, 0.4, 16, 2048, nthreads=8)
+    _, K, vb, ns = oracle.layout(off, 0.4, 16, 2048)
+    compare_payload(off, 0.4, 16, 2048, (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns]), want)
+    assert np.array_equal(c.r.cpu().numpy().view(np.uint32), c.r_host.view(np.uint32))
+
+
 @pytest.mark.parametrize("bits", [4, 8, 32])
 @pytest.mark.parametrize("ratio", [0.09, 0.12, 0.13, 0.3])
 def test_more_chunks_than_workgroups_that_code_them(ratio, bits):
