@@ -30,6 +30,9 @@ constexpr int STH = TILE / 4;     /* threads of a streaming workgroup */
 constexpr int WTILE = 1024;       /* elements one wavefront covers per iteration in the passes over the dense accumulator */
 constexpr uint32_t XCD_RUN = 16;  /* consecutive tiles per die, see xcd_tile */
 constexpr uint32_t SEG_CAP = TILE / 4;      /* staging entries per tile: a quarter of its elements */
+/* Whether all of a bucket's k largest may be staged (half of what its tiles hold: k of up to an eighth of the bucket, and a little
+ * more of a small one) */
+__host__ __device__ inline bool candidates_fit(uint64_t k, uint64_t tiles) { return 2u * k <= tiles * SEG_CAP; }
 constexpr uint32_t SELC_SEGS = 64;          /* most segments per workgroup of k_select_count: one per lane */
 /* The undecided keys of a bucket, from list_base on: OWN_PER_SEG words per segment that belong to the workgroup of
  * k_select_count that counts it, then list_room words for the workgroups that have more than that (a third of

@@ -130,6 +130,7 @@ struct nsml_ctx {
     bool tables_valid;
     double t_ratio; int t_bits;       /* what d_k/d_P/... were computed for */
     uint64_t K, NC;                   /* totals for (layout, t_ratio, t_bits) */
+    uint64_t NC_cand;                 /* ... and the chunks of the buckets that may be decided from candidates */
     void *pinned; size_t pinned_bytes;
     int decomp_variant;    /* decompress: 1 zeros then survivors, 0 tiles assembled in LDS, -1 by the share of survivors */
     int force_dense;
@@ -358,15 +359,19 @@ int plan_tables(nsml_ctx *c, double ratio, int bits, bool &stale)
     stale = !(c->tables_valid && c->t_ratio == ratio && c->t_bits == bits);
     if (!stale) return NSML_OK;
     c->tables_valid = false;
-    uint64_t K = 0, nc = 0;
+    uint64_t K = 0, nc = 0, cand = 0;
     {
         std::vector<uint64_t> kb(c->B);
         int rc = nsml_payload_layout(c->h_off.data(), c->B, ratio, bits, c->chunk, kb.data(), &K, nullptr, nullptr);
         if (rc) return rc;
-        for (uint32_t b = 0; b < c->B; ++b) nc += (kb[b] + c->chunk - 1) / c->chunk;
+        for (uint32_t b = 0; b < c->B; ++b) {
+            const uint64_t lo = c->h_off[b], hi = c->h_off[b + 1], chunks = (kb[b] + c->chunk - 1) / c->chunk;
+            nc += chunks;
+            if (kb[b] < hi - lo && candidates_fit(kb[b], (hi - (lo & ~3ull) + TILE - 1) / TILE)) cand += chunks;
+        }
     }
     if (nc >= 0x7FFFFFFFull || nc > c->max_chunks) return NSML_ECAP;
-    c->K = K; c->NC = nc;
+    c->K = K; c->NC = nc; c->NC_cand = cand;
     c->t_ratio = ratio; c->t_bits = bits;
     return NSML_OK;
 }
@@ -715,9 +720,10 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
              * survivors a chunk, 22 / 45; 600 of 30000 at 0.1, 1500 a chunk, 32 / 45; fewer workgroups: ResNet-50's
              * 165 chunks of 156 survivors 25 / 18, 279 of 940 22 / 20; full chunks: 3072 of 2048 190 / 182). */
             const bool narrow = c->NC >= 2u * (uint64_t)c->n_cu && c->K <= 1900u * c->NC;
-            /* A workgroup per chunk; not of very many (2^32 threads cannot be launched), nor beyond a ratio of an eighth, where
-             * all but the smallest buckets are coded by k_hard. */
-            const uint32_t egrid2 = (uint32_t)std::min<uint64_t>(c->NC, c->K * 8u > n ? (narrow ? 4u : 2u) * (uint64_t)c->n_cu : 16384u);
+            /* A workgroup per chunk that may be coded here (beyond a ratio of an eighth those of the smallest buckets: k_hard
+             * codes the others), a few to look for them, and not very many (2^32 threads cannot be launched).  (A small grid as soon
+             * as K * 8 > n codes all of it at a ratio of 1/8 and odd sizes: 4 buckets of 27370561 elements 677 us a round, so 663.) */
+            const uint32_t egrid2 = (uint32_t)std::min<uint64_t>({c->NC, std::max<uint64_t>(c->NC_cand, (narrow ? 4u : 2u) * (uint64_t)c->n_cu), 16384u});
 #define NSML_ENCODE(BITS_)                                                                                                              \
     do {                                                                                                                                 \
         if (narrow) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, 256>), B + egrid2, 256, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, (const double *)c->d_tile_sq, c->d_l2sq);  \

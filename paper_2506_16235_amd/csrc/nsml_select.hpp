@@ -108,7 +108,7 @@ __device__ __forceinline__ bool predict_bucket(const Tables &t, uint32_t b, uint
         /* every thread comes to the same p */
         KeyPar p = nothing;
         bool done = false;
-        if (want_d <= (double)m && (double)k <= 0.5 * cap_b) {
+        if (want_d <= (double)m && candidates_fit(k, t.tile0[b + 1] - t.tile0[b])) {
             const double est = (double)(res[1] + res[2]) * pop / (double)m;
             if (est <= 0.8 * cap_b) {
                 p.x = res[0] << SH0;

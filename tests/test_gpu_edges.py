@@ -108,7 +108,7 @@ def test_buckets_sampled_a_second_time(sizes, values):
 
 
 @pytest.mark.parametrize("bits", [4, 8, 32])
-@pytest.mark.parametrize("ratio", [0.09, 0.12, 0.13, 0.3])
+@pytest.mark.parametrize("ratio", [0.09, 0.12, 0.125, 0.13, 0.3])
 def test_more_chunks_than_workgroups_that_code_them(ratio, bits):
     """More chunks than the launch that codes staged survivors has workgroups, below and above a ratio of an eighth:
     chunks of other paths between them (a bucket of mostly zeros), buckets of a few survivors, a last short chunk."""
