@@ -295,6 +295,7 @@ __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g
                                                      int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
 {
     __shared__ __align__(16) uint32_t h[PRE_COPIES * PRE_ROW];
+    static_assert(sizeof h >= (SETUP_MAX_B + 1) * sizeof(uint64_t), "the set-up's chunk prefixes take its place");
     __shared__ uint32_t tmp[PRE_T / 64], res[10];
     const uint32_t b = blockIdx.x, tid = threadIdx.x;
     if (b >= t.B) {                                  /* workgroups beyond the buckets: set-up */
