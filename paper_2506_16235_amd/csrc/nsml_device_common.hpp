@@ -58,7 +58,7 @@ constexpr int SH0 = 19;   /* key >> 19         : level-0 digit (sign-less expone
 constexpr int SH1 = 7;    /* (key >> 7) & 4095 : level-1 digit;  key & 127 : level-2 digit */
 constexpr uint32_t NONE = 0xFFFFFFFFu;
 constexpr uint32_t SH_NONE = 31;  /* Tables::sh of a bucket of whose threshold nothing is known yet */
-constexpr uint32_t SAMPLE_ALL_BELOW = 262144;  /* buckets smaller than this are sampled in full */
+constexpr uint32_t SAMPLE_ALL_BELOW = 262144;  /* buckets smaller than this are sampled in full (by k_presample when a small sample does not do) */
 constexpr uint32_t SAMPLE_STRIDE = 64;         /* of larger ones at most every 64th element, */
 constexpr uint32_t SAMPLE_ELEMS = 131072;      /* and at most about so many: the margins they leave (a third more staged than sent at
                                                * ratio 0.001) cost less than reading more (1/64 of 1.7 G elements: 95 us, this: 70) */
@@ -96,7 +96,7 @@ const char *const kKernelNames[KID_N] = {
 };
 static_assert(KID_N <= NSML_MAX_KERNELS, "raise NSML_MAX_KERNELS");
 
-/* What the streaming pass does with a bucket's keys (k_predict / k_wpredict):
+/* What the streaming pass does with a bucket's keys (predict_bucket / k_wpredict):
  *   x  L    the elements with L <= key < y are staged (NONE: none)
  *   y  H    NONE: no upper bound (everything from L up is staged: "candidates"); else a band is staged.
  *           L == H == 1: nothing is staged, non-zero and zero keys are counted per tile
@@ -124,7 +124,7 @@ struct Tables {
     KeyPar *par;             /* B   what the streaming pass stages and counts */
     uint32_t *fast;          /* B   how the bucket is decided (PATH_*) */
     uint32_t *sh;            /* B   T holds the key bits from this position up */
-    uint32_t *margin;        /* B   what the bucket has learned about its sample: factor on k_predict's margin (kept across calls) */
+    uint32_t *margin;        /* B   what the bucket has learned about its sample: factor on the margin of predict_bucket (kept across calls) */
     uint32_t *why;           /* B   diagnostic: why the plan did not take the staged elements (WHY_* bits, 0 if it did) */
     uint32_t *ovf;           /* B   a staging segment of the bucket overflowed */
     uint32_t *ftile0;        /* B+1 prefix of the tiles of buckets on the dense passes */

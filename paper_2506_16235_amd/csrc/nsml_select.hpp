@@ -148,7 +148,8 @@ __device__ __forceinline__ bool predict_bucket(const Tables &t, uint32_t b, uint
     }
 }
 
-/* The sample was taken by k_sample (many small buckets). */
+/* The sample was taken by k_sample: more than four buckets for every compute unit, one of PRE_BIG elements and more among them, or every bucket
+ * is sent to the dense passes (then there is none). */
 __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__ hist_s, int force_dense)
 {
     __shared__ uint32_t tmp[WG];
@@ -493,7 +494,7 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
     }
 }
 
-/* What the exact counts of a bucket say, for the gradient and the weight stage alike.  hist_b, n_hi: the
+/* What the exact counts of a bucket's weights say (the gradient's: k_select_count).  hist_b, n_hi: the
  * window's bins (NHC copies) and the number of elements at or above its top.  Every thread of a workgroup of NHB
  * threads calls it with its own bin (thread i: bin i, counted from the top of the window) and the
  * want-th key's bin comes back in res[0] with what lies above it (res[1]) and in it (res[2]); false in
