@@ -2,8 +2,9 @@
  * Device code on the CPU, one workgroup at a time: a fiber per thread, wavefronts of 64.
  *
  * A thread runs until it needs another one.  An operation over the wavefront is carried out once every
- * thread of it that still runs waits for something, among those that wait at that place of the source: the
- * threads that have left a loop, and stand at the barrier behind it, take no part, as on the GPU.  A
+ * thread of it that still runs waits for something, among those that wait for it: the
+ * threads that have left a loop, and stand at the barrier behind it, take no part, as on the GPU.  (Code in
+ * which they would stand at another operation over the wavefront instead cannot be run here.)  A
  * barrier is passed once every thread of the workgroup has come to it or has ended.
  * Only what the sources under test use is here.
  */
@@ -88,13 +89,15 @@ inline void run(uint32_t threads, dim3 block_, dim3 grid_, std::function<void()>
             while (true) {
                 int line = 0;
                 uint64_t group = 0;
-                for (uint32_t i = w0; i < w0 + 64; ++i) {
-                    while (fibers[i].state == READY) resume(&fibers[i]);
-                    if (fibers[i].state == WAVE && (!line || fibers[i].line < line)) line = fibers[i].line;
+                for (uint32_t i = 0; i < 64; ++i) {
+                    Fiber &f = fibers[w0 + i];
+                    while (f.state == READY) resume(&f);
+                    if (f.state != WAVE) continue;
+                    if (line && f.line != line) { fprintf(stderr, "lanes at lines %d and %d: who waits for whom is not known here\n", line, f.line); abort(); }
+                    line = f.line;
+                    group |= 1ull << i;
                 }
                 if (!line) break;
-                for (uint32_t i = 0; i < 64; ++i)
-                    if (fibers[w0 + i].state == WAVE && fibers[w0 + i].line == line) group |= 1ull << i;
                 for (uint32_t i = 0; i < 64; ++i)
                     if ((group >> i) & 1ull) { fibers[w0 + i].mask = group; fibers[w0 + i].state = READY; }
             }
@@ -137,14 +140,14 @@ inline bool all(bool p, int line)
 }
 template <typename T> T read(T x, int from, int line)
 {
-    static_assert(sizeof(T) == 4, "one word");
-    uint32_t v;
-    memcpy(&v, &x, 4);
+    static_assert(sizeof(T) <= 8, "an operand");
+    uint64_t v = 0;
+    memcpy(&v, &x, sizeof x);
     const uint64_t g = meet(v, line);
     const int src = from < 0 ? __builtin_ctzll(g) : from;
-    if ((g >> src) & 1ull) v = (uint32_t)wave0()[src].in;
+    if ((g >> src) & 1ull) v = wave0()[src].in;
     leave(line);
-    memcpy(&x, &v, 4);
+    memcpy(&x, &v, sizeof x);
     return x;
 }
 template <typename T> T shfl_up(T x, int d, int line) { const int l = (int)lane(); return read(x, l >= d ? l - d : l, line); }
