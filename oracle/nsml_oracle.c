@@ -303,10 +303,10 @@ int64_t orc_compress_bucket_pruned(const float *g, float *r, const float *w, uin
     /* from here on nothing differs from the unpruned path: code the gathered values and leave
      * the coding error in the residual.  Done by handing the survivors to the plain routine on
      * a compact copy: a bucket that consists of exactly the survivors, at ratio 1. */
-    float *gv = (float *)malloc(k * sizeof(float)), *rv = (float *)calloc(k, sizeof(float));
+    float *gv = (float *)malloc(k * sizeof(float)), *rv = (float *)malloc(k * sizeof(float));
     uint32_t *tmp_idx = (uint32_t *)malloc(k * sizeof(uint32_t));
     if (!gv || !rv || !tmp_idx) { free(gv); free(rv); free(tmp_idx); return ORC_ENOMEM; }
-    for (uint64_t j = 0; j < k; ++j) gv[j] = r[idx[j]];
+    for (uint64_t j = 0; j < k; ++j) { gv[j] = r[idx[j]]; rv[j] = -0.0f; }      /* x + -0 is x, also for -0 */
     int64_t kk = orc_compress_bucket(gv, rv, k, 1.0, bits, chunk, tmp_idx, val, scales);
     if (kk == (int64_t)k)
         for (uint64_t j = 0; j < k; ++j) r[idx[j]] = rv[j];

@@ -89,3 +89,16 @@ def test_pruned_payload_is_the_plain_coding_of_the_survivors(bits):
             keep = oracle.keep_mask(w[lo:hi], 0.05)
             assert np.all(keep[idx[p:p + kb]])
         p += kb
+
+
+@pytest.mark.parametrize("ratio", [0.4, 1.0])
+def test_a_sum_of_negative_zeros_is_sent_as_one(ratio):
+    """The value of a survivor is the binary32 sum g + r, whose sign a zero keeps as well, as without pruning."""
+    n = 50
+    g = np.where(np.arange(n) % 3 == 0, F32(-0.0), F32(0.0)).astype(F32)
+    r = np.where(np.arange(n) % 2 == 0, F32(-0.0), F32(0.0)).astype(F32)
+    want = (g + r).view(np.uint32)
+    assert 0 < np.count_nonzero(want) < n
+    w = np.arange(n, 0, -1).astype(F32)
+    idx, val, _ = oracle.compress_pruned(g, r.copy(), w, [0, n], ratio, 32, 8)
+    assert np.array_equal(val.view(np.uint32), want[idx])
