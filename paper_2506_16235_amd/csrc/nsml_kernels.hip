@@ -689,7 +689,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     if (presample) {
         uint64_t chunks = 0;
         const uint32_t extra = stale ? setup_grid(c, PRE_T, chunks) : 0u;
-        LAUNCHB(c, KID_SAMPLE, st, k_presample, B + extra, PRE_T, grad, (const float *)residual, t, ratio, bits, chunks, c->d_chunk_b);
+        LAUNCHB(c, KID_SAMPLE, st, k_presample, B + extra, PRE_T, grad, (const float *)residual, t, ratio, bits, c->max_nb < SAMPLE_ALL_BELOW, chunks, c->d_chunk_b);
         if (stale) { rc = chunk_map(c, st); if (rc) return rc; }
     } else {
         if (!c->force_dense)

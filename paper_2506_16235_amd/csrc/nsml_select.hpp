@@ -180,15 +180,21 @@ __global__ __launch_bounds__(WG) void k_predict(Tables t, uint32_t *__restrict__
  * PRE_ELEMS elements (in the same runs of 16), and in buckets of which k_sample takes every element the margin of the
  * candidates is twice as wide (a wider band would overflow the segments of clustered values).  ResNet-50's 161 buckets: 9.6 us, by k_sample and k_predict 12 + 8 (and 5 for the tables); 1 Mi
  * elements 7.5, 6.2 + 5.5.  With 32768 elements 22 us.
- * A bucket in which so few leave nothing to stage (a large group of equal values near the threshold) is sampled once more as
- * k_sample does: a narrower band may fit, or the dense passes need not look for the first digit, which costs them a read and
- * two barriers (compress at 0.4 as 32-bit values, us, without / with: 400 buckets of 40003 clipped values 245 / 178, 12 of 3 M 277 /
- * 241, 100000 elements of two magnitudes 194 / 169, by k_sample 160). */
+ * A bucket in which so few leave nothing to stage (a large group of equal values near the threshold) is sampled once more, for
+ * a narrower band may fit: 32768 elements at most (compress at 0.4 as 32-bit values, us, without / with: 400 buckets of 40003 clipped values
+ * 245 / 178, 12 of 3 M 277 / 242).  All of it where no bucket of the layout is too large for that: then the dense passes need not look
+ * for the first digit, a read and two barriers less for all of them (100000 elements of two magnitudes 194 / 169, by k_sample 160;
+ * 250000 220 / 214, 189; with a larger bucket beside it nothing is gained: 4 M elements in 100 buckets 290 / 328). */
 constexpr uint32_t PRE_T = 1024, PRE_U = 2, PRE_AGAIN_U = 4;       /* 16-byte accesses a thread has in flight, per operand */
-constexpr uint32_t PRE_ELEMS = 8192;
+constexpr uint32_t PRE_ELEMS = 8192, PRE_AGAIN_ELEMS = 32768;
 constexpr uint32_t PRE_COPIES = 8, PRE_ROW = NB0 + 4;       /* copies of the histogram, and words of one: the copies of a digit in different banks */
 constexpr uint64_t PRE_BIG = 1ull << 22;           /* larger buckets need a larger sample (16 of 4 M, rows of zeros: already 4 % slower) */
 __device__ __forceinline__ uint64_t pre_stride(uint64_t nb) { return nb < 2u * PRE_ELEMS ? 1u : nb / PRE_ELEMS; }
+/* of the second sample; whole: every bucket of the layout has less than SAMPLE_ALL_BELOW elements */
+__device__ __forceinline__ uint64_t again_stride(uint64_t nb, bool whole)
+{
+    return whole ? 1u : max(sample_stride(nb), nb / PRE_AGAIN_ELEMS);
+}
 /* the histogram's digits from the top, four per thread */
 struct DigitWalk1024 {
     uint32_t c[NB0 / PRE_T], sum, incl, total;
@@ -293,7 +299,7 @@ __device__ __forceinline__ void sample_bucket(const float *__restrict__ g, const
     }
 }
 __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g, const float *__restrict__ r, Tables t, double ratio,
-                                                     int bits, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
+                                                     int bits, bool whole, uint64_t n_chunks, uint32_t *__restrict__ chunk_b)
 {
     __shared__ __align__(16) uint32_t h[PRE_COPIES * PRE_ROW];
     static_assert(sizeof h >= (SETUP_MAX_B + 1) * sizeof(uint64_t), "the set-up's chunk prefixes take its place");
@@ -310,14 +316,18 @@ __global__ __launch_bounds__(PRE_T) void k_presample(const float *__restrict__ g
         if (tid == 0) t.par[b] = nb == 0 ? make_uint4(NONE, NONE, NONE, SH1) : make_uint4(1u, 1u, 1u, SH1);
         return;
     }
-    auto pop = [&]() { return t.pmask ? (double)kept_dev(ratio, nb) : (double)nb; };
-    sample_bucket<PRE_U, 1>(g, r, t, b, lo, hi, stride, h);
     DigitWalk1024 w;
-    w.load(h, tmp);
-    if (predict_bucket(t, b, nb, k, pop(), stride == 1u, nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, w, res) || stride <= sample_stride(nb)) return;
-    sample_bucket<PRE_AGAIN_U, PRE_COPIES>(g, r, t, b, lo, hi, sample_stride(nb), h);
-    w.load(h, tmp);
-    (void)predict_bucket(t, b, nb, k, pop(), nb < SAMPLE_ALL_BELOW, 1u, w, res);
+    auto predict = [&](uint64_t step) __attribute__((always_inline)) {
+        w.load(h, tmp);
+        return predict_bucket(t, b, nb, k, t.pmask ? (double)kept_dev(ratio, nb) : (double)nb, step == 1u,
+                              nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, w, res);
+    };
+    sample_bucket<PRE_U, 1>(g, r, t, b, lo, hi, stride, h);
+    if (predict(stride)) return;
+    const uint64_t again = again_stride(nb, whole);
+    if (stride <= again || (!whole && w.total != 0u && res[3] == res[6])) return;      /* (a band of one digit cannot get narrower) */
+    sample_bucket<PRE_AGAIN_U, PRE_COPIES>(g, r, t, b, lo, hi, again, h);
+    (void)predict(again);
 }
 
 /* ------------------------------------------------------------------ the streaming pass */

@@ -36,12 +36,14 @@ struct Layout {
 };
 
 /* predict_bucket on counts made elsewhere */
+static uint32_t digit_up, digit_dn;       /* of the band it tried last */
 static void from_counts(const Tables &t, uint32_t b, uint64_t nb, uint32_t k, double pop, bool exact, uint32_t wide, const uint32_t *counts)
 {
     static uint32_t tmp[PRE_T / 64], res[10];
     DigitWalk1024 w;
     w.load(counts, tmp);
     predict_bucket(t, b, nb, k, pop, exact, wide, w, res);
+    digit_up = res[3]; digit_dn = res[6];
 }
 
 static uint64_t rng_state = 88172645463325252ull;
@@ -56,9 +58,10 @@ static void check(uint64_t lead, uint64_t nb, int values, uint32_t tail, double 
     Layout a(off), w(off);
     const uint64_t lo = lead, n = lead + nb, a0 = lo & ~3ull;
     std::vector<float> gs(n + 8), rs(n + 8, 0.0f);
-    /* values: 0 one magnitude, 1 zeros, 2 continuous, 3 two magnitudes in turn by run of 16; the last `tail` are larger */
+    /* values: 0 one magnitude, 1 zeros, 2 continuous, 3 two magnitudes in turn by run of 16, 4 two in five of one magnitude above the others; the last `tail` are larger */
     for (uint64_t i = 0; i < n; ++i) {
-        float v = values == 0 ? 1e-3f : values == 1 ? 0.0f : values == 2 ? (uniform() - 0.5f) * 1e-3f : (i / 16) % 3 ? 1e-3f : 3e-3f;
+        float v = values == 0 ? 1e-3f : values == 1 ? 0.0f : values == 2 ? (uniform() - 0.5f) * 1e-3f : values == 3 ? ((i / 16) % 3 ? 1e-3f : 3e-3f)
+                : i % 5 < 2 ? 1e-3f : uniform() * 1e-3f;
         if (i + tail >= n) v = 2.0f * 1e-3f;
         gs[i] = (rnd() & 1) ? v : -v;
     }
@@ -70,11 +73,12 @@ static void check(uint64_t lead, uint64_t nb, int values, uint32_t tail, double 
     const uint32_t k = (uint32_t)survivors_dev(ratio, nb);
     double pop = (double)nb;
     if (pruned) pop = (double)kept_dev(ratio, nb);
-    simt::run(PRE_T, dim3(b), dim3(2), [&] { k_presample(gs.data(), rs.data(), a.t, ratio, 8, 0, nullptr); });
-    /* a small sample, and where that leaves nothing to stage the one of k_sample */
+    const bool all = lead < 262144 && nb < 262144;       /* no bucket is too large to be sampled whole */
+    simt::run(PRE_T, dim3(b), dim3(2), [&] { k_presample(gs.data(), rs.data(), a.t, ratio, 8, all, 0, nullptr); });
+    /* a small sample, and where that leaves nothing to stage all of the bucket, or a larger one */
     std::vector<uint32_t> h;
     bool exact = false;
-    for (uint64_t stride = pre_stride(nb);; stride = sample_stride(nb)) {
+    for (uint64_t stride = pre_stride(nb), again_at = all ? 1u : std::max<uint64_t>(nb < 262144 ? 1u : 64u, nb / 32768);; stride = again_at) {
         const uint64_t run_elems = SAMPLE_RUN * stride;
         h.assign(NB0, 0);
         for (uint64_t i = lo; i < n; ++i) {
@@ -86,7 +90,7 @@ static void check(uint64_t lead, uint64_t nb, int values, uint32_t tail, double 
         simt::run(PRE_T, dim3(b), dim3(2), [&] {
             from_counts(w.t, b, nb, k, pop, exact, nb < SAMPLE_ALL_BELOW && (uint64_t)k * 8u <= nb ? 2u : 1u, h.data());
         });
-        if (w.par[b].x != NONE || stride <= sample_stride(nb)) break;
+        if (w.par[b].x != NONE || stride <= again_at || (!all && digit_up == digit_dn)) break;
         ++again;
     }
     bool ok = memcmp(&a.par[b], &w.par[b], sizeof(uint4)) == 0 && a.T[b] == w.T[b] && a.need[b] == w.need[b];
@@ -118,13 +122,15 @@ int main()
     for (uint64_t nb : {8207ull, 8208ull, 8209ull, 7840ull, 4112ull, 16383ull, 16384ull, 16400ull, 24592ull, 40016ull, 70000ull, 262143ull, 262144ull, 600000ull})
         for (int values = 0; values < 4; ++values)
             for (uint64_t lead : {40000ull, 40003ull}) check(lead, nb, values, 16, ratios[turn++ % 4], false);
+    for (uint64_t nb : {8208ull, 40016ull, 70000ull, 200000ull})
+        for (int values = 0; values < 5; ++values) check(300000, nb, values, 16, ratios[turn++ % 4], values == 3);
     /* set-up beside the sampling: the tables of two buckets and the chunks of both */
     {
         Layout a({0, 40001, 48209});
         std::vector<uint32_t> map(400, NONE);
         const uint64_t n_chunks = (survivors_dev(0.3, 40001) + 255) / 256 + (survivors_dev(0.3, 8208) + 255) / 256;
         for (uint32_t wg = 0; wg < 2; ++wg)
-            simt::run(PRE_T, dim3(2 + wg), dim3(4), [&] { k_presample(nullptr, nullptr, a.t, 0.3, 8, n_chunks, map.data()); });
+            simt::run(PRE_T, dim3(2 + wg), dim3(4), [&] { k_presample(nullptr, nullptr, a.t, 0.3, 8, true, n_chunks, map.data()); });
         const uint64_t k0 = survivors_dev(0.3, 40001), c0 = (k0 + 255) / 256;
         bool ok = a.k[0] == k0 && a.k[1] == survivors_dev(0.3, 8208) && a.P[2] == a.k[0] + a.k[1] && a.C[1] == c0 && a.C[2] == n_chunks;
         for (uint64_t c = 0; c < n_chunks; ++c) ok = ok && map[c] == (c >= c0);
