@@ -79,7 +79,8 @@ enum Path : uint32_t {
     PATH_DENSE = 0,   /* the staged elements cannot decide: every step over the dense accumulator */
     PATH_CAND = 1,    /* staged = everything from L up: threshold and survivors from the staged entries alone */
     PATH_BAND = 2,    /* staged = a band of keys around the threshold: threshold from the band, survivors from the dense accumulator */
-    PATH_ZERO = 3     /* more survivors than non-zero elements: threshold key 0, known from the counts alone */
+    PATH_ZERO = 3,    /* more survivors than non-zero elements: threshold key 0, known from the counts alone */
+    PATH_LEFT = 4     /* counts that disagree on the dense passes (cannot happen; the flag is raised): nothing is written for the bucket */
 };
 
 enum KernelId {
@@ -138,6 +139,7 @@ struct Tables {
     uint32_t chunk;
     uint32_t chunkSh;        /* log2(chunk) when chunk is a power of two, else NONE */
     uint32_t dencTiles;      /* tiles per work unit of the one-pass dense encode: more on large gradients (fewer chunks straddle units) */
+    uint32_t *ties;          /* B   elements equal to the threshold key, of the buckets that k_select_finish decides */
 };
 
 /* Candidate staging: tile t owns entries [t * SEG_CAP, t * SEG_CAP + cnt[t]) */

@@ -720,8 +720,9 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
         const uint32_t above = (uint32_t)(carry >> 32), ties = (uint32_t)carry, e_b = t.need[b];
         if (above + e_b != t.k[b] || e_b > ties) {
             err[0] = 1u;
-            if (coded) t.fast[b] = PATH_CAND;
+            if (coded) t.fast[b] = PATH_LEFT;
         }
+        t.ftile0[b] = ties;                              /* (not needed any more as the prefix of the tile list) */
     }
 }
 
