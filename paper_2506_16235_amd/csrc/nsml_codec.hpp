@@ -54,14 +54,11 @@ __device__ __forceinline__ void quant_wave(const float *__restrict__ v, const ui
         const uint32_t b = bq[q];
         const uint64_t lo = t.off[b];
         uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
-        float scale = 0.0f;
-        if (BITS <= 8) {
-            float m = fmaxf(fmaxf(fabsf(x[q][0][0]), fabsf(x[q][0][1])), fmaxf(fabsf(x[q][1][0]), fabsf(x[q][1][1])));
+        float m = fmaxf(fmaxf(fabsf(x[q][0][0]), fabsf(x[q][0][1])), fmaxf(fabsf(x[q][1][0]), fabsf(x[q][1][1])));
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
-            scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
-            if (lane == 0) scales[t.S[b] + cbq[q]] = scale;
-        }
+        for (int d = 32; d >= 1; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+        const float scale = m == 0.0f ? 0.0f : __fdiv_rn(m, QMAX);
+        if (lane == 0) scales[t.S[b] + cbq[q]] = scale;
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const uint32_t i0 = 2 * (lane + u * 64);
@@ -73,21 +70,13 @@ __device__ __forceinline__ void quant_wave(const float *__restrict__ v, const ui
             for (int hh = 0; hh < 2; ++hh) {
                 if (hh >= have) continue;
                 const float xv = x[q][u][hh];
-                float deq;
-                if (BITS == 16) {
-                    const __half hv = __float2half_rn(xv);
-                    reinterpret_cast<__half *>(vb)[j0[q] + i0 + hh] = hv;
-                    deq = __half2float(hv);
-                } else {
-                    if (scale != 0.0f) {
-                        float tq = rintf(__fdiv_rn(xv, scale));
-                        tq = fminf(fmaxf(tq, -QMAX), QMAX);
-                        qq[hh] = (int)tq;
-                    }
-                    deq = __fmul_rn((float)qq[hh], scale);
-                    if (BITS == 8) reinterpret_cast<int8_t *>(vb)[j0[q] + i0 + hh] = (int8_t)qq[hh];
+                if (scale != 0.0f) {
+                    float tq = rintf(__fdiv_rn(xv, scale));
+                    tq = fminf(fmaxf(tq, -QMAX), QMAX);
+                    qq[hh] = (int)tq;
                 }
-                res[hh] = __fsub_rn(xv, deq);
+                if (BITS == 8) reinterpret_cast<int8_t *>(vb)[j0[q] + i0 + hh] = (int8_t)qq[hh];
+                res[hh] = __fsub_rn(xv, __fmul_rn((float)qq[hh], scale));
             }
             if (BITS == 4) vb[(j0[q] + i0) >> 1] = (uint8_t)((qq[0] & 0xF) | ((qq[1] & 0xF) << 4));
 #pragma unroll
@@ -125,7 +114,7 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
     constexpr uint32_t BLK = WG * 8;
     const bool one_block = cnt <= BLK;
     float scale = 0.0f;
-    if (BITS <= 8 && !one_block) {
+    if (!one_block) {
         float m = 0.0f;
         for (uint32_t i = tid; i < cnt; i += WG) m = fmaxf(m, fabsf(v[jg + i]));
 #pragma unroll
@@ -149,7 +138,7 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
                 li[u][hh] = i < cnt ? idx[jg + i] : 0u;
             }
         }
-        if (BITS <= 8 && one_block) {
+        if (one_block) {
             float m = 0.0f;
 #pragma unroll
             for (int u = 0; u < 4; ++u) m = fmaxf(m, fmaxf(fabsf(x[u][0]), fabsf(x[u][1])));   /* absent ones are 0 */
@@ -173,22 +162,14 @@ __device__ __forceinline__ void quant_body(const float *__restrict__ v, const ui
             for (int hh = 0; hh < 2; ++hh) {
                 if (hh >= have) continue;
                 const float xv = x[u][hh];
-                float deq;
-                if (BITS == 16) {
-                    const __half hv = __float2half_rn(xv);
-                    reinterpret_cast<__half *>(vb)[j0 + i0 + hh] = hv;
-                    deq = __half2float(hv);
-                } else {
-                    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
-                    if (scale != 0.0f) {
-                        float tq = rintf(__fdiv_rn(xv, scale));
-                        tq = fminf(fmaxf(tq, -QMAX), QMAX);
-                        q[hh] = (int)tq;
-                    }
-                    deq = __fmul_rn((float)q[hh], scale);
-                    if (BITS == 8) reinterpret_cast<int8_t *>(vb)[j0 + i0 + hh] = (int8_t)q[hh];
+                constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
+                if (scale != 0.0f) {
+                    float tq = rintf(__fdiv_rn(xv, scale));
+                    tq = fminf(fmaxf(tq, -QMAX), QMAX);
+                    q[hh] = (int)tq;
                 }
-                res[hh] = __fsub_rn(xv, deq);
+                if (BITS == 8) reinterpret_cast<int8_t *>(vb)[j0 + i0 + hh] = (int8_t)q[hh];
+                res[hh] = __fsub_rn(xv, __fmul_rn((float)q[hh], scale));
             }
             if (BITS == 4) vb[(j0 + i0) >> 1] = (uint8_t)((q[0] & 0xF) | ((q[1] & 0xF) << 4));
 #pragma unroll

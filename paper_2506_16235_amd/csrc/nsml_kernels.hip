@@ -29,7 +29,8 @@
  *   encode    PATH_CAND: one workgroup per chunk of survivors gathers them from the segments and
  *             codes them (absmax scale, codes, packing, indices, coding error into the residual)
  *             and, when no more than an eighth is sent, the buckets of the next two as well
- *   hard      PATH_BAND / PATH_ZERO: survivors taken from the dense
+ *   band      16- and 32-bit values beyond an eighth, PATH_BAND / PATH_ZERO: survivors taken from the dense accumulator tile by tile
+ *   hard      codes, PATH_BAND / PATH_ZERO: survivors taken from the dense
  *             accumulator and coded in one streaming pass; PATH_DENSE (an unlucky sample, a
  *             staging segment that overflowed, huge groups of equal keys): all radix steps over
  *             the dense accumulator, in a small resident grid with barriers between the steps
@@ -598,7 +599,6 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     const Hists h = hists_of(c, B);
     const uint64_t zw = zero_words(B);
     const uint32_t clear_grid = (uint32_t)((zw + WG * 8 - 1) / (WG * 8));
-    float *vdst = bits == 32 ? static_cast<float *>(val) : c->d_v;
     const dim3 sgrid = xcd_grid(c->n_tiles);         /* streaming passes: a workgroup per tile */
     const bool nt = c->nt_acc < 0 ? n > NT_ELEMS : c->nt_acc != 0;
     /* the window's bins by a kernel of their own: with many tiles, which may be those of many small buckets (and
@@ -706,7 +706,6 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
 #undef NSML_EF
     if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, 1, (const float *)residual);
     if (c->force_dense) LAUNCHB(c, KID_PLAN, st, k_plan_dense, B, 1024, t, (const double *)c->d_tile_sq, c->d_l2sq);
-    const uint32_t qgrid = (uint32_t)c->NC;
     /* the workgroups that meet at barriers on the dense passes: one per compute unit, so that the teams of two or
      * three contexts working at the same time still fit the device together */
     const bool big = c->chunk > DENC_SMALL_CHUNK;
@@ -731,7 +730,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             /* A workgroup per chunk that may be coded here (beyond a ratio of an eighth those of the smallest buckets: k_hard
              * codes the others), a few to look for them, and not very many (2^32 threads cannot be launched).  (A small grid as soon
              * as K * 8 > n codes all of it at a ratio of 1/8 and odd sizes: 4 buckets of 27370561 elements 677 us a round, so 663.) */
-            const uint32_t first = units ? std::max(B, team) : B;
+            const uint32_t first = units || bits >= 16 ? std::max(B, team) : B;
             const uint32_t egrid2 = (uint32_t)std::min<uint64_t>({c->NC, std::max<uint64_t>(c->NC_cand, (narrow ? 4u : 2u) * (uint64_t)c->n_cu), 16384u});
 #define NSML_ENCODE1(BITS_, T_, U_) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, T_, U_>), first + egrid2, T_, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, \
                                             (const double *)c->d_tile_sq, c->d_l2sq, h.f0, h.f1, h.f2, first, team)
@@ -752,35 +751,34 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
 #undef NSML_ENCODE1
         }
     }
-    /* the buckets whose survivors come from the dense accumulator, where k_encode has not coded them: a fixed grid, resident at
-     * once, that streams the band and zero-threshold buckets (ordered write and coding in one pass) and then does all the steps of
-     * the buckets on the dense passes with barriers between; then the value coding of what those
-     * left uncoded */
-    if (!units) {
+    /* the buckets whose survivors come from the dense accumulator, where k_encode has not coded them: whole values tile by tile; codes by a
+     * fixed grid, resident at once, that streams the band and zero-threshold buckets (ordered write and coding in one pass) and then does all
+     * the steps of the buckets on the dense passes with barriers between (force_dense: for all widths), and after it what that left uncoded */
+    if (!units && bits >= 16 && !c->force_dense) {
+        if (bits == 32 && nt) LAUNCHB(c, KID_HARD, st, (k_band<32, true>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+        else if (bits == 32) LAUNCHB(c, KID_HARD, st, (k_band<32, false>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+        else if (nt) LAUNCHB(c, KID_HARD, st, (k_band<16, true>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+        else LAUNCHB(c, KID_HARD, st, (k_band<16, false>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+    } else if (!units) {
         const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
         const int stream_coding = c->chunk <= DENC_MAX_CHUNK ? 1 : 0;
-#define NSML_HARD(BITS_, BIG_) LAUNCHB(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, HTH, residual, t, cd0, h.f0, h.f1, h.f2, idx, vdst, val, scales, c->d_flags, stream_coding, team)
+#define NSML_HARD(BITS_, BIG_) LAUNCHB(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, HTH, residual, t, cd0, h.f0, h.f1, h.f2, idx, c->d_v, val, scales, c->d_flags, stream_coding, team)
         switch (bits) {
         case 32: NSML_HARD(32, false); break;
-        case 16: if (big) NSML_HARD(16, true); else NSML_HARD(16, false); break;
+        case 16: NSML_HARD(16, false); break;
         case 8:  if (big) NSML_HARD(8, true); else NSML_HARD(8, false); break;
         default: if (big) NSML_HARD(4, true); else NSML_HARD(4, false); break;
         }
 #undef NSML_HARD
-        const uint32_t per_wg = (WG / 64) * QUANT_PER_WAVE;
+        const uint32_t qgrid = (uint32_t)c->NC, per_wg = (WG / 64) * QUANT_PER_WAVE;
         /* a chunk longer than a wavefront's per workgroup as long as that is not more than 16 for a compute unit (BERT-shaped gradient at 0.1,
          * 5496 chunks: 11.5 us, with eight 22.9), up to eight beyond (419 M elements at a half, 102400 of them: the round 2434 us,
          * with one each 2541) */
         const uint32_t big_per_wg = std::max(1u, std::min(QUANT_BIG_PER_WG, qgrid / (16u * (uint32_t)c->n_cu)));
         const uint32_t ngrid = c->chunk <= QUANT_WAVE_CHUNK ? (qgrid + per_wg - 1) / per_wg
                                                             : (qgrid + big_per_wg - 1) / big_per_wg;
-        const uint64_t nc64 = c->NC;
-        switch (bits) {
-        case 32: break;        /* the ordered write left values and residual in their final state */
-        case 16: LAUNCH(c, KID_QUANT, st, k_quant<16>, ngrid, (const float *)vdst, (const uint32_t *)idx, t, cd0, residual, val, scales, cb_, cs_, nc64, stream_coding); break;
-        case 8:  LAUNCH(c, KID_QUANT, st, k_quant<8>,  ngrid, (const float *)vdst, (const uint32_t *)idx, t, cd0, residual, val, scales, cb_, cs_, nc64, stream_coding); break;
-        default: LAUNCH(c, KID_QUANT, st, k_quant<4>,  ngrid, (const float *)vdst, (const uint32_t *)idx, t, cd0, residual, val, scales, cb_, cs_, nc64, stream_coding); break;
-        }
+        if (bits == 8) LAUNCH(c, KID_QUANT, st, k_quant<8>, ngrid, (const float *)c->d_v, (const uint32_t *)idx, t, cd0, residual, val, scales, cb_, cs_, c->NC, stream_coding);
+        if (bits == 4) LAUNCH(c, KID_QUANT, st, k_quant<4>, ngrid, (const float *)c->d_v, (const uint32_t *)idx, t, cd0, residual, val, scales, cb_, cs_, c->NC, stream_coding);
     }
     c->have_l2 = true;
     c->have_prune = pruned || none_pruned;

@@ -839,8 +839,7 @@ __device__ __forceinline__ float wave_max(float v)
  * one wavefront per staging segment walks the elements the segment covers, in index order, and writes the
  * survivors' indices and values to their final slots.  Ranks inside a row of 64 lanes x 4
  * elements come from ballots; nothing crosses wavefronts.  which: bit p set = serve PATH p. */
-template <bool DIRECT>   /* DIRECT (32-bit values): v_out is the payload itself and the survivors' residual is zero */
-__device__ __forceinline__ void write_dense_body(float *__restrict__ r, const Tables &t, const Cand &c,
+__device__ __forceinline__ void write_dense_body(const float *__restrict__ r, const Tables &t, const Cand &c,
                                                  uint32_t *__restrict__ idx_out, float *__restrict__ v_out,
                                                  uint32_t which, uint32_t bid, uint32_t nblk)
 {
@@ -903,7 +902,6 @@ __device__ __forceinline__ void write_dense_body(float *__restrict__ r, const Ta
                     const uint64_t pos = Pb + pg + min(e_b, pe);
                     idx_out[pos] = (uint32_t)(gi + j - s.lo);
                     v_out[pos] = x[u][j];
-                    if (DIRECT) r[gi + j] = __fsub_rn(x[u][j], x[u][j]);      /* nothing is left behind (NaN where no value was) */
                 }
                 pg += isg ? 1u : 0u;
                 pe += ise ? 1u : 0u;
@@ -1340,6 +1338,10 @@ __device__ __forceinline__ void code_dense_unit(float *__restrict__ r, const Tab
                 else code8[s] = (uint8_t)q;
                 ++s;
             }
+            uint32_t diff = 0;
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) diff |= __float_as_uint(y[j]) ^ __float_as_uint(x[u][j]);
+            if (!__any(diff)) continue;              /* zeros that survive leave what they were */
             if (whole && li >= e0 && li + 3u <= e1) {
                 *reinterpret_cast<f4 *>(r + base + elem_of(u)) = f4{y[0], y[1], y[2], y[3]};
             } else {
@@ -1377,12 +1379,154 @@ __device__ __forceinline__ void code_dense_unit(float *__restrict__ r, const Tab
         else if (BITS == 16) reinterpret_cast<uint16_t *>(vb)[j0 + i] = (uint16_t)h;
         else if (BITS == 8) vb[j0 + i] = (uint8_t)q;
         else if (!(lane & 1u)) vb[(j0 + i) >> 1] = (uint8_t)((q & 0xF) | ((odd & 0xF) << 4));
-        r[lo + li] = left;
+        if (__float_as_uint(left) != __float_as_uint(xv)) r[lo + li] = left;      /* (zeros that survive leave what they were) */
     }
 }
 
+/* ------------------------------------------------------------------ whole values from the dense accumulator */
+
+/* 16- and 32-bit values wait for no scale, so the survivors of a tile of a bucket whose threshold, tie allowance and
+ * prefixes are known need nothing from any other tile: elements read once, ranks from ballots, values and indices through LDS to
+ * where they go, and the elements written back as whole lines with what the survivors leave behind (see code_dense_unit).  A tile
+ * per workgroup of NT threads.  pool: 2 * TILE words. */
+constexpr uint32_t BAND_ROW = 16;       /* survivors of 256 elements from which their lines are written whole */
+template <int BITS, uint32_t NT, bool PAST>       /* PAST: whole lines go past the caches, see st_out */
+__device__ __forceinline__ void band_tile(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ idx_out, void *__restrict__ val,
+                                          uint32_t *__restrict__ err, uint32_t tile, const uint4 &d, uint32_t *pool)
+{
+    static_assert(BITS >= 16, "no chunks");
+    constexpr uint32_t Q = TILE / (4u * NT), W = NT / 64;
+    __shared__ uint32_t wt[8];
+    float *sv = reinterpret_cast<float *>(pool);
+    uint32_t *si = pool + TILE;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t b = d.z, first = d.w & 0xFFFFu, last = d.w >> 16;
+    float *rt = r + (((uint64_t)d.y << 32) | d.x);
+    const bool whole = first == 0u && last == (uint32_t)TILE, full = whole && t.pmask == nullptr;
+    float x[Q][4];
+    uint32_t m[Q];
+#pragma unroll
+    for (uint32_t u = 0; u < Q; ++u) {
+        const uint32_t e = (u * NT + tid) * 4u;
+        m[u] = 0;
+        if (whole) {
+            const f4 v = *reinterpret_cast<const f4 *>(rt + e);
+            x[u][0] = v.x; x[u][1] = v.y; x[u][2] = v.z; x[u][3] = v.w;
+            m[u] = 0xFu;
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                x[u][j] = 0.0f;
+                if (e + j >= first && e + j < last) { x[u][j] = rt[e + j]; m[u] |= 1u << j; }
+            }
+        }
+        if (t.pmask) m[u] &= ~pruned_bits(t.pmask, tile, u * NT + tid);
+    }
+    const uint32_t T = t.T[b], e_b = t.need[b], kb = t.k[b], Gs = c.G[tile], Es = c.E[tile];
+    const uint64_t Pb = t.P[b];
+    uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
+    const uint32_t li0 = (tile - t.tile0[b]) * (uint32_t)TILE - (uint32_t)(t.off[b] & 3ull);      /* (mod 2^32) */
+    const uint32_t lim = e_b > Es ? e_b - Es : 0u, R0 = Gs + min(e_b, Es);                         /* ties still admitted, rank of the tile's first survivor */
+    uint32_t row_g[Q], row_e[Q], bef[Q];
+    /* keys as signed numbers, what does not count the lowest of them */
+    auto keys = [&](uint32_t u, int32_t (&key)[4]) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) key[j] = (int32_t)keyof(x[u][j]);
+        if (!full) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) key[j] = (m[u] >> j) & 1u ? key[j] : (int32_t)0x80000000u;
+        }
+    };
+#pragma unroll
+    for (uint32_t u = 0; u < Q; ++u) {
+        row_g[u] = row_e[u] = bef[u] = 0;
+        int32_t key[4];
+        keys(u, key);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint64_t bg = __ballot(key[j] > (int32_t)T);
+            row_g[u] += (uint32_t)__popcll(bg);
+            row_e[u] += (uint32_t)__popcll(__ballot(key[j] == (int32_t)T));
+            bef[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, bef[u]));
+        }
+        if (lane == 0) wt[u * W + wave] = row_g[u] | (row_e[u] << 16);
+    }
+    wg_sync();
+    uint32_t all = 0, before[Q];
+    {
+        const uint32_t mine = wt[lane & 7u];
+#pragma unroll
+        for (uint32_t w = 0; w < 8u; ++w) {
+#pragma unroll
+            for (uint32_t u = 0; u < Q; ++u) if (u * W + wave == w) before[u] = all;
+            all += (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)w);
+        }
+    }
+    const uint32_t nsurv = (all & 0xFFFFu) + min(all >> 16, lim);
+    if (R0 > kb || nsurv > kb - R0) {                /* the prefixes and the elements disagree: nothing is written (same for the whole workgroup) */
+        if (tid == 0) err[0] = 1u;
+        return;
+    }
+    auto left_of = [&](float v) { return BITS == 32 ? __fsub_rn(v, v) : __fsub_rn(v, __half2float(__float2half_rn(v))); };      /* (32 bits: NaN where no value was) */
+#pragma unroll
+    for (uint32_t u = 0; u < Q; ++u) {
+        if (row_g[u] + row_e[u] == 0u) continue;     /* same for the whole wavefront */
+        const uint32_t fg = before[u] & 0xFFFFu, fe = before[u] >> 16, e = (u * NT + tid) * 4u;
+        int32_t key[4];
+        keys(u, key);
+        uint32_t bits = 0, s;
+        if (row_e[u] == 0u || fe >= lim) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bits |= (key[j] > (int32_t)T ? 1u : 0u) << j;
+            s = fg + min(fe, lim) + bef[u];
+        } else {
+            uint32_t pe = fe;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint64_t be = __ballot(key[j] == (int32_t)T);
+                pe = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, pe));
+            }
+            s = fg + bef[u] + min(pe, lim);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool tie = key[j] == (int32_t)T;
+                bits |= (key[j] > (int32_t)T || (tie && pe < lim) ? 1u : 0u) << j;
+                pe += tie ? 1u : 0u;
+            }
+        }
+        float y[4];
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) {
+            y[j] = x[u][j];
+            if (!((bits >> j) & 1u)) continue;
+            sv[s] = x[u][j];
+            si[s] = li0 + e + j;
+            y[j] = left_of(x[u][j]);
+            ++s;
+        }
+        /* (zeros that survive leave what they were: an embedding's untouched rows are not written back) */
+        uint32_t diff = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < 4; ++j) diff |= __float_as_uint(y[j]) ^ __float_as_uint(x[u][j]);
+        if (!__any(diff)) continue;
+        if (whole && row_g[u] + row_e[u] >= BAND_ROW) {
+            st_out<PAST>(reinterpret_cast<f4 *>(rt + e), f4{y[0], y[1], y[2], y[3]});
+        } else {
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j)
+                if ((bits >> j) & 1u) rt[e + j] = y[j];
+        }
+    }
+    wg_sync();
+    for (uint32_t i = tid; i < nsurv; i += NT) {
+        const float v = sv[i];
+        idx_out[Pb + R0 + i] = si[i];
+        if (BITS == 32) reinterpret_cast<float *>(vb)[R0 + i] = v;
+        else reinterpret_cast<__half *>(vb)[R0 + i] = __float2half_rn(v);
+    }
+}
 /* The buckets on the dense passes, by the nblk workgroups of a resident team (WG threads of each): threshold, counts and
- * prefixes, then their survivors, coded. */
+ * prefixes, then their survivors, coded: whole values tile by tile, others unit by unit. */
 template <int BITS>
 __device__ __forceinline__ void code_dense_buckets(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
                                                    uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ idx,
@@ -1393,7 +1537,19 @@ __device__ __forceinline__ void code_dense_buckets(float *__restrict__ r, const 
     static_assert(2 * TILE >= NB1, "the pool must hold the level-1 histogram");
     __shared__ uint32_t sh;
     dense_threshold(r, t, c, f0, f1, f2, pool, t.nhard + 1, bid, nblk, true, err);
-    const uint32_t g = unit_chunks(t.chunk), lane = threadIdx.x & 63;
+    const uint32_t lane = threadIdx.x & 63;
+    if constexpr (BITS >= 16) {
+        for (uint64_t t0 = bid; t0 < t.n_tiles; t0 += 64ull * nblk) {
+            const uint64_t tl = t0 + (uint64_t)lane * nblk;
+            for (uint64_t todo = __ballot(tl < t.n_tiles && t.fast[t.tile_b[min(tl, (uint64_t)t.n_tiles - 1u)]] == PATH_DENSE); todo; todo &= todo - 1ull) {
+                const uint32_t tile = (uint32_t)(t0 + (uint64_t)__builtin_ctzll(todo) * nblk);
+                wg_sync();                           /* LDS is written again */
+                band_tile<BITS, WG, false>(r, t, c, idx, val, err, tile, t.desc[tile], pool);
+            }
+        }
+        return;
+    }
+    const uint32_t g = unit_chunks(t.chunk);
     for (uint64_t c0 = bid; c0 < n_chunks; c0 += 64ull * nblk) {
         const uint64_t cl = c0 + (uint64_t)lane * nblk;
         bool mine = false;
@@ -1452,7 +1608,7 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
                 t.ovf[b] = 0u;
             }
         }
-        if constexpr (UNITS) {
+        if constexpr (UNITS || BITS >= 16) {
             if (blockIdx.x >= team || t.nhard[2] == 0u || threadIdx.x >= WG) return;
             wg_sync();
             code_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx_out, val, scales, err, chunk_b, n_chunks, pool, blockIdx.x, team);
@@ -1606,14 +1762,13 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
  * codes, indices, and the coding error scattered into the accumulator lines the workgroup has
  * just read, which are still in the cache).  A chunk that reaches across the unit's ends (or a
  * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
- * those afterwards (same test, see chunk_coded_by_stream).  16-bit values need no chunk and are
- * all coded here. */
+ * those afterwards (same test, see chunk_coded_by_stream).  (16- and 32-bit values: band_tile.) */
 /* What bounds it: half of 419 M elements sent as 8-bit codes take 860 - 960 us, from one machine to another; without the scattered residual
  * 680, without any store 690, so the steps' chain of barriers and the instructions between them (59 per element
  * before the counts came from comparison masks and the codes from a product, 37 now) come first.  Was 1010 with four
  * wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
- * alignment, residual stores 8 elements apart) 975, full residual lines 1057, non-temporal index stores 1169.
- * 32-bit values, 25.6 M elements: 65 -> 62. */
+ * alignment, residual stores 8 elements apart) 975, full residual lines 1057, non-temporal index stores 1169; the elements
+ * written back when they are read, so that the errors meet whole lines in the cache, 997 (they have left it by then). */
 constexpr uint32_t DENC_SMALL_CHUNK = 256;         /* up to here a wavefront codes a chunk */
 constexpr uint32_t DENC_MAX_CHUNK = 2048;
 constexpr uint32_t DENC_STEP = 4096;               /* elements per step: all of them can be survivors */
@@ -1629,7 +1784,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                                                   float *sv, uint32_t *si, uint32_t *wtot, uint32_t *__restrict__ err,
                                                   uint32_t bid, uint32_t nblk)
 {
-    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;     /* (unused for 16 / 32 bits) */
+    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t chunk = t.chunk;
     const uint32_t n_units = (t.n_tiles + t.dencTiles - 1) / t.dencTiles;
@@ -1668,7 +1823,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
             run_g = c.G[tile]; run_e = c.E[tile];
             Rbase = run_g + min(e_b, run_e);
             carry = 0;
-            head = BITS <= 8 && (Rbase % chunk) != 0u;
+            head = (Rbase % chunk) != 0u;
             const uint32_t nwt = (send - tile) * (TILE / DENC_WT);
             /* the next 4096 elements are fetched while the survivors of these are coded */
             float xn[DENC_ROWS][4];
@@ -1788,24 +1943,7 @@ __device__ __forceinline__ void dense_encode_body(float *__restrict__ r, const T
                 /* consume what is complete */
                 const uint32_t total = carry + nsurv;
                 uint32_t p = 0;
-                if (BITS >= 16) {
-                    /* no scale to wait for: every survivor is final at once */
-                    for (uint32_t i = tid; i < total; i += HTH) {
-                        const float xv = sv[i];
-                        const uint32_t at = si[i];
-                        idx_out[Pb + Rbase + i] = at + li_base;
-                        float left = __fsub_rn(xv, xv);  /* nothing is left behind (NaN where no value was) */
-                        if (BITS == 16) {
-                            const __half hv = __float2half_rn(xv);
-                            reinterpret_cast<__half *>(vb)[Rbase + i] = hv;
-                            left = __fsub_rn(xv, __half2float(hv));
-                        } else {
-                            reinterpret_cast<float *>(vb)[Rbase + i] = xv;
-                        }
-                        *reinterpret_cast<float *>(reinterpret_cast<char *>(rb) + at * 4u) = left;
-                    }
-                    p = total;
-                } else {
+                {
                     if (head) {
                         /* up to the next chunk boundary: part of a chunk that began before this stream */
                         const uint32_t to_edge = chunk - (Rbase % chunk);
@@ -1939,12 +2077,13 @@ __global__ __launch_bounds__(HTH, hard_wg_per_cu(BIG) * (HTH / 256)) void k_hard
     const uint32_t bid = blockIdx.x;
     uint32_t nblk = gridDim.x;
     /* band and zero-threshold buckets: survivors from the dense accumulator, threshold known */
-    if (stream_coding)
-        dense_encode_body<BITS, BIG>(r, t, c, idx, vdst, val, scales, reinterpret_cast<float *>(pool),
-                                     pool + denc_cap(BIG), pool + 2 * denc_cap(BIG), err, bid, nblk);
+    if constexpr (BITS <= 8)
+        if (stream_coding)
+            dense_encode_body<BITS, BIG>(r, t, c, idx, vdst, val, scales, reinterpret_cast<float *>(pool),
+                                         pool + denc_cap(BIG), pool + 2 * denc_cap(BIG), err, bid, nblk);
     if (threadIdx.x >= WG) return;                   /* what follows is work for four wavefronts */
-    if (!stream_coding)
-        write_dense_body<BITS == 32>(r, t, c, idx, vdst, (1u << PATH_BAND) | (1u << PATH_ZERO), bid, nblk);
+    if constexpr (BITS <= 8)
+        if (!stream_coding) write_dense_body(r, t, c, idx, vdst, (1u << PATH_BAND) | (1u << PATH_ZERO), bid, nblk);
     /* the dense passes: the first `team` workgroups only.  They are dispatched before the others
      * of this launch, and the team is small enough (one workgroup per compute unit) to be
      * resident at once even next to the teams of other contexts; a barrier that still cannot
@@ -1952,10 +2091,28 @@ __global__ __launch_bounds__(HTH, hard_wg_per_cu(BIG) * (HTH / 256)) void k_hard
     if (t.nhard[2] == 0u || bid >= team) return;
     wg_sync();
     nblk = team;
-    uint32_t *h = pool;
-    uint32_t *bar = t.nhard + 1;
-    dense_threshold(r, t, c, f0, f1, f2, h, bar, bid, nblk, true, err);
-    write_dense_body<BITS == 32>(r, t, c, idx, vdst, 1u << PATH_DENSE, bid, nblk);
+    if constexpr (BITS >= 16) {
+        code_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx, val, scales, err, nullptr, 0u, pool, bid, nblk);
+    } else {
+        dense_threshold(r, t, c, f0, f1, f2, pool, t.nhard + 1, bid, nblk, true, err);
+        write_dense_body(r, t, c, idx, vdst, 1u << PATH_DENSE, bid, nblk);
+    }
+}
+
+/* The buckets of a call with 16- or 32-bit values whose survivors come from the dense accumulator (more than an eighth sent), in the order of
+ * the streaming passes.  Bound by memory: 25.6 M elements, 0.13 to 0.71 of them as 32-bit values, 50 us on average (5.7 TB/s); by
+ * the stream that codes narrower values, with its steps of 4096 elements and scattered errors, 66. */
+constexpr uint32_t BAND_T = STH;
+template <int BITS, bool PAST>
+__global__ __launch_bounds__(BAND_T, 8) void k_band(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ idx, void *__restrict__ val, uint32_t *__restrict__ err)
+{
+    __shared__ __align__(16) uint32_t pool[2 * TILE];
+    const uint32_t tile = grid_tile();
+    if (tile >= t.n_tiles) return;
+    const uint4 d = t.desc[tile];
+    const uint32_t path = t.fast[d.z];
+    if (path != PATH_BAND && path != PATH_ZERO) return;
+    band_tile<BITS, BAND_T, PAST>(r, t, c, idx, val, err, tile, d, pool);
 }
 
 /* Value coding of the survivors the ordered writes above left uncoded in idx / vdst: every chunk
@@ -1985,7 +2142,7 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
                 const uint32_t path = t.fast[b];
                 todo = path != PATH_CAND && path != PATH_LEFT;
                 if (todo && stream_coding && path != PATH_DENSE)
-                    todo = BITS <= 8 && !chunk_coded_by_stream(t, c, b, cid - t.C[b], chunk_seg[cid]);
+                    todo = !chunk_coded_by_stream(t, c, b, cid - t.C[b], chunk_seg[cid]);
             }
             const uint64_t bal = __ballot(todo);
             if (threadIdx.x == 0) todo_sh = (uint32_t)bal;
@@ -2008,7 +2165,7 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
                 const uint32_t path = t.fast[b];
                 todo = path != PATH_CAND && path != PATH_LEFT;
                 if (todo && stream_coding && path != PATH_DENSE)
-                    todo = BITS <= 8 && !chunk_coded_by_stream(t, c, b, cid - t.C[b], chunk_seg[cid]);
+                    todo = !chunk_coded_by_stream(t, c, b, cid - t.C[b], chunk_seg[cid]);
             }
             const uint64_t bal = __ballot(todo);
             if (threadIdx.x == 0) todo_big = (uint32_t)bal;

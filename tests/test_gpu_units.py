@@ -76,3 +76,33 @@ def test_units_beside_pruned_parameters(kind):
             _, K, vb, ns = oracle.layout(off, ratio, bits, 2048)
             compare_payload(off, ratio, bits, 2048, (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns]), want)
             assert np.array_equal(c.r.cpu().numpy().view(np.uint32), c.r_host.view(np.uint32))
+
+
+@pytest.mark.parametrize("kind", ["normal", "block", "clusters", "zeros", "ties", "one"])
+@pytest.mark.parametrize("bits,nt", [(32, 3), (16, 3), (32, 7), (16, 7)])
+def test_whole_values_tile_by_tile(monkeypatch, kind, bits, nt):
+    """16- and 32-bit values beyond an eighth: tiles without survivors, of survivors only, with fewer of them than lines are
+    written whole for, ties that end inside a tile, a bucket's first and last tile; into the caches and past them."""
+    from paper_2506_16235_amd import binding as nsml
+    monkeypatch.setitem(nsml.Context.default_options, "nt", nt)
+    for seed, lead in ((1, 40_000), (2, 40_003)):
+        rng = np.random.default_rng([seed, bits])
+        off = W.offsets_of([lead, 2048 * 40 + seed - 1, 5, 2049, 100_000])
+        n = int(off[-1])
+        g = (rng.standard_normal(n) * 1e-3).astype(np.float32)
+        if kind != "normal":
+            for b in (1, 3, 4):
+                g[int(off[b]):int(off[b + 1])] = _values(kind, int(off[b + 1] - off[b]), rng)
+        w = rng.standard_normal(n).astype(np.float32)
+        for ratio in (0.126, 0.4, 0.93):
+            say(kind, bits, nt, lead, ratio)
+            c = Case(torch.from_numpy(g).to(DEV), off, chunk=24)
+            c.step(ratio, bits)
+            c.step(ratio, bits)
+            idx, val, sc = c.ctx.compress_pruned(c.g, c.r, torch.from_numpy(w).to(DEV), off, ratio, bits)
+            torch.cuda.synchronize()
+            c.ctx.path_stats()
+            want = oracle.compress_pruned(c.g_host, c.r_host, w, off, ratio, bits, 24, nthreads=8)
+            _, K, vb, ns = oracle.layout(off, ratio, bits, 24)
+            compare_payload(off, ratio, bits, 24, (idx.cpu().numpy().view(np.uint32)[:K], val.cpu().numpy()[:vb], sc.cpu().numpy()[:ns]), want)
+            assert np.array_equal(c.r.cpu().numpy().view(np.uint32), c.r_host.view(np.uint32))
