@@ -148,13 +148,27 @@ def _off(bucket_off) -> np.ndarray:
     return np.ascontiguousarray(bucket_off, dtype=np.uint64)
 
 
+def _at(a: np.ndarray) -> int:
+    """Address of an array (its ctypes attribute takes 2 us to make)."""
+    return a.__array_interface__["data"][0]
+
+
+def _totals(at: int, buckets: int, ratio: float, bits: int, chunk: int):
+    """-> (K, val_bytes, n_scales) of the offsets at an address."""
+    K, vb, ns = _u64(), _u64(), _u64()
+    rc = _lib.nsml_payload_layout(at, max(buckets, 0), ratio, bits, chunk, None, C.byref(K), C.byref(vb), C.byref(ns))
+    if rc != OK:
+        _check(rc, "nsml_payload_layout")
+    return K.value, vb.value, ns.value
+
+
 def payload_layout(bucket_off, ratio: float, bits: int, chunk: int = 2048):
     """-> (k_b uint64[B], K, val_bytes, n_scales)."""
     off = _off(bucket_off)
     B = len(off) - 1
     k_b = np.zeros(max(B, 1), dtype=np.uint64)
     K, vb, ns = _u64(), _u64(), _u64()
-    _check(_lib.nsml_payload_layout(off.ctypes.data, B, ratio, bits, chunk, k_b.ctypes.data,
+    _check(_lib.nsml_payload_layout(_at(off), B, ratio, bits, chunk, _at(k_b),
                                     C.byref(K), C.byref(vb), C.byref(ns)), "nsml_payload_layout")
     return k_b[:B], K.value, vb.value, ns.value
 
@@ -165,8 +179,9 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else C.c_void_p(t.data_ptr())
 
 
-def _stream(device) -> C.c_void_p:
-    return C.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device: int) -> C.c_void_p:
+    """torch's current stream on the device (by index: no Stream object is made)."""
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(device))
 
 
 def validate_buffers(device, bucket_off, ratio, bits, chunk, *, n=None, grad=None, residual=None,
@@ -174,39 +189,52 @@ def validate_buffers(device, bucket_off, ratio, bits, chunk, *, n=None, grad=Non
     """The C ABI carries no capacities, so the sizes, types and placement of every tensor are
     checked here, before a pointer reaches a kernel: a short buffer would be an out-of-bounds
     device write.  Raises ValueError; returns (K, val_bytes, n_scales)."""
-    device = torch.device(device)
     off = _off(bucket_off)
+    return _validate(torch.device(device), off, _at(off), ratio, bits, chunk, n, grad, residual, weights, idx, val, scales, dense)
+
+
+_F32, _INDEX, _BYTES = (torch.float32,), (torch.int32, torch.uint32), (torch.uint8, torch.int8)
+
+
+def _validate(device, off, at, ratio, bits, chunk, n, grad, residual, weights, idx, val, scales, dense):
+    """validate_buffers for offsets as _off gives them, at address `at`."""
     if off.ndim != 1 or len(off) < 2:
         raise ValueError("bucket_off needs at least two entries")
     total = int(off[-1])
     if n is not None and int(n) != total:
         raise ValueError(f"n = {n} but bucket_off ends at {total}")
-    _, K, vb, ns = payload_layout(off, ratio, bits, chunk)
+    K, vb, ns = _totals(at, len(off) - 1, ratio, bits, chunk)
 
-    def want(name, t, dtype, numel, exact):
-        if t is None:
-            return
+    def want(name, t, dtypes, numel, exact):
         if not isinstance(t, torch.Tensor):
             raise ValueError(f"{name} must be a torch tensor")
         if t.device != device:
             raise ValueError(f"{name} is on {t.device}, the context is on {device}")
-        if t.dtype not in (dtype if isinstance(dtype, tuple) else (dtype,)):
+        if t.dtype not in dtypes:
             raise ValueError(f"{name} has dtype {t.dtype}")
         if not t.is_contiguous():
             raise ValueError(f"{name} is not contiguous")
-        if (t.numel() != numel) if exact else (t.numel() < numel):
-            raise ValueError(f"{name} holds {t.numel()} elements, needs {'exactly' if exact else 'at least'} {numel}")
+        have = t.numel()
+        if (have != numel) if exact else (have < numel):
+            raise ValueError(f"{name} holds {have} elements, needs {'exactly' if exact else 'at least'} {numel}")
 
-    want("grad", grad, torch.float32, total, True)
-    want("residual", residual, torch.float32, total, True)
-    want("weights", weights, torch.float32, total, True)
-    want("dense", dense, torch.float32, total, True)
-    want("idx", idx, (torch.int32, torch.uint32), K, False)
-    want("val", val, (torch.uint8, torch.int8), vb, False)
+    if grad is not None:
+        want("grad", grad, _F32, total, True)
+    if residual is not None:
+        want("residual", residual, _F32, total, True)
+    if weights is not None:
+        want("weights", weights, _F32, total, True)
+    if dense is not None:
+        want("dense", dense, _F32, total, True)
+    if idx is not None:
+        want("idx", idx, _INDEX, K, False)
+    if val is not None:
+        want("val", val, _BYTES, vb, False)
     if bits <= 8:
         if (idx is not None or val is not None) and scales is None:
             raise ValueError("scales is required for 8- and 4-bit codes")
-        want("scales", scales, torch.float32, ns, False)
+        if scales is not None:
+            want("scales", scales, _F32, ns, False)
     return K, vb, ns
 
 
@@ -248,8 +276,9 @@ class Context:
 
     def alloc_payload(self, bucket_off, ratio: float, bits: int):
         """Device buffers sized by nsml_payload_layout: (idx, val, scales)."""
-        _, K, vb, ns = payload_layout(bucket_off, ratio, bits, self.chunk)
-        dev = torch.device("cuda", self.device)
+        off = _off(bucket_off)
+        K, vb, ns = _totals(_at(off), len(off) - 1, ratio, bits, self.chunk)
+        dev = self._dev
         idx = torch.empty(K, dtype=torch.int32, device=dev)
         val = torch.empty((vb + 3) // 4 * 4, dtype=torch.uint8, device=dev)
         scales = torch.empty(max(ns, 1), dtype=torch.float32, device=dev)
@@ -263,9 +292,9 @@ class Context:
         off = _off(bucket_off)
         if idx is None:
             idx, val, scales = self.alloc_payload(off, ratio, bits)
-        validate_buffers(self._dev, off, ratio, bits, self.chunk, grad=grad, residual=residual,
-                         idx=idx, val=val, scales=scales)
-        rc = _lib.nsml_compress(self._h, _ptr(grad), _ptr(residual), grad.numel(), off.ctypes.data,
+        at = _at(off)
+        _validate(self._dev, off, at, ratio, bits, self.chunk, None, grad, residual, None, idx, val, scales, None)
+        rc = _lib.nsml_compress(self._h, _ptr(grad), _ptr(residual), grad.numel(), at,
                                 len(off) - 1, float(ratio), int(bits), _ptr(idx), _ptr(val),
                                 _ptr(scales), _stream(self.device))
         _check(rc, "nsml_compress", self._h)
@@ -278,10 +307,10 @@ class Context:
         off = _off(bucket_off)
         if idx is None:
             idx, val, scales = self.alloc_payload(off, ratio, bits)
-        validate_buffers(self._dev, off, ratio, bits, self.chunk, grad=grad, residual=residual,
-                         weights=weights, idx=idx, val=val, scales=scales)
+        at = _at(off)
+        _validate(self._dev, off, at, ratio, bits, self.chunk, None, grad, residual, weights, idx, val, scales, None)
         rc = _lib.nsml_compress_pruned(self._h, _ptr(grad), _ptr(residual), _ptr(weights), grad.numel(),
-                                       off.ctypes.data, len(off) - 1, float(ratio), int(bits),
+                                       at, len(off) - 1, float(ratio), int(bits),
                                        _ptr(idx), _ptr(val), _ptr(scales), _stream(self.device))
         _check(rc, "nsml_compress_pruned", self._h)
         return idx, val, scales
@@ -291,10 +320,10 @@ class Context:
         off = _off(bucket_off)
         if out is None:
             out = torch.empty(int(n), dtype=torch.float32, device=self._dev)
-        validate_buffers(self._dev, off, ratio, bits, self.chunk, n=n, idx=idx, val=val, scales=scales,
-                         dense=out)
+        at = _at(off)
+        _validate(self._dev, off, at, ratio, bits, self.chunk, n, None, None, None, idx, val, scales, out)
         rc = _lib.nsml_decompress(self._h, _ptr(idx), _ptr(val), _ptr(scales), int(n),
-                                  off.ctypes.data, len(off) - 1, float(ratio), int(bits),
+                                  at, len(off) - 1, float(ratio), int(bits),
                                   _ptr(out), _stream(self.device))
         _check(rc, "nsml_decompress", self._h)
         return out
@@ -303,10 +332,10 @@ class Context:
                               dense: torch.Tensor) -> torch.Tensor:
         """dense[bucket_off[b] + idx[j]] += decoded value j, in place."""
         off = _off(bucket_off)
-        validate_buffers(self._dev, off, ratio, bits, self.chunk, idx=idx, val=val, scales=scales,
-                         dense=dense)
+        at = _at(off)
+        _validate(self._dev, off, at, ratio, bits, self.chunk, None, None, None, None, idx, val, scales, dense)
         rc = _lib.nsml_decompress_accumulate(self._h, _ptr(idx), _ptr(val), _ptr(scales),
-                                             dense.numel(), off.ctypes.data, len(off) - 1,
+                                             dense.numel(), at, len(off) - 1,
                                              float(ratio), int(bits), _ptr(dense), _stream(self.device))
         _check(rc, "nsml_decompress_accumulate", self._h)
         return dense
@@ -315,7 +344,7 @@ class Context:
         """-> (norm of the last compressed gradient, per-bucket norms or None).  Synchronises."""
         tot = _dbl()
         per = np.zeros(n_buckets, dtype=np.float64) if n_buckets else None
-        _check(_lib.nsml_last_l2norm(self._h, C.byref(tot), per.ctypes.data if n_buckets else None),
+        _check(_lib.nsml_last_l2norm(self._h, C.byref(tot), _at(per) if n_buckets else None),
                "nsml_last_l2norm", self._h)
         return tot.value, per
 
@@ -366,10 +395,18 @@ def decompress_static(idx: torch.Tensor, val: torch.Tensor, scales: Optional[tor
     dev = idx.device
     if out is None:
         out = torch.empty(int(n), dtype=torch.float32, device=dev)
-    validate_buffers(dev, off, ratio, bits, chunk, n=n, idx=idx, val=val, scales=scales, dense=out)
-    with torch.cuda.device(dev):
-        rc = _lib.nsml_decompress_static(_ptr(idx), _ptr(val), _ptr(scales), int(n), off.ctypes.data,
-                                         len(off) - 1, float(ratio), int(bits), int(chunk), _ptr(out), _stream(dev))
+    at, index = _at(off), dev.index
+    _validate(dev, off, at, ratio, bits, chunk, n, None, None, None, idx, val, scales, out)
+
+    def call():
+        return _lib.nsml_decompress_static(_ptr(idx), _ptr(val), _ptr(scales), int(n), at, len(off) - 1, float(ratio),
+                                           int(bits), int(chunk), _ptr(out), _stream(index))
+
+    if dev.type == "cuda" and torch.cuda.current_device() == index:
+        rc = call()
+    else:
+        with torch.cuda.device(dev):
+            rc = call()
     _check(rc, "nsml_decompress_static")
     return out
 
@@ -382,14 +419,14 @@ def calibration_stream(mode: str, a: torch.Tensor, b: torch.Tensor, nontemporal:
     nbytes = a.numel() * a.element_size()
     assert nbytes == b.numel() * b.element_size()
     _check(_lib.nsml_calibration_stream(CALIB_MODES[mode], _ptr(a), _ptr(b), nbytes, 1 if nontemporal else 0,
-                                        _stream(a.device)), "nsml_calibration_stream")
+                                        _stream(a.device.index)), "nsml_calibration_stream")
 
 
 def calibration_copy(src: torch.Tensor, dst: torch.Tensor):
     """Plain copy kernel of known size (src -> dst, same byte size, a multiple of 16)."""
     nbytes = src.numel() * src.element_size()
     assert nbytes == dst.numel() * dst.element_size()
-    _check(_lib.nsml_calibration_copy(_ptr(src), _ptr(dst), nbytes, _stream(src.device)),
+    _check(_lib.nsml_calibration_copy(_ptr(src), _ptr(dst), nbytes, _stream(src.device.index)),
            "nsml_calibration_copy")
 
 
