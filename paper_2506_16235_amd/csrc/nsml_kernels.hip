@@ -665,25 +665,25 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         Tables tw = t;
         tw.k = c->d_kw; tw.T = c->d_Tw; tw.need = c->d_needw; tw.fast = c->d_wfast;
         tw.par = c->d_wpar;                            /* the staged band of weight keys (never without an upper bound) */
+        const uint32_t *known = c->whistory && !c->wband_miss ? c->d_wprevT : nullptr;      /* what the last call found */
         if (!c->force_dense)
-            LAUNCH(c, KID_SAMPLE, st, k_sample<false>, c->n_samp, weights, (const float *)nullptr, tw, h.hs);
-        LAUNCH(c, KID_WPLAN, st, k_wpredict, B, tw, h.hs, c->force_dense, c->wband_miss,
-               c->whistory ? (const uint32_t *)c->d_wprevT : (const uint32_t *)nullptr, (const uint32_t *)c->d_wprevHw);
+            LAUNCH(c, KID_SAMPLE, st, k_sample<false>, c->n_samp, weights, (const float *)nullptr, tw, h.hs, known);
+        LAUNCH(c, KID_WPLAN, st, k_wpredict, B, tw, h.hs, c->force_dense, c->wband_miss, known, (const uint32_t *)c->d_wprevHw);
         if (bins) LAUNCHB(c, KID_WHIST, st, k_whist<false>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
         else LAUNCHB(c, KID_WHIST, st, k_whist<true>, sgrid, WTH, weights, tw, h.hw, cd0, c->d_pmask);
-        if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, 0, weights);
-        LAUNCHB(c, KID_WPLAN, st, k_wplan, B, NHB, tw, h.hw, cd0, c->d_wnband);
         /* buckets decided from their band: undecided keys, threshold key and tie count, the pruned
-         * band elements' bits; buckets on the dense passes (no band, or one that missed):
-         * everything in one resident launch */
-        if (!c->force_dense) {
-            LAUNCH(c, KID_SELECT, st, k_select_count<false>, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, (const uint32_t *)nullptr, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights);
+         * band elements' bits; buckets on the dense passes (no band, or one that missed): by the last launch's first workgroups */
+        if (c->force_dense) {
+            LAUNCH(c, KID_WPLAN, st, k_wplan_dense, (B + WG - 1) / WG, tw);
+            LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
+        } else {
+            if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, weights);
+            LAUNCH(c, KID_SELECT, st, k_select_count<false>, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights, c->d_wnband);
             LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                     (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1, c->force_rescan);
-            LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
+            LAUNCH(c, KID_WMASK, st, k_wrest, (uint32_t)c->n_cu + (c->n_tiles + 15) / 16, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1, (uint32_t)c->n_cu, h.hw,
+                   (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
         }
-        LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
-        LAUNCH(c, KID_WPLAN, st, k_wremember, (B + WG - 1) / WG, tw, (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
         t.pmask = c->d_pmask;
     }
 
@@ -695,7 +695,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         if (stale) { rc = chunk_map(c, st); if (rc) return rc; }
     } else {
         if (!c->force_dense)
-            LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs);
+            LAUNCH(c, KID_SAMPLE, st, k_sample<true>, c->n_samp, grad, (const float *)residual, t, h.hs, (const uint32_t *)nullptr);
         LAUNCH(c, KID_PREDICT, st, k_predict, B, t, h.hs, c->force_dense);
     }
 #define NSML_EF(EMIT_, PRUNE_, NT_, HIST_) LAUNCHB(c, KID_EF_EMIT, st, (k_ef_emit<EMIT_, PRUNE_, NT_, HIST_>), sgrid, STH, grad, residual, t, h.hw, cd0, c->d_tile_sq)
@@ -704,7 +704,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
     else if (bins) { if (pruned) NSML_EF(true, true, false, false); else NSML_EF(true, false, false, false); }
     else { if (pruned) NSML_EF(true, true, false, true); else NSML_EF(true, false, false, true); }
 #undef NSML_EF
-    if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, 1, (const float *)residual);
+    if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, t, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, (const float *)residual);
     if (c->force_dense) LAUNCHB(c, KID_PLAN, st, k_plan_dense, B, 1024, t, (const double *)c->d_tile_sq, c->d_l2sq);
     /* the workgroups that meet at barriers on the dense passes: one per compute unit, so that the teams of two or
      * three contexts working at the same time still fit the device together */
@@ -716,7 +716,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         /* buckets decided from their staged elements: undecided keys set apart, threshold and
          * survivor order per bucket, then the payload of the candidate-path buckets */
         const uint4 *selw = c->d_selw;
-        LAUNCH(c, KID_SELECT, st, k_select_count<true>, c->n_sel, t, cd0, selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags, (const float *)residual);
+        LAUNCH(c, KID_SELECT, st, k_select_count<true>, c->n_sel, t, cd0, selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags, (const float *)residual, (uint32_t *)nullptr);
         LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, t, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                 (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, c->d_chunk_seg, c->d_flags, c->force_rescan);
         {

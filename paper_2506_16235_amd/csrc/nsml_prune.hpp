@@ -17,7 +17,7 @@ namespace {
  * before found (weights move little between steps).  One pass over the weights stages the
  * elements inside the band, counts those above it and writes the pruning bitmap (1 = pruned)
  * for everything outside it; the threshold key T and the number e of admitted elements equal to
- * T come from the staged elements alone (k_select_count / k_select_finish), and k_wfix sets the
+ * T come from the staged elements alone (k_select_count / k_select_finish), and k_wrest sets the
  * bits of the band elements that turn out pruned.  A bucket whose band missed or overflowed
  * takes the dense ordered passes (k_whard), which write its bitmap.  The gradient kernels read one bit per parameter.  Pruned parameters are
  * neither counted nor emitted, and their accumulated gradient is still written to the residual:
@@ -34,17 +34,14 @@ __global__ __launch_bounds__(WG) void k_wpredict(Tables t, uint32_t *__restrict_
     const uint64_t nb = t.off[b + 1] - t.off[b];
     const uint32_t k = t.k[b];
     const KeyPar nothing = make_uint4(NONE, NONE, NONE, SH1);
-    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by k_wplan ([1]: the barrier of k_whard) */
+    if (b == 0 && tid < 4) t.nhard[tid] = 0u;      /* counted anew by k_select_count ([1]: the barrier of the dense passes) */
     if (nb == 0 || k == 0 || force_dense) {
         if (tid == 0) t.par[b] = nothing;
         return;
     }
-    DigitWalk<NB0> w;
-    w.load(hist_s + (uint64_t)b * NB0, tmp);
-    w.clear(hist_s + (uint64_t)b * NB0);
-    if (prevT && prevT[b] != NONE && !miss) {
+    if (prevT && prevT[b] != NONE) {                 /* (then no sample was taken) */
         /* weights move little from one step to the next: a narrow band around the threshold the
-         * last call found (k_wremember chose its width); if it misses, the dense passes decide */
+         * last call found (remember_weights chose its width); if it misses, the dense passes decide */
         if (tid == 0) {
             const uint32_t T = prevT[b], hw = prevHw[b];
             KeyPar p;
@@ -57,6 +54,9 @@ __global__ __launch_bounds__(WG) void k_wpredict(Tables t, uint32_t *__restrict_
         }
         return;
     }
+    DigitWalk<NB0> w;
+    w.load(hist_s + (uint64_t)b * NB0, tmp);
+    w.clear(hist_s + (uint64_t)b * NB0);
     const uint32_t m = w.total;
     if (m == 0) {
         if (tid == 0) t.par[b] = nothing;
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(WG) void k_wpredict(Tables t, uint32_t *__restrict_
  * with a band [lo, hi): every element whose key lies in the band is staged and counted in its bin;
  * the elements above the band are only counted (c.G); and the pruning bitmap gets a first version: 1
  * for the elements below the band (pruned for certain), 0 for the rest (the few band elements that
- * end up pruned are set later by k_wfix).  A bucket without a band (no usable sample, or the dense
+ * end up pruned are set later by k_wrest).  A bucket without a band (no usable sample, or the dense
  * passes were asked for) is left to k_whard.  Bound by reading w, 4 bytes per element, a third of what
  * the gradient's pass has in flight per tile: so two wavefronts take a tile, 16 tiles per compute unit
  * (109 M elements: 147 us with eight wavefronts per tile). */
@@ -151,62 +151,52 @@ __global__ __launch_bounds__(WTH, 8) void k_whist(const float *__restrict__ w, T
         word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)word, 0x104, 0xF, 0xF, true);     /* from lane + 4 */
         if ((lane & 7u) == 0u) pmask[(uint64_t)tile * (TILE / 32) + ((u * WTH + tid) >> 3)] = word;
     }
-    stage_tile<WTH, HIST>(a, m, p, b, tile, (uint32_t)(g0 - t.off[b]), c, hist, false, t.ovf + b, sm);
+    stage_tile<WTH, HIST>(a, m, p, b, tile, (uint32_t)(g0 - t.off[b]), c, hist, t.ovf + b, sm);
 }
 
-/* Per bucket: the bin of the kw-th largest |weight|, from the counts above the band and the bins of
- * the band; the staged band decides the rest iff the kw-th largest lies inside it, no staging
- * segment overflowed and the list of undecided keys holds them, otherwise the bucket takes the dense passes. */
-__global__ __launch_bounds__(NHB) void k_wplan(Tables t, uint32_t *__restrict__ hist, Cand c, uint32_t *__restrict__ nband_out)
+/* The plan of a bucket of weights, from the exact counts as plan_bucket has them for the gradient: the staged band decides the rest iff the kw-th
+ * largest lies inside it, no staging segment overflowed and the list of undecided keys holds them, otherwise the
+ * bucket takes the dense passes (k_whard). */
+__device__ __forceinline__ Plan plan_weights(const Tables &t, const KeyPar &p, uint32_t want, bool found, uint32_t bin, uint32_t above, uint32_t at,
+                                             uint32_t ovf, uint32_t segs)
 {
-    __shared__ uint32_t wsum[NHB / 64], red[NHB / 64], res[3];
-    const uint32_t b = blockIdx.x, tid = threadIdx.x;
-    const uint32_t want = t.k[b];
-    if (want == 0) {
-        if (tid == 0) { t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_BAND; t.sh[b] = SH0; }
-        return;
-    }
-    const KeyPar p = t.par[b];
-    uint32_t n_above = 0;
-    {
-        uint32_t ca = 0;
-#pragma unroll 4
-        for (uint32_t s = t.tile0[b] + tid; s < t.tile0[b + 1]; s += NHB) ca += c.G[s];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) ca += __shfl_xor(ca, d, 64);
-        if ((tid & 63) == 0) red[tid >> 6] = ca;
-        wg_sync();
-        for (uint32_t w = 0; w < NHB / 64; ++w) n_above += red[w];
-    }
-    uint32_t total;
-    const bool found = window_find(hist + (uint64_t)b * NHC * HROW, n_above, want, wsum, res, total);
-    if (tid != 0) return;
-    const uint32_t ovf = t.ovf[b];
-    if (ovf) t.ovf[b] = 0u;
-    nband_out[b] = total;
     const uint32_t top = (p.z - 1u) >> p.w;
-    const bool known = p.x != NONE && found && !(res[0] == (uint32_t)NHB - 1u && (p.x >> p.w) != top - res[0]);
-    t.T[b] = known ? top - res[0] : 0u;
-    t.need[b] = known ? want - res[1] : want;
-    t.sh[b] = known ? p.w : SH_NONE;
-    if (known && !ovf && list_pays(res[2], t.tile0[b + 1] - t.tile0[b], t.n_tiles)) {
-        t.fast[b] = PATH_BAND;
-    } else {
-        t.fast[b] = PATH_DENSE;
-        atomicAdd(t.nhard + 2, 1u);                      /* k_whard has work */
-        if (!known) atomicAdd(t.nhard + 3, 1u);
+    const bool known = p.x != NONE && found && !(bin == (uint32_t)NHB - 1u && (p.x >> p.w) != top - bin);      /* (not in the open last bin) */
+    Plan q = {PATH_DENSE, 0u, want, SH_NONE, 0u};
+    if (known) {
+        q.T = top - bin; q.need = want - above; q.sh = p.w;
+        if (!ovf && list_pays(at, segs, t.n_tiles)) q.path = PATH_BAND;
     }
+    return q;
+}
+/* Its record (one thread per bucket). */
+__device__ __forceinline__ void plan_weights_store(const Tables &t, uint32_t b, const Plan &q)
+{
+    t.T[b] = q.T;
+    t.need[b] = q.need;
+    t.sh[b] = q.sh;
+    t.fast[b] = q.path;
+    if (q.path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);      /* k_whard has work */
+    if (q.path == PATH_DENSE && q.sh == SH_NONE) atomicAdd(t.nhard + 3, 1u);
+}
+__device__ __forceinline__ void plan_weights_empty(const Tables &t, uint32_t b) { t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_BAND; t.sh[b] = SH0; }
+
+/* The plan when every bucket is sent to the dense passes (force_dense). */
+__global__ __launch_bounds__(WG) void k_wplan_dense(Tables t)
+{
+    const uint32_t b = blockIdx.x * WG + threadIdx.x;
+    if (b >= t.B) return;
+    if (t.k[b] == 0u) plan_weights_empty(t, b);
+    else plan_weights_store(t, b, Plan{PATH_DENSE, 0u, t.k[b], SH_NONE, 0u});
 }
 
 /* What the next call's band is built from, per bucket: the threshold key this call found, and a
  * half-width that would have staged about 0.2 % of the bucket (at least 4096 elements, but no more
  * than a sixteenth of the bucket: a staging segment holds a quarter of its tile) at the
  * density of keys this call's band had.  A bucket that took the dense passes remembers nothing. */
-__global__ __launch_bounds__(WG) void k_wremember(Tables t, const uint32_t *__restrict__ nband, uint32_t *__restrict__ prevT,
-                                                  uint32_t *__restrict__ prevHw)
+__device__ __forceinline__ void remember_weights(const Tables &t, uint32_t b, const uint32_t *__restrict__ nband, uint32_t *__restrict__ prevT,
+                                                 uint32_t *__restrict__ prevHw)
 {
-    const uint32_t b = blockIdx.x * WG + threadIdx.x;
-    if (b >= t.B) return;
     const uint64_t nb = t.off[b + 1] - t.off[b];
     const KeyPar p = t.par[b];
     if (!t.fast[b] || t.k[b] == 0u || t.T[b] == NONE || p.x == NONE) { prevT[b] = NONE; return; }

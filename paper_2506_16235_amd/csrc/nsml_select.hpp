@@ -11,15 +11,17 @@ namespace {
 /* ------------------------------------------------------------------ sample / predict */
 
 /* Level-0 histogram of a sample of acc = grad + residual: runs of 16 consecutive elements,
- * every run of a small bucket, evenly spaced ones of a large one. */
+ * every run of a small bucket, evenly spaced ones of a large one.  skip (weights): buckets whose word is not NONE need no sample
+ * (see k_wpredict; 109 M weights 9.4 us, so 4.6). */
 template <bool SUM>   /* SUM: keys of g + r; else keys of g alone (the weight stage) */
 __global__ __launch_bounds__(WG) void k_sample(const float *__restrict__ g, const float *__restrict__ r,
-                                               Tables t, uint32_t *__restrict__ hist_s)
+                                               Tables t, uint32_t *__restrict__ hist_s, const uint32_t *__restrict__ skip)
 {
     __shared__ uint32_t h[NB0];
     const uint32_t tid = threadIdx.x;
     for (int i = tid; i < NB0; i += WG) h[i] = 0;
     const uint32_t b = find_bucket<uint32_t>(t.samp0, t.B, blockIdx.x);
+    if (!SUM && skip && skip[b] != NONE) return;     /* same for the whole workgroup */
     const uint32_t wi = blockIdx.x - t.samp0[b];
     const uint64_t lo = t.off[b], hi = t.off[b + 1];
     const uint64_t a0 = lo & ~3ull;
@@ -356,7 +358,7 @@ struct StageShared {
 template <int NTH, bool HIST>
 __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4], const uint32_t (&cm)[TILE / (4 * NTH)], const KeyPar &p,
                                            uint32_t b, uint32_t tile, uint32_t li0, const Cand &c, uint32_t *__restrict__ hist,
-                                           bool count_hi, uint32_t *__restrict__ ovf, StageShared<HIST> &sm)
+                                           uint32_t *__restrict__ ovf, StageShared<HIST> &sm)
 {
     constexpr int Q = TILE / (4 * NTH);
     constexpr uint32_t W = NTH / 64;
@@ -416,7 +418,7 @@ __device__ __forceinline__ void stage_tile(const float (&a)[TILE / (4 * NTH)][4]
         c.E[tile] = tlo;
         if (all > SEG_CAP) *ovf = 1u;
         if constexpr (HIST)
-            if (count_hi && thi) atomicAdd(hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW + NHB, thi);
+            if (thi) atomicAdd(hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW + NHB, thi);
     }
     if (all == 0u) return;                             /* same for the whole workgroup */
     const uint32_t top = (p.z - 1u) >> p.w;
@@ -492,7 +494,7 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
     if (EMIT) {
         if (PRUNE) m &= ~pruned_bits(t.pmask, tile, tid);
         const uint32_t b = d.z;
-        stage_tile<STH, HIST>(av, mv, t.par[b], b, tile, (uint32_t)(gi - e - t.off[b]), c, hist, true, t.ovf + b, sm);
+        stage_tile<STH, HIST>(av, mv, t.par[b], b, tile, (uint32_t)(gi - e - t.off[b]), c, hist, t.ovf + b, sm);
     } else {
         wg_sync();
     }
@@ -502,36 +504,6 @@ __global__ __launch_bounds__(STH, 8) void k_ef_emit(const float *__restrict__ g,
         for (uint32_t w = 0; w < STH / 64; w += 4) tot += (sq_w[w] + sq_w[w + 1]) + (sq_w[w + 2] + sq_w[w + 3]);
         tile_sq[tile] = tot;
     }
-}
-
-/* What the exact counts of a bucket's weights say (the gradient's: k_select_count).  hist_b, n_hi: the
- * window's bins (NHC copies) and the number of elements at or above its top.  Every thread of a workgroup of NHB
- * threads calls it with its own bin (thread i: bin i, counted from the top of the window) and the
- * want-th key's bin comes back in res[0] with what lies above it (res[1]) and in it (res[2]); false in
- * every thread if the window does not hold that key.  The bins are zeroed for the next call. */
-__device__ __forceinline__ bool window_find(uint32_t *__restrict__ hist_b, uint32_t n_hi, uint32_t want, uint32_t *wsum,
-                                            uint32_t *res, uint32_t &total)
-{
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t cnt = 0;
-#pragma unroll
-    for (uint32_t q = 0; q < NHC; ++q) {
-        const uint32_t v = hist_b[q * HROW + tid];
-        if (v) hist_b[q * HROW + tid] = 0u;
-        cnt += v;
-    }
-    uint32_t incl = cnt;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) { const uint32_t y = __shfl_up(incl, d, 64); if (lane >= (uint32_t)d) incl += y; }
-    if (lane == 63) wsum[wave] = incl;
-    wg_sync();
-    total = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < NHB / 64; ++w) { incl += w < wave ? wsum[w] : 0u; total += wsum[w]; }
-    const uint64_t upto = (uint64_t)n_hi + incl;
-    if (upto >= want && upto - cnt < want) { res[0] = tid; res[1] = (uint32_t)(upto - cnt); res[2] = cnt; }
-    wg_sync();
-    return n_hi < want && (uint64_t)n_hi + total >= want;
 }
 
 /* How a bucket is decided (PATH_*), from its exact counts: n_hi elements at or above the window's top; found: the k-th key lies

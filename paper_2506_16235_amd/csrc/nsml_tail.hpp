@@ -23,7 +23,7 @@
  *                    taken from the dense accumulator and coded in one streaming pass;
  *                    PATH_DENSE: every radix step over the dense accumulator, barriers between
  *   k_quant          codes the chunks k_hard wrote uncoded
- *   k_wfix, k_whard  the same machinery for the pruning bitmap of the weight stage
+ *   k_wrest, k_whard the same machinery for the pruning bitmap of the weight stage
  * Every small kernel here is a handful of dependent memory round trips long, which is what a
  * small kernel costs on this GPU; tables that a kernel would otherwise search for (workgroup ->
  * segments, chunk -> bucket, chunk -> first segment) are therefore prepared by the kernel before.
@@ -170,25 +170,23 @@ __device__ __forceinline__ bool pruned_elem(const uint32_t *__restrict__ pmask, 
  * way 65, one load after the other 71). */
 constexpr uint32_t BINS_U = 8;             /* entries a lane has in flight */
 __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__restrict__ selw, uint32_t selSh,
-                                             uint32_t *__restrict__ hist, int count_hi, const float *__restrict__ r)
+                                             uint32_t *__restrict__ hist, const float *__restrict__ r)
 {
     __shared__ uint32_t h[NHB], hi_all;
     const uint4 wk = selw[blockIdx.x];
     const uint32_t b = wk.x, s0 = wk.y, s1 = wk.z, tid = threadIdx.x;
     const uint32_t lanes = WG >> selSh, seg = s0 + (tid >> (8u - selSh)), gl = tid & (lanes - 1u);
     const uint32_t cnt = seg < s1 ? c.cnt[seg] : 0u;
-    uint32_t hi = count_hi && gl == 0u && seg < s1 ? c.G[seg] : 0u;     /* elements at or above the window's top */
+    uint32_t hi = gl == 0u && seg < s1 ? c.G[seg] : 0u;     /* elements at or above the window's top */
     const KeyPar p = t.par[b];
     uint32_t *row = hist + ((uint64_t)b * NHC + blockIdx.x % NHC) * HROW;
     if (p.x == NONE) return;                         /* no guess; the same for the whole workgroup */
-    if (count_hi) {
-        if (tid == 0) hi_all = 0u;
-        wg_sync();
-        hi = wave_incl_scan(hi);
-        if ((tid & 63u) == 63u && hi) atomicAdd(&hi_all, hi);
-        wg_sync();
-        if (tid == 0 && hi_all) atomicAdd(row + NHB, hi_all);
-    }
+    if (tid == 0) hi_all = 0u;
+    wg_sync();
+    hi = wave_incl_scan(hi);
+    if ((tid & 63u) == 63u && hi) atomicAdd(&hi_all, hi);
+    wg_sync();
+    if (tid == 0 && hi_all) atomicAdd(row + NHB, hi_all);
     if (p.x == p.y) return;                          /* nothing was staged */
     if (!__syncthreads_or(cnt != 0u)) return;
     for (uint32_t i = tid; i < (uint32_t)NHB; i += WG) h[i] = 0u;
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
     hist_flush(h, row, NHB);
 }
 
-/* PLAN (the gradient): every workgroup first makes its bucket's plan for itself from the window's bins, 33 KB that the L2
+/* Every workgroup first makes its bucket's plan for itself from the window's bins, 33 KB that the L2
  * holds; a kernel of its own for it was one more that the next had to wait for (ResNet-50's 161 buckets: 9.0 + 9.9 us, so
  * 12.8; BERT's 199: 9.2 + 10.2, so 15.3; one bucket of 1 Mi elements: 6.0 + 5.4, so 7.0).
  * Then, per staging segment of the buckets decided from staged elements (PATH_CAND, PATH_BAND), with
@@ -253,11 +251,12 @@ __global__ __launch_bounds__(WG) void k_bins(Tables t, Cand c, const uint4 *__re
  * of every wavefront keeps the count of segment l, from the ballots of the rows and the part of each row
  * that belongs to it.  Overflowed segments are read from the accumulator, the next one on its way while one is counted:
  * up to 16 of them are a workgroup's longest work (BERT-shaped gradient at 0.1: 42 us one after the other, so 28). */
-template <bool PLAN>
+template <bool GRAD>      /* GRAD: the gradient; else weights (nband: how many the bucket's band holds) */
 __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const uint4 *__restrict__ selw,
                                                      const uint32_t *__restrict__ hist,
                                                      uint32_t *__restrict__ cursor, uint2 *__restrict__ part,
-                                                     uint32_t *__restrict__ lkey, uint32_t *__restrict__ err, const float *__restrict__ r)
+                                                     uint32_t *__restrict__ lkey, uint32_t *__restrict__ err, const float *__restrict__ r,
+                                                     uint32_t *__restrict__ nband)
 {
     __shared__ uint32_t lk[LCAP];
     __shared__ uint32_t pre[SELC_SEGS], cg[SELC_SEGS];
@@ -272,7 +271,7 @@ __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const 
     uint32_t mg0 = mine ? c.G[ms] : 0u;              /* band mode: elements above the band, counted by the streaming pass */
     const KeyPar p = t.par[b];
     uint32_t path, b0, sh;                           /* b0: the key bits from position sh up */
-    if constexpr (PLAN) {
+    {
         /* the bucket's plan, made by each of its workgroups for itself, four bins of the window per thread from the top */
         const uint32_t seg0 = t.tile0[b], segs_b = t.tile0[b + 1] - seg0, want = t.k[b], ovf = t.ovf[b];
         const uint32_t *row = hist + (uint64_t)b * NHC * HROW;
@@ -297,14 +296,15 @@ __global__ __launch_bounds__(WG, 8) void k_select_count(Tables t, Cand c, const 
             cg[0] = 4u * tid + i; cg[1] = (uint32_t)acc; cg[2] = i == 0 ? h[0] : i == 1 ? h[1] : i == 2 ? h[2] : h[3];
         }
         wg_sync();
-        const Plan q = plan_bucket(t, b, p, want, n_hi, tot, n_hi < want && (uint64_t)n_hi + tot >= want, cg[0], cg[1], cg[2], ovf, segs_b);
-        if (s0 == seg0 && tid == 0) plan_store(t, b, q);
+        const bool found = n_hi < want && (uint64_t)n_hi + tot >= want;
+        const Plan q = GRAD ? plan_bucket(t, b, p, want, n_hi, tot, found, cg[0], cg[1], cg[2], ovf, segs_b) : plan_weights(t, p, want, found, cg[0], cg[1], cg[2], ovf, segs_b);
+        if (s0 == seg0 && tid == 0) {
+            if (GRAD) plan_store(t, b, q);
+            else { plan_weights_store(t, b, q); nband[b] = tot; }
+        }
         path = q.path; b0 = q.T; sh = q.sh;
         if (path != PATH_CAND && path != PATH_BAND) return;      /* same for the whole workgroup */
         wg_sync();                                   /* pre and cg are written again */
-    } else {
-        path = t.fast[b]; b0 = t.T[b]; sh = t.sh[b];
-        if (path != PATH_CAND && path != PATH_BAND) return;
     }
     if (p.y == NONE) mg0 = 0u;                       /* no band was staged: the staged entries hold everything above */
     const bool dense = mcnt > SEG_CAP;               /* an overflowed segment is read from the dense accumulator, where nothing is missing */
@@ -2195,10 +2195,10 @@ __global__ __launch_bounds__(WG) void k_quant(const float *__restrict__ v, const
  * among the first e equal ones in index order (k_select_finish left T, e and, per segment, the
  * number of equal keys before it).  Sixteen lanes per staging segment, four segments per
  * wavefront. */
-__global__ __launch_bounds__(WG) void k_wfix(Tables t, Cand c, uint32_t *__restrict__ pmask)
+__device__ __forceinline__ void wfix_body(const Tables &t, const Cand &c, uint32_t *__restrict__ pmask, uint32_t bid)
 {
     const uint32_t lane = threadIdx.x & 63, sub = lane >> 4, gl = lane & 15u;
-    const uint32_t ss = (blockIdx.x * (WG / 64) + (threadIdx.x >> 6)) * 4u + sub;
+    const uint32_t ss = (bid * (WG / 64) + (threadIdx.x >> 6)) * 4u + sub;
     uint32_t cnt = 0, T = 0, e_b = 0, run_e = 0, b = 0, head = 0;
     if (ss < t.n_tiles) {
         b = t.tile_b[ss];
@@ -2284,19 +2284,47 @@ __device__ __forceinline__ void mask_dense_body(const float *__restrict__ w, con
     }
 }
 
-/* The weight buckets on the dense passes (no usable band, a band that missed or overflowed), in
- * one launch of a small resident grid with barriers between the steps, like k_hard: list of tiles,
+/* The weight buckets on the dense passes (no usable band, a band that missed or overflowed), by a
+ * small resident team with barriers between the steps, like k_hard: list of tiles,
  * up to three histograms of |w| and their digits, counts per segment, prefixes,
- * bitmap.  Leaves at once when there is no such bucket. */
+ * bitmap.  Leaves at once when there is no such bucket.  k_whard: the team alone (force_dense); k_wrest: the team is the first workgroups of
+ * the launch, which also keep the buckets' records (what the next call's band is built from; what the plan was made from left clean for the
+ * gradient), the others complete the bitmap of the staged bands (three launches that waited for each other, 109 M weights in 199 buckets: 16.3 + 4.7 + 4.7 us). */
+__device__ __forceinline__ void whard_body(const float *__restrict__ w, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
+                                           uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
+                                           uint32_t *__restrict__ err, uint32_t *h, uint32_t bid, uint32_t nblk)
+{
+    if (t.nhard[2] == 0u) return;
+    dense_threshold(w, t, c, f0, f1, f2, h, t.nhard + 1, bid, nblk, false, err);
+    mask_dense_body(w, t, c, pmask, bid, nblk);
+}
 __global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
                                               uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
                                               uint32_t *__restrict__ err)
 {
     __shared__ uint32_t h[NB1];
-    if (t.nhard[2] == 0u) return;
-    const uint32_t bid = blockIdx.x, nblk = gridDim.x;
-    dense_threshold(w, t, c, f0, f1, f2, h, t.nhard + 1, bid, nblk, false, err);
-    mask_dense_body(w, t, c, pmask, bid, nblk);
+    whard_body(w, t, c, f0, f1, f2, pmask, err, h, blockIdx.x, gridDim.x);
+}
+__global__ __launch_bounds__(WG) void k_wrest(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
+                                              uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
+                                              uint32_t *__restrict__ err, uint32_t team, uint32_t *__restrict__ hist,
+                                              const uint32_t *__restrict__ nband, uint32_t *__restrict__ prevT, uint32_t *__restrict__ prevHw)
+{
+    __shared__ uint32_t h[NB1];
+    if (blockIdx.x >= team) {
+        wfix_body(t, c, pmask, blockIdx.x - team);
+        return;
+    }
+    for (uint32_t b = blockIdx.x; b < t.B; b += team) {
+        for (uint32_t i = threadIdx.x * 4u; i < NHC * HROW; i += WG * 4u) *reinterpret_cast<uint4 *>(hist + (uint64_t)b * NHC * HROW + i) = make_uint4(0u, 0u, 0u, 0u);
+        if (threadIdx.x == 0) {
+            if (t.k[b] == 0u) plan_weights_empty(t, b);
+            t.ovf[b] = 0u;
+            remember_weights(t, b, nband, prevT, prevHw);
+        }
+    }
+    wg_sync();
+    whard_body(w, t, c, f0, f1, f2, pmask, err, h, blockIdx.x, team);
 }
 
 }  // namespace
