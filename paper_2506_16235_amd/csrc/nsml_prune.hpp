@@ -19,9 +19,9 @@ namespace {
  * for everything outside it; the threshold key T and the number e of admitted elements equal to
  * T come from the staged elements alone (k_select_count / k_select_finish), and k_wrest sets the
  * bits of the band elements that turn out pruned.  A bucket whose band missed or overflowed
- * takes the dense ordered passes (k_whard), which write its bitmap.  The gradient kernels read one bit per parameter.  Pruned parameters are
- * neither counted nor emitted, and their accumulated gradient is still written to the residual:
- * pruning is not permanent. */
+ * takes the dense ordered passes (k_wrest's first workgroups; k_whard when they are asked for), which write its bitmap.  The
+ * gradient kernels read one bit per parameter.  Pruned parameters are neither counted nor emitted, and their accumulated gradient is
+ * still written to the residual: pruning is not permanent. */
 
 /* Per bucket: the band of keys [lo, hi) to stage, from the sample histogram of |w|, and the shift of
  * its bins.  The sample histogram is left clean. */
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(WG) void k_wpredict(Tables t, uint32_t *__restrict_
  * the elements above the band are only counted (c.G); and the pruning bitmap gets a first version: 1
  * for the elements below the band (pruned for certain), 0 for the rest (the few band elements that
  * end up pruned are set later by k_wrest).  A bucket without a band (no usable sample, or the dense
- * passes were asked for) is left to k_whard.  Bound by reading w, 4 bytes per element, a third of what
+ * passes were asked for) is left to k_wrest or k_whard.  Bound by reading w, 4 bytes per element, a third of what
  * the gradient's pass has in flight per tile: so two wavefronts take a tile, 16 tiles per compute unit
  * (109 M elements: 147 us with eight wavefronts per tile). */
 constexpr int WTH = 128;
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(WTH, 8) void k_whist(const float *__restrict__ w, T
 
 /* The plan of a bucket of weights, from the exact counts as plan_bucket has them for the gradient: the staged band decides the rest iff the kw-th
  * largest lies inside it, no staging segment overflowed and the list of undecided keys holds them, otherwise the
- * bucket takes the dense passes (k_whard). */
+ * bucket takes the dense passes. */
 __device__ __forceinline__ Plan plan_weights(const Tables &t, const KeyPar &p, uint32_t want, bool found, uint32_t bin, uint32_t above, uint32_t at,
                                              uint32_t ovf, uint32_t segs)
 {
@@ -176,7 +176,7 @@ __device__ __forceinline__ void plan_weights_store(const Tables &t, uint32_t b, 
     t.need[b] = q.need;
     t.sh[b] = q.sh;
     t.fast[b] = q.path;
-    if (q.path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);      /* k_whard has work */
+    if (q.path == PATH_DENSE) atomicAdd(t.nhard + 2, 1u);      /* the dense passes have work */
     if (q.path == PATH_DENSE && q.sh == SH_NONE) atomicAdd(t.nhard + 3, 1u);
 }
 __device__ __forceinline__ void plan_weights_empty(const Tables &t, uint32_t b) { t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_BAND; t.sh[b] = SH0; }

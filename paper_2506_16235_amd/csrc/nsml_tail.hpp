@@ -18,7 +18,9 @@
  *                    order from the staged entries into LDS, then scale, codes, packing, indices
  *                    and the residual update, all from LDS; up to a ratio of an eighth also what
  *                    k_hard and k_quant do otherwise, unit by unit
- *   k_hard           PATH_BAND / PATH_ZERO (survivors too many to stage: a band of keys around
+ *   k_band           16- and 32-bit values beyond an eighth: the survivors of PATH_BAND and
+ *                    PATH_ZERO from the dense accumulator, tile by tile
+ *   k_hard           codes beyond an eighth, PATH_BAND / PATH_ZERO (survivors too many to stage: a band of keys around
  *                    the threshold was staged instead, or the threshold is key 0): survivors
  *                    taken from the dense accumulator and coded in one streaming pass;
  *                    PATH_DENSE: every radix step over the dense accumulator, barriers between
