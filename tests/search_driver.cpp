@@ -1,0 +1,48 @@
+/*
+ * A tile's first survivor as the decoder's wavefronts look for it, on the CPU: against a plain search for ascending lists
+ * (even, clustered, up to what 32 bits hold), and within [0, k] for lists that are not ascending.
+ */
+#include "simt.hpp"
+
+#include "nsml.h"
+
+#include "nsml_device_common.hpp"
+#include "nsml_codec.hpp"
+
+static uint64_t rng_state = 88172645463325252ull;
+static uint32_t rnd() { rng_state ^= rng_state << 13; rng_state ^= rng_state >> 7; rng_state ^= rng_state << 17; return (uint32_t)(rng_state >> 20); }
+
+int main()
+{
+    int failures = 0, checked = 0;
+    for (uint32_t k : {1u, 2u, 63u, 64u, 65u, 66u, 127u, 128u, 129u, 1000u, 5000u, 70001u})
+        for (int kind = 0; kind < 6; ++kind) {
+            const uint64_t nb = kind == 3 ? 0xFFFFF000ull : kind == 2 ? k : 40ull * k;
+            std::vector<uint32_t> idx(k);
+            uint64_t at = 0;
+            for (uint32_t j = 0; j < k; ++j) {
+                if (kind == 0 || kind == 5) idx[j] = (uint32_t)((nb - 40) * j / k + rnd() % 40);                      /* even; 5: not ascending */
+                else if (kind == 1) { at += j % 300 ? 1 : 1 + rnd() % 10000; idx[j] = (uint32_t)std::min<uint64_t>(at, nb - k + j); }      /* runs */
+                else if (kind == 2) idx[j] = j;
+                else if (kind == 3) idx[j] = j < k / 2 ? j : (uint32_t)(nb - k + j);                                  /* the two ends */
+                else idx[j] = (uint32_t)(nb - k + j);
+            }
+            if (kind != 5) std::sort(idx.begin(), idx.end());
+            else for (uint32_t j = 0; j < k; ++j) std::swap(idx[j], idx[rnd() % k]);
+            for (uint32_t turn = 0; turn < 40; ++turn) {
+                const uint32_t head = turn % 4;
+                const uint64_t edge = turn == 0 ? 0 : turn == 1 ? nb + head : turn == 2 ? (nb + head) / TILE * TILE
+                                    : turn < 20 ? (uint64_t)idx[rnd() % k] + head + turn % 3 : rnd() % (nb + head + 1);
+                uint64_t want = 0;
+                while (want < k && (uint64_t)idx[want] + head < edge) ++want;
+                uint32_t got[64];
+                simt::run(64, dim3(0), dim3(1), [&] { got[threadIdx.x] = tilestart_wave(idx.data(), k, head, edge, (float)k / (float)nb); });
+                bool ok = true;
+                for (uint32_t l = 0; l < 64; ++l) ok = ok && got[l] == got[0] && (kind == 5 ? got[l] <= k : got[l] == want);
+                ++checked;
+                if (!ok) { ++failures; printf("k %u kind %d edge %llu: %u, by a plain search %llu\n", k, kind, (unsigned long long)edge, got[0], (unsigned long long)want); }
+            }
+        }
+    printf("checked %d, failures %d\n", checked, failures);
+    return failures ? 1 : 0;
+}

@@ -27,3 +27,7 @@ def test_sampled_counts_are_those_of_a_plain_histogram(tmp_path):
 
 def test_dense_passes_notice_a_wrong_count_before_they_write(tmp_path):
     _run(tmp_path, "dense_driver.cpp")
+
+
+def test_first_survivor_of_a_tile_by_a_wavefront(tmp_path):
+    _run(tmp_path, "search_driver.cpp")
