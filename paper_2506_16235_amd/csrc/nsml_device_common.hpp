@@ -139,7 +139,6 @@ struct Tables {
     uint32_t chunk;
     uint32_t chunkSh;        /* log2(chunk) when chunk is a power of two, else NONE */
     uint32_t dencTiles;      /* tiles per work unit of the one-pass dense encode: more on large gradients (fewer chunks straddle units) */
-    uint32_t *ties;          /* B   elements equal to the threshold key, of the buckets that k_select_finish decides */
 };
 
 /* Candidate staging: tile t owns entries [t * SEG_CAP, t * SEG_CAP + cnt[t]) */

@@ -28,8 +28,8 @@
  *             are admitted (lowest indices first), and every segment's place in the survivor order
  *   encode    PATH_CAND: one workgroup per chunk of survivors gathers them from the segments and
  *             codes them (absmax scale, codes, packing, indices, coding error into the residual)
- *             and, when no more than an eighth is sent, the buckets of the next two as well
- *   band      16- and 32-bit values beyond an eighth, PATH_BAND / PATH_ZERO: survivors taken from the dense accumulator tile by tile
+ *             (16- and 32-bit values: PATH_DENSE as well)
+ *   band      16- and 32-bit values, PATH_BAND / PATH_ZERO: survivors taken from the dense accumulator tile by tile
  *   hard      codes, PATH_BAND / PATH_ZERO: survivors taken from the dense
  *             accumulator and coded in one streaming pass; PATH_DENSE (an unlucky sample, a
  *             staging segment that overflowed, huge groups of equal keys): all radix steps over
@@ -100,7 +100,7 @@ struct nsml_ctx {
     uint4 *d_selw;         /* per workgroup of k_select_count: bucket, first and last segment */
     uint32_t *d_chunk_b;   /* per chunk of the payload: its bucket (fixed by layout, ratio, bits) */
     uint32_t *d_chunk_seg; /* per chunk: the staging segment that holds its first survivor */
-    uint32_t *d_sh, *d_why, *d_margin, *d_ties, *d_wprevT, *d_wprevHw, *d_wnband;
+    uint32_t *d_sh, *d_why, *d_margin, *d_wprevT, *d_wprevHw, *d_wnband;
     uint2 *d_part;         /* per workgroup of k_select_count: its part of the bucket's list of undecided keys */
     uint32_t *d_lkey;      /* the lists */
     uint64_t max_chunks; uint32_t max_sel;
@@ -224,7 +224,6 @@ Tables tables_of(const nsml_ctx *c)
     t.ovf = hists_of(c, c->B).ovf; t.ftile0 = c->d_ftile0; t.nhard = hists_of(c, c->B).nhard;
     t.kw = c->d_kw; t.pmask = nullptr;
     t.B = c->B; t.n_tiles = c->n_tiles; t.chunk = c->chunk; t.chunkSh = chunk_shift(c->chunk);
-    t.ties = c->d_ties;
     t.dencTiles = c->unit_tiles > 0 ? (uint32_t)c->unit_tiles : denc_tiles(c->n_tiles);
     return t;
 }
@@ -443,7 +442,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     c->d_off = c->d_P = c->d_V = c->d_S = c->d_C = nullptr;
     c->d_tile0 = c->d_samp0 = c->d_tile_b = c->d_k = c->d_T = c->d_need = nullptr;
     c->d_fast = c->d_ftile0 = c->d_zero = nullptr; c->d_desc = nullptr; c->d_par = c->d_wpar = nullptr;
-    c->d_sel0 = nullptr; c->d_selw = nullptr; c->d_chunk_b = c->d_chunk_seg = c->d_sh = c->d_why = c->d_margin = c->d_ties = c->d_wprevT = c->d_wprevHw = c->d_wnband = nullptr;
+    c->d_sel0 = nullptr; c->d_selw = nullptr; c->d_chunk_b = c->d_chunk_seg = c->d_sh = c->d_why = c->d_margin = c->d_wprevT = c->d_wprevHw = c->d_wnband = nullptr;
     c->d_part = nullptr; c->d_lkey = nullptr;
     c->d_ccnt = c->d_cG = c->d_cE = c->d_cidx = nullptr;
     c->d_cval = nullptr; c->d_v = nullptr; c->d_ts = nullptr; c->d_tile_sq = c->d_l2sq = nullptr; c->have_l2 = false;
@@ -493,7 +492,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     A(dev_alloc(c, &c->d_tile0, B1)); A(dev_alloc(c, &c->d_samp0, B1));
     A(dev_alloc(c, &c->d_k, B1)); A(dev_alloc(c, &c->d_T, B1)); A(dev_alloc(c, &c->d_need, B1));
     A(dev_alloc(c, &c->d_par, B1)); A(dev_alloc(c, &c->d_wpar, B1)); A(dev_alloc(c, &c->d_fast, B1)); A(dev_alloc(c, &c->d_ftile0, B1));
-    A(dev_alloc(c, &c->d_sel0, B1)); A(dev_alloc(c, &c->d_sh, B1)); A(dev_alloc(c, &c->d_why, B1)); A(dev_alloc(c, &c->d_margin, B1)); A(dev_alloc(c, &c->d_ties, B1));
+    A(dev_alloc(c, &c->d_sel0, B1)); A(dev_alloc(c, &c->d_sh, B1)); A(dev_alloc(c, &c->d_why, B1)); A(dev_alloc(c, &c->d_margin, B1));
     A(dev_alloc(c, &c->d_tile_b, mt)); A(dev_alloc(c, &c->d_desc, mt));
     A(dev_alloc(c, &c->d_zero, zero_words(max_buckets)));
     A(dev_alloc(c, &c->d_ccnt, mt)); A(dev_alloc(c, &c->d_cG, mt)); A(dev_alloc(c, &c->d_cE, mt));
@@ -556,7 +555,7 @@ int nsml_destroy(nsml_ctx *c)
                     c->d_zero, c->d_ccnt, c->d_cG, c->d_cE, c->d_cidx,
                     c->d_cval, c->d_v, c->d_ts, c->d_tile_sq, c->d_l2sq, c->d_pmask, c->d_kw,
                     c->d_Tw, c->d_needw, c->d_wfast,
-                    c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_part, c->d_lkey, c->d_sh, c->d_why, c->d_margin, c->d_ties, c->d_wprevT, c->d_wprevHw, c->d_wnband};
+                    c->d_sel0, c->d_selw, c->d_chunk_b, c->d_chunk_seg, c->d_part, c->d_lkey, c->d_sh, c->d_why, c->d_margin, c->d_wprevT, c->d_wprevHw, c->d_wnband};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     if (c->pinned) (void)hipHostFree(c->pinned);
     if (c->h_flags) (void)hipHostFree(c->h_flags);
@@ -710,8 +709,6 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
      * three contexts working at the same time still fit the device together */
     const bool big = c->chunk > DENC_SMALL_CHUNK;
     const uint32_t hgrid = (uint32_t)(c->hard_occ[big ? 1 : 0] * c->n_cu), team = std::min((uint32_t)c->n_cu, hgrid);
-    /* the rule of k_encode's UNITS, where both sides are measured */
-    const bool units = !c->force_dense && c->K * 8u <= n && (uint32_t)TILE % c->chunk == 0u;
     if (!c->force_dense) {
         /* buckets decided from their staged elements: undecided keys set apart, threshold and
          * survivor order per bucket, then the payload of the candidate-path buckets */
@@ -730,16 +727,14 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             /* A workgroup per chunk that may be coded here (beyond a ratio of an eighth those of the smallest buckets: k_hard
              * codes the others), a few to look for them, and not very many (2^32 threads cannot be launched).  (A small grid as soon
              * as K * 8 > n codes all of it at a ratio of 1/8 and odd sizes: 4 buckets of 27370561 elements 677 us a round, so 663.) */
-            const uint32_t first = units || bits >= 16 ? std::max(B, team) : B;
+            const uint32_t first = bits >= 16 ? std::max(B, team) : B;
             const uint32_t egrid2 = (uint32_t)std::min<uint64_t>({c->NC, std::max<uint64_t>(c->NC_cand, (narrow ? 4u : 2u) * (uint64_t)c->n_cu), 16384u});
-#define NSML_ENCODE1(BITS_, T_, U_) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, T_, U_>), first + egrid2, T_, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, \
-                                            (const double *)c->d_tile_sq, c->d_l2sq, h.f0, h.f1, h.f2, first, team)
-#define NSML_ENCODE(BITS_)                                 \
-    do {                                                    \
-        if (units && narrow) NSML_ENCODE1(BITS_, 256, true); \
-        else if (units) NSML_ENCODE1(BITS_, 512, true);      \
-        else if (narrow) NSML_ENCODE1(BITS_, 256, false);    \
-        else NSML_ENCODE1(BITS_, 512, false);                \
+#define NSML_ENCODE1(BITS_, T_) LAUNCHB(c, KID_ENCODE, st, (k_encode<BITS_, T_>), first + egrid2, T_, t, cd0, cb_, cs_, residual, idx, val, scales, c->d_flags, nc64e, h.hw, \
+                                        (const double *)c->d_tile_sq, c->d_l2sq, h.f0, h.f1, h.f2, first, team)
+#define NSML_ENCODE(BITS_)                     \
+    do {                                        \
+        if (narrow) NSML_ENCODE1(BITS_, 256);    \
+        else NSML_ENCODE1(BITS_, 512);           \
     } while (0)
             switch (bits) {
             case 32: NSML_ENCODE(32); break;
@@ -751,15 +746,18 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
 #undef NSML_ENCODE1
         }
     }
-    /* the buckets whose survivors come from the dense accumulator, where k_encode has not coded them: whole values tile by tile; codes by a
-     * fixed grid, resident at once, that streams the band and zero-threshold buckets (ordered write and coding in one pass) and then does all
+    /* the buckets whose survivors come from the dense accumulator (up to an eighth sent usually none: the workgroups read one
+     * word and leave): whole values tile by tile; codes by a fixed grid, resident at once, that streams the band and zero-threshold buckets (ordered write and coding in one pass) and then does all
      * the steps of the buckets on the dense passes with barriers between (force_dense: for all widths), and after it what that left uncoded */
-    if (!units && bits >= 16 && !c->force_dense) {
-        if (bits == 32 && nt) LAUNCHB(c, KID_HARD, st, (k_band<32, true>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+    if (bits >= 16 && !c->force_dense) {
+        const uint32_t fgrid = std::min(c->n_tiles, BAND_WG_PER_CU * (uint32_t)c->n_cu);
+        if (c->K * 8u <= n && bits == 32) LAUNCHB(c, KID_HARD, st, k_band_few<32>, fgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+        else if (c->K * 8u <= n) LAUNCHB(c, KID_HARD, st, k_band_few<16>, fgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
+        else if (bits == 32 && nt) LAUNCHB(c, KID_HARD, st, (k_band<32, true>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
         else if (bits == 32) LAUNCHB(c, KID_HARD, st, (k_band<32, false>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
         else if (nt) LAUNCHB(c, KID_HARD, st, (k_band<16, true>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
         else LAUNCHB(c, KID_HARD, st, (k_band<16, false>), sgrid, BAND_T, residual, t, cd0, idx, val, c->d_flags);
-    } else if (!units) {
+    } else {
         const uint32_t *cb_ = c->d_chunk_b, *cs_ = c->d_chunk_seg;
         const int stream_coding = c->chunk <= DENC_MAX_CHUNK ? 1 : 0;
 #define NSML_HARD(BITS_, BIG_) LAUNCHB(c, KID_HARD, st, (k_hard<BITS_, BIG_>), hgrid, HTH, residual, t, cd0, h.f0, h.f1, h.f2, idx, c->d_v, val, scales, c->d_flags, stream_coding, team)

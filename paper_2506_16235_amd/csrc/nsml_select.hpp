@@ -694,7 +694,6 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
             err[0] = 1u;
             if (coded) t.fast[b] = PATH_LEFT;
         }
-        t.ftile0[b] = ties;                              /* (not needed any more as the prefix of the tile list) */
     }
 }
 

@@ -16,11 +16,11 @@
  *                    per chunk of the payload the segment that holds its first survivor
  *   k_encode         PATH_CAND, per chunk of `chunk` consecutive survivors: gathers them in index
  *                    order from the staged entries into LDS, then scale, codes, packing, indices
- *                    and the residual update, all from LDS; up to a ratio of an eighth also what
- *                    k_hard and k_quant do otherwise, unit by unit
- *   k_band           16- and 32-bit values beyond an eighth: the survivors of PATH_BAND and
- *                    PATH_ZERO from the dense accumulator, tile by tile
- *   k_hard           codes beyond an eighth, PATH_BAND / PATH_ZERO (survivors too many to stage: a band of keys around
+ *                    and the residual update, all from LDS; with 16- and 32-bit values also
+ *                    PATH_DENSE
+ *   k_band           16- and 32-bit values: the survivors of PATH_BAND and PATH_ZERO from the dense
+ *                    accumulator, tile by tile
+ *   k_hard           codes, PATH_BAND / PATH_ZERO (survivors too many to stage: a band of keys around
  *                    the threshold was staged instead, or the threshold is key 0): survivors
  *                    taken from the dense accumulator and coded in one streaming pass;
  *                    PATH_DENSE: every radix step over the dense accumulator, barriers between
@@ -533,7 +533,6 @@ __device__ __forceinline__ void finish_state(const Tables &t, uint32_t b, uint32
     if (threadIdx.x != 0) return;
     t.T[b] = T;
     t.need[b] = e_b;
-    t.ties[b] = ties;
     /* above + admitted ties must be exactly k */
     if (above + e_b != kb || e_b > ties) err[0] = 1u;
 }
@@ -1018,385 +1017,13 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
     grid_barrier(bar, arrivals += nblk, err);
 }
 
-/* ------------------------------------------------------------------ survivors from the dense accumulator, coded */
-
-constexpr uint32_t UNIT_ROWS = 4;                  /* 16-byte accesses a thread has in flight */
-/* Chunks of a unit: no fewer survivors than a tile has elements */
-__host__ __device__ constexpr uint32_t unit_chunks(uint32_t chunk) { return ((uint32_t)TILE + chunk - 1u) / chunk; }
-/* Survivors number cb * chunk and on of bucket b, as many as a unit has, taken from the dense accumulator and coded in one go
- * by a workgroup of NT threads: for the buckets whose threshold, tie allowance and prefixes per tile are known but whose survivors
- * are not all staged.  Tiles that hold none of them are not read.  sA: the tile of the first one; ties: the bucket's elements equal
- * to T.  pool: 2 * TILE words.
- *
- * Units share a tile where one ends and the next begins, and either may already have written its coding errors
- * there.  So in the tile a unit begins in, it counts from the tile's end, behind which nothing of an earlier unit lies,
- * and in all others from the front: what other units have written is then before or behind its own survivors, whatever
- * it looks like (a survivor's error is never larger than the survivor, but may still be a survivor's size).  That needs a unit
- * that does not begin and end inside one tile between two others, so it has at least as many survivors as a tile has elements.
- *
- * What bounds it is the memory behind the caches, which reads a 64-byte line before it writes a part of it: half the words of
- * 268 M elements written 400 us, read and then written 402, read and written whole 340 (one in ten: 390 and 339).  So when all of a
- * unit's tiles fit the registers, the lanes that hold the elements write whole lines: survivors' errors and the others as they were.
- * Otherwise (survivors far apart) the errors are stored one by one. */
-template <int BITS, uint32_t NT>
-__device__ __forceinline__ void code_dense_unit(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ idx_out,
-                                                void *__restrict__ val, float *__restrict__ scales, uint32_t *__restrict__ err,
-                                                uint32_t b, uint32_t cb, uint32_t sA, uint32_t ties, uint32_t *pool)
-{
-    constexpr float QMAX = BITS == 8 ? 127.0f : 7.0f;     /* (unused for 16 / 32 bits) */
-    constexpr bool CODED = BITS <= 8;
-    constexpr uint32_t W = NT / 64, QT = TILE / (4u * NT), TB = UNIT_ROWS / QT;      /* rows of a tile, tiles at a time */
-    static_assert(W * QT == 8u, "eight counts per tile");
-    __shared__ uint32_t wt[2][64], cmax[TILE / 8], ends[2], filled;
-    float *sv = reinterpret_cast<float *>(pool);
-    uint32_t *si = pool + TILE;
-    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint32_t chunk = t.chunk, g = unit_chunks(chunk), kb = t.k[b], e_b = t.need[b], T = t.T[b];
-    const uint32_t j0 = cb * chunk, n = min(g * chunk, kb - j0), j1 = j0 + n;
-    const uint32_t tile0b = t.tile0[b], seg_hi = t.tile0[b + 1];
-    const uint64_t lo = t.off[b], hi = t.off[b + 1], lo_al = lo & ~3ull, Pb = t.P[b];
-    uint8_t *vb = reinterpret_cast<uint8_t *>(val) + t.V[b];
-    /* 64 tiles at a time, one per lane: elements above and equal to T before each and before the one behind it, and which hold
-     * survivors of the unit (the same in every wavefront) */
-    uint32_t s_base = sA, Gl = 0, El = 0, Gn = 0, En = 0;
-    uint64_t todo = 0;
-    bool more = false;
-    auto look = [&]() {
-        const uint32_t s = s_base + lane;
-        const bool in = s < seg_hi, last = s + 1u >= seg_hi;
-        Gl = in ? c.G[s] : 0u; El = in ? c.E[s] : 0u;
-        Gn = last ? kb - e_b : c.G[s + 1u]; En = last ? ties : c.E[s + 1u];
-        const uint32_t r0 = Gl + min(e_b, El), r1 = Gn + min(e_b, En);
-        todo = __ballot(in && r1 > r0 && r1 > j0 && r0 < j1);
-        more = __ballot(in && r0 < j1) == ~0ull && s_base + 64u < seg_hi;
-    };
-    look();
-    const bool keep = !more && (uint32_t)__popcll(todo) <= TB;      /* same for the whole workgroup */
-    wg_sync();                                       /* what LDS held has been consumed */
-    if (CODED) for (uint32_t i = tid; i < g; i += NT) cmax[i] = 0u;
-    if (tid == 0) filled = 0u;
-    auto chunk_of = [&](uint32_t slot) { return t.chunkSh < 32u ? slot >> t.chunkSh : slot / chunk; };
-
-    float x[UNIT_ROWS][4];
-    int32_t slot0[UNIT_ROWS];                        /* of the first survivor among a row's four */
-    uint32_t sb = 0, tl[TB], got = 0;                /* four bits per row: the unit's survivors; tiles, counted from s_base */
-    float m = 0.0f;
-    auto tile_of = [&](uint32_t v) { return s_base + tl[v]; };
-    auto elem_of = [&](uint32_t u) { return (u % QT * NT + tid) * 4u; };       /* this thread's first element of row u, counted from its tile */
-    for (uint32_t half = 0;; half ^= 1u) {
-        uint32_t valid = 0;
-        bool full = t.pmask == nullptr;              /* every element counts */
-#pragma unroll
-        for (uint32_t v = 0; v < TB; ++v) {
-            tl[v] = NONE;
-            if (todo) { tl[v] = (uint32_t)__builtin_ctzll(todo); todo &= todo - 1ull; }
-            const uint64_t base = lo_al + (uint64_t)(tile_of(v) - tile0b) * TILE;
-            const bool whole = tl[v] != NONE && base >= lo && base + TILE <= hi;
-            full = full && (whole || tl[v] == NONE);
-#pragma unroll
-            for (uint32_t q = 0; q < QT; ++q) {
-                const uint32_t u = v * QT + q;
-                const uint64_t gi = base + elem_of(u);
-                uint32_t have = 0;
-                if (whole) {
-                    const f4 y = *reinterpret_cast<const f4 *>(r + gi);
-                    x[u][0] = y.x; x[u][1] = y.y; x[u][2] = y.z; x[u][3] = y.w;
-                    have = 0xFu;
-                } else if (tl[v] != NONE) {
-                    have = load_quad(r, gi, lo, hi, x[u]);
-                } else {
-                    x[u][0] = x[u][1] = x[u][2] = x[u][3] = 0.0f;
-                }
-                if (t.pmask && tl[v] != NONE) have &= ~pruned_bits(t.pmask, tile_of(v), elem_of(u) / 4u);
-                valid |= have << (4u * u);
-            }
-        }
-        /* Counts and ranks: a comparison's result is the mask over the wavefront that counting needs.  Keys are compared as signed
-         * numbers, and what does not count as the lowest of them. */
-        auto keys = [&](uint32_t u, int32_t (&key)[4]) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) key[j] = (int32_t)keyof(x[u][j]);
-            if (!full) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) key[j] = (valid >> (4u * u + j)) & 1u ? key[j] : (int32_t)0x80000000u;
-            }
-        };
-        uint32_t row_g[UNIT_ROWS], row_e[UNIT_ROWS], bef_g[UNIT_ROWS];      /* above / equal to T in a row of the wavefront; above it in the lower lanes */
-#pragma unroll
-        for (uint32_t u = 0; u < UNIT_ROWS; ++u) {
-            row_g[u] = row_e[u] = bef_g[u] = 0u;
-            if (tl[u / QT] == NONE) continue;
-            int32_t key[4];
-            keys(u, key);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint64_t bg = __ballot(key[j] > (int32_t)T);
-                row_g[u] += (uint32_t)__popcll(bg);
-                row_e[u] += (uint32_t)__popcll(__ballot(key[j] == (int32_t)T));
-                bef_g[u] = __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, bef_g[u]));
-            }
-        }
-        if (lane == 0) {
-#pragma unroll
-            for (uint32_t u = 0; u < UNIT_ROWS; ++u) wt[half][u / QT * 8u + u % QT * W + wave] = row_g[u] | (row_e[u] << 16);
-        }
-        wg_sync();
-        /* eight counts per tile, in the order of its elements: a scan over every eight lanes */
-        uint32_t incl = wt[half][lane & (TB * 8u - 1u)];
-        {
-            const uint32_t at = lane & 7u;
-            uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x111, 0xF, 0xF, true);
-            incl += at >= 1u ? y : 0u;
-            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x112, 0xF, 0xF, true);
-            incl += at >= 2u ? y : 0u;
-            y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)incl, 0x114, 0xF, 0xF, true);
-            incl += at >= 4u ? y : 0u;
-        }
-        sb = 0;
-#pragma unroll
-        for (uint32_t u = 0; u < UNIT_ROWS; ++u) slot0[u] = 0;
-#pragma unroll
-        for (uint32_t v = 0; v < TB; ++v) {
-            if (tl[v] == NONE) continue;
-            /* elements above and equal to T before the tile: as the prefixes have it, or, in the tile the unit begins in, its end's less what it holds */
-            const uint32_t Gs = (uint32_t)__builtin_amdgcn_readlane((int)Gl, (int)tl[v]), Es = (uint32_t)__builtin_amdgcn_readlane((int)El, (int)tl[v]);
-            int64_t g64 = Gs, e64 = Es;
-            if (Gs + min(e_b, Es) < j0) {
-                const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)(v * 8u + 7u));
-                g64 = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)Gn, (int)tl[v]) - (int64_t)(tot & 0xFFFFu);
-                e64 = (int64_t)(uint32_t)__builtin_amdgcn_readlane((int)En, (int)tl[v]) - (int64_t)(tot >> 16);
-            }
-            /* ties of the tile that are still admitted, and the slot of the tile's first survivor (clamped far beyond what a tile can change) */
-            const int64_t lim64 = (int64_t)e_b - e64, base64 = g64 + (lim64 < 0 ? (int64_t)e_b : e64) - (int64_t)j0, far = 1 << 30;
-            const uint32_t lim = lim64 < 0 ? 0u : lim64 > 4096 ? 4096u : (uint32_t)lim64;
-            const int32_t base = (int32_t)(base64 < -far ? -far : base64 > far ? far : base64);
-#pragma unroll
-            for (uint32_t q = 0; q < QT; ++q) {
-                const uint32_t u = v * QT + q;
-                if (row_g[u] + row_e[u] == 0u) continue;         /* same for the whole wavefront */
-                const uint32_t excl = (uint32_t)__builtin_amdgcn_readlane((int)incl, (int)(v * 8u + q * W + wave)) - (row_g[u] | (row_e[u] << 16));
-                const uint32_t fg = excl & 0xFFFFu, fe = excl >> 16;
-                int32_t key[4];
-                keys(u, key);
-                uint32_t bits = 0;
-                int32_t first = base + (int32_t)(fg + min(fe, lim));           /* of the row */
-                const int32_t behind = first + (int32_t)(row_g[u] + row_e[u]);
-                if (row_e[u] == 0u || fe >= lim) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) bits |= (key[j] > (int32_t)T ? 1u : 0u) << j;
-                    slot0[u] = first + (int32_t)bef_g[u];
-                } else {
-                    uint32_t pe = fe;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const uint64_t be = __ballot(key[j] == (int32_t)T);
-                        pe = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, pe));
-                    }
-                    slot0[u] = base + (int32_t)(fg + bef_g[u] + min(pe, lim));
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const bool tie = key[j] == (int32_t)T;
-                        bits |= (key[j] > (int32_t)T || (tie && pe < lim) ? 1u : 0u) << j;
-                        pe += tie ? 1u : 0u;
-                    }
-                }
-                if (first < 0 || behind > (int32_t)n) {          /* some of the row's are other units' */
-                    int32_t s = slot0[u];
-                    uint32_t own = 0;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        if (!((bits >> j) & 1u)) continue;
-                        if ((uint32_t)s < n) own |= 1u << j;
-                        if (s < 0) ++slot0[u];
-                        ++s;
-                    }
-                    bits = own;
-                }
-                sb |= bits << (4u * u);
-                if (first <= 0 || behind >= (int32_t)n) {
-                    /* where the unit begins and ends */
-                    int32_t s = slot0[u];
-                    const uint32_t li = (tile_of(v) - tile0b) * (uint32_t)TILE + elem_of(u) - (uint32_t)(lo - lo_al);
-#pragma unroll
-                    for (uint32_t j = 0; j < 4; ++j) {
-                        if (!((bits >> j) & 1u)) continue;
-                        if (s == 0) ends[0] = li + j;
-                        if (s == (int32_t)n - 1) ends[1] = li + j;
-                        ++s;
-                    }
-                }
-            }
-        }
-        got += (uint32_t)__popc(sb);
-        if (keep) break;                             /* same for the whole workgroup */
-#pragma unroll
-        for (uint32_t u = 0; u < UNIT_ROWS; ++u) {
-            if (!__any((sb >> (4u * u)) & 0xFu)) continue;
-            const uint32_t li = (tile_of(u / QT) - tile0b) * (uint32_t)TILE + elem_of(u) - (uint32_t)(lo - lo_al);
-            uint32_t s = (uint32_t)slot0[u];
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j)
-                if ((sb >> (4u * u + j)) & 1u) { sv[s] = x[u][j]; si[s] = li + j; ++s; }
-        }
-        if (!todo) {
-            if (!more) break;
-            do { s_base += 64u; look(); } while (!todo && more);
-            if (!todo) break;
-        }
-    }
-    /* the largest magnitude of each chunk */
-    auto chunk_max = [&](uint32_t s, float y) {      /* slot s (NONE: none) holds y; the lanes' slots ascend */
-        const uint64_t who = __ballot(s != NONE);
-        if (!who) return;
-        const uint32_t c0 = chunk_of((uint32_t)__builtin_amdgcn_readlane((int)s, (int)__builtin_ctzll(who))), c1 = chunk_of((uint32_t)__builtin_amdgcn_readlane((int)s, (int)(63 - __builtin_clzll(who))));
-        y = s != NONE && !(y != y) ? fabsf(y) : 0.0f;          /* NaN is passed over */
-        if (c0 == c1) {
-            y = wave_max(y);
-            if (lane == 0) atomicMax(&cmax[c0], __float_as_uint(y));
-        } else if (s != NONE) {
-            atomicMax(&cmax[chunk_of(s)], __float_as_uint(y));
-        }
-    };
-    if (CODED && keep) {
-        if (g == 1u) {
-#pragma unroll
-            for (uint32_t u = 0; u < UNIT_ROWS; ++u)
-#pragma unroll
-                for (uint32_t j = 0; j < 4; ++j)
-                    if ((sb >> (4u * u + j)) & 1u) m = fmaxf(m, fabsf(x[u][j]));
-            m = wave_max(m);
-            if (lane == 0) atomicMax(&cmax[0], __float_as_uint(m));
-        } else {
-#pragma unroll
-            for (uint32_t u = 0; u < UNIT_ROWS; ++u) {
-                uint32_t s = (uint32_t)slot0[u];
-#pragma unroll
-                for (uint32_t j = 0; j < 4; ++j) {
-                    const bool is = (sb >> (4u * u + j)) & 1u;
-                    chunk_max(is ? s : NONE, x[u][j]);
-                    s += is ? 1u : 0u;
-                }
-            }
-        }
-    }
-    got = wave_incl_scan(got);
-    if (lane == 63 && got) atomicAdd(&filled, got);
-    wg_sync();
-    if (filled != n) {                               /* the prefixes and the elements disagree: nothing is written (same for the whole workgroup) */
-        if (tid == 0) err[0] = 1u;
-        return;
-    }
-    if (CODED && !keep) {
-        for (uint32_t i = tid; i < (n + 63u) / 64u * 64u; i += NT) chunk_max(i < n ? i : NONE, i < n ? sv[i] : 0.0f);
-        wg_sync();
-    }
-    float scale = 0.0f;
-    if (CODED) {
-        const uint32_t nch = (n + chunk - 1u) / chunk;
-        if (g == 1u) {
-            const float mx = __uint_as_float(cmax[0]);
-            scale = mx == 0.0f ? 0.0f : __fdiv_rn(mx, QMAX);
-            if (tid == 0) scales[t.S[b] + cb] = scale;
-        } else {
-            for (uint32_t i = tid; i < nch; i += NT) {
-                const float mx = __uint_as_float(cmax[i]), sc = mx == 0.0f ? 0.0f : __fdiv_rn(mx, QMAX);
-                scales[t.S[b] + cb + i] = sc;
-                cmax[i] = __float_as_uint(sc);
-            }
-            wg_sync();
-        }
-    }
-    uint8_t *code8 = reinterpret_cast<uint8_t *>(pool);
-    uint16_t *code16 = reinterpret_cast<uint16_t *>(pool);
-    /* code of x in slot s -> what it leaves behind */
-    auto code_one = [&](float xv, uint32_t s, int &q, uint32_t &h) {
-        q = 0; h = 0;
-        if (BITS == 32) return __fsub_rn(xv, xv);    /* nothing is left behind (NaN where no value was) */
-        if (BITS == 16) {
-            const __half hv = __float2half_rn(xv);
-            h = __half_as_ushort(hv);
-            return __fsub_rn(xv, __half2float(hv));
-        }
-        const float sc = g == 1u ? scale : __uint_as_float(cmax[chunk_of(s)]);
-        const float y = __fmul_rn(xv, __builtin_amdgcn_rcpf(sc));      /* (the quotient's code away from the middle of two: see quantize_four) */
-        float w = rintf(y);
-        if (!(fabsf(__fsub_rn(y, w)) < 0.4999f)) w = sc != 0.0f ? rintf(__fdiv_rn(xv, sc)) : 0.0f;
-        q = (int)fminf(fmaxf(w, -QMAX), QMAX);
-        return __fsub_rn(xv, __fmul_rn((float)q, sc));
-    };
-    if (keep) {
-        const uint32_t e0 = ends[0], e1 = ends[1];
-#pragma unroll
-        for (uint32_t u = 0; u < UNIT_ROWS; ++u) {
-            const uint32_t bits = (sb >> (4u * u)) & 0xFu;
-            if (tl[u / QT] == NONE || !__any(bits)) continue;
-            const uint64_t base = lo_al + (uint64_t)(tile_of(u / QT) - tile0b) * TILE;
-            const bool whole = base >= lo && base + TILE <= hi;
-            const uint32_t li = (tile_of(u / QT) - tile0b) * (uint32_t)TILE + elem_of(u) - (uint32_t)(lo - lo_al);
-            uint32_t s = (uint32_t)slot0[u];
-            float y[4] = {x[u][0], x[u][1], x[u][2], x[u][3]};
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) {
-                if (!((bits >> j) & 1u)) continue;
-                int q;
-                uint32_t h;
-                y[j] = code_one(x[u][j], s, q, h);
-                si[s] = li + j;
-                if (BITS == 32) sv[s] = x[u][j];
-                else if (BITS == 16) code16[s] = (uint16_t)h;
-                else code8[s] = (uint8_t)q;
-                ++s;
-            }
-            uint32_t diff = 0;
-#pragma unroll
-            for (uint32_t j = 0; j < 4; ++j) diff |= __float_as_uint(y[j]) ^ __float_as_uint(x[u][j]);
-            if (!__any(diff)) continue;              /* zeros that survive leave what they were */
-            if (whole && li >= e0 && li + 3u <= e1) {
-                *reinterpret_cast<f4 *>(r + base + elem_of(u)) = f4{y[0], y[1], y[2], y[3]};
-            } else {
-#pragma unroll
-                for (uint32_t j = 0; j < 4; ++j)
-                    if ((bits >> j) & 1u) r[base + elem_of(u) + j] = y[j];
-            }
-        }
-        wg_sync();
-        if (BITS == 8) {
-            const uint32_t words = (reinterpret_cast<uintptr_t>(vb + j0) & 3u) == 0u ? n / 4u : 0u;      /* (a bucket's codes start at any byte) */
-            for (uint32_t i = tid; i < words; i += NT) *reinterpret_cast<uint32_t *>(vb + j0 + 4u * i) = pool[i];
-            for (uint32_t i = 4u * words + tid; i < n; i += NT) vb[j0 + i] = code8[i];
-        }
-        for (uint32_t i = tid; i < n; i += NT) {
-            idx_out[Pb + j0 + i] = si[i];
-            if (BITS == 32) reinterpret_cast<float *>(vb)[j0 + i] = sv[i];
-            if (BITS == 16) reinterpret_cast<uint16_t *>(vb)[j0 + i] = code16[i];
-            if (BITS == 4 && !(i & 1u)) vb[(j0 + i) >> 1] = (uint8_t)((code8[i] & 0xFu) | (i + 1u < n ? (uint32_t)code8[i + 1u] << 4 : 0u));
-        }
-        return;
-    }
-    for (uint32_t i = tid; i < (n + 63u) / 64u * 64u; i += NT) {
-        const bool is = i < n;
-        const float xv = is ? sv[i] : 0.0f;
-        const uint32_t li = is ? si[i] : 0u;
-        int q;
-        uint32_t h;
-        const float left = code_one(xv, is ? i : 0u, q, h);
-        /* a pair's codes in one byte at 4 bits: the odd lane's comes over (0 beyond the last) */
-        const int odd = BITS == 4 ? __builtin_amdgcn_mov_dpp(is ? q : 0, 0xF5, 0xF, 0xF, false) : 0;      /* lanes 1 1 3 3 */
-        if (!is) continue;
-        idx_out[Pb + j0 + i] = li;
-        if (BITS == 32) reinterpret_cast<float *>(vb)[j0 + i] = xv;
-        else if (BITS == 16) reinterpret_cast<uint16_t *>(vb)[j0 + i] = (uint16_t)h;
-        else if (BITS == 8) vb[j0 + i] = (uint8_t)q;
-        else if (!(lane & 1u)) vb[(j0 + i) >> 1] = (uint8_t)((q & 0xF) | ((odd & 0xF) << 4));
-        if (__float_as_uint(left) != __float_as_uint(xv)) r[lo + li] = left;      /* (zeros that survive leave what they were) */
-    }
-}
-
 /* ------------------------------------------------------------------ whole values from the dense accumulator */
 
 /* 16- and 32-bit values wait for no scale, so the survivors of a tile of a bucket whose threshold, tie allowance and
  * prefixes are known need nothing from any other tile: elements read once, ranks from ballots, values and indices through LDS to
- * where they go, and the elements written back as whole lines with what the survivors leave behind (see code_dense_unit).  A tile
+ * where they go, and the elements written back as whole lines with what the survivors leave behind: the memory behind the caches reads a
+ * 64-byte line before it writes a part of it (half the words of 268 M elements written 400 us, read and then written 402, read and
+ * written whole 340; one in ten: 390 and 339).  A tile
  * per workgroup of NT threads.  pool: 2 * TILE words. */
 constexpr uint32_t BAND_ROW = 16;       /* survivors of 256 elements from which their lines are written whole */
 template <int BITS, uint32_t NT, bool PAST>       /* PAST: whole lines go past the caches, see st_out */
@@ -1534,46 +1161,32 @@ __device__ __forceinline__ void band_tile(float *__restrict__ r, const Tables &t
         else reinterpret_cast<__half *>(vb)[R0 + i] = __float2half_rn(v);
     }
 }
-/* The buckets on the dense passes, by the nblk workgroups of a resident team (WG threads of each): threshold, counts and
- * prefixes, then their survivors, coded: whole values tile by tile, others unit by unit. */
+/* Tiles of buckets on the paths `which` (bit p: PATH p), by nblk workgroups of NT threads. */
+template <int BITS, uint32_t NT>
+__device__ __forceinline__ void band_tiles(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ idx, void *__restrict__ val,
+                                           uint32_t *__restrict__ err, uint32_t which, uint32_t *pool, uint32_t bid, uint32_t nblk)
+{
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint64_t t0 = bid; t0 < t.n_tiles; t0 += 64ull * nblk) {
+        const uint64_t tl = t0 + (uint64_t)lane * nblk;
+        const uint32_t path = t.fast[t.tile_b[min(tl, (uint64_t)t.n_tiles - 1u)]];
+        for (uint64_t todo = __ballot(tl < t.n_tiles && ((which >> path) & 1u)); todo; todo &= todo - 1ull) {
+            const uint32_t tile = (uint32_t)(t0 + (uint64_t)__builtin_ctzll(todo) * nblk);
+            wg_sync();                               /* LDS is written again */
+            band_tile<BITS, NT, false>(r, t, c, idx, val, err, tile, t.desc[tile], pool);
+        }
+    }
+}
+/* The buckets on the dense passes where values are whole, by the nblk workgroups of a resident team (WG threads of each): threshold,
+ * counts and prefixes, then their survivors tile by tile. */
 template <int BITS>
-__device__ __forceinline__ void code_dense_buckets(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
+__device__ __forceinline__ void band_dense_buckets(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ f0,
                                                    uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ idx,
-                                                   void *__restrict__ val, float *__restrict__ scales,
-                                                   uint32_t *__restrict__ err, const uint32_t *__restrict__ chunk_b, uint64_t n_chunks,
-                                                   uint32_t *pool, uint32_t bid, uint32_t nblk)
+                                                   void *__restrict__ val, uint32_t *__restrict__ err, uint32_t *pool, uint32_t bid, uint32_t nblk)
 {
     static_assert(2 * TILE >= NB1, "the pool must hold the level-1 histogram");
-    __shared__ uint32_t sh;
     dense_threshold(r, t, c, f0, f1, f2, pool, t.nhard + 1, bid, nblk, true, err);
-    const uint32_t lane = threadIdx.x & 63;
-    if constexpr (BITS >= 16) {
-        for (uint64_t t0 = bid; t0 < t.n_tiles; t0 += 64ull * nblk) {
-            const uint64_t tl = t0 + (uint64_t)lane * nblk;
-            for (uint64_t todo = __ballot(tl < t.n_tiles && t.fast[t.tile_b[min(tl, (uint64_t)t.n_tiles - 1u)]] == PATH_DENSE); todo; todo &= todo - 1ull) {
-                const uint32_t tile = (uint32_t)(t0 + (uint64_t)__builtin_ctzll(todo) * nblk);
-                wg_sync();                           /* LDS is written again */
-                band_tile<BITS, WG, false>(r, t, c, idx, val, err, tile, t.desc[tile], pool);
-            }
-        }
-        return;
-    }
-    const uint32_t g = unit_chunks(t.chunk);
-    for (uint64_t c0 = bid; c0 < n_chunks; c0 += 64ull * nblk) {
-        const uint64_t cl = c0 + (uint64_t)lane * nblk;
-        bool mine = false;
-        if (cl < n_chunks) {
-            const uint32_t b = chunk_b[cl];
-            mine = t.fast[b] == PATH_DENSE && (cl - t.C[b]) % g == 0u;
-        }
-        for (uint64_t todo = __ballot(mine); todo; todo &= todo - 1ull) {
-            const uint64_t cid = c0 + (uint64_t)__builtin_ctzll(todo) * nblk;
-            const uint32_t b = chunk_b[cid], cb = (uint32_t)(cid - t.C[b]), e_b = t.need[b];
-            auto rank0 = [&](uint32_t s) { return (uint64_t)c.G[s] + (uint64_t)min(e_b, c.E[s]); };
-            const uint32_t sA = wg_search_le<WG>(t.tile0[b], t.tile0[b + 1], (uint64_t)cb * t.chunk, rank0, &sh);
-            code_dense_unit<BITS, WG>(r, t, c, idx, val, scales, err, b, cb, sA, t.ftile0[b], pool);
-        }
-    }
+    band_tiles<BITS, WG>(r, t, c, idx, val, err, 1u << PATH_DENSE, pool, bid, nblk);
 }
 
 /* ------------------------------------------------------------------ k_encode */
@@ -1582,14 +1195,12 @@ __device__ __forceinline__ void code_dense_buckets(float *__restrict__ r, const 
  * absmax, scale, codes, packing, indices, and the coding error left in the residual.  Every
  * floating-point step is a single correctly rounded binary32 operation.  A chunk longer than
  * ENC_BLK is gathered block by block, once for its absmax and once more for the codes.
- * UNITS (no more than an eighth of the elements sent, chunks that nest in 2048): the other buckets are coded by the same launch, a
- * workgroup per unit of their chunks, and its first `team` workgroups, dispatched before the others and so resident when they
- * meet, do the dense passes.  Nearly always there is no such bucket, and then k_hard and k_quant are two launches that
- * do nothing, 4.5 us each (ResNet-50 at 0.05, 8 bits: 28.3 + 4.6 + 4.6 us, so 29.7; one bucket of 1 Mi elements: a call 46.4 us, so 42); where
- * there is one, its work runs beside the gathers (BERT-shaped gradient at 0.1, 4 bits: 154 + 56 + 11.5 us, so 171 - 193).  With more sent
- * the dense accumulator is most of the work, and k_hard's stream of it, which fetches ahead, is faster than units of 2048 survivors (419 M elements at a
- * half, 8 bits: k_hard and k_quant 1034 us, units in a launch of their own 1199; 25.6 M at 0.7, 32 bits: 66 and 91). */
-template <int BITS, uint32_t ENC_T, bool UNITS>
+ * Where values are whole (16 and 32 bits) its first `team` workgroups, dispatched before the others and so resident when they
+ * meet, do the dense passes, so that the rest of such a call is k_band alone.  (Everything that is not staged coded here, a workgroup per 2048
+ * survivors of the dense accumulator, saves two launches that nearly always have nothing to do, 3 us of 46 with one bucket of 1 Mi elements; but
+ * survivors far apart are then a long chain in one workgroup: such a bucket at 0.01 with values clipped at one sigma 160 - 500 us instead
+ * of 70.) */
+template <int BITS, uint32_t ENC_T>
 __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uint32_t *__restrict__ chunk_b,
                                                const uint32_t *__restrict__ chunk_seg, float *__restrict__ r,
                                                uint32_t *__restrict__ idx_out, void *__restrict__ val,
@@ -1604,7 +1215,7 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
     uint32_t *si = pool + ENC_BLK;
     __shared__ float red[ENC_T / 64];
     __shared__ uint32_t sh, filled, meta[3 * ENC_T];       /* of segments: entries, and what lies above and at T before */
-    static_assert(ENC_BLK == (uint32_t)TILE, "a unit's survivors");
+    static_assert(ENC_BLK == (uint32_t)TILE, "the pool holds a tile's survivors");
     if (blockIdx.x < first) {
         if (blockIdx.x < t.B) {
             /* The first workgroups keep the buckets' records: the norm, and what the plan was made from left clean for the next
@@ -1617,10 +1228,10 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
                 t.ovf[b] = 0u;
             }
         }
-        if constexpr (UNITS || BITS >= 16) {
+        if constexpr (BITS >= 16) {
             if (blockIdx.x >= team || t.nhard[2] == 0u || threadIdx.x >= WG) return;
             wg_sync();
-            code_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx_out, val, scales, err, chunk_b, n_chunks, pool, blockIdx.x, team);
+            band_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx_out, val, err, pool, blockIdx.x, team);
         }
         return;
     }
@@ -1636,25 +1247,14 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
     uint64_t todo = 1ull;
     if (!single) {
         const uint64_t cl = c0 + (uint64_t)lane * grid;
-        const uint32_t bl = chunk_b[min(cl, n_chunks - 1u)], path = t.fast[bl];
-        todo = __ballot(cl < n_chunks && (path == PATH_CAND || (UNITS && (path == PATH_BAND || path == PATH_ZERO) && (uint32_t)(cl - t.C[bl]) % unit_chunks(t.chunk) == 0u)));
+        todo = __ballot(cl < n_chunks && t.fast[chunk_b[min(cl, n_chunks - 1u)]] == PATH_CAND);
     }
     for (; todo; todo &= todo - 1ull) {
     const uint64_t cid = c0 + (uint64_t)__builtin_ctzll(todo) * grid;
     const uint32_t b = chunk_b[cid];
     const uint32_t sFirst = chunk_seg[cid];          /* meaningful for PATH_CAND buckets only, like the next one */
     const uint32_t sNext = cid + 1 < n_chunks ? chunk_seg[cid + 1] : 0u;
-    if (UNITS || single) {
-        const uint32_t path = t.fast[b];
-        if (path != PATH_CAND) {
-            if constexpr (UNITS) {
-                const uint32_t cu = (uint32_t)(cid - t.C[b]);
-                if ((path == PATH_BAND || path == PATH_ZERO) && cu % unit_chunks(t.chunk) == 0u) code_dense_unit<BITS, ENC_T>(r, t, c, idx_out, val, scales, err, b, cu, sFirst, t.ties[b], pool);
-            }
-            if (single) return;
-            continue;
-        }
-    }
+    if (single && t.fast[b] != PATH_CAND) return;
     const uint64_t cb = cid - t.C[b];
     const uint64_t j0c = cb * t.chunk;                         /* first survivor of the chunk, bucket-local */
     const uint32_t cnt_c = (uint32_t)min((uint64_t)t.chunk, (uint64_t)t.k[b] - j0c);
@@ -2101,14 +1701,14 @@ __global__ __launch_bounds__(HTH, hard_wg_per_cu(BIG) * (HTH / 256)) void k_hard
     wg_sync();
     nblk = team;
     if constexpr (BITS >= 16) {
-        code_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx, val, scales, err, nullptr, 0u, pool, bid, nblk);
+        band_dense_buckets<BITS>(r, t, c, f0, f1, f2, idx, val, err, pool, bid, nblk);
     } else {
         dense_threshold(r, t, c, f0, f1, f2, pool, t.nhard + 1, bid, nblk, true, err);
         write_dense_body(r, t, c, idx, vdst, 1u << PATH_DENSE, bid, nblk);
     }
 }
 
-/* The buckets of a call with 16- or 32-bit values whose survivors come from the dense accumulator (more than an eighth sent), in the order of
+/* The buckets of a call with 16- or 32-bit values whose survivors come from the dense accumulator, in the order of
  * the streaming passes.  Bound by memory: 25.6 M elements, 0.13 to 0.71 of them as 32-bit values, 50 us on average (5.7 TB/s); by
  * the stream that codes narrower values, with its steps of 4096 elements and scattered errors, 66. */
 constexpr uint32_t BAND_T = STH;
@@ -2122,6 +1722,16 @@ __global__ __launch_bounds__(BAND_T, 8) void k_band(float *__restrict__ r, Table
     const uint32_t path = t.fast[d.z];
     if (path != PATH_BAND && path != PATH_ZERO) return;
     band_tile<BITS, BAND_T, PAST>(r, t, c, idx, val, err, tile, d, pool);
+}
+/* The same where no more than an eighth is sent, which nearly always leaves nothing to do: a grid of a few workgroups per compute unit, which look
+ * for their tiles 64 at a time (a workgroup for each of 820 thousand tiles that leaves at once is a launch of 100 us and more). */
+constexpr uint32_t BAND_WG_PER_CU = 4;
+template <int BITS>
+__global__ __launch_bounds__(BAND_T, 8) void k_band_few(float *__restrict__ r, Tables t, Cand c, uint32_t *__restrict__ idx, void *__restrict__ val, uint32_t *__restrict__ err)
+{
+    __shared__ __align__(16) uint32_t pool[2 * TILE];
+    if (t.nhard[0] == 0u) return;                    /* every bucket was coded from its staged elements */
+    band_tiles<BITS, BAND_T>(r, t, c, idx, val, err, (1u << PATH_BAND) | (1u << PATH_ZERO), pool, blockIdx.x, gridDim.x);
 }
 
 /* Value coding of the survivors the ordered writes above left uncoded in idx / vdst: every chunk

@@ -1,6 +1,5 @@
-"""Calls of up to an eighth of the elements whose survivors are not all staged: units of chunks taken from the dense
-accumulator beside the chunks that come from staged entries, in the launch that codes both; bit for bit
-against the oracle."""
+"""Calls whose survivors are not all staged: buckets taken from the dense accumulator beside those that come from staged
+entries, bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -41,8 +40,8 @@ def _values(kind, n, rng):
 @pytest.mark.parametrize("kind", ["block", "clusters", "zeros", "ties", "one"])
 @pytest.mark.parametrize("bits,chunk", [(8, 2048), (4, 2048), (8, 256), (4, 8), (16, 64), (32, 1024)])
 def test_units_of_survivors_not_staged(kind, bits, chunk):
-    """Units that fill a tile exactly, that fit the registers and that do not, a last one of one survivor, chunks from 8
-    to 2048; a bucket that starts beside a multiple of 4.  256 threads per chunk (many chunks) and 512."""
+    """Up to an eighth sent: tiles of survivors only, survivors in clusters and far apart, a last chunk of one survivor, chunks from
+    8 to 2048; a bucket that starts beside a multiple of 4.  256 threads per chunk (many chunks) and 512."""
     for seed, nb in ((1, 2048 * 128), (2, 300_007)):
         rng = np.random.default_rng([seed, bits, chunk])
         sizes = [ELSEWHERE + seed - 1, nb, ELSEWHERE]
