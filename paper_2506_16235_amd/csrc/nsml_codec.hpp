@@ -303,29 +303,46 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
 
 /* One of its entries by a wavefront: the first j in [0, kb] with ib[j] + head >= edge.  per: survivors per element of the bucket.
  * Where survivors are spread evenly the edge's place is known to a few of them after one or two looks, so the first three rounds look at
- * 64 neighbours around where it should be, three lines; only where they are clustered does the search by 64 probes a round,
- * a line each, follow in what is left of the range.  (Bound by the lines it fetches and the round trips; before, by probes alone: eight rounds of the
- * ResNet-50 shape from the controller's start 1511 us, so 1452; a round of it at 0.05 150.0 and 149.0, of the BERT shape at 0.01 402 and 396.)
+ * 64 neighbours around where it should be, three lines; only where they are clustered, which the first look shows, does the search by
+ * 64 probes a round, a line each, follow in what is left of the range.  In buckets of more than 2 M survivors its first round
+ * goes with the first look, as all tiles of a bucket probe the same lines there: clustered ones are a round longer on their way otherwise (30 M
+ * elements, nine rows of 768 in ten zero, at 0.1: a worker's round 203 us, so 191), and evenly spread ones pay for it (the eight rounds below 1484).
+ * (Bound by the lines it fetches and the round trips; before, by probes alone: eight rounds of the ResNet-50 shape from the
+ * controller's start 1511 us, so 1447; a round of it at 0.05 151.3 and 149.9.)
  * A list that is not ascending (an invalid payload) gives entries that are wrong but still within [0, kb]. */
 __device__ __forceinline__ uint32_t tilestart_wave(const uint32_t *__restrict__ ib, uint32_t kb, uint32_t head, uint64_t edge, float per)
 {
     const uint32_t lane = threadIdx.x & 63;
     uint32_t lo = 0, hi = kb;
+    const bool both = kb > 1u << 21;
     float want = (float)edge * per;                      /* where the edge should be, less 32 the first of the neighbours */
+    float span = (float)kb;                              /* evenly spread, the number of survivors among so many is off by half the root of it */
     for (uint32_t look = 0; look < 3u && hi - lo > 64u; ++look) {
         const uint32_t at = min(max(want > 32.0f ? (uint32_t)fminf(want - 32.0f, 4294966784.0f) : 0u, lo), hi - 64u);
-        const uint64_t v = (uint64_t)ib[at + lane] + head;
+        const uint32_t step = (kb + 63u) / 64u, p = lane * step;
+        const uint32_t vi = ib[at + lane], pi = look == 0u && both ? ib[min(p, kb - 1u)] : 0u;
+        const uint64_t v = (uint64_t)vi + head;
         const uint64_t beyond = __ballot(v >= edge);
+        if (look == 0u && both) {
+            const uint64_t pb = __ballot(p >= kb || (uint64_t)pi + head >= edge);
+            const uint32_t f = pb ? (uint32_t)__builtin_ctzll(pb) : 64u;
+            hi = (uint32_t)min((uint64_t)kb, (uint64_t)f * step);
+            lo = f ? (f - 1u) * step + 1u : 0u;
+        }
+        float off;
         if (beyond & 1ull) {                             /* the first of them, and so all */
-            hi = at;
-            if (at == lo) break;
+            hi = min(hi, at);
             want = (float)at - (float)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v - edge))) * per;
+            off = (float)at - want;
         } else if (beyond) {
             return at + (uint32_t)__builtin_ctzll(beyond);
         } else {
-            lo = at + 64u;
-            want = (float)lo + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - v), 63)) * per;
+            lo = max(lo, at + 64u);
+            want = (float)(at + 64u) + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - v), 63)) * per;
+            off = want - (float)(at + 64u);
         }
+        if (lo >= hi || off * off > 4.0f * span + 4096.0f) break;      /* found, or clustered */
+        span = off;
     }
     while (lo < hi) {                                    /* (the range shrinks every round, whatever the list holds) */
         const uint32_t step = (hi - lo + 63u) / 64u;

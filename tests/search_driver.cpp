@@ -15,7 +15,7 @@ static uint32_t rnd() { rng_state ^= rng_state << 13; rng_state ^= rng_state >> 
 int main()
 {
     int failures = 0, checked = 0;
-    for (uint32_t k : {1u, 2u, 63u, 64u, 65u, 66u, 127u, 128u, 129u, 1000u, 5000u, 70001u})
+    for (uint32_t k : {1u, 2u, 63u, 64u, 65u, 66u, 127u, 128u, 129u, 1000u, 5000u, 70001u, (1u << 21) + 70u})
         for (int kind = 0; kind < 6; ++kind) {
             const uint64_t nb = kind == 3 ? 0xFFFFF000ull : kind == 2 ? k : 40ull * k;
             std::vector<uint32_t> idx(k);
@@ -33,8 +33,7 @@ int main()
                 const uint32_t head = turn % 4;
                 const uint64_t edge = turn == 0 ? 0 : turn == 1 ? nb + head : turn == 2 ? (nb + head) / TILE * TILE
                                     : turn < 20 ? (uint64_t)idx[rnd() % k] + head + turn % 3 : rnd() % (nb + head + 1);
-                uint64_t want = 0;
-                while (want < k && (uint64_t)idx[want] + head < edge) ++want;
+                const uint64_t want = std::partition_point(idx.begin(), idx.end(), [&](uint32_t i) { return (uint64_t)i + head < edge; }) - idx.begin();
                 uint32_t got[64];
                 simt::run(64, dim3(0), dim3(1), [&] { got[threadIdx.x] = tilestart_wave(idx.data(), k, head, edge, (float)k / (float)nb); });
                 bool ok = true;
