@@ -680,7 +680,9 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             LAUNCH(c, KID_SELECT, st, k_select_count<false>, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights, c->d_wnband);
             LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                     (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1, c->force_rescan);
-            LAUNCH(c, KID_WMASK, st, k_wrest, (uint32_t)c->n_cu + (c->n_tiles + 15) / 16, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1, (uint32_t)c->n_cu, h.hw,
+            const bool apart = c->n_tiles > 131072u;       /* see k_wfix */
+            if (apart) LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
+            LAUNCH(c, KID_WMASK, st, k_wrest, (uint32_t)c->n_cu + (apart ? 0u : (c->n_tiles + 15) / 16), weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1, (uint32_t)c->n_cu, h.hw,
                    (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
         }
         t.pmask = c->d_pmask;

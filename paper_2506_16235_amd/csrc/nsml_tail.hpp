@@ -1917,6 +1917,9 @@ __global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Table
     __shared__ uint32_t h[NB1];
     whard_body(w, t, c, f0, f1, f2, pmask, err, h, blockIdx.x, gridDim.x);
 }
+/* The bitmap of the staged bands alone: many tiles are better off without the registers and the LDS of the dense passes (6.7 G weights: 605 us, by
+ * k_wrest 1029; beside it a launch costs 4 - 5). */
+__global__ __launch_bounds__(WG) void k_wfix(Tables t, Cand c, uint32_t *__restrict__ pmask) { wfix_body(t, c, pmask, blockIdx.x); }
 __global__ __launch_bounds__(WG) void k_wrest(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
                                               uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,
                                               uint32_t *__restrict__ err, uint32_t team, uint32_t *__restrict__ hist,
