@@ -628,9 +628,10 @@ __device__ __forceinline__ void pick_body(const Tables &t, uint32_t *__restrict_
     constexpr int NB = LEVEL == 0 ? NB0 : LEVEL == 1 ? NB1 : NB2;
     __shared__ uint32_t tmp[WG];
     const uint32_t tid = threadIdx.x;
+    if (t.k[b] == 0u) return;                  /* an empty bucket: other workgroups may be writing its words (plan_empty) */
     if (t.fast[b]) return;                     /* decided from its staged elements */
     const uint32_t want = t.need[b], sh = t.sh[b];
-    if (want == 0) return;                     /* empty bucket */
+    if (want == 0) return;
     if (LEVEL == 0 && sh != SH_NONE) return;
     DigitWalk<NB> w;
     w.load(hist + (uint64_t)b * NB, tmp);
@@ -657,7 +658,7 @@ __device__ __forceinline__ void scan_body(const Tables &t, uint32_t *__restrict_
 {
     __shared__ uint64_t tmp[WG / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (t.fast[b] != PATH_DENSE) return;
+    if (t.k[b] == 0u || t.fast[b] != PATH_DENSE) return;      /* (empty: see pick_body) */
     const uint32_t t0 = t.tile0[b], t1 = t.tile0[b + 1];
     uint64_t carry = 0;
     for (uint32_t base = t0; base < t1; base += WG * 4) {

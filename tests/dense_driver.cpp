@@ -1,7 +1,7 @@
 /*
  * The dense passes on the CPU (a team of one workgroup) and the coding behind them, from leading bits of the threshold that
  * are right, and from numbers of wanted keys that are not: those have to be noticed before anything is written for
- * the bucket, since the coding stores to where the index list says.
+ * the bucket, since the coding stores to where the index list says.  Then beside empty buckets.
  */
 #include "simt.hpp"
 
@@ -105,6 +105,41 @@ static void check(uint64_t lead, uint64_t nb, double ratio, uint32_t chunk, int 
     }
 }
 
+/* Whole values by the dense passes beside empty buckets, before and behind, whose words hold what another layout left there (a dense
+ * bucket's): other workgroups of the same launch write them, in no order with the team, so nothing may be taken from them. */
+static void check_empty(uint32_t stale_need, uint32_t stale_sh)
+{
+    constexpr uint32_t B = 4, GUARD = 64;
+    const uint64_t nb = 9001;
+    const std::vector<uint64_t> off = {0, 0, nb, nb, nb};
+    std::vector<float> r(nb + 8 + GUARD, 7.0f);
+    for (uint64_t i = 0; i < nb; ++i) r[i] = (rnd() & 1 ? 1.0f : -1.0f) * (1e-3f + (i % 5 ? 0.0f : 1e-9f * (float)(rnd() % 64)));
+    const std::vector<float> before = r;
+    const uint32_t nt = (uint32_t)((nb + TILE - 1) / TILE), kb = (uint32_t)survivors_dev(0.3, nb);
+    std::vector<uint32_t> tile0 = {0, 0, nt, nt, nt}, tile_b(nt, 1u), G(nt), E(nt), cnt(nt);
+    std::vector<uint4> desc(nt);
+    for (uint32_t i = 0; i < nt; ++i) desc[i] = make_uint4(i * (uint32_t)TILE, 0u, 1u, std::min<uint32_t>(TILE, (uint32_t)nb - i * TILE) << 16);
+    uint32_t k[B] = {0, kb, 0, 0}, T[B] = {5, 0, 5, 5}, need[B] = {stale_need, kb, stale_need, stale_need}, fast[B] = {}, sh[B] = {stale_sh, SH_NONE, stale_sh, stale_sh};
+    uint32_t margin[B] = {}, why[B] = {}, ovf[B] = {}, ftile0[B + 1] = {}, nhard[4] = {1, 0, 1, 1}, err = 0;
+    uint64_t P[B + 1] = {0, 0, kb, kb, kb}, V[B + 1] = {0, 0, 4 * kb, 4 * kb, 4 * kb}, S[B + 1] = {}, C[B + 1] = {};
+    Tables t = {};
+    t.off = off.data(); t.tile0 = tile0.data(); t.tile_b = tile_b.data(); t.desc = desc.data(); t.k = k; t.P = P; t.V = V; t.S = S; t.C = C; t.T = T; t.need = need;
+    t.fast = fast; t.sh = sh; t.margin = margin; t.why = why; t.ovf = ovf; t.ftile0 = ftile0; t.nhard = nhard; t.B = B; t.n_tiles = nt; t.chunk = 2048; t.chunkSh = 11;
+    Cand c = {nullptr, nullptr, cnt.data(), G.data(), E.data()};
+    std::vector<uint32_t> f0(B * NB0, 0), f1(B * NB1, 0), f2(B * NB2, 0), idx(kb + GUARD, 77u), pool(2 * TILE);
+    std::vector<float> val(kb + GUARD, 5.0f);
+    simt::run(WG, dim3(0), dim3(1), [&] { band_dense_buckets<32>(r.data(), t, c, f0.data(), f1.data(), f2.data(), idx.data(), val.data(), &err, pool.data(), 0, 1); });
+    std::vector<uint32_t> order(nb), want(kb + GUARD, 77u);
+    std::vector<float> values(kb + GUARD, 5.0f), rest = before;
+    for (uint32_t i = 0; i < nb; ++i) order[i] = i;
+    std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return keyof(before[x]) > keyof(before[y]); });
+    order.resize(kb);
+    std::sort(order.begin(), order.end());
+    for (uint32_t j = 0; j < kb; ++j) { want[j] = order[j]; values[j] = before[order[j]]; rest[order[j]] = 0.0f; }
+    const bool same = r == rest && idx == want && val == values;
+    if (err || !same) { ++failures; printf("empty buckets, left there: need %u sh %u: flag %u, outputs %s\n", stale_need, stale_sh, err, same ? "as they should be" : "differ"); }
+}
+
 int main()
 {
     setvbuf(stdout, nullptr, _IONBF, 0);
@@ -115,6 +150,8 @@ int main()
             check<true>(5002, nb, 0.5, 4096, wrong, false);
             check<false>(5003, nb, 0.6, 256, wrong, true);
         }
+    for (uint32_t need : {0u, 1u, 7u})
+        for (uint32_t sh : {(uint32_t)SH_NONE, (uint32_t)SH0, (uint32_t)SH1}) check_empty(need, sh);
     printf("failures %d\n", failures);
     return failures != 0;
 }
