@@ -673,7 +673,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
         /* buckets decided from their band: undecided keys, threshold key and tie count, the pruned
          * band elements' bits; buckets on the dense passes (no band, or one that missed): by the last launch's first workgroups */
         if (c->force_dense) {
-            LAUNCH(c, KID_WPLAN, st, k_wplan_dense, (B + WG - 1) / WG, tw);
+            LAUNCH(c, KID_WPLAN, st, k_wplan_dense, (B + WG - 1) / WG, tw, c->d_wprevT);
             LAUNCH(c, KID_WHARD, st, k_whard, (uint32_t)c->n_cu, weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1);
         } else {
             if (bins) LAUNCH(c, KID_BINS, st, k_bins, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, c->selSh, h.hw, weights);

@@ -181,11 +181,12 @@ __device__ __forceinline__ void plan_weights_store(const Tables &t, uint32_t b, 
 }
 __device__ __forceinline__ void plan_weights_empty(const Tables &t, uint32_t b) { t.T[b] = NONE; t.need[b] = 0; t.fast[b] = PATH_BAND; t.sh[b] = SH0; }
 
-/* The plan when every bucket is sent to the dense passes (force_dense). */
-__global__ __launch_bounds__(WG) void k_wplan_dense(Tables t)
+/* The plan when every bucket is sent to the dense passes (force_dense): no band, so the next call has nothing to go by. */
+__global__ __launch_bounds__(WG) void k_wplan_dense(Tables t, uint32_t *__restrict__ prevT)
 {
     const uint32_t b = blockIdx.x * WG + threadIdx.x;
     if (b >= t.B) return;
+    prevT[b] = NONE;
     if (t.k[b] == 0u) plan_weights_empty(t, b);
     else plan_weights_store(t, b, Plan{PATH_DENSE, 0u, t.k[b], SH_NONE, 0u});
 }

@@ -98,6 +98,23 @@ def test_weights_that_move_little_between_steps(path):
     _run([300_000, 2_000_003, 70_000], 0.01, 4, 256, steps=3, seed=78, drift=1e-2)
 
 
+def test_nothing_is_remembered_of_a_call_by_the_dense_passes(path):
+    """A call that was sent to the dense passes has no band, so the next one samples: it does not look for its threshold where the
+    call before both had it (here at weights a hundred times as large)."""
+    if path != "auto":
+        pytest.skip("switches the paths itself")
+    off = W.offsets_of([300_000, 70_000])
+    n = int(off[-1])
+    ctx = nsml.Context(n, 2, 256)
+    r = torch.zeros(n, device=DEV)
+    for step, (dense, sigma) in enumerate(((0, 5.0), (1, 0.05), (0, 0.05))):
+        ctx.set_option("force_dense", dense)
+        ctx.compress_pruned(_rand(n, 40 + step), r, _rand(n, 50, sigma=sigma), off, 0.01, 8)
+        torch.cuda.synchronize()
+        ctx.path_stats()
+        assert ctx.prune_stats() == ((0, 2) if dense else (2, 0)), step
+
+
 def test_clustered_survivors_with_pruning():
     """Runs of large gradients longer than a staging segment holds, under pruning: the segments
     that overflow are read from the dense accumulator, minus the pruned parameters."""
