@@ -182,6 +182,8 @@ int nsml_destroy(nsml_ctx *ctx);
  *                  threshold the previous call on this context found for the bucket (weights move
  *                  little between steps; a bucket whose band misses takes the dense passes, the
  *                  result is the same), 0: the band always comes from a sample of the weights
+ *   "wfix_apart"   pruning step: the bitmap of the staged bands by a launch of its own: 1, 0, -1 (default) =
+ *                  by gradient size
  *   "wband_miss"   diagnostic: 1 places the band of weight magnitudes that the pruning step stages
  *                  beside the threshold, so that every bucket takes the dense passes (the path of a
  *                  band that missed), 0: default

@@ -144,6 +144,7 @@ struct nsml_ctx {
     int n_cu;
     int hard_occ[2];       /* workgroups of k_hard that fit a compute unit at once (short / long chunks) */
     int whistory;          /* the weight band follows the threshold of the last call (1, default) or always comes from a sample (0) */
+    int wfix_apart;        /* the staged weight bands' bitmap by a launch of its own: 1, 0, -1 (default) = by gradient size */
     int wband_miss;        /* diagnostic: the weight band is placed beside the threshold, so every bucket takes the dense passes */
     int force_rescan;      /* diagnostic: k_select_finish in small windows; small buckets by the chain of kernels */
 
@@ -454,7 +455,7 @@ int nsml_create_ex(nsml_ctx **out, int device, uint64_t max_n, uint32_t max_buck
     c->zero_clean = false; c->zero_B = 0;
     c->n_cu = 256; c->decomp_variant = -1;
     c->unit_tiles = c->sel_waves = c->built_sel_waves = 0; c->nt_acc = c->nt_dense = -1;
-    c->force_dense = 0; c->force_rescan = 0; c->wband_miss = 0; c->whistory = 1;
+    c->force_dense = 0; c->force_rescan = 0; c->wband_miss = 0; c->whistory = 1; c->wfix_apart = -1;
 
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) {
@@ -680,7 +681,7 @@ static int compress_impl(nsml_ctx *c, const float *grad, float *residual, const 
             LAUNCH(c, KID_SELECT, st, k_select_count<false>, c->n_sel, tw, cd0, (const uint4 *)c->d_selw, (const uint32_t *)h.hw, h.cursor, c->d_part, c->d_lkey, c->d_flags + 1, weights, c->d_wnband);
             LAUNCHB(c, KID_FINISH, st, k_select_finish, B, SEL_THREADS, tw, cd0, (const uint32_t *)c->d_sel0, c->selSh, h.cursor,
                     (const uint2 *)c->d_part, (const uint32_t *)c->d_lkey, (uint32_t *)nullptr, c->d_flags + 1, c->force_rescan);
-            const bool apart = c->n_tiles > 131072u;       /* see k_wfix */
+            const bool apart = c->wfix_apart < 0 ? c->n_tiles > 65536u : c->wfix_apart != 0;       /* see k_wfix */
             if (apart) LAUNCH(c, KID_WMASK, st, k_wfix, (c->n_tiles + 15) / 16, tw, cd0, c->d_pmask);
             LAUNCH(c, KID_WMASK, st, k_wrest, (uint32_t)c->n_cu + (apart ? 0u : (c->n_tiles + 15) / 16), weights, tw, cd0, h.f0, h.f1, h.f2, c->d_pmask, c->d_flags + 1, (uint32_t)c->n_cu, h.hw,
                    (const uint32_t *)c->d_wnband, c->d_wprevT, c->d_wprevHw);
@@ -1209,6 +1210,9 @@ int nsml_set_option(nsml_ctx *c, const char *name, int value)
     } else if (is("whistory")) {
         if (value != 0 && value != 1) return NSML_EINVAL;
         c->whistory = value;
+    } else if (is("wfix_apart")) {
+        if (value < -1 || value > 1) return NSML_EINVAL;
+        c->wfix_apart = value;
     } else if (is("wband_miss")) {
         if (value != 0 && value != 1) return NSML_EINVAL;
         c->wband_miss = value;

@@ -1917,8 +1917,10 @@ __global__ __launch_bounds__(WG) void k_whard(const float *__restrict__ w, Table
     __shared__ uint32_t h[NB1];
     whard_body(w, t, c, f0, f1, f2, pmask, err, h, blockIdx.x, gridDim.x);
 }
-/* The bitmap of the staged bands alone: many tiles are better off without the registers and the LDS of the dense passes (6.7 G weights: 605 us, by
- * k_wrest 1029; beside it a launch costs 4 - 5). */
+/* The bitmap of the staged bands alone: many tiles are better off without the registers and the LDS of the dense passes.  Beside it k_wrest
+ * takes 4 - 5 us.  One launch / two, us together: 10 thousand tiles 4.4 / 8.5, 31 thousand 10.0 / 10.3, 47 thousand 13.8 / 14.6, 53 thousand in
+ * 199 buckets 22.3 / 21.1 (the call 495.4 / 495.5), 78 thousand 22.2 / 20.3, 117 thousand 32.0 / 25.7, 390 thousand 104 / 72, 3.3 M (6.7 G
+ * weights) 1029 / 643. */
 __global__ __launch_bounds__(WG) void k_wfix(Tables t, Cand c, uint32_t *__restrict__ pmask) { wfix_body(t, c, pmask, blockIdx.x); }
 __global__ __launch_bounds__(WG) void k_wrest(const float *__restrict__ w, Tables t, Cand c, uint32_t *__restrict__ f0,
                                               uint32_t *__restrict__ f1, uint32_t *__restrict__ f2, uint32_t *__restrict__ pmask,

@@ -154,3 +154,14 @@ def test_pruning_by_the_route_of_large_gradients(monkeypatch, seg_waves):
     test_clustered_survivors_with_pruning()
     _run([1, 70, 4095, 0, 300_003, 65_537, 900_001], 0.01, 8, 64, steps=3, seed=5)
     _run([300_003, 65_537], 0.3, 32, 64, steps=2, ties=True, seed=6)
+
+
+def test_bitmap_of_the_bands_by_a_launch_of_its_own(monkeypatch, path):
+    """The route of more than 65536 tiles, forced on small layouts: bands from a sample, from what the call before found, and bands that miss."""
+    monkeypatch.setitem(nsml.Context.default_options, "wfix_apart", 1)
+    _run([1, 64, 2048, 0, 4095, 4097, 3, 17889, 8192, 12289, 1, 50001, 7, 131072 + 5], 0.05, 8, 64, steps=3, seed=40)
+    test_equal_weights_at_the_threshold_decided_from_the_band(path)
+    test_weights_that_move_little_between_steps(path)
+    monkeypatch.setitem(nsml.Context.default_options, "nt", 7)
+    test_weights_that_move_little_between_steps(path)
+    test_clustered_survivors_with_pruning()
