@@ -301,51 +301,69 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
     if (g < n_tiles) tilestart_find(idx, t, g, ts);
 }
 
+constexpr uint32_t TOGETHER = 1u << 17;    /* survivors of a bucket up to which the first look goes with the first round */
 /* One of its entries by a wavefront: the first j in [0, kb] with ib[j] + head >= edge.  per: survivors per element of the bucket.
- * Where survivors are spread evenly the edge's place is known to a few of them after one or two looks, so the first three rounds look at
- * 64 neighbours around where it should be, three lines; only where they are clustered, which the first look shows, does the search by
- * 64 probes a round, a line each, follow in what is left of the range.  In buckets of more than 2 M survivors its first round
- * goes with the first look, as all tiles of a bucket probe the same lines there: clustered ones are a round longer on their way otherwise (30 M
- * elements, nine rows of 768 in ten zero, at 0.1: a worker's round 203 us, so 191), and evenly spread ones pay for it (the eight rounds below 1484).
- * (Bound by the lines it fetches and the round trips; before, by probes alone: eight rounds of the ResNet-50 shape from the
- * controller's start 1511 us, so 1447; a round of it at 0.05 151.3 and 149.9.)
+ * Bound by round trips and by the lines they fetch.  The first round's probes lie as far apart as the rounds after it can resolve, 64 probes
+ * each.  All tiles of the bucket probe the same lines there, and it shows how the survivors lie.
+ * Where they are spread evenly the edge's place is then known to a few of them after one or two looks at 64 neighbours, three lines each.
+ * Where they are clustered the rounds of probes, a line each, go on: no round is lost to them.
+ * In short lists the first look does not wait for the first round.  In long ones its lines would be too many where survivors are clustered (30 buckets of
+ * 1 M elements, the decoder alone, in turn / together: 0.1 sent, clipped at one sigma 28.7 / 29.0, normal 25.9 / 25.6; 0.4 sent, clipped 52.0 / 57.2,
+ * normal 39.4 / 38.3).
+ * The decoder alone, us, by probes alone / looks before any probe / this: ResNet-50's shape, normal values, at 0.1 24.5 / 20.4 / 20.5, at 0.7
+ * 56.9 / 45.0 / 45.9; values clipped at one sigma, of which the first equal ones are sent, at 0.1 24.7 / 26.6 / 23.0; nine rows of 768 in ten zero,
+ * at 0.4 28.0 / 35.6 / 28.0; 30 M such elements at 0.05 24.2 / 29.9 / 24.5.
  * A list that is not ascending (an invalid payload) gives entries that are wrong but still within [0, kb]. */
 __device__ __forceinline__ uint32_t tilestart_wave(const uint32_t *__restrict__ ib, uint32_t kb, uint32_t head, uint64_t edge, float per)
 {
     const uint32_t lane = threadIdx.x & 63;
-    uint32_t lo = 0, hi = kb;
-    const bool both = kb > 1u << 21;
+    if (kb == 0u) return 0u;
+    uint32_t lo = 0, hi = kb, step = 1;
+#pragma unroll 1
+    while (64ull * step < kb) step = 64u * step + 1u;    /* (r rounds resolve 64 times as much as r - 1 do, and one more) */
     float want = (float)edge * per;                      /* where the edge should be, less 32 the first of the neighbours */
-    float span = (float)kb;                              /* evenly spread, the number of survivors among so many is off by half the root of it */
-    for (uint32_t look = 0; look < 3u && hi - lo > 64u; ++look) {
-        const uint32_t at = min(max(want > 32.0f ? (uint32_t)fminf(want - 32.0f, 4294966784.0f) : 0u, lo), hi - 64u);
-        const uint32_t step = (kb + 63u) / 64u, p = lane * step;
-        const uint32_t vi = ib[at + lane], pi = look == 0u && both ? ib[min(p, kb - 1u)] : 0u;
-        const uint64_t v = (uint64_t)vi + head;
-        const uint64_t beyond = __ballot(v >= edge);
-        if (look == 0u && both) {
-            const uint64_t pb = __ballot(p >= kb || (uint64_t)pi + head >= edge);
-            const uint32_t f = pb ? (uint32_t)__builtin_ctzll(pb) : 64u;
-            hi = (uint32_t)min((uint64_t)kb, (uint64_t)f * step);
-            lo = f ? (f - 1u) * step + 1u : 0u;
+    auto place = [&]() { return min(max(want > 32.0f ? (uint32_t)fminf(want - 32.0f, 4294966784.0f) : 0u, lo), hi - 64u); };
+    const bool together = kb > 64u && kb <= TOGETHER;
+    uint32_t at = together ? place() : 0u, x = 0;
+    if (together) x = ib[at + lane];
+    const uint64_t p = (uint64_t)lane * step;
+    const uint64_t v = (uint64_t)ib[p < kb ? (uint32_t)p : kb - 1u] + head;
+    const uint64_t beyond = __ballot(p >= kb || v >= edge);
+    const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */
+    if (f == 0u) return 0u;
+    hi = (uint32_t)min((uint64_t)kb, (uint64_t)f * step);
+    lo = (f - 1u) * step + 1u;
+    /* evenly spread, the number of survivors among so many elements is off by half the root of it at most */
+    const float d = (float)v * per - (float)p;
+    bool even = !__any(p < kb && d * d > 4.0f * (float)kb + 4096.0f);
+    float span = (float)(together ? kb : step);
+    if (!together) want = (float)lo + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - v), (int)(f - 1u))) * per;
+#pragma unroll 1
+    for (uint32_t look = together ? 0u : 1u; look < 4u; ++look) {
+        if (look) {
+            if (!even || lo >= hi || hi - lo <= 64u) break;
+            at = place();
+            x = ib[at + lane];
         }
+        const uint64_t w = (uint64_t)x + head;
+        const uint64_t past = __ballot(w >= edge);
         float off;
-        if (beyond & 1ull) {                             /* the first of them, and so all */
+        if (past & 1ull) {                               /* the first of them, and so all */
             hi = min(hi, at);
-            want = (float)at - (float)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v - edge))) * per;
+            want = (float)at - (float)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(w - edge))) * per;
             off = (float)at - want;
-        } else if (beyond) {
-            return at + (uint32_t)__builtin_ctzll(beyond);
+        } else if (past) {
+            return at + (uint32_t)__builtin_ctzll(past);
         } else {
             lo = max(lo, at + 64u);
-            want = (float)(at + 64u) + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - v), 63)) * per;
+            want = (float)(at + 64u) + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - w), 63)) * per;
             off = want - (float)(at + 64u);
         }
-        if (lo >= hi || off * off > 4.0f * span + 4096.0f) break;      /* found, or clustered */
+        even = even && off * off <= 4.0f * span + 4096.0f;
         span = off;
     }
     while (lo < hi) {                                    /* (the range shrinks every round, whatever the list holds) */
-        const uint32_t step = (hi - lo + 63u) / 64u;
+        step = (hi - lo + 63u) / 64u;
         const uint64_t p = (uint64_t)lo + (uint64_t)lane * step;
         const uint64_t beyond = __ballot(p >= hi || (uint64_t)ib[p < hi ? p : lo] + head >= edge);
         const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */

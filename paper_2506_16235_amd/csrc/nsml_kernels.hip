@@ -828,9 +828,9 @@ static ScatterGrid scatter_grid(uint64_t K, uint64_t n, bool add)
 }
 /* Whether the decoder's workgroups look for their tile's survivors themselves (tilestart_wave), and no table is
  * made beforehand: its launch costs more than that as long as few tiles, or few survivors, are in the way of each other's
- * looks (a worker's round, us, with table / without, by probes alone: 60 Ki elements 29.7 / 26.5, ResNet-50 at 5 % 158.6 / 153.4, at 40 % 222 / 218;
- * 110 M in 250 buckets at 1 % 418 / 398; with the neighbours looked at first: BERT-shaped gradient at 10 %, its embedding's survivors in
- * rows, 631 / 645, 419 M at a half 2438 / 2440). */
+ * looks (a worker's round, us, with table / without: 60 Ki elements 22.6 / 18.4, ResNet-50 at 5 % 157 / 151, at 40 % 206 / 197; 110 M in
+ * 250 buckets at 1 % 428 / 407, but at 10 % 646 / 656, the BERT-shaped gradient's rows at 10 % 647 / 675; 419 M at 1 % 1445 / 1535, at a half
+ * 2453 / 2472). */
 static bool decomp_searches(uint64_t K, uint64_t n, uint32_t n_tiles) { return n_tiles <= 16384u || (n_tiles <= 65536u && K * 64u <= n); }
 static bool tilestart_by_search(uint64_t K, uint32_t n_tiles) { return K >= 32ull * n_tiles; }      /* many survivors per tile */
 template <typename MAP>
