@@ -45,3 +45,37 @@ def test_candidates_of_small_buckets(kind, bits, chunk):
         c.step(ratio, bits)
         if kind != "nan":
             c.step(ratio, bits)
+
+
+@pytest.mark.parametrize("bits,chunk", [(4, 64), (8, 2048), (16, 2048), (32, 2048)])
+def test_a_digit_too_full_for_the_list(bits, chunk):
+    """More keys share a digit than the list of candidates holds: the k-th key's digit, few and many keys in it, and one that only the sample
+    takes for it; keys of one magnitude."""
+    sizes = [32_000, 20_001, 32_764, 9_000, 4097]
+    off = W.offsets_of(sizes)
+    for kind in ("crowd", "off", "one", "two"):
+        rng = np.random.default_rng([len(kind), bits])
+        parts = []
+        for nb in sizes:
+            x = (rng.standard_normal(nb) * 1e-6).astype(np.float32)
+            if kind == "one":
+                x[:] = 0.25
+            elif kind == "two":
+                x = rng.choice(np.array([0.25, 0.5], np.float32), nb)
+            else:
+                above = rng.permutation(nb)[:int(0.12 * nb)]
+                if kind == "off":        # not among every fourth element, which are what is sampled
+                    above = np.flatnonzero(np.arange(nb) % 4)[:int(0.14 * nb)]
+                rest = np.setdiff1d(np.arange(nb), above)
+                if kind == "off":
+                    x[rest] = rng.uniform(1.0, 1.03, len(rest))
+                else:
+                    x[rng.permutation(rest)[:int(0.1125 * nb)]] = rng.uniform(1.0, 1.03, int(0.1125 * nb))
+                x[above] = 2.0 + np.abs(rng.standard_normal(len(above)))
+            parts.append((x * np.where(rng.random(nb) < 0.5, -1, 1)).astype(np.float32))
+        g = np.concatenate(parts)
+        for ratio in (0.125, 0.01, 0.06):
+            say(kind, bits, chunk, ratio)
+            c = Case(torch.from_numpy(g).to(DEV), off, chunk=chunk)
+            c.step(ratio, bits)
+            c.step(ratio, bits)
