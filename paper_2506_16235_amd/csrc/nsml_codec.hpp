@@ -301,73 +301,60 @@ __global__ __launch_bounds__(WG) void k_tilestart_search(const uint32_t *__restr
     if (g < n_tiles) tilestart_find(idx, t, g, ts);
 }
 
-constexpr uint32_t TOGETHER = 1u << 17;    /* survivors of a bucket up to which the first look goes with the first round */
 /* One of its entries by a wavefront: the first j in [0, kb] with ib[j] + head >= edge.  per: survivors per element of the bucket.
- * Bound by round trips and by the lines they fetch.  The first round's probes lie as far apart as the rounds after it can resolve, 64 probes
- * each.  All tiles of the bucket probe the same lines there, and it shows how the survivors lie.
+ * Bound by round trips, by the lines they fetch, and in short lists by its instructions (edge and list are the same for the wavefront: scalar).
+ * In lists of more than two rounds of 64 probes the first round probes where the rounds after it can resolve the distance.  All tiles of
+ * the bucket probe the same lines there, and it shows how the survivors lie.
  * Where they are spread evenly the edge's place is then known to a few of them after one or two looks at 64 neighbours, three lines each.
  * Where they are clustered the rounds of probes, a line each, go on: no round is lost to them.
- * In short lists the first look does not wait for the first round.  In long ones its lines would be too many where survivors are clustered (30 buckets of
- * 1 M elements, the decoder alone, in turn / together: 0.1 sent, clipped at one sigma 28.7 / 29.0, normal 25.9 / 25.6; 0.4 sent, clipped 52.0 / 57.2,
- * normal 39.4 / 38.3).
- * The decoder alone, us, by probes alone / looks before any probe / this: ResNet-50's shape, normal values, at 0.1 24.5 / 20.4 / 20.5, at 0.7
- * 56.9 / 45.0 / 45.9; values clipped at one sigma, of which the first equal ones are sent, at 0.1 24.7 / 26.6 / 23.0; nine rows of 768 in ten zero,
- * at 0.4 28.0 / 35.6 / 28.0; 30 M such elements at 0.05 24.2 / 29.9 / 24.5.
+ * (Up to 65536 survivors the probes lie 1024 apart, so that one look nearly always does.)
+ * Short lists look first: it may be the only round.
+ * The kernel in a worker's round, us, by probes alone / looks before any probe / this.  ResNet-50's shape at 0.2: normal values 29.7 / 24.9 / 26.2,
+ * nine rows of 768 in ten zero 24.4 / 29.3 / 23.9, clipped at one sigma (of the equal ones the first are sent) 29.2 / 31.5 / 28.8; 30 M in
+ * one bucket at 0.01 25.6 / 21.8 / 22.0; 110 M in 250 buckets at 0.01 88.4 / 87.4 / 82.9, but lists not in the caches 83.0 / 92.8 / 89.0 (the probes
+ * of one tile fetch its neighbours' lines); 60 Ki in 24 buckets, rows, at 0.05 4.3 / 4.9 / 4.6.
  * A list that is not ascending (an invalid payload) gives entries that are wrong but still within [0, kb]. */
 __device__ __forceinline__ uint32_t tilestart_wave(const uint32_t *__restrict__ ib, uint32_t kb, uint32_t head, uint64_t edge, float per)
 {
-    const uint32_t lane = threadIdx.x & 63;
-    if (kb == 0u) return 0u;
-    uint32_t lo = 0, hi = kb, step = 1;
+    if (edge <= head) return 0u;
+    const uint32_t lane = threadIdx.x & 63, e = (uint32_t)(edge - head);       /* (an element of the bucket, or their number) */
+    uint32_t lo = 0, hi = kb;
+    float want = (float)e * per, span = (float)kb;       /* where the edge should be; off by half the root of span at most, if survivors are spread evenly */
+    uint32_t looks = 2;
+    bool even = true;
+    if (kb > 4160u) {
+        const uint32_t step = kb <= 65536u ? 1024u : kb <= 266304u ? 4161u : kb <= 17043520u ? 266305u : 17043521u;
+        const uint32_t p = lane * step, v = ib[min(p, kb - 1u)];
+        const uint64_t beyond = __ballot(p >= kb || v >= e);
+        const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */
+        if (f == 0u) return 0u;
+        const float d = (float)v * per - (float)p;
+        even = !__any(p < kb && d * d > 4.0f * span + 4096.0f);
+        hi = f < 64u ? min(kb, f * step) : kb;
+        lo = (f - 1u) * step + 1u;
+        want = (float)lo + (float)(uint32_t)__builtin_amdgcn_readlane((int)(e - v), (int)(f - 1u)) * per;
+        span = (float)step;
+        looks = 3;
+    }
 #pragma unroll 1
-    while (64ull * step < kb) step = 64u * step + 1u;    /* (r rounds resolve 64 times as much as r - 1 do, and one more) */
-    float want = (float)edge * per;                      /* where the edge should be, less 32 the first of the neighbours */
-    auto place = [&]() { return min(max(want > 32.0f ? (uint32_t)fminf(want - 32.0f, 4294966784.0f) : 0u, lo), hi - 64u); };
-    const bool together = kb > 64u && kb <= TOGETHER;
-    uint32_t at = together ? place() : 0u, x = 0;
-    if (together) x = ib[at + lane];
-    const uint64_t p = (uint64_t)lane * step;
-    const uint64_t v = (uint64_t)ib[p < kb ? (uint32_t)p : kb - 1u] + head;
-    const uint64_t beyond = __ballot(p >= kb || v >= edge);
-    const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */
-    if (f == 0u) return 0u;
-    hi = (uint32_t)min((uint64_t)kb, (uint64_t)f * step);
-    lo = (f - 1u) * step + 1u;
-    /* evenly spread, the number of survivors among so many elements is off by half the root of it at most */
-    const float d = (float)v * per - (float)p;
-    bool even = !__any(p < kb && d * d > 4.0f * (float)kb + 4096.0f);
-    float span = (float)(together ? kb : step);
-    if (!together) want = (float)lo + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - v), (int)(f - 1u))) * per;
-#pragma unroll 1
-    for (uint32_t look = together ? 0u : 1u; look < 4u; ++look) {
-        if (look) {
-            if (!even || lo >= hi || hi - lo <= 64u) break;
-            at = place();
-            x = ib[at + lane];
-        }
-        const uint64_t w = (uint64_t)x + head;
-        const uint64_t past = __ballot(w >= edge);
-        float off;
-        if (past & 1ull) {                               /* the first of them, and so all */
-            hi = min(hi, at);
-            want = (float)at - (float)((uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(w - edge))) * per;
-            off = (float)at - want;
-        } else if (past) {
-            return at + (uint32_t)__builtin_ctzll(past);
-        } else {
-            lo = max(lo, at + 64u);
-            want = (float)(at + 64u) + (float)((uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(edge - w), 63)) * per;
-            off = want - (float)(at + 64u);
-        }
-        even = even && off * off <= 4.0f * span + 4096.0f;
-        span = off;
+    for (; even && looks && hi - lo > 64u; --looks) {
+        /* 64 neighbours, half of them before it */
+        const uint32_t at = min(max((uint32_t)fminf(fmaxf(want - 32.0f, 0.0f), 4294966784.0f), lo), hi - 64u), v = ib[at + lane];
+        const uint64_t beyond = __ballot(v >= e);
+        if (beyond && !(beyond & 1ull)) return at + (uint32_t)__builtin_ctzll(beyond);
+        const uint32_t to = beyond ? at : at + 64u;      /* the edge is not beyond it, or not before */
+        const int diff = __builtin_amdgcn_readlane((int)(e - v), beyond ? 0 : 63);
+        const float off = (beyond ? -(float)(0u - (uint32_t)diff) : (float)(uint32_t)diff) * per;
+        if (beyond) hi = to; else lo = to;
+        want = (float)to + off;
+        even = off * off <= 4.0f * span + 1024.0f;
+        span = fabsf(off);
     }
     while (lo < hi) {                                    /* (the range shrinks every round, whatever the list holds) */
-        step = (hi - lo + 63u) / 64u;
-        const uint64_t p = (uint64_t)lo + (uint64_t)lane * step;
-        const uint64_t beyond = __ballot(p >= hi || (uint64_t)ib[p < hi ? p : lo] + head >= edge);
-        const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;      /* the first probe at or beyond the edge */
-        hi = (uint32_t)min((uint64_t)hi, (uint64_t)lo + (uint64_t)f * step);
+        const uint32_t n = hi - lo, step = (n - 1u) / 64u + 1u, p = lane * step;
+        const uint64_t beyond = __ballot(p >= n || ib[lo + min(p, n - 1u)] >= e);
+        const uint32_t f = beyond ? (uint32_t)__builtin_ctzll(beyond) : 64u;
+        hi = lo + min(n, f * step);
         if (f) lo += (f - 1u) * step + 1u;
     }
     return lo;
@@ -454,7 +441,7 @@ __global__ __launch_bounds__(NTH, 8) void k_decomp(const uint32_t *__restrict__ 
         } else {
             /* no table: a wavefront each for the tile's first survivor and the one after its last */
             __shared__ uint32_t place[2];
-            const uint32_t w = tid >> 6, i = tile - t.tile0[b] + w, tiles_b = t.tile0[b + 1] - t.tile0[b];
+            const uint32_t w = __builtin_amdgcn_readfirstlane(tid >> 6), i = tile - t.tile0[b] + w, tiles_b = t.tile0[b + 1] - t.tile0[b];
             if (w < 2u) {
                 const uint32_t at = i >= tiles_b ? kb : tilestart_wave(ib, kb, (uint32_t)(s.lo & 3ull), (uint64_t)i * TILE, (float)kb / (float)nb);
                 if ((tid & 63u) == 0u) place[w] = at;
