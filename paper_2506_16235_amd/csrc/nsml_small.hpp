@@ -326,7 +326,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
     /* The candidates' way: a lower bound of the k-th key from every fourth element (the first of each lane's four, so that runs of large values
      * weigh what they do); the elements from there up go into LDS, a wavefront's side by side, and are counted in bins that are fine where the
      * k-th key must lie; the rest is theirs.  A bound that leaves too many or too few leads to the way below. */
-    bool few = false;
+    bool found = false;                                  /* the k-th key's digit, or all of it, without the digits of all elements */
     uint32_t zeros = 0, crowded = NONE;                  /* crowded: a digit with more keys than the list holds, which seems to be the k-th key's */
     if (some) {
         uint32_t low = 0, s = SH0;                       /* keys from low up, bins of 2^s keys */
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
                 small_candidates<BITS>(sc, first, n, kb, chunk, low, s, res[0], kb - res[1], res[2], t, b, cmax, code4, wg_, idx_out + Pb, vb, scales, r + lo, chunk_of, record);
                 return;
             }
-            few = low == 1u && n_all < kb;               /* fewer values than survivors: the first zeros survive as well */
+            found = low == 1u && n_all < kb;             /* fewer values than survivors: the first zeros survive as well */
             zeros = kb - n_all;
             wg_sync();                                   /* LDS is written again */
         }
@@ -466,7 +466,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
     /* The k-th largest key, a digit of 12, 12 and 7 bits at a time: the first over all elements, and the next as well as long as
      * more keys are undecided than the list holds; then those keys are listed and the remaining digits come from the list. */
     uint32_t T = 0, want = kb, psh = 31u, at = 0;        /* T: the bits from psh up */
-    if (few) { want = zeros; psh = 0u; }
+    if (found) { want = zeros; psh = 0u; }
     if (crowded != NONE) {
         /* The first digit without a histogram, in which equal digits wait for each other (60 thousand elements in 24 buckets, 1 % as 8-bit codes: of two
          * magnitudes and zero 49.9 us, so 37.9, with no sample taken 45.3; of one magnitude 24.2, 22.8, 22.6). */
@@ -486,10 +486,10 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
         if (tid == 0) listed = 0u;
         wg_sync();
         (void)scan_totals(tmp, all);
-        if ((all & 0xFFFFu) < kb && kb <= (all & 0xFFFFu) + (all >> 16)) { T = crowded; want = kb - (all & 0xFFFFu); at = all >> 16; psh = SH0; }
+        if ((all & 0xFFFFu) < kb && kb <= (all & 0xFFFFu) + (all >> 16)) { T = crowded; want = kb - (all & 0xFFFFu); at = all >> 16; psh = SH0; found = at <= SMALL_LIST; }
     }
 #pragma unroll 1
-    while (!few && (psh == 31u || (psh != 0u && at > SMALL_LIST))) {
+    while (!found) {
         const uint32_t dsh = psh == 31u ? (uint32_t)SH0 : psh == (uint32_t)SH0 ? (uint32_t)SH1 : 0u;
         const uint32_t nbin = dsh == 0u ? (uint32_t)NB2 : (uint32_t)NB0;
         for (uint32_t i = tid; i < nbin; i += SMALL_T) hist[i] = 0u;
@@ -523,6 +523,7 @@ __global__ __launch_bounds__(SMALL_T) void k_small(const float *__restrict__ g, 
         at = res[2];
         psh = dsh;
         wg_sync();
+        if (psh == 0u || at <= SMALL_LIST) break;
     }
 
     /* keys above T's bits per wavefront, those that share them into the list (its order does not matter; when T is complete they are counted) */
