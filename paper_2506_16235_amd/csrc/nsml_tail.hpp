@@ -1025,7 +1025,10 @@ __device__ __forceinline__ void dense_threshold(const float *__restrict__ r, con
  * 64-byte line before it writes a part of it (half the words of 268 M elements written 400 us, read and then written 402, read and
  * written whole 340; one in ten: 390 and 339).  A tile
  * per workgroup of NT threads.  pool: 2 * TILE words. */
-constexpr uint32_t BAND_ROW = 16;       /* survivors of 256 elements from which their lines are written whole */
+/* Survivors of 256 elements from which their lines are written whole.  Compress, us, 30 buckets of 1 M elements as 32-bit values, from 6 / 16 / 40 up:
+ * 33 of 256 on average 168.7 / 168.1 / 175.0, 15 in half of the rows 177.6 / 177.7 / 179.7, 8 in half of them 178.0 / 178.4 / 180.7.  Anything from 6 to
+ * 16 does. */
+constexpr uint32_t BAND_ROW = 16;
 template <int BITS, uint32_t NT, bool PAST>       /* PAST: whole lines go past the caches, see st_out */
 __device__ __forceinline__ void band_tile(float *__restrict__ r, const Tables &t, const Cand &c, uint32_t *__restrict__ idx_out, void *__restrict__ val,
                                           uint32_t *__restrict__ err, uint32_t tile, const uint4 &d, uint32_t *pool)
@@ -1372,10 +1375,11 @@ __global__ __launch_bounds__(ENC_T, 4) void k_encode(Tables t, Cand c, const uin
  * just read, which are still in the cache).  A chunk that reaches across the unit's ends (or a
  * bucket's tiles of another unit) is written uncoded to idx / v_out, and k_quant codes exactly
  * those afterwards (same test, see chunk_coded_by_stream).  (16- and 32-bit values: band_tile.) */
-/* What bounds it: half of 419 M elements sent as 8-bit codes take 860 - 960 us, from one machine to another; without the scattered residual
- * 680, without any store 690, so the steps' chain of barriers and the instructions between them (59 per element
- * before the counts came from comparison masks and the codes from a product, 37 now) come first.  Was 1010 with four
- * wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
+/* What bounds it: the steps, not memory.  Half of 419 M elements sent as 8-bit codes take 860 - 960 us, from one machine to another, for 4.35 GB.
+ * Without the scattered residual it is 708 of 948, without any store 690.  The wavefronts spend 21 % of their time issuing (37 instructions per
+ * element; 59 before the counts came from comparison masks and the codes from a product), 30 % ready and waiting to issue, and 50 % waiting
+ * for memory, LDS or each other, of which barriers are 26 (SQ_ACTIVE_INST_ANY, SQ_WAIT_INST_ANY, SQ_WAIT_ANY; barriers by the clock in a
+ * copy).  Was 1010 with four wavefronts and two survivors per lane; four consecutive survivors per lane (16-byte index stores at 4-byte
  * alignment, residual stores 8 elements apart) 975, full residual lines 1057, non-temporal index stores 1169; the elements
  * written back when they are read, so that the errors meet whole lines in the cache, 997 (they have left it by then). */
 constexpr uint32_t DENC_SMALL_CHUNK = 256;         /* up to here a wavefront codes a chunk */

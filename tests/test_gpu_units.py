@@ -1,5 +1,5 @@
-"""Calls whose survivors are not all staged: buckets taken from the dense accumulator beside those that come from staged
-entries, bit for bit against the oracle."""
+"""Calls whose survivors are not all staged: buckets taken from the dense accumulator (by k_hard and k_quant, or as whole values tile by
+tile) beside those that come from staged entries, bit for bit against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -21,7 +21,7 @@ def _values(kind, n, rng):
     x = (rng.standard_normal(n) * 1e-5).astype(np.float32)
     if kind == "block":          # as many large values as survive, in one place: tiles of survivors only
         x[n // 3:n // 3 + n // 8] = (rng.standard_normal(n // 8) + 3.0).astype(np.float32)
-    elif kind == "clusters":     # runs of large values: some units within a few tiles, others over many
+    elif kind == "clusters":     # runs of large values: tiles of survivors only, others with none
         for at in range(0, n - 900, 9973):
             m = int(rng.integers(200, 900))
             x[at:at + m] = rng.standard_normal(m)
@@ -41,7 +41,7 @@ def _values(kind, n, rng):
 @pytest.mark.parametrize("bits,chunk", [(8, 2048), (4, 2048), (8, 256), (4, 8), (16, 64), (32, 1024)])
 def test_units_of_survivors_not_staged(kind, bits, chunk):
     """Up to an eighth sent: tiles of survivors only, survivors in clusters and far apart, a last chunk of one survivor, chunks from
-    8 to 2048; a bucket that starts beside a multiple of 4.  256 threads per chunk (many chunks) and 512."""
+    8 to 2048; a bucket that starts beside a multiple of 4."""
     for seed, nb in ((1, 2048 * 128), (2, 300_007)):
         rng = np.random.default_rng([seed, bits, chunk])
         sizes = [ELSEWHERE + seed - 1, nb, ELSEWHERE]
